@@ -69,21 +69,26 @@ void mod_up(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, uint
     launch_bconv_ntt_cols(c, lv.modup, lv.ell + lv.n_new, coeff, coeff_ps, lifted, lifted_ps, bc, s, ops);
 }
 
-// Words of workspace the gathers' sources of a chunk take: the finished raised digits as 32-bit words (words32), or as
-// 32-bit low words plus high bytes, own limbs included (64-bit operands).
-static uint64_t gather_words(const KsWorkspace& w, bool words32) { return (w.lifted + 1) / 2 + (words32 ? 0 : (w.lifted + 7) / 8); }
+// Words of workspace the bundle of a chunk of bc ciphertexts takes: low words, then (64-bit operands) the bits above;
+// with_c0: the addend's limbs as well.
+static uint64_t gather_lo_words(const ks_ctx* c, const Level& lv, uint32_t bc, bool with_c0) {
+    return ((uint64_t)lv.ndig * lv.E + (with_c0 ? lv.ell : 0)) * c->N * gather_group(bc) / 2;
+}
+static uint64_t gather_words(const ks_ctx* c, const Level& lv, uint32_t bc, bool with_c0, bool words32) {
+    const uint64_t lo = gather_lo_words(c, lv, bc, with_c0);
+    return lo + (words32 ? 0 : lo / 4 * gather_hi_bytes(gather_group(bc)) / gather_group(bc));
+}
 
-// mod_up finished for the rotation gathers: `region` (gather_words() words) ends as the bundle the gathers read, the
-// raised digits as canonical evaluation-domain residues and d's own limbs in their digits' slots, 32-bit words (words32)
-// or packed.  `lifted` is only scratch here.
-static GatherSources mod_up_for_gather(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, uint64_t* coeff,
-                                       uint64_t* lifted, uint64_t* region, uint32_t bc, hipStream_t s, bool words32) {
-    mod_up(c, lv, d, d_ps, coeff, lifted, bc, s, words32);
-    const uint64_t lifted_words = (uint64_t)bc * lv.ndig * lv.E * c->N;
-    const PackedDigits bundle{reinterpret_cast<uint32_t*>(region),
-                              words32 ? nullptr : reinterpret_cast<uint8_t*>(region + (lifted_words + 1) / 2)};
-    launch_gather_bundle_rows(c, lv, lifted, d, d_ps, words32, bundle, bc, s);
-    return GatherSources{bundle.lo, bundle.hi};
+// mod_up finished for the rotation gathers: `region` (gather_words() words) ends as the bundle they read.  `lifted` is only
+// scratch here.  raised == false: only the own limbs (and c0) are filled in, for a caller whose rotations are all identities.
+static GatherBundle mod_up_for_gather(const ks_ctx* c, const Level& lv, const void* d, const void* c0, uint64_t d_ps, uint64_t* coeff,
+                                      uint64_t* lifted, uint64_t* region, uint32_t bc, hipStream_t s, bool words32, bool raised = true) {
+    if (raised) mod_up(c, lv, d, d_ps, coeff, lifted, bc, s, words32);
+    const GatherBundle bundle{reinterpret_cast<uint32_t*>(region),
+                              words32 ? nullptr : reinterpret_cast<uint8_t*>(region + gather_lo_words(c, lv, bc, c0 != nullptr)),
+                              gather_group(bc)};
+    launch_gather_bundle_rows(c, lv, lifted, d, c0, d_ps, bundle, bc, raised, s);
+    return bundle;
 }
 
 // algorithmic fp64 work per coefficient of the ModDown conversion + column half (see mod_up)
@@ -121,10 +126,10 @@ extern "C" size_t ks_workspace_bytes(const ks_ctx* c, int op, uint32_t ell, uint
         case KS_OP_ROTATE_HOISTED:
         case KS_OP_ROTATE_HOISTED_U32:
             if (n_rot == 0) return 0;
-            // accumulators and converted limbs for a whole group of rotations
+            // the gathers' sources (rotate-multiply-accumulate keeps c0 among them)
+            words += gather_words(c, lv, bc, true, op == KS_OP_ROTATE_HOISTED_U32);
+            // accumulators and converted limbs for a whole group of rotations; the ciphertext limbs of a group's accumulators, packed
             words += (uint64_t)(std::min(n_rot, kRotGroup) - 1) * bc * (2 * lv.E + 2 * ell) * N;
-            // the gathers' sources; the ciphertext limbs of a group's accumulators, packed
-            words += gather_words(ks_ws_words(c, lv, bc), op == KS_OP_ROTATE_HOISTED_U32);
             words += (uint64_t)(std::min(n_rot, kRotGroup) - 1) * ks_ws_words(c, lv, bc).accq;
             break;
         case KS_OP_BSGS:
@@ -132,7 +137,7 @@ extern "C" size_t ks_workspace_bytes(const ks_ctx* c, int op, uint32_t ell, uint
             // accumulators of the outer level, inner result [bc][2][ell], the gathers' sources of both levels (the
             // inner results are 64-bit words either way)
             const KsWorkspace w = ks_ws_words(c, lv, bc);
-            words += w.acc + (uint64_t)bc * 2 * ell * N + gather_words(w, op == KS_OP_BSGS_U32) + gather_words(w, false);
+            words += w.acc + (uint64_t)bc * 2 * ell * N + gather_words(c, lv, bc, true, op == KS_OP_BSGS_U32) + gather_words(c, lv, bc, true, false);
             break;
         }
         case KS_OP_HMULT_RELIN_RESCALE:
@@ -358,17 +363,16 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
         const KsWorkspace w = ks_ws_words(c, lv, bc);
-        // The gathers read c1 and its finished raised digits in a compact form (32-bit words, or 32-bit low words plus
-        // high bytes for 64-bit operands: their traffic bounds the gather kernels); the last kernel's addend c0 is gathered
+        // The gathers read c1 and its finished raised digits from a compact bundle; the last kernel's addend c0 is gathered
         // from the ciphertext in its own word size.
         uint64_t* region = static_cast<uint64_t*>(ws);
-        uint64_t* coeff = region + gather_words(w, words32);
+        uint64_t* coeff = region + gather_words(c, lv, bc, false, words32);
         const char* c0 = static_cast<const char*>(ct) + (uint64_t)b0 * ct_bs * word;
         const void* c1 = c0 + (uint64_t)ell * N * word;
         uint64_t* lifted = coeff + w.coeff;
         uint64_t* acc = lifted + w.lifted;
         // finished once, shared by every rotation
-        const GatherSources digits = mod_up_for_gather(c, lv, c1, ct_bs, coeff, lifted, region, bc, s, words32);
+        const GatherBundle digits = mod_up_for_gather(c, lv, c1, nullptr, ct_bs, coeff, lifted, region, bc, s, words32);
         // Rotations go in groups: one gather launch forms the accumulators of the whole group (the raised digits then come
         // from memory once per group), the inverse transform and the conversion run over the group as one batch, and only
         // the last kernel, which adds sigma_g(c0) through a rotation's own permutation, runs per rotation.
@@ -429,7 +433,7 @@ static int check_mac_rotations(const ks_ctx* c, const uint32_t* galois, const vo
 }
 
 // u (+)= sum_r pt_r * rot_{g_r}(ct) for all n rotations, in launches of kMacRotations
-static void rotate_mac_all(const ks_ctx* c, const Level& lv, const void* ct, uint64_t ct_bs, const GatherSources& src,
+static void rotate_mac_all(const ks_ctx* c, const Level& lv, const GatherBundle& src,
                            const uint32_t* galois, const void* const* keys, const void* const* pts, uint32_t n, uint64_t* u,
                            uint32_t bc, bool accumulate, hipStream_t s, bool key_words32 = false) {
     for (uint32_t r0 = 0; r0 < n; r0 += kMacRotations) {
@@ -440,7 +444,7 @@ static void rotate_mac_all(const ks_ctx* c, const Level& lv, const void* ct, uin
             rot.key[r] = keys[r0 + r];
             rot.pt[r] = pts ? pts[r0 + r] : nullptr;
         }
-        launch_rotate_mac(c, lv, ct, ct_bs, src, rot, u, bc, accumulate || r0 != 0, s, key_words32);
+        launch_rotate_mac(c, lv, src, rot, u, bc, accumulate || r0 != 0, s, key_words32);
     }
 }
 
@@ -460,16 +464,16 @@ static int rotate_mac_impl(const ks_ctx* c, const void* ct, uint32_t ell, const 
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
         const KsWorkspace w = ks_ws_words(c, lv, bc);
-        // the gathers read c1 and its finished raised digits in a compact form (see rotate_hoisted_impl)
+        // the gathers read c0, c1 and its finished raised digits from a compact bundle
         const char* c0 = static_cast<const char*>(ct) + (uint64_t)b0 * ct_bs * word;
         uint64_t* region = static_cast<uint64_t*>(ws);
-        uint64_t* coeff = region + gather_words(w, words32);
+        uint64_t* coeff = region + gather_words(c, lv, bc, true, words32);
         uint64_t* lifted = coeff + w.coeff;
         uint64_t* acc = lifted + w.lifted;
         uint64_t* conv = acc + w.acc;
         // finished once, shared by every rotation
-        const GatherSources digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, ct_bs, coeff, lifted, region, bc, s, words32);
-        rotate_mac_all(c, lv, c0, ct_bs, digits, galois, rot_keys, pts, n_rot, acc, bc, false, s, words32);
+        const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, s, words32);
+        rotate_mac_all(c, lv, digits, galois, rot_keys, pts, n_rot, acc, bc, false, s, words32);
         mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, s, words32);
     }
     return finish(words32 ? "ks_rotate_mac_hoisted_u32" : "ks_rotate_mac_hoisted");
@@ -507,26 +511,24 @@ static int bsgs_impl(const ks_ctx* c, const void* ct, uint32_t ell, const uint32
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
         const KsWorkspace w = ks_ws_words(c, lv, bc);
-        // The gathers of the inner level read the input ciphertext and its finished raised digits in a compact form (see
-        // rotate_hoisted_impl); the inner results are 64-bit words either way, so the outer level reads the packed form.
+        // The gathers of the inner level read the input ciphertext and its finished raised digits from a compact bundle; the
+        // inner results are 64-bit words either way, so the outer level's bundle is the packed one.
         const char* c0 = static_cast<const char*>(ct) + (uint64_t)b0 * ct_bs * word;
         uint64_t* region = static_cast<uint64_t*>(ws);   // sources of the inner level, shared by every baby step of every giant step
-        uint64_t* region_v = region + gather_words(w, words32);   // sources of the outer level: the current inner result
-        uint64_t* coeff = region_v + gather_words(w, false);
+        uint64_t* region_v = region + gather_words(c, lv, bc, true, words32);   // sources of the outer level: the current inner result
+        uint64_t* coeff = region_v + gather_words(c, lv, bc, true, false);
         uint64_t* lifted = coeff + w.coeff;          // scratch of a ModUp
         uint64_t* acc = lifted + w.lifted;           // inner sum of the current giant step
         uint64_t* conv = acc + w.acc;
         uint64_t* acc_outer = conv + w.conv;         // outer sum over the giant steps
         uint64_t* v = acc_outer + w.acc;             // [bc][2][ell][N] inner result of the current giant step (64-bit words)
-        const GatherSources digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, ct_bs, coeff, lifted, region, bc, s, words32);
-        GatherSources digits_v{};
+        const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, s, words32);
         for (uint32_t g = 0; g < n2; ++g) {
-            rotate_mac_all(c, lv, c0, ct_bs, digits, baby_galois, bkeys, ptv + (size_t)g * n1, n1, acc, bc, false, s, words32);
+            rotate_mac_all(c, lv, digits, baby_galois, bkeys, ptv + (size_t)g * n1, n1, acc, bc, false, s, words32);
             mod_down(c, lv, acc, conv, v, ct_bs, nullptr, 0, 0, 1, bc, false, s);
-            if (giant_galois[g] != 1) digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, ct_bs, coeff, lifted, region_v, bc, s, false);
-            // Galois element 1 gathers nothing; the packed form still says that v holds 64-bit words
-            else digits_v = GatherSources{reinterpret_cast<const uint32_t*>(region_v), reinterpret_cast<const uint8_t*>(region_v)};
-            rotate_mac_all(c, lv, v, ct_bs, digits_v, giant_galois + g, gkeys + g, nullptr, 1, acc_outer, bc, g != 0, s, words32);
+            const GatherBundle digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, v, ct_bs, coeff, lifted, region_v, bc, s, false,
+                                                            giant_galois[g] != 1);
+            rotate_mac_all(c, lv, digits_v, giant_galois + g, gkeys + g, nullptr, 1, acc_outer, bc, g != 0, s, words32);
         }
         mod_down(c, lv, acc_outer, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, s,
                  words32);

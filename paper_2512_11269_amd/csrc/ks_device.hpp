@@ -67,6 +67,26 @@ KS_HD double reduce_lazy(double x, Mod m) {
     return __builtin_fma(-q, m.p, x);
 }
 
+// Exact multiply-accumulate of residues: (hi - kMacBias) + lo is the running sum of products as an integer.  hi lives in
+// [2^80, 2^81), where doubles are 2^28 apart, so fma(x, k, hi) rounds x k to a multiple of 2^28; the part it dropped,
+// x k - (hi_new - hi), is an integer of magnitude <= 2^27 that the second FMA recovers exactly and lo collects.  Four
+// instructions a product and one reduction per sum, where a Barrett product and an addition take seven.
+// Requires |x|, |k| <= 2^36 and sums below 2^79, i.e. at most 128 products (256 if |k| <= 0.51 * 2^36, a lazy residue).
+constexpr double kMacBias = 0x1.8p80;
+KS_HD void mac_exact(double x, double k, double& hi, double& lo) {
+    const double t = __builtin_fma(x, k, hi);
+    const double d = hi - t;
+    lo += __builtin_fma(x, k, d);
+    hi = t;
+}
+// The sum of a mac_exact accumulation as a lazy residue (|r| <= 0.51 p).  For products of residues of p the quotient
+// estimate of the high part stays below 256 p < 2^44, so it is off by far less than one and the FMA is exact.
+KS_HD double mac_reduce(double hi, double lo, Mod m) {
+    const double s = hi - kMacBias;
+    const double q = __builtin_rint(s * m.pinv);
+    return reduce_lazy(__builtin_fma(-q, m.p, s) + lo, m);
+}
+
 // Split an integer-valued 0 <= y < 2^36 into y = y2 + y1 + y0 with y2 a multiple of 2^24 (0 <= y2 <= 2^36), y1 a
 // multiple of 2^12 (|y1| <= 2^23) and |y0| <= 2^11, by rounding to nearest at the two granularities (adding and
 // subtracting 1.5 * 2^(52 + g) rounds to a multiple of 2^g).  Six additions, no products.

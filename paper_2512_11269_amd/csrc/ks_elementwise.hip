@@ -6,106 +6,170 @@
 
 namespace ks {
 
-constexpr int kBatchGroup = 8;  // batch items sharing one read of the key slots
-
-// What a gather reads for one (ciphertext, digit) at this limb position: a slot of the bundle [b][ndig][E][N] that holds
-// the finished raised digits and, in the slots of a digit's own positions, the limbs of the polynomial itself.  PACKED:
-// bits 0..31 of the residue from a 32-bit word array and the bits above from a byte array (5 bytes a residue); otherwise
-// one 32-bit word.  These kernels are bound by the gather traffic (every rotation re-reads all raised digits of the
-// chunk), so the bytes per residue are what sets their speed.
-// A thread keeps one source per (ciphertext of its group, digit).  As pointers they would be one or two 64-bit scalars
-// each, up to 48 pairs for three digits: more than the scalar register file holds beside everything else, and the spills
-// made rotate_mac 201 vector registers wide.  So there is ONE pair of base pointers (the bundle slice of the thread's
-// ciphertext group) and a 32-bit element offset per source; a load's address is base + 32-bit offset.
-struct SrcBases {
-    const char* lo;
-    const uint8_t* hi;
+// One slot of a bundle slab as a gather loads it: the low words of the group's ciphertexts and the word of their bits above.
+template <int G>
+struct SlotRaw {
+    uint32_t lo[G];
+    uint32_t hi, from;
 };
-template <bool PACKED>
-struct SrcRaw {
-    uint32_t lo, hi;
+// Loads of the gather kernels go through buffer descriptors: a uniform byte offset in a scalar register plus one 32-bit
+// byte offset per lane.  As 64-bit addresses per stream they pushed the sums out of the register file.
+template <typename T, int CPOL = 0>
+__device__ __forceinline__ T buffer_load(BufferRsrc rsrc, uint32_t lane_bytes, uint32_t uniform_bytes) {
+    if constexpr (sizeof(T) == 16) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)lane_bytes, (int)uniform_bytes, CPOL));
+    else if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)lane_bytes, (int)uniform_bytes, CPOL));
+    else if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)lane_bytes, (int)uniform_bytes, CPOL));
+    else if constexpr (sizeof(T) == 2) return (T)__builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)lane_bytes, (int)uniform_bytes, CPOL);
+    else return (T)__builtin_amdgcn_raw_buffer_load_b8(rsrc, (int)lane_bytes, (int)uniform_bytes, CPOL);
+}
+// Descriptor of a tensor whose address is uniform, kept in scalar registers.
+__device__ __forceinline__ BufferRsrc uniform_rsrc(const void* p, uint64_t bytes) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32));
+    const uint64_t u = (uint64_t)hi << 32 | lo;
+    return make_buffer_rsrc(reinterpret_cast<const void*>(u), bytes);
+}
+// The bundle (below 4 GB: at most 192 + 192 slabs of 2^16 slots of 32 bytes).
+struct BundleRsrc {
+    BufferRsrc lo, hi;
 };
-// e: element offset from the group's bases; below 2^30 (8 ciphertexts x 8 digits x 255 limbs x 2^16)
-template <bool PACKED>
-__device__ __forceinline__ SrcRaw<PACKED> src_load(const SrcBases& g, uint32_t e, uint32_t sn) {
-    const uint32_t i = e + sn;
-    SrcRaw<PACKED> r;
-    r.lo = *reinterpret_cast<const uint32_t*>(g.lo + (i << 2));
-    r.hi = PACKED ? g.hi[i] : 0u;
+template <int G>
+__device__ __forceinline__ BundleRsrc bundle_rsrc(const GatherBundle& src, uint64_t slots) {
+    return BundleRsrc{uniform_rsrc(src.lo, slots * (4 * G)), uniform_rsrc(src.hi, slots * (G > 1 ? G / 2 : 1))};
+}
+// The slots sigma_g sends to a wavefront's 64 consecutive slots are one aligned block of 64, permuted.  The block is read
+// in its own order and the lanes exchange what they hold on use (slot_take; 5 % on both kernels over permuted loads).  slab: uniform; slot: the lane's source slot.
+template <int G, bool PACKED>
+__device__ __forceinline__ SlotRaw<G> slot_load(const BundleRsrc& src, uint32_t slab, uint32_t N, uint32_t slot) {
+    using HW = std::conditional_t<G == 8, uint32_t, std::conditional_t<G == 4, uint16_t, uint8_t>>;
+    const uint32_t block = slab * N + (__builtin_amdgcn_readfirstlane(slot) & ~63u), lane = threadIdx.x & 63u;
+    SlotRaw<G> r;
+    r.from = (slot & 63u) * 4;
+    if constexpr (G >= 4) {
+#pragma unroll
+        for (int q = 0; q < G / 4; ++q) {
+            const uint4 t = buffer_load<uint4>(src.lo, lane * 16, block * (4 * G) + 1024 * q);
+            r.lo[4 * q] = t.x; r.lo[4 * q + 1] = t.y; r.lo[4 * q + 2] = t.z; r.lo[4 * q + 3] = t.w;
+        }
+    } else if constexpr (G == 2) {
+        const uint2 t = buffer_load<uint2>(src.lo, lane * 8, block * 8);
+        r.lo[0] = t.x; r.lo[1] = t.y;
+    } else {
+        r.lo[0] = buffer_load<uint32_t>(src.lo, lane * 4, block * 4);
+    }
+    r.hi = PACKED ? buffer_load<HW>(src.hi, lane * (uint32_t)sizeof(HW), block * (uint32_t)sizeof(HW)) : 0u;
     return r;
 }
-template <bool PACKED>
-__device__ __forceinline__ double src_f64(const SrcRaw<PACKED>& r) {
-    return PACKED ? u64_to_f64((uint64_t)r.hi << 32 | r.lo) : (double)r.lo;
+__device__ __forceinline__ uint32_t from_lane(uint32_t v, uint32_t lane_bytes) {
+    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)lane_bytes, (int)v);
 }
-// The bundle slice of the ciphertext group that starts at batch item b_lo.
-template <bool PACKED>
-__device__ __forceinline__ SrcBases src_bases(const GatherSources& g, uint32_t ndig, uint32_t E, uint32_t N, uint32_t b_lo) {
-    const uint64_t e = (uint64_t)b_lo * ndig * E * N;
-    return SrcBases{reinterpret_cast<const char*>(g.lo + e), PACKED ? g.hi + e : nullptr};
+// the slot of this lane out of what the wavefront loaded
+template <int G, bool PACKED>
+__device__ __forceinline__ SlotRaw<G> slot_take(const SlotRaw<G>& l) {
+    SlotRaw<G> r;
+    r.from = l.from;
+#pragma unroll
+    for (int g = 0; g < G; ++g) r.lo[g] = from_lane(l.lo[g], l.from);
+    r.hi = PACKED ? from_lane(l.hi, l.from) : 0u;
+    return r;
 }
-// Offset of the sources of (ciphertext b of the group starting at b_lo, digit j) at limb position pos.
-__device__ __forceinline__ uint32_t src_offset(uint32_t ndig, uint32_t E, uint32_t N, uint32_t b_lo, uint32_t b, uint32_t j,
-                                               uint32_t pos) {
-    return (((b - b_lo) * ndig + j) * E + pos) * N;
+template <int G, bool PACKED>
+__device__ __forceinline__ double slot_f64(const SlotRaw<G>& r, int g) {
+    return PACKED ? u64_to_f64((uint64_t)((r.hi >> (4 * g)) & 15u) << 32 | r.lo[g]) : (double)r.lo[g];
+}
+
+// Workgroup -> (limb position, 256 slots) for the gather kernels.  Multiplication by a Galois element permutes the slots
+// inside each half of a limb (g = 1 mod 4, every power of 5) or swaps the halves, so the sources of all rotations of a
+// (position, half) are the bundle's slots of that position and half: 1.2 MB per digit for eight ciphertexts at N = 2^16,
+// where the whole limb position of a chunk is 7 MB.  Consecutive workgroup ids go to the eight XCDs in turn, each with a
+// 4 MB L2 of its own, so unit u = (position, part) goes to the workgroups of XCD u % 8, which walk one unit after the other:
+// every rotation but the first finds its sources in that L2.  parts_log: parts per position, 2 unless that would leave
+// XCDs idle in the last round of units.
+struct GatherTile {
+    uint32_t pos, n;
+    bool valid;
+};
+__device__ __forceinline__ GatherTile gather_tile(uint32_t E, uint32_t logN, uint32_t parts_log) {
+    const uint32_t per_unit = 1u << (logN - 8 - parts_log), local = blockIdx.x >> 3;
+    const uint32_t unit = (local / per_unit) * 8 + (blockIdx.x & 7);
+    GatherTile t;
+    t.valid = unit < (E << parts_log);
+    t.pos = unit >> parts_log;
+    t.n = (((unit & ((1u << parts_log) - 1)) * per_unit + local % per_unit) << 8) + threadIdx.x;
+    return t;
+}
+static uint32_t gather_parts_log(const ks_ctx* c, uint32_t E) {
+    uint32_t pl = 1;
+    while (pl < 4 && ((E << pl) % 8) * 16 > (E << pl)) ++pl;  // a last round of units that is not full costs at most 1/16
+    return pl;
+}
+static uint32_t gather_grid(const ks_ctx* c, uint32_t E, uint32_t parts_log) {
+    return (((E << parts_log) + 7) / 8) * 8 * ((c->N / 256) >> parts_log);
 }
 
 // Inner products through the sigma_g gather for a group of hoisted rotations: acc[r][b][c][pos] = sum_j sigma_{g_r}(src_j)[pos]
-// key_r[j][c][pos].  One thread owns one slot of one limb position for a group of ciphertexts and walks the rotations of
-// the launch, so the raised digits it gathers from are read from memory once per launch and from cache afterwards.
-// Branch-free like rotate_mac_kernel below: the digit count is a template parameter and a short last group recomputes
-// its last ciphertext, so every load of a rotation is issued before the first product.
-// WK: word type of the keys; PACKED: format of the gathered sources (see SrcPtr).
+// key_r[j][c][pos].  One thread owns one slot of one limb position for all ciphertexts of the group and walks the
+// rotations of the launch; the operands of the next (rotation, digit) are requested before the current products.
+// WK: word type of the keys; PACKED: the bundle's sources have bits above 32.
+// Four rotations of 8 ciphertexts, N = 2^16, E = 32, three digits: 350 -> 305 us, 1.4 GB of compulsory traffic.
 // The special limbs of the result go to acc ([r][b][2][E][N] 64-bit words, the inverse transform reads them next), the
 // ciphertext limbs to (accq_lo, accq_hi) as [r][b][2][ell][N] packed residues: they are only read back by the last
 // kernel of the rotation, and written and read once per rotation they are a fifth of these two kernels' traffic.
-template <int NDIG, typename WK, bool PACKED>
-__global__ __launch_bounds__(256) void inner_product_kernel(const Mod* __restrict__ mods, uint32_t ell, uint32_t E,
-                                                            uint32_t L, uint32_t M, uint32_t logN, GatherSources src, MacRotations rot,
-                                                            uint64_t* __restrict__ acc, uint32_t* __restrict__ accq_lo,
+template <int G, typename WK, bool PACKED>
+__global__ __launch_bounds__(256, 4) void inner_product_kernel(const Mod* __restrict__ mods, uint32_t ell, uint32_t E, uint32_t L, uint32_t M,
+                                                            uint32_t logN, uint32_t ndig, uint32_t parts_log, GatherBundle src,
+                                                            MacRotations rot, uint64_t* __restrict__ acc, uint32_t* __restrict__ accq_lo,
                                                             uint8_t* __restrict__ accq_hi, uint32_t batch) {
     const uint32_t N = 1u << logN;
-    const uint32_t pos = blockIdx.y;
-    const uint32_t mid = pos < ell ? pos : L + (pos - ell);
+    const GatherTile tile = gather_tile(E, logN, parts_log);
+    if (!tile.valid) return;  // uniform
+    const uint32_t pos = tile.pos, n = tile.n, mid = pos < ell ? pos : L + (pos - ell);
     const Mod m = mods[mid];
-    const uint32_t n = blockIdx.x * 256 + threadIdx.x;
-    const uint32_t b_lo = blockIdx.z * kBatchGroup;
-    const SrcBases bases = src_bases<PACKED>(src, NDIG, E, N, b_lo);
-    uint32_t srce[kBatchGroup][NDIG];
-#pragma unroll
-    for (int bi = 0; bi < kBatchGroup; ++bi) {
-        const uint32_t b = min(b_lo + bi, batch - 1);
-#pragma unroll
-        for (int j = 0; j < NDIG; ++j) srce[bi][j] = src_offset(NDIG, E, N, b_lo, b, j, pos);
-    }
+    const BundleRsrc bundle = bundle_rsrc<G>(src, (uint64_t)ndig * E * N);
+    struct Raw {
+        SlotRaw<G> x;
+        WK k0, k1;
+    };
+    auto fetch = [&](uint32_t r, uint32_t j) {
+        Raw w;
+        const uint32_t sn = galois_source_slot(n, rot.galois[r], logN);
+        // a key is below 4 GB: [8][2][255][2^16] words of at most 8 bytes
+        const BufferRsrc key = uniform_rsrc(rot.key[r], (uint64_t)ndig * 2 * M * N * sizeof(WK));
+        const uint32_t at = (j * 2 * M + mid) * N * (uint32_t)sizeof(WK);
+        w.k0 = buffer_load<WK>(key, n * (uint32_t)sizeof(WK), at);
+        w.k1 = buffer_load<WK>(key, n * (uint32_t)sizeof(WK), at + M * N * (uint32_t)sizeof(WK));
+        w.x = slot_load<G, PACKED>(bundle, j * E + pos, N, sn);
+        return w;
+    };
+    Raw cur = fetch(0, 0);
 #pragma unroll 1
     for (uint32_t r = 0; r < rot.n; ++r) {
-        const uint32_t sn = galois_source_slot(n, rot.galois[r], logN);
-        const WK* key = static_cast<const WK*>(rot.key[r]) + (uint64_t)mid * N + n;
-        WK kraw[NDIG][2];
-        SrcRaw<PACKED> xraw[kBatchGroup][NDIG];
+        double h0[G], l0[G], h1[G], l1[G];
 #pragma unroll
-        for (int j = 0; j < NDIG; ++j) {
-            kraw[j][0] = key[(uint64_t)(j * 2 + 0) * M * N];
-            kraw[j][1] = key[(uint64_t)(j * 2 + 1) * M * N];
+        for (int b = 0; b < G; ++b) {
+            h0[b] = h1[b] = kMacBias;
+            l0[b] = l1[b] = 0.0;
         }
+#pragma unroll 1
+        for (uint32_t j = 0; j < ndig; ++j) {
+            const bool last = j + 1 == ndig;
+            const Raw next = fetch(last ? min(r + 1, rot.n - 1) : r, last ? 0 : j + 1);
+            const double k0 = word_to_f64<WK>(cur.k0), k1 = word_to_f64<WK>(cur.k1);
+            const SlotRaw<G> s = slot_take<G, PACKED>(cur.x);
 #pragma unroll
-        for (int bi = 0; bi < kBatchGroup; ++bi)
-#pragma unroll
-            for (int j = 0; j < NDIG; ++j) xraw[bi][j] = src_load<PACKED>(bases, srce[bi][j], sn);
+            for (int b = 0; b < G; ++b) {
+                const double x = slot_f64<G, PACKED>(s, b);
+                mac_exact(x, k0, h0[b], l0[b]);
+                mac_exact(x, k1, h1[b], l1[b]);
+            }
+            cur = next;
+        }
         uint64_t* ar = acc + (uint64_t)r * batch * 2 * E * N;
         const uint64_t rq = (uint64_t)r * batch * 2 * ell * N;
 #pragma unroll
-        for (int bi = 0; bi < kBatchGroup; ++bi) {
-            const uint32_t b = min(b_lo + bi, batch - 1);
-            double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-            for (int j = 0; j < NDIG; ++j) {
-                const double x = src_f64<PACKED>(xraw[bi][j]);
-                a0 += mulmod_lazy(x, word_to_f64<WK>(kraw[j][0]), m);
-                a1 += mulmod_lazy(x, word_to_f64<WK>(kraw[j][1]), m);
-            }
-            const uint64_t u0 = f64_to_u64(canon(reduce_lazy(a0, m), m)), u1 = f64_to_u64(canon(reduce_lazy(a1, m), m));
+        for (int b = 0; b < G; ++b) {
+            if (b >= (int)batch) break;  // uniform
+            const uint64_t u0 = f64_to_u64(canon(mac_reduce(h0[b], l0[b], m), m)), u1 = f64_to_u64(canon(mac_reduce(h1[b], l1[b], m), m));
             if (pos < ell) {  // uniform: ciphertext limbs go out packed, 5 bytes a residue
                 const uint64_t e0 = rq + (((uint64_t)b * 2 + 0) * ell + pos) * N + n, e1 = e0 + (uint64_t)ell * N;
                 accq_lo[e0] = (uint32_t)u0;
@@ -120,183 +184,205 @@ __global__ __launch_bounds__(256) void inner_product_kernel(const Mod* __restric
     }
 }
 
-// bytes a gathered source residue takes
-static double src_bytes(const GatherSources& g) { return g.hi ? 5.0 : 4.0; }
+#define KS_FOR_GATHER_KERNEL(LAUNCH)                                                       \
+    {                                                                                      \
+        const int kind = !src.hi ? 0 : key_words32 ? 1 : 2;                                \
+        switch (src.group * 4 + kind) {                                                    \
+            case 4: LAUNCH(1, uint32_t, false); break;                                     \
+            case 5: LAUNCH(1, uint32_t, true); break;                                      \
+            case 6: LAUNCH(1, uint64_t, true); break;                                      \
+            case 8: LAUNCH(2, uint32_t, false); break;                                     \
+            case 9: LAUNCH(2, uint32_t, true); break;                                      \
+            case 10: LAUNCH(2, uint64_t, true); break;                                     \
+            case 16: LAUNCH(4, uint32_t, false); break;                                    \
+            case 17: LAUNCH(4, uint32_t, true); break;                                     \
+            case 18: LAUNCH(4, uint64_t, true); break;                                     \
+            case 32: LAUNCH(8, uint32_t, false); break;                                    \
+            case 33: LAUNCH(8, uint32_t, true); break;                                     \
+            default: LAUNCH(8, uint64_t, true); break;                                     \
+        }                                                                                  \
+    }
 
-void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherSources& src, const MacRotations& rot, uint64_t* acc,
+// bytes a gathered source residue takes
+static double src_bytes(const GatherBundle& g) { return g.hi ? 4.0 + (double)gather_hi_bytes(g.group) / g.group : 4.0; }
+
+void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* acc,
                           const PackedDigits& accq, uint32_t batch, hipStream_t s, bool key_words32) {
     if (batch == 0 || rot.n == 0) return;
-    const uint32_t groups = (batch + kBatchGroup - 1) / kBatchGroup;
-    const dim3 grid(c->N / 256, lv.E, groups), block(256);
-    // reads: every raised digit limb per ciphertext once per launch, each rotation's key once per group; writes: both
-    // accumulators of every rotation
+    const uint32_t pl = gather_parts_log(c, lv.E);
+    // reads: every raised digit limb per ciphertext once per launch, each rotation's key once; writes: both accumulators of
+    // every rotation
     const double wk = key_words32 ? 4.0 : 8.0;
     ProfScope ps("inner_product",
-                 (src_bytes(src) * batch * lv.ndig * lv.E + (double)rot.n * (wk * 2.0 * lv.ndig * lv.E * groups + (16.0 * (lv.E - lv.ell) + 10.0 * lv.ell) * batch)) * c->N,
+                 (src_bytes(src) * batch * lv.ndig * lv.E + (double)rot.n * (wk * 2.0 * lv.ndig * lv.E + (16.0 * (lv.E - lv.ell) + 10.0 * lv.ell) * batch)) * c->N,
                  s);
-#define KS_LAUNCH_IP_W(ND, WKT, PK)                                                                                                \
-    hipLaunchKernelGGL((inner_product_kernel<ND, WKT, PK>), grid, block, 0, s, c->d_mod, lv.ell, lv.E, c->L, c->M, c->logN, src, \
-                       rot, acc, accq.lo, accq.hi, batch)
-#define KS_LAUNCH_IP(ND)                                                \
-    if (!src.hi) KS_LAUNCH_IP_W(ND, uint32_t, false);                   \
-    else if (key_words32) KS_LAUNCH_IP_W(ND, uint32_t, true);           \
-    else KS_LAUNCH_IP_W(ND, uint64_t, true)
-    switch (lv.ndig) {
-        case 1: KS_LAUNCH_IP(1); break;
-        case 2: KS_LAUNCH_IP(2); break;
-        case 3: KS_LAUNCH_IP(3); break;
-        case 4: KS_LAUNCH_IP(4); break;
-        case 5: KS_LAUNCH_IP(5); break;
-        case 6: KS_LAUNCH_IP(6); break;
-        case 7: KS_LAUNCH_IP(7); break;
-        default: KS_LAUNCH_IP(8); break;
-    }
+#define KS_LAUNCH_IP(GV, WKT, PK)                                                                                                         \
+    hipLaunchKernelGGL((inner_product_kernel<GV, WKT, PK>), dim3(gather_grid(c, lv.E, pl)), dim3(256), 0, s, c->d_mod, lv.ell, lv.E, c->L, \
+                       c->M, c->logN, lv.ndig, pl, src, rot, acc, accq.lo, accq.hi, batch)
+    KS_FOR_GATHER_KERNEL(KS_LAUNCH_IP)
 #undef KS_LAUNCH_IP
-#undef KS_LAUNCH_IP_W
 }
 
 // Rotate-multiply-accumulate on the extended basis (inner sum of a baby-step giant-step transform with the division by P
-// deferred to the whole sum).  One thread owns one slot of one limb position for a group of ciphertexts and walks the
-// rotations: key slots and the plaintext slot of a rotation are read once per group, the raised digits and c0 come
-// through the sigma_g gather, and the two running sums stay in registers until every rotation of the launch is in.
-// Branch-free within a rotation on purpose (digit count as a template parameter, a short last group recomputes its last
-// ciphertext, special limbs read a c0 limb they multiply by zero): every load of a rotation is then issued before the
-// first product.  Galois element 1 is the unrotated ciphertext (P (c0, c1), no key read).
-// WC: word type of the ciphertext ct (64-bit with packed sources, 32-bit with 32-bit sources).
-template <int NDIG, typename WK, bool PACKED>
-__global__ __launch_bounds__(256) void rotate_mac_kernel(const Mod* __restrict__ mods, const double* __restrict__ Pmod,
-                                                         uint32_t ell, uint32_t E, uint32_t L, uint32_t M, uint32_t logN,
-                                                         const void* __restrict__ ct_, uint64_t ct_bs, GatherSources src,
-                                                         MacRotations rot, const uint64_t* __restrict__ one,
+// deferred to the whole sum).  One thread owns one slot of one limb position for all ciphertexts of the group; the two
+// running sums of each stay in registers as exact integers (mac_exact) until every rotation of the launch is in.  The digits
+// are the OUTER loop and the rotations the inner one, so that between two rotations only one digit's slots are gathered from
+// and about half of them are found in the XCD's L2 (see gather_tile); each key slot is still read once, the plaintext slot
+// once per digit.  The operands of the next (digit, rotation) are requested before the current products.
+// 8 ciphertexts x (15 keyed rotations + 1 identity), three digits, N = 2^16, E = 32: 650 us, where one thread per slot that
+// walked digits inside rotations and gathered each ciphertext on its own took 980 us (9.2 GB through the fabric, now 5).
+// What bounds it: the stream of keys and plaintexts (2.5 GB; alone 600 us) and fp64 issue (alone 470 us), partly overlapped.
+// Three wavefronts per SIMD: squeezed into 128 registers for a fourth, the few spilled words cost more fabric traffic than
+// the occupancy gains (690-750 us).  Sixteen ciphertexts per launch sharing the key reads measured the same per ciphertext:
+// what the shared keys save, the doubled sources lose in L2.
+// rot: the n_key rotations that take a key come first, then the identities (the term P (c0, c1), no key read).
+template <int G, typename WK, bool PACKED>
+__global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restrict__ mods, const double* __restrict__ Pmod, uint32_t ell,
+                                                         uint32_t E, uint32_t L, uint32_t M, uint32_t logN, DigitRanges dg,
+                                                         uint32_t parts_log, GatherBundle src, MacRotations rot, uint32_t n_key,
                                                          uint64_t* __restrict__ u, uint32_t batch, int accumulate) {
-    using WC = std::conditional_t<PACKED, uint64_t, uint32_t>;
-    const WC* ct = static_cast<const WC*>(ct_);
     const uint32_t N = 1u << logN;
-    const uint32_t pos = blockIdx.y;
-    const uint32_t mid = pos < ell ? pos : L + (pos - ell);
+    const GatherTile tile = gather_tile(E, logN, parts_log);
+    if (!tile.valid) return;  // uniform
+    const uint32_t pos = tile.pos, n = tile.n, mid = pos < ell ? pos : L + (pos - ell);
     const Mod m = mods[mid];
-    const uint32_t c0_limb = min(pos, ell - 1);
-    const double pm = pos < ell ? Pmod[c0_limb] : 0.0;
-    const uint32_t n = blockIdx.x * 256 + threadIdx.x;
-    const uint32_t b_lo = blockIdx.z * kBatchGroup;
-    const SrcBases bases = src_bases<PACKED>(src, NDIG, E, N, b_lo);
-    // per ciphertext of the group: where its c0 limb and its NDIG source limbs of this position start
-    const WC* c0p[kBatchGroup];
-    uint32_t srce[kBatchGroup][NDIG];
-    uint64_t* up[kBatchGroup];
+    const BundleRsrc bundle = bundle_rsrc<G>(src, ((uint64_t)dg.ndig * E + ell) * N);
+    double h0[G], l0[G], h1[G], l1[G];
 #pragma unroll
-    for (int bi = 0; bi < kBatchGroup; ++bi) {
-        const uint32_t b = min(b_lo + bi, batch - 1);
-        c0p[bi] = ct + (uint64_t)b * ct_bs + (uint64_t)c0_limb * N;
-#pragma unroll
-        for (int j = 0; j < NDIG; ++j) srce[bi][j] = src_offset(NDIG, E, N, b_lo, b, j, pos);
-        up[bi] = u + (((uint64_t)b * 2) * E + pos) * N + n;
+    for (int b = 0; b < G; ++b) {
+        h0[b] = h1[b] = kMacBias;
+        const uint64_t* ub = u + ((uint64_t)min((uint32_t)b, batch - 1) * 2 * E + pos) * N;
+        l0[b] = accumulate ? u64_to_f64(ub[n]) : 0.0;
+        l1[b] = accumulate ? u64_to_f64(ub[(uint64_t)E * N + n]) : 0.0;
     }
-    double u0[kBatchGroup], u1[kBatchGroup];
-#pragma unroll
-    for (int bi = 0; bi < kBatchGroup; ++bi) {
-        u0[bi] = accumulate ? u64_to_f64(up[bi][0]) : 0.0;
-        u1[bi] = accumulate ? u64_to_f64(up[bi][(uint64_t)E * N]) : 0.0;
-    }
-#pragma unroll 1
-    for (uint32_t r = 0; r < rot.n; ++r) {
-        // the plaintext slot; a null plaintext is the constant 1, read (by every lane) from a one-word table so that the
-        // load stays unconditional
-        // (the table holds the 64-bit word 1, whose low half is the 32-bit word 1)
-        const WK* wp = rot.pt[r] ? static_cast<const WK*>(rot.pt[r]) + (uint64_t)mid * N + n : reinterpret_cast<const WK*>(one);
-        if (rot.galois[r] == 1) {  // uniform: the unrotated ciphertext, P (c0, c1), no key
-            WC c0raw[kBatchGroup], c1raw[kBatchGroup];
-            const WK wraw = *wp;
-#pragma unroll
-            for (int bi = 0; bi < kBatchGroup; ++bi) {
-                c0raw[bi] = c0p[bi][n];
-                c1raw[bi] = c0p[bi][(uint64_t)ell * N + n];
-            }
-            const double pw = mulmod_lazy(pm, word_to_f64<WK>(wraw), m);
-#pragma unroll
-            for (int bi = 0; bi < kBatchGroup; ++bi) {
-                u0[bi] += mulmod_lazy(word_to_f64<WC>(c0raw[bi]), pw, m);
-                u1[bi] += mulmod_lazy(word_to_f64<WC>(c1raw[bi]), pw, m);
-            }
-            continue;
-        }
+    struct Raw {
+        SlotRaw<G> x;
+        WK k0, k1, w;
+    };
+    auto fetch = [&](uint32_t j, uint32_t r) {
+        Raw w;
         const uint32_t sn = galois_source_slot(n, rot.galois[r], logN);
-        const WK* key = static_cast<const WK*>(rot.key[r]) + (uint64_t)mid * N + n;
-        WK kraw[NDIG][2];
-        SrcRaw<PACKED> xraw[kBatchGroup][NDIG];
-        WC craw[kBatchGroup];
+        // a key is below 4 GB: [8][2][255][2^16] words of at most 8 bytes
+        const BufferRsrc key = uniform_rsrc(rot.key[r], (uint64_t)dg.ndig * 2 * M * N * sizeof(WK));
+        const uint32_t at = (j * 2 * M + mid) * N * (uint32_t)sizeof(WK);
+        w.x = slot_load<G, PACKED>(bundle, j * E + pos, N, sn);
+        w.k0 = buffer_load<WK, 2>(key, n * (uint32_t)sizeof(WK), at);
+        w.k1 = buffer_load<WK, 2>(key, n * (uint32_t)sizeof(WK), at + M * N * (uint32_t)sizeof(WK));
+        // a null plaintext is the constant 1: the load stays unconditional and its value (a key's residue) is multiplied by 0
+        w.w = buffer_load<WK, 0>(uniform_rsrc(rot.pt[r] ? rot.pt[r] : rot.key[r], (uint64_t)M * N * sizeof(WK)), n * (uint32_t)sizeof(WK),
+                              mid * N * (uint32_t)sizeof(WK));
+        return w;
+    };
+    if (n_key != 0) {
+        const uint32_t steps = dg.ndig * n_key;
+        uint32_t j = 0, r = 0;
+        auto advance = [&]() {  // to the next (digit, rotation); stays on the last one at the end
+            if (r + 1 < n_key) ++r;
+            else if (j + 1 < dg.ndig) { r = 0; ++j; }
+        };
+        // live: false for the padding step of an odd count, multiplied by zero
+        auto products = [&](const Raw& q, uint32_t rq, bool live) {
+            // the plaintext slot is folded into the key slots, not multiplied per ciphertext
+            const double given = rot.pt[rq] && live ? 1.0 : 0.0, one = !rot.pt[rq] && live ? 1.0 : 0.0;  // uniform
+            const double w = __builtin_fma(word_to_f64<WK>(q.w), given, one);
+            const double k0 = mulmod_lazy(word_to_f64<WK>(q.k0), w, m), k1 = mulmod_lazy(word_to_f64<WK>(q.k1), w, m);
+            const SlotRaw<G> s = slot_take<G, PACKED>(q.x);
 #pragma unroll
-        for (int j = 0; j < NDIG; ++j) {
-            kraw[j][0] = key[(uint64_t)(j * 2 + 0) * M * N];
-            kraw[j][1] = key[(uint64_t)(j * 2 + 1) * M * N];
-        }
-        const WK wraw = *wp;
-#pragma unroll
-        for (int bi = 0; bi < kBatchGroup; ++bi) {
-#pragma unroll
-            for (int j = 0; j < NDIG; ++j) xraw[bi][j] = src_load<PACKED>(bases, srce[bi][j], sn);
-            craw[bi] = c0p[bi][sn];
-        }
-        // the plaintext slot is folded into the key slots and into P once per rotation, not multiplied per ciphertext
-        const double w = word_to_f64<WK>(wraw), pw = mulmod_lazy(pm, w, m);
-        double kw[NDIG][2];
-#pragma unroll
-        for (int j = 0; j < NDIG; ++j) {
-            kw[j][0] = mulmod_lazy(word_to_f64<WK>(kraw[j][0]), w, m);
-            kw[j][1] = mulmod_lazy(word_to_f64<WK>(kraw[j][1]), w, m);
-        }
-#pragma unroll
-        for (int bi = 0; bi < kBatchGroup; ++bi) {
-            double t0 = mulmod_lazy(word_to_f64<WC>(craw[bi]), pw, m), t1 = 0.0;
-#pragma unroll
-            for (int j = 0; j < NDIG; ++j) {
-                const double x = src_f64<PACKED>(xraw[bi][j]);
-                t0 += mulmod_lazy(x, kw[j][0], m);
-                t1 += mulmod_lazy(x, kw[j][1], m);
+            for (int b = 0; b < G; ++b) {
+                const double x = slot_f64<G, PACKED>(s, b);
+                mac_exact(x, k0, h0[b], l0[b]);
+                mac_exact(x, k1, h1[b], l1[b]);
             }
-            // the sums grow by at most (digits + 1) * 0.51 p a rotation: below 2^43 after the 16 rotations of a launch
-            u0[bi] += t0;
-            u1[bi] += t1;
+        };
+        // two steps a trip: operands and sums alternate between two register sets instead of being copied
+        Raw qa = fetch(0, 0);
+#pragma unroll 1
+        for (uint32_t t = 0; t < steps; t += 2) {
+            const uint32_t ra = r;
+            advance();
+            const uint32_t rb = r;
+            const Raw qb = fetch(j, r);
+            products(qa, ra, true);
+            advance();
+            qa = fetch(j, r);
+            products(qb, rb, t + 1 < steps);
+        }
+    }
+    if (pos < ell) {  // uniform: P c0 of every rotation, P c1 of the identities
+        const double pm = Pmod[pos];
+        auto plaintext = [&](uint32_t r) { return rot.pt[r] ? static_cast<const WK*>(rot.pt[r])[(uint64_t)mid * N + n] : (WK)1; };
+        uint32_t own = 0;
+        while (own + 1 < dg.ndig && pos >= dg.hi[own]) ++own;
+        constexpr uint32_t AHEAD = 2;  // rotations in flight
+        SlotRaw<G> x[AHEAD];
+        WK w[AHEAD];
+        auto fetch0 = [&](uint32_t r, int i) {
+            r = min(r, rot.n - 1);
+            x[i] = slot_load<G, PACKED>(bundle, dg.ndig * E + pos, N, r < n_key ? galois_source_slot(n, rot.galois[r], logN) : n);
+            w[i] = plaintext(r);
+        };
+#pragma unroll
+        for (uint32_t i = 0; i < AHEAD; ++i) fetch0(i, i);
+#pragma unroll 1
+        for (uint32_t r0 = 0; r0 < rot.n; r0 += AHEAD) {
+#pragma unroll
+            for (uint32_t i = 0; i < AHEAD; ++i) {
+                const double pw = mulmod_lazy(r0 + i < rot.n ? pm : 0.0, word_to_f64<WK>(w[i]), m);
+                const SlotRaw<G> s = slot_take<G, PACKED>(x[i]);
+#pragma unroll
+                for (int b = 0; b < G; ++b) mac_exact(slot_f64<G, PACKED>(s, b), pw, h0[b], l0[b]);
+                fetch0(r0 + i + AHEAD, i);
+            }
+        }
+#pragma unroll 1
+        for (uint32_t r = n_key; r < rot.n; ++r) {
+            const SlotRaw<G> x = slot_load<G, PACKED>(bundle, own * E + pos, N, n);
+            const double pw = mulmod_lazy(pm, word_to_f64<WK>(plaintext(r)), m);
+#pragma unroll
+            for (int b = 0; b < G; ++b) mac_exact(slot_f64<G, PACKED>(x, b), pw, h1[b], l1[b]);
         }
     }
 #pragma unroll
-    for (int bi = 0; bi < kBatchGroup; ++bi) {
-        up[bi][0] = f64_to_u64(canon(reduce_lazy(u0[bi], m), m));
-        up[bi][(uint64_t)E * N] = f64_to_u64(canon(reduce_lazy(u1[bi], m), m));
+    for (int b = 0; b < G; ++b) {
+        if (b >= (int)batch) break;  // uniform
+        uint64_t* ub = u + ((uint64_t)b * 2 * E + pos) * N + n;
+        ub[0] = f64_to_u64(canon(mac_reduce(h0[b], l0[b], m), m));
+        ub[(uint64_t)E * N] = f64_to_u64(canon(mac_reduce(h1[b], l1[b], m), m));
     }
 }
 
-void launch_rotate_mac(const ks_ctx* c, const Level& lv, const void* ct, uint64_t ct_bs, const GatherSources& src,
-                       const MacRotations& rot, uint64_t* u, uint32_t batch, bool accumulate, hipStream_t s, bool key_words32) {
+void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* u, uint32_t batch,
+                       bool accumulate, hipStream_t s, bool key_words32) {
     if (batch == 0 || rot.n == 0) return;
-    const uint32_t groups = (batch + kBatchGroup - 1) / kBatchGroup;
-    const dim3 grid(c->N / 256, lv.E, groups), block(256);
-    // Algorithmic traffic: the raised digits and c0 of a ciphertext once (the rotations of a launch re-read them through
-    // the gather; those re-reads are meant to come from cache), key and plaintext of every rotation once per group, both
-    // sums written once.  Algorithmic work per slot, ciphertext and rotation: 2 NDIG + 1 modular products (+ 2 NDIG + 1 per group).
-    const double reads = batch * (src_bytes(src) * lv.ndig * lv.E + (src.hi ? 8.0 : 4.0) * lv.ell) +
-                         (key_words32 ? 4.0 : 8.0) * (double)rot.n * groups * (2.0 * lv.ndig + 1.0) * lv.E;
-    ProfScope ps("rotate_mac", (reads + (double)batch * 16 * lv.E * (accumulate ? 2 : 1)) * c->N, s,
-                 (double)rot.n * batch * lv.E * c->N * (7.0 * (2 * lv.ndig + 1)));
-#define KS_LAUNCH_MAC_W(ND, WKT, PK)                                                                                                  \
-    hipLaunchKernelGGL((rotate_mac_kernel<ND, WKT, PK>), grid, block, 0, s, c->d_mod, c->d_Pmod, lv.ell, lv.E, c->L, c->M, c->logN, \
-                       ct, ct_bs, src, rot, c->d_one, u, batch, accumulate ? 1 : 0)
-#define KS_LAUNCH_MAC(ND)                                               \
-    if (!src.hi) KS_LAUNCH_MAC_W(ND, uint32_t, false);                  \
-    else if (key_words32) KS_LAUNCH_MAC_W(ND, uint32_t, true);          \
-    else KS_LAUNCH_MAC_W(ND, uint64_t, true)
-    switch (lv.ndig) {
-        case 1: KS_LAUNCH_MAC(1); break;
-        case 2: KS_LAUNCH_MAC(2); break;
-        case 3: KS_LAUNCH_MAC(3); break;
-        case 4: KS_LAUNCH_MAC(4); break;
-        case 5: KS_LAUNCH_MAC(5); break;
-        case 6: KS_LAUNCH_MAC(6); break;
-        case 7: KS_LAUNCH_MAC(7); break;
-        default: KS_LAUNCH_MAC(8); break;
+    const uint32_t pl = gather_parts_log(c, lv.E);
+    DigitRanges dg;
+    dg.ndig = lv.ndig;
+    for (uint32_t j = 0; j < kMaxDigits; ++j) {
+        dg.lo[j] = j < lv.ndig ? lv.digit_lo[j] : 0;
+        dg.hi[j] = j < lv.ndig ? lv.digit_hi[j] : 0;
     }
+    MacRotations sorted = rot;
+    uint32_t n_key = 0, n_id = 0;
+    for (int pass = 0; pass < 2; ++pass)
+        for (uint32_t r = 0; r < rot.n; ++r) {
+            if ((rot.galois[r] == 1) != (pass == 1)) continue;
+            const uint32_t to = n_key + n_id;
+            sorted.galois[to] = rot.galois[r];
+            sorted.key[to] = rot.key[r];
+            sorted.pt[to] = rot.pt[r];
+            ++(pass == 0 ? n_key : n_id);
+        }
+    // Algorithmic traffic: the raised digits and c0 of a ciphertext once (the rotations of a launch re-read them through
+    // the gather; those re-reads are meant to come from cache), key and plaintext of every rotation once, both sums written
+    // once.  Algorithmic work per slot, ciphertext and rotation: 2 NDIG + 1 exact products (+ 2 NDIG + 1 modular ones per group).
+    const double reads = batch * src_bytes(src) * (lv.ndig * lv.E + lv.ell) + (key_words32 ? 4.0 : 8.0) * (double)rot.n * (2.0 * lv.ndig + 1.0) * lv.E;
+    ProfScope ps("rotate_mac", (reads + (double)batch * 16 * lv.E * (accumulate ? 2 : 1)) * c->N, s,
+                 (double)rot.n * lv.E * c->N * (4.0 * batch + 6.0) * (2 * lv.ndig + 1));
+#define KS_LAUNCH_MAC(GV, WKT, PK)                                                                                                        \
+    hipLaunchKernelGGL((rotate_mac_kernel<GV, WKT, PK>), dim3(gather_grid(c, lv.E, pl)), dim3(256), 0, s, c->d_mod, c->d_Pmod, lv.ell, lv.E, \
+                       c->L, c->M, c->logN, dg, pl, src, sorted, n_key, u, batch, accumulate ? 1 : 0)
+    KS_FOR_GATHER_KERNEL(KS_LAUNCH_MAC)
 #undef KS_LAUNCH_MAC
-#undef KS_LAUNCH_MAC_W
 }
 
 // (b1, a1) x (b2, a2) -> d0 = b1 b2, d1 = a1 b2 + a2 b1, d2 = a1 a2.  d2, the polynomial that is key-switched, goes out as

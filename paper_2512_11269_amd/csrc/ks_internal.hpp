@@ -111,7 +111,6 @@ struct ks_ctx {
     double* d_ninv = nullptr;             // [M]  N^-1 mod m
     double* d_Pinv = nullptr;             // [L]  P^-1 mod q_i
     double* d_Pmod = nullptr;             // [L]  P mod q_i
-    uint64_t* d_one = nullptr;            // [2]  the residue 1 (unit plaintext slot)
     double* d_moddown_scale = nullptr;    // [K]  N^-1 (P / p_k)^-1 mod p_k
     double* d_tw_fwd = nullptr;           // [M][N] psi^brv(k)
     double* d_tw_inv = nullptr;           // [M][N] psi^-brv(k)
@@ -248,34 +247,41 @@ struct MacRotations {
     const void* key[kMacRotations];  // [dnum][2][L+K][N], 64- or 32-bit words
     const void* pt[kMacRotations];   // [L+K][N], same word size as the keys
 };
-// What the sigma_g gathers of a rotation read: the bundle [b][ndig][E][N] of the finished raised digits with, in the slots
-// of a digit's own positions, the limbs of the polynomial itself.  hi != nullptr: packed residues (lo, hi); hi == nullptr:
-// 32-bit words in lo (moduli below 2^32).
-struct GatherSources {
-    const uint32_t* lo;
-    const uint8_t* hi;
+// What the sigma_g gathers of a rotation read, for a group of up to 8 ciphertexts: slabs of N slots, slab j E + pos the
+// finished raised digit j at limb position pos (in the slots of a digit's own positions the limbs of the polynomial
+// itself), slabs ndig E + pos, pos < ell, the limbs of the addend c0 where a caller asked for them.  A slot holds the
+// residues of all `group` ciphertexts side by side (group = 1, 2, 4 or 8, the batch rounded up; the places past the batch
+// repeat its last ciphertext), so that one gathered slot is one contiguous access for every ciphertext that needs it:
+// lo the 32-bit low words, 64 consecutive slots of up to four ciphertexts at a time ([slot / 64][group / 4][slot % 64][4]: a
+// wavefront reads a kilobyte per 16-byte load) and, hi != nullptr, hi[slot] the bits above (moduli are below 2^36) as one 4-bit
+// field per ciphertext in a word of group / 2 bytes (one byte for group 1).  hi == nullptr: moduli below 2^32, lo alone.
+struct GatherBundle {
+    uint32_t* lo;
+    uint8_t* hi;
+    uint32_t group;
 };
-// Finish the bundle in one launch: the row half of the forward transform of the raised limbs (`lifted`, the bundle's
-// element layout, raw doubles after the column half) and a copy of the polynomials' own limbs d[b][pos] (64-bit words with
-// a packed bundle, 32-bit words with a 32-bit one; d_ps words apart) into the slots (b, digit of pos, pos).
-// out.hi == nullptr: a bundle of 32-bit words.
-void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t* lifted, const void* d, uint64_t d_ps, bool d_words32,
-                               const PackedDigits& out, uint32_t n_polys, hipStream_t s);
+inline uint32_t gather_group(uint32_t batch) { return batch > 4 ? 8 : batch > 2 ? 4 : batch; }
+inline uint32_t gather_hi_bytes(uint32_t group) { return group > 1 ? group / 2 : 1; }
+// Fill a bundle in one launch.  raised: the row half of the forward transform of the raised limbs (`lifted`,
+// [b][ndig][E][N] raw doubles after the column half), all digits.  The polynomials' own limbs d[b][pos] and, c0 != nullptr,
+// the addend's limbs c0[b][pos] (64-bit words with a packed bundle, 32-bit words with a 32-bit one; ps words apart) are
+// copied.
+void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t* lifted, const void* d, const void* c0, uint64_t ps,
+                               const GatherBundle& out, uint32_t batch, bool raised, hipStream_t s);
 
 // acc[r][b][c][pos] = sum_j sigma_{g_r}(src_j)[pos] * key_r[j][c][ext_id(pos)] for every rotation r of `rot` (pt unused);
-// src_j[pos] = d[b][pos] when pos lies in digit j, otherwise lifted[b][j][pos]: slot (b, j, pos) of the bundle `src`.
+// src_j[pos] = slab j E + pos of the bundle.
 // key_words32: keys (and plaintexts) hold one residue per 32-bit word; 32-bit sources imply 32-bit keys.
 // The special limbs of the result go to acc ([r][b][2][E][N], ciphertext limbs left untouched), the ciphertext limbs to
 // accq ([r][b][2][ell][N], packed).
-void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherSources& src, const MacRotations& rot, uint64_t* acc,
+void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* acc,
                           const PackedDigits& accq, uint32_t batch, hipStream_t s, bool key_words32 = false);
 
 // u[b][c][pos] (+)= sum_r pt_r[pos] * (sum_j sigma_r(src_j)[pos] key_r[j][c][pos] + [c = 0][pos < ell] P sigma_r(c0)[pos]);
-// ct: [b][2][ell][N] (c0, c1) in 64-bit words with packed sources, in 32-bit words with 32-bit sources (ct_bs in words);
-// src: c1 and its finished raised digits.  accumulate: add to what u already holds.
+// src: c1 and its finished raised digits, and c0.  accumulate: add to what u already holds.
 // galois[r] == 1: the term is P (c0, c1) and key[r] is not read; pt[r] == nullptr: the constant 1.
-void launch_rotate_mac(const ks_ctx* c, const Level& lv, const void* ct, uint64_t ct_bs, const GatherSources& src,
-                       const MacRotations& rot, uint64_t* u, uint32_t batch, bool accumulate, hipStream_t s, bool key_words32 = false);
+void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* u, uint32_t batch,
+                       bool accumulate, hipStream_t s, bool key_words32 = false);
 
 // The key-switch chain behind ks_keyswitch / ks_keyswitch_u32 (argument checks included); ws is any device buffer of
 // at least ks_workspace_bytes(KS_OP_KEYSWITCH) bytes, whose contents need no initialisation.

@@ -69,70 +69,81 @@ __global__ __launch_bounds__(64) void ntt_fwd_rows(TwTables tw, const Mod* __res
     for (int k = 0; k < 16; ++k) p[j0 + 16 * k] = f64_to_u64(canon(reduce_lazy(v[k], m), m));
 }
 
-// The bundle [b][ndig][E][N] the rotation gathers read, finished in one launch.  The first n_new_blocks workgroups run the
-// row half of the forward transform on the raised limbs (`lifted`, the same element layout, raw doubles after the column
-// half) and write canonical residues; the others copy the polynomial's own limbs d[b][pos] (WD words, d_ps apart) into
-// the slots (b, digit of pos, pos), so that every slot of the bundle is filled and a gather needs no own / raised
-// distinction.  PACKED: bits 0..31 of a residue go to the 32-bit word array lo and the bits above (moduli are below 2^36)
-// to the byte array hi with the same element index, 5 bytes a residue instead of 8; a transforming thread then ends with
-// sixteen consecutive points and stores them as four 16-byte words plus one 16-byte word of high bytes, so the row needs
-// no last exchange through LDS.  Otherwise (moduli below 2^32) lo alone holds 32-bit words.
-template <int LOG_R, bool PACKED, typename WD>
-__global__ __launch_bounds__(64) void gather_bundle_rows(TwTables tw, const Mod* __restrict__ mods, LimbMap map, DigitRanges dg,
-                                                         uint32_t ell, uint32_t E, const uint64_t* __restrict__ lifted,
-                                                         const WD* __restrict__ d, uint64_t d_ps, uint32_t n_new_blocks,
-                                                         uint32_t* __restrict__ lo, uint8_t* __restrict__ hi) {
-    constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R, GROUPS = R / 4;
-    __shared__ double lds[4 * kRowPitch];
-    const uint32_t tid = threadIdx.x, j0 = tid & 15, rr = tid >> 4;
-    const uint64_t ps = (uint64_t)dg.ndig * E * N;
-    if (blockIdx.x >= n_new_blocks) {  // uniform: copy four rows of an own limb
-        const uint32_t t = blockIdx.x - n_new_blocks, li = t / GROUPS, row = (t - li * GROUPS) * 4 + rr;
-        const uint32_t poly = li / ell, pos = li - poly * ell;
+// The bundle the rotation gathers read (layout: GatherBundle), filled in one launch.  A workgroup owns four rows of one slab
+// for all ciphertexts of the group, one wavefront per ciphertext: the first n_new workgroups run the row half of the
+// forward transform on the raised limbs and leave canonical residues in LDS, from where every thread collects whole slots;
+// the others copy the polynomial's own limbs into the slabs of their digits and the addend's limbs behind the digits.
+// Interleaving here, once, makes the gathers of every rotation read one contiguous 36 bytes per slot and digit for eight
+// ciphertexts.
+template <int LOG_R, int G, bool PACKED>
+__global__ __launch_bounds__(64 * G) void gather_bundle_rows(TwTables tw, const Mod* __restrict__ mods, LimbMap map, DigitRanges dg,
+                                                             uint32_t ell, uint32_t E, const uint64_t* __restrict__ lifted,
+                                                             const void* __restrict__ d, const void* __restrict__ c0, uint64_t d_ps,
+                                                             uint32_t batch, uint32_t n_new, uint32_t* __restrict__ lo,
+                                                             uint8_t* __restrict__ hi) {
+    using WD = std::conditional_t<PACKED, uint64_t, uint32_t>;
+    using HW = std::conditional_t<G == 8, uint32_t, std::conditional_t<G == 4, uint16_t, uint8_t>>;
+    constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R, GROUPS = R / 4, TPB = 64 * G, WAVE_LDS = 4 * kRowPitch;
+    __shared__ double lds[G * WAVE_LDS];
+    const uint32_t tid = threadIdx.x;
+    uint32_t slab, rg;
+    uint64_t v[16 / G * G];  // the 1024 / TPB slots of this thread, G residues each
+    if (blockIdx.x < n_new) {  // uniform
+        const uint32_t lane = tid & 63, j0 = lane & 15, rr = lane >> 4, w = tid >> 6, b = min(w, batch - 1);
+        const uint32_t idx = blockIdx.x / GROUPS, mod_id = map.mod[idx];
+        rg = blockIdx.x - idx * GROUPS;
+        slab = map.off[idx];
+        const Mod m = mods[mod_id];
+        const uint32_t row = rg * 4 + rr;
+        const uint64_t* ip = lifted + ((uint64_t)b * dg.ndig * E + slab) * N + row * 256;
+        double x[16];
+        PassTwiddles t;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) x[k] = load_f64(ip + j0 + 16 * k);
+        load_row_twiddles(t, tw, mod_id, N, R + row, j0, m);
+        double* lrow = lds + w * WAVE_LDS + rr * kRowPitch;
+        row_fwd_core_consecutive(x, t, j0, lrow, m);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) lrow[17 * j0 + k] = canon(reduce_lazy(x[k], m), m);
+        __syncthreads();
+#pragma unroll
+        for (uint32_t i = 0; i < 16 / G; ++i) {
+            const uint32_t s = tid + i * TPB, p = s & 255;
+#pragma unroll
+            for (int g = 0; g < G; ++g) v[i * G + g] = f64_to_u64(lds[g * WAVE_LDS + (s >> 8) * kRowPitch + p + (p >> 4)]);
+        }
+    } else {
+        const uint32_t t = blockIdx.x - n_new, li = t / GROUPS, pos = li < ell ? li : li - ell;
+        rg = t - li * GROUPS;
         uint32_t j = 0;
         while (j + 1 < dg.ndig && pos >= dg.hi[j]) ++j;  // uniform
-        const WD* src = d + poly * d_ps + (uint64_t)pos * N + row * 256 + j0;
-        const uint64_t e = poly * ps + ((uint64_t)j * E + pos) * N + row * 256 + j0;
-        WD u[16];
+        slab = (li < ell ? j : dg.ndig) * E + pos;
+        const WD* src = static_cast<const WD*>(li < ell ? d : c0) + (uint64_t)pos * N + rg * 1024 + tid;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) u[k] = src[16 * k];
+        for (uint32_t i = 0; i < 16 / G; ++i)
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            lo[e + 16 * k] = (uint32_t)u[k];
-            if constexpr (PACKED) hi[e + 16 * k] = (uint8_t)((uint64_t)u[k] >> 32);
-        }
-        return;
+            for (uint32_t g = 0; g < G; ++g) v[i * G + g] = src[min(g, batch - 1) * d_ps + i * TPB];
     }
-    const uint32_t li = blockIdx.x / GROUPS, rg = blockIdx.x - li * GROUPS;
-    const uint32_t poly = li / map.n, idx = li - poly * map.n, mod_id = map.mod[idx];
-    const uint64_t off = poly * ps + (uint64_t)map.off[idx] * N;
-    const Mod m = mods[mod_id];
-    const uint32_t row = rg * 4 + rr;
-    const uint64_t* ip = lifted + off + row * 256;
-    double v[16];
-    PassTwiddles t;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = load_f64(ip + j0 + 16 * k);
-    load_row_twiddles(t, tw, mod_id, N, R + row, j0, m);
-    if constexpr (PACKED) {
-        row_fwd_core_consecutive(v, t, j0, lds + rr * kRowPitch, m);
-        uint32_t l[16], h[4] = {0, 0, 0, 0};
+    for (uint32_t i = 0; i < 16 / G; ++i) {
+        const uint64_t slot = (uint64_t)slab * N + rg * 1024 + tid + i * TPB;
+        uint32_t h = 0;
+        if constexpr (G >= 4) {
+            uint4* lp = reinterpret_cast<uint4*>(lo + (slot & ~63ull) * G) + (slot & 63);
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const uint64_t u = f64_to_u64(canon(reduce_lazy(v[k], m), m));
-            l[k] = (uint32_t)u;
-            h[k >> 2] |= (uint32_t)(u >> 32) << (8 * (k & 3));
+            for (int q = 0; q < G / 4; ++q)
+                lp[64 * q] = make_uint4((uint32_t)v[i * G + 4 * q], (uint32_t)v[i * G + 4 * q + 1], (uint32_t)v[i * G + 4 * q + 2],
+                                   (uint32_t)v[i * G + 4 * q + 3]);
+        } else if constexpr (G == 2) {
+            reinterpret_cast<uint2*>(lo)[slot] = make_uint2((uint32_t)v[i * G], (uint32_t)v[i * G + 1]);
+        } else {
+            lo[slot] = (uint32_t)v[i];
         }
-        const uint64_t e = off + row * 256 + 16 * j0;
-        uint4* lp = reinterpret_cast<uint4*>(lo + e);
+        if constexpr (PACKED) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) lp[q] = make_uint4(l[4 * q], l[4 * q + 1], l[4 * q + 2], l[4 * q + 3]);
-        *reinterpret_cast<uint4*>(hi + e) = make_uint4(h[0], h[1], h[2], h[3]);
-    } else {
-        row_fwd_core(v, t, j0, lds + rr * kRowPitch, m);
-        uint32_t* op = lo + off + row * 256 + j0;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) op[16 * k] = (uint32_t)canon(reduce_lazy(v[k], m), m);
+            for (int g = 0; g < G; ++g) h |= (uint32_t)(v[i * G + g] >> 32) << (4 * g);
+            reinterpret_cast<HW*>(hi)[slot] = (HW)h;
+        }
     }
 }
 
@@ -272,29 +283,34 @@ void launch_ntt_fwd_rows(const ks_ctx* c, const LimbMap& map, uint64_t* data, ui
 #undef KS_LAUNCH
 }
 
-void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t* lifted, const void* d, uint64_t d_ps, bool d_words32,
-                               const PackedDigits& out, uint32_t n_polys, hipStream_t s) {
-    if (n_polys == 0) return;
-    const uint32_t n_new = lv.lifted_map.n * n_polys, n_own = lv.ell * n_polys;
+void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t* lifted, const void* d, const void* c0, uint64_t ps_words,
+                               const GatherBundle& out, uint32_t batch, bool raised, hipStream_t s) {
+    if (batch == 0) return;
+    const uint32_t n_new = raised ? lv.lifted_map.n : 0, n_copy = c0 ? 2 * lv.ell : lv.ell;
     DigitRanges dg;
     dg.ndig = lv.ndig;
     for (uint32_t j = 0; j < kMaxDigits; ++j) {
         dg.lo[j] = j < lv.ndig ? lv.digit_lo[j] : 0;
         dg.hi[j] = j < lv.ndig ? lv.digit_hi[j] : 0;
     }
-    const double wb = out.hi ? 5.0 : 4.0;
-    ProfScope ps("gather_bundle_rows", ((8.0 + wb) * n_new + ((d_words32 ? 4.0 : 8.0) + wb) * n_own) * c->N, s);
-#define KS_LAUNCH(LOGR)                                                                                                              \
-    if (out.hi)                                                                                                                      \
-        hipLaunchKernelGGL((gather_bundle_rows<LOGR, true, uint64_t>), dim3((n_new + n_own) << (LOGR - 2)), dim3(64), 0, s, c->tw_fwd, \
-                           c->d_mod, lv.lifted_map, dg, lv.ell, lv.E, lifted, static_cast<const uint64_t*>(d), d_ps,                 \
-                           n_new << (LOGR - 2), out.lo, out.hi);                                                                     \
-    else                                                                                                                             \
-        hipLaunchKernelGGL((gather_bundle_rows<LOGR, false, uint32_t>), dim3((n_new + n_own) << (LOGR - 2)), dim3(64), 0, s, c->tw_fwd, \
-                           c->d_mod, lv.lifted_map, dg, lv.ell, lv.E, lifted, static_cast<const uint32_t*>(d), d_ps,                 \
-                           n_new << (LOGR - 2), out.lo, out.hi)
+    const double wb = out.hi ? 4.5 : 4.0;
+    ProfScope ps("gather_bundle_rows", ((8.0 + wb) * n_new + ((out.hi ? 8.0 : 4.0) + wb) * n_copy) * c->N * batch, s);
+    const uint32_t groups = c->N / 1024;
+#define KS_LAUNCH_BUNDLE(LOGR, GV, PK)                                                                                               \
+    hipLaunchKernelGGL((gather_bundle_rows<LOGR, GV, PK>), dim3((n_new + n_copy) * groups), dim3(64 * GV), 0, s, c->tw_fwd, c->d_mod,  \
+                       lv.lifted_map, dg, lv.ell, lv.E, lifted, d, c0, ps_words, batch, n_new * groups, out.lo, out.hi)
+#define KS_LAUNCH_G(LOGR, GV)                       \
+    if (out.hi) KS_LAUNCH_BUNDLE(LOGR, GV, true);   \
+    else KS_LAUNCH_BUNDLE(LOGR, GV, false)
+#define KS_LAUNCH(LOGR)                                   \
+    if (out.group == 8) { KS_LAUNCH_G(LOGR, 8); }         \
+    else if (out.group == 4) { KS_LAUNCH_G(LOGR, 4); }    \
+    else if (out.group == 2) { KS_LAUNCH_G(LOGR, 2); }    \
+    else { KS_LAUNCH_G(LOGR, 1); }
     KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
+#undef KS_LAUNCH_G
+#undef KS_LAUNCH_BUNDLE
 }
 
 // Polynomials per launch pair of a two-pass transform: the second pass of a group should find what the first pass wrote

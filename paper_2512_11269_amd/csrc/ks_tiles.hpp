@@ -18,7 +18,8 @@ struct DigitRanges {
 // Slot permutation of sigma_g (X -> X^g) on a bit-reversed evaluation vector: slot n holds the point
 // psi^(2 brv(n) + 1); sigma_g(a) evaluated there is a evaluated at that point raised to g.
 __device__ __forceinline__ uint32_t galois_source_slot(uint32_t n, uint32_t g, uint32_t logN) {
-    const uint32_t e = (g * (2u * (__brev(n) >> (32 - logN)) + 1u)) & ((2u << logN) - 1u);
+    // both factors are below 2^17: the full-rate 24-bit product has the bits that count
+    const uint32_t e = __umul24(g, 2u * (__brev(n) >> (32 - logN)) + 1u) & ((2u << logN) - 1u);
     return __brev((e - 1u) >> 1) >> (32 - logN);
 }
 

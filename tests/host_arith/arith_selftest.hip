@@ -69,6 +69,24 @@ static void check_prime(uint64_t p) {
         const i128 exact = ((i128)s2 << 24) + ((i128)s1 << 12) + s0;
         CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "combine3");
     }
+    // mac_exact: 128 products of the largest operands (256 with a lazy second factor) and smaller ones, reduced once
+    for (int rep = 0; rep < 3000; ++rep) {
+        double hi = kMacBias, lo = 0.0;
+        i128 exact = 0;
+        const int terms = rep % 3 == 0 ? 256 : 128;
+        for (int i = 0; i < terms; ++i) {
+            int64_t x = (int64_t)(rnd() % p), k = (int64_t)(rnd() % p);
+            if (rep % 5 == 0) x = p - 1;
+            if (rep % 3 == 0) k = rep % 5 == 0 ? (int64_t)(0.51 * p) * (rep & 1 ? -1 : 1) : k / 2 - (int64_t)(p / 4);
+            else if (rep % 5 == 0) k = p - 1;
+            mac_exact((double)x, (double)k, hi, lo);
+            exact += (i128)x * k;
+        }
+        CHECK(lo == floor(lo) && fabs(lo) <= 256.0 * 134217728.0, "mac_exact low sum");
+        CHECK((i128)(hi - kMacBias) + (i128)(int64_t)lo == exact, "mac_exact sum");
+        const double r = mac_reduce(hi, lo, m);
+        CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "mac_reduce");
+    }
     // split3: the pieces add up, have the stated granularity and magnitude; with the centred shifted factors, sixteen
     // sources accumulate exactly and reduce to sum y_i f_i mod p
     for (int rep = 0; rep < 20000; ++rep) {

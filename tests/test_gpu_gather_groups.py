@@ -1,0 +1,35 @@
+"""The rotation gathers lay the sources of 1, 2, 4 or 8 ciphertexts side by side (the batch rounded up): every group size, full
+and partly filled, and a batch of more than one group, with Galois elements of both kinds (powers of 5 permute the slots
+inside each half of a limb, -5^r swaps the halves), bit-exact against the plain-C reference."""
+
+import pytest
+import torch
+
+import ks_inputs
+import paper_2512_11269_amd as K
+from gpu_util import Setup, assert_equal, host, workspace
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", params=[12, 13], ids=lambda n: "N2^%d" % n)
+def st(request):
+    return Setup(request.param, 5, 2, 3)
+
+
+@pytest.mark.parametrize("batch", [1, 2, 3, 4, 5, 7, 8, 9, 11])
+def test_every_group_size(st, batch):
+    ell, all_ids = 4, list(range(st.L + st.K))
+    g = ks_inputs.galois_elements(st.logN, 2)
+    galois = [g[0], 2 * st.N - g[1], 2 * st.N - 1]
+    ct = st.uniform(4001, batch, (batch, 2), list(range(ell)))
+    keys = [st.uniform(4001, 50 + r, (st.ctx.dnum, 2), all_ids) for r in range(3)]
+    pts = [st.uniform(4001, 70 + r, (), all_ids) for r in range(4)]
+    ws = workspace(st.ctx, K.KS_OP_ROTATE_HOISTED, ell, batch, 4)
+    out = torch.empty((batch, 3, 2, ell, st.N), dtype=torch.int64, device="cuda")
+    K.ks_rotate_hoisted(st.ctx, ct, ell, galois, keys, out, ws)
+    assert_equal(out, st.ref.rotate_hoisted(host(ct), galois, [host(k) for k in keys], ell))
+    mac = torch.empty((batch, 2, ell, st.N), dtype=torch.int64, device="cuda")
+    K.ks_rotate_mac_hoisted(st.ctx, ct, ell, [galois[0], 1] + galois[1:], [keys[0], None] + keys[1:], pts, mac, ws)
+    assert_equal(mac, st.ref.rotate_mac_hoisted(host(ct), [galois[0], 1] + galois[1:], [host(keys[0]), None] + [host(k) for k in keys[1:]],
+                                                [host(w) for w in pts], ell))
