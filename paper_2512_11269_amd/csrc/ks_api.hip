@@ -142,8 +142,8 @@ extern "C" size_t ks_workspace_bytes(const ks_ctx* c, int op, uint32_t ell, uint
         }
         case KS_OP_HMULT_RELIN_RESCALE:
             if (ell < 2) return 0;
-            // d2 [bc][ell], (d0, d1) packed like the accumulator limbs, sum [bc][2][ell], last limb [2 bc], spread [2 bc][ell-1]
-            words += (uint64_t)bc * (ell + 2 * ell + 2 + 2 * (ell - 1)) * N + ks_ws_words(c, lv, bc).accq;
+            // d2 [bc][ell], (d0, d1) packed like the accumulator limbs
+            words += (uint64_t)bc * ell * N + ks_ws_words(c, lv, bc).accq;
             break;
         default: return 0;
     }
@@ -213,7 +213,7 @@ extern "C" int ntt_inv_u32(const ks_ctx* c, uint32_t* data, const uint32_t* mod_
 static int bconv_key(const ks_ctx* c, const uint32_t* src_ids, uint32_t n_src, const uint32_t* dst_ids, uint32_t n_dst,
                      std::vector<uint32_t>* key) {
     if (!c || !src_ids || !dst_ids) return KS_EINVAL;
-    if (n_src == 0 || n_src > (uint32_t)kMaxSrc || n_dst == 0 || n_dst > 255) return KS_EINVAL;
+    if (n_src == 0 || n_src > (uint32_t)kMaxLimbsIn || n_dst == 0 || n_dst > 255) return KS_EINVAL;
     key->push_back(n_src);
     for (uint32_t i = 0; i < n_src; ++i) {
         if (src_ids[i] >= c->M) return KS_EINVAL;
@@ -326,7 +326,7 @@ int ks::keyswitch_impl(const ks_ctx* c, const void* d, uint32_t ell, const void*
         const PackedDigits accq = packed_at(conv + w.conv, w.conv);
         const char* dc = static_cast<const char*>(d) + (uint64_t)b0 * d_ps * word;
         mod_up(c, lv, dc, d_ps, coeff, lifted, bc, s, words32);
-        launch_rows_inner_product(c, lv, dc, d_ps, lifted, evk, acc, bc, s, words32, words32, &accq, ell);
+        launch_rows_inner_product(c, lv, dc, d_ps, lifted, evk, acc, bc, s, words32, words32, accq);
         mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * out_bs * word, out_bs, nullptr, 0, 0, 1, bc, true, s, words32,
                  &accq);
     }
@@ -554,22 +554,20 @@ extern "C" int ks_bsgs_linear_transform_u32(const ks_ctx* c, const uint32_t* ct,
                      ws_bytes, stream, true);
 }
 
-// Division by P q_{ell-1} of acc + P addend in one conversion (ModDown merged with the rescale that would follow):
-// limb ell-1 joins the special limbs as a source, the targets are q_0..q_{ell-2}.  The fused inner product has already
-// run the row half of the inverse transform on the special limbs.
-// accq: the ciphertext limbs below ell-1 of the accumulators, packed (limb ell-1 is a conversion source and stays in acc).
-// addend: [b][2][ell][N] packed.
-static void mod_down_merged(const ks_ctx* c, const Level& lv, uint64_t* acc, uint64_t* conv, void* out, uint64_t out_bs,
-                            const PackedDigits& addend, uint32_t bc, hipStream_t s, bool out_words32, const PackedDigits* accq) {
+// Division by P q_{ell-1} of acc + P addend in one conversion to q_0..q_{ell-2}, limb ell-1 joining the special limbs as a
+// source.  merged: ModDown and rescale merged (floor throughout); otherwise floor(/ P), then round(/ q_{ell-1}).  The fused
+// inner product has already added the dropped limb's addend and run the row half of the inverse transform on the sources.
+// accq: the ciphertext limbs below ell-1 of the accumulators, packed.  addend: [b][2][ell][N] packed.
+static void mod_down_drop(const ks_ctx* c, const Level& lv, uint64_t* acc, uint64_t* conv, void* out, uint64_t out_bs,
+                          const PackedDigits& addend, uint32_t bc, hipStream_t s, bool merged, bool out_words32, const PackedDigits& accq) {
     const uint64_t N = c->N, acc_ps = (uint64_t)lv.E * N, conv_ps = (uint64_t)lv.ell * N;
-    launch_add_scaled_limb(c, acc, acc_ps, addend, lv.ell, lv.ell - 1, lv.Pmod_last, bc, s);
-    launch_ntt_inv_rows(c, lv.last_map, XformIO{acc, acc, acc_ps, acc_ps, 2 * bc}, s);
-    launch_ntt_inv_cols(c, lv.merged_map, acc, acc_ps, 2 * bc, lv.d_merged_scale, true, true, s);
+    launch_ntt_inv_cols(c, lv.drop_map, acc, acc_ps, 2 * bc, merged ? lv.d_merged_scale : lv.d_rescale_scale, true, true, s);
+    if (!merged) launch_rescale_remainder(c, lv, acc, 2 * bc, s);
     const uint32_t n_src = c->K + 1, n_dst = lv.ell - 1;
     const double ops = (double)n_src * n_dst * 4.5 + n_dst * (3.0 + 4.0 * (c->logN - 8));
-    launch_bconv_ntt_cols(c, lv.merged, n_src + n_dst, acc, acc_ps, conv, conv_ps, 2 * bc, s, ops);
+    launch_bconv_ntt_cols(c, merged ? lv.merged : lv.rescale, n_src + n_dst, acc, acc_ps, conv, conv_ps, 2 * bc, s, ops);
     const FinishScale fs{lv.d_Dinv, lv.d_qlinv, n_dst};
-    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 2ull * lv.ell * N, 2, 1, bc, s, &fs, out_words32, accq, &addend);
+    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 2ull * lv.ell * N, 2, 1, bc, s, &fs, out_words32, &accq, &addend);
 }
 
 // cta, ctb, rlk and out in 64-bit words, or all four in 32-bit words (words32); the tensor product and everything after it
@@ -586,10 +584,6 @@ static int hmult_impl(const ks_ctx* c, const void* cta, const void* ctb, uint32_
     if (merged && !lv.merged.d_plans) return KS_EINVAL;  // K + 1 sources exceed what one conversion takes
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint64_t N = c->N, ct_bs = 2ull * ell * N, out_bs = 2ull * (ell - 1) * N, word = words32 ? 4 : 8;
-    LimbMap one;
-    one.n = 1;
-    one.off[0] = 0;
-    one.mod[0] = (uint8_t)(ell - 1);
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
         const KsWorkspace w = ks_ws_words(c, lv, bc);
@@ -601,24 +595,12 @@ static int hmult_impl(const ks_ctx* c, const void* cta, const void* ctb, uint32_
         uint64_t* d2 = conv + w.conv + w.accq;                  // [bc][ell][N], the polynomial that is key-switched
         const uint64_t d2_ps = (uint64_t)ell * N;
         const PackedDigits dq = packed_at(d2 + (uint64_t)bc * d2_ps, w.conv);   // (d0, d1): [bc][2][ell][N] packed
-        uint64_t* sum = d2 + (uint64_t)bc * d2_ps + w.accq;     // [bc][2][ell][N]
-        uint64_t* last = sum + (uint64_t)bc * ct_bs;            // [2 bc][N]
-        uint64_t* spread = last + (uint64_t)bc * 2 * N;         // [2 bc][ell-1][N]
         char* oc = static_cast<char*>(out) + (uint64_t)b0 * out_bs * word;
         launch_tensor_product(c, static_cast<const char*>(cta) + (uint64_t)b0 * ct_bs * word,
                               static_cast<const char*>(ctb) + (uint64_t)b0 * ct_bs * word, d2, dq, ell, bc, s, words32);
         mod_up(c, lv, d2, d2_ps, coeff, lifted, bc, s);
-        launch_rows_inner_product(c, lv, d2, d2_ps, lifted, rlk, acc, bc, s, false, words32, &accq, merged ? ell - 1 : ell);
-        if (merged) {
-            mod_down_merged(c, lv, acc, conv, oc, out_bs, dq, bc, s, words32, &accq);
-            continue;
-        }
-        mod_down(c, lv, acc, conv, sum, ct_bs, nullptr, ct_bs, 2, 1, bc, true, s, false, &accq, &dq);
-        // rescale both components: inverse transform of the last limb, centred remainder to every q_i, forward
-        // transform, subtract and divide
-        launch_ntt_inv_rows(c, one, XformIO{sum + (uint64_t)(ell - 1) * N, last, (uint64_t)ell * N, N, 2 * bc}, s);
-        launch_ntt_inv_cols(c, one, last, N, 2 * bc, c->d_ninv, false, true, s);   // canonical doubles
-        launch_rescale_fused(c, lv, sum, last, spread, oc, 2 * bc, s, words32);
+        launch_rows_inner_product(c, lv, d2, d2_ps, lifted, rlk, acc, bc, s, false, words32, accq, &dq);
+        mod_down_drop(c, lv, acc, conv, oc, out_bs, dq, bc, s, merged, words32, accq);
     }
     if (merged) return finish(words32 ? "hmult_relin_rescale_merged_u32" : "hmult_relin_rescale_merged");
     return finish(words32 ? "hmult_relin_rescale_u32" : "hmult_relin_rescale");

@@ -76,7 +76,8 @@ static uint32_t h_brv(uint32_t k, uint32_t bits) {
 static Mod make_mod(uint64_t m) { return Mod{(double)m, 1.0 / (double)m}; }
 
 void fill_bconv_plan(const ks_ctx* c, BConvPlan* plan, const uint32_t* src_ids, const uint16_t* src_limb, uint32_t n_src,
-                     const uint32_t* dst_ids, const uint16_t* dst_limb, uint32_t n_dst, uint32_t shape_src) {
+                     const uint32_t* dst_ids, const uint16_t* dst_limb, uint32_t n_dst, uint32_t shape_src, uint32_t n_extra) {
+    const uint32_t n_basis = n_src - n_extra;
     memset(plan, 0, sizeof(BConvPlan));
     if (shape_src < n_src) shape_src = n_src;
     plan->n_src = n_src;
@@ -87,7 +88,7 @@ void fill_bconv_plan(const ks_ctx* c, BConvPlan* plan, const uint32_t* src_ids, 
     for (uint32_t i = 0; i < n_src; ++i) {
         const uint64_t si = c->mod[src_ids[i]];
         uint64_t prod = 1;
-        for (uint32_t k = 0; k < n_src; ++k)
+        for (uint32_t k = 0; k < n_basis; ++k)
             if (k != i) prod = h_mulmod(prod, c->mod[src_ids[k]] % si, si);
         plan->src_limb[i] = src_limb[i];
         plan->src_mod[i] = make_mod(si);
@@ -106,7 +107,7 @@ void fill_bconv_plan(const ks_ctx* c, BConvPlan* plan, const uint32_t* src_ids, 
         plan->trec[t].limb = dst_limb[t];
         for (uint32_t i = 0; i < n_src; ++i) {
             uint64_t prod = 1 % mt;
-            for (uint32_t k = 0; k < n_src; ++k)
+            for (uint32_t k = 0; k < n_basis; ++k)
                 if (k != i) prod = h_mulmod(prod, c->mod[src_ids[k]] % mt, mt);
             // factors against the pieces of a source residue: cut at 12 and 24 bits, or at 16 bits when every modulus is
             // below 2^32 (split3 / split2)
@@ -221,7 +222,10 @@ extern "C" int ks_ctx_destroy(ks_ctx* c) {
         (void)hipFree(lv.d_qlinv);
         (void)hipFree(lv.d_modup_scale);
         (void)hipFree(lv.merged.d_plans);
+        (void)hipFree(lv.rescale.d_plans);
         (void)hipFree(lv.d_merged_scale);
+        (void)hipFree(lv.d_rescale_scale);
+        (void)hipFree(lv.d_pinv_last);
         (void)hipFree(lv.d_Dinv);
     }
     for (auto& kv : c->bconv_cache) (void)hipFree(kv.second.d_plans);
@@ -237,8 +241,8 @@ extern "C" int ks_ctx_create(ks_ctx** out, uint32_t logN, uint32_t L, uint32_t K
     if (L == 0 || !q || (K > 0 && !p) || L + K > 255 || dnum == 0 || dnum > L) return KS_EINVAL;
     const uint32_t N = 1u << logN, M = L + K;
     const uint32_t alpha = (L + dnum - 1) / dnum;
-    if (K > (uint32_t)kMaxSrc) return KS_EINVAL;
-    if (K > 0 && alpha > (uint32_t)kMaxSrc) return KS_EINVAL;
+    if (K > (uint32_t)kMaxLimbsIn) return KS_EINVAL;
+    if (K > 0 && alpha > (uint32_t)kMaxLimbsIn) return KS_EINVAL;
     if ((L + alpha - 1) / alpha > (uint32_t)kMaxDigits) return KS_EINVAL;
     if (K > 0 && ((L + alpha - 1) / alpha) * M > (uint32_t)kMaxLimbs) return KS_EINVAL;
 
@@ -398,47 +402,57 @@ extern "C" int ks_ctx_create(ks_ctx** out, uint32_t logN, uint32_t L, uint32_t K
             fill_bconv_plan(c, &down, src_ids, src_limb, K, dst_ids.data(), dst_limb.data(), ell);
             CK(upload_plans(&down, 1, K, &lv.moddown));
 
-            if (ell >= 2 && K + 1 <= (uint32_t)kMaxSrc) {
-                BConvPlan merged;
+            if (ell >= 2) {
                 uint32_t m_ids[kMaxSrc];
                 uint16_t m_limb[kMaxSrc];
-                lv.merged_map.n = K + 1;
+                lv.drop_map.n = K + 1;
                 for (uint32_t k = 0; k <= K; ++k) {
                     m_ids[k] = k < K ? L + k : ell - 1;
                     m_limb[k] = (uint16_t)(k < K ? ell + k : ell - 1);
-                    lv.merged_map.off[k] = m_limb[k];
-                    lv.merged_map.mod[k] = (uint8_t)m_ids[k];
+                    lv.drop_map.off[k] = m_limb[k];
+                    lv.drop_map.mod[k] = (uint8_t)m_ids[k];
                 }
-                lv.last_map.n = 1;
-                lv.last_map.off[0] = (uint16_t)(ell - 1);
-                lv.last_map.mod[0] = (uint8_t)(ell - 1);
-                fill_bconv_plan(c, &merged, m_ids, m_limb, K + 1, dst_ids.data(), dst_limb.data(), ell - 1);
-                CK(upload_plans(&merged, 1, K + 1, &lv.merged));
-                std::vector<double> sc(K + 1), dinv(ell - 1);
-                for (uint32_t k = 0; k <= K; ++k) {
-                    const uint64_t sk = c->mod[m_ids[k]];
-                    sc[k] = (double)h_mulmod((uint64_t)merged.src_inv[k], h_invmod(N % sk, sk), sk);
-                }
+                auto upload = [](double** dst, const std::vector<double>& v) {
+                    const hipError_t e = hipMalloc(dst, sizeof(double) * v.size());
+                    return e != hipSuccess ? e : hipMemcpy(*dst, v.data(), sizeof(double) * v.size(), hipMemcpyHostToDevice);
+                };
                 const uint64_t qlast = c->mod[ell - 1];
-                uint64_t pl = 1;
-                for (uint32_t k = 0; k < K; ++k) pl = h_mulmod(pl, c->mod[L + k] % qlast, qlast);
-                lv.Pmod_last = (double)pl;
+                uint64_t P_last = 1;
+                std::vector<double> pinv(K);
+                for (uint32_t k = 0; k < K; ++k) {
+                    P_last = h_mulmod(P_last, c->mod[L + k] % qlast, qlast);
+                    pinv[k] = (double)h_invmod(c->mod[L + k] % qlast, qlast);
+                }
+                lv.Pmod_last = (double)P_last;
+                CK(upload(&lv.d_pinv_last, pinv));
+                BConvPlan plan;
+                std::vector<double> sc(K + 1);
+                auto scales = [&]() {
+                    for (uint32_t k = 0; k <= K; ++k) {
+                        const uint64_t sk = c->mod[m_ids[k]];
+                        sc[k] = (double)h_mulmod((uint64_t)plan.src_inv[k], h_invmod(N % sk, sk), sk);
+                    }
+                };
+                fill_bconv_plan(c, &plan, m_ids, m_limb, K + 1, dst_ids.data(), dst_limb.data(), ell - 1, 0, 1);
+                CK(upload_plans(&plan, 1, K + 1, &lv.rescale));
+                scales();
+                CK(upload(&lv.d_rescale_scale, sc));
+                if (K + 1 <= (uint32_t)kMaxLimbsIn) {
+                    fill_bconv_plan(c, &plan, m_ids, m_limb, K + 1, dst_ids.data(), dst_limb.data(), ell - 1);
+                    CK(upload_plans(&plan, 1, K + 1, &lv.merged));
+                    scales();
+                    CK(upload(&lv.d_merged_scale, sc));
+                }
+                std::vector<double> dinv(ell - 1), ql(ell - 1);
                 for (uint32_t i = 0; i + 1 < ell; ++i) {
                     const uint64_t qi = c->mod[i];
                     uint64_t D = qlast % qi;
                     for (uint32_t k = 0; k < K; ++k) D = h_mulmod(D, c->mod[L + k] % qi, qi);
                     dinv[i] = (double)h_invmod(D, qi);
+                    ql[i] = (double)h_invmod(qlast % qi, qi);
                 }
-                CK(hipMalloc(&lv.d_merged_scale, sizeof(double) * (K + 1)));
-                CK(hipMemcpy(lv.d_merged_scale, sc.data(), sizeof(double) * (K + 1), hipMemcpyHostToDevice));
-                CK(hipMalloc(&lv.d_Dinv, sizeof(double) * (ell - 1)));
-                CK(hipMemcpy(lv.d_Dinv, dinv.data(), sizeof(double) * (ell - 1), hipMemcpyHostToDevice));
-            }
-            if (ell >= 2) {
-                std::vector<double> ql(ell - 1);
-                for (uint32_t i = 0; i + 1 < ell; ++i) ql[i] = (double)h_invmod(c->mod[ell - 1] % c->mod[i], c->mod[i]);
-                CK(hipMalloc(&lv.d_qlinv, sizeof(double) * (ell - 1)));
-                CK(hipMemcpy(lv.d_qlinv, ql.data(), sizeof(double) * (ell - 1), hipMemcpyHostToDevice));
+                CK(upload(&lv.d_Dinv, dinv));
+                CK(upload(&lv.d_qlinv, ql));
             }
         }
     }

@@ -79,19 +79,19 @@ KS_HD void mac_exact(double x, double k, double& hi, double& lo) {
     lo += __builtin_fma(x, k, d);
     hi = t;
 }
-// The sum of a mac_exact accumulation as a lazy residue (|r| <= 0.51 p).  For products of residues of p the quotient
-// estimate of the high part stays below 256 p < 2^44, so it is off by far less than one and the FMA is exact.
+// The sum of a mac_exact accumulation as a lazy residue (|r| <= 0.51 p).  With |x| <= 2^36 and |k| <= p the quotient
+// of the high part stays below 2^44 whatever p is, so its estimate is off by far less than one and the FMA is exact.
 KS_HD double mac_reduce(double hi, double lo, Mod m) {
     const double s = hi - kMacBias;
     const double q = __builtin_rint(s * m.pinv);
     return reduce_lazy(__builtin_fma(-q, m.p, s) + lo, m);
 }
 
-// Split an integer-valued 0 <= y < 2^36 into y = y2 + y1 + y0 with y2 a multiple of 2^24 (0 <= y2 <= 2^36), y1 a
+// Split an integer-valued |y| < 2^36 into y = y2 + y1 + y0 with y2 a multiple of 2^24 (|y2| <= 2^36), y1 a
 // multiple of 2^12 (|y1| <= 2^23) and |y0| <= 2^11, by rounding to nearest at the two granularities (adding and
 // subtracting 1.5 * 2^(52 + g) rounds to a multiple of 2^g).  Six additions, no products.
 // Use: with factors f_k = centred([f * 2^(12 k)]_t) * 2^(-12 k), |f_k| * 2^(12 k) <= 2^35, the sum
-// y2 f_2 + y1 f_1 + y0 f_0 is an integer congruent to y f modulo t and at most 2^48 in magnitude, so up to sixteen
+// y2 f_2 + y1 f_1 + y0 f_0 is an integer congruent to y f modulo t and at most 2^48 in magnitude, so up to seventeen
 // such triples accumulate exactly in one double: a conversion costs three FMAs per source and target, the split is
 // shared by all targets of the source, and one reduction per target finishes it.
 KS_HD void split3(double y, double& y2, double& y1, double& y0) {
@@ -102,10 +102,10 @@ KS_HD void split3(double y, double& y2, double& y1, double& y0) {
     y0 = rem - y1;
 }
 
-// The same for 0 <= y < 2^32 (contexts whose moduli are all below 2^32, i.e. every context the 32-bit-word entry points
+// The same for |y| < 2^32 (contexts whose moduli are all below 2^32, i.e. every context the 32-bit-word entry points
 // accept, the paper's 28-bit primes included): y = y1 + y0 with y1 a multiple of 2^16 and |y0| <= 2^15.  With
 // f_k = centred([f * 2^(16 k)]_t) * 2^(-16 k), |f_k| * 2^(16 k) <= 2^31, the sum y1 f_1 + y0 f_0 is an integer congruent to
-// y f modulo t and below 1.5 * 2^47 in magnitude: sixteen accumulate exactly (below 2^53), at two FMAs per source and
+// y f modulo t and below 1.5 * 2^47 in magnitude: seventeen accumulate exactly (below 2^53), at two FMAs per source and
 // target and three additions per split.
 KS_HD void split2(double y, double& y1, double& y0) {
     constexpr double kRound16 = 0x1.8p68;

@@ -420,26 +420,4 @@ void launch_tensor_product(const ks_ctx* c, const void* cta, const void* ctb, ui
                            static_cast<const uint64_t*>(cta), static_cast<const uint64_t*>(ctb), d2, dq.lo, dq.hi);
 }
 
-// acc[b][comp][limb] = (acc + mul * addend[b][comp][limb]) mod q_limb, canonical: the one ciphertext limb that joins the
-// special limbs as a conversion source when ModDown and rescale are merged.  The addend is packed ([b][2][ell][N]).
-__global__ __launch_bounds__(256) void add_scaled_limb_kernel(const Mod* __restrict__ mods, uint32_t limb, double mul, uint32_t ell,
-                                                              uint32_t N, uint64_t* __restrict__ acc, uint64_t acc_ps,
-                                                              const uint32_t* __restrict__ addend_lo,
-                                                              const uint8_t* __restrict__ addend_hi) {
-    const Mod m = mods[limb];
-    const uint64_t n = blockIdx.x * 256 + threadIdx.x;
-    uint64_t* a = acc + (uint64_t)blockIdx.z * acc_ps + (uint64_t)limb * N + n;
-    const uint64_t e = ((uint64_t)blockIdx.z * ell + limb) * N + n;   // blockIdx.z = 2 b + comp
-    const double d = u64_to_f64((uint64_t)addend_hi[e] << 32 | addend_lo[e]);
-    *a = f64_to_u64(canon(reduce_lazy(u64_to_f64(*a) + mulmod_lazy(d, mul, m), m), m));
-}
-
-void launch_add_scaled_limb(const ks_ctx* c, uint64_t* acc, uint64_t acc_ps, const PackedDigits& addend, uint32_t ell, uint32_t limb,
-                            double mul, uint32_t batch, hipStream_t s) {
-    if (batch == 0) return;
-    ProfScope ps("add_scaled_limb", (double)batch * 2 * (16 + 5) * c->N, s);
-    hipLaunchKernelGGL(add_scaled_limb_kernel, dim3(c->N / 256, 1, batch * 2), dim3(256), 0, s, c->d_mod, limb, mul, ell, c->N, acc,
-                       acc_ps, addend.lo, addend.hi);
-}
-
 }  // namespace ks

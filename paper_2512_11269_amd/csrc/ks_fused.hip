@@ -250,8 +250,9 @@ __global__ __launch_bounds__(64, PREFETCH ? 2 : 0) void rows_inner_product(TwTab
                                                          const WD* __restrict__ d, uint64_t d_ps,
                                                          const uint64_t* __restrict__ lifted, const WK* __restrict__ evk,
                                                          uint64_t* __restrict__ acc, uint32_t* __restrict__ accq_lo,
-                                                         uint8_t* __restrict__ accq_hi, uint32_t packed_limbs, uint32_t batch,
-                                                         uint32_t special_first) {
+                                                         uint8_t* __restrict__ accq_hi, const uint32_t* __restrict__ drop_lo,
+                                                         const uint8_t* __restrict__ drop_hi, double drop_mul,
+                                                         uint32_t packed_limbs, uint32_t batch, uint32_t special_first) {
     constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R;
     __shared__ double lds[4 * kRowPitch];
     __shared__ double lds_ta[4 * 16];
@@ -270,16 +271,16 @@ __global__ __launch_bounds__(64, PREFETCH ? 2 : 0) void rows_inner_product(TwTab
     const uint32_t pos = !special_first ? slot_pos : slot_pos < n_special ? ell + slot_pos : slot_pos - n_special;
     task_rows_inner_product<LOG_R, WD, WK, PREFETCH>(tw, twi, mods, dg, ell, E, L, M, d + (uint64_t)b * d_ps, lifted + (uint64_t)b * dg.ndig * E * N, evk,
                                       acc + (uint64_t)b * 2 * E * N, accq_lo + (uint64_t)b * 2 * ell * N,
-                                      accq_hi + (uint64_t)b * 2 * ell * N, packed_limbs, pos, rg, threadIdx.x, lds, lds_ta);
+                                      accq_hi + (uint64_t)b * 2 * ell * N, drop_lo + (uint64_t)b * 2 * ell * N,
+                                      drop_hi + (uint64_t)b * 2 * ell * N, drop_mul, packed_limbs, pos, rg, threadIdx.x, lds, lds_ta);
 }
 
 void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint64_t* lifted,
                                const void* evk, uint64_t* acc, uint32_t batch, hipStream_t s, bool d_words32, bool key_words32,
-                               const PackedDigits* accq, uint32_t packed_limbs) {
+                               const PackedDigits& accq, const PackedDigits* drop_addend) {
     if (batch == 0) return;
-    if (!accq) packed_limbs = 0;
-    uint32_t* accq_lo = accq ? accq->lo : nullptr;
-    uint8_t* accq_hi = accq ? accq->hi : nullptr;
+    const uint32_t packed_limbs = drop_addend ? lv.ell - 1 : lv.ell;
+    const PackedDigits drop = drop_addend ? *drop_addend : accq;  // never read without a dropped limb
     DigitRanges dg;
     dg.ndig = lv.ndig;
     for (uint32_t j = 0; j < kMaxDigits; ++j) {
@@ -301,8 +302,8 @@ void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, 
     const bool prefetch = grid.x > 2048;
 #define KS_LAUNCH_IP(LOGR, WDT, WKT, PF)                                                                                           \
     hipLaunchKernelGGL((rows_inner_product<LOGR, WDT, WKT, PF>), grid, block, 0, s, c->tw_fwd, c->tw_inv, c->d_mod, dg, lv.ell, lv.E, c->L, \
-                       c->M, static_cast<const WDT*>(d), d_ps, lifted, static_cast<const WKT*>(evk), acc, accq_lo, accq_hi, packed_limbs, batch,   \
-                       prefetch ? 0u : 1u)
+                       c->M, static_cast<const WDT*>(d), d_ps, lifted, static_cast<const WKT*>(evk), acc, accq.lo, accq.hi, drop.lo, drop.hi,       \
+                       lv.Pmod_last, packed_limbs, batch, prefetch ? 0u : 1u)
 #define KS_LAUNCH(LOGR)                                                          \
     if (d_words32 && key_words32) KS_LAUNCH_IP(LOGR, uint32_t, uint32_t, false); \
     else if (key_words32) KS_LAUNCH_IP(LOGR, uint64_t, uint32_t, false);         \
@@ -429,85 +430,30 @@ void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t
 }
 
 // ------------------------------------------------------------------------------------------------
-// Rescale, first half: the centred remainder of the dropped limb (coefficient domain, canonical doubles) is
-// reduced modulo q_i and sent straight through the column half of NTT_{q_i}; the "spread" limbs never exist
-// in coefficient form.  last: [polys][N]; out: [polys][ell-1][N] raw doubles.
+// Rescale.  The rescale's remainder r = (sum - conv)[ell-1] P^-1 (coefficient domain, centred) has to be subtracted from every
+// other limb after the division by P: (acc_i - conv_i) P^-1 + d_i - r, times q_{ell-1}^-1.  As P r joins conv_i before the
+// forward transform, it costs one more source of that conversion, and the rescale needs no transforms of its own (a
+// forward transform and two more passes over every limb: 290 of 1310 us per 8 multiplications at L = 35).
+// With y_k = [x_k (P / p_k)^-1]_{p_k} the converted special part of limb ell-1 times P^-1 is sum_k y_k p_k^-1.
+// One thread per coefficient, K + 1 limbs read and one written.
 // ------------------------------------------------------------------------------------------------
-template <int LOG_R>
-__global__ __launch_bounds__(256) void rescale_cols(const double* __restrict__ tw, const Mod* __restrict__ mods, uint32_t ell,
-                                                    const uint64_t* __restrict__ last, uint64_t* __restrict__ out) {
-    constexpr uint32_t N = 256u << LOG_R, TILES = 1u << (LOG_R - 4), TC = 256 / TILES;
-    __shared__ double lds[LOG_R > 4 ? 4096 : 1];
-    const uint32_t tid = threadIdx.x, tile = blockIdx.x, i = blockIdx.y, p = blockIdx.z;
-    const Mod m = mods[i];
-    const double ql = mods[ell - 1].p, half = (ql - 1.0) * 0.5;
-    const uint32_t c = tid & (TC - 1), r0 = tid / TC, col = tile * TC + c;
-    const uint64_t* src = last + (uint64_t)p * N;
-    double v[16];
-    PassTwiddles t;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = load_f64(src + col_row_strided<LOG_R>(r0, k) * 256 + col);
-    load_col_twiddles<LOG_R>(t, tw + (size_t)i * N, r0);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = reduce_lazy(v[k] > half ? v[k] - ql : v[k], m);
-    col_fwd_core<LOG_R>(v, t, c, r0, lds, m);
-    uint64_t* dst = out + ((uint64_t)p * (ell - 1) + i) * N;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) store_f64(dst + col_row_grouped<LOG_R>(r0, k) * 256 + col, v[k]);
+__global__ __launch_bounds__(256) void rescale_remainder_kernel(Mod m, const double* __restrict__ pinv, uint32_t ell, uint32_t K,
+                                                                uint32_t N, uint64_t* __restrict__ acc) {
+    const uint32_t n = blockIdx.x * 256 + threadIdx.x;
+    uint64_t* last = acc + ((uint64_t)blockIdx.y * (ell + K) + ell - 1) * N + n;
+    double hi = kMacBias, lo = 0.0;
+#pragma unroll 4
+    for (uint32_t k = 0; k < K; ++k) mac_exact(load_f64(last + (uint64_t)(k + 1) * N), pinv[k], hi, lo);
+    const double r = canon(reduce_lazy(load_f64(last) - mac_reduce(hi, lo, m), m), m);
+    store_f64(last, r > (m.p - 1.0) * 0.5 ? r - m.p : r);
 }
 
-// Rescale, second half: row half of the forward transform, then out = (x - w) * q_{ell-1}^-1 mod q_i.
-// x: [polys][ell][N] canonical; spread: [polys][ell-1][N] raw doubles; out: [polys][ell-1][N] canonical.
-template <int LOG_R, typename W>
-__global__ __launch_bounds__(64) void rows_rescale_finish(TwTables tw, const Mod* __restrict__ mods,
-                                                          const double* __restrict__ qlinv, uint32_t ell,
-                                                          const uint64_t* __restrict__ x, const uint64_t* __restrict__ spread,
-                                                          W* __restrict__ out) {
-    constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R;
-    __shared__ double lds[4 * kRowPitch];
-    const uint32_t tid = threadIdx.x, rg = blockIdx.x, i = blockIdx.y, p = blockIdx.z;
-    const Mod m = mods[i];
-    const double scale = qlinv[i];
-    const uint32_t j0 = tid & 15, rr = tid >> 4, row = rg * 4 + rr;
-    const uint32_t off = row * 256 + j0;
-    const uint64_t* src = spread + ((uint64_t)p * (ell - 1) + i) * N + off;
-    const uint64_t* xp = x + ((uint64_t)p * ell + i) * N + off;
-    W* op = out + ((uint64_t)p * (ell - 1) + i) * N + off;
-    double w[16], a[16];
-    PassTwiddles t;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) w[k] = load_f64(src + 16 * k);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) a[k] = u64_to_f64(xp[16 * k]);
-    load_row_twiddles(t, tw, i, N, R + row, j0, m);
-    row_fwd_core(w, t, j0, lds + rr * kRowPitch, m);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) op[16 * k] = f64_to_word<W>(canon(mulmod_lazy(a[k] - w[k], scale, m), m));
-}
-
-void launch_rescale_fused(const ks_ctx* c, const Level& lv, const uint64_t* x, const uint64_t* last, uint64_t* spread,
-                          void* out, uint32_t n_polys, hipStream_t s, bool out_words32) {
-    if (n_polys == 0 || lv.ell < 2) return;
-    const uint32_t nl = lv.ell - 1;
-    {
-        ProfScope ps("rescale_cols", ((double)n_polys * (1 + nl)) * c->N * 8.0, s);
-#define KS_LAUNCH(LOGR) \
-    hipLaunchKernelGGL(rescale_cols<LOGR>, dim3(1u << (LOGR - 4), nl, n_polys), dim3(256), 0, s, c->d_tw_fwd, c->d_mod, lv.ell, last, spread)
-        KS_FOR_LOG_R(c->logN, KS_LAUNCH)
-#undef KS_LAUNCH
-    }
-    {
-        ProfScope ps("rows_rescale_finish", (double)n_polys * nl * (out_words32 ? 2.5 : 3.0) * c->N * 8.0, s);
-#define KS_LAUNCH(LOGR)                                                                                                                      \
-    if (out_words32)                                                                                                                         \
-        hipLaunchKernelGGL((rows_rescale_finish<LOGR, uint32_t>), dim3(1u << (LOGR - 2), nl, n_polys), dim3(64), 0, s, c->tw_fwd, c->d_mod,   \
-                           lv.d_qlinv, lv.ell, x, spread, static_cast<uint32_t*>(out));                                                      \
-    else                                                                                                                                     \
-        hipLaunchKernelGGL((rows_rescale_finish<LOGR, uint64_t>), dim3(1u << (LOGR - 2), nl, n_polys), dim3(64), 0, s, c->tw_fwd, c->d_mod,   \
-                           lv.d_qlinv, lv.ell, x, spread, static_cast<uint64_t*>(out))
-        KS_FOR_LOG_R(c->logN, KS_LAUNCH)
-#undef KS_LAUNCH
-    }
+void launch_rescale_remainder(const ks_ctx* c, const Level& lv, uint64_t* acc, uint32_t n_polys, hipStream_t s) {
+    if (n_polys == 0) return;
+    ProfScope ps("rescale_remainder", (double)n_polys * (c->K + 2) * c->N * 8.0, s);
+    const uint64_t q = c->mod[lv.ell - 1];
+    hipLaunchKernelGGL(rescale_remainder_kernel, dim3(c->N / 256, n_polys), dim3(256), 0, s, Mod{(double)q, 1.0 / (double)q}, lv.d_pinv_last,
+                       lv.ell, c->K, c->N, acc);
 }
 
 }  // namespace ks

@@ -13,7 +13,8 @@
 
 namespace ks {
 
-constexpr int kMaxSrc = 16;     // source limbs of one base conversion (alpha or K)
+constexpr int kMaxLimbsIn = 16; // source limbs a caller may ask for (alpha, K, bconv)
+constexpr int kMaxSrc = 18;     // source slots of a conversion plan: kMaxLimbsIn, the dropped limb of a rescale, one of padding
 constexpr int kMfmaSlots = 6;   // 16-byte operand slots of the matrix-core conversion: 3 instructions x 2 lane halves, 3 sources each
 constexpr int kMfmaPlanes = 5;  // signed base-256 digits of a 36-bit residue or factor
 constexpr int kMaxDst = 256;    // target limbs of one base conversion
@@ -92,11 +93,15 @@ struct Level {
     uint32_t digit_lo[kMaxDigits], digit_hi[kMaxDigits];
     double* d_qlinv = nullptr;             // [ell-1] device: q_{ell-1}^-1 mod q_i (rescale)
     double* d_modup_scale = nullptr;       // [ell] device: N^-1 (D_j / q_i)^-1 mod q_i, j = digit of limb i
-    // ModDown merged with rescale: one conversion from {p_0..p_{K-1}, q_{ell-1}} (product D) to q_0..q_{ell-2}
-    PlanSet merged;                        // d_plans == nullptr when unavailable (ell < 2 or K + 1 sources too many)
-    LimbMap merged_map;                    // the K special limbs and limb ell-1 inside an [E][N] accumulator
-    LimbMap last_map;                      // limb ell-1 alone
-    double* d_merged_scale = nullptr;      // [K+1] device: N^-1 (D / s)^-1 mod s, s in merged_map order
+    // Division by P followed by the rescale (ell >= 2), both in one conversion to q_0..q_{ell-2} with limb ell-1 as a further
+    // source.  merged: ModDown and rescale merged, a conversion from the basis {p_0..p_{K-1}, q_{ell-1}} (product D = P q_{ell-1}).
+    // rescale: the sum of the conversion P -> q_i and P times the centred remainder of the dropped limb.
+    PlanSet merged;                        // d_plans == nullptr when unavailable (K + 1 sources exceed kMaxLimbsIn)
+    PlanSet rescale;
+    LimbMap drop_map;                      // the K special limbs and limb ell-1 inside an [E][N] accumulator
+    double* d_merged_scale = nullptr;      // [K+1] device: N^-1 (D / s)^-1 mod s, s in drop_map order
+    double* d_rescale_scale = nullptr;     // [K+1] device: N^-1 (P / p_k)^-1 mod p_k, then N^-1 P^-1 mod q_{ell-1}
+    double* d_pinv_last = nullptr;         // [K] device: p_k^-1 mod q_{ell-1}
     double* d_Dinv = nullptr;              // [ell-1] device: D^-1 mod q_i
     double Pmod_last = 0.0;                // P mod q_{ell-1}
 };
@@ -131,9 +136,10 @@ uint64_t h_mulmod(uint64_t a, uint64_t b, uint64_t m);
 uint64_t h_powmod(uint64_t a, uint64_t e, uint64_t m);
 uint64_t h_invmod(uint64_t a, uint64_t m);
 // shape_src: the source count that fixes the operand-slot layout of the matrix-core tables (all plans of one launch must
-// agree on it); 0 = n_src.
+// agree on it); 0 = n_src.  The last n_extra sources are not part of the basis: their factor is the product of all moduli
+// of the others, which they do not enter.
 void fill_bconv_plan(const ks_ctx* c, BConvPlan* plan, const uint32_t* src_ids, const uint16_t* src_limb, uint32_t n_src,
-                     const uint32_t* dst_ids, const uint16_t* dst_limb, uint32_t n_dst, uint32_t shape_src = 0);
+                     const uint32_t* dst_ids, const uint16_t* dst_limb, uint32_t n_dst, uint32_t shape_src = 0, uint32_t n_extra = 0);
 
 // thread-local HIP error text
 void set_hip_error(hipError_t e, const char* where);
@@ -202,10 +208,12 @@ struct PackedDigits {
 };
 // Fused row half of the forward transform of the raised digits + inner product with the key.
 // d_words32 / key_words32: d / the key hold one residue per 32-bit word (d_words32 implies key_words32)
-// accq != nullptr: the first packed_limbs ciphertext limbs of the sums go to accq ([b][2][ell][N], packed) instead of acc.
+// The ciphertext limbs of the sums go to accq ([b][2][ell][N], packed), the special limbs to acc after the row half of their
+// inverse transform.  drop_addend != nullptr: limb ell-1 joins the special limbs (acc[ell-1]) after P times limb ell-1 of
+// that addend ([b][2][ell][N] packed) has been added.
 void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint64_t* lifted,
-                               const void* evk, uint64_t* acc, uint32_t batch, hipStream_t s, bool d_words32 = false,
-                               bool key_words32 = false, const PackedDigits* accq = nullptr, uint32_t packed_limbs = 0);
+                               const void* evk, uint64_t* acc, uint32_t batch, hipStream_t s, bool d_words32, bool key_words32,
+                               const PackedDigits& accq, const PackedDigits* drop_addend = nullptr);
 // Fused row half of the forward transform of the converted limbs + (acc - conv) P^-1 (+ addend).
 // fs == nullptr: multiply by P^-1, addend unscaled, ell output limbs.  Otherwise (merged ModDown + rescale): multiply by
 // fs->mul[i], scale the addend by fs->addend_mul[i], and write only the first fs->out_limbs limbs per component.
@@ -222,15 +230,10 @@ void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t
                                 uint32_t addend_comps, uint32_t galois, uint32_t batch, hipStream_t s,
                                 const FinishScale* fs = nullptr, bool out_words32 = false, const PackedDigits* acc_packed = nullptr,
                                 const PackedDigits* addend_packed = nullptr, bool addend_words32 = false);
-// acc[b][comp][limb] += mul * addend[b][comp][limb] for one ciphertext limb of both components (canonical in, canonical
-// out); addend: [b][2][ell][N] packed
-void launch_add_scaled_limb(const ks_ctx* c, uint64_t* acc, uint64_t acc_ps, const PackedDigits& addend, uint32_t ell, uint32_t limb,
-                            double mul, uint32_t batch, hipStream_t s);
-
-// Fused rescale: last = coefficient-domain dropped limb as canonical doubles [polys][N]; spread = scratch
-// [polys][ell-1][N]; out[p][i] = (x[p][i] - NTT(centred last mod q_i)) * q_{ell-1}^-1.
-void launch_rescale_fused(const ks_ctx* c, const Level& lv, const uint64_t* x, const uint64_t* last, uint64_t* spread,
-                          void* out, uint32_t n_polys, hipStream_t s, bool out_words32 = false);
+// Remainder of the dropped limb for a rescale.  acc: [polys][E][N], the drop_map limbs in the coefficient domain as canonical
+// doubles (y_k on the special limbs, P^-1 times the dropped limb's sum on limb ell-1); limb ell-1 becomes the centred
+// remainder of (sum - converted special part) P^-1 modulo q_{ell-1}, a signed double.
+void launch_rescale_remainder(const ks_ctx* c, const Level& lv, uint64_t* acc, uint32_t n_polys, hipStream_t s);
 
 // words32: in and out hold one residue per 32-bit word (strides in words either way)
 void launch_bconv(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const void* in, uint64_t in_poly_stride,

@@ -50,10 +50,10 @@ __device__ __forceinline__ void task_inv_cols(const double* __restrict__ Wi, Mod
 }
 
 // ---- base conversion on the matrix cores + column half of the forward transform (see ks_bconv_mfma.hip) --------------
-// Adding 2^52 + 0x80808080 to a canonical residue y < 2^36 (held as a double) leaves y + 0x80808080 in the mantissa:
-// its low four bytes, each with the top bit flipped, are the signed digits d_0..d_3 (digit = byte - 128), and bits
-// 32..39 are the non-negative digit d_4 <= 16.
-constexpr double kDigitBias = 4503599627370496.0 + 2155905152.0;
+// Adding 1.5 * 2^52 + 0x80808080 to a residue |y| < 2^36 (held as a double; canonical, or the signed remainder of a
+// rescale) leaves 2^51 + y + 0x80808080 in the mantissa: its low four bytes, each with the top bit flipped, are the signed
+// digits d_0..d_3 (digit = byte - 128), and bits 32..39 are the signed digit d_4, |d_4| <= 16.
+constexpr double kDigitBias = 6755399441055744.0 + 2155905152.0;
 
 // Twiddles of the column butterflies, staged in LDS (both lane halves of a workgroup need different tables, so they
 // cannot ride in scalar registers, and 30 vector registers per target would cost a wavefront of occupancy):
@@ -236,8 +236,8 @@ __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ 
 // ---- row half of the forward transform of the raised limbs + inner product with the key (see ks_fused.hip) ----------
 // One wavefront: four rows (group rg) of limb position pos of one batch item.  d_b / lifted_b / acc_b: that batch item's
 // d [ell][N], raised digits [ndig][E][N] and accumulators [2][E][N].  lds_wave: 4 * kRowPitch doubles, lds_ta_wave: 64.
-// accq_lo_b / accq_hi_b, packed_limbs: the first packed_limbs ciphertext limbs of the sums go to that batch item's packed
-// [2][ell][N] accumulator instead of acc_b.
+// accq_lo_b / accq_hi_b, packed_limbs: the first packed_limbs (ell, or ell - 1 where limb ell - 1 is dropped) ciphertext limbs
+// of the sums go to that batch item's packed [2][ell][N] accumulator instead of acc_b.  drop_*_b: the dropped limb's addend.
 // WD / WK: word types of d and of the key (64-bit, or 32-bit for moduli below 2^32).
 // PREFETCH (64-bit words only): loads are requested in the order x(0), key(0), x(1), key(1), ... and return in that order.
 // While digit j is transformed, key(j) and x(j + 1) are in flight; every key slot is refilled with the next digit's as soon
@@ -248,7 +248,8 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
                                                         const WD* __restrict__ d_b, const uint64_t* __restrict__ lifted_b,
                                                         const WK* __restrict__ evk, uint64_t* __restrict__ acc_b,
                                                         uint32_t* __restrict__ accq_lo_b, uint8_t* __restrict__ accq_hi_b,
-                                                        uint32_t packed_limbs, uint32_t pos,
+                                                        const uint32_t* __restrict__ drop_lo_b, const uint8_t* __restrict__ drop_hi_b,
+                                                        double drop_mul, uint32_t packed_limbs, uint32_t pos,
                                                         uint32_t rg, uint32_t lane, double* lds_wave, double* lds_ta_wave) {
     constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R;
     const uint32_t mid = pos < ell ? pos : L + (pos - ell);
@@ -389,13 +390,23 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
             accq_hi_b[e0 + 16 * k] = (uint8_t)(u0 >> 32);
             accq_hi_b[e1 + 16 * k] = (uint8_t)(u1 >> 32);
         }
-    } else if (pos < ell) {  // uniform: a ciphertext limb that another kernel reads as a 64-bit word
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            o0[16 * k] = f64_to_u64(canon(a0[k], m));
-            o1[16 * k] = f64_to_u64(canon(a1[k], m));
-        }
     } else {
+        if (pos < ell) {  // uniform: the limb a rescale drops becomes a source like the special limbs, its addend included
+            const uint64_t e0 = (uint64_t)pos * N + off, e1 = e0 + (uint64_t)ell * N;
+            uint32_t lo0[16], lo1[16], hi0[16], hi1[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                lo0[k] = drop_lo_b[e0 + 16 * k];
+                lo1[k] = drop_lo_b[e1 + 16 * k];
+                hi0[k] = drop_hi_b[e0 + 16 * k];
+                hi1[k] = drop_hi_b[e1 + 16 * k];
+            }
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                a0[k] = reduce_lazy(a0[k] + mulmod_lazy(u64_to_f64((uint64_t)hi0[k] << 32 | lo0[k]), drop_mul, m), m);
+                a1[k] = reduce_lazy(a1[k] + mulmod_lazy(u64_to_f64((uint64_t)hi1[k] << 32 | lo1[k]), drop_mul, m), m);
+            }
+        }
         // Special limbs go straight into ModDown: the row half of their inverse transform works on the very
         // rows this wavefront holds, so it is done here and raw doubles are handed to the column half.
         PassTwiddles ti;

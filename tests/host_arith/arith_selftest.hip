@@ -87,20 +87,21 @@ static void check_prime(uint64_t p) {
         const double r = mac_reduce(hi, lo, m);
         CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "mac_reduce");
     }
-    // split3: the pieces add up, have the stated granularity and magnitude; with the centred shifted factors, sixteen
+    // split3: the pieces add up, have the stated granularity and magnitude; with the centred shifted factors, seventeen
     // sources accumulate exactly and reduce to sum y_i f_i mod p
     for (int rep = 0; rep < 20000; ++rep) {
         double acc = 0.0;
         i128 exact = 0;
-        for (int i = 0; i < 16; ++i) {
-            uint64_t y = rnd() >> 28;  // below 2^36
+        for (int i = 0; i < 17; ++i) {
+            int64_t y = rnd() >> 28;  // below 2^36
             if (rep % 9 == 0) y = (uint64_t[]){0, (1ull << 36) - 1, (1ull << 24) - 1, 1ull << 23, (1ull << 23) + (1ull << 11), p - 1, 0xFFF800800ull, 0x800800ull}[(rep / 9 + i) % 8];
+            if (i == 16) y = -(y / 2);  // the signed remainder of a rescale
             uint64_t f = rnd() % p;
             if (rep % 5 == 0) f = (i & 1) ? p / 2 : p / 2 + 1;  // largest centred magnitudes
             double y2, y1, y0;
             split3((double)y, y2, y1, y0);
             CHECK(y2 + y1 + y0 == (double)y, "split3 sum %llu", (unsigned long long)y);
-            CHECK(fmod(y2, 16777216.0) == 0 && y2 >= 0 && y2 <= 68719476736.0, "split3 y2 %llu", (unsigned long long)y);
+            CHECK(fmod(y2, 16777216.0) == 0 && (y2 >= 0 || i == 16) && fabs(y2) <= 68719476736.0, "split3 y2 %llu", (unsigned long long)y);
             CHECK(fmod(y1, 4096.0) == 0 && fabs(y1) <= 8388608.0, "split3 y1 %llu", (unsigned long long)y);
             CHECK(fabs(y0) <= 2048.0 && y0 == floor(y0), "split3 y0 %llu", (unsigned long long)y);
             double fk[3];
@@ -116,20 +117,21 @@ static void check_prime(uint64_t p) {
         CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "split3 conversion sum");
     }
     // split2 (contexts whose moduli are all below 2^32): the two pieces add up, have the stated granularity and magnitude;
-    // with the centred factors cut at 16 bits, sixteen sources accumulate exactly and reduce to sum y_i f_i mod p
+    // with the centred factors cut at 16 bits, seventeen sources accumulate exactly and reduce to sum y_i f_i mod p
     if (p < (1ull << 32)) {
         for (int rep = 0; rep < 20000; ++rep) {
             double acc = 0.0;
             i128 exact = 0;
-            for (int i = 0; i < 16; ++i) {
-                uint64_t y = rnd() >> 32;  // below 2^32: a residue of some other modulus of such a context
+            for (int i = 0; i < 17; ++i) {
+                int64_t y = rnd() >> 32;  // below 2^32: a residue of some other modulus of such a context
                 if (rep % 9 == 0) y = (uint64_t[]){0, (1ull << 32) - 1, (1ull << 16) - 1, 1ull << 15, (1ull << 15) + 1, p - 1, 0xFFFF8000ull, 0x8000ull}[(rep / 9 + i) % 8];
+                if (i == 16) y = -(y / 2);
                 uint64_t f = rnd() % p;
                 if (rep % 5 == 0) f = (i & 1) ? p / 2 : p / 2 + 1;  // largest centred magnitudes
                 double y1, y0;
                 split2((double)y, y1, y0);
                 CHECK(y1 + y0 == (double)y, "split2 sum %llu", (unsigned long long)y);
-                CHECK(fmod(y1, 65536.0) == 0 && y1 >= 0 && y1 <= 4294967296.0, "split2 y1 %llu", (unsigned long long)y);
+                CHECK(fmod(y1, 65536.0) == 0 && (y1 >= 0 || i == 16) && fabs(y1) <= 4294967296.0, "split2 y1 %llu", (unsigned long long)y);
                 CHECK(fabs(y0) <= 32768.0 && y0 == floor(y0), "split2 y0 %llu", (unsigned long long)y);
                 double fk[2];
                 for (int k = 0; k < 2; ++k) {

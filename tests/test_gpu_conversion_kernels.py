@@ -111,3 +111,16 @@ def test_option_values_are_checked(small):
         small.ctx.set_option(99, 0)
     small.ctx.set_option(K.KS_OPT_BCONV_KERNEL, 0)
     small.ctx.set_option(K.KS_OPT_BCONV_TARGETS, 0)
+
+
+@pytest.mark.parametrize("kernel,targets", KERNELS)
+def test_rescale_with_the_most_sources(kernel, targets):
+    """K = 16: the conversion of a multiplication's division by P and the rescale takes seventeen sources, the last one signed."""
+    st = Setup(12, 17, 16, 2)
+    _select(st, kernel, targets)
+    for ell, batch in ((17, 2), (2, 3)):
+        cta, ctb = (st.uniform(35 + i, 1, (batch, 2), list(range(ell))) for i in range(2))
+        rlk = st.uniform(37, 2, (st.ctx.dnum, 2), list(range(33)))
+        out = torch.empty((batch, 2, ell - 1, st.N), dtype=torch.int64, device="cuda")
+        K.hmult_relin_rescale(st.ctx, cta, ctb, ell, rlk, out, workspace(st.ctx, K.KS_OP_HMULT_RELIN_RESCALE, ell, batch))
+        assert_equal(out, st.ref.hmult_relin_rescale(host(cta), host(ctb), host(rlk), ell))
