@@ -538,7 +538,7 @@ def bench_ntt(args, torch, K, ks_inputs):
 
 def bench_bconv(args, torch, K, ks_inputs):
     """The standalone base conversion at the two shapes the key-switch uses most (configuration 2's ModUp digit: 8 -> 24
-    moduli; configuration 5's: 12 -> 35), vector kernel against the int8 matrix-core kernel, one polynomial and 64."""
+    moduli; configuration 5's: 12 -> 35), one polynomial and 64."""
     rows = []
     for cfg_id, n_src, n_dst in ((2, 8, 24), (5, 12, 35)):
         cfg = ks_inputs.CONFIGS[cfg_id]
@@ -552,34 +552,31 @@ def bench_bconv(args, torch, K, ks_inputs):
             x = ks_inputs.uniform_residues(cfg["seed"], 1, (batch,), [(q + p)[i] for i in src], N, device="cuda")
             out = torch.empty((batch, n_dst, N), dtype=torch.int64, device="cuda")
             row = {"shape": f"{n_src}->{n_dst} moduli, N=2^{logN}, {batch} polynomial(s)", "bytes": (n_src + n_dst) * batch * N * 8}
-            for name, kernel in (("vector", 1), ("int8_mfma", 2)):
-                ctx.set_option(K.KS_OPT_BCONV_KERNEL, kernel)
-                fn = lambda: K.bconv(ctx, x, src, out, dst)
-                fn()
-                # kernel durations from the library's own HIP events (a single-polynomial launch is shorter than the
-                # host-side cost of a call, so back-to-back wall time would measure the host)
-                reps, trials = (100 if batch == 1 else 20), []
-                for _ in range(3):
-                    torch.cuda.synchronize()
-                    K.ks_profile_enable(True)
-                    for _ in range(reps):
-                        fn()
-                    torch.cuda.synchronize()
-                    rec = K.ks_profile_report()
-                    K.ks_profile_enable(False)
-                    trials.append(sum(k["total_ms"] for k in rec) * 1e3 / reps)
-                us = sorted(trials)[1]
-                row[name + "_us"] = round(us, 2)
-                row[name + "_GBs"] = round(row["bytes"] / (us * 1e-6) / 1e9, 1)
-            ctx.set_option(K.KS_OPT_BCONV_KERNEL, 0)
+            fn = lambda: K.bconv(ctx, x, src, out, dst)
+            fn()
+            # kernel durations from the library's own HIP events (a single-polynomial launch is shorter than the
+            # host-side cost of a call, so back-to-back wall time would measure the host)
+            reps, trials = (100 if batch == 1 else 20), []
+            for _ in range(3):
+                torch.cuda.synchronize()
+                K.ks_profile_enable(True)
+                for _ in range(reps):
+                    fn()
+                torch.cuda.synchronize()
+                rec = K.ks_profile_report()
+                K.ks_profile_enable(False)
+                trials.append(sum(k["total_ms"] for k in rec) * 1e3 / reps)
+            us = sorted(trials)[1]
+            row["us"] = round(us, 2)
+            row["GBs"] = round(row["bytes"] / (us * 1e-6) / 1e9, 1)
             rows.append(row)
     big = rows[1]
-    return {"metric": "bconv_GBps", "value": big["vector_GBs"], "unit": "GB/s", "n_gpus": 1, "steps": 20, "warmup": 1,
-            "ms_per_step": round(big["vector_us"] * 1e-3, 5), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-            "dtype": "f64 (vector) / int8 (matrix cores)", "data": "synthetic",
-            "config": {"workload": "standalone base conversion, vector kernel vs int8 matrix-core kernel"}, "shapes": rows,
-            "roofline": {"bound": "hbm", "kernel": "bconv_kernel", "achieved": big["vector_GBs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                         "frac": round(big["vector_GBs"] / HBM_PEAK_GBS, 4), "traffic": None}}
+    return {"metric": "bconv_GBps", "value": big["GBs"], "unit": "GB/s", "n_gpus": 1, "steps": 20, "warmup": 1,
+            "ms_per_step": round(big["us"] * 1e-3, 5), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
+            "dtype": "int8 (matrix cores)", "data": "synthetic",
+            "config": {"workload": "standalone base conversion"}, "shapes": rows,
+            "roofline": {"bound": "hbm", "kernel": "bconv_mfma_kernel", "achieved": big["GBs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                         "frac": round(big["GBs"] / HBM_PEAK_GBS, 4), "traffic": None}}
 
 
 def bench_copy(args, torch):

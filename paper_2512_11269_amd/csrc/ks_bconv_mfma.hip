@@ -81,76 +81,147 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
 }
 
 // ------------------------------------------------------------------------------------------------
-// Standalone conversion on the matrix cores (the `bconv` entry point's second kernel): canonical residues in, canonical
-// residues out, no transform.  A wavefront owns 32 consecutive positions: lane (position l % 32, half l / 32) scales
-// its slots' source residues to y_i = [x_i (D / s_i)^-1]_{s_i}, cuts them into bytes once, and then walks the targets six
-// at a time (three per lane half), writing 256-byte segments per target.
+// Standalone conversion on the matrix cores (the `bconv` entry point): canonical residues in, canonical residues out, no
+// transform.  A wavefront owns PG groups of 32 positions, V of them interleaved so that a lane's V positions are one 16-byte
+// access: lane (position l % 32, half l / 32) scales its slots' source residues to y_i = [x_i (D / s_i)^-1]_{s_i}, cuts them into bytes once, and then walks the targets six at a time
+// (three per lane half), writing 512-byte segments per target.  The factors and constants of the next six
+// targets are requested before the current ones' stores: loads and stores share one in-order counter, so a load behind the
+// stores would wait for memory to acknowledge them.  About 16 vector instructions per position and target remain, where
+// fp64 accumulation takes three per source more; what bounds a full launch is the traffic itself:
+// 24 polynomials, 12 -> 35 moduli, N = 2^16: 121 us = 4.9 TB/s (64: 5.4), where fp64 accumulation of 12-bit pieces took
+// 198; one polynomial, 8 -> 24: 12.6 against 18.7; in 32-bit words 76 against 162.
 // ------------------------------------------------------------------------------------------------
-template <int NM, int NPS>
+template <int NM, int NPS, int PG, typename W>
 __global__ __launch_bounds__(256) void bconv_mfma_kernel(const BConvPlan* __restrict__ plans, LaunchMeta meta,
-                                                         const uint64_t* __restrict__ in, uint64_t in_ps,
-                                                         uint64_t* __restrict__ out, uint64_t out_ps, uint32_t N) {
+                                                         const W* __restrict__ in, uint64_t in_ps,
+                                                         W* __restrict__ out, uint64_t out_ps, uint32_t N) {
     const uint32_t tid = threadIdx.x, lane = tid & 63u, h = lane >> 5;
-    const uint32_t n = (blockIdx.x * 4 + (tid >> 6)) * 32 + (lane & 31u);  // N is a multiple of 128
+    constexpr int V = PG * (int)sizeof(W) <= 16 ? PG : 16 / (int)sizeof(W);
+    struct alignas(V * sizeof(W)) Vec {
+        W w[V];
+    };
+    const uint32_t n = (blockIdx.x * 4 + (tid >> 6)) * (32 * PG) + (lane & 31u) * V;  // N is a multiple of 128 PG
     const BConvPlan& P = plans[blockIdx.y];
     const int n_dst = (int)meta.plan[blockIdx.y].n_dst, n_src = (int)P.n_src;
-    const uint64_t* ip = in + (uint64_t)blockIdx.z * in_ps + n;
-    uint64_t* op = out + (uint64_t)blockIdx.z * out_ps + n;
-    v4i bq[NM];
+    const W* ip = in + (uint64_t)blockIdx.z * in_ps + n;
+    W* op = out + (uint64_t)blockIdx.z * out_ps + n;
+    W xraw[PG][NM][NPS];
+    Mod mi[NM][NPS];
+    double inv[NM][NPS];
 #pragma unroll
-    for (int m = 0; m < NM; ++m) {
-        bq[m] = v4i{0, 0, 0, 0};
-        uint32_t top = 0;
+    for (int m = 0; m < NM; ++m)
 #pragma unroll
         for (int e = 0; e < NPS; ++e) {
             const int i = min((int)((2 * m + h) * NPS + e), n_src - 1);  // slots past the last source repeat it against zero factors
-            const Mod mi = P.src_mod[i];
-            const double x = u64_to_f64(ip[(uint64_t)P.src_limb[i] * N]);
-            const double yi = canon(mulmod_lazy(x, P.src_inv[i], mi), mi);
-            const uint64_t bits = __builtin_bit_cast(uint64_t, yi + kDigitBias);
-            bq[m][e] = (int)((uint32_t)bits ^ 0x80808080u);
-            top |= ((uint32_t)(bits >> 32) & 0xFFu) << (8 * e);
+            const W* src = ip + (uint64_t)P.src_limb[i] * N;
+#pragma unroll
+            for (int g = 0; g < PG; g += V) {
+                const Vec v = *reinterpret_cast<const Vec*>(src + 32 * g);
+#pragma unroll
+                for (int k = 0; k < V; ++k) xraw[g + k][m][e] = v.w[k];
+            }
+            mi[m][e] = P.src_mod[i];
+            inv[m][e] = P.src_inv[i];
         }
-        bq[m][3] = (int)top;
-    }
-    const uint32_t r = lane & 31u, hp = (r >> 2) & 1u, j = 4 * (r >> 3) + (r & 3u), ua = j / 5, b = j - 5 * ua;
-#pragma unroll 1
-    for (int t0 = 0; t0 < n_dst; t0 += 6) {
-        v16i s = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-        const int ta = min(t0 + (int)(hp * 3 + ua), n_dst - 1);
+    // row r of the factor matrix: result register 4 (r / 8) + r % 4 of lane half (r / 4) % 2, i.e. digit plane b of that
+    // half's target ua
+    const uint32_t r = lane & 31u, hp = (r >> 2) & 1u, j = 4 * (r >> 3) + (r & 3u), ua = min(j / 5, 2u), b = min(j - 5 * ua, 4u);
+    v4i afac[NM];
+    BConvPlan::TargetRec rec[3];
+    auto request = [&](int t0) {
+        const int ta = min(t0 + (int)(hp * 3 + ua), n_dst - 1);  // (register 15 is unused: it repeats a valid row)
+#pragma unroll
+        for (int m = 0; m < NM; ++m) afac[m] = *reinterpret_cast<const v4i*>(&P.afac[ta][b][2 * m + h][0]);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) rec[u] = P.trec[min(t0 + (int)h * 3 + u, n_dst - 1)];
+    };
+    request(0);
+    v4i bq[PG][NM];
+#pragma unroll
+    for (int g = 0; g < PG; ++g)
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
-            const v4i afac = ua < 3 ? *reinterpret_cast<const v4i*>(&P.afac[ta][b][2 * m + h][0]) : v4i{0, 0, 0, 0};
-            s = __builtin_amdgcn_mfma_i32_32x32x32_i8(afac, bq[m], s, 0, 0, 0);
+            bq[g][m] = v4i{0, 0, 0, 0};
+            uint32_t top = 0;
+#pragma unroll
+            for (int e = 0; e < NPS; ++e) {
+                const double yi = canon(mulmod_lazy(word_to_f64<W>(xraw[g][m][e]), inv[m][e], mi[m][e]), mi[m][e]);
+                const uint64_t bits = __builtin_bit_cast(uint64_t, yi + kDigitBias);
+                bq[g][m][e] = (int)((uint32_t)bits ^ 0x80808080u);
+                top |= ((uint32_t)(bits >> 32) & 0xFFu) << (8 * e);
+            }
+            bq[g][m][3] = (int)top;
         }
+#pragma unroll 1
+    for (int t0 = 0; t0 < n_dst; t0 += 6) {
+        v16i s[PG];
+#pragma unroll
+        for (int g = 0; g < PG; ++g) {
+            s[g] = v16i{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+            for (int m = 0; m < NM; ++m) s[g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(afac[m], bq[g][m], s[g], 0, 0, 0);
+        }
+        Mod mt[3];
+        uint32_t limb[3];
 #pragma unroll
         for (int u = 0; u < 3; ++u) {
-            const int t = t0 + (int)h * 3 + u;
-            if (t < n_dst) {
-                const BConvPlan::TargetRec rec = P.trec[t];
-                const int lo = s[5 * u] + (s[5 * u + 1] << 8), mid = s[5 * u + 2] + (s[5 * u + 3] << 8);
-                const double v = __builtin_fma((double)s[5 * u + 4], 4294967296.0, __builtin_fma((double)mid, 65536.0, (double)lo));
-                op[(uint64_t)rec.limb * N] = f64_to_u64(canon(reduce_lazy(v, rec.m), rec.m));
+            mt[u] = rec[u].m;
+            limb[u] = rec[u].limb;
+        }
+        request(t0 + 6);  // past the end: the last target again
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            if (t0 + (int)h * 3 + u < n_dst) {
+                W* dst = op + (uint64_t)limb[u] * N;
+#pragma unroll
+                for (int g = 0; g < PG; g += V) {
+                    Vec o;
+#pragma unroll
+                    for (int k = 0; k < V; ++k) {
+                        const v16i& q = s[g + k];
+                        const int lo = q[5 * u] + (q[5 * u + 1] << 8), mid = q[5 * u + 2] + (q[5 * u + 3] << 8);
+                        const double v = __builtin_fma((double)q[5 * u + 4], 4294967296.0, __builtin_fma((double)mid, 65536.0, (double)lo));
+                        o.w[k] = f64_to_word<W>(canon(reduce_lazy(v, mt[u]), mt[u]));
+                    }
+                    *reinterpret_cast<Vec*>(dst + 32 * g) = o;
+                }
             }
         }
     }
 }
 
-void launch_bconv_mfma(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint64_t* in, uint64_t in_ps,
-                       uint64_t* out, uint64_t out_ps, uint32_t n_polys, hipStream_t s) {
+void launch_bconv_mfma(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const void* in, uint64_t in_ps,
+                       void* out, uint64_t out_ps, uint32_t n_polys, hipStream_t s, bool words32) {
     if (n_polys == 0 || plans.n_plans == 0) return;
     const uint32_t n_src = plans.shape_src, nm = (n_src + 5) / 6, nps = (n_src + 2 * nm - 1) / (2 * nm);
-    const dim3 grid(c->N / 128, plans.n_plans, n_polys), block(256);
-    ProfScope ps("bconv_mfma", (double)limbs_moved_per_poly * n_polys * c->N * 8.0, s);
-#define KS_LAUNCH_BM(NMV, NPSV) \
-    hipLaunchKernelGGL((bconv_mfma_kernel<NMV, NPSV>), grid, block, 0, s, plans.d_plans, plans.meta, in, in_ps, out, out_ps, c->N)
-    if (nm == 1 && nps == 1) KS_LAUNCH_BM(1, 1);
-    else if (nm == 1 && nps == 2) KS_LAUNCH_BM(1, 2);
-    else if (nm == 1) KS_LAUNCH_BM(1, 3);
-    else if (nm == 2 && nps == 2) KS_LAUNCH_BM(2, 2);
-    else if (nm == 2) KS_LAUNCH_BM(2, 3);
-    else KS_LAUNCH_BM(3, 3);
+    // position groups per wavefront: more of them share the factor loads of a step and widen the accesses, as long as the
+    // launch still fills the chip (256 compute units) a few times over
+    const uint64_t tiles = (uint64_t)n_polys * plans.n_plans * (c->N / 128);
+    const int pg = tiles / 4 >= 1024 ? 4 : tiles / 2 >= 512 ? 2 : 1;
+    const dim3 grid(c->N / (128 * pg), plans.n_plans, n_polys), block(256);
+    ProfScope ps("bconv_mfma", (double)limbs_moved_per_poly * n_polys * c->N * (words32 ? 4.0 : 8.0), s);
+#define KS_LAUNCH_BM_W(NMV, NPSV, PGV, WT)                                                                                                  \
+    hipLaunchKernelGGL((bconv_mfma_kernel<NMV, NPSV, PGV, WT>), grid, block, 0, s, plans.d_plans, plans.meta, static_cast<const WT*>(in), in_ps, \
+                       static_cast<WT*>(out), out_ps, c->N)
+#define KS_LAUNCH_BM_PG(NMV, NPSV, WT)                        \
+    if (pg == 4) KS_LAUNCH_BM_W(NMV, NPSV, 4, WT);            \
+    else if (pg == 2) KS_LAUNCH_BM_W(NMV, NPSV, 2, WT);       \
+    else KS_LAUNCH_BM_W(NMV, NPSV, 1, WT)
+#define KS_LAUNCH_BM(NMV, NPSV)                                       \
+    {                                                                 \
+        if (words32) { KS_LAUNCH_BM_PG(NMV, NPSV, uint32_t); }        \
+        else { KS_LAUNCH_BM_PG(NMV, NPSV, uint64_t); }                \
+    }
+    if (nm == 1 && nps == 1) KS_LAUNCH_BM(1, 1)
+    else if (nm == 1 && nps == 2) KS_LAUNCH_BM(1, 2)
+    else if (nm == 1) KS_LAUNCH_BM(1, 3)
+    else if (nm == 2 && nps == 2) KS_LAUNCH_BM(2, 2)
+    else if (nm == 2) KS_LAUNCH_BM(2, 3)
+    else KS_LAUNCH_BM(3, 3)
 #undef KS_LAUNCH_BM
+#undef KS_LAUNCH_BM_PG
+#undef KS_LAUNCH_BM_W
 }
 
 }  // namespace ks

@@ -117,9 +117,6 @@ void fill_bconv_plan(const ks_ctx* c, BConvPlan* plan, const uint32_t* src_ids, 
                 const double centred = f > mt / 2 ? -(double)(mt - f) : (double)f;
                 plan->hats[t][i][k] = k < c->pieces ? ldexp(centred, -cut * k) : 0.0;
             }
-            plan->hat3[t][i][0] = (double)(prod & 0xFFFu);
-            plan->hat3[t][i][1] = (double)((prod >> 12) & 0xFFFu);
-            plan->hat3[t][i][2] = (double)(prod >> 24);
             // matrix-core operand rows: digit b of centred([(D / s_i) 256^a]_t), at the byte that pairs with digit a of source i
             const uint32_t slot = i / plan->mfma_nps, e = i % plan->mfma_nps;
             for (int a = 0; a < kMfmaPlanes; ++a) {

@@ -38,10 +38,6 @@ struct BConvPlan {
     double src_inv[kMaxSrc];     // (D / s_i)^-1 mod s_i
     Mod dst_mod[kMaxDst];
     uint32_t dst_mod_id[kMaxDst];  // modulus id of each target (selects its twiddle table)
-    // hat3[t][i][k], k = 0..2: the three 12-bit pieces (low to high) of (D / s_i) mod t.  A 36-bit residue times a
-    // 12-bit piece is below 2^48, so up to 16 such products add up exactly in a double: the conversion sum costs
-    // three FMAs per source and target plus one short recombination per target instead of a full modular product.
-    double hat3[kMaxDst][kMaxSrc][3];
     // hats[t][i][k], k = 0..2: centred([(D / s_i) 2^(12 k)]_t) * 2^(-12 k), the factors that go with the three pieces
     // of a split source residue (split3); [3] pads the row to 32 bytes.  Zero for padding sources.
     double hats[kMaxDst][kMaxSrc][4];
@@ -235,12 +231,10 @@ void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t
 // remainder of (sum - converted special part) P^-1 modulo q_{ell-1}, a signed double.
 void launch_rescale_remainder(const ks_ctx* c, const Level& lv, uint64_t* acc, uint32_t n_polys, hipStream_t s);
 
+// The standalone conversion, on the matrix cores (ks_bconv_mfma.hip).
 // words32: in and out hold one residue per 32-bit word (strides in words either way)
-void launch_bconv(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const void* in, uint64_t in_poly_stride,
-                  void* out, uint64_t out_poly_stride, uint32_t n_polys, hipStream_t s, bool words32 = false);
-// the same conversion on the matrix cores (ks_bconv_mfma.hip)
-void launch_bconv_mfma(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint64_t* in, uint64_t in_poly_stride,
-                       uint64_t* out, uint64_t out_poly_stride, uint32_t n_polys, hipStream_t s);
+void launch_bconv_mfma(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const void* in, uint64_t in_poly_stride,
+                       void* out, uint64_t out_poly_stride, uint32_t n_polys, hipStream_t s, bool words32);
 
 // Rotations handled by one launch of the gather kernels (more are chained).
 constexpr int kMacRotations = 16;
