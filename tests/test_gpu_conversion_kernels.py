@@ -124,3 +124,26 @@ def test_rescale_with_the_most_sources(kernel, targets):
         out = torch.empty((batch, 2, ell - 1, st.N), dtype=torch.int64, device="cuda")
         K.hmult_relin_rescale(st.ctx, cta, ctb, ell, rlk, out, workspace(st.ctx, K.KS_OP_HMULT_RELIN_RESCALE, ell, batch))
         assert_equal(out, st.ref.hmult_relin_rescale(host(cta), host(ctb), host(rlk), ell))
+
+
+@pytest.mark.parametrize("batch", [31, 32, 33, 127, 128, 129])
+def test_standalone_conversion_positions_per_wavefront(small, batch):
+    """N = 2^12 has 32 wavefront tiles of 128 positions per polynomial: 1, 2 and 4 position groups per wavefront, at the batch sizes
+    where the count changes."""
+    src, dst = [0, 2, 4, 6, 8], [1, 3, 5, 7, 9, 10, 11]
+    x = small.uniform(41, batch, (batch,), src)
+    out = torch.full((batch, len(dst), small.N), -1, dtype=torch.int64, device="cuda")
+    K.bconv_prepare(small.ctx, src, dst)
+    K.bconv(small.ctx, x, src, out, dst)
+    assert_equal(out, small.ref.bconv(host(x), src, dst))
+
+
+@pytest.mark.parametrize("batch", [3, 32, 128])
+def test_standalone_conversion_positions_per_wavefront_words32(batch):
+    st = Setup(12, 9, 3, 3, bits=28)
+    src, dst = [0, 2, 4, 6, 8], [1, 3, 5, 7, 9, 10, 11]
+    x = st.uniform(42, batch, (batch,), src)
+    out = torch.full((batch, len(dst), st.N), -1, dtype=torch.int32, device="cuda")
+    K.bconv_prepare(st.ctx, src, dst)
+    K.bconv_u32(st.ctx, x.to(torch.int32), src, out, dst)
+    assert_equal(out.to(torch.int64), st.ref.bconv(host(x), src, dst))
