@@ -27,53 +27,64 @@ namespace ks {
 // matrix instructions of all 16 positions (256 result registers) and the kernel drops to one wavefront per SIMD.
 constexpr int mfma_min_blocks(int tl) { return tl == 1 ? 4 : 2; }
 
-template <int LOG_R, int TL, int NM, int NPS>
-__global__ __launch_bounds__(256, mfma_min_blocks(TL)) void bconv_mfma_ntt_cols(const double* __restrict__ tw, const BConvPlan* __restrict__ plans,
+template <int LOG_R, int TL, int NM, int NPS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? mfma_min_blocks(TL) : 1) void bconv_mfma_ntt_cols(const double* __restrict__ tw, const BConvPlan* __restrict__ plans,
                                                            LaunchMeta meta, const uint64_t* __restrict__ y, uint64_t y_ps,
-                                                           uint64_t* __restrict__ out, uint64_t out_ps, uint32_t n_subsets) {
-    using Shape = MfmaConvShape<LOG_R, TL>;
+                                                           uint64_t* __restrict__ out, uint64_t out_ps, uint32_t n_subsets, uint32_t pair) {
+    using Shape = MfmaConvShape<LOG_R, TL, WAVES>;
     __shared__ double lds[Shape::LDS_WORDS];
     __shared__ double lds_tw[Shape::LDS_TW_WORDS];
     const uint32_t plan_id = blockIdx.y / n_subsets, subset = blockIdx.y - plan_id * n_subsets;
     const PlanMeta& PM = meta.plan[plan_id];  // kernel arguments: scalar loads, nothing else to wait for
     const int t0 = (int)subset * 2 * TL;
     if (t0 >= (int)PM.n_dst) return;  // uniform for the whole workgroup
-    task_bconv_mfma_cols<LOG_R, TL, NM, NPS>(tw, plans[plan_id], PM, y + (uint64_t)blockIdx.z * y_ps, y_ps * 8,
-                                             out + (uint64_t)blockIdx.z * out_ps, blockIdx.x, t0, threadIdx.x, lds, lds_tw);
+    uint32_t tile = blockIdx.x;
+    // Tiles of 8 columns are half a 128-byte line wide.  Workgroup ids x and x + 8 run on the same XCD at about the same time:
+    // they take the two halves of a line, so that its second half is read from, and its stores meet in, that XCD's L2 (eight
+    // ciphertexts, L = 35: 438 -> 386 us of conversions).  Not where one round holds the whole launch: there the second fetch is
+    // served by the memory-side cache and pairing cost the single-ciphertext key-switch 1.3 % (106.2 -> 107.6 us).
+    if (Shape::TC == 8 && pair) tile = (tile & ~15u) | ((tile & 7u) << 1) | ((tile >> 3) & 1u);
+    task_bconv_mfma_cols<LOG_R, TL, NM, NPS, WAVES>(tw, plans[plan_id], PM, y + (uint64_t)blockIdx.z * y_ps, y_ps * 8,
+                                             out + (uint64_t)blockIdx.z * out_ps, tile, t0, threadIdx.x, lds, lds_tw);
 }
 
 // Targets per lane half: one gives the most workgroups, three shares the byte-cutting of the sources among the most
-// targets (and keeps the stores of one target under the butterflies of the next).
+// targets (and keeps the stores of one target under the butterflies of the next).  wide: tiles of 16 columns and 512 threads
+// instead of 8 and 256 at N = 2^16, whole 128-byte lines, for launches of many rounds (see launch_bconv_ntt_cols).
 void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uint64_t* y, uint64_t y_ps, uint64_t* out,
-                                uint64_t out_ps, uint32_t n_polys, int tl, hipStream_t s) {
+                                uint64_t out_ps, uint32_t n_polys, int tl, bool wide, hipStream_t s) {
     const uint32_t n_src = plans.shape_src, n_plans = plans.n_plans, max_targets = plans.max_targets;
     const BConvPlan* d_plans = plans.d_plans;
     const uint32_t nm = (n_src + 5) / 6, nps = (n_src + 2 * nm - 1) / (2 * nm);
-    const uint32_t tiles = c->N / 2048;
-    tl = (c->logN != 12 && c->logN != 16) || tl < 2 ? 1 : 3;  // built shapes: one or three targets per lane half
+    tl = (c->logN == 13 || c->logN == 14) || tl < 2 ? 1 : 3;  // built shapes: one or three targets per lane half
+    const int waves = wide && c->logN == 16 && tl == 3 ? 8 : 4;
+    const uint32_t tiles = c->N / (512 * waves);
     const uint32_t n_subsets = (max_targets + 2 * tl - 1) / (2 * tl);
-    const dim3 grid(tiles, n_plans * n_subsets, n_polys), block(256);
-#define KS_LAUNCH_MFMA(LOGR, TLV, NMV, NPSV)                                                                                        \
-    hipLaunchKernelGGL((bconv_mfma_ntt_cols<LOGR, TLV, NMV, NPSV>), grid, block, 0, s, c->d_tw_fwd, d_plans, plans.meta, y, y_ps, \
-                       out, out_ps, n_subsets)
-#define KS_MFMA_SHAPE(LOGR, TLV)                                      \
-    if (nm == 1 && nps == 1) KS_LAUNCH_MFMA(LOGR, TLV, 1, 1);         \
-    else if (nm == 1 && nps == 2) KS_LAUNCH_MFMA(LOGR, TLV, 1, 2);    \
-    else if (nm == 1) KS_LAUNCH_MFMA(LOGR, TLV, 1, 3);                \
-    else if (nm == 2 && nps == 2) KS_LAUNCH_MFMA(LOGR, TLV, 2, 2);    \
-    else if (nm == 2) KS_LAUNCH_MFMA(LOGR, TLV, 2, 3);                \
-    else KS_LAUNCH_MFMA(LOGR, TLV, 3, 3)
-    // every shape for the benchmarked ring degree and for the smallest one (which the parity sweeps run on); the degrees
-    // in between take one target per lane half
-#define KS_LAUNCH_TL(LOGR)                   \
-    if (tl == 1) { KS_MFMA_SHAPE(LOGR, 1); } \
-    else { KS_MFMA_SHAPE(LOGR, 3); }
+    const dim3 grid(tiles, n_plans * n_subsets, n_polys), block(64 * waves);
+#define KS_LAUNCH_MFMA(LOGR, TLV, NMV, NPSV, WV)                                                                                        \
+    hipLaunchKernelGGL((bconv_mfma_ntt_cols<LOGR, TLV, NMV, NPSV, WV>), grid, block, 0, s, c->d_tw_fwd, d_plans, plans.meta, y, y_ps, \
+                       out, out_ps, n_subsets, grid.x * grid.y * grid.z > 512)
+#define KS_MFMA_SHAPE(LOGR, TLV, WV)                                      \
+    if (nm == 1 && nps == 1) KS_LAUNCH_MFMA(LOGR, TLV, 1, 1, WV);         \
+    else if (nm == 1 && nps == 2) KS_LAUNCH_MFMA(LOGR, TLV, 1, 2, WV);    \
+    else if (nm == 1) KS_LAUNCH_MFMA(LOGR, TLV, 1, 3, WV);                \
+    else if (nm == 2 && nps == 2) KS_LAUNCH_MFMA(LOGR, TLV, 2, 2, WV);    \
+    else if (nm == 2) KS_LAUNCH_MFMA(LOGR, TLV, 2, 3, WV);                \
+    else KS_LAUNCH_MFMA(LOGR, TLV, 3, 3, WV)
+#define KS_LAUNCH_TL(LOGR)                      \
+    if (tl == 1) { KS_MFMA_SHAPE(LOGR, 1, 4); } \
+    else { KS_MFMA_SHAPE(LOGR, 3, 4); }
+    // every shape for the degrees that the rule of launch_bconv_ntt_cols takes here and for the smallest one (which the parity
+    // sweeps run on); the degrees in between take one target per lane half
     switch (c->logN) {
         case 12: KS_LAUNCH_TL(4); break;
-        case 13: KS_MFMA_SHAPE(5, 1); break;
-        case 14: KS_MFMA_SHAPE(6, 1); break;
-        case 15: KS_MFMA_SHAPE(7, 1); break;
-        default: KS_LAUNCH_TL(8); break;
+        case 13: KS_MFMA_SHAPE(5, 1, 4); break;
+        case 14: KS_MFMA_SHAPE(6, 1, 4); break;
+        case 15: KS_LAUNCH_TL(7); break;
+        default:
+            if (waves == 8) { KS_MFMA_SHAPE(8, 3, 8); }
+            else KS_LAUNCH_TL(8)
+            break;
     }
 #undef KS_LAUNCH_TL
 #undef KS_MFMA_SHAPE

@@ -186,11 +186,29 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
     const uint32_t n_plans = plans.n_plans, max_targets = plans.max_targets;
     const BConvPlan* d_plans = plans.d_plans;
     if (n_polys == 0 || n_plans == 0) return;
-    // Which kernel: on launches too small to fill the chip (a single ciphertext) the matrix-core kernel measured 4-5 %
-    // faster per key-switch; once a launch has a few workgroups per compute unit the vector kernel wins by 13-24 %.
-    const uint32_t tiles16 = 1u << (c->logN - 12);
-    const bool small_launch = (uint64_t)tiles16 * n_plans * ((max_targets + 3) / 4) * n_polys < 512;
-    const int kernel = c->opt[KS_OPT_BCONV_KERNEL] ? c->opt[KS_OPT_BCONV_KERNEL] : (small_launch && c->logN == 16 ? 2 : 1);
+    // Which kernel.  G counts the matrix-core kernel's workgroups (six targets and 2048 positions each), of which 512 run at once.
+    //   The matrix cores win at N >= 2^15 with 64-bit words (three pieces in the vector kernel): 8 -> 3 x 24 moduli at N = 2^16
+    // 25.9 -> 22.4 us for one polynomial (G = 384), 66.8 -> 55.5 for four; 13 -> 34, eight: 83.8 -> 66.8; 7 -> 20 at 2^15,
+    // sixteen: 43.9 -> 35.2.  Below 2^15 launches are at their floor and the vector kernel is 0-1 us ahead.
+    //   Up to three sources cost the vector kernel less than the byte sums do (3 -> 4 x 12, eight: 59.8 against 61.5 us), and a
+    // second round that is almost empty costs more than a few sources save (7 -> 3 x 21 at 2^15, G = 576: 24.9 against 27.7; with
+    // twelve sources, same G: 42.2 against 36.3).
+    //   Moduli below 2^32 (two pieces): the vector kernel is ahead once its launch has a few rounds (9 -> 20, sixteen, G = 2048: 66.8
+    // against 71.0 us; 13 -> 34, G = 3072: 138.4 against 149.6), until whole-line tiles take the lead (12 -> 3 x 36, G = 4608:
+    // 220.7 against 213.8; 8 -> 24, G = 8192: 383 against 348).
+    //   Whole-line tiles (one workgroup of 512 threads per compute unit, in step) pay from six rounds on: G = 3072, 13 -> 34: 151.4
+    // with 8 columns, 138.3 with 16, 148.7 vector; G = 2304, 8 -> 3 x 24: 78.0, 89.0, 89.1.
+    uint64_t subsets = 0;
+    for (uint32_t j = 0; j < n_plans; ++j) subsets += (plans.meta.plan[j].n_dst + 5) / 6;
+    const uint64_t G = (uint64_t)(c->N / 2048) * subsets * n_polys;
+    const bool two_pieces = c->pieces == 2, wide = G >= (two_pieces ? 4096 : 3072);
+    bool matrix;
+    if (c->logN < 15) matrix = false;
+    else if (plans.shape_src < 4) matrix = G <= 512 && c->logN == 16;
+    else if (G <= 512) matrix = true;
+    else if (G <= 640 && plans.shape_src < 8) matrix = false;
+    else matrix = !two_pieces || G < 2048 || wide;
+    const int kernel = c->opt[KS_OPT_BCONV_KERNEL] ? c->opt[KS_OPT_BCONV_KERNEL] : (matrix ? 2 : 1);
     if (kernel == 2) {
         // algorithmic fp64 / integer vector work per coefficient of this kernel: per target 9 to recombine and reduce the
         // five sums and 35 for the column half; per source 2 to cut it into bytes (the contraction itself runs on the
@@ -199,7 +217,7 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
         for (uint32_t j = 0; j < n_plans; ++j) vec_ops += plans.meta.plan[j].n_dst * 44.0 + plans.shape_src * 2.0;
         ProfScope ps("bconv_mfma_ntt_cols", (double)limbs_moved_per_poly * n_polys * c->N * 8.0, s, vec_ops * n_polys * c->N);
         const int tl = c->opt[KS_OPT_BCONV_TARGETS] >= 1 && c->opt[KS_OPT_BCONV_TARGETS] <= 3 ? c->opt[KS_OPT_BCONV_TARGETS] : 3;
-        launch_bconv_mfma_ntt_cols(c, plans, y, y_ps, out, out_ps, n_polys, tl, s);
+        launch_bconv_mfma_ntt_cols(c, plans, y, y_ps, out, out_ps, n_polys, tl, wide, s);
         return;
     }
     // Targets per workgroup: fewer targets = more workgroups but more re-reads and re-splits of the sources.  Four (with

@@ -192,7 +192,7 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
                            uint64_t* out, uint64_t out_ps, uint32_t n_polys, hipStream_t s, double ops_per_coeff = 0.0);
 // The same conversion + column half on the matrix cores (ks_bconv_mfma.hip); tl = targets per lane half, 1..3.
 void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uint64_t* y, uint64_t y_ps, uint64_t* out,
-                                uint64_t out_ps, uint32_t n_polys, int tl, hipStream_t s);
+                                uint64_t out_ps, uint32_t n_polys, int tl, bool wide, hipStream_t s);
 // Upload host plans as a PlanSet (allocates; ks_ctx_create and bconv plan registration only).  Returns a HIP error code.
 hipError_t upload_plans(const BConvPlan* host_plans, uint32_t n_plans, uint32_t shape_src, PlanSet* out);
 // Canonical residues in packed form: bits 0..31 in lo, the bits above (moduli are below 2^36) in hi, both with the

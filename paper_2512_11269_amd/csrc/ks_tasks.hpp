@@ -70,9 +70,9 @@ __device__ __forceinline__ uint32_t col_twiddle_index(uint32_t slot, uint32_t j)
     return (int)ul >= 4 - E ? (1u << (E + ul)) + (r0 << ul) + g : 0u;
 }
 
-template <int LOG_R, int TL>
+template <int LOG_R, int TL, int WAVES>
 struct MfmaConvShape {
-    static constexpr uint32_t R = 1u << LOG_R, TC = 2048u >> LOG_R;  // tile: TC columns x R rows = 2048 positions
+    static constexpr uint32_t R = 1u << LOG_R, TC = (512u * WAVES) >> LOG_R;  // tile: TC columns x R rows, 512 positions a wavefront
     static constexpr int E = LOG_R - 4, S = 1 << E;
     // exchange buffer of the column butterflies, one region per lane half; rows are padded so that the 16-row groups the
     // second pass reads start in different banks
@@ -81,13 +81,13 @@ struct MfmaConvShape {
     static constexpr uint32_t LDS_WORDS = LOG_R > 4 ? 2 * HALF_WORDS : 1, LDS_TW_WORDS = 2 * TL * TW_WORDS;
 };
 
-// 256 threads; yp / y_bytes: the source bundle of this polynomial; op: its output bundle; tile: 2048 positions;
+// 64 WAVES threads; yp / y_bytes: the source bundle of this polynomial; op: its output bundle; tile: 512 WAVES positions;
 // t0: first of the 2 TL targets (t0 < n_dst); lds: LDS_WORDS doubles; lds_tw: LDS_TW_WORDS doubles.
-template <int LOG_R, int TL, int NM, int NPS>
+template <int LOG_R, int TL, int NM, int NPS, int WAVES>
 __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ tw, const BConvPlan& P, const PlanMeta& PM,
                                                      const uint64_t* __restrict__ yp, uint64_t y_bytes, uint64_t* __restrict__ op,
                                                      uint32_t tile, int t0, uint32_t tid, double* lds, double* lds_tw) {
-    using Shape = MfmaConvShape<LOG_R, TL>;
+    using Shape = MfmaConvShape<LOG_R, TL, WAVES>;
     constexpr uint32_t N = 256u << LOG_R, TC = Shape::TC, PADW = Shape::PADW, HALF_WORDS = Shape::HALF_WORDS, TW_WORDS = Shape::TW_WORDS;
     constexpr int E = Shape::E, S = Shape::S;
     const uint32_t lane = tid & 63u, h = lane >> 5, p = (tid >> 6) * 32u + (lane & 31u);
@@ -148,11 +148,12 @@ __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ 
         dst_limb[u] = rec.limb;
     }
     // twiddles of all 2 TL targets -> LDS (requested now, written after the conversion, used after a barrier)
-    constexpr int TW_PER_THREAD = (2 * TL * TW_WORDS + 255) / 256;
+    constexpr uint32_t THREADS = 64 * WAVES;
+    constexpr int TW_PER_THREAD = (2 * TL * TW_WORDS + THREADS - 1) / THREADS;
     double twv[TW_PER_THREAD];
 #pragma unroll
     for (int i = 0; i < TW_PER_THREAD; ++i) {
-        const uint32_t w = min(tid + 256u * i, 2u * TL * TW_WORDS - 1), ht = w / TW_WORDS, rem = w - ht * TW_WORDS;
+        const uint32_t w = min(tid + THREADS * i, 2u * TL * TW_WORDS - 1), ht = w / TW_WORDS, rem = w - ht * TW_WORDS;
         const int t = min(t0 + (int)ht, n_dst - 1);  // ht = half * TL + u, the order of the targets
         twv[i] = tw[(size_t)P.trec[t].mod_id * N + col_twiddle_index<LOG_R>(rem >> 4, rem & 15u)];
     }
@@ -204,7 +205,7 @@ __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ 
     if (OVERLAP) recombine(15);
 #pragma unroll
     for (int i = 0; i < TW_PER_THREAD; ++i)
-        if (tid + 256u * i < 2u * TL * TW_WORDS) lds_tw[tid + 256u * i] = twv[i];
+        if (tid + THREADS * i < 2u * TL * TW_WORDS) lds_tw[tid + THREADS * i] = twv[i];
     __syncthreads();
 
     // column half of the forward transform of each target, both lane halves at once (different moduli per half)

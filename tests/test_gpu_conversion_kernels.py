@@ -147,3 +147,26 @@ def test_standalone_conversion_positions_per_wavefront_words32(batch):
     K.bconv_prepare(st.ctx, src, dst)
     K.bconv_u32(st.ctx, x.to(torch.int32), src, out, dst)
     assert_equal(out.to(torch.int64), st.ref.bconv(host(x), src, dst))
+
+
+@pytest.mark.parametrize("logN,L,Kk,dnum,batch", [
+    (16, 16, 4, 4, 8),    # 16-column tiles with every operand-slot shape: 4, 6, 8, 12 and 13 sources
+    (16, 24, 6, 4, 8),
+    (16, 24, 8, 3, 9),    # a last chunk of one ciphertext: 16- and 8-column tiles in one call
+    (16, 36, 12, 3, 8),
+    (16, 39, 13, 3, 8),
+    (15, 20, 7, 3, 5),    # three targets per lane half at N = 2^15
+])
+def test_conversion_tiles_of_large_launches(logN, L, Kk, dnum, batch):
+    """The kernel chosen from the launch size against the vector kernel on every residue, and against the reference on the last item."""
+    st = Setup(logN, L, Kk, dnum)
+    evk = st.uniform(43, 1, (dnum, 2), list(range(L + Kk)))
+    d = st.uniform(43, 2, (batch,), list(range(L)))
+    ws = workspace(st.ctx, K.KS_OP_KEYSWITCH, L, batch)
+    out = []
+    for kernel in (0, 1):
+        _select(st, kernel, 0)
+        out.append(torch.full((batch, 2, L, st.N), -1, dtype=torch.int64, device="cuda"))
+        K.ks_keyswitch(st.ctx, d, L, evk, out[-1], ws)
+    assert torch.equal(out[0], out[1])
+    assert_equal(out[0][-1:], st.ref.keyswitch(host(d[-1:]), host(evk), L))
