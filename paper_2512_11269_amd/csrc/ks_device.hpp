@@ -71,8 +71,10 @@ KS_HD double reduce_lazy(double x, Mod m) {
 // [2^80, 2^81), where doubles are 2^28 apart, so fma(x, k, hi) rounds x k to a multiple of 2^28; the part it dropped,
 // x k - (hi_new - hi), is an integer of magnitude <= 2^27 that the second FMA recovers exactly and lo collects.  Four
 // instructions a product and one reduction per sum, where a Barrett product and an addition take seven.
-// Requires |x|, |k| <= 2^36 and sums below 2^79, i.e. at most 128 products (256 if |k| <= 0.51 * 2^36, a lazy residue).
+// Requires |x|, |k| <= 2^36 and sums of at most 2^79: kMacTerms products, or kMacTermsLazy if |k| <= 0.51 * 2^36 (a lazy
+// residue; 0.51 * 250 < 128).
 constexpr double kMacBias = 0x1.8p80;
+constexpr int kMacTerms = 128, kMacTermsLazy = 250;
 KS_HD void mac_exact(double x, double k, double& hi, double& lo) {
     const double t = __builtin_fma(x, k, hi);
     const double d = hi - t;

@@ -6,6 +6,10 @@
 
 namespace ks {
 
+// What one sum of the gather kernels takes at most: the digits of a rotation, and with lazy factors those of all rotations of a
+// launch and their c0.
+static_assert(kMaxDigits <= kMacTerms && kMacRotations * (kMaxDigits + 1) <= kMacTermsLazy, "products per exact sum");
+
 // One slot of a bundle slab as a gather loads it: the low words of the group's ciphertexts and the word of their bits above.
 template <int G>
 struct SlotRaw {

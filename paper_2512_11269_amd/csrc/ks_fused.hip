@@ -459,6 +459,7 @@ __global__ __launch_bounds__(256) void rescale_remainder_kernel(Mod m, const dou
                                                                 uint32_t N, uint64_t* __restrict__ acc) {
     const uint32_t n = blockIdx.x * 256 + threadIdx.x;
     uint64_t* last = acc + ((uint64_t)blockIdx.y * (ell + K) + ell - 1) * N + n;
+    static_assert(kMaxLimbsIn <= kMacTerms, "products per exact sum");
     double hi = kMacBias, lo = 0.0;
 #pragma unroll 4
     for (uint32_t k = 0; k < K; ++k) mac_exact(load_f64(last + (uint64_t)(k + 1) * N), pinv[k], hi, lo);

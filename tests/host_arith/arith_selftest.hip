@@ -69,11 +69,12 @@ static void check_prime(uint64_t p) {
         const i128 exact = ((i128)s2 << 24) + ((i128)s1 << 12) + s0;
         CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "combine3");
     }
-    // mac_exact: 128 products of the largest operands (256 with a lazy second factor) and smaller ones, reduced once
+    // mac_exact: as many products as it takes, of the largest operands and of smaller ones, reduced once; the high sum stays
+    // where doubles are 2^28 apart
     for (int rep = 0; rep < 3000; ++rep) {
         double hi = kMacBias, lo = 0.0;
         i128 exact = 0;
-        const int terms = rep % 3 == 0 ? 256 : 128;
+        const int terms = rep % 3 == 0 ? kMacTermsLazy : kMacTerms;
         for (int i = 0; i < terms; ++i) {
             int64_t x = (int64_t)(rnd() % p), k = (int64_t)(rnd() % p);
             if (rep % 5 == 0) x = p - 1;
@@ -81,8 +82,9 @@ static void check_prime(uint64_t p) {
             else if (rep % 5 == 0) k = p - 1;
             mac_exact((double)x, (double)k, hi, lo);
             exact += (i128)x * k;
+            CHECK(hi >= 0x1p80 && hi < 0x1p81, "mac_exact high sum after %d of %d terms", i + 1, terms);
         }
-        CHECK(lo == floor(lo) && fabs(lo) <= 256.0 * 134217728.0, "mac_exact low sum");
+        CHECK(lo == floor(lo) && fabs(lo) <= terms * 134217728.0, "mac_exact low sum");
         CHECK((i128)(hi - kMacBias) + (i128)(int64_t)lo == exact, "mac_exact sum");
         const double r = mac_reduce(hi, lo, m);
         CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "mac_reduce");
