@@ -10,6 +10,7 @@ namespace {
 // Ciphertexts processed per pass of a pipeline; bounds the workspace.  Eight fill every launch and keep more of the
 // intermediates in the last-level cache than sixteen (3-4 % faster on batched key-switches and multiplications).
 constexpr uint32_t kChunk = 8;
+static_assert(kChunk <= kMaxGroup, "ciphertexts of one gather bundle");
 constexpr uint32_t kRotGroup = 4;  // hoisted rotations per gather launch (larger groups measured no faster); bounds the workspace
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -72,11 +73,11 @@ void mod_up(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, uint
 // Words of workspace the bundle of a chunk of bc ciphertexts takes: low words, then (64-bit operands) the bits above;
 // with_c0: the addend's limbs as well.
 static uint64_t gather_lo_words(const ks_ctx* c, const Level& lv, uint32_t bc, bool with_c0) {
-    return ((uint64_t)lv.ndig * lv.E + (with_c0 ? lv.ell : 0)) * c->N * gather_group(bc) / 2;
+    return ((uint64_t)lv.ndig * lv.E + (with_c0 ? lv.ell : 0)) * c->N * bc / 2;
 }
 static uint64_t gather_words(const ks_ctx* c, const Level& lv, uint32_t bc, bool with_c0, bool words32) {
-    const uint64_t lo = gather_lo_words(c, lv, bc, with_c0);
-    return lo + (words32 ? 0 : lo / 4 * gather_hi_bytes(gather_group(bc)) / gather_group(bc));
+    const uint64_t slots = ((uint64_t)lv.ndig * lv.E + (with_c0 ? lv.ell : 0)) * c->N;
+    return gather_lo_words(c, lv, bc, with_c0) + (words32 ? 0 : slots * gather_hi_bytes(bc) / 8);
 }
 
 // mod_up finished for the rotation gathers: `region` (gather_words() words) ends as the bundle they read.  `lifted` is only
@@ -86,8 +87,8 @@ static GatherBundle mod_up_for_gather(const ks_ctx* c, const Level& lv, const vo
     if (raised) mod_up(c, lv, d, d_ps, coeff, lifted, bc, s, words32);
     const GatherBundle bundle{reinterpret_cast<uint32_t*>(region),
                               words32 ? nullptr : reinterpret_cast<uint8_t*>(region + gather_lo_words(c, lv, bc, c0 != nullptr)),
-                              gather_group(bc)};
-    launch_gather_bundle_rows(c, lv, lifted, d, c0, d_ps, bundle, bc, raised, s);
+                              bc};
+    launch_gather_bundle_rows(c, lv, lifted, d, c0, d_ps, bundle, raised, s);
     return bundle;
 }
 
@@ -380,7 +381,7 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
                 rot.key[r] = rot_keys[r0 + r];
                 rot.pt[r] = nullptr;
             }
-            launch_inner_product(c, lv, digits, rot, acc, accq, bc, s, words32);
+            launch_inner_product(c, lv, digits, rot, acc, accq, s, words32);
             const uint32_t polys = 2 * rot.n * bc;
             launch_ntt_inv_rows(c, lv.special_map, XformIO{acc, acc, acc_ps, acc_ps, polys}, s);
             launch_ntt_inv_cols(c, lv.special_map, acc, acc_ps, polys, c->d_moddown_scale, true, true, s);
@@ -425,7 +426,7 @@ static int check_mac_rotations(const ks_ctx* c, const uint32_t* galois, const vo
 // u (+)= sum_r pt_r * rot_{g_r}(ct) for all n rotations, in launches of kMacRotations
 static void rotate_mac_all(const ks_ctx* c, const Level& lv, const GatherBundle& src,
                            const uint32_t* galois, const void* const* keys, const void* const* pts, uint32_t n, uint64_t* u,
-                           uint32_t bc, bool accumulate, hipStream_t s, bool key_words32 = false) {
+                           bool accumulate, hipStream_t s, bool key_words32 = false) {
     for (uint32_t r0 = 0; r0 < n; r0 += kMacRotations) {
         MacRotations rot;
         rot.n = std::min<uint32_t>(n - r0, kMacRotations);
@@ -434,7 +435,7 @@ static void rotate_mac_all(const ks_ctx* c, const Level& lv, const GatherBundle&
             rot.key[r] = keys[r0 + r];
             rot.pt[r] = pts ? pts[r0 + r] : nullptr;
         }
-        launch_rotate_mac(c, lv, src, rot, u, bc, accumulate || r0 != 0, s, key_words32);
+        launch_rotate_mac(c, lv, src, rot, u, accumulate || r0 != 0, s, key_words32);
     }
 }
 
@@ -463,7 +464,7 @@ static int rotate_mac_impl(const ks_ctx* c, const void* ct, uint32_t ell, const 
         uint64_t* conv = acc + w.acc;
         // finished once, shared by every rotation
         const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, s, words32);
-        rotate_mac_all(c, lv, digits, galois, rot_keys, pts, n_rot, acc, bc, false, s, words32);
+        rotate_mac_all(c, lv, digits, galois, rot_keys, pts, n_rot, acc, false, s, words32);
         mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, s, words32);
     }
     return finish(words32 ? "ks_rotate_mac_hoisted_u32" : "ks_rotate_mac_hoisted");
@@ -514,11 +515,11 @@ static int bsgs_impl(const ks_ctx* c, const void* ct, uint32_t ell, const uint32
         uint64_t* v = acc_outer + w.acc;             // [bc][2][ell][N] inner result of the current giant step (64-bit words)
         const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, s, words32);
         for (uint32_t g = 0; g < n2; ++g) {
-            rotate_mac_all(c, lv, digits, baby_galois, bkeys, ptv + (size_t)g * n1, n1, acc, bc, false, s, words32);
+            rotate_mac_all(c, lv, digits, baby_galois, bkeys, ptv + (size_t)g * n1, n1, acc, false, s, words32);
             mod_down(c, lv, acc, conv, v, ct_bs, nullptr, 0, 0, 1, bc, false, s);
             const GatherBundle digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, v, ct_bs, coeff, lifted, region_v, bc, s, false,
                                                             giant_galois[g] != 1);
-            rotate_mac_all(c, lv, digits_v, giant_galois + g, gkeys + g, nullptr, 1, acc_outer, bc, g != 0, s, words32);
+            rotate_mac_all(c, lv, digits_v, giant_galois + g, gkeys + g, nullptr, 1, acc_outer, g != 0, s, words32);
         }
         mod_down(c, lv, acc_outer, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, s,
                  words32);

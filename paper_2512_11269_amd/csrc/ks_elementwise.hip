@@ -26,6 +26,21 @@ __device__ __forceinline__ T buffer_load(BufferRsrc rsrc, uint32_t lane_bytes, u
     else if constexpr (sizeof(T) == 2) return (T)__builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)lane_bytes, (int)uniform_bytes, CPOL);
     else return (T)__builtin_amdgcn_raw_buffer_load_b8(rsrc, (int)lane_bytes, (int)uniform_bytes, CPOL);
 }
+// W consecutive 32-bit words
+template <int W>
+__device__ __forceinline__ void buffer_load_words(uint32_t* w, BufferRsrc rsrc, uint32_t lane_bytes, uint32_t uniform_bytes) {
+    if constexpr (W == 3) {
+        const auto t = __builtin_amdgcn_raw_buffer_load_b96(rsrc, (int)lane_bytes, (int)uniform_bytes, 0);
+        w[0] = t[0]; w[1] = t[1]; w[2] = t[2];
+    } else {
+        struct alignas(4 * W) Words {
+            uint32_t w[W];
+        };
+        const Words t = buffer_load<Words>(rsrc, lane_bytes, uniform_bytes);
+#pragma unroll
+        for (int k = 0; k < W; ++k) w[k] = t.w[k];
+    }
+}
 // Descriptor of a tensor whose address is uniform, kept in scalar registers.
 __device__ __forceinline__ BufferRsrc uniform_rsrc(const void* p, uint64_t bytes) {
     const uint64_t a = reinterpret_cast<uint64_t>(p);
@@ -39,28 +54,19 @@ struct BundleRsrc {
 };
 template <int G>
 __device__ __forceinline__ BundleRsrc bundle_rsrc(const GatherBundle& src, uint64_t slots) {
-    return BundleRsrc{uniform_rsrc(src.lo, slots * (4 * G)), uniform_rsrc(src.hi, slots * (G > 1 ? G / 2 : 1))};
+    return BundleRsrc{uniform_rsrc(src.lo, slots * (4 * G)), uniform_rsrc(src.hi, slots * gather_hi_bytes(G))};
 }
 // The slots sigma_g sends to a wavefront's 64 consecutive slots are one aligned block of 64, permuted.  The block is read
 // in its own order and the lanes exchange what they hold on use (slot_take; 5 % on both kernels over permuted loads).  slab: uniform; slot: the lane's source slot.
 template <int G, bool PACKED>
 __device__ __forceinline__ SlotRaw<G> slot_load(const BundleRsrc& src, uint32_t slab, uint32_t N, uint32_t slot) {
-    using HW = std::conditional_t<G == 8, uint32_t, std::conditional_t<G == 4, uint16_t, uint8_t>>;
+    using Layout = SlotLayout<G>;
+    using HW = typename Layout::HW;
     const uint32_t block = slab * N + (__builtin_amdgcn_readfirstlane(slot) & ~63u), lane = threadIdx.x & 63u;
     SlotRaw<G> r;
     r.from = (slot & 63u) * 4;
-    if constexpr (G >= 4) {
-#pragma unroll
-        for (int q = 0; q < G / 4; ++q) {
-            const uint4 t = buffer_load<uint4>(src.lo, lane * 16, block * (4 * G) + 1024 * q);
-            r.lo[4 * q] = t.x; r.lo[4 * q + 1] = t.y; r.lo[4 * q + 2] = t.z; r.lo[4 * q + 3] = t.w;
-        }
-    } else if constexpr (G == 2) {
-        const uint2 t = buffer_load<uint2>(src.lo, lane * 8, block * 8);
-        r.lo[0] = t.x; r.lo[1] = t.y;
-    } else {
-        r.lo[0] = buffer_load<uint32_t>(src.lo, lane * 4, block * 4);
-    }
+    buffer_load_words<Layout::FIRST>(r.lo, src.lo, lane * (4 * Layout::FIRST), block * (4 * G));
+    if constexpr (Layout::REST > 0) buffer_load_words<Layout::REST>(r.lo + 4, src.lo, lane * (4 * Layout::REST), block * (4 * G) + 1024);
     r.hi = PACKED ? buffer_load<HW>(src.hi, lane * (uint32_t)sizeof(HW), block * (uint32_t)sizeof(HW)) : 0u;
     return r;
 }
@@ -123,7 +129,7 @@ template <int G, typename WK, bool PACKED>
 __global__ __launch_bounds__(256, 4) void inner_product_kernel(const Mod* __restrict__ mods, uint32_t ell, uint32_t E, uint32_t L, uint32_t M,
                                                             uint32_t logN, uint32_t ndig, uint32_t parts_log, GatherBundle src,
                                                             MacRotations rot, uint64_t* __restrict__ acc, uint32_t* __restrict__ accq_lo,
-                                                            uint8_t* __restrict__ accq_hi, uint32_t batch) {
+                                                            uint8_t* __restrict__ accq_hi) {
     const uint32_t N = 1u << logN;
     const GatherTile tile = gather_tile(E, logN, parts_log);
     if (!tile.valid) return;  // uniform
@@ -168,11 +174,10 @@ __global__ __launch_bounds__(256, 4) void inner_product_kernel(const Mod* __rest
             }
             cur = next;
         }
-        uint64_t* ar = acc + (uint64_t)r * batch * 2 * E * N;
-        const uint64_t rq = (uint64_t)r * batch * 2 * ell * N;
+        uint64_t* ar = acc + (uint64_t)r * G * 2 * E * N;
+        const uint64_t rq = (uint64_t)r * G * 2 * ell * N;
 #pragma unroll
         for (int b = 0; b < G; ++b) {
-            if (b >= (int)batch) break;  // uniform
             const uint64_t u0 = f64_to_u64(canon(mac_reduce(h0[b], l0[b], m), m)), u1 = f64_to_u64(canon(mac_reduce(h1[b], l1[b], m), m));
             if (pos < ell) {  // uniform: ciphertext limbs go out packed, 5 bytes a residue
                 const uint64_t e0 = rq + (((uint64_t)b * 2 + 0) * ell + pos) * N + n, e1 = e0 + (uint64_t)ell * N;
@@ -188,31 +193,22 @@ __global__ __launch_bounds__(256, 4) void inner_product_kernel(const Mod* __rest
     }
 }
 
-#define KS_FOR_GATHER_KERNEL(LAUNCH)                                                       \
-    {                                                                                      \
-        const int kind = !src.hi ? 0 : key_words32 ? 1 : 2;                                \
-        switch (src.group * 4 + kind) {                                                    \
-            case 4: LAUNCH(1, uint32_t, false); break;                                     \
-            case 5: LAUNCH(1, uint32_t, true); break;                                      \
-            case 6: LAUNCH(1, uint64_t, true); break;                                      \
-            case 8: LAUNCH(2, uint32_t, false); break;                                     \
-            case 9: LAUNCH(2, uint32_t, true); break;                                      \
-            case 10: LAUNCH(2, uint64_t, true); break;                                     \
-            case 16: LAUNCH(4, uint32_t, false); break;                                    \
-            case 17: LAUNCH(4, uint32_t, true); break;                                     \
-            case 18: LAUNCH(4, uint64_t, true); break;                                     \
-            case 32: LAUNCH(8, uint32_t, false); break;                                    \
-            case 33: LAUNCH(8, uint32_t, true); break;                                     \
-            default: LAUNCH(8, uint64_t, true); break;                                     \
-        }                                                                                  \
-    }
+// LAUNCH(group, word type of the keys, PACKED)
+#define KS_GATHER_32(GV) KS_GATHER_LAUNCH(GV, uint32_t, false)
+#define KS_GATHER_PACKED_32(GV) KS_GATHER_LAUNCH(GV, uint32_t, true)
+#define KS_GATHER_PACKED_64(GV) KS_GATHER_LAUNCH(GV, uint64_t, true)
+#define KS_FOR_GATHER_KERNEL()                                             \
+    if (!src.hi) { KS_FOR_GROUP(src.group, KS_GATHER_32) }                 \
+    else if (key_words32) { KS_FOR_GROUP(src.group, KS_GATHER_PACKED_32) } \
+    else { KS_FOR_GROUP(src.group, KS_GATHER_PACKED_64) }
 
 // bytes a gathered source residue takes
 static double src_bytes(const GatherBundle& g) { return g.hi ? 4.0 + (double)gather_hi_bytes(g.group) / g.group : 4.0; }
 
 void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* acc,
-                          const PackedDigits& accq, uint32_t batch, hipStream_t s, bool key_words32) {
-    if (batch == 0 || rot.n == 0) return;
+                          const PackedDigits& accq, hipStream_t s, bool key_words32) {
+    if (rot.n == 0) return;
+    const uint32_t batch = src.group;
     const uint32_t pl = gather_parts_log(c, lv.E);
     // reads: every raised digit limb per ciphertext once per launch, each rotation's key once; writes: both accumulators of
     // every rotation
@@ -220,11 +216,11 @@ void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& 
     ProfScope ps("inner_product",
                  (src_bytes(src) * batch * lv.ndig * lv.E + (double)rot.n * (wk * 2.0 * lv.ndig * lv.E + (16.0 * (lv.E - lv.ell) + 10.0 * lv.ell) * batch)) * c->N,
                  s);
-#define KS_LAUNCH_IP(GV, WKT, PK)                                                                                                         \
+#define KS_GATHER_LAUNCH(GV, WKT, PK)                                                                                                     \
     hipLaunchKernelGGL((inner_product_kernel<GV, WKT, PK>), dim3(gather_grid(c, lv.E, pl)), dim3(256), 0, s, c->d_mod, lv.ell, lv.E, c->L, \
-                       c->M, c->logN, lv.ndig, pl, src, rot, acc, accq.lo, accq.hi, batch)
-    KS_FOR_GATHER_KERNEL(KS_LAUNCH_IP)
-#undef KS_LAUNCH_IP
+                       c->M, c->logN, lv.ndig, pl, src, rot, acc, accq.lo, accq.hi)
+    KS_FOR_GATHER_KERNEL()
+#undef KS_GATHER_LAUNCH
 }
 
 // Rotate-multiply-accumulate on the extended basis (inner sum of a baby-step giant-step transform with the division by P
@@ -244,7 +240,7 @@ template <int G, typename WK, bool PACKED>
 __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restrict__ mods, const double* __restrict__ Pmod, uint32_t ell,
                                                          uint32_t E, uint32_t L, uint32_t M, uint32_t logN, DigitRanges dg,
                                                          uint32_t parts_log, GatherBundle src, MacRotations rot, uint32_t n_key,
-                                                         uint64_t* __restrict__ u, uint32_t batch, int accumulate) {
+                                                         uint64_t* __restrict__ u, int accumulate) {
     const uint32_t N = 1u << logN;
     const GatherTile tile = gather_tile(E, logN, parts_log);
     if (!tile.valid) return;  // uniform
@@ -255,7 +251,7 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
 #pragma unroll
     for (int b = 0; b < G; ++b) {
         h0[b] = h1[b] = kMacBias;
-        const uint64_t* ub = u + ((uint64_t)min((uint32_t)b, batch - 1) * 2 * E + pos) * N;
+        const uint64_t* ub = u + ((uint64_t)b * 2 * E + pos) * N;
         l0[b] = accumulate ? u64_to_f64(ub[n]) : 0.0;
         l1[b] = accumulate ? u64_to_f64(ub[(uint64_t)E * N + n]) : 0.0;
     }
@@ -348,16 +344,16 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
     }
 #pragma unroll
     for (int b = 0; b < G; ++b) {
-        if (b >= (int)batch) break;  // uniform
         uint64_t* ub = u + ((uint64_t)b * 2 * E + pos) * N + n;
         ub[0] = f64_to_u64(canon(mac_reduce(h0[b], l0[b], m), m));
         ub[(uint64_t)E * N] = f64_to_u64(canon(mac_reduce(h1[b], l1[b], m), m));
     }
 }
 
-void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* u, uint32_t batch,
+void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* u,
                        bool accumulate, hipStream_t s, bool key_words32) {
-    if (batch == 0 || rot.n == 0) return;
+    if (rot.n == 0) return;
+    const uint32_t batch = src.group;
     const uint32_t pl = gather_parts_log(c, lv.E);
     DigitRanges dg;
     dg.ndig = lv.ndig;
@@ -382,11 +378,15 @@ void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src
     const double reads = batch * src_bytes(src) * (lv.ndig * lv.E + lv.ell) + (key_words32 ? 4.0 : 8.0) * (double)rot.n * (2.0 * lv.ndig + 1.0) * lv.E;
     ProfScope ps("rotate_mac", (reads + (double)batch * 16 * lv.E * (accumulate ? 2 : 1)) * c->N, s,
                  (double)rot.n * lv.E * c->N * (4.0 * batch + 6.0) * (2 * lv.ndig + 1));
-#define KS_LAUNCH_MAC(GV, WKT, PK)                                                                                                        \
+#define KS_GATHER_LAUNCH(GV, WKT, PK)                                                                                                     \
     hipLaunchKernelGGL((rotate_mac_kernel<GV, WKT, PK>), dim3(gather_grid(c, lv.E, pl)), dim3(256), 0, s, c->d_mod, c->d_Pmod, lv.ell, lv.E, \
-                       c->L, c->M, c->logN, dg, pl, src, sorted, n_key, u, batch, accumulate ? 1 : 0)
-    KS_FOR_GATHER_KERNEL(KS_LAUNCH_MAC)
-#undef KS_LAUNCH_MAC
+                       c->L, c->M, c->logN, dg, pl, src, sorted, n_key, u, accumulate ? 1 : 0)
+    KS_FOR_GATHER_KERNEL()
+#undef KS_GATHER_LAUNCH
+#undef KS_FOR_GATHER_KERNEL
+#undef KS_GATHER_32
+#undef KS_GATHER_PACKED_32
+#undef KS_GATHER_PACKED_64
 }
 
 // (b1, a1) x (b2, a2) -> d0 = b1 b2, d1 = a1 b2 + a2 b1, d2 = a1 a2.  d2, the polynomial that is key-switched, goes out as

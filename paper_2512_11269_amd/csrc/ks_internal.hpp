@@ -5,6 +5,7 @@
 
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/ks.h"
@@ -247,24 +248,43 @@ struct MacRotations {
 // What the sigma_g gathers of a rotation read, for a group of up to 8 ciphertexts: slabs of N slots, slab j E + pos the
 // finished raised digit j at limb position pos (in the slots of a digit's own positions the limbs of the polynomial
 // itself), slabs ndig E + pos, pos < ell, the limbs of the addend c0 where a caller asked for them.  A slot holds the
-// residues of all `group` ciphertexts side by side (group = 1, 2, 4 or 8, the batch rounded up; the places past the batch
-// repeat its last ciphertext), so that one gathered slot is one contiguous access for every ciphertext that needs it:
-// lo the 32-bit low words, 64 consecutive slots of up to four ciphertexts at a time ([slot / 64][group / 4][slot % 64][4]: a
-// wavefront reads a kilobyte per 16-byte load) and, hi != nullptr, hi[slot] the bits above (moduli are below 2^36) as one 4-bit
-// field per ciphertext in a word of group / 2 bytes (one byte for group 1).  hi == nullptr: moduli below 2^32, lo alone.
+// residues of all `group` ciphertexts side by side, so that one gathered slot is one contiguous access or two for every
+// ciphertext that needs it.  lo: the 32-bit low words, per 64 consecutive slots first the words of up to four ciphertexts, then
+// those of the others (a wavefront reads both parts as whole lines); hi != nullptr: hi[slot] holds the bits above (moduli are
+// below 2^36) as one 4-bit field per ciphertext in a word of gather_hi_bytes(group).  hi == nullptr: moduli below 2^32, lo alone.
+//   The group is the batch, whatever it is.  Rounded up to 1, 2, 4 or 8, five ciphertexts were transformed, written and
+// gathered as eight: one rotate-multiply-accumulate of five, N = 2^16, E = 32, three digits 504 us against 470 (28-bit moduli 447
+// against 417); at N = 2^14 91 against 82.
 struct GatherBundle {
     uint32_t* lo;
     uint8_t* hi;
     uint32_t group;
 };
-inline uint32_t gather_group(uint32_t batch) { return batch > 4 ? 8 : batch > 2 ? 4 : batch; }
-inline uint32_t gather_hi_bytes(uint32_t group) { return group > 1 ? group / 2 : 1; }
+constexpr int kMaxGroup = 8;
+constexpr uint32_t gather_hi_bytes(uint32_t group) { return group > 4 ? 4 : group > 2 ? 2 : 1; }
+template <int G>
+struct SlotLayout {
+    static constexpr int FIRST = G < 4 ? G : 4, REST = G - FIRST;  // low words of a slot in the first and in the second part
+    using HW = std::conditional_t<gather_hi_bytes(G) == 4, uint32_t, std::conditional_t<gather_hi_bytes(G) == 2, uint16_t, uint8_t>>;
+};
+// One launch of a kernel with the group size as a template parameter: LAUNCH(G)
+#define KS_FOR_GROUP(group, LAUNCH)   \
+    switch (group) {                  \
+        case 1: LAUNCH(1); break;     \
+        case 2: LAUNCH(2); break;     \
+        case 3: LAUNCH(3); break;     \
+        case 4: LAUNCH(4); break;     \
+        case 5: LAUNCH(5); break;     \
+        case 6: LAUNCH(6); break;     \
+        case 7: LAUNCH(7); break;     \
+        default: LAUNCH(8); break;    \
+    }
 // Fill a bundle in one launch.  raised: the row half of the forward transform of the raised limbs (`lifted`,
 // [b][ndig][E][N] raw doubles after the column half), all digits.  The polynomials' own limbs d[b][pos] and, c0 != nullptr,
 // the addend's limbs c0[b][pos] (64-bit words with a packed bundle, 32-bit words with a 32-bit one; ps words apart) are
 // copied.
 void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t* lifted, const void* d, const void* c0, uint64_t ps,
-                               const GatherBundle& out, uint32_t batch, bool raised, hipStream_t s);
+                               const GatherBundle& out, bool raised, hipStream_t s);
 
 // acc[r][b][c][pos] = sum_j sigma_{g_r}(src_j)[pos] * key_r[j][c][ext_id(pos)] for every rotation r of `rot` (pt unused);
 // src_j[pos] = slab j E + pos of the bundle.
@@ -272,12 +292,12 @@ void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t*
 // The special limbs of the result go to acc ([r][b][2][E][N], ciphertext limbs left untouched), the ciphertext limbs to
 // accq ([r][b][2][ell][N], packed).
 void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* acc,
-                          const PackedDigits& accq, uint32_t batch, hipStream_t s, bool key_words32 = false);
+                          const PackedDigits& accq, hipStream_t s, bool key_words32 = false);
 
 // u[b][c][pos] (+)= sum_r pt_r[pos] * (sum_j sigma_r(src_j)[pos] key_r[j][c][pos] + [c = 0][pos < ell] P sigma_r(c0)[pos]);
 // src: c1 and its finished raised digits, and c0.  accumulate: add to what u already holds.
 // galois[r] == 1: the term is P (c0, c1) and key[r] is not read; pt[r] == nullptr: the constant 1.
-void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* u, uint32_t batch,
+void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* u,
                        bool accumulate, hipStream_t s, bool key_words32 = false);
 
 // The key-switch chain behind ks_keyswitch / ks_keyswitch_u32 (argument checks included); ws is any device buffer of

@@ -69,33 +69,44 @@ __global__ __launch_bounds__(64) void ntt_fwd_rows(TwTables tw, const Mod* __res
     for (int k = 0; k < 16; ++k) p[j0 + 16 * k] = f64_to_u64(canon(reduce_lazy(v[k], m), m));
 }
 
+template <int W>
+__device__ __forceinline__ void store_slot_words(uint32_t* p, const uint64_t* v) {
+    struct alignas(W == 4 ? 16 : W == 2 ? 8 : 4) Words {
+        uint32_t w[W];
+    } o;
+#pragma unroll
+    for (int k = 0; k < W; ++k) o.w[k] = (uint32_t)v[k];
+    *reinterpret_cast<Words*>(p) = o;
+}
+
 // The bundle the rotation gathers read (layout: GatherBundle), filled in one launch.  A workgroup owns four rows of one slab
 // for all ciphertexts of the group, one wavefront per ciphertext: the first n_new workgroups run the row half of the
 // forward transform on the raised limbs and leave canonical residues in LDS, from where every thread collects whole slots;
 // the others copy the polynomial's own limbs into the slabs of their digits and the addend's limbs behind the digits.
-// Interleaving here, once, makes the gathers of every rotation read one contiguous 36 bytes per slot and digit for eight
-// ciphertexts.
+// Interleaving here, once, makes the gathers of every rotation read 36 bytes per slot and digit for eight ciphertexts in runs
+// of whole lines.
 template <int LOG_R, int G, bool PACKED>
 __global__ __launch_bounds__(64 * G) void gather_bundle_rows(TwTables tw, const Mod* __restrict__ mods, LimbMap map, DigitRanges dg,
                                                              uint32_t ell, uint32_t E, const uint64_t* __restrict__ lifted,
                                                              const void* __restrict__ d, const void* __restrict__ c0, uint64_t d_ps,
-                                                             uint32_t batch, uint32_t n_new, uint32_t* __restrict__ lo,
-                                                             uint8_t* __restrict__ hi) {
+                                                             uint32_t n_new, uint32_t* __restrict__ lo, uint8_t* __restrict__ hi) {
     using WD = std::conditional_t<PACKED, uint64_t, uint32_t>;
-    using HW = std::conditional_t<G == 8, uint32_t, std::conditional_t<G == 4, uint16_t, uint8_t>>;
+    using Layout = SlotLayout<G>;
+    using HW = typename Layout::HW;
     constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R, GROUPS = R / 4, TPB = 64 * G, WAVE_LDS = 4 * kRowPitch;
+    constexpr uint32_t SLOTS = (1024 + TPB - 1) / TPB;  // slots of a thread; where G is no power of two the last one may be past the 1024
     __shared__ double lds[G * WAVE_LDS];
     const uint32_t tid = threadIdx.x;
     uint32_t slab, rg;
-    uint64_t v[16 / G * G];  // the 1024 / TPB slots of this thread, G residues each
+    uint64_t v[SLOTS * G];
     if (blockIdx.x < n_new) {  // uniform
-        const uint32_t lane = tid & 63, j0 = lane & 15, rr = lane >> 4, w = tid >> 6, b = min(w, batch - 1);
+        const uint32_t lane = tid & 63, j0 = lane & 15, rr = lane >> 4, w = tid >> 6;
         const uint32_t idx = blockIdx.x / GROUPS, mod_id = map.mod[idx];
         rg = blockIdx.x - idx * GROUPS;
         slab = map.off[idx];
         const Mod m = mods[mod_id];
         const uint32_t row = rg * 4 + rr;
-        const uint64_t* ip = lifted + ((uint64_t)b * dg.ndig * E + slab) * N + row * 256;
+        const uint64_t* ip = lifted + ((uint64_t)w * dg.ndig * E + slab) * N + row * 256;
         double x[16];
         PassTwiddles t;
 #pragma unroll
@@ -107,8 +118,9 @@ __global__ __launch_bounds__(64 * G) void gather_bundle_rows(TwTables tw, const 
         for (int k = 0; k < 16; ++k) lrow[17 * j0 + k] = canon(reduce_lazy(x[k], m), m);
         __syncthreads();
 #pragma unroll
-        for (uint32_t i = 0; i < 16 / G; ++i) {
+        for (uint32_t i = 0; i < SLOTS; ++i) {
             const uint32_t s = tid + i * TPB, p = s & 255;
+            if (s >= 1024) break;  // the same for a whole wavefront
 #pragma unroll
             for (int g = 0; g < G; ++g) v[i * G + g] = f64_to_u64(lds[g * WAVE_LDS + (s >> 8) * kRowPitch + p + (p >> 4)]);
         }
@@ -120,25 +132,20 @@ __global__ __launch_bounds__(64 * G) void gather_bundle_rows(TwTables tw, const 
         slab = (li < ell ? j : dg.ndig) * E + pos;
         const WD* src = static_cast<const WD*>(li < ell ? d : c0) + (uint64_t)pos * N + rg * 1024 + tid;
 #pragma unroll
-        for (uint32_t i = 0; i < 16 / G; ++i)
+        for (uint32_t i = 0; i < SLOTS; ++i) {
+            if (tid + i * TPB >= 1024) break;
 #pragma unroll
-            for (uint32_t g = 0; g < G; ++g) v[i * G + g] = src[min(g, batch - 1) * d_ps + i * TPB];
+            for (uint32_t g = 0; g < G; ++g) v[i * G + g] = src[g * d_ps + i * TPB];
+        }
     }
 #pragma unroll
-    for (uint32_t i = 0; i < 16 / G; ++i) {
+    for (uint32_t i = 0; i < SLOTS; ++i) {
+        if (tid + i * TPB >= 1024) break;
         const uint64_t slot = (uint64_t)slab * N + rg * 1024 + tid + i * TPB;
         uint32_t h = 0;
-        if constexpr (G >= 4) {
-            uint4* lp = reinterpret_cast<uint4*>(lo + (slot & ~63ull) * G) + (slot & 63);
-#pragma unroll
-            for (int q = 0; q < G / 4; ++q)
-                lp[64 * q] = make_uint4((uint32_t)v[i * G + 4 * q], (uint32_t)v[i * G + 4 * q + 1], (uint32_t)v[i * G + 4 * q + 2],
-                                   (uint32_t)v[i * G + 4 * q + 3]);
-        } else if constexpr (G == 2) {
-            reinterpret_cast<uint2*>(lo)[slot] = make_uint2((uint32_t)v[i * G], (uint32_t)v[i * G + 1]);
-        } else {
-            lo[slot] = (uint32_t)v[i];
-        }
+        uint32_t* block = lo + (slot & ~63ull) * G;
+        store_slot_words<Layout::FIRST>(block + (slot & 63) * Layout::FIRST, v + i * G);
+        if constexpr (Layout::REST > 0) store_slot_words<Layout::REST>(block + 256 + (slot & 63) * Layout::REST, v + i * G + 4);
         if constexpr (PACKED) {
 #pragma unroll
             for (int g = 0; g < G; ++g) h |= (uint32_t)(v[i * G + g] >> 32) << (4 * g);
@@ -284,8 +291,7 @@ void launch_ntt_fwd_rows(const ks_ctx* c, const LimbMap& map, uint64_t* data, ui
 }
 
 void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t* lifted, const void* d, const void* c0, uint64_t ps_words,
-                               const GatherBundle& out, uint32_t batch, bool raised, hipStream_t s) {
-    if (batch == 0) return;
+                               const GatherBundle& out, bool raised, hipStream_t s) {
     const uint32_t n_new = raised ? lv.lifted_map.n : 0, n_copy = c0 ? 2 * lv.ell : lv.ell;
     DigitRanges dg;
     dg.ndig = lv.ndig;
@@ -293,23 +299,24 @@ void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t*
         dg.lo[j] = j < lv.ndig ? lv.digit_lo[j] : 0;
         dg.hi[j] = j < lv.ndig ? lv.digit_hi[j] : 0;
     }
-    const double wb = out.hi ? 4.5 : 4.0;
-    ProfScope ps("gather_bundle_rows", ((8.0 + wb) * n_new + ((out.hi ? 8.0 : 4.0) + wb) * n_copy) * c->N * batch, s);
+    const double wb = 4.0 + (out.hi ? (double)gather_hi_bytes(out.group) / out.group : 0.0);
+    ProfScope ps("gather_bundle_rows", ((8.0 + wb) * n_new + ((out.hi ? 8.0 : 4.0) + wb) * n_copy) * c->N * out.group, s);
     const uint32_t groups = c->N / 1024;
 #define KS_LAUNCH_BUNDLE(LOGR, GV, PK)                                                                                               \
     hipLaunchKernelGGL((gather_bundle_rows<LOGR, GV, PK>), dim3((n_new + n_copy) * groups), dim3(64 * GV), 0, s, c->tw_fwd, c->d_mod,  \
-                       lv.lifted_map, dg, lv.ell, lv.E, lifted, d, c0, ps_words, batch, n_new * groups, out.lo, out.hi)
-#define KS_LAUNCH_G(LOGR, GV)                       \
-    if (out.hi) KS_LAUNCH_BUNDLE(LOGR, GV, true);   \
-    else KS_LAUNCH_BUNDLE(LOGR, GV, false)
-#define KS_LAUNCH(LOGR)                                   \
-    if (out.group == 8) { KS_LAUNCH_G(LOGR, 8); }         \
-    else if (out.group == 4) { KS_LAUNCH_G(LOGR, 4); }    \
-    else if (out.group == 2) { KS_LAUNCH_G(LOGR, 2); }    \
-    else { KS_LAUNCH_G(LOGR, 1); }
+                       lv.lifted_map, dg, lv.ell, lv.E, lifted, d, c0, ps_words, n_new * groups, out.lo, out.hi)
+#define KS_LAUNCH(LOGR)                                              \
+    {                                                                \
+        constexpr int kLogR = LOGR;                                  \
+        if (out.hi) { KS_FOR_GROUP(out.group, KS_LAUNCH_PACKED) }    \
+        else { KS_FOR_GROUP(out.group, KS_LAUNCH_WORDS32) }          \
+    }
+#define KS_LAUNCH_PACKED(GV) KS_LAUNCH_BUNDLE(kLogR, GV, true)
+#define KS_LAUNCH_WORDS32(GV) KS_LAUNCH_BUNDLE(kLogR, GV, false)
     KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
-#undef KS_LAUNCH_G
+#undef KS_LAUNCH_PACKED
+#undef KS_LAUNCH_WORDS32
 #undef KS_LAUNCH_BUNDLE
 }
 
