@@ -51,9 +51,9 @@ KsWorkspace ks_ws_words(const ks_ctx* c, const Level& lv, uint32_t bc) {
 
 // Decompose and raise: d (evaluation domain, `bc` polynomials d_ps words apart) -> lifted [bc][ndig][E][N].
 // The raised limbs stop after the column half of the forward transform (raw doubles); the row half is left to the
-// fused inner product, or to mod_up_for_gather below.
+// fused inner product, or to mod_up_for_gather below.  tile: the conversion kernel of the call (conversion_tile).
 void mod_up(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, uint64_t* coeff, uint64_t* lifted, uint32_t bc,
-            hipStream_t s, bool d_words32 = false) {
+            int tile, hipStream_t s, bool d_words32 = false) {
     const uint64_t N = c->N, coeff_ps = (uint64_t)lv.ell * N, lifted_ps = (uint64_t)lv.ndig * lv.E * N;
     launch_ntt_inv_rows(c, lv.q_map, XformIO{d, coeff, d_ps, coeff_ps, bc}, s, d_words32);
     // the column half also multiplies by N^-1 (D_j/q_i)^-1 and leaves canonical doubles for the conversion
@@ -67,7 +67,7 @@ void mod_up(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, uint
         ops += a * (lv.E - a) * 4.5;
     }
     ops += lv.n_new * (3.0 + 4.0 * (c->logN - 8));
-    launch_bconv_ntt_cols(c, lv.modup, lv.ell + lv.n_new, coeff, coeff_ps, lifted, lifted_ps, bc, s, ops);
+    launch_bconv_ntt_cols(c, lv.modup, lv.ell + lv.n_new, coeff, coeff_ps, lifted, lifted_ps, bc, tile, s, ops);
 }
 
 // Words of workspace the bundle of a chunk of bc ciphertexts takes: low words, then (64-bit operands) the bits above;
@@ -83,8 +83,9 @@ static uint64_t gather_words(const ks_ctx* c, const Level& lv, uint32_t bc, bool
 // mod_up finished for the rotation gathers: `region` (gather_words() words) ends as the bundle they read.  `lifted` is only
 // scratch here.  raised == false: only the own limbs (and c0) are filled in, for a caller whose rotations are all identities.
 static GatherBundle mod_up_for_gather(const ks_ctx* c, const Level& lv, const void* d, const void* c0, uint64_t d_ps, uint64_t* coeff,
-                                      uint64_t* lifted, uint64_t* region, uint32_t bc, hipStream_t s, bool words32, bool raised = true) {
-    if (raised) mod_up(c, lv, d, d_ps, coeff, lifted, bc, s, words32);
+                                      uint64_t* lifted, uint64_t* region, uint32_t bc, int tile, hipStream_t s, bool words32,
+                                      bool raised = true) {
+    if (raised) mod_up(c, lv, d, d_ps, coeff, lifted, bc, tile, s, words32);
     const GatherBundle bundle{reinterpret_cast<uint32_t*>(region),
                               words32 ? nullptr : reinterpret_cast<uint8_t*>(region + gather_lo_words(c, lv, bc, c0 != nullptr)),
                               bc};
@@ -103,13 +104,13 @@ static double moddown_ops(const ks_ctx* c, const Level& lv) {
 // addend_packed (with accq): the addend is there, [b][2][ell][N] packed (addend_bs in elements), instead of at addend.
 void mod_down(const ks_ctx* c, const Level& lv, uint64_t* acc, uint64_t* conv, void* out, uint64_t out_bs,
               const uint64_t* addend, uint64_t addend_bs, uint32_t addend_comps, uint32_t galois, uint32_t bc,
-              bool special_rows_done, hipStream_t s, bool out_words32 = false, const PackedDigits* accq = nullptr,
+              bool special_rows_done, int tile, hipStream_t s, bool out_words32 = false, const PackedDigits* accq = nullptr,
               const PackedDigits* addend_packed = nullptr) {
     const uint64_t N = c->N, acc_ps = (uint64_t)lv.E * N, conv_ps = (uint64_t)lv.ell * N;
     // the fused inner product already ran the row half of the inverse transform on the special limbs
     if (!special_rows_done) launch_ntt_inv_rows(c, lv.special_map, XformIO{acc, acc, acc_ps, acc_ps, 2 * bc}, s);
     launch_ntt_inv_cols(c, lv.special_map, acc, acc_ps, 2 * bc, c->d_moddown_scale, true, true, s);
-    launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, 2 * bc, s, moddown_ops(c, lv));
+    launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s, moddown_ops(c, lv));
     launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, addend, addend_bs, addend_comps, galois, bc, s, nullptr, out_words32, accq,
                                addend_packed);
 }
@@ -316,9 +317,10 @@ int ks::keyswitch_impl(const ks_ctx* c, const void* d, uint32_t ell, const void*
         uint64_t* conv = acc + w.acc;
         const PackedDigits accq = packed_at(conv + w.conv, w.conv);
         const char* dc = static_cast<const char*>(d) + (uint64_t)b0 * d_ps * word;
-        mod_up(c, lv, dc, d_ps, coeff, lifted, bc, s, words32);
+        const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
+        mod_up(c, lv, dc, d_ps, coeff, lifted, bc, tile, s, words32);
         launch_rows_inner_product(c, lv, dc, d_ps, lifted, evk, acc, bc, s, words32, words32, accq);
-        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * out_bs * word, out_bs, nullptr, 0, 0, 1, bc, true, s, words32,
+        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * out_bs * word, out_bs, nullptr, 0, 0, 1, bc, true, tile, s, words32,
                  &accq);
     }
     return finish(words32 ? "ks_keyswitch_u32" : "ks_keyswitch");
@@ -362,12 +364,13 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
         const void* c1 = c0 + (uint64_t)ell * N * word;
         uint64_t* lifted = coeff + w.coeff;
         uint64_t* acc = lifted + w.lifted;
+        const uint32_t group = std::min(n_rot, kRotGroup);
+        const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * group * bc);
         // finished once, shared by every rotation
-        const GatherBundle digits = mod_up_for_gather(c, lv, c1, nullptr, ct_bs, coeff, lifted, region, bc, s, words32);
+        const GatherBundle digits = mod_up_for_gather(c, lv, c1, nullptr, ct_bs, coeff, lifted, region, bc, tile, s, words32);
         // Rotations go in groups: one gather launch forms the accumulators of the whole group (the raised digits then come
         // from memory once per group), the inverse transform and the conversion run over the group as one batch, and only
         // the last kernel, which adds sigma_g(c0) through a rotation's own permutation, runs per rotation.
-        const uint32_t group = std::min(n_rot, kRotGroup);
         uint64_t* conv = acc + (uint64_t)group * w.acc;
         // ciphertext limbs of the group's accumulators, packed: [group][bc][2][ell][N]
         const uint64_t accq_n = w.conv;
@@ -385,7 +388,7 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
             const uint32_t polys = 2 * rot.n * bc;
             launch_ntt_inv_rows(c, lv.special_map, XformIO{acc, acc, acc_ps, acc_ps, polys}, s);
             launch_ntt_inv_cols(c, lv.special_map, acc, acc_ps, polys, c->d_moddown_scale, true, true, s);
-            launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, polys, s, moddown_ops(c, lv));
+            launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, polys, tile, s, moddown_ops(c, lv));
             for (uint32_t r = 0; r < rot.n; ++r) {
                 const PackedDigits accq_r{accq.lo + (uint64_t)r * accq_n, accq.hi + (uint64_t)r * accq_n};
                 launch_rows_moddown_finish(c, lv, nullptr, conv + (uint64_t)r * w.conv,
@@ -462,10 +465,11 @@ static int rotate_mac_impl(const ks_ctx* c, const void* ct, uint32_t ell, const 
         uint64_t* lifted = coeff + w.coeff;
         uint64_t* acc = lifted + w.lifted;
         uint64_t* conv = acc + w.acc;
+        const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
         // finished once, shared by every rotation
-        const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, s, words32);
+        const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, tile, s, words32);
         rotate_mac_all(c, lv, digits, galois, rot_keys, pts, n_rot, acc, false, s, words32);
-        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, s, words32);
+        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, tile, s, words32);
     }
     return finish(words32 ? "ks_rotate_mac_hoisted_u32" : "ks_rotate_mac_hoisted");
 }
@@ -513,15 +517,16 @@ static int bsgs_impl(const ks_ctx* c, const void* ct, uint32_t ell, const uint32
         uint64_t* conv = acc + w.acc;
         uint64_t* acc_outer = conv + w.conv;         // outer sum over the giant steps
         uint64_t* v = acc_outer + w.acc;             // [bc][2][ell][N] inner result of the current giant step (64-bit words)
-        const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, s, words32);
+        const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
+        const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, tile, s, words32);
         for (uint32_t g = 0; g < n2; ++g) {
             rotate_mac_all(c, lv, digits, baby_galois, bkeys, ptv + (size_t)g * n1, n1, acc, false, s, words32);
-            mod_down(c, lv, acc, conv, v, ct_bs, nullptr, 0, 0, 1, bc, false, s);
-            const GatherBundle digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, v, ct_bs, coeff, lifted, region_v, bc, s, false,
+            mod_down(c, lv, acc, conv, v, ct_bs, nullptr, 0, 0, 1, bc, false, tile, s);
+            const GatherBundle digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, v, ct_bs, coeff, lifted, region_v, bc, tile, s, false,
                                                             giant_galois[g] != 1);
             rotate_mac_all(c, lv, digits_v, giant_galois + g, gkeys + g, nullptr, 1, acc_outer, g != 0, s, words32);
         }
-        mod_down(c, lv, acc_outer, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, s,
+        mod_down(c, lv, acc_outer, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, tile, s,
                  words32);
     }
     return finish(words32 ? "ks_bsgs_linear_transform_u32" : "ks_bsgs_linear_transform");
@@ -550,13 +555,14 @@ extern "C" int ks_bsgs_linear_transform_u32(const ks_ctx* c, const uint32_t* ct,
 // inner product has already added the dropped limb's addend and run the row half of the inverse transform on the sources.
 // accq: the ciphertext limbs below ell-1 of the accumulators, packed.  addend: [b][2][ell][N] packed.
 static void mod_down_drop(const ks_ctx* c, const Level& lv, uint64_t* acc, uint64_t* conv, void* out, uint64_t out_bs,
-                          const PackedDigits& addend, uint32_t bc, hipStream_t s, bool merged, bool out_words32, const PackedDigits& accq) {
+                          const PackedDigits& addend, uint32_t bc, int tile, hipStream_t s, bool merged, bool out_words32,
+                          const PackedDigits& accq) {
     const uint64_t N = c->N, acc_ps = (uint64_t)lv.E * N, conv_ps = (uint64_t)lv.ell * N;
     launch_ntt_inv_cols(c, lv.drop_map, acc, acc_ps, 2 * bc, merged ? lv.d_merged_scale : lv.d_rescale_scale, true, true, s);
     if (!merged) launch_rescale_remainder(c, lv, acc, 2 * bc, s);
     const uint32_t n_src = c->K + 1, n_dst = lv.ell - 1;
     const double ops = (double)n_src * n_dst * 4.5 + n_dst * (3.0 + 4.0 * (c->logN - 8));
-    launch_bconv_ntt_cols(c, merged ? lv.merged : lv.rescale, n_src + n_dst, acc, acc_ps, conv, conv_ps, 2 * bc, s, ops);
+    launch_bconv_ntt_cols(c, merged ? lv.merged : lv.rescale, n_src + n_dst, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s, ops);
     const FinishScale fs{lv.d_Dinv, lv.d_qlinv, n_dst};
     launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 2ull * lv.ell * N, 2, 1, bc, s, &fs, out_words32, &accq, &addend);
 }
@@ -589,9 +595,10 @@ static int hmult_impl(const ks_ctx* c, const void* cta, const void* ctb, uint32_
         char* oc = static_cast<char*>(out) + (uint64_t)b0 * out_bs * word;
         launch_tensor_product(c, static_cast<const char*>(cta) + (uint64_t)b0 * ct_bs * word,
                               static_cast<const char*>(ctb) + (uint64_t)b0 * ct_bs * word, d2, dq, ell, bc, s, words32);
-        mod_up(c, lv, d2, d2_ps, coeff, lifted, bc, s);
+        const int tile = conversion_tile(c, lv.modup, bc, merged ? lv.merged : lv.rescale, 2 * bc);
+        mod_up(c, lv, d2, d2_ps, coeff, lifted, bc, tile, s);
         launch_rows_inner_product(c, lv, d2, d2_ps, lifted, rlk, acc, bc, s, false, words32, accq, &dq);
-        mod_down_drop(c, lv, acc, conv, oc, out_bs, dq, bc, s, merged, words32, accq);
+        mod_down_drop(c, lv, acc, conv, oc, out_bs, dq, bc, tile, s, merged, words32, accq);
     }
     if (merged) return finish(words32 ? "hmult_relin_rescale_merged_u32" : "hmult_relin_rescale_merged");
     return finish(words32 ? "hmult_relin_rescale_u32" : "hmult_relin_rescale");

@@ -50,40 +50,45 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? mfma_min_blocks(TL) : 1) v
 
 // Targets per lane half: one gives the most workgroups, three shares the byte-cutting of the sources among the most
 // targets (and keeps the stores of one target under the butterflies of the next).  wide: tiles of 16 columns and 512 threads
-// instead of 8 and 256 at N = 2^16, whole 128-byte lines, for launches of many rounds (see launch_bconv_ntt_cols).
+// instead of 8 and 256 at N = 2^16, whole 128-byte lines, for launches of many rounds and many sources (conversion_tile).
 void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uint64_t* y, uint64_t y_ps, uint64_t* out,
                                 uint64_t out_ps, uint32_t n_polys, int tl, bool wide, hipStream_t s) {
     const uint32_t n_src = plans.shape_src, n_plans = plans.n_plans, max_targets = plans.max_targets;
     const BConvPlan* d_plans = plans.d_plans;
     const uint32_t nm = (n_src + 5) / 6, nps = (n_src + 2 * nm - 1) / (2 * nm);
     tl = (c->logN == 13 || c->logN == 14) || tl < 2 ? 1 : 3;  // built shapes: one or three targets per lane half
-    const int waves = wide && c->logN == 16 && tl == 3 ? 8 : 4;
+    const int waves = wide && c->logN == 16 && tl == 3 && n_src > 4 ? 8 : 4;
     const uint32_t tiles = c->N / (512 * waves);
     const uint32_t n_subsets = (max_targets + 2 * tl - 1) / (2 * tl);
     const dim3 grid(tiles, n_plans * n_subsets, n_polys), block(64 * waves);
 #define KS_LAUNCH_MFMA(LOGR, TLV, NMV, NPSV, WV)                                                                                        \
     hipLaunchKernelGGL((bconv_mfma_ntt_cols<LOGR, TLV, NMV, NPSV, WV>), grid, block, 0, s, c->d_tw_fwd, d_plans, plans.meta, y, y_ps, \
                        out, out_ps, n_subsets, grid.x * grid.y * grid.z > 512)
-#define KS_MFMA_SHAPE(LOGR, TLV, WV)                                      \
-    if (nm == 1 && nps == 1) KS_LAUNCH_MFMA(LOGR, TLV, 1, 1, WV);         \
-    else if (nm == 1 && nps == 2) KS_LAUNCH_MFMA(LOGR, TLV, 1, 2, WV);    \
-    else if (nm == 1) KS_LAUNCH_MFMA(LOGR, TLV, 1, 3, WV);                \
-    else if (nm == 2 && nps == 2) KS_LAUNCH_MFMA(LOGR, TLV, 2, 2, WV);    \
-    else if (nm == 2) KS_LAUNCH_MFMA(LOGR, TLV, 2, 3, WV);                \
-    else KS_LAUNCH_MFMA(LOGR, TLV, 3, 3, WV)
-#define KS_LAUNCH_TL(LOGR)                      \
-    if (tl == 1) { KS_MFMA_SHAPE(LOGR, 1, 4); } \
-    else { KS_MFMA_SHAPE(LOGR, 3, 4); }
-    // every shape for the degrees that the rule of launch_bconv_ntt_cols takes here and for the smallest one (which the parity
+#define KS_MFMA_SHAPE(LOGR, TLV)                                       \
+    if (nm == 1 && nps == 1) KS_LAUNCH_MFMA(LOGR, TLV, 1, 1, 4);       \
+    else if (nm == 1 && nps == 2) KS_LAUNCH_MFMA(LOGR, TLV, 1, 2, 4);  \
+    else if (nm == 1) KS_LAUNCH_MFMA(LOGR, TLV, 1, 3, 4);              \
+    else if (nm == 2 && nps == 2) KS_LAUNCH_MFMA(LOGR, TLV, 2, 2, 4);  \
+    else if (nm == 2) KS_LAUNCH_MFMA(LOGR, TLV, 2, 3, 4);              \
+    else KS_LAUNCH_MFMA(LOGR, TLV, 3, 3, 4)
+#define KS_LAUNCH_TL(LOGR)                       \
+    {                                            \
+        if (tl == 1) { KS_MFMA_SHAPE(LOGR, 1); } \
+        else { KS_MFMA_SHAPE(LOGR, 3); }         \
+    }
+    // every shape for the degrees that conversion_tile takes here and for the smallest one (which the parity
     // sweeps run on); the degrees in between take one target per lane half
     switch (c->logN) {
-        case 12: KS_LAUNCH_TL(4); break;
-        case 13: KS_MFMA_SHAPE(5, 1, 4); break;
-        case 14: KS_MFMA_SHAPE(6, 1, 4); break;
-        case 15: KS_LAUNCH_TL(7); break;
+        case 12: KS_LAUNCH_TL(4) break;
+        case 13: KS_MFMA_SHAPE(5, 1); break;
+        case 14: KS_MFMA_SHAPE(6, 1); break;
+        case 15: KS_LAUNCH_TL(7) break;
         default:
-            if (waves == 8) { KS_MFMA_SHAPE(8, 3, 8); }
-            else KS_LAUNCH_TL(8)
+            if (waves == 4) KS_LAUNCH_TL(8)
+            else if (nm == 1) KS_LAUNCH_MFMA(8, 3, 1, 3, 8);
+            else if (nm == 2 && nps == 2) KS_LAUNCH_MFMA(8, 3, 2, 2, 8);
+            else if (nm == 2) KS_LAUNCH_MFMA(8, 3, 2, 3, 8);
+            else KS_LAUNCH_MFMA(8, 3, 3, 3, 8);
             break;
     }
 #undef KS_LAUNCH_TL

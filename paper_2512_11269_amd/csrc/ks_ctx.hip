@@ -147,6 +147,9 @@ hipError_t upload_plans(const BConvPlan* host_plans, uint32_t n_plans, uint32_t 
     out->shape_src = shape_src;
     for (uint32_t j = 0; j < n_plans; ++j) {
         out->max_targets = std::max(out->max_targets, host_plans[j].n_dst);
+        out->targets += host_plans[j].n_dst;
+        out->sixes += (host_plans[j].n_dst + 5) / 6;
+        out->products += host_plans[j].n_src * host_plans[j].n_dst;
         out->meta.plan[j].n_dst = host_plans[j].n_dst;
         for (int k = 0; k < kMfmaSlots * 3; ++k) out->meta.plan[j].src_limb[k] = host_plans[j].mfma_src_limb[k];
     }

@@ -181,34 +181,51 @@ __global__ __launch_bounds__(256) void bconv_ntt_cols(const double* __restrict__
     }
 }
 
+// Which kernel the two conversions of a call take: 0 vector, 8 or 16 matrix cores with tiles of 8 or 16 columns.  One answer
+// for both: the code of a kernel that ran a moment ago is still in the caches, so a call that mixes them pays 1-2 us at
+// small sizes and 5-8 where its data exceed the memory-side cache (three key-switches 8 -> 3 x 24 and 8 -> 24, N = 2^16,
+// 36-bit: vector 248 us, matrix cores in ModUp only 246, in ModDown only 242, in both 230).
+//   G counts the matrix-core kernel's workgroups, six targets and 2048 positions each, of which 512 run at once.  Their cost
+// hardly depends on the sources; the vector kernel takes one instruction per source and piece of a residue (three pieces,
+// two for moduli below 2^32) and some for the transform.  So the line is drawn by the load, the vector instructions that a
+// group of six targets replaces, 20 per target besides the products: many sources and full groups (20 targets take four, 24
+// too) favour the matrix cores.  The lines come from key-switches of 42 parameter sets, 1 to 8 ciphertexts, and hoisted
+// rotations of 20, in both word sizes with every pair of kernels.  Times of calls in us, vector / 8 columns / 16 columns:
+//   N = 2^16, 36-bit moduli.  4 -> 16 (load 171), 6 ciphertexts: 305 / 314; 5 -> 20 (175), 2: 169 / 157, 4: 280 / 274;
+// 8 -> 24 (264), 1: 103 / 98, 4: 302 / 287; 12 -> 36 (336), 2: 272 / 241.  28-bit: 4 -> 16 (149), 6: 264 / 279; 8 -> 24
+// (216), 2: 155 / 145, 7: 425 / 416.  In a single round one workgroup's chain is what counts, so the sources alone decide:
+// 36-bit 4 -> 12 70 / 71, 5 -> 5 58 / 56, 7 -> 7 63 / 60, 10 -> 20 91 / 87; 28-bit 7 -> 7 58 / 59, 10 -> 20 82 / 83,
+// 12 -> 18 84 / 84.
+//   16 columns are whole lines, but one workgroup of 512 threads per compute unit that works in step: ahead when a launch
+// has six rounds or more.  8 -> 24, 8 ciphertexts (G = 3072): 550 / 545 / 546; 12 -> 36 (4608): 906 / 903 / 887; four
+// rotations of them (G of ModDown 8192 and 12288): 1663 / 1697 / 1614 and 2685 / 2730 / 2618, 28-bit 1492 / 1547 / 1464 and
+// 2423 / 2508 / 2379, but at G = 3456 582 / 587 / 585.  10 -> 20 (250), whose last group of six is mostly empty:
+// 1477 / 1580 / 1497, hence the fill.
+//   N = 2^15, 36-bit: 3 -> 9 (130), 8 ciphertexts: 123 / 120, 7: +3.5 %; 7 -> 21 (215), 4: 158 / 139; 28-bit: 3 -> 9 (117),
+// 7: +5.6 %; 4 -> 12 (168), 4: 82 / 83, 8: 137 / 132; 5 -> 20 (150), 4: 140 / 133.  Where a launch has just more than 256 or
+// 512 workgroups a few compute units do twice the work of the others: 3 -> 9, 3: 70 / 74; 13 -> 13 (256), 6: 130 / 134.
+//   Below N = 2^15 launches are at their floor and the vector kernel is 0-1 us ahead.
+int conversion_tile(const ks_ctx* c, const PlanSet& up, uint32_t up_polys, const PlanSet& down, uint32_t down_polys) {
+    if (c->logN < 15) return 0;
+    const uint64_t tiles = c->N / 2048, g_up = tiles * up.sixes * up_polys, g_down = tiles * down.sixes * down_polys;
+    const uint64_t sixes = up.sixes + 2 * down.sixes, targets = up.targets + 2 * down.targets;
+    const uint64_t load = 20 * targets + c->pieces * (up.products + 2ull * down.products);   // of one ciphertext
+    const bool two_pieces = c->pieces == 2;
+    const auto uneven = [](uint64_t g) { return (g > 256 && g <= 300) || (g > 512 && g <= 600); };
+    const uint64_t extra = uneven(g_up) || uneven(g_down) ? 45 : 0;
+    if (c->logN == 15) return load >= (extra + (two_pieces && g_up + g_down <= 1024 ? 160 : 132)) * sixes ? 8 : 0;
+    if (g_up + g_down <= 512) return load >= (two_pieces ? 44 : 35) * targets ? 8 : 0;   // sources x pieces of 24 or 15
+    if (std::max(g_up, g_down) < 3072) return load >= (extra + 173) * sixes ? 8 : 0;
+    const bool full = targets * 10 >= sixes * 54;
+    return full && load >= 220 * sixes && (!two_pieces || std::max(g_up, g_down) >= 4096) ? 16 : 0;
+}
+
 void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint64_t* y, uint64_t y_ps,
-                           uint64_t* out, uint64_t out_ps, uint32_t n_polys, hipStream_t s, double ops_per_coeff) {
+                           uint64_t* out, uint64_t out_ps, uint32_t n_polys, int tile, hipStream_t s, double ops_per_coeff) {
     const uint32_t n_plans = plans.n_plans, max_targets = plans.max_targets;
     const BConvPlan* d_plans = plans.d_plans;
     if (n_polys == 0 || n_plans == 0) return;
-    // Which kernel.  G counts the matrix-core kernel's workgroups (six targets and 2048 positions each), of which 512 run at once.
-    //   The matrix cores win at N >= 2^15 with 64-bit words (three pieces in the vector kernel): 8 -> 3 x 24 moduli at N = 2^16
-    // 25.9 -> 22.4 us for one polynomial (G = 384), 66.8 -> 55.5 for four; 13 -> 34, eight: 83.8 -> 66.8; 7 -> 20 at 2^15,
-    // sixteen: 43.9 -> 35.2.  Below 2^15 launches are at their floor and the vector kernel is 0-1 us ahead.
-    //   Up to three sources cost the vector kernel less than the byte sums do (3 -> 4 x 12, eight: 59.8 against 61.5 us), and a
-    // second round that is almost empty costs more than a few sources save (7 -> 3 x 21 at 2^15, G = 576: 24.9 against 27.7; with
-    // twelve sources, same G: 42.2 against 36.3).
-    //   Moduli below 2^32 (two pieces): the vector kernel is ahead once its launch has a few rounds (9 -> 20, sixteen, G = 2048: 66.8
-    // against 71.0 us; 13 -> 34, G = 3072: 138.4 against 149.6), until whole-line tiles take the lead (12 -> 3 x 36, G = 4608:
-    // 220.7 against 213.8; 8 -> 24, G = 8192: 383 against 348).
-    //   Whole-line tiles (one workgroup of 512 threads per compute unit, in step) pay from six rounds on: G = 3072, 13 -> 34: 151.4
-    // with 8 columns, 138.3 with 16, 148.7 vector; G = 2304, 8 -> 3 x 24: 78.0, 89.0, 89.1.
-    uint64_t subsets = 0;
-    for (uint32_t j = 0; j < n_plans; ++j) subsets += (plans.meta.plan[j].n_dst + 5) / 6;
-    const uint64_t G = (uint64_t)(c->N / 2048) * subsets * n_polys;
-    const bool two_pieces = c->pieces == 2, wide = G >= (two_pieces ? 4096 : 3072);
-    bool matrix;
-    if (c->logN < 15) matrix = false;
-    else if (plans.shape_src < 4) matrix = G <= 512 && c->logN == 16;
-    else if (G <= 512) matrix = true;
-    else if (G <= 640 && plans.shape_src < 8) matrix = false;
-    else matrix = !two_pieces || G < 2048 || wide;
-    const int kernel = c->opt[KS_OPT_BCONV_KERNEL] ? c->opt[KS_OPT_BCONV_KERNEL] : (matrix ? 2 : 1);
+    const int kernel = c->opt[KS_OPT_BCONV_KERNEL] ? c->opt[KS_OPT_BCONV_KERNEL] : (tile ? 2 : 1);
     if (kernel == 2) {
         // algorithmic fp64 / integer vector work per coefficient of this kernel: per target 9 to recombine and reduce the
         // five sums and 35 for the column half; per source 2 to cut it into bytes (the contraction itself runs on the
@@ -217,7 +234,7 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
         for (uint32_t j = 0; j < n_plans; ++j) vec_ops += plans.meta.plan[j].n_dst * 44.0 + plans.shape_src * 2.0;
         ProfScope ps("bconv_mfma_ntt_cols", (double)limbs_moved_per_poly * n_polys * c->N * 8.0, s, vec_ops * n_polys * c->N);
         const int tl = c->opt[KS_OPT_BCONV_TARGETS] >= 1 && c->opt[KS_OPT_BCONV_TARGETS] <= 3 ? c->opt[KS_OPT_BCONV_TARGETS] : 3;
-        launch_bconv_mfma_ntt_cols(c, plans, y, y_ps, out, out_ps, n_polys, tl, wide, s);
+        launch_bconv_mfma_ntt_cols(c, plans, y, y_ps, out, out_ps, n_polys, tl, tile == 16, s);
         return;
     }
     // Targets per workgroup: fewer targets = more workgroups but more re-reads and re-splits of the sources.  Four (with

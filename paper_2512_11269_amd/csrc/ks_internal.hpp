@@ -75,6 +75,7 @@ struct PlanSet {
     uint32_t n_plans = 0;
     uint32_t max_targets = 0;      // largest target count of a plan
     uint32_t shape_src = 0;        // source count the matrix-core operand slots were laid out for (the largest of the plans)
+    uint32_t targets = 0, sixes = 0, products = 0;  // sums over the plans: targets, groups of six targets, sources x targets
     LaunchMeta meta{};
 };
 
@@ -187,10 +188,12 @@ void launch_ntt_inv_rows(const ks_ctx* c, const LimbMap& map, const XformIO& io,
 void launch_ntt_inv_cols(const ks_ctx* c, const LimbMap& map, uint64_t* data, uint64_t ps_words, uint32_t n_polys,
                          const double* scale_tab, bool scale_by_idx, bool out_f64, hipStream_t s);
 
-// Fused base conversion + column half of the forward transform.  y: pre-scaled canonical doubles
+// The kernel of both conversions of a call (ks_fused.hip): 0 vector, 8 or 16 matrix cores with tiles of that many columns.
+int conversion_tile(const ks_ctx* c, const PlanSet& up, uint32_t up_polys, const PlanSet& down, uint32_t down_polys);
+// Fused base conversion + column half of the forward transform, with the kernel `tile` (conversion_tile).  y: pre-scaled canonical doubles
 // y_i = [x_i N^-1 (D/s_i)^-1]; out: raw doubles ready for the row half.  One plan per blockIdx.y group.
 void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint64_t* y, uint64_t y_ps,
-                           uint64_t* out, uint64_t out_ps, uint32_t n_polys, hipStream_t s, double ops_per_coeff = 0.0);
+                           uint64_t* out, uint64_t out_ps, uint32_t n_polys, int tile, hipStream_t s, double ops_per_coeff = 0.0);
 // The same conversion + column half on the matrix cores (ks_bconv_mfma.hip); tl = targets per lane half, 1..3.
 void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uint64_t* y, uint64_t y_ps, uint64_t* out,
                                 uint64_t out_ps, uint32_t n_polys, int tl, bool wide, hipStream_t s);

@@ -170,3 +170,32 @@ def test_conversion_tiles_of_large_launches(logN, L, Kk, dnum, batch):
         K.ks_keyswitch(st.ctx, d, L, evk, out[-1], ws)
     assert torch.equal(out[0], out[1])
     assert_equal(out[0][-1:], st.ref.keyswitch(host(d[-1:]), host(evk), L))
+
+
+@pytest.mark.parametrize("bits,logN,L,Kk,dnum,batch,want", [
+    (36, 16, 16, 4, 4, 6, "vector"),     # 4 -> 16: few sources, groups of six targets that are not full
+    (28, 16, 16, 4, 4, 6, "vector"),
+    (36, 16, 24, 8, 3, 1, "matrix"),
+    (28, 16, 24, 8, 3, 7, "matrix"),
+    (28, 16, 36, 12, 3, 6, "vector"),    # seven rounds of workgroups: too many for 8 columns, too few for 16
+    (36, 16, 36, 12, 3, 8, "matrix"),
+    (36, 16, 3, 3, 1, 2, "vector"),      # a single round
+    (36, 15, 21, 7, 3, 3, "matrix"),
+    (36, 15, 9, 3, 3, 3, "vector"),      # 288 workgroups on 256 compute units
+    (36, 14, 12, 4, 3, 3, "vector"),
+])
+def test_conversion_kernel_that_is_chosen(bits, logN, L, Kk, dnum, batch, want):
+    """Both conversions of a call run on the kernel that measured faster at this size; its outputs are those of the other one."""
+    st = Setup(logN, L, Kk, dnum, bits=bits)
+    evk = st.uniform(44, 1, (dnum, 2), list(range(L + Kk)))
+    d = st.uniform(44, 2, (batch,), list(range(L)))
+    ws = workspace(st.ctx, K.KS_OP_KEYSWITCH, L, batch)
+    out = [torch.full((batch, 2, L, st.N), -1, dtype=torch.int64, device="cuda") for _ in range(2)]
+    K.ks_profile_enable(True)
+    K.ks_keyswitch(st.ctx, d, L, evk, out[0], ws)
+    launches = {r["kernel"]: r["launches"] for r in K.ks_profile_report()}
+    K.ks_profile_enable(False)
+    assert launches.get("bconv_mfma_ntt_cols" if want == "matrix" else "bconv_ntt_cols") == 2
+    _select(st, 1 if want == "matrix" else 2, 0)
+    K.ks_keyswitch(st.ctx, d, L, evk, out[1], ws)
+    assert torch.equal(out[0], out[1])
