@@ -93,8 +93,7 @@ __device__ __forceinline__ double slot_f64(const SlotRaw<G>& r, int g) {
 // (position, half) are the bundle's slots of that position and half: 1.2 MB per digit for eight ciphertexts at N = 2^16,
 // where the whole limb position of a chunk is 7 MB.  Consecutive workgroup ids go to the eight XCDs in turn, each with a
 // 4 MB L2 of its own, so unit u = (position, part) goes to the workgroups of XCD u % 8, which walk one unit after the other:
-// every rotation but the first finds its sources in that L2.  parts_log: parts per position, 2 unless that would leave
-// XCDs idle in the last round of units.
+// every rotation but the first finds its sources in that L2.  parts_log: gather_parts_log.
 struct GatherTile {
     uint32_t pos, n;
     bool valid;
@@ -107,11 +106,6 @@ __device__ __forceinline__ GatherTile gather_tile(uint32_t E, uint32_t logN, uin
     t.pos = unit >> parts_log;
     t.n = (((unit & ((1u << parts_log) - 1)) * per_unit + local % per_unit) << 8) + threadIdx.x;
     return t;
-}
-static uint32_t gather_parts_log(const ks_ctx* c, uint32_t E) {
-    uint32_t pl = 1;
-    while (pl < 4 && ((E << pl) % 8) * 16 > (E << pl)) ++pl;  // a last round of units that is not full costs at most 1/16
-    return pl;
 }
 static uint32_t gather_grid(const ks_ctx* c, uint32_t E, uint32_t parts_log) {
     return (((E << parts_log) + 7) / 8) * 8 * ((c->N / 256) >> parts_log);
@@ -209,7 +203,7 @@ void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& 
                           const PackedDigits& accq, hipStream_t s, bool key_words32) {
     if (rot.n == 0) return;
     const uint32_t batch = src.group;
-    const uint32_t pl = gather_parts_log(c, lv.E);
+    const uint32_t pl = gather_parts_log(lv.E);
     // reads: every raised digit limb per ciphertext once per launch, each rotation's key once; writes: both accumulators of
     // every rotation
     const double wk = key_words32 ? 4.0 : 8.0;
@@ -354,7 +348,7 @@ void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src
                        bool accumulate, hipStream_t s, bool key_words32) {
     if (rot.n == 0) return;
     const uint32_t batch = src.group;
-    const uint32_t pl = gather_parts_log(c, lv.E);
+    const uint32_t pl = gather_parts_log(lv.E);
     DigitRanges dg;
     dg.ndig = lv.ndig;
     for (uint32_t j = 0; j < kMaxDigits; ++j) {

@@ -15,6 +15,13 @@ struct DigitRanges {
     uint32_t lo[8], hi[8];
 };
 
+// log2 of the parts into which the rotation gathers cut each of the E limb positions (gather_tile).  Halves keep a part's
+// sources to one XCD's L2; where E % 4 is 1 or 2, halves leave 6 or 4 of the eight XCDs idle in the last round, and quarters
+// pay for sources that two XCDs then read (eighths only in few rounds).  Sixteen rotation-multiplications of eight
+// ciphertexts, N = 2^16, halves -> quarters: E = 10 226 -> 212 us, 17 566 -> 553, 26 1050 -> 1026, but 12 268 -> 271,
+// 23 730 -> 738, 32 1274 -> 1288; E = 9 in eighths 207 -> 189, quarters 193; 13 -4.6 and -5.4 %, at N = 2^14 +3.8 and -1.3 %.
+constexpr uint32_t gather_parts_log(uint32_t E) { return E % 4 == 1 ? (E < 12 ? 3 : 2) : E % 4 == 2 ? 2 : 1; }
+
 // Slot permutation of sigma_g (X -> X^g) on a bit-reversed evaluation vector: slot n holds the point
 // psi^(2 brv(n) + 1); sigma_g(a) evaluated there is a evaluated at that point raised to g.
 __device__ __forceinline__ uint32_t galois_source_slot(uint32_t n, uint32_t g, uint32_t logN) {

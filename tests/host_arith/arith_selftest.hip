@@ -4,7 +4,7 @@
 #include <stdlib.h>
 #include <math.h>
 #include <stdint.h>
-#include "../../paper_2512_11269_amd/csrc/ks_device.hpp"
+#include "../../paper_2512_11269_amd/csrc/ks_tiles.hpp"
 
 using namespace ks;
 typedef __int128 i128;
@@ -191,7 +191,16 @@ static void check_prime(uint64_t p) {
     }
 }
 
+// The units of the rotation gathers go to eight XCDs in rounds: the last round leaves at most an eighth of all places idle.
+static void check_gather_parts() {
+    for (uint32_t E = 4; E <= 255; ++E) {
+        const uint32_t units = E << gather_parts_log(E), places = (units + 7) / 8 * 8;
+        CHECK((places - units) * 8 <= places, "%u limb positions: %u of %u places idle", E, places - units, places);
+    }
+}
+
 int main() {
+    check_gather_parts();
     const uint64_t primes[] = {68718428161ull /* largest, N=2^16 */, 68617633793ull /* 60th, N=2^16 */, 68719403009ull /* largest, N=2^12 */,
                                68718764033ull /* 6th, N=2^12 */, 34359754753ull /* a 35-bit prime = 1 mod 2^17 */,
                                // the rest of the admitted range: the paper's word size, the top of the 32-bit range, a tiny modulus
