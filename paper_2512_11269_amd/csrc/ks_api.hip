@@ -80,16 +80,24 @@ static uint64_t gather_words(const ks_ctx* c, const Level& lv, uint32_t bc, bool
     return gather_lo_words(c, lv, bc, with_c0) + (words32 ? 0 : slots * gather_hi_bytes(bc) / 8);
 }
 
+// Rotations from which on the bundle holds the addend c0; below, copying it there costs more than gathering it from the
+// ciphertexts (24 limbs of 100, written and read back).  Rotate-multiply-accumulate, N = 2^16, E = 32, three digits, copied -> gathered:
+// one rotation of 1, 3 and 8 ciphertexts 131 -> 128, 293 -> 282 and 688 -> 665 us (28-bit moduli 117 -> 116, 261 -> 253,
+// 622 -> 607); five -3.2, -2.1 and -0.5 %; six -2.4, -1.9 and +0.6 %; sixteen +0.2, +0.1 and +3.7 %.
+constexpr uint32_t kC0InBundle = 6;
+
 // mod_up finished for the rotation gathers: `region` (gather_words() words) ends as the bundle they read.  `lifted` is only
 // scratch here.  raised == false: only the own limbs (and c0) are filled in, for a caller whose rotations are all identities.
+// n_rot: rotations that read the bundle.
 static GatherBundle mod_up_for_gather(const ks_ctx* c, const Level& lv, const void* d, const void* c0, uint64_t d_ps, uint64_t* coeff,
-                                      uint64_t* lifted, uint64_t* region, uint32_t bc, int tile, hipStream_t s, bool words32,
+                                      uint64_t* lifted, uint64_t* region, uint32_t bc, uint32_t n_rot, int tile, hipStream_t s, bool words32,
                                       bool raised = true) {
     if (raised) mod_up(c, lv, d, d_ps, coeff, lifted, bc, tile, s, words32);
+    const bool with_c0 = c0 && n_rot >= kC0InBundle;
     const GatherBundle bundle{reinterpret_cast<uint32_t*>(region),
-                              words32 ? nullptr : reinterpret_cast<uint8_t*>(region + gather_lo_words(c, lv, bc, c0 != nullptr)),
-                              bc};
-    launch_gather_bundle_rows(c, lv, lifted, d, c0, d_ps, bundle, raised, s);
+                              words32 ? nullptr : reinterpret_cast<uint8_t*>(region + gather_lo_words(c, lv, bc, with_c0)),
+                              bc, with_c0 ? nullptr : c0, d_ps};
+    launch_gather_bundle_rows(c, lv, lifted, d, with_c0 ? c0 : nullptr, d_ps, bundle, raised, s);
     return bundle;
 }
 
@@ -128,8 +136,8 @@ extern "C" size_t ks_workspace_bytes(const ks_ctx* c, int op, uint32_t ell, uint
         case KS_OP_ROTATE_HOISTED:
         case KS_OP_ROTATE_HOISTED_U32:
             if (n_rot == 0) return 0;
-            // the gathers' sources (rotate-multiply-accumulate keeps c0 among them)
-            words += gather_words(c, lv, bc, true, op == KS_OP_ROTATE_HOISTED_U32);
+            // the gathers' sources (rotate-multiply-accumulate may keep c0 among them)
+            words += gather_words(c, lv, bc, n_rot >= kC0InBundle, op == KS_OP_ROTATE_HOISTED_U32);
             // accumulators and converted limbs for a whole group of rotations; the ciphertext limbs of a group's accumulators, packed
             words += (uint64_t)(std::min(n_rot, kRotGroup) - 1) * bc * (2 * lv.E + 2 * ell) * N;
             words += (uint64_t)(std::min(n_rot, kRotGroup) - 1) * ks_ws_words(c, lv, bc).accq;
@@ -139,7 +147,8 @@ extern "C" size_t ks_workspace_bytes(const ks_ctx* c, int op, uint32_t ell, uint
             // accumulators of the outer level, inner result [bc][2][ell], the gathers' sources of both levels (the
             // inner results are 64-bit words either way)
             const KsWorkspace w = ks_ws_words(c, lv, bc);
-            words += w.acc + (uint64_t)bc * 2 * ell * N + gather_words(c, lv, bc, true, op == KS_OP_BSGS_U32) + gather_words(c, lv, bc, true, false);
+            words += w.acc + (uint64_t)bc * 2 * ell * N + gather_words(c, lv, bc, true, op == KS_OP_BSGS_U32) +
+                     gather_words(c, lv, bc, false, false);
             break;
         }
         case KS_OP_HMULT_RELIN_RESCALE:
@@ -367,7 +376,7 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
         const uint32_t group = std::min(n_rot, kRotGroup);
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * group * bc);
         // finished once, shared by every rotation
-        const GatherBundle digits = mod_up_for_gather(c, lv, c1, nullptr, ct_bs, coeff, lifted, region, bc, tile, s, words32);
+        const GatherBundle digits = mod_up_for_gather(c, lv, c1, nullptr, ct_bs, coeff, lifted, region, bc, n_rot, tile, s, words32);
         // Rotations go in groups: one gather launch forms the accumulators of the whole group (the raised digits then come
         // from memory once per group), the inverse transform and the conversion run over the group as one batch, and only
         // the last kernel, which adds sigma_g(c0) through a rotation's own permutation, runs per rotation.
@@ -458,16 +467,16 @@ static int rotate_mac_impl(const ks_ctx* c, const void* ct, uint32_t ell, const 
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
         const KsWorkspace w = ks_ws_words(c, lv, bc);
-        // the gathers read c0, c1 and its finished raised digits from a compact bundle
+        // the gathers read c1 and its finished raised digits, and c0 for many rotations, from a compact bundle
         const char* c0 = static_cast<const char*>(ct) + (uint64_t)b0 * ct_bs * word;
         uint64_t* region = static_cast<uint64_t*>(ws);
-        uint64_t* coeff = region + gather_words(c, lv, bc, true, words32);
+        uint64_t* coeff = region + gather_words(c, lv, bc, n_rot >= kC0InBundle, words32);
         uint64_t* lifted = coeff + w.coeff;
         uint64_t* acc = lifted + w.lifted;
         uint64_t* conv = acc + w.acc;
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
         // finished once, shared by every rotation
-        const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, tile, s, words32);
+        const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, n_rot, tile, s, words32);
         rotate_mac_all(c, lv, digits, galois, rot_keys, pts, n_rot, acc, false, s, words32);
         mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, tile, s, words32);
     }
@@ -511,18 +520,18 @@ static int bsgs_impl(const ks_ctx* c, const void* ct, uint32_t ell, const uint32
         const char* c0 = static_cast<const char*>(ct) + (uint64_t)b0 * ct_bs * word;
         uint64_t* region = static_cast<uint64_t*>(ws);   // sources of the inner level, shared by every baby step of every giant step
         uint64_t* region_v = region + gather_words(c, lv, bc, true, words32);   // sources of the outer level: the current inner result
-        uint64_t* coeff = region_v + gather_words(c, lv, bc, true, false);
+        uint64_t* coeff = region_v + gather_words(c, lv, bc, false, false);
         uint64_t* lifted = coeff + w.coeff;          // scratch of a ModUp
         uint64_t* acc = lifted + w.lifted;           // inner sum of the current giant step
         uint64_t* conv = acc + w.acc;
         uint64_t* acc_outer = conv + w.conv;         // outer sum over the giant steps
         uint64_t* v = acc_outer + w.acc;             // [bc][2][ell][N] inner result of the current giant step (64-bit words)
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
-        const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, tile, s, words32);
+        const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, n1 * n2, tile, s, words32);
         for (uint32_t g = 0; g < n2; ++g) {
             rotate_mac_all(c, lv, digits, baby_galois, bkeys, ptv + (size_t)g * n1, n1, acc, false, s, words32);
             mod_down(c, lv, acc, conv, v, ct_bs, nullptr, 0, 0, 1, bc, false, tile, s);
-            const GatherBundle digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, v, ct_bs, coeff, lifted, region_v, bc, tile, s, false,
+            const GatherBundle digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, v, ct_bs, coeff, lifted, region_v, bc, 1, tile, s, false,
                                                             giant_galois[g] != 1);
             rotate_mac_all(c, lv, digits_v, giant_galois + g, gkeys + g, nullptr, 1, acc_outer, g != 0, s, words32);
         }

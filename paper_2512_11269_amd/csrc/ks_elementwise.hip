@@ -307,25 +307,39 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
         auto plaintext = [&](uint32_t r) { return rot.pt[r] ? static_cast<const WK*>(rot.pt[r])[(uint64_t)mid * N + n] : (WK)1; };
         uint32_t own = 0;
         while (own + 1 < dg.ndig && pos >= dg.hi[own]) ++own;
-        constexpr uint32_t AHEAD = 2;  // rotations in flight
-        SlotRaw<G> x[AHEAD];
-        WK w[AHEAD];
-        auto fetch0 = [&](uint32_t r, int i) {
-            r = min(r, rot.n - 1);
-            x[i] = slot_load<G, PACKED>(bundle, dg.ndig * E + pos, N, r < n_key ? galois_source_slot(n, rot.galois[r], logN) : n);
-            w[i] = plaintext(r);
-        };
-#pragma unroll
-        for (uint32_t i = 0; i < AHEAD; ++i) fetch0(i, i);
+        if (src.c0) {  // uniform
+            using WC = std::conditional_t<PACKED, uint64_t, uint32_t>;
 #pragma unroll 1
-        for (uint32_t r0 = 0; r0 < rot.n; r0 += AHEAD) {
+            for (uint32_t r = 0; r < rot.n; ++r) {
+                const WC* cp = static_cast<const WC*>(src.c0) + (uint64_t)pos * N + (r < n_key ? galois_source_slot(n, rot.galois[r], logN) : n);
+                WC x[G];
 #pragma unroll
-            for (uint32_t i = 0; i < AHEAD; ++i) {
-                const double pw = mulmod_lazy(r0 + i < rot.n ? pm : 0.0, word_to_f64<WK>(w[i]), m);
-                const SlotRaw<G> s = slot_take<G, PACKED>(x[i]);
+                for (int b = 0; b < G; ++b) x[b] = cp[b * src.c0_ps];
+                const double pw = mulmod_lazy(pm, word_to_f64<WK>(plaintext(r)), m);
 #pragma unroll
-                for (int b = 0; b < G; ++b) mac_exact(slot_f64<G, PACKED>(s, b), pw, h0[b], l0[b]);
-                fetch0(r0 + i + AHEAD, i);
+                for (int b = 0; b < G; ++b) mac_exact(word_to_f64<WC>(x[b]), pw, h0[b], l0[b]);
+            }
+        } else {
+            constexpr uint32_t AHEAD = 2;  // rotations in flight
+            SlotRaw<G> x[AHEAD];
+            WK w[AHEAD];
+            auto fetch0 = [&](uint32_t r, int i) {
+                r = min(r, rot.n - 1);
+                x[i] = slot_load<G, PACKED>(bundle, dg.ndig * E + pos, N, r < n_key ? galois_source_slot(n, rot.galois[r], logN) : n);
+                w[i] = plaintext(r);
+            };
+#pragma unroll
+            for (uint32_t i = 0; i < AHEAD; ++i) fetch0(i, i);
+#pragma unroll 1
+            for (uint32_t r0 = 0; r0 < rot.n; r0 += AHEAD) {
+#pragma unroll
+                for (uint32_t i = 0; i < AHEAD; ++i) {
+                    const double pw = mulmod_lazy(r0 + i < rot.n ? pm : 0.0, word_to_f64<WK>(w[i]), m);
+                    const SlotRaw<G> s = slot_take<G, PACKED>(x[i]);
+#pragma unroll
+                    for (int b = 0; b < G; ++b) mac_exact(slot_f64<G, PACKED>(s, b), pw, h0[b], l0[b]);
+                    fetch0(r0 + i + AHEAD, i);
+                }
             }
         }
 #pragma unroll 1

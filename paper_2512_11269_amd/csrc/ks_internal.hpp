@@ -258,10 +258,14 @@ struct MacRotations {
 //   The group is the batch, whatever it is.  Rounded up to 1, 2, 4 or 8, five ciphertexts were transformed, written and
 // gathered as eight: one rotate-multiply-accumulate of five, N = 2^16, E = 32, three digits 504 us against 470 (28-bit moduli 447
 // against 417); at N = 2^14 91 against 82.
+//   c0 != nullptr: rotate_mac gathers the addend from these ciphertexts (64-bit words with a packed bundle, 32-bit words with
+// a 32-bit one; c0_ps words apart) instead of from slabs of the bundle.
 struct GatherBundle {
     uint32_t* lo;
     uint8_t* hi;
     uint32_t group;
+    const void* c0;
+    uint64_t c0_ps;
 };
 constexpr int kMaxGroup = 8;
 constexpr uint32_t gather_hi_bytes(uint32_t group) { return group > 4 ? 4 : group > 2 ? 2 : 1; }

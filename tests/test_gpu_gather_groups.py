@@ -54,6 +54,26 @@ def test_every_group_size_words32(batch):
     assert_equal(mac.to(torch.int64), st.ref.rotate_mac_hoisted(host(ct), [1] + galois, [None] + [host(k) for k in keys], [host(w) for w in pts], ell))
 
 
+@pytest.mark.parametrize("n_rot", [1, 5, 6])
+@pytest.mark.parametrize("bits,batch", [(36, 1), (36, 3), (36, 8), (28, 2), (28, 7)])
+def test_addend_from_the_ciphertexts_and_from_the_bundle(bits, batch, n_rot):
+    """Up to five rotations gather c0 from the ciphertexts, six read a copy; an identity and a unit plaintext among them."""
+    st = Setup(12, 5, 2, 3, bits=bits)
+    ell, all_ids = 4, list(range(st.L + st.K))
+    g = ks_inputs.galois_elements(st.logN, n_rot)
+    galois = [2 * st.N - g[0]] + [1 if r == 2 else g[r] for r in range(1, n_rot)]
+    ct = st.uniform(4003, batch, (batch, 2), list(range(ell)))
+    keys = [None if e == 1 else st.uniform(4003, 50 + r, (st.ctx.dnum, 2), all_ids) for r, e in enumerate(galois)]
+    pts = [None if r == 3 else st.uniform(4003, 70 + r, (), all_ids) for r in range(n_rot)]
+    want = st.ref.rotate_mac_hoisted(host(ct), galois, [k if k is None else host(k) for k in keys],
+                                     [w if w is None else host(w) for w in pts], ell)
+    word = (lambda t: t) if bits == 36 else (lambda t: t if t is None else t.to(torch.int32))
+    op, fn = (K.KS_OP_ROTATE_HOISTED, K.ks_rotate_mac_hoisted) if bits == 36 else (K.KS_OP_ROTATE_HOISTED_U32, K.ks_rotate_mac_hoisted_u32)
+    out = word(torch.zeros((batch, 2, ell, st.N), dtype=torch.int64, device="cuda"))
+    fn(st.ctx, word(ct), ell, galois, [word(k) for k in keys], [word(w) for w in pts], out, workspace(st.ctx, op, ell, batch, n_rot))
+    assert_equal(out.to(torch.int64), want)
+
+
 @pytest.mark.parametrize("bits,op", [(36, K.KS_OP_ROTATE_HOISTED), (28, K.KS_OP_ROTATE_HOISTED_U32)])
 def test_workspace_holds_no_ciphertexts_beyond_the_batch(bits, op):
     """Everything a rotation keeps is per ciphertext but the words of the bits above 32, of which two to eight ciphertexts share one
