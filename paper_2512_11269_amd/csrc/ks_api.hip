@@ -283,7 +283,7 @@ static int bconv_impl(const ks_ctx* c, const void* in, const uint32_t* src_ids, 
         const uint32_t nb = std::min(batch - b0, 32768u);
         const char* ip = static_cast<const char*>(in) + (uint64_t)b0 * n_src * N * word;
         char* op = static_cast<char*>(out) + (uint64_t)b0 * n_dst * N * word;
-        launch_bconv_mfma(c, set, n_src + n_dst, ip, (uint64_t)n_src * N, op, (uint64_t)n_dst * N, nb, s, words32);
+        launch_bconv(c, set, n_src + n_dst, ip, (uint64_t)n_src * N, op, (uint64_t)n_dst * N, nb, s, words32);
     }
     return finish(words32 ? "bconv_u32" : "bconv");
 }

@@ -235,8 +235,11 @@ void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t
 // remainder of (sum - converted special part) P^-1 modulo q_{ell-1}, a signed double.
 void launch_rescale_remainder(const ks_ctx* c, const Level& lv, uint64_t* acc, uint32_t n_polys, hipStream_t s);
 
-// The standalone conversion, on the matrix cores (ks_bconv_mfma.hip).
+// The standalone conversion (ks_bconv.hip: the choice of the kernel, and the vector kernel).
 // words32: in and out hold one residue per 32-bit word (strides in words either way)
+void launch_bconv(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const void* in, uint64_t in_poly_stride,
+                  void* out, uint64_t out_poly_stride, uint32_t n_polys, hipStream_t s, bool words32);
+// the same on the matrix cores (ks_bconv_mfma.hip)
 void launch_bconv_mfma(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const void* in, uint64_t in_poly_stride,
                        void* out, uint64_t out_poly_stride, uint32_t n_polys, hipStream_t s, bool words32);
 

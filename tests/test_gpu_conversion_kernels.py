@@ -150,7 +150,7 @@ def test_standalone_conversion_positions_per_wavefront_words32(batch):
 
 
 @pytest.mark.parametrize("logN,L,Kk,dnum,batch", [
-    (16, 16, 4, 4, 8),    # 16-column tiles with every operand-slot shape: 4, 6, 8, 12 and 13 sources
+    (16, 16, 4, 4, 8),    # 4 sources (8 columns at most); tiles of 16 with every operand-slot shape they come in: 6, 8, 12 and 13
     (16, 24, 6, 4, 8),
     (16, 24, 8, 3, 9),    # a last chunk of one ciphertext: 16- and 8-column tiles in one call
     (16, 36, 12, 3, 8),
@@ -158,17 +158,18 @@ def test_standalone_conversion_positions_per_wavefront_words32(batch):
     (15, 20, 7, 3, 5),    # three targets per lane half at N = 2^15
 ])
 def test_conversion_tiles_of_large_launches(logN, L, Kk, dnum, batch):
-    """The kernel chosen from the launch size against the vector kernel on every residue, and against the reference on the last item."""
+    """The kernel that is chosen, the vector kernel and the matrix cores against each other on every residue, and against the
+    reference on the last item."""
     st = Setup(logN, L, Kk, dnum)
     evk = st.uniform(43, 1, (dnum, 2), list(range(L + Kk)))
     d = st.uniform(43, 2, (batch,), list(range(L)))
     ws = workspace(st.ctx, K.KS_OP_KEYSWITCH, L, batch)
     out = []
-    for kernel in (0, 1):
+    for kernel in (0, 1, 2):
         _select(st, kernel, 0)
         out.append(torch.full((batch, 2, L, st.N), -1, dtype=torch.int64, device="cuda"))
         K.ks_keyswitch(st.ctx, d, L, evk, out[-1], ws)
-    assert torch.equal(out[0], out[1])
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
     assert_equal(out[0][-1:], st.ref.keyswitch(host(d[-1:]), host(evk), L))
 
 
@@ -199,3 +200,27 @@ def test_conversion_kernel_that_is_chosen(bits, logN, L, Kk, dnum, batch, want):
     _select(st, 1 if want == "matrix" else 2, 0)
     K.ks_keyswitch(st.ctx, d, L, evk, out[1], ws)
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("bits,n_src,n_dst,want", [
+    (36, 1, 1, "vector"), (36, 1, 12, "vector"), (36, 1, 13, "matrix"), (36, 2, 4, "vector"), (36, 2, 5, "matrix"), (36, 3, 4, "vector"),
+    (36, 3, 5, "matrix"), (36, 4, 2, "vector"), (36, 4, 3, "matrix"), (36, 5, 2, "vector"), (36, 5, 3, "matrix"), (36, 6, 1, "matrix"),
+    (28, 1, 12, "vector"), (28, 1, 13, "matrix"), (28, 4, 6, "vector"), (28, 5, 10, "vector"), (28, 6, 1, "matrix"),
+])
+@pytest.mark.parametrize("batch", [1, 5])
+def test_standalone_conversion_of_few_sources(bits, n_src, n_dst, want, batch):
+    """Both sides of the line between the two standalone kernels, 28-bit moduli in both word sizes."""
+    st = Setup(12, 15, 1, 3, bits=bits)
+    src, dst = list(range(1, 1 + n_src)), [m for m in range(16) if not 1 <= m <= n_src][:n_dst]
+    x = st.uniform(45, n_src, (batch,), src)
+    ref = st.ref.bconv(host(x), src, dst)
+    K.bconv_prepare(st.ctx, src, dst)
+    for words in (64,) if bits == 36 else (64, 32):
+        dtype = torch.int64 if words == 64 else torch.int32
+        out = torch.full((batch, len(dst), st.N), -1, dtype=dtype, device="cuda")
+        K.ks_profile_enable(True)
+        (K.bconv if words == 64 else K.bconv_u32)(st.ctx, x.to(dtype), src, out, dst)
+        ran = {r["kernel"] for r in K.ks_profile_report()}
+        K.ks_profile_enable(False)
+        assert ran == {"bconv" if want == "vector" else "bconv_mfma"}
+        assert_equal(out.to(torch.int64), ref)
