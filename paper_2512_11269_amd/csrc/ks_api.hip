@@ -106,21 +106,18 @@ static double moddown_ops(const ks_ctx* c, const Level& lv) {
     return (double)c->K * lv.ell * 4.5 + lv.ell * (3.0 + 4.0 * (c->logN - 8));
 }
 
-// Division by P of both accumulators, optional addend: INTT of the special limbs (in place), fused base
-// conversion + column half, fused row half + (acc - conv) P^-1.
+// Division by P of both accumulators: INTT of the special limbs (in place), fused base conversion + column half, fused row
+// half + (acc - conv) P^-1.
 // accq: the ciphertext limbs of the accumulators are there, packed, instead of in acc.
-// addend_packed (with accq): the addend is there, [b][2][ell][N] packed (addend_bs in elements), instead of at addend.
 void mod_down(const ks_ctx* c, const Level& lv, uint64_t* acc, uint64_t* conv, void* out, uint64_t out_bs,
-              const uint64_t* addend, uint64_t addend_bs, uint32_t addend_comps, uint32_t galois, uint32_t bc,
-              bool special_rows_done, int tile, hipStream_t s, bool out_words32 = false, const PackedDigits* accq = nullptr,
-              const PackedDigits* addend_packed = nullptr) {
+              uint32_t bc, bool special_rows_done, int tile, hipStream_t s, bool out_words32 = false,
+              const PackedDigits* accq = nullptr) {
     const uint64_t N = c->N, acc_ps = (uint64_t)lv.E * N, conv_ps = (uint64_t)lv.ell * N;
     // the fused inner product already ran the row half of the inverse transform on the special limbs
     if (!special_rows_done) launch_ntt_inv_rows(c, lv.special_map, XformIO{acc, acc, acc_ps, acc_ps, 2 * bc}, s);
     launch_ntt_inv_cols(c, lv.special_map, acc, acc_ps, 2 * bc, c->d_moddown_scale, true, true, s);
     launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s, moddown_ops(c, lv));
-    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, addend, addend_bs, addend_comps, galois, bc, s, nullptr, out_words32, accq,
-                               addend_packed);
+    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 0, 0, 1, bc, s, nullptr, out_words32, accq);
 }
 
 }  // namespace
@@ -329,8 +326,7 @@ int ks::keyswitch_impl(const ks_ctx* c, const void* d, uint32_t ell, const void*
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
         mod_up(c, lv, dc, d_ps, coeff, lifted, bc, tile, s, words32);
         launch_rows_inner_product(c, lv, dc, d_ps, lifted, evk, acc, bc, s, words32, words32, accq);
-        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * out_bs * word, out_bs, nullptr, 0, 0, 1, bc, true, tile, s, words32,
-                 &accq);
+        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * out_bs * word, out_bs, bc, true, tile, s, words32, &accq);
     }
     return finish(words32 ? "ks_keyswitch_u32" : "ks_keyswitch");
 }
@@ -402,7 +398,7 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
                 const PackedDigits accq_r{accq.lo + (uint64_t)r * accq_n, accq.hi + (uint64_t)r * accq_n};
                 launch_rows_moddown_finish(c, lv, nullptr, conv + (uint64_t)r * w.conv,
                                            static_cast<char*>(out) + ((uint64_t)b0 * out_bs + (uint64_t)(r0 + r) * 2 * ell * N) * word,
-                                           out_bs, c0, ct_bs, 1, galois[r0 + r], bc, s, nullptr, words32, &accq_r, nullptr, words32);
+                                           out_bs, c0, ct_bs, 1, galois[r0 + r], bc, s, nullptr, words32, &accq_r);
             }
         }
     }
@@ -478,7 +474,7 @@ static int rotate_mac_impl(const ks_ctx* c, const void* ct, uint32_t ell, const 
         // finished once, shared by every rotation
         const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, n_rot, tile, s, words32);
         rotate_mac_all(c, lv, digits, galois, rot_keys, pts, n_rot, acc, false, s, words32);
-        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, tile, s, words32);
+        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, bc, false, tile, s, words32);
     }
     return finish(words32 ? "ks_rotate_mac_hoisted_u32" : "ks_rotate_mac_hoisted");
 }
@@ -530,12 +526,12 @@ static int bsgs_impl(const ks_ctx* c, const void* ct, uint32_t ell, const uint32
         const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, n1 * n2, tile, s, words32);
         for (uint32_t g = 0; g < n2; ++g) {
             rotate_mac_all(c, lv, digits, baby_galois, bkeys, ptv + (size_t)g * n1, n1, acc, false, s, words32);
-            mod_down(c, lv, acc, conv, v, ct_bs, nullptr, 0, 0, 1, bc, false, tile, s);
+            mod_down(c, lv, acc, conv, v, ct_bs, bc, false, tile, s);
             const GatherBundle digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, v, ct_bs, coeff, lifted, region_v, bc, 1, tile, s, false,
                                                             giant_galois[g] != 1);
             rotate_mac_all(c, lv, digits_v, giant_galois + g, gkeys + g, nullptr, 1, acc_outer, g != 0, s, words32);
         }
-        mod_down(c, lv, acc_outer, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, nullptr, 0, 0, 1, bc, false, tile, s,
+        mod_down(c, lv, acc_outer, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, bc, false, tile, s,
                  words32);
     }
     return finish(words32 ? "ks_bsgs_linear_transform_u32" : "ks_bsgs_linear_transform");

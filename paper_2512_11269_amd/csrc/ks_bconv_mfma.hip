@@ -7,7 +7,7 @@
 // the same way into digits e_{t,i,a,b}.  Then
 //     y_i (D / s_i) = sum_b 256^b  S_b   (mod t),     S_b = sum_{i,a} d_{i,a} e_{t,i,a,b},
 // and the five S_b of a target are dot products of length 5 n_src over small integers: one row of an int8 matrix
-// product with exact 32-bit accumulation (|S_b| <= 16 * 5 * 2^14).  The recombined value is below 2^49 in magnitude,
+// product with exact 32-bit accumulation (|S_b| <= 17 * 5 * 2^14).  The recombined value is below 2^49 in magnitude,
 // exact in a double, and one Barrett step makes it a lazy residue modulo t.
 //
 // v_mfma_i32_32x32x32_i8: every lane supplies 16 bytes of A (row = lane % 32) and 16 bytes of B (column = lane % 32) for
@@ -15,7 +15,7 @@
 // of its column.  Here a COLUMN IS A COEFFICIENT POSITION, so the B operand of a lane is made of the bytes of that lane's
 // own source residues: no data crosses lanes on the way in.  The two lanes that share a column (l and l + 32) read
 // different sources and receive different targets: rows are ordered so that result registers 5 u + b of a lane are the
-// five digit planes b of its u-th target.  A workgroup owns a tile of 2048 positions and 2 TL targets (TL per lane half):
+// five digit planes b of its u-th target.  A workgroup owns a tile of 2048 positions (4096 with eight wavefronts) and 2 TL targets (TL per lane half):
 // thread (pair p = 32 wave + lane % 32, half h) walks the 16 positions (row r0 + 16 k, column c) of pair p, exactly the
 // points the column butterflies need in its registers afterwards.
 #include "ks_internal.hpp"
@@ -99,8 +99,8 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
 // ------------------------------------------------------------------------------------------------
 // Standalone conversion on the matrix cores (the `bconv` entry point): canonical residues in, canonical residues out, no
 // transform.  A wavefront owns PG groups of 32 positions, V of them interleaved so that a lane's V positions are one 16-byte
-// access: lane (position l % 32, half l / 32) scales its slots' source residues to y_i = [x_i (D / s_i)^-1]_{s_i}, cuts them into bytes once, and then walks the targets six at a time
-// (three per lane half), writing 512-byte segments per target.  The factors and constants of the next six
+// access: lane (position l % 32, half l / 32) scales its slots' source residues to y_i = [x_i (D / s_i)^-1]_{s_i}, cuts them
+// into bytes once, and then walks the targets six at a time (three per lane half), writing 512-byte segments per target.  The factors and constants of the next six
 // targets are requested before the current ones' stores: loads and stores share one in-order counter, so a load behind the
 // stores would wait for memory to acknowledge them.  About 16 vector instructions per position and target remain, where
 // fp64 accumulation takes three per source more; what bounds a full launch is the traffic itself:

@@ -115,14 +115,6 @@ KS_HD void split2(double y, double& y1, double& y0) {
     y0 = y - y1;
 }
 
-// (s2 * 2^24 + s1 * 2^12 + s0) mod p as a lazy representative, for exact non-negative integer sums s_k < 2^52
-// (the three partial sums of a base conversion whose factors were split into 12-bit pieces).
-KS_HD double combine3_lazy(double s0, double s1, double s2, Mod m) {
-    double r = reduce_lazy(s2, m);
-    r = reduce_lazy(__builtin_fma(r, 4096.0, s1), m);
-    return reduce_lazy(__builtin_fma(r, 4096.0, s0), m);
-}
-
 // Representative in (-p, p) -> canonical [0, p).
 KS_HD double canon(double r, Mod m) { return r < 0.0 ? r + m.p : r; }
 

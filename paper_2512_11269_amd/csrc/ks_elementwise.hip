@@ -1,6 +1,6 @@
-// Slot-wise kernels (Kernel Code Generation, "Elementwise" kernel class): inner product with the
-// evaluation key through the evaluation-domain automorphism (a gather), tensor product, and a scaled add.  These are bandwidth-bound: one thread per slot, contiguous
-// 512-byte segments per wavefront, operands shared by both key components are read once ("load reuse").
+// Slot-wise kernels (Kernel Code Generation, "Elementwise" kernel class): inner products with evaluation keys through the
+// evaluation-domain automorphism (gathers) and the tensor product.  One thread per slot, contiguous segments per wavefront,
+// operands shared by both key components and by all ciphertexts of a group are read once ("load reuse").
 #include "ks_internal.hpp"
 #include "ks_tiles.hpp"
 

@@ -359,7 +359,7 @@ void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, 
 // above) instead of as the first ell limbs of [b][2][E][N] 64-bit words.
 // ADF: format of the addend: 0 = 64-bit words; 1 = packed the same way (addend: [b][2][ell][N] low words, addend_hi: the
 // bytes above); 2 = 32-bit words.
-template <int LOG_R, bool GATHER, int ADDEND, typename W = uint64_t, bool ACCP = false, int ADF = 0>
+template <int LOG_R, bool GATHER, int ADDEND, typename W, bool ACCP, int ADF>
 __global__ __launch_bounds__(64) void rows_moddown_finish(TwTables tw, const Mod* __restrict__ mods,
                                                           const double* __restrict__ Pinv, const double* __restrict__ addend_mul,
                                                           uint32_t ell, uint32_t E, uint32_t out_limbs,
@@ -407,7 +407,7 @@ __global__ __launch_bounds__(64) void rows_moddown_finish(TwTables tw, const Mod
 void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t* acc, const uint64_t* conv, void* out_words,
                                 uint64_t out_bs, const void* addend, uint64_t addend_bs, uint32_t addend_comps,
                                 uint32_t galois, uint32_t batch, hipStream_t s, const FinishScale* fs, bool out_words32,
-                                const PackedDigits* acc_packed, const PackedDigits* addend_packed, bool addend_words32) {
+                                const PackedDigits* acc_packed, const PackedDigits* addend_packed) {
     if (batch == 0) return;
     const void* addend_p = addend_packed ? static_cast<const void*>(addend_packed->lo) : addend;
     const uint8_t* addend_h = addend_packed ? addend_packed->hi : nullptr;
@@ -418,7 +418,7 @@ void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t
     if (!addend_p) addend_comps = 0;
     ProfScope ps("rows_moddown_finish",
                  (double)batch * out_limbs *
-                     (2 * 8 + 2 * (acc_packed ? 5 : 8) + (out_words32 ? 1 : 2) * 8 + addend_comps * (addend_packed ? 5 : addend_words32 ? 4 : 8)) * c->N,
+                     (2 * 8 + 2 * (acc_packed ? 5 : 8) + (out_words32 ? 1 : 2) * 8 + addend_comps * (addend_packed ? 5 : out_words32 ? 4 : 8)) * c->N,
                  s);
     const dim3 block(64);
     const uint32_t row_groups = c->N / 1024;
@@ -434,32 +434,20 @@ void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t
     hipLaunchKernelGGL((rows_moddown_finish<LOGR, GATHER, MODE, WT, ACCP, ADF>), grid, block, 0, s, c->tw_fwd, c->d_mod, mul, admul, \
                        lv.ell, lv.E, out_limbs, accp, acch, conv, static_cast<WT*>(out_words), out_bs, addend_p, addend_h, addend_bs, \
                        comp0, n_comps, galois)
-#define KS_LAUNCH_FINISH(LOGR, GATHER, MODE, WT, ACCP) KS_LAUNCH_FINISH_P(LOGR, GATHER, MODE, WT, ACCP, 0)
-    // a packed addend comes with a packed accumulator (multiplications); an addend in 32-bit words with a packed accumulator
-    // and 32-bit output (hoisted rotations in 32-bit words)
-#define KS_LAUNCH_MODES(LOGR, WT)                                                        \
-    if (addend_packed && mode != 0) {                                                    \
-        if (mode == 2) KS_LAUNCH_FINISH_P(LOGR, false, 2, WT, true, 1);                  \
-        else KS_LAUNCH_FINISH_P(LOGR, false, 1, WT, true, 1);                            \
-    } else if (addend_words32 && mode != 0) {                                            \
-        if (galois == 1) KS_LAUNCH_FINISH_P(LOGR, false, 1, uint32_t, true, 2);          \
-        else KS_LAUNCH_FINISH_P(LOGR, true, 1, uint32_t, true, 2);                       \
-    } else if (acc_packed) {                                                             \
-        if (mode == 0) KS_LAUNCH_FINISH(LOGR, false, 0, WT, true);                       \
-        else if (mode == 2) KS_LAUNCH_FINISH(LOGR, false, 2, WT, true);                  \
-        else if (galois == 1) KS_LAUNCH_FINISH(LOGR, false, 1, WT, true);                \
-        else KS_LAUNCH_FINISH(LOGR, true, 1, WT, true);                                  \
-    } else if (mode == 0) KS_LAUNCH_FINISH(LOGR, false, 0, WT, false);                   \
-    else if (mode == 2) KS_LAUNCH_FINISH(LOGR, false, 2, WT, false);                     \
-    else if (galois == 1) KS_LAUNCH_FINISH(LOGR, false, 1, WT, false);                   \
-    else KS_LAUNCH_FINISH(LOGR, true, 1, WT, false)
-#define KS_LAUNCH(LOGR)                                     \
-    if (out_words32) { KS_LAUNCH_MODES(LOGR, uint32_t); }   \
-    else { KS_LAUNCH_MODES(LOGR, uint64_t); }
+    // Who calls: a scaled addend is packed and comes with a packed accumulator (multiplications); an addend as it is comes with
+    // a packed accumulator, in the word size of the output (hoisted rotations).
+#define KS_LAUNCH_MODES(LOGR, WT, ADF)                                                  \
+    if (mode == 2) KS_LAUNCH_FINISH_P(LOGR, false, 2, WT, true, 1);                     \
+    else if (mode == 1 && galois != 1) KS_LAUNCH_FINISH_P(LOGR, true, 1, WT, true, ADF);  \
+    else if (mode == 1) KS_LAUNCH_FINISH_P(LOGR, false, 1, WT, true, ADF);              \
+    else if (acc_packed) KS_LAUNCH_FINISH_P(LOGR, false, 0, WT, true, 0);               \
+    else KS_LAUNCH_FINISH_P(LOGR, false, 0, WT, false, 0)
+#define KS_LAUNCH(LOGR)                                      \
+    if (out_words32) { KS_LAUNCH_MODES(LOGR, uint32_t, 2); } \
+    else { KS_LAUNCH_MODES(LOGR, uint64_t, 0); }
         KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
 #undef KS_LAUNCH_MODES
-#undef KS_LAUNCH_FINISH
 #undef KS_LAUNCH_FINISH_P
     }
 }

@@ -200,8 +200,8 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
 // Upload host plans as a PlanSet (allocates; ks_ctx_create and bconv plan registration only).  Returns a HIP error code.
 hipError_t upload_plans(const BConvPlan* host_plans, uint32_t n_plans, uint32_t shape_src, PlanSet* out);
 // Canonical residues in packed form: bits 0..31 in lo, the bits above (moduli are below 2^36) in hi, both with the
-// element index of the tensor they stand for; 5 bytes a residue instead of 8.  The hoisted rotations keep the finished
-// raised digits ([b][ndig][E][N], what their gathers read) and the ciphertext limbs of their accumulators this way.
+// element index of the tensor they stand for; 5 bytes a residue instead of 8.  The ciphertext limbs of accumulators and the
+// tensor product's d0 and d1 are kept this way.
 struct PackedDigits {
     uint32_t* lo;
     uint8_t* hi;
@@ -215,11 +215,10 @@ void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, 
                                const void* evk, uint64_t* acc, uint32_t batch, hipStream_t s, bool d_words32, bool key_words32,
                                const PackedDigits& accq, const PackedDigits* drop_addend = nullptr);
 // Fused row half of the forward transform of the converted limbs + (acc - conv) P^-1 (+ addend).
-// fs == nullptr: multiply by P^-1, addend unscaled, ell output limbs.  Otherwise (merged ModDown + rescale): multiply by
-// fs->mul[i], scale the addend by fs->addend_mul[i], and write only the first fs->out_limbs limbs per component.
 // acc_packed: the ciphertext limbs of the accumulator are read from there ([b][2][ell][N]) instead of from acc.
-// addend_packed (with acc_packed, galois == 1): the addend is read from there ([b][2][ell][N], addend_batch_stride in
-// elements) instead of from addend.  addend_words32 (with acc_packed and out_words32): addend holds 32-bit words.
+// fs == nullptr: multiply by P^-1, ell output limbs; an addend (with acc_packed) is in the word size of the output and read
+// through sigma_galois.  Otherwise (division by P and a rescale, with acc_packed): multiply by fs->mul[i], add addend_packed
+// ([b][2][ell][N], addend_batch_stride in elements) times fs->addend_mul[i], write the first fs->out_limbs limbs per component.
 struct FinishScale {
     const double* mul;
     const double* addend_mul;
@@ -229,7 +228,7 @@ void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t
                                 uint64_t out_batch_stride, const void* addend, uint64_t addend_batch_stride,
                                 uint32_t addend_comps, uint32_t galois, uint32_t batch, hipStream_t s,
                                 const FinishScale* fs = nullptr, bool out_words32 = false, const PackedDigits* acc_packed = nullptr,
-                                const PackedDigits* addend_packed = nullptr, bool addend_words32 = false);
+                                const PackedDigits* addend_packed = nullptr);
 // Remainder of the dropped limb for a rescale.  acc: [polys][E][N], the drop_map limbs in the coefficient domain as canonical
 // doubles (y_k on the special limbs, P^-1 times the dropped limb's sum on limb ell-1); limb ell-1 becomes the centred
 // remainder of (sum - converted special part) P^-1 modulo q_{ell-1}, a signed double.

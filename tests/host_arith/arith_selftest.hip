@@ -62,13 +62,6 @@ static void check_prime(uint64_t p) {
         const double r = reduce_lazy((double)x, m);
         CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128((i128)x, p), "reduce x=%lld r=%.0f", (long long)x, r);
     }
-    // combine3_lazy: three exact sums below 2^52
-    for (int i = 0; i < 100000; ++i) {
-        const uint64_t s0 = rnd() >> 12, s1 = rnd() >> 12, s2 = rnd() >> 12;
-        const double r = combine3_lazy((double)s0, (double)s1, (double)s2, m);
-        const i128 exact = ((i128)s2 << 24) + ((i128)s1 << 12) + s0;
-        CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "combine3");
-    }
     // mac_exact: as many products as it takes, of the largest operands and of smaller ones, reduced once; the high sum stays
     // where doubles are 2^28 apart
     for (int rep = 0; rep < 3000; ++rep) {

@@ -1,6 +1,6 @@
 """The library's double-precision modular arithmetic, compiled for the host and checked against exact 128-bit
 integer arithmetic: value congruence and the stated magnitude bounds of every primitive (lazy product,
-lazy reduction, three-sum recombination, sixteen-point forward / inverse passes), on random and
+lazy reduction, exact multiply-accumulate, splits, sixteen-point forward / inverse passes), on random and
 boundary-seeking inputs, for the primes the workloads use."""
 
 import os
