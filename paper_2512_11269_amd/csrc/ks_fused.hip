@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void bconv_ntt_cols(const double* __restrict__
 //   16 columns are whole lines, but one workgroup of 512 threads per compute unit that works in step: ahead when a launch
 // has six rounds or more.  8 -> 24, 8 ciphertexts (G = 3072): 550 / 545 / 546; 12 -> 36 (4608): 906 / 903 / 887; four
 // rotations of them (G of ModDown 8192 and 12288): 1663 / 1697 / 1614 and 2685 / 2730 / 2618, 28-bit 1492 / 1547 / 1464 and
-// 2423 / 2508 / 2379, but at G = 3456 582 / 587 / 585.  10 -> 20 (250), whose last group of six is mostly empty:
+// 2423 / 2508 / 2379 (8 -> 24 has a load of 216 there), but at G = 3456 582 / 587 / 585.  10 -> 20 (250), whose last group of six is mostly empty:
 // 1477 / 1580 / 1497, hence the fill.
 //   N = 2^15, 36-bit: 3 -> 9 (130), 8 ciphertexts: 123 / 120, 7: +3.5 %; 7 -> 21 (215), 4: 158 / 139; 28-bit: 3 -> 9 (117),
 // 7: +5.6 %; 4 -> 12 (168), 4: 82 / 83, 8: 137 / 132; 5 -> 20 (150), 4: 140 / 133.  Where a launch has just more than 256 or
@@ -217,7 +217,7 @@ int conversion_tile(const ks_ctx* c, const PlanSet& up, uint32_t up_polys, const
     if (g_up + g_down <= 512) return load >= (two_pieces ? 44 : 35) * targets ? 8 : 0;   // sources x pieces of 24 or 15
     if (std::max(g_up, g_down) < 3072) return load >= (extra + 173) * sixes ? 8 : 0;
     const bool full = targets * 10 >= sixes * 54;
-    return full && load >= 220 * sixes && (!two_pieces || std::max(g_up, g_down) >= 4096) ? 16 : 0;
+    return full && load >= 216 * sixes && (!two_pieces || std::max(g_up, g_down) >= 4096) ? 16 : 0;
 }
 
 void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint64_t* y, uint64_t y_ps,

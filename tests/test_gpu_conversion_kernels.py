@@ -138,9 +138,24 @@ def test_standalone_conversion_positions_per_wavefront(small, batch):
     assert_equal(out, small.ref.bconv(host(x), src, dst))
 
 
+@pytest.mark.parametrize("bits,n_src", [(36, 7), (36, 13), (28, 8), (28, 16)])
+@pytest.mark.parametrize("batch", [3, 32, 128])
+def test_standalone_conversion_positions_and_instructions(bits, n_src, batch):
+    """1, 2 and 4 position groups with two and three matrix instructions per position, both word sizes."""
+    st = Setup(12, 18, 3, 3, bits=bits)
+    src, dst = list(range(n_src)), [17, 18, 20, 16, 19]
+    x = st.uniform(46, batch, (batch,), src)
+    K.bconv_prepare(st.ctx, src, dst)
+    dtype = torch.int64 if bits == 36 else torch.int32
+    out = torch.full((batch, len(dst), st.N), -1, dtype=dtype, device="cuda")
+    (K.bconv if bits == 36 else K.bconv_u32)(st.ctx, x.to(dtype), src, out, dst)
+    assert_equal(out.to(torch.int64), st.ref.bconv(host(x), src, dst))
+
+
 @pytest.mark.parametrize("batch", [3, 32, 128])
 def test_standalone_conversion_positions_per_wavefront_words32(batch):
     st = Setup(12, 9, 3, 3, bits=28)
+    _select(st, 2, 0)
     src, dst = [0, 2, 4, 6, 8], [1, 3, 5, 7, 9, 10, 11]
     x = st.uniform(42, batch, (batch,), src)
     out = torch.full((batch, len(dst), st.N), -1, dtype=torch.int32, device="cuda")
@@ -224,3 +239,20 @@ def test_standalone_conversion_of_few_sources(bits, n_src, n_dst, want, batch):
         K.ks_profile_enable(False)
         assert ran == {"bconv" if want == "vector" else "bconv_mfma"}
         assert_equal(out.to(torch.int64), ref)
+
+
+def test_sixteen_column_tiles_on_28_bit_moduli():
+    """Four hoisted rotations of eight ciphertexts: the ModDown conversion of 64 polynomials takes whole-line tiles in this word size
+    too; every residue against the vector kernel."""
+    st = Setup(16, 24, 8, 3, bits=28)
+    g = [pow(5, r, 2 * st.N) for r in range(1, 5)]
+    word = lambda t: t.to(torch.int32)
+    ct = word(st.uniform(47, 1, (8, 2), list(range(24))))
+    keys = [word(st.uniform(47, 10 + r, (3, 2), list(range(32)))) for r in range(4)]
+    ws = workspace(st.ctx, K.KS_OP_ROTATE_HOISTED_U32, 24, 8, 4)
+    out = []
+    for kernel in (0, 1):
+        _select(st, kernel, 0)
+        out.append(torch.full((8, 4, 2, 24, st.N), -1, dtype=torch.int32, device="cuda"))
+        K.ks_rotate_hoisted_u32(st.ctx, ct, 24, g, keys, out[-1], ws)
+    assert torch.equal(out[0], out[1])
