@@ -97,15 +97,15 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
 }
 
 // ------------------------------------------------------------------------------------------------
-// Standalone conversion on the matrix cores (the `bconv` entry point): canonical residues in, canonical residues out, no
+// Standalone conversion on the matrix cores (the `bconv` entry point but for few sources): canonical residues in, canonical residues out, no
 // transform.  A wavefront owns PG groups of 32 positions, V of them interleaved so that a lane's V positions are one 16-byte
 // access: lane (position l % 32, half l / 32) scales its slots' source residues to y_i = [x_i (D / s_i)^-1]_{s_i}, cuts them
-// into bytes once, and then walks the targets six at a time (three per lane half), writing 512-byte segments per target.  The factors and constants of the next six
-// targets are requested before the current ones' stores: loads and stores share one in-order counter, so a load behind the
+// into bytes once, and then walks the targets six at a time (three per lane half), writing 512-byte segments per target.  The factors and
+// constants of the next six targets are requested before the current ones' stores: loads and stores share one in-order counter, so a load behind the
 // stores would wait for memory to acknowledge them.  About 16 vector instructions per position and target remain, where
 // fp64 accumulation takes three per source more; what bounds a full launch is the traffic itself:
-// 24 polynomials, 12 -> 35 moduli, N = 2^16: 121 us = 4.9 TB/s (64: 5.4), where fp64 accumulation of 12-bit pieces took
-// 198; one polynomial, 8 -> 24: 12.6 against 18.7; in 32-bit words 76 against 162.
+// 24 polynomials, 12 -> 35 moduli, N = 2^16: 118 us = 5.0 TB/s (64: 5.4), where fp64 accumulation of 12-bit pieces took
+// 187; in 32-bit words 76 against 162; calls of one polynomial, 8 -> 24: 11.9 against 18.6.  Few sources: ks_bconv.hip.
 // ------------------------------------------------------------------------------------------------
 template <int NM, int NPS, int PG, typename W>
 __global__ __launch_bounds__(256) void bconv_mfma_kernel(const BConvPlan* __restrict__ plans, LaunchMeta meta,

@@ -57,7 +57,8 @@ __device__ __forceinline__ BundleRsrc bundle_rsrc(const GatherBundle& src, uint6
     return BundleRsrc{uniform_rsrc(src.lo, slots * (4 * G)), uniform_rsrc(src.hi, slots * gather_hi_bytes(G))};
 }
 // The slots sigma_g sends to a wavefront's 64 consecutive slots are one aligned block of 64, permuted.  The block is read
-// in its own order and the lanes exchange what they hold on use (slot_take; 5 % on both kernels over permuted loads).  slab: uniform; slot: the lane's source slot.
+// in its own order and the lanes exchange what they hold on use (slot_take; 5 % on both kernels over permuted loads).
+// slab: uniform; slot: the lane's source slot.
 template <int G, bool PACKED>
 __device__ __forceinline__ SlotRaw<G> slot_load(const BundleRsrc& src, uint32_t slab, uint32_t N, uint32_t slot) {
     using Layout = SlotLayout<G>;
@@ -115,7 +116,7 @@ static uint32_t gather_grid(const ks_ctx* c, uint32_t E, uint32_t parts_log) {
 // key_r[j][c][pos].  One thread owns one slot of one limb position for all ciphertexts of the group and walks the
 // rotations of the launch; the operands of the next (rotation, digit) are requested before the current products.
 // WK: word type of the keys; PACKED: the bundle's sources have bits above 32.
-// Four rotations of 8 ciphertexts, N = 2^16, E = 32, three digits: 350 -> 305 us, 1.4 GB of compulsory traffic.
+// Four rotations of 8 ciphertexts, N = 2^16, E = 32, three digits: 350 -> 315 us, 1.4 GB of compulsory traffic.
 // The special limbs of the result go to acc ([r][b][2][E][N] 64-bit words, the inverse transform reads them next), the
 // ciphertext limbs to (accq_lo, accq_hi) as [r][b][2][ell][N] packed residues: they are only read back by the last
 // kernel of the rotation, and written and read once per rotation they are a fifth of these two kernels' traffic.
@@ -223,11 +224,11 @@ void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& 
 // are the OUTER loop and the rotations the inner one, so that between two rotations only one digit's slots are gathered from
 // and about half of them are found in the XCD's L2 (see gather_tile); each key slot is still read once, the plaintext slot
 // once per digit.  The operands of the next (digit, rotation) are requested before the current products.
-// 8 ciphertexts x (15 keyed rotations + 1 identity), three digits, N = 2^16, E = 32: 650 us, where one thread per slot that
-// walked digits inside rotations and gathered each ciphertext on its own took 980 us (9.2 GB through the fabric, now 5).
+// 8 ciphertexts x 16 keyed rotations, three digits, N = 2^16, E = 32: 690 us (28-bit moduli 512), where one thread per slot that
+// walked digits inside rotations and gathered each ciphertext on its own took 1037 (9.6 GB through the fabric, now 4.6 of 7 GB).
 // What bounds it: the stream of keys and plaintexts (2.5 GB; alone 600 us) and fp64 issue (alone 470 us), partly overlapped.
 // Three wavefronts per SIMD: squeezed into 128 registers for a fourth, the few spilled words cost more fabric traffic than
-// the occupancy gains (690-750 us).  Sixteen ciphertexts per launch sharing the key reads measured the same per ciphertext:
+// the occupancy gains (40-100 us more).  Sixteen ciphertexts per launch sharing the key reads measured the same per ciphertext:
 // what the shared keys save, the doubled sources lose in L2.
 // rot: the n_key rotations that take a key come first, then the identities (the term P (c0, c1), no key read).
 template <int G, typename WK, bool PACKED>
