@@ -24,41 +24,49 @@ int finish(const char* where) {
     return KS_OK;
 }
 
-struct KsWorkspace {  // element counts (uint64 words) for a chunk of `bc` ciphertexts
-    uint64_t coeff, lifted, acc, conv;
-    uint64_t accq;  // ciphertext limbs of the accumulators in packed form, [bc][2][ell][N] residues
+// Bytes of the packed regions of a chunk of `bc` ciphertexts.
+struct KsWorkspace {
+    uint64_t coeff, lifted, acc, conv;   // [bc][ell], [bc][ndig][E], [bc][2][E], [bc][2][ell] packed limbs
+};
+
+KsWorkspace ks_ws_regions(const ks_ctx* c, const Level& lv, uint32_t bc) {
+    const uint64_t limb = packed_limb_bytes(c->N);
+    KsWorkspace w;
+    w.coeff = (uint64_t)bc * lv.ell * limb;
+    w.lifted = (uint64_t)bc * lv.ndig * lv.E * limb;
+    w.acc = (uint64_t)bc * 2 * lv.E * limb;
+    w.conv = (uint64_t)bc * 2 * lv.ell * limb;
+    return w;
+}
+
+// What ks_workspace_bytes asks for: the same regions with 8 bytes a residue and a packed copy of the ciphertext limbs of the
+// accumulators, in 64-bit words.  More than ks_ws_regions adds up to, and kept: the figure is part of the interface.
+struct KsWorkspaceWords {
+    uint64_t coeff, lifted, acc, conv, accq;
     uint64_t total() const { return coeff + lifted + acc + conv + accq; }
 };
 
-// 64-bit words that n residues take in packed form (32-bit low words, then the bytes above; each part 8-byte aligned)
-static uint64_t packed_words(uint64_t n) { return (n + 1) / 2 + (n + 7) / 8; }
-
-// the packed tensor of n residues that starts at `words`
-static PackedDigits packed_at(uint64_t* words, uint64_t n) {
-    return PackedDigits{reinterpret_cast<uint32_t*>(words), reinterpret_cast<uint8_t*>(words + (n + 1) / 2)};
-}
-
-KsWorkspace ks_ws_words(const ks_ctx* c, const Level& lv, uint32_t bc) {
+KsWorkspaceWords ks_ws_words(const ks_ctx* c, const Level& lv, uint32_t bc) {
     const uint64_t N = c->N;
-    KsWorkspace w;
+    KsWorkspaceWords w;
     w.coeff = (uint64_t)bc * lv.ell * N;
     w.lifted = (uint64_t)bc * lv.ndig * lv.E * N;
     w.acc = (uint64_t)bc * 2 * lv.E * N;
     w.conv = (uint64_t)bc * 2 * lv.ell * N;
-    w.accq = packed_words(w.conv);
+    w.accq = packed_limb_bytes(w.conv) / 8;
     return w;
 }
 
-// Decompose and raise: d (evaluation domain, `bc` polynomials d_ps words apart) -> lifted [bc][ndig][E][N].
-// The raised limbs stop after the column half of the forward transform (raw doubles); the row half is left to the
+// Decompose and raise: d (evaluation domain, `bc` polynomials d_ps words apart) -> lifted [bc][ndig][E] packed.
+// The raised limbs stop after the column half of the forward transform; the row half is left to the
 // fused inner product, or to mod_up_for_gather below.  tile: the conversion kernel of the call (conversion_tile).
-void mod_up(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, uint64_t* coeff, uint64_t* lifted, uint32_t bc,
+void mod_up(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, uint8_t* coeff, uint8_t* lifted, uint32_t bc,
             int tile, hipStream_t s, bool d_words32 = false) {
-    const uint64_t N = c->N, coeff_ps = (uint64_t)lv.ell * N, lifted_ps = (uint64_t)lv.ndig * lv.E * N;
-    launch_ntt_inv_rows(c, lv.q_map, XformIO{d, coeff, d_ps, coeff_ps, bc}, s, d_words32);
-    // the column half also multiplies by N^-1 (D_j/q_i)^-1 and leaves canonical doubles for the conversion
-    launch_ntt_inv_cols(c, lv.q_map, coeff, coeff_ps, bc, lv.d_modup_scale, true, true, s);
-    // algorithmic fp64 work per coefficient: 3 FMAs per source x target plus the 6-addition split of the source shared
+    const uint64_t limb = packed_limb_bytes(c->N), coeff_ps = lv.ell * limb, lifted_ps = (uint64_t)lv.ndig * lv.E * limb;
+    launch_inv_rows_packed(c, lv.q_map, d, d_ps, d_words32 ? 4 : 8, coeff, coeff_ps, bc, s);
+    // the column half also multiplies by N^-1 (D_j/q_i)^-1 and leaves the sources of the conversion
+    launch_inv_cols_packed(c, lv.q_map, coeff, coeff_ps, bc, lv.d_modup_scale, s);
+    // algorithmic fp64 work per coefficient: 3 FMAs per source x target plus the 6 instructions that cut the source, shared
     // by four targets (4.5 in all), then per target one reduction and the column stages (8 per butterfly, half a
     // butterfly per point and stage)
     double ops = 0.0;
@@ -86,11 +94,11 @@ static uint64_t gather_words(const ks_ctx* c, const Level& lv, uint32_t bc, bool
 // 622 -> 607); five -3.2, -2.1 and -0.5 %; six -2.4, -1.9 and +0.6 %; sixteen +0.2, +0.1 and +3.7 %.
 constexpr uint32_t kC0InBundle = 6;
 
-// mod_up finished for the rotation gathers: `region` (gather_words() words) ends as the bundle they read.  `lifted` is only
+// mod_up finished for the rotation gathers: `region` (gather_words() 64-bit words) ends as the bundle they read.  `lifted` is only
 // scratch here.  raised == false: only the own limbs (and c0) are filled in, for a caller whose rotations are all identities.
 // n_rot: rotations that read the bundle.
-static GatherBundle mod_up_for_gather(const ks_ctx* c, const Level& lv, const void* d, const void* c0, uint64_t d_ps, uint64_t* coeff,
-                                      uint64_t* lifted, uint64_t* region, uint32_t bc, uint32_t n_rot, int tile, hipStream_t s, bool words32,
+static GatherBundle mod_up_for_gather(const ks_ctx* c, const Level& lv, const void* d, const void* c0, uint64_t d_ps, uint8_t* coeff,
+                                      uint8_t* lifted, uint64_t* region, uint32_t bc, uint32_t n_rot, int tile, hipStream_t s, bool words32,
                                       bool raised = true) {
     if (raised) mod_up(c, lv, d, d_ps, coeff, lifted, bc, tile, s, words32);
     const bool with_c0 = c0 && n_rot >= kC0InBundle;
@@ -108,16 +116,14 @@ static double moddown_ops(const ks_ctx* c, const Level& lv) {
 
 // Division by P of both accumulators: INTT of the special limbs (in place), fused base conversion + column half, fused row
 // half + (acc - conv) P^-1.
-// accq: the ciphertext limbs of the accumulators are there, packed, instead of in acc.
-void mod_down(const ks_ctx* c, const Level& lv, uint64_t* acc, uint64_t* conv, void* out, uint64_t out_bs,
-              uint32_t bc, bool special_rows_done, int tile, hipStream_t s, bool out_words32 = false,
-              const PackedDigits* accq = nullptr) {
-    const uint64_t N = c->N, acc_ps = (uint64_t)lv.E * N, conv_ps = (uint64_t)lv.ell * N;
+void mod_down(const ks_ctx* c, const Level& lv, uint8_t* acc, uint8_t* conv, void* out, uint64_t out_bs,
+              uint32_t bc, bool special_rows_done, int tile, hipStream_t s, bool out_words32 = false) {
+    const uint64_t limb = packed_limb_bytes(c->N), acc_ps = lv.E * limb, conv_ps = lv.ell * limb;
     // the fused inner product already ran the row half of the inverse transform on the special limbs
-    if (!special_rows_done) launch_ntt_inv_rows(c, lv.special_map, XformIO{acc, acc, acc_ps, acc_ps, 2 * bc}, s);
-    launch_ntt_inv_cols(c, lv.special_map, acc, acc_ps, 2 * bc, c->d_moddown_scale, true, true, s);
+    if (!special_rows_done) launch_inv_rows_packed(c, lv.special_map, acc, acc_ps, 1, acc, acc_ps, 2 * bc, s);
+    launch_inv_cols_packed(c, lv.special_map, acc, acc_ps, 2 * bc, c->d_moddown_scale, s);
     launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s, moddown_ops(c, lv));
-    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 0, 0, 1, bc, s, nullptr, out_words32, accq);
+    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 0, 0, 1, bc, s, nullptr, out_words32);
 }
 
 }  // namespace
@@ -143,7 +149,7 @@ extern "C" size_t ks_workspace_bytes(const ks_ctx* c, int op, uint32_t ell, uint
         case KS_OP_BSGS_U32: {
             // accumulators of the outer level, inner result [bc][2][ell], the gathers' sources of both levels (the
             // inner results are 64-bit words either way)
-            const KsWorkspace w = ks_ws_words(c, lv, bc);
+            const KsWorkspaceWords w = ks_ws_words(c, lv, bc);
             words += w.acc + (uint64_t)bc * 2 * ell * N + gather_words(c, lv, bc, true, op == KS_OP_BSGS_U32) +
                      gather_words(c, lv, bc, false, false);
             break;
@@ -316,17 +322,16 @@ int ks::keyswitch_impl(const ks_ctx* c, const void* d, uint32_t ell, const void*
     const uint64_t N = c->N, d_ps = (uint64_t)ell * N, out_bs = 2ull * ell * N, word = words32 ? 4 : 8;
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
-        const KsWorkspace w = ks_ws_words(c, lv, bc);
-        uint64_t* coeff = static_cast<uint64_t*>(ws);
-        uint64_t* lifted = coeff + w.coeff;
-        uint64_t* acc = lifted + w.lifted;
-        uint64_t* conv = acc + w.acc;
-        const PackedDigits accq = packed_at(conv + w.conv, w.conv);
+        const KsWorkspace w = ks_ws_regions(c, lv, bc);
+        uint8_t* coeff = static_cast<uint8_t*>(ws);
+        uint8_t* lifted = coeff + w.coeff;
+        uint8_t* acc = lifted + w.lifted;
+        uint8_t* conv = acc + w.acc;
         const char* dc = static_cast<const char*>(d) + (uint64_t)b0 * d_ps * word;
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
         mod_up(c, lv, dc, d_ps, coeff, lifted, bc, tile, s, words32);
-        launch_rows_inner_product(c, lv, dc, d_ps, lifted, evk, acc, bc, s, words32, words32, accq);
-        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * out_bs * word, out_bs, bc, true, tile, s, words32, &accq);
+        launch_rows_inner_product(c, lv, dc, d_ps, lifted, evk, acc, bc, s, words32, words32);
+        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * out_bs * word, out_bs, bc, true, tile, s, words32);
     }
     return finish(words32 ? "ks_keyswitch_u32" : "ks_keyswitch");
 }
@@ -360,15 +365,15 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
     const uint64_t N = c->N, ct_bs = 2ull * ell * N, out_bs = (uint64_t)n_rot * 2 * ell * N, word = words32 ? 4 : 8;
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
-        const KsWorkspace w = ks_ws_words(c, lv, bc);
+        const KsWorkspace w = ks_ws_regions(c, lv, bc);
         // The gathers read c1 and its finished raised digits from a compact bundle; the last kernel's addend c0 is gathered
         // from the ciphertext in its own word size.
         uint64_t* region = static_cast<uint64_t*>(ws);
-        uint64_t* coeff = region + gather_words(c, lv, bc, false, words32);
+        uint8_t* coeff = reinterpret_cast<uint8_t*>(region + gather_words(c, lv, bc, false, words32));
         const char* c0 = static_cast<const char*>(ct) + (uint64_t)b0 * ct_bs * word;
         const void* c1 = c0 + (uint64_t)ell * N * word;
-        uint64_t* lifted = coeff + w.coeff;
-        uint64_t* acc = lifted + w.lifted;
+        uint8_t* lifted = coeff + w.coeff;
+        uint8_t* acc = lifted + w.lifted;
         const uint32_t group = std::min(n_rot, kRotGroup);
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * group * bc);
         // finished once, shared by every rotation
@@ -376,11 +381,8 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
         // Rotations go in groups: one gather launch forms the accumulators of the whole group (the raised digits then come
         // from memory once per group), the inverse transform and the conversion run over the group as one batch, and only
         // the last kernel, which adds sigma_g(c0) through a rotation's own permutation, runs per rotation.
-        uint64_t* conv = acc + (uint64_t)group * w.acc;
-        // ciphertext limbs of the group's accumulators, packed: [group][bc][2][ell][N]
-        const uint64_t accq_n = w.conv;
-        const PackedDigits accq = packed_at(conv + (uint64_t)group * w.conv, (uint64_t)group * accq_n);
-        const uint64_t acc_ps = (uint64_t)lv.E * N, conv_ps = (uint64_t)ell * N;
+        uint8_t* conv = acc + (uint64_t)group * w.acc;
+        const uint64_t limb = packed_limb_bytes(N), acc_ps = lv.E * limb, conv_ps = ell * limb;
         for (uint32_t r0 = 0; r0 < n_rot; r0 += group) {
             MacRotations rot;
             rot.n = std::min(n_rot - r0, group);
@@ -389,17 +391,15 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
                 rot.key[r] = rot_keys[r0 + r];
                 rot.pt[r] = nullptr;
             }
-            launch_inner_product(c, lv, digits, rot, acc, accq, s, words32);
+            launch_inner_product(c, lv, digits, rot, acc, s, words32);
             const uint32_t polys = 2 * rot.n * bc;
-            launch_ntt_inv_rows(c, lv.special_map, XformIO{acc, acc, acc_ps, acc_ps, polys}, s);
-            launch_ntt_inv_cols(c, lv.special_map, acc, acc_ps, polys, c->d_moddown_scale, true, true, s);
+            launch_inv_rows_packed(c, lv.special_map, acc, acc_ps, 1, acc, acc_ps, polys, s);
+            launch_inv_cols_packed(c, lv.special_map, acc, acc_ps, polys, c->d_moddown_scale, s);
             launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, polys, tile, s, moddown_ops(c, lv));
-            for (uint32_t r = 0; r < rot.n; ++r) {
-                const PackedDigits accq_r{accq.lo + (uint64_t)r * accq_n, accq.hi + (uint64_t)r * accq_n};
-                launch_rows_moddown_finish(c, lv, nullptr, conv + (uint64_t)r * w.conv,
+            for (uint32_t r = 0; r < rot.n; ++r)
+                launch_rows_moddown_finish(c, lv, acc + r * w.acc, conv + r * w.conv,
                                            static_cast<char*>(out) + ((uint64_t)b0 * out_bs + (uint64_t)(r0 + r) * 2 * ell * N) * word,
-                                           out_bs, c0, ct_bs, 1, galois[r0 + r], bc, s, nullptr, words32, &accq_r);
-            }
+                                           out_bs, c0, ct_bs, 1, galois[r0 + r], bc, s, nullptr, words32);
         }
     }
     return finish(words32 ? "ks_rotate_hoisted_u32" : "ks_rotate_hoisted");
@@ -433,7 +433,7 @@ static int check_mac_rotations(const ks_ctx* c, const uint32_t* galois, const vo
 
 // u (+)= sum_r pt_r * rot_{g_r}(ct) for all n rotations, in launches of kMacRotations
 static void rotate_mac_all(const ks_ctx* c, const Level& lv, const GatherBundle& src,
-                           const uint32_t* galois, const void* const* keys, const void* const* pts, uint32_t n, uint64_t* u,
+                           const uint32_t* galois, const void* const* keys, const void* const* pts, uint32_t n, uint8_t* u,
                            bool accumulate, hipStream_t s, bool key_words32 = false) {
     for (uint32_t r0 = 0; r0 < n; r0 += kMacRotations) {
         MacRotations rot;
@@ -462,14 +462,14 @@ static int rotate_mac_impl(const ks_ctx* c, const void* ct, uint32_t ell, const 
     const uint64_t N = c->N, ct_bs = 2ull * ell * N, word = words32 ? 4 : 8;
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
-        const KsWorkspace w = ks_ws_words(c, lv, bc);
+        const KsWorkspace w = ks_ws_regions(c, lv, bc);
         // the gathers read c1 and its finished raised digits, and c0 for many rotations, from a compact bundle
         const char* c0 = static_cast<const char*>(ct) + (uint64_t)b0 * ct_bs * word;
         uint64_t* region = static_cast<uint64_t*>(ws);
-        uint64_t* coeff = region + gather_words(c, lv, bc, n_rot >= kC0InBundle, words32);
-        uint64_t* lifted = coeff + w.coeff;
-        uint64_t* acc = lifted + w.lifted;
-        uint64_t* conv = acc + w.acc;
+        uint8_t* coeff = reinterpret_cast<uint8_t*>(region + gather_words(c, lv, bc, n_rot >= kC0InBundle, words32));
+        uint8_t* lifted = coeff + w.coeff;
+        uint8_t* acc = lifted + w.lifted;
+        uint8_t* conv = acc + w.acc;
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
         // finished once, shared by every rotation
         const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, n_rot, tile, s, words32);
@@ -510,18 +510,18 @@ static int bsgs_impl(const ks_ctx* c, const void* ct, uint32_t ell, const uint32
     const uint64_t N = c->N, ct_bs = 2ull * ell * N, word = words32 ? 4 : 8;
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
-        const KsWorkspace w = ks_ws_words(c, lv, bc);
+        const KsWorkspace w = ks_ws_regions(c, lv, bc);
         // The gathers of the inner level read the input ciphertext and its finished raised digits from a compact bundle; the
         // inner results are 64-bit words either way, so the outer level's bundle is the packed one.
         const char* c0 = static_cast<const char*>(ct) + (uint64_t)b0 * ct_bs * word;
         uint64_t* region = static_cast<uint64_t*>(ws);   // sources of the inner level, shared by every baby step of every giant step
         uint64_t* region_v = region + gather_words(c, lv, bc, true, words32);   // sources of the outer level: the current inner result
-        uint64_t* coeff = region_v + gather_words(c, lv, bc, false, false);
-        uint64_t* lifted = coeff + w.coeff;          // scratch of a ModUp
-        uint64_t* acc = lifted + w.lifted;           // inner sum of the current giant step
-        uint64_t* conv = acc + w.acc;
-        uint64_t* acc_outer = conv + w.conv;         // outer sum over the giant steps
-        uint64_t* v = acc_outer + w.acc;             // [bc][2][ell][N] inner result of the current giant step (64-bit words)
+        uint8_t* coeff = reinterpret_cast<uint8_t*>(region_v + gather_words(c, lv, bc, false, false));
+        uint8_t* lifted = coeff + w.coeff;          // scratch of a ModUp
+        uint8_t* acc = lifted + w.lifted;           // inner sum of the current giant step
+        uint8_t* conv = acc + w.acc;
+        uint8_t* acc_outer = conv + w.conv;         // outer sum over the giant steps
+        uint64_t* v = reinterpret_cast<uint64_t*>(acc_outer + w.acc);   // [bc][2][ell][N] inner result of the current giant step (64-bit words)
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
         const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, n1 * n2, tile, s, words32);
         for (uint32_t g = 0; g < n2; ++g) {
@@ -558,18 +558,17 @@ extern "C" int ks_bsgs_linear_transform_u32(const ks_ctx* c, const uint32_t* ct,
 // Division by P q_{ell-1} of acc + P addend in one conversion to q_0..q_{ell-2}, limb ell-1 joining the special limbs as a
 // source.  merged: ModDown and rescale merged (floor throughout); otherwise floor(/ P), then round(/ q_{ell-1}).  The fused
 // inner product has already added the dropped limb's addend and run the row half of the inverse transform on the sources.
-// accq: the ciphertext limbs below ell-1 of the accumulators, packed.  addend: [b][2][ell][N] packed.
-static void mod_down_drop(const ks_ctx* c, const Level& lv, uint64_t* acc, uint64_t* conv, void* out, uint64_t out_bs,
-                          const PackedDigits& addend, uint32_t bc, int tile, hipStream_t s, bool merged, bool out_words32,
-                          const PackedDigits& accq) {
-    const uint64_t N = c->N, acc_ps = (uint64_t)lv.E * N, conv_ps = (uint64_t)lv.ell * N;
-    launch_ntt_inv_cols(c, lv.drop_map, acc, acc_ps, 2 * bc, merged ? lv.d_merged_scale : lv.d_rescale_scale, true, true, s);
+// addend: [b][2][ell] packed.
+static void mod_down_drop(const ks_ctx* c, const Level& lv, uint8_t* acc, uint8_t* conv, void* out, uint64_t out_bs,
+                          const uint8_t* addend, uint32_t bc, int tile, hipStream_t s, bool merged, bool out_words32) {
+    const uint64_t limb = packed_limb_bytes(c->N), acc_ps = lv.E * limb, conv_ps = lv.ell * limb;
+    launch_inv_cols_packed(c, lv.drop_map, acc, acc_ps, 2 * bc, merged ? lv.d_merged_scale : lv.d_rescale_scale, s);
     if (!merged) launch_rescale_remainder(c, lv, acc, 2 * bc, s);
     const uint32_t n_src = c->K + 1, n_dst = lv.ell - 1;
     const double ops = (double)n_src * n_dst * 4.5 + n_dst * (3.0 + 4.0 * (c->logN - 8));
     launch_bconv_ntt_cols(c, merged ? lv.merged : lv.rescale, n_src + n_dst, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s, ops);
     const FinishScale fs{lv.d_Dinv, lv.d_qlinv, n_dst};
-    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 2ull * lv.ell * N, 2, 1, bc, s, &fs, out_words32, &accq, &addend);
+    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, addend, 0, 2, 1, bc, s, &fs, out_words32);
 }
 
 // cta, ctb, rlk and out in 64-bit words, or all four in 32-bit words (words32); the tensor product and everything after it
@@ -588,22 +587,21 @@ static int hmult_impl(const ks_ctx* c, const void* cta, const void* ctb, uint32_
     const uint64_t N = c->N, ct_bs = 2ull * ell * N, out_bs = 2ull * (ell - 1) * N, word = words32 ? 4 : 8;
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
-        const KsWorkspace w = ks_ws_words(c, lv, bc);
-        uint64_t* coeff = static_cast<uint64_t*>(ws);
-        uint64_t* lifted = coeff + w.coeff;
-        uint64_t* acc = lifted + w.lifted;
-        uint64_t* conv = acc + w.acc;
-        const PackedDigits accq = packed_at(conv + w.conv, w.conv);
-        uint64_t* d2 = conv + w.conv + w.accq;                  // [bc][ell][N], the polynomial that is key-switched
+        const KsWorkspace w = ks_ws_regions(c, lv, bc);
+        uint8_t* coeff = static_cast<uint8_t*>(ws);
+        uint8_t* lifted = coeff + w.coeff;
+        uint8_t* acc = lifted + w.lifted;
+        uint8_t* conv = acc + w.acc;
+        uint8_t* dq = conv + w.conv;                                    // (d0, d1): [bc][2][ell] packed
+        uint64_t* d2 = reinterpret_cast<uint64_t*>(dq + w.conv);        // [bc][ell][N], the polynomial that is key-switched
         const uint64_t d2_ps = (uint64_t)ell * N;
-        const PackedDigits dq = packed_at(d2 + (uint64_t)bc * d2_ps, w.conv);   // (d0, d1): [bc][2][ell][N] packed
         char* oc = static_cast<char*>(out) + (uint64_t)b0 * out_bs * word;
         launch_tensor_product(c, static_cast<const char*>(cta) + (uint64_t)b0 * ct_bs * word,
                               static_cast<const char*>(ctb) + (uint64_t)b0 * ct_bs * word, d2, dq, ell, bc, s, words32);
         const int tile = conversion_tile(c, lv.modup, bc, merged ? lv.merged : lv.rescale, 2 * bc);
         mod_up(c, lv, d2, d2_ps, coeff, lifted, bc, tile, s);
-        launch_rows_inner_product(c, lv, d2, d2_ps, lifted, rlk, acc, bc, s, false, words32, accq, &dq);
-        mod_down_drop(c, lv, acc, conv, oc, out_bs, dq, bc, tile, s, merged, words32, accq);
+        launch_rows_inner_product(c, lv, d2, d2_ps, lifted, rlk, acc, bc, s, false, words32, dq);
+        mod_down_drop(c, lv, acc, conv, oc, out_bs, dq, bc, tile, s, merged, words32);
     }
     if (merged) return finish(words32 ? "hmult_relin_rescale_merged_u32" : "hmult_relin_rescale_merged");
     return finish(words32 ? "hmult_relin_rescale_u32" : "hmult_relin_rescale");

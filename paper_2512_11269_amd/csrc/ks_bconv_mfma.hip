@@ -29,8 +29,8 @@ constexpr int mfma_min_blocks(int tl) { return tl == 1 ? 4 : 2; }
 
 template <int LOG_R, int TL, int NM, int NPS, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? mfma_min_blocks(TL) : 1) void bconv_mfma_ntt_cols(const double* __restrict__ tw, const BConvPlan* __restrict__ plans,
-                                                           LaunchMeta meta, const uint64_t* __restrict__ y, uint64_t y_ps,
-                                                           uint64_t* __restrict__ out, uint64_t out_ps, uint32_t n_subsets, uint32_t pair) {
+                                                           LaunchMeta meta, const uint8_t* __restrict__ y, uint64_t y_ps,
+                                                           uint8_t* __restrict__ out, uint64_t out_ps, uint32_t n_subsets, uint32_t pair) {
     using Shape = MfmaConvShape<LOG_R, TL, WAVES>;
     __shared__ double lds[Shape::LDS_WORDS];
     __shared__ double lds_tw[Shape::LDS_TW_WORDS];
@@ -44,14 +44,14 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? mfma_min_blocks(TL) : 1) v
     // ciphertexts, L = 35: 438 -> 386 us of conversions).  Not where one round holds the whole launch: there the second fetch is
     // served by the memory-side cache and pairing cost the single-ciphertext key-switch 1.3 % (106.2 -> 107.6 us).
     if (Shape::TC == 8 && pair) tile = (tile & ~15u) | ((tile & 7u) << 1) | ((tile >> 3) & 1u);
-    task_bconv_mfma_cols<LOG_R, TL, NM, NPS, WAVES>(tw, plans[plan_id], PM, y + (uint64_t)blockIdx.z * y_ps, y_ps * 8,
+    task_bconv_mfma_cols<LOG_R, TL, NM, NPS, WAVES>(tw, plans[plan_id], PM, y + (uint64_t)blockIdx.z * y_ps, y_ps,
                                              out + (uint64_t)blockIdx.z * out_ps, tile, t0, threadIdx.x, lds, lds_tw);
 }
 
 // Targets per lane half: one gives the most workgroups, three shares the byte-cutting of the sources among the most
 // targets (and keeps the stores of one target under the butterflies of the next).  wide: tiles of 16 columns and 512 threads
 // instead of 8 and 256 at N = 2^16, whole 128-byte lines, for launches of many rounds and many sources (conversion_tile).
-void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uint64_t* y, uint64_t y_ps, uint64_t* out,
+void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uint8_t* y, uint64_t y_ps, uint8_t* out,
                                 uint64_t out_ps, uint32_t n_polys, int tl, bool wide, hipStream_t s) {
     const uint32_t n_src = plans.shape_src, n_plans = plans.n_plans, max_targets = plans.max_targets;
     const BConvPlan* d_plans = plans.d_plans;

@@ -105,6 +105,7 @@ void fill_bconv_plan(const ks_ctx* c, BConvPlan* plan, const uint32_t* src_ids, 
         plan->trec[t].m = plan->dst_mod[t];
         plan->trec[t].mod_id = dst_ids[t];
         plan->trec[t].limb = dst_limb[t];
+        uint64_t start = 0;
         for (uint32_t i = 0; i < n_src; ++i) {
             uint64_t prod = 1 % mt;
             for (uint32_t k = 0; k < n_basis; ++k)
@@ -116,7 +117,9 @@ void fill_bconv_plan(const ks_ctx* c, BConvPlan* plan, const uint32_t* src_ids, 
                 const uint64_t f = h_mulmod(prod, (1ull << (cut * k)) % mt, mt);
                 const double centred = f > mt / 2 ? -(double)(mt - f) : (double)f;
                 plan->hats[t][i][k] = k < c->pieces ? ldexp(centred, -cut * k) : 0.0;
+                if (k + 1 == c->pieces) plan->hats[t][i][3] = centred;
             }
+            start = (start + h_mulmod(prod, 0x80808080ull % mt, mt)) % mt;
             // matrix-core operand rows: digit b of centred([(D / s_i) 256^a]_t), at the byte that pairs with digit a of source i
             const uint32_t slot = i / plan->mfma_nps, e = i % plan->mfma_nps;
             for (int a = 0; a < kMfmaPlanes; ++a) {
@@ -129,6 +132,7 @@ void fill_bconv_plan(const ks_ctx* c, BConvPlan* plan, const uint32_t* src_ids, 
                 }
             }
         }
+        plan->dst_start[t] = start > mt / 2 ? (double)(mt - start) : -(double)start;
     }
 }
 

@@ -117,14 +117,11 @@ static uint32_t gather_grid(const ks_ctx* c, uint32_t E, uint32_t parts_log) {
 // rotations of the launch; the operands of the next (rotation, digit) are requested before the current products.
 // WK: word type of the keys; PACKED: the bundle's sources have bits above 32.
 // Four rotations of 8 ciphertexts, N = 2^16, E = 32, three digits: 350 -> 315 us, 1.4 GB of compulsory traffic.
-// The special limbs of the result go to acc ([r][b][2][E][N] 64-bit words, the inverse transform reads them next), the
-// ciphertext limbs to (accq_lo, accq_hi) as [r][b][2][ell][N] packed residues: they are only read back by the last
-// kernel of the rotation, and written and read once per rotation they are a fifth of these two kernels' traffic.
+// The result is packed ([r][b][2][E] limbs in rows order).
 template <int G, typename WK, bool PACKED>
 __global__ __launch_bounds__(256, 4) void inner_product_kernel(const Mod* __restrict__ mods, uint32_t ell, uint32_t E, uint32_t L, uint32_t M,
                                                             uint32_t logN, uint32_t ndig, uint32_t parts_log, GatherBundle src,
-                                                            MacRotations rot, uint64_t* __restrict__ acc, uint32_t* __restrict__ accq_lo,
-                                                            uint8_t* __restrict__ accq_hi) {
+                                                            MacRotations rot, uint8_t* __restrict__ acc) {
     const uint32_t N = 1u << logN;
     const GatherTile tile = gather_tile(E, logN, parts_log);
     if (!tile.valid) return;  // uniform
@@ -147,6 +144,7 @@ __global__ __launch_bounds__(256, 4) void inner_product_kernel(const Mod* __rest
         return w;
     };
     Raw cur = fetch(0, 0);
+    const uint32_t element = packed_element(n & ~63u);
 #pragma unroll 1
     for (uint32_t r = 0; r < rot.n; ++r) {
         double h0[G], l0[G], h1[G], l1[G];
@@ -169,22 +167,14 @@ __global__ __launch_bounds__(256, 4) void inner_product_kernel(const Mod* __rest
             }
             cur = next;
         }
-        uint64_t* ar = acc + (uint64_t)r * G * 2 * E * N;
-        const uint64_t rq = (uint64_t)r * G * 2 * ell * N;
+        uint8_t* ar = acc + ((uint64_t)r * G * 2 * E + pos) * packed_limb_bytes(N);
+        double sums[2 * G];
 #pragma unroll
         for (int b = 0; b < G; ++b) {
-            const uint64_t u0 = f64_to_u64(canon(mac_reduce(h0[b], l0[b], m), m)), u1 = f64_to_u64(canon(mac_reduce(h1[b], l1[b], m), m));
-            if (pos < ell) {  // uniform: ciphertext limbs go out packed, 5 bytes a residue
-                const uint64_t e0 = rq + (((uint64_t)b * 2 + 0) * ell + pos) * N + n, e1 = e0 + (uint64_t)ell * N;
-                accq_lo[e0] = (uint32_t)u0;
-                accq_hi[e0] = (uint8_t)(u0 >> 32);
-                accq_lo[e1] = (uint32_t)u1;
-                accq_hi[e1] = (uint8_t)(u1 >> 32);
-            } else {
-                ar[(((uint64_t)b * 2 + 0) * E + pos) * N + n] = u0;
-                ar[(((uint64_t)b * 2 + 1) * E + pos) * N + n] = u1;
-            }
+            sums[2 * b] = mac_reduce(h0[b], l0[b], m);
+            sums[2 * b + 1] = mac_reduce(h1[b], l1[b], m);
         }
+        packed_put<2 * G>(ar, E * packed_limb_bytes(N), N, element, sums);
     }
 }
 
@@ -200,8 +190,8 @@ __global__ __launch_bounds__(256, 4) void inner_product_kernel(const Mod* __rest
 // bytes a gathered source residue takes
 static double src_bytes(const GatherBundle& g) { return g.hi ? 4.0 + (double)gather_hi_bytes(g.group) / g.group : 4.0; }
 
-void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* acc,
-                          const PackedDigits& accq, hipStream_t s, bool key_words32) {
+void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint8_t* acc,
+                          hipStream_t s, bool key_words32) {
     if (rot.n == 0) return;
     const uint32_t batch = src.group;
     const uint32_t pl = gather_parts_log(lv.E);
@@ -209,11 +199,11 @@ void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& 
     // every rotation
     const double wk = key_words32 ? 4.0 : 8.0;
     ProfScope ps("inner_product",
-                 (src_bytes(src) * batch * lv.ndig * lv.E + (double)rot.n * (wk * 2.0 * lv.ndig * lv.E + (16.0 * (lv.E - lv.ell) + 10.0 * lv.ell) * batch)) * c->N,
+                 (src_bytes(src) * batch * lv.ndig * lv.E + (double)rot.n * (wk * 2.0 * lv.ndig * lv.E + 10.0 * lv.E * batch)) * c->N,
                  s);
 #define KS_GATHER_LAUNCH(GV, WKT, PK)                                                                                                     \
     hipLaunchKernelGGL((inner_product_kernel<GV, WKT, PK>), dim3(gather_grid(c, lv.E, pl)), dim3(256), 0, s, c->d_mod, lv.ell, lv.E, c->L, \
-                       c->M, c->logN, lv.ndig, pl, src, rot, acc, accq.lo, accq.hi)
+                       c->M, c->logN, lv.ndig, pl, src, rot, acc)
     KS_FOR_GATHER_KERNEL()
 #undef KS_GATHER_LAUNCH
 }
@@ -235,20 +225,22 @@ template <int G, typename WK, bool PACKED>
 __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restrict__ mods, const double* __restrict__ Pmod, uint32_t ell,
                                                          uint32_t E, uint32_t L, uint32_t M, uint32_t logN, DigitRanges dg,
                                                          uint32_t parts_log, GatherBundle src, MacRotations rot, uint32_t n_key,
-                                                         uint64_t* __restrict__ u, int accumulate) {
+                                                         uint8_t* __restrict__ u, int accumulate) {
     const uint32_t N = 1u << logN;
     const GatherTile tile = gather_tile(E, logN, parts_log);
     if (!tile.valid) return;  // uniform
     const uint32_t pos = tile.pos, n = tile.n, mid = pos < ell ? pos : L + (pos - ell);
     const Mod m = mods[mid];
     const BundleRsrc bundle = bundle_rsrc<G>(src, ((uint64_t)dg.ndig * E + ell) * N);
+    const uint32_t element = packed_element(n);
+    uint8_t* up = u + (uint64_t)pos * packed_limb_bytes(N);
+    const uint64_t comp = E * packed_limb_bytes(N);
     double h0[G], l0[G], h1[G], l1[G];
 #pragma unroll
     for (int b = 0; b < G; ++b) {
         h0[b] = h1[b] = kMacBias;
-        const uint64_t* ub = u + ((uint64_t)b * 2 * E + pos) * N;
-        l0[b] = accumulate ? u64_to_f64(ub[n]) : 0.0;
-        l1[b] = accumulate ? u64_to_f64(ub[(uint64_t)E * N + n]) : 0.0;
+        l0[b] = accumulate ? packed_get(up + 2 * b * comp, N, element) : 0.0;
+        l1[b] = accumulate ? packed_get(up + (2 * b + 1) * comp, N, element) : 0.0;
     }
     struct Raw {
         SlotRaw<G> x;
@@ -351,15 +343,16 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
             for (int b = 0; b < G; ++b) mac_exact(slot_f64<G, PACKED>(x, b), pw, h1[b], l1[b]);
         }
     }
+    double sums[2 * G];
 #pragma unroll
     for (int b = 0; b < G; ++b) {
-        uint64_t* ub = u + ((uint64_t)b * 2 * E + pos) * N + n;
-        ub[0] = f64_to_u64(canon(mac_reduce(h0[b], l0[b], m), m));
-        ub[(uint64_t)E * N] = f64_to_u64(canon(mac_reduce(h1[b], l1[b], m), m));
+        sums[2 * b] = mac_reduce(h0[b], l0[b], m);
+        sums[2 * b + 1] = mac_reduce(h1[b], l1[b], m);
     }
+    packed_put<2 * G>(up, comp, N, packed_element(n & ~63u), sums);
 }
 
-void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* u,
+void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint8_t* u,
                        bool accumulate, hipStream_t s, bool key_words32) {
     if (rot.n == 0) return;
     const uint32_t batch = src.group;
@@ -385,7 +378,7 @@ void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src
     // the gather; those re-reads are meant to come from cache), key and plaintext of every rotation once, both sums written
     // once.  Algorithmic work per slot, ciphertext and rotation: 2 NDIG + 1 exact products (+ 2 NDIG + 1 modular ones per group).
     const double reads = batch * src_bytes(src) * (lv.ndig * lv.E + lv.ell) + (key_words32 ? 4.0 : 8.0) * (double)rot.n * (2.0 * lv.ndig + 1.0) * lv.E;
-    ProfScope ps("rotate_mac", (reads + (double)batch * 16 * lv.E * (accumulate ? 2 : 1)) * c->N, s,
+    ProfScope ps("rotate_mac", (reads + (double)batch * 10 * lv.E * (accumulate ? 2 : 1)) * c->N, s,
                  (double)rot.n * lv.E * c->N * (4.0 * batch + 6.0) * (2 * lv.ndig + 1));
 #define KS_GATHER_LAUNCH(GV, WKT, PK)                                                                                                     \
     hipLaunchKernelGGL((rotate_mac_kernel<GV, WKT, PK>), dim3(gather_grid(c, lv.E, pl)), dim3(256), 0, s, c->d_mod, c->d_Pmod, lv.ell, lv.E, \
@@ -399,38 +392,33 @@ void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src
 }
 
 // (b1, a1) x (b2, a2) -> d0 = b1 b2, d1 = a1 b2 + a2 b1, d2 = a1 a2.  d2, the polynomial that is key-switched, goes out as
-// 64-bit words ([b][ell][N]); d0 and d1 are only added back by the last kernel of the chain and go out packed
-// ([b][2][ell][N]: bits 0..31 in dq_lo, the bits above in dq_hi).
+// 64-bit words ([b][ell][N]); d0 and d1 are only added back by the last kernel of the chain and go out packed ([b][2][ell] limbs
+// in rows order).
 template <typename W>
 __global__ __launch_bounds__(256) void tensor_product_kernel(const Mod* __restrict__ mods, uint32_t ell, uint32_t N,
                                                              const W* __restrict__ cta, const W* __restrict__ ctb,
-                                                             uint64_t* __restrict__ d2, uint32_t* __restrict__ dq_lo,
-                                                             uint8_t* __restrict__ dq_hi) {
+                                                             uint64_t* __restrict__ d2, uint8_t* __restrict__ dq) {
     const uint32_t i = blockIdx.y, b = blockIdx.z;
     const Mod m = mods[i];
     const uint64_t n = blockIdx.x * 256 + threadIdx.x;
     const uint64_t ct_off = ((uint64_t)b * 2 * ell + i) * N + n, comp = (uint64_t)ell * N;
     const double b1 = word_to_f64<W>(cta[ct_off]), a1 = word_to_f64<W>(cta[ct_off + comp]);
     const double b2 = word_to_f64<W>(ctb[ct_off]), a2 = word_to_f64<W>(ctb[ct_off + comp]);
-    const uint64_t u0 = f64_to_u64(canon(mulmod_lazy(b1, b2, m), m));
-    const uint64_t u1 = f64_to_u64(canon(reduce_lazy(mulmod_lazy(a1, b2, m) + mulmod_lazy(a2, b1, m), m), m));
-    dq_lo[ct_off] = (uint32_t)u0;
-    dq_hi[ct_off] = (uint8_t)(u0 >> 32);
-    dq_lo[ct_off + comp] = (uint32_t)u1;
-    dq_hi[ct_off + comp] = (uint8_t)(u1 >> 32);
+    const double sums[2] = {mulmod_lazy(b1, b2, m), reduce_lazy(mulmod_lazy(a1, b2, m) + mulmod_lazy(a2, b1, m), m)};
+    packed_put<2>(dq + ((uint64_t)b * 2 * ell + i) * packed_limb_bytes(N), ell * packed_limb_bytes(N), N, packed_element((uint32_t)n & ~63u), sums);
     d2[((uint64_t)b * ell + i) * N + n] = f64_to_u64(canon(mulmod_lazy(a1, a2, m), m));
 }
 
-void launch_tensor_product(const ks_ctx* c, const void* cta, const void* ctb, uint64_t* d2, const PackedDigits& dq, uint32_t ell,
+void launch_tensor_product(const ks_ctx* c, const void* cta, const void* ctb, uint64_t* d2, uint8_t* dq, uint32_t ell,
                            uint32_t batch, hipStream_t s, bool in_words32) {
     if (batch == 0) return;
     ProfScope ps("tensor_product", (double)batch * ell * ((in_words32 ? 16 : 32) + 8 + 10) * c->N, s);
     if (in_words32)
         hipLaunchKernelGGL(tensor_product_kernel<uint32_t>, dim3(c->N / 256, ell, batch), dim3(256), 0, s, c->d_mod, ell, c->N,
-                           static_cast<const uint32_t*>(cta), static_cast<const uint32_t*>(ctb), d2, dq.lo, dq.hi);
+                           static_cast<const uint32_t*>(cta), static_cast<const uint32_t*>(ctb), d2, dq);
     else
         hipLaunchKernelGGL(tensor_product_kernel<uint64_t>, dim3(c->N / 256, ell, batch), dim3(256), 0, s, c->d_mod, ell, c->N,
-                           static_cast<const uint64_t*>(cta), static_cast<const uint64_t*>(ctb), d2, dq.lo, dq.hi);
+                           static_cast<const uint64_t*>(cta), static_cast<const uint64_t*>(ctb), d2, dq);
 }
 
 }  // namespace ks

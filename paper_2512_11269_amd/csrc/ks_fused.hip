@@ -16,62 +16,59 @@
 
 namespace ks {
 
-// One source of a conversion: acc[t][k] += y[k] * f[t] as exact integers -- each source point is split once (split3, or
-// split2 when every modulus is below 2^32), every target adds PIECES products against its shifted, centred factors.
-// REFILL: once y[k] has been consumed, the same registers receive point k of the next source (byte offset next_off in
-// the buffer), which then has a whole source's worth of arithmetic to arrive.
-// The factors of the next source (fnext: uniform, scalar loads) are requested after the first point, together with
-// the limb index of the source after next: scalar loads complete out of order, so the first use of f waits for every
-// scalar load in flight, and at that moment only f's own, requested a source ago, should be.
-template <int LOG_R, int TS, bool REFILL, int PIECES>
-__device__ __forceinline__ void bconv_accumulate(double (&acc)[TS][16], double (&y)[16], const double (&f)[TS][3],
-                                                 double (&fnext)[TS][3], const double* const (&hat_row)[TS], int inext,
-                                                 uint32_t& limb_after, const uint32_t* src_limb, int iafter, BufferRsrc rsrc,
-                                                 uint32_t lane_off, uint32_t next_off) {
+// The 16 positions of a source that a thread owns, as they lie in memory (kDigitBias).
+struct SourceRaw {
+    Words4 lo[4], top;
+};
+template <int LOG_R>
+__device__ __forceinline__ SourceRaw load_source(BufferRsrc rsrc, uint32_t limb, uint32_t lo_off, uint32_t top_off) {
+    constexpr uint32_t N = 256u << LOG_R;
+    const uint32_t base = limb * (uint32_t)packed_limb_bytes(N);
+    SourceRaw r;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        r.lo[q] = __builtin_bit_cast(Words4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)lo_off, (int)(base + q * 4096), 0));
+    r.top = __builtin_bit_cast(Words4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)top_off, (int)(base + 4 * N), 0));
+    return r;
+}
+
+// One source of a conversion: acc[t][k] += (y[k] + 0x80808080) * f[t] as exact integers (the constant is taken out by what acc
+// starts from).  The 40 bits of a source point are cut once into PIECES whole numbers, every target adds PIECES products
+// against its centred factors; the bounds of these sums are stated at BConvPlan::hats.
+template <int TS, int PIECES>
+__device__ __forceinline__ void bconv_accumulate(double (&acc)[TS][16], const SourceRaw& y, const double (&f)[TS][3]) {
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
-        double y2 = 0.0, y1, y0;
-        if constexpr (PIECES == 3) split3(y[k], y2, y1, y0);
-        else split2(y[k], y1, y0);
-        if (REFILL) y[k] = load_strided_point<LOG_R>(rsrc, lane_off, next_off, k);
-#pragma unroll
-        for (int tt = 0; tt < TS; ++tt) {
-            acc[tt][k] = __builtin_fma(y1, f[tt][1], __builtin_fma(y0, f[tt][0], acc[tt][k]));
-            if constexpr (PIECES == 3) acc[tt][k] = __builtin_fma(y2, f[tt][2], acc[tt][k]);
+        const uint32_t w = y.lo[k >> 2].w[k & 3];
+        const int top = (int)(y.top.w[k >> 2] << (24 - 8 * (k & 3))) >> 24;
+        double p[PIECES];
+        if constexpr (PIECES == 3) {
+            p[0] = (double)(w & 0xFFFu);
+            p[1] = (double)(w & 0xFFF000u);
+            p[2] = (double)(int)__builtin_amdgcn_alignbit((uint32_t)top, w, 24);
+        } else {
+            p[0] = (double)(w & 0xFFFFu);
+            p[1] = (double)(int)__builtin_amdgcn_alignbit((uint32_t)top, w, 16);
         }
-        if (k == 0) {
-            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int tt = 0; tt < TS; ++tt)
+        for (int tt = 0; tt < TS; ++tt)
 #pragma unroll
-                for (int p = 0; p < PIECES; ++p) fnext[tt][p] = hat_row[tt][inext * 4 + p];
-            limb_after = src_limb[iafter];
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-    // one refill per point, in order, each after a point's worth of arithmetic: the wait before point k then leaves 15
-    // loads in flight, while the arithmetic of neighbouring points may still interleave
-    if (REFILL) {
-#pragma unroll
-        for (int k = 1; k < 16; ++k) {
-            __builtin_amdgcn_sched_group_barrier(0x002, PIECES == 3 ? 6 + 3 * TS : 3 + 2 * TS, 0);
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-        }
+            for (int i = 0; i < PIECES; ++i) acc[tt][k] = __builtin_fma(p[i], f[tt][i], acc[tt][k]);
     }
 }
 
 // ------------------------------------------------------------------------------------------------
-// y: [poly][..][N] canonical doubles y_i = [x_i N^-1 (D/s_i)^-1]_{s_i} (written by ntt_inv_cols with its
-// scale table).  Each workgroup owns one column tile (4096 positions) and TS targets of one digit: it
-// accumulates sum_i y_i * (D/s_i mod t) as an exact integer (split3) for its 16 positions per thread, then runs the
-// column stages of the forward transform modulo t and stores raw doubles.  The sources are re-read by the workgroups of
-// the other target subsets; those reads are served by L2 / the last-level cache.
+// y: [poly][..] packed sources y_i = [x_i N^-1 (D/s_i)^-1]_{s_i} (written by inv_cols_packed with its scale table).  Each
+// workgroup owns one column tile (4096 positions) and TS targets of one digit: it accumulates sum_i y_i * (D/s_i mod t) as
+// an exact integer for its 16 positions per thread, then runs the column stages of the forward transform modulo t and stores
+// packed limbs.  The sources are re-read by the workgroups of the other target subsets; those reads are served by L2 / the
+// last-level cache.
 // ------------------------------------------------------------------------------------------------
 // PIECES: 3 in general (moduli below 2^36); 2 when every modulus of the context is below 2^32 (the plan's factors are
 // then cut at 16 bits: two products per source and target instead of three).
-template <int LOG_R, int TS, bool TWO_SETS, int PIECES>
+template <int LOG_R, int TS, int PIECES>
 __global__ __launch_bounds__(256) void bconv_ntt_cols(const double* __restrict__ tw, const BConvPlan* __restrict__ plans,
-                                                      const uint64_t* __restrict__ y, uint64_t y_ps, uint64_t* __restrict__ out,
+                                                      const uint8_t* __restrict__ y, uint64_t y_ps, uint8_t* __restrict__ out,
                                                       uint64_t out_ps, uint32_t n_subsets) {
     constexpr uint32_t N = 256u << LOG_R, TILES = 1u << (LOG_R - 4), TC = 256 / TILES;
     __shared__ double lds[LOG_R > 4 ? 4096 : 1];
@@ -81,82 +78,59 @@ __global__ __launch_bounds__(256) void bconv_ntt_cols(const double* __restrict__
     const int n_dst = (int)P.n_dst, n_src = (int)P.n_src;
     const int t0 = (int)subset * TS;
     if (t0 >= n_dst) return;  // uniform for the whole workgroup
-    const uint64_t* yp = y + (uint64_t)blockIdx.z * y_ps;
-    uint64_t* op = out + (uint64_t)blockIdx.z * out_ps;
+    const uint8_t* yp = y + (uint64_t)blockIdx.z * y_ps;
+    uint8_t* op = out + (uint64_t)blockIdx.z * out_ps;
     const uint32_t c = tid & (TC - 1), r0 = tid / TC, col = tile * TC + c;
-
-    double acc[TS][16];
-#pragma unroll
-    for (int tt = 0; tt < TS; ++tt)
-#pragma unroll
-        for (int k = 0; k < 16; ++k) acc[tt][k] = 0.0;
 
     // Per-target constants.  They are uniform across the workgroup and travel through scalar loads.
     Mod mt[TS];
     const double* hat_row[TS];
+    double acc[TS][16];
 #pragma unroll
     for (int tt = 0; tt < TS; ++tt) {
         const int t = min(t0 + tt, n_dst - 1);  // a ragged last subset recomputes its last target (stored once)
         mt[tt] = P.dst_mod[t];
         hat_row[tt] = &P.hats[t][0][0];
+        const double start = P.dst_start[t];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc[tt][k] = start;
     }
 
-    // Software pipeline over the sources, two per trip so that the uniform factors can alternate between two scalar
-    // register sets, with the limb index of the source after next fetched ahead as well: nothing is waited for right
-    // after it was requested.  The 16 points of a source are either held in ONE register set that is refilled point by
-    // point with the next source while it is consumed (fewer registers; best for the few-workgroup launches of a single
-    // ciphertext), or in TWO sets, the idle one filled by a burst of 16 loads (measured 6 % faster on full-chip launches).
-    // Sources past the end are zero-padded in the plan (factor 0, a valid limb): prefetches are unconditional -- a
+    // Software pipeline over the sources, two per trip so that the points and the uniform factors can alternate between two
+    // register sets, with the limb index of the source after next fetched ahead as well: nothing is waited for right after it was
+    // requested.  Sources past the end are zero-padded in the plan (factor 0, a valid limb): prefetches are unconditional -- a
     // conditional one would make the wait-count bookkeeping assume the worst at the join and stall every use on the
-    // newest loads -- and an odd source count simply runs one padding source.  Loads are fenced into use order, before
-    // the loop as inside it, so that every wait leaves exactly the younger loads in flight.  The points are read through a
-    // buffer descriptor of this polynomial's bundle: per-lane offset in a vector register, limb and row offset in a
+    // newest loads -- and an odd source count simply runs one padding source.  The factors of the next source are requested
+    // before the products of the current one: scalar loads complete out of order, so the first use of f waits for every
+    // scalar load in flight, and at that moment only f's own, requested a source ago, should be.  The points are read through
+    // a buffer descriptor of this polynomial's bundle: per-lane offset in a vector register, limb and row offset in a
     // scalar one, so switching limb costs no vector instructions.
-    const BufferRsrc ysrd = make_buffer_rsrc(yp, y_ps * 8);
-    const uint32_t lane_off = (r0 * 256 + col) * 8;
-    double yv[16], ha[TS][3], hb[TS][3];
+    const BufferRsrc ysrd = make_buffer_rsrc(yp, y_ps);
+    const uint32_t lo_off = (r0 * 1024 + col) * 16, top_off = source_bytes_offset(r0, col);
+    const auto load_factors = [&](double (&f)[TS][3], int i) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        yv[k] = load_strided_point<LOG_R>(ysrd, lane_off, P.src_limb[0] * (N * 8), k);
-        __builtin_amdgcn_sched_barrier(0);
-    }
+        for (int tt = 0; tt < TS; ++tt)
 #pragma unroll
-    for (int tt = 0; tt < TS; ++tt)
-#pragma unroll
-        for (int p = 0; p < PIECES; ++p) ha[tt][p] = hat_row[tt][p];
+            for (int p = 0; p < PIECES; ++p) f[tt][p] = hat_row[tt][i * 4 + (p + 1 < PIECES ? p : 3)];
+    };
+    SourceRaw ya = load_source<LOG_R>(ysrd, P.src_limb[0], lo_off, top_off), yb;
+    double fa[TS][3], fb[TS][3];
+    load_factors(fa, 0);
     uint32_t limb_next = P.src_limb[1];
-
-    if constexpr (!TWO_SETS) {
 #pragma unroll 1
-        for (int i = 0; i < n_src; i += 2) {
-            uint32_t limb_after;
-            bconv_accumulate<LOG_R, TS, true, PIECES>(acc, yv, ha, hb, hat_row, min(i + 1, kMaxSrc - 1), limb_after, P.src_limb,
-                                              min(i + 2, kMaxSrc - 1), ysrd, lane_off, limb_next * (N * 8));
-            bconv_accumulate<LOG_R, TS, true, PIECES>(acc, yv, hb, ha, hat_row, min(i + 2, kMaxSrc - 1), limb_next, P.src_limb,
-                                              min(i + 3, kMaxSrc - 1), ysrd, lane_off, limb_after * (N * 8));
-        }
-    } else {
-        double yw[16];
-#pragma unroll 1
-        for (int i = 0; i < n_src; i += 2) {
-            uint32_t limb_after;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                yw[k] = load_strided_point<LOG_R>(ysrd, lane_off, limb_next * (N * 8), k);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            bconv_accumulate<LOG_R, TS, false, PIECES>(acc, yv, ha, hb, hat_row, min(i + 1, kMaxSrc - 1), limb_after, P.src_limb,
-                                               min(i + 2, kMaxSrc - 1), ysrd, lane_off, 0);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                yv[k] = load_strided_point<LOG_R>(ysrd, lane_off, limb_after * (N * 8), k);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            bconv_accumulate<LOG_R, TS, false, PIECES>(acc, yw, hb, ha, hat_row, min(i + 2, kMaxSrc - 1), limb_next, P.src_limb,
-                                               min(i + 3, kMaxSrc - 1), ysrd, lane_off, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+    for (int i = 0; i < n_src; i += 2) {
+        yb = load_source<LOG_R>(ysrd, limb_next, lo_off, top_off);
+        load_factors(fb, min(i + 1, kMaxSrc - 1));
+        limb_next = P.src_limb[min(i + 2, kMaxSrc - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+        bconv_accumulate<TS, PIECES>(acc, ya, fa);
+        __builtin_amdgcn_sched_barrier(0);
+        ya = load_source<LOG_R>(ysrd, limb_next, lo_off, top_off);
+        load_factors(fa, min(i + 2, kMaxSrc - 1));
+        limb_next = P.src_limb[min(i + 3, kMaxSrc - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+        bconv_accumulate<TS, PIECES>(acc, yb, fb);
+        __builtin_amdgcn_sched_barrier(0);
     }
 
     // Twiddles are requested one target ahead and always before the previous target's stores are issued: loads and
@@ -173,9 +147,7 @@ __global__ __launch_bounds__(256) void bconv_ntt_cols(const double* __restrict__
 #pragma unroll
             for (int k = 0; k < 16; ++k) acc[tt][k] = reduce_lazy(acc[tt][k], mt[tt]);
             col_fwd_core<LOG_R>(acc[tt], cur, c, r0, lds, mt[tt]);
-            uint64_t* dst = op + (uint64_t)P.dst_limb[t] * N;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) store_f64(dst + col_row_grouped<LOG_R>(r0, k) * 256 + col, acc[tt][k]);
+            packed_store<256>(op + (uint64_t)P.dst_limb[t] * packed_limb_bytes(N), N, r0 * 1024 + col, pack(acc[tt]));
             if constexpr (LOG_R > 4) __syncthreads();  // the exchange buffer is reused by the next target
         }
     }
@@ -220,8 +192,8 @@ int conversion_tile(const ks_ctx* c, const PlanSet& up, uint32_t up_polys, const
     return full && load >= 216 * sixes && (!two_pieces || std::max(g_up, g_down) >= 4096) ? 16 : 0;
 }
 
-void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint64_t* y, uint64_t y_ps,
-                           uint64_t* out, uint64_t out_ps, uint32_t n_polys, int tile, hipStream_t s, double ops_per_coeff) {
+void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint8_t* y, uint64_t y_ps,
+                           uint8_t* out, uint64_t out_ps, uint32_t n_polys, int tile, hipStream_t s, double ops_per_coeff) {
     const uint32_t n_plans = plans.n_plans, max_targets = plans.max_targets;
     const BConvPlan* d_plans = plans.d_plans;
     if (n_polys == 0 || n_plans == 0) return;
@@ -232,7 +204,7 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
         // matrix cores: 25 int8 multiply-adds per source and target)
         double vec_ops = 0.0;
         for (uint32_t j = 0; j < n_plans; ++j) vec_ops += plans.meta.plan[j].n_dst * 44.0 + plans.shape_src * 2.0;
-        ProfScope ps("bconv_mfma_ntt_cols", (double)limbs_moved_per_poly * n_polys * c->N * 8.0, s, vec_ops * n_polys * c->N);
+        ProfScope ps("bconv_mfma_ntt_cols", (double)limbs_moved_per_poly * n_polys * packed_limb_bytes(c->N), s, vec_ops * n_polys * c->N);
         const int tl = c->opt[KS_OPT_BCONV_TARGETS] >= 1 && c->opt[KS_OPT_BCONV_TARGETS] <= 3 ? c->opt[KS_OPT_BCONV_TARGETS] : 3;
         launch_bconv_mfma_ntt_cols(c, plans, y, y_ps, out, out_ps, n_polys, tl, tile == 16, s);
         return;
@@ -248,13 +220,13 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
     if (c->logN != 16 && ts < 3) ts = 3;  // the other ring degrees come with the two production shapes only
     const uint32_t n_subsets = (max_targets + ts - 1) / ts;
     const dim3 grid(tiles, n_plans * n_subsets, n_polys), block(256);
-    ProfScope ps("bconv_ntt_cols", (double)limbs_moved_per_poly * n_polys * c->N * 8.0, s, ops_per_coeff * n_polys * c->N);
+    ProfScope ps("bconv_ntt_cols", (double)limbs_moved_per_poly * n_polys * packed_limb_bytes(c->N), s, ops_per_coeff * n_polys * c->N);
 #define KS_LAUNCH_BCONV(LOGR, TSV)                                                                                                      \
     if (c->pieces == 2)                                                                                                                 \
-        hipLaunchKernelGGL((bconv_ntt_cols<LOGR, TSV, (TSV == 4), 2>), grid, block, 0, s, c->d_tw_fwd, d_plans, y, y_ps, out, out_ps,  \
+        hipLaunchKernelGGL((bconv_ntt_cols<LOGR, TSV, 2>), grid, block, 0, s, c->d_tw_fwd, d_plans, y, y_ps, out, out_ps,  \
                            n_subsets);                                                                                                  \
     else                                                                                                                                \
-        hipLaunchKernelGGL((bconv_ntt_cols<LOGR, TSV, (TSV == 4), 3>), grid, block, 0, s, c->d_tw_fwd, d_plans, y, y_ps, out, out_ps,  \
+        hipLaunchKernelGGL((bconv_ntt_cols<LOGR, TSV, 3>), grid, block, 0, s, c->d_tw_fwd, d_plans, y, y_ps, out, out_ps,  \
                            n_subsets)
     if (c->logN == 16) {
         if (ts == 4) { KS_LAUNCH_BCONV(8, 4); }
@@ -274,23 +246,20 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
 // ------------------------------------------------------------------------------------------------
 // acc[b][c][pos] = sum_j d~_j[pos] * key[j][c][m(pos)].  For pos inside digit j, d~_j[pos] is the input limb
 // itself; otherwise it is the raised limb, whose row half of the forward transform is done here.
-// One wavefront = four rows of one limb position; it walks the digits, so d~ is read once and feeds both key
+// A workgroup = four rows of one limb position; it walks the digits, so d~ is read once and feeds both key
 // components (load reuse), and the accumulators are reduced and written once.
 // ------------------------------------------------------------------------------------------------
 // WD / WK: word types of d and of the key (64-bit, or 32-bit for moduli below 2^32).
 template <int LOG_R, typename WD, typename WK, bool PREFETCH>
-__global__ __launch_bounds__(64, PREFETCH ? 2 : 0) void rows_inner_product(TwTables tw, TwTables twi,
-                                                         const Mod* __restrict__ mods, DigitRanges dg,
+__global__ __launch_bounds__(64, 2) void rows_inner_product(TwTables tw, TwTables twi, const Mod* __restrict__ mods, DigitRanges dg,
                                                          uint32_t ell, uint32_t E, uint32_t L, uint32_t M,
                                                          const WD* __restrict__ d, uint64_t d_ps,
-                                                         const uint64_t* __restrict__ lifted, const WK* __restrict__ evk,
-                                                         uint64_t* __restrict__ acc, uint32_t* __restrict__ accq_lo,
-                                                         uint8_t* __restrict__ accq_hi, const uint32_t* __restrict__ drop_lo,
-                                                         const uint8_t* __restrict__ drop_hi, double drop_mul,
-                                                         uint32_t packed_limbs, uint32_t batch, uint32_t special_first) {
+                                                         const uint8_t* __restrict__ lifted, const WK* __restrict__ evk,
+                                                         uint8_t* __restrict__ acc, const uint8_t* __restrict__ drop, double drop_mul,
+                                                         uint32_t batch, uint32_t special_first) {
     constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R;
-    __shared__ double lds[4 * kRowPitch];
-    __shared__ double lds_ta[4 * 16];
+    constexpr uint64_t LIMB = packed_limb_bytes(N);
+    __shared__ InnerProductLds lds;
     // Workgroup -> (row group, limb position, batch item).  Consecutive workgroup ids go to the eight XCDs in
     // turn, each with its own L2; the ids that land on one XCD walk through all batch items of one
     // (row group, position) tile before moving to the next tile, so the key slots and twiddles of a tile are
@@ -304,18 +273,15 @@ __global__ __launch_bounds__(64, PREFETCH ? 2 : 0) void rows_inner_product(TwTab
     // launches keep them last: the next kernel reads exactly these limbs and finds them cached (0.5-2 % per call).
     const uint32_t rg = tile % (R / 4), slot_pos = tile / (R / 4), n_special = E - ell;
     const uint32_t pos = !special_first ? slot_pos : slot_pos < n_special ? ell + slot_pos : slot_pos - n_special;
-    task_rows_inner_product<LOG_R, WD, WK, PREFETCH>(tw, twi, mods, dg, ell, E, L, M, d + (uint64_t)b * d_ps, lifted + (uint64_t)b * dg.ndig * E * N, evk,
-                                      acc + (uint64_t)b * 2 * E * N, accq_lo + (uint64_t)b * 2 * ell * N,
-                                      accq_hi + (uint64_t)b * 2 * ell * N, drop_lo + (uint64_t)b * 2 * ell * N,
-                                      drop_hi + (uint64_t)b * 2 * ell * N, drop_mul, packed_limbs, pos, rg, threadIdx.x, lds, lds_ta);
+    task_rows_inner_product<LOG_R, WD, WK, PREFETCH>(tw, twi, mods, dg, ell, E, L, M, d + (uint64_t)b * d_ps, lifted + (uint64_t)b * dg.ndig * E * LIMB,
+                                      evk, acc + (uint64_t)b * 2 * E * LIMB, drop ? drop + (uint64_t)b * 2 * ell * LIMB : nullptr, drop_mul,
+                                      pos, rg, threadIdx.x, lds);
 }
 
-void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint64_t* lifted,
-                               const void* evk, uint64_t* acc, uint32_t batch, hipStream_t s, bool d_words32, bool key_words32,
-                               const PackedDigits& accq, const PackedDigits* drop_addend) {
+void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted,
+                               const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, bool d_words32, bool key_words32,
+                               const uint8_t* drop_addend) {
     if (batch == 0) return;
-    const uint32_t packed_limbs = drop_addend ? lv.ell - 1 : lv.ell;
-    const PackedDigits drop = drop_addend ? *drop_addend : accq;  // never read without a dropped limb
     DigitRanges dg;
     dg.ndig = lv.ndig;
     for (uint32_t j = 0; j < kMaxDigits; ++j) {
@@ -323,132 +289,101 @@ void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, 
         dg.hi[j] = j < lv.ndig ? lv.digit_hi[j] : 0;
     }
     // reads: every raised digit limb per ciphertext and the key (once per call); writes: both accumulators
-    // d (ell limbs per ciphertext) and the key arrive in boundary words, the raised limbs and the sums in 8 bytes
-    const double wd = d_words32 ? 0.5 : 1.0, wk = key_words32 ? 0.5 : 1.0;
+    // d (ell limbs per ciphertext) and the key arrive in boundary words, the raised limbs and the sums packed
+    const double wd = d_words32 ? 4.0 : 8.0, wk = key_words32 ? 4.0 : 8.0;
     ProfScope ps("rows_inner_product",
-                 ((double)batch * ((lv.ndig * lv.E - lv.ell) + wd * lv.ell + 2.0 * lv.E - 0.75 * packed_limbs) + wk * 2.0 * lv.ndig * lv.E) *
-                     c->N * 8.0,
-                 s);
+                 ((double)batch * (5.0 * (lv.ndig * lv.E - lv.ell) + wd * lv.ell + 10.0 * lv.E) + wk * 2.0 * lv.ndig * lv.E) * c->N, s);
     const uint32_t tiles = (c->N / 1024) * lv.E;
     const dim3 grid(((tiles + 7) / 8) * 8 * batch), block(64);
     // launches with more than two wavefronts per SIMD (1024 SIMDs) to run take the variant that requests the next digit's
     // loads early: 3 % faster there (32.1 -> 31.0 us per multiplication at L = 35); the single-ciphertext launch is bound by
     // bandwidth and gains nothing from it
     const bool prefetch = grid.x > 2048;
-#define KS_LAUNCH_IP(LOGR, WDT, WKT, PF)                                                                                           \
-    hipLaunchKernelGGL((rows_inner_product<LOGR, WDT, WKT, PF>), grid, block, 0, s, c->tw_fwd, c->tw_inv, c->d_mod, dg, lv.ell, lv.E, c->L, \
-                       c->M, static_cast<const WDT*>(d), d_ps, lifted, static_cast<const WKT*>(evk), acc, accq.lo, accq.hi, drop.lo, drop.hi,       \
-                       lv.Pmod_last, packed_limbs, batch, prefetch ? 0u : 1u)
-#define KS_LAUNCH(LOGR)                                                          \
-    if (d_words32 && key_words32) KS_LAUNCH_IP(LOGR, uint32_t, uint32_t, false); \
-    else if (key_words32) KS_LAUNCH_IP(LOGR, uint64_t, uint32_t, false);         \
-    else if (prefetch) KS_LAUNCH_IP(LOGR, uint64_t, uint64_t, true);             \
-    else KS_LAUNCH_IP(LOGR, uint64_t, uint64_t, false)
+#define KS_LAUNCH_IP(LOGR, WDT, WKT, PF)                                                                                                 \
+    hipLaunchKernelGGL((rows_inner_product<LOGR, WDT, WKT, PF>), grid, block, 0, s, c->tw_fwd, c->tw_inv, c->d_mod, dg, lv.ell, lv.E, c->L,  \
+                       c->M, static_cast<const WDT*>(d), d_ps, lifted, static_cast<const WKT*>(evk), acc, drop_addend, lv.Pmod_last, batch, \
+                       prefetch ? 0u : 1u)
+#define KS_LAUNCH_PF(LOGR, PF)                                                \
+    if (d_words32 && key_words32) KS_LAUNCH_IP(LOGR, uint32_t, uint32_t, PF); \
+    else if (key_words32) KS_LAUNCH_IP(LOGR, uint64_t, uint32_t, PF);         \
+    else KS_LAUNCH_IP(LOGR, uint64_t, uint64_t, PF)
+#define KS_LAUNCH(LOGR)                          \
+    if (prefetch) { KS_LAUNCH_PF(LOGR, true); } \
+    else { KS_LAUNCH_PF(LOGR, false); }
     KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
+#undef KS_LAUNCH_PF
 #undef KS_LAUNCH_IP
 }
 
 // ------------------------------------------------------------------------------------------------
 // out[b][comp][i] = (acc[b][comp][i] - NTT_rows(conv[b][comp][i])) * P^-1 (+ addend), canonical.
 // ------------------------------------------------------------------------------------------------
-// ADDEND: 0 = none, 1 = added as it is, 2 = multiplied by addend_mul[i] first.  Compile-time so that the kernel has no
-// branch: behind a run-time test every addend load became its own load-wait-use round trip.  A launch covers the
-// components comp0 .. comp0 + n_comps - 1 of every batch item.
-// ACCP: the ciphertext limbs of the accumulator come packed (acc: [b][2][ell][N] 32-bit low words, acc_hi: the bytes
-// above) instead of as the first ell limbs of [b][2][E][N] 64-bit words.
-// ADF: format of the addend: 0 = 64-bit words; 1 = packed the same way (addend: [b][2][ell][N] low words, addend_hi: the
-// bytes above); 2 = 32-bit words.
-template <int LOG_R, bool GATHER, int ADDEND, typename W, bool ACCP, int ADF>
+// ADDEND: 0 = none, 1 = words, added as they are, 2 = packed ([b][2][ell]), multiplied by addend_mul[i] first.  Compile-time so
+// that the kernel has no branch: behind a run-time test every addend load became its own load-wait-use round trip.  A launch
+// covers the components comp0 .. comp0 + n_comps - 1 of every batch item.
+template <int LOG_R, bool GATHER, int ADDEND, typename W>
 __global__ __launch_bounds__(64) void rows_moddown_finish(TwTables tw, const Mod* __restrict__ mods,
                                                           const double* __restrict__ Pinv, const double* __restrict__ addend_mul,
-                                                          uint32_t ell, uint32_t E, uint32_t out_limbs,
-                                                          const void* __restrict__ acc, const uint8_t* __restrict__ acc_hi,
-                                                          const uint64_t* __restrict__ conv,
-                                                          W* __restrict__ out, uint64_t out_bs,
-                                                          const void* __restrict__ addend, const uint8_t* __restrict__ addend_hi,
-                                                          uint64_t addend_bs, uint32_t comp0, uint32_t n_comps, uint32_t galois) {
+                                                          uint32_t ell, uint32_t E, uint32_t out_limbs, const uint8_t* __restrict__ acc,
+                                                          const uint8_t* __restrict__ conv, W* __restrict__ out, uint64_t out_bs,
+                                                          const void* __restrict__ addend, uint64_t addend_bs, uint32_t comp0,
+                                                          uint32_t n_comps, uint32_t galois) {
     constexpr uint32_t N = 256u << LOG_R;
+    constexpr uint64_t LIMB = packed_limb_bytes(N);
     __shared__ double lds[4 * kRowPitch];
     const uint32_t rg = blockIdx.x, i = blockIdx.y;
     // batch items in descending order: the conversion kernel before this one wrote them in ascending order, so the most
     // recently written ones, still in the last-level cache, are read first (4-5 % on this kernel in batched calls)
     const uint32_t zz = gridDim.z - 1 - blockIdx.z;
     const uint32_t b = zz / n_comps, comp = comp0 + (zz - b * n_comps);
+    const uint64_t ct_limb = ((uint64_t)b * 2 + comp) * ell + i;
     const void* adp = nullptr;
-    const uint8_t* adp_hi = nullptr;
     double admul = 0.0;
-    if constexpr (ADDEND != 0) {
-        const uint64_t ad_off = (uint64_t)b * addend_bs + ((uint64_t)comp * ell + i) * N;
-        if constexpr (ADF == 1) {
-            adp = static_cast<const uint32_t*>(addend) + ad_off;
-            adp_hi = addend_hi + ad_off;
-        } else if constexpr (ADF == 2) {
-            adp = static_cast<const uint32_t*>(addend) + ad_off;
-        } else {
-            adp = static_cast<const uint64_t*>(addend) + ad_off;
-        }
+    if constexpr (ADDEND == 1) adp = static_cast<const W*>(addend) + (uint64_t)b * addend_bs + ((uint64_t)comp * ell + i) * N;
+    if constexpr (ADDEND == 2) {
+        adp = static_cast<const uint8_t*>(addend) + ct_limb * LIMB;
+        admul = addend_mul[i];
     }
-    if constexpr (ADDEND == 2) admul = addend_mul[i];
-    const uint64_t conv_off = (((uint64_t)b * 2 + comp) * ell + i) * N;
-    const void* ap;
-    const uint8_t* ap_hi = nullptr;
-    if constexpr (ACCP) {
-        ap = static_cast<const uint32_t*>(acc) + conv_off;
-        ap_hi = acc_hi + conv_off;
-    } else {
-        ap = static_cast<const uint64_t*>(acc) + (((uint64_t)b * 2 + comp) * E + i) * N;
-    }
-    task_rows_finish<LOG_R, GATHER, ADDEND, W, ACCP, ADF>(tw, mods[i], i, Pinv[i], admul, conv + conv_off, ap, ap_hi,
-                                                          out + (uint64_t)b * out_bs + ((uint64_t)comp * out_limbs + i) * N, adp,
-                                                          adp_hi, galois, rg, threadIdx.x, lds);
+    task_rows_finish<LOG_R, GATHER, ADDEND, W>(tw, mods[i], i, Pinv[i], admul, conv + ct_limb * LIMB,
+                                               acc + (((uint64_t)b * 2 + comp) * E + i) * LIMB,
+                                               out + (uint64_t)b * out_bs + ((uint64_t)comp * out_limbs + i) * N, adp, galois, rg, threadIdx.x, lds);
 }
 
-void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t* acc, const uint64_t* conv, void* out_words,
-                                uint64_t out_bs, const void* addend, uint64_t addend_bs, uint32_t addend_comps,
-                                uint32_t galois, uint32_t batch, hipStream_t s, const FinishScale* fs, bool out_words32,
-                                const PackedDigits* acc_packed, const PackedDigits* addend_packed) {
+void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint8_t* acc, const uint8_t* conv, void* out_words, uint64_t out_bs,
+                                const void* addend, uint64_t addend_bs, uint32_t addend_comps, uint32_t galois, uint32_t batch,
+                                hipStream_t s, const FinishScale* fs, bool out_words32) {
     if (batch == 0) return;
-    const void* addend_p = addend_packed ? static_cast<const void*>(addend_packed->lo) : addend;
-    const uint8_t* addend_h = addend_packed ? addend_packed->hi : nullptr;
     const double* mul = fs ? fs->mul : c->d_Pinv;
     const double* admul = fs ? fs->addend_mul : nullptr;
     const uint32_t out_limbs = fs ? fs->out_limbs : lv.ell;
     if (out_limbs == 0) return;
-    if (!addend_p) addend_comps = 0;
-    ProfScope ps("rows_moddown_finish",
-                 (double)batch * out_limbs *
-                     (2 * 8 + 2 * (acc_packed ? 5 : 8) + (out_words32 ? 1 : 2) * 8 + addend_comps * (addend_packed ? 5 : out_words32 ? 4 : 8)) * c->N,
-                 s);
+    if (!addend) addend_comps = 0;
+    const double wo = out_words32 ? 4.0 : 8.0;
+    ProfScope ps("rows_moddown_finish", (double)batch * out_limbs * (2 * 5 + 2 * 5 + 2 * wo + addend_comps * (admul ? 5.0 : wo)) * c->N, s);
     const dim3 block(64);
     const uint32_t row_groups = c->N / 1024;
-    const void* accp = acc_packed ? static_cast<const void*>(acc_packed->lo) : static_cast<const void*>(acc);
-    const uint8_t* acch = acc_packed ? acc_packed->hi : nullptr;
     // one launch for the components that take the addend, one for those that do not
     for (int pass = 0; pass < 2; ++pass) {
         const uint32_t comp0 = pass == 0 ? 0 : addend_comps, n_comps = pass == 0 ? addend_comps : 2 - addend_comps;
         if (n_comps == 0) continue;
         const int mode = pass == 1 ? 0 : (admul ? 2 : 1);
         const dim3 grid(row_groups, out_limbs, batch * n_comps);
-#define KS_LAUNCH_FINISH_P(LOGR, GATHER, MODE, WT, ACCP, ADF)                                                                      \
-    hipLaunchKernelGGL((rows_moddown_finish<LOGR, GATHER, MODE, WT, ACCP, ADF>), grid, block, 0, s, c->tw_fwd, c->d_mod, mul, admul, \
-                       lv.ell, lv.E, out_limbs, accp, acch, conv, static_cast<WT*>(out_words), out_bs, addend_p, addend_h, addend_bs, \
-                       comp0, n_comps, galois)
-    // Who calls: a scaled addend is packed and comes with a packed accumulator (multiplications); an addend as it is comes with
-    // a packed accumulator, in the word size of the output (hoisted rotations).
-#define KS_LAUNCH_MODES(LOGR, WT, ADF)                                                  \
-    if (mode == 2) KS_LAUNCH_FINISH_P(LOGR, false, 2, WT, true, 1);                     \
-    else if (mode == 1 && galois != 1) KS_LAUNCH_FINISH_P(LOGR, true, 1, WT, true, ADF);  \
-    else if (mode == 1) KS_LAUNCH_FINISH_P(LOGR, false, 1, WT, true, ADF);              \
-    else if (acc_packed) KS_LAUNCH_FINISH_P(LOGR, false, 0, WT, true, 0);               \
-    else KS_LAUNCH_FINISH_P(LOGR, false, 0, WT, false, 0)
-#define KS_LAUNCH(LOGR)                                      \
-    if (out_words32) { KS_LAUNCH_MODES(LOGR, uint32_t, 2); } \
-    else { KS_LAUNCH_MODES(LOGR, uint64_t, 0); }
+#define KS_LAUNCH_FINISH(LOGR, GATHER, MODE, WT)                                                                                        \
+    hipLaunchKernelGGL((rows_moddown_finish<LOGR, GATHER, MODE, WT>), grid, block, 0, s, c->tw_fwd, c->d_mod, mul, admul, lv.ell, lv.E, \
+                       out_limbs, acc, conv, static_cast<WT*>(out_words), out_bs, addend, addend_bs, comp0, n_comps, galois)
+#define KS_LAUNCH_MODES(LOGR, WT)                                         \
+    if (mode == 2) KS_LAUNCH_FINISH(LOGR, false, 2, WT);                  \
+    else if (mode == 1 && galois != 1) KS_LAUNCH_FINISH(LOGR, true, 1, WT); \
+    else if (mode == 1) KS_LAUNCH_FINISH(LOGR, false, 1, WT);             \
+    else KS_LAUNCH_FINISH(LOGR, false, 0, WT)
+#define KS_LAUNCH(LOGR)                                   \
+    if (out_words32) { KS_LAUNCH_MODES(LOGR, uint32_t); } \
+    else { KS_LAUNCH_MODES(LOGR, uint64_t); }
         KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
 #undef KS_LAUNCH_MODES
-#undef KS_LAUNCH_FINISH_P
+#undef KS_LAUNCH_FINISH
     }
 }
 
@@ -458,25 +393,56 @@ void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t
 // forward transform, it costs one more source of that conversion, and the rescale needs no transforms of its own (a
 // forward transform and two more passes over every limb: 290 of 1310 us per 8 multiplications at L = 35).
 // With y_k = [x_k (P / p_k)^-1]_{p_k} the converted special part of limb ell-1 times P^-1 is sum_k y_k p_k^-1.
-// One thread per coefficient, K + 1 limbs read and one written.
+// One thread per four coefficients, K + 1 sources read and one written.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void rescale_remainder_kernel(Mod m, const double* __restrict__ pinv, uint32_t ell, uint32_t K,
-                                                                uint32_t N, uint64_t* __restrict__ acc) {
-    const uint32_t n = blockIdx.x * 256 + threadIdx.x;
-    uint64_t* last = acc + ((uint64_t)blockIdx.y * (ell + K) + ell - 1) * N + n;
+                                                                uint32_t N, uint8_t* __restrict__ acc) {
+    // quad t: rows 4 q .. 4 q + 3 of the 16 that the thread (r0, column) of the column kernels holds
+    const uint32_t t = blockIdx.x * 256 + threadIdx.x, q = (t >> 8) & 3u;
+    const uint64_t limb = packed_limb_bytes(N);
+    const uint32_t bytes = 4 * N + source_bytes_offset(t >> 10, t & 255u) + 4 * q;
+    uint8_t* last = acc + ((uint64_t)blockIdx.y * (ell + K) + ell - 1) * limb;
+    const auto load = [&](const uint8_t* p, double (&v)[4]) {
+        const Words4 lo = reinterpret_cast<const Words4*>(p)[t];
+        const uint32_t top = *reinterpret_cast<const uint32_t*>(p + bytes);
+#pragma unroll
+        for (int x = 0; x < 4; ++x)   // canonical residues: the byte above is not negative
+            v[x] = __builtin_bit_cast(double, (uint64_t)(0x43380000u | ((top >> (8 * x)) & 0xFFu)) << 32 | lo.w[x]) - kDigitBias;
+    };
     static_assert(kMaxLimbsIn <= kMacTerms, "products per exact sum");
-    double hi = kMacBias, lo = 0.0;
+    double hi[4], lo[4], sum[4], r[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        hi[x] = kMacBias;
+        lo[x] = 0.0;
+    }
+    load(last, sum);
 #pragma unroll 4
-    for (uint32_t k = 0; k < K; ++k) mac_exact(load_f64(last + (uint64_t)(k + 1) * N), pinv[k], hi, lo);
-    const double r = canon(reduce_lazy(load_f64(last) - mac_reduce(hi, lo, m), m), m);
-    store_f64(last, r > (m.p - 1.0) * 0.5 ? r - m.p : r);
+    for (uint32_t k = 0; k < K; ++k) {
+        double y[4];
+        load(last + (uint64_t)(k + 1) * limb, y);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) mac_exact(y[x], pinv[k], hi[x], lo[x]);
+    }
+    Words4 o;
+    uint32_t h[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const double c = canon(reduce_lazy(sum[x] - mac_reduce(hi[x], lo[x], m), m), m);
+        r[x] = c > (m.p - 1.0) * 0.5 ? c - m.p : c;
+        const uint64_t bits = __builtin_bit_cast(uint64_t, r[x] + kDigitBias);
+        o.w[x] = (uint32_t)bits;
+        h[x] = (uint32_t)(bits >> 32);
+    }
+    reinterpret_cast<Words4*>(last)[t] = o;
+    *reinterpret_cast<uint32_t*>(last + bytes) = low_bytes(h[0], h[1], h[2], h[3]);
 }
 
-void launch_rescale_remainder(const ks_ctx* c, const Level& lv, uint64_t* acc, uint32_t n_polys, hipStream_t s) {
+void launch_rescale_remainder(const ks_ctx* c, const Level& lv, uint8_t* acc, uint32_t n_polys, hipStream_t s) {
     if (n_polys == 0) return;
-    ProfScope ps("rescale_remainder", (double)n_polys * (c->K + 2) * c->N * 8.0, s);
+    ProfScope ps("rescale_remainder", (double)n_polys * (c->K + 2) * packed_limb_bytes(c->N), s);
     const uint64_t q = c->mod[lv.ell - 1];
-    hipLaunchKernelGGL(rescale_remainder_kernel, dim3(c->N / 256, n_polys), dim3(256), 0, s, Mod{(double)q, 1.0 / (double)q}, lv.d_pinv_last,
+    hipLaunchKernelGGL(rescale_remainder_kernel, dim3(c->N / 1024, n_polys), dim3(256), 0, s, Mod{(double)q, 1.0 / (double)q}, lv.d_pinv_last,
                        lv.ell, c->K, c->N, acc);
 }
 

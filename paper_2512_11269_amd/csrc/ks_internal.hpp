@@ -40,8 +40,14 @@ struct BConvPlan {
     Mod dst_mod[kMaxDst];
     uint32_t dst_mod_id[kMaxDst];  // modulus id of each target (selects its twiddle table)
     // hats[t][i][k], k = 0..2: centred([(D / s_i) 2^(12 k)]_t) * 2^(-12 k), the factors that go with the three pieces
-    // of a split source residue (split3); [3] pads the row to 32 bytes.  Zero for padding sources.
+    // of a split source residue (split3; two pieces and 16 bits where every modulus is below 2^32).  Zero for padding sources.
+    // The fused vector kernel takes y + 0x80808080 (kDigitBias) apart into the low 12 bits, the next 12 in place and what is left
+    // shifted down by 24: factors [0], [1] and [3] = [2] * 2^24.  Products are whole numbers of at most 2^47 (2^12 2^35, 2^24 2^23,
+    // 2^12.1 2^35): three for each of seventeen sources stay below 2^52.8.  With two pieces: the low 16 bits and the rest, [0] and
+    // [3] = [1] * 2^16, 2^16 2^31 and 1.5 2^16 2^31, 2^52.5 in all.
     double hats[kMaxDst][kMaxSrc][4];
+    // centred(-0x80808080 sum_i [D / s_i]_t), which takes the constant out of the sum
+    double dst_start[kMaxDst];
     // Matrix-core form (int8 MFMA, see ks_bconv_mfma.hip).  A source residue y = sum_a d_a 256^a is cut into five signed
     // digits; for every digit position a the factor F_a = centred([(D / s_i) 256^a]_t) is cut the same way into digits
     // e_b, so that y (D / s_i) = sum_b 256^b sum_a d_a e_{a,b} (mod t): five small integer sums per target, each a dot
@@ -181,58 +187,51 @@ void launch_ntt_u32(const ks_ctx* c, const LimbMap& map, uint32_t* data, uint64_
 // The two halves of each transform on their own (the fused pipeline replaces some halves by fused kernels).
 void launch_ntt_fwd_cols(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipStream_t s);
 void launch_ntt_fwd_rows(const ks_ctx* c, const LimbMap& map, uint64_t* data, uint64_t ps_words, uint32_t n_polys, hipStream_t s);
-// in_words32: io.in holds 32-bit words (strides still count elements)
-void launch_ntt_inv_rows(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipStream_t s, bool in_words32 = false);
-// scale_tab: multiplier applied with the final reduction, indexed by the limb's position in `map` (scale_by_idx)
-// or by its modulus id; out_f64: leave the canonical result as a double for a following fused kernel.
-void launch_ntt_inv_cols(const ks_ctx* c, const LimbMap& map, uint64_t* data, uint64_t ps_words, uint32_t n_polys,
-                         const double* scale_tab, bool scale_by_idx, bool out_f64, hipStream_t s);
+// The inverse transform that feeds a conversion (packed limbs: ks_tiles.hpp).  Rows: `in` holds words of in_word = 8 or 4 bytes, or
+// (1) packed accumulators, converted in place; in_ps counts words (bytes for 1), out_ps bytes.
+void launch_inv_rows_packed(const ks_ctx* c, const LimbMap& map, const void* in, uint64_t in_ps, int in_word, uint8_t* out, uint64_t out_ps,
+                            uint32_t n_polys, hipStream_t s);
+// Columns, in place: leaves the conversion's sources.  scale_tab: multiplier applied with the final reduction, by position in `map`.
+void launch_inv_cols_packed(const ks_ctx* c, const LimbMap& map, uint8_t* data, uint64_t ps_bytes, uint32_t n_polys, const double* scale_tab,
+                            hipStream_t s);
 
 // The kernel of both conversions of a call (ks_fused.hip): 0 vector, 8 or 16 matrix cores with tiles of that many columns.
 int conversion_tile(const ks_ctx* c, const PlanSet& up, uint32_t up_polys, const PlanSet& down, uint32_t down_polys);
-// Fused base conversion + column half of the forward transform, with the kernel `tile` (conversion_tile).  y: pre-scaled canonical doubles
-// y_i = [x_i N^-1 (D/s_i)^-1]; out: raw doubles ready for the row half.  One plan per blockIdx.y group.
-void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint64_t* y, uint64_t y_ps,
-                           uint64_t* out, uint64_t out_ps, uint32_t n_polys, int tile, hipStream_t s, double ops_per_coeff = 0.0);
+// Fused base conversion + column half of the forward transform, with the kernel `tile` (conversion_tile).  y: packed sources
+// y_i = [x_i N^-1 (D/s_i)^-1]; out: packed limbs ready for the row half; strides in bytes.  One plan per blockIdx.y group.
+void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint8_t* y, uint64_t y_ps,
+                           uint8_t* out, uint64_t out_ps, uint32_t n_polys, int tile, hipStream_t s, double ops_per_coeff = 0.0);
 // The same conversion + column half on the matrix cores (ks_bconv_mfma.hip); tl = targets per lane half, 1..3.
-void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uint64_t* y, uint64_t y_ps, uint64_t* out,
+void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uint8_t* y, uint64_t y_ps, uint8_t* out,
                                 uint64_t out_ps, uint32_t n_polys, int tl, bool wide, hipStream_t s);
 // Upload host plans as a PlanSet (allocates; ks_ctx_create and bconv plan registration only).  Returns a HIP error code.
 hipError_t upload_plans(const BConvPlan* host_plans, uint32_t n_plans, uint32_t shape_src, PlanSet* out);
-// Canonical residues in packed form: bits 0..31 in lo, the bits above (moduli are below 2^36) in hi, both with the
-// element index of the tensor they stand for; 5 bytes a residue instead of 8.  The ciphertext limbs of accumulators and the
-// tensor product's d0 and d1 are kept this way.
-struct PackedDigits {
-    uint32_t* lo;
-    uint8_t* hi;
-};
 // Fused row half of the forward transform of the raised digits + inner product with the key.
 // d_words32 / key_words32: d / the key hold one residue per 32-bit word (d_words32 implies key_words32)
-// The ciphertext limbs of the sums go to accq ([b][2][ell][N], packed), the special limbs to acc after the row half of their
-// inverse transform.  drop_addend != nullptr: limb ell-1 joins the special limbs (acc[ell-1]) after P times limb ell-1 of
-// that addend ([b][2][ell][N] packed) has been added.
-void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint64_t* lifted,
-                               const void* evk, uint64_t* acc, uint32_t batch, hipStream_t s, bool d_words32, bool key_words32,
-                               const PackedDigits& accq, const PackedDigits* drop_addend = nullptr);
-// Fused row half of the forward transform of the converted limbs + (acc - conv) P^-1 (+ addend).
-// acc_packed: the ciphertext limbs of the accumulator are read from there ([b][2][ell][N]) instead of from acc.
-// fs == nullptr: multiply by P^-1, ell output limbs; an addend (with acc_packed) is in the word size of the output and read
-// through sigma_galois.  Otherwise (division by P and a rescale, with acc_packed): multiply by fs->mul[i], add addend_packed
-// ([b][2][ell][N], addend_batch_stride in elements) times fs->addend_mul[i], write the first fs->out_limbs limbs per component.
+// acc: [b][2][E] packed.  The ciphertext limbs are in rows order; the special limbs have been through the row half of their inverse
+// transform and are in columns order.  drop_addend != nullptr: limb ell-1 joins the special limbs after P times limb ell-1 of that
+// addend ([b][2][ell] packed) has been added.
+void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted,
+                               const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, bool d_words32, bool key_words32,
+                               const uint8_t* drop_addend = nullptr);
+// Fused row half of the forward transform of the converted limbs (conv, [b][2][ell] packed) + (acc - conv) P^-1 (+ addend);
+// the ciphertext limbs of acc ([b][2][E] packed) are in rows order.
+// fs == nullptr: multiply by P^-1, ell output limbs; an addend is in the word size of the output (addend_batch_stride words
+// between batch items) and read through sigma_galois.  Otherwise (division by P and a rescale): multiply by fs->mul[i], add the
+// packed addend ([b][2][ell]) times fs->addend_mul[i], write the first fs->out_limbs limbs per component.
 struct FinishScale {
     const double* mul;
     const double* addend_mul;
     uint32_t out_limbs;
 };
-void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint64_t* acc, const uint64_t* conv, void* out,
+void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint8_t* acc, const uint8_t* conv, void* out,
                                 uint64_t out_batch_stride, const void* addend, uint64_t addend_batch_stride,
                                 uint32_t addend_comps, uint32_t galois, uint32_t batch, hipStream_t s,
-                                const FinishScale* fs = nullptr, bool out_words32 = false, const PackedDigits* acc_packed = nullptr,
-                                const PackedDigits* addend_packed = nullptr);
-// Remainder of the dropped limb for a rescale.  acc: [polys][E][N], the drop_map limbs in the coefficient domain as canonical
-// doubles (y_k on the special limbs, P^-1 times the dropped limb's sum on limb ell-1); limb ell-1 becomes the centred
-// remainder of (sum - converted special part) P^-1 modulo q_{ell-1}, a signed double.
-void launch_rescale_remainder(const ks_ctx* c, const Level& lv, uint64_t* acc, uint32_t n_polys, hipStream_t s);
+                                const FinishScale* fs = nullptr, bool out_words32 = false);
+// Remainder of the dropped limb for a rescale.  acc: [polys][E], the drop_map limbs as sources of a conversion (canonical: y_k on the
+// special limbs, P^-1 times the dropped limb's sum on limb ell-1); limb ell-1 becomes the centred remainder of (sum - converted
+// special part) P^-1 modulo q_{ell-1}, a signed source.
+void launch_rescale_remainder(const ks_ctx* c, const Level& lv, uint8_t* acc, uint32_t n_polys, hipStream_t s);
 
 // The standalone conversion (ks_bconv.hip: the choice of the kernel, and the vector kernel).
 // words32: in and out hold one residue per 32-bit word (strides in words either way)
@@ -289,24 +288,23 @@ struct SlotLayout {
         default: LAUNCH(8); break;    \
     }
 // Fill a bundle in one launch.  raised: the row half of the forward transform of the raised limbs (`lifted`,
-// [b][ndig][E][N] raw doubles after the column half), all digits.  The polynomials' own limbs d[b][pos] and, c0 != nullptr,
+// [b][ndig][E] packed limbs after the column half), all digits.  The polynomials' own limbs d[b][pos] and, c0 != nullptr,
 // the addend's limbs c0[b][pos] (64-bit words with a packed bundle, 32-bit words with a 32-bit one; ps words apart) are
 // copied.
-void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t* lifted, const void* d, const void* c0, uint64_t ps,
+void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint8_t* lifted, const void* d, const void* c0, uint64_t ps,
                                const GatherBundle& out, bool raised, hipStream_t s);
 
 // acc[r][b][c][pos] = sum_j sigma_{g_r}(src_j)[pos] * key_r[j][c][ext_id(pos)] for every rotation r of `rot` (pt unused);
 // src_j[pos] = slab j E + pos of the bundle.
 // key_words32: keys (and plaintexts) hold one residue per 32-bit word; 32-bit sources imply 32-bit keys.
-// The special limbs of the result go to acc ([r][b][2][E][N], ciphertext limbs left untouched), the ciphertext limbs to
-// accq ([r][b][2][ell][N], packed).
-void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* acc,
-                          const PackedDigits& accq, hipStream_t s, bool key_words32 = false);
+// acc: [r][b][2][E], packed limbs in rows order.
+void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint8_t* acc, hipStream_t s,
+                          bool key_words32 = false);
 
 // u[b][c][pos] (+)= sum_r pt_r[pos] * (sum_j sigma_r(src_j)[pos] key_r[j][c][pos] + [c = 0][pos < ell] P sigma_r(c0)[pos]);
-// src: c1 and its finished raised digits, and c0.  accumulate: add to what u already holds.
+// src: c1 and its finished raised digits, and c0.  u: packed limbs in rows order.  accumulate: add to what u already holds.
 // galois[r] == 1: the term is P (c0, c1) and key[r] is not read; pt[r] == nullptr: the constant 1.
-void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint64_t* u,
+void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint8_t* u,
                        bool accumulate, hipStream_t s, bool key_words32 = false);
 
 // The key-switch chain behind ks_keyswitch / ks_keyswitch_u32 (argument checks included); ws is any device buffer of
@@ -318,7 +316,7 @@ int keyswitch_impl(const ks_ctx* c, const void* d, uint32_t ell, const void* evk
 // the device current.  Returns a HIP error code.
 hipError_t bind_static_scratch(int device);
 
-// d0 = b1 b2, d1 = a1 b2 + a2 b1 -> dq [batch][2][ell][N] packed; d2 = a1 a2 -> d2 [batch][ell][N] 64-bit words
-void launch_tensor_product(const ks_ctx* c, const void* cta, const void* ctb, uint64_t* d2, const PackedDigits& dq, uint32_t ell,
+// d0 = b1 b2, d1 = a1 b2 + a2 b1 -> dq [batch][2][ell] packed, rows order; d2 = a1 a2 -> d2 [batch][ell][N] 64-bit words
+void launch_tensor_product(const ks_ctx* c, const void* cta, const void* ctb, uint64_t* d2, uint8_t* dq, uint32_t ell,
                            uint32_t batch, hipStream_t s, bool in_words32 = false);
 }  // namespace ks

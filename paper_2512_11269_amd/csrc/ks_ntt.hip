@@ -87,7 +87,7 @@ __device__ __forceinline__ void store_slot_words(uint32_t* p, const uint64_t* v)
 // of whole lines.
 template <int LOG_R, int G, bool PACKED>
 __global__ __launch_bounds__(64 * G) void gather_bundle_rows(TwTables tw, const Mod* __restrict__ mods, LimbMap map, DigitRanges dg,
-                                                             uint32_t ell, uint32_t E, const uint64_t* __restrict__ lifted,
+                                                             uint32_t ell, uint32_t E, const uint8_t* __restrict__ lifted,
                                                              const void* __restrict__ d, const void* __restrict__ c0, uint64_t d_ps,
                                                              uint32_t n_new, uint32_t* __restrict__ lo, uint8_t* __restrict__ hi) {
     using WD = std::conditional_t<PACKED, uint64_t, uint32_t>;
@@ -106,12 +106,11 @@ __global__ __launch_bounds__(64 * G) void gather_bundle_rows(TwTables tw, const 
         slab = map.off[idx];
         const Mod m = mods[mod_id];
         const uint32_t row = rg * 4 + rr;
-        const uint64_t* ip = lifted + ((uint64_t)w * dg.ndig * E + slab) * N + row * 256;
         double x[16];
         PassTwiddles t;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) x[k] = load_f64(ip + j0 + 16 * k);
+        const PackedRaw raw = packed_load<64>(lifted + ((uint64_t)w * dg.ndig * E + slab) * packed_limb_bytes(N), N, rg * 256 + lane);
         load_row_twiddles(t, tw, mod_id, N, R + row, j0, m);
+        unpack_rows(raw, x);
         double* lrow = lds + w * WAVE_LDS + rr * kRowPitch;
         row_fwd_core_consecutive(x, t, j0, lrow, m);
 #pragma unroll
@@ -154,31 +153,55 @@ __global__ __launch_bounds__(64 * G) void gather_bundle_rows(TwTables tw, const 
     }
 }
 
-// inverse, rows first: canonical residues in (64- or 32-bit words), raw doubles out (|x| <= 0.501 p).
-template <int LOG_R, typename W>
-__global__ __launch_bounds__(64) void ntt_inv_rows(TwTables twi, const Mod* __restrict__ mods, LimbMap map,
-                                                   const W* in, uint64_t* out, uint64_t in_ps, uint64_t out_ps) {
+// inverse, rows first, in place: canonical residues in, raw doubles out (|x| <= 0.501 p).
+template <int LOG_R>
+__global__ __launch_bounds__(64) void ntt_inv_rows(TwTables twi, const Mod* __restrict__ mods, LimbMap map, uint64_t* data, uint64_t ps) {
     constexpr uint32_t N = 256u << LOG_R, GROUPS = (1u << LOG_R) / 4;
     __shared__ double lds[4 * kRowPitch];
     const uint32_t li = blockIdx.x / GROUPS, rg = blockIdx.x - li * GROUPS;
     const uint32_t poly = li / map.n, idx = li - poly * map.n, mod_id = map.mod[idx];
-    const uint64_t off = (uint64_t)map.off[idx] * N;
-    task_inv_rows<LOG_R, W>(twi, mods[mod_id], mod_id, in + poly * in_ps + off, out + poly * out_ps + off, rg, threadIdx.x, lds);
+    uint64_t* limb = data + poly * ps + (uint64_t)map.off[idx] * N;
+    task_inv_rows<LOG_R, uint64_t>(twi, mods[mod_id], mod_id, limb, limb, rg, threadIdx.x, lds);
 }
 
-// inverse, columns last, in place: raw doubles in; out = canonical [x * scale]_m where scale is N^-1,
-// optionally pre-multiplied by a per-limb constant (base conversion folds its (D/s_i)^-1 in here).
-// OUT_F64: store the canonical result as a double instead of a 64-bit integer.
-template <int LOG_R, int TC, bool OUT_F64>
+// inverse, columns last, in place: raw doubles in; out = canonical [x N^-1]_m.
+template <int LOG_R, int TC>
 __global__ __launch_bounds__((TC << LOG_R) / 16) void ntt_inv_cols(const double* __restrict__ twi, const Mod* __restrict__ mods,
-                                                        const double* __restrict__ scale_tab, int scale_by_idx, LimbMap map,
-                                                        uint64_t* data, uint64_t ps) {
+                                                        const double* __restrict__ ninv, LimbMap map, uint64_t* data, uint64_t ps) {
     constexpr uint32_t N = 256u << LOG_R, TILES = 256 / TC;
     __shared__ double lds[LOG_R > 4 ? (TC << LOG_R) : 1];
     const uint32_t li = blockIdx.x / TILES, tile = blockIdx.x - li * TILES;
     const LimbRef L = locate(map, li, data, data, ps, ps, N);
-    task_inv_cols<LOG_R, TC, OUT_F64>(twi + (size_t)L.mod_id * N, mods[L.mod_id], scale_tab[scale_by_idx ? L.idx : L.mod_id], L.in,
-                                      L.out, tile, threadIdx.x, lds);
+    task_inv_cols<LOG_R, TC>(twi + (size_t)L.mod_id * N, mods[L.mod_id], ninv[L.mod_id], L.out, tile, threadIdx.x, lds);
+}
+
+// ------------------------------------------------------------------------------------------------
+// The inverse transform that feeds a conversion, packed limbs between its halves and at its end (ks_tiles.hpp).
+// ------------------------------------------------------------------------------------------------
+// W: 64- or 32-bit words of a tensor, or uint8_t: a packed limb of accumulators, then in place (in == out).
+// in_ps: words (bytes for uint8_t) between polynomials, out_ps: bytes.
+template <int LOG_R, typename W>
+__global__ __launch_bounds__(64) void inv_rows_packed(TwTables twi, const Mod* __restrict__ mods, LimbMap map, const W* in, uint64_t in_ps,
+                                                      uint8_t* out, uint64_t out_ps) {
+    constexpr uint32_t N = 256u << LOG_R, GROUPS = (1u << LOG_R) / 4;
+    __shared__ double lds[4 * kRowPitch];
+    const uint32_t li = blockIdx.x / GROUPS, rg = blockIdx.x - li * GROUPS;
+    const uint32_t poly = li / map.n, idx = li - poly * map.n, mod_id = map.mod[idx];
+    const uint64_t limb = map.off[idx];
+    task_inv_rows_packed<LOG_R, W>(twi, mods[mod_id], mod_id, in + poly * in_ps + limb * (sizeof(W) == 1 ? packed_limb_bytes(N) : N),
+                                   out + poly * out_ps + limb * packed_limb_bytes(N), rg, threadIdx.x, lds);
+}
+
+// Out: [x * scale]_m as sources of a conversion; scale_tab holds N^-1 times the conversion's (D / s_i)^-1, by position in the map.
+template <int LOG_R>
+__global__ __launch_bounds__(256) void inv_cols_packed(const double* __restrict__ twi, const Mod* __restrict__ mods,
+                                                       const double* __restrict__ scale_tab, LimbMap map, uint8_t* data, uint64_t ps) {
+    constexpr uint32_t N = 256u << LOG_R, TILES = 1u << (LOG_R - 4);
+    __shared__ double lds[LOG_R > 4 ? 4096 : 1];
+    const uint32_t li = blockIdx.x / TILES, tile = blockIdx.x - li * TILES;
+    const uint32_t poly = li / map.n, idx = li - poly * map.n, mod_id = map.mod[idx];
+    task_inv_cols_packed<LOG_R>(twi + (size_t)mod_id * N, mods[mod_id], scale_tab[idx],
+                                data + poly * ps + (uint64_t)map.off[idx] * packed_limb_bytes(N), tile, threadIdx.x, lds);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -290,7 +313,7 @@ void launch_ntt_fwd_rows(const ks_ctx* c, const LimbMap& map, uint64_t* data, ui
 #undef KS_LAUNCH
 }
 
-void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t* lifted, const void* d, const void* c0, uint64_t ps_words,
+void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint8_t* lifted, const void* d, const void* c0, uint64_t ps_words,
                                const GatherBundle& out, bool raised, hipStream_t s) {
     const uint32_t n_new = raised ? lv.lifted_map.n : 0, n_copy = c0 ? 2 * lv.ell : lv.ell;
     DigitRanges dg;
@@ -300,7 +323,7 @@ void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint64_t*
         dg.hi[j] = j < lv.ndig ? lv.digit_hi[j] : 0;
     }
     const double wb = 4.0 + (out.hi ? (double)gather_hi_bytes(out.group) / out.group : 0.0);
-    ProfScope ps("gather_bundle_rows", ((8.0 + wb) * n_new + ((out.hi ? 8.0 : 4.0) + wb) * n_copy) * c->N * out.group, s);
+    ProfScope ps("gather_bundle_rows", ((5.0 + wb) * n_new + ((out.hi ? 8.0 : 4.0) + wb) * n_copy) * c->N * out.group, s);
     const uint32_t groups = c->N / 1024;
 #define KS_LAUNCH_BUNDLE(LOGR, GV, PK)                                                                                               \
     hipLaunchKernelGGL((gather_bundle_rows<LOGR, GV, PK>), dim3((n_new + n_copy) * groups), dim3(64 * GV), 0, s, c->tw_fwd, c->d_mod,  \
@@ -340,53 +363,57 @@ void launch_ntt_fwd(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipS
     }
 }
 
-void launch_ntt_inv_rows(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipStream_t s, bool in_words32) {
-    const uint32_t limbs = map.n * io.n_polys;
-    if (limbs == 0) return;
-    uint64_t* out = static_cast<uint64_t*>(io.out);
-    ProfScope ps("ntt_inv_rows", (in_words32 ? 1.5 : 2.0) * limbs * c->N * 8.0, s);
-#define KS_LAUNCH(LOGR)                                                                                                          \
-    if (in_words32)                                                                                                              \
-        hipLaunchKernelGGL((ntt_inv_rows<LOGR, uint32_t>), dim3(limbs << (LOGR - 2)), dim3(64), 0, s, c->tw_inv, c->d_mod, map,          \
-                           static_cast<const uint32_t*>(io.in), out, io.in_poly_stride, io.out_poly_stride);                     \
-    else                                                                                                                         \
-        hipLaunchKernelGGL((ntt_inv_rows<LOGR, uint64_t>), dim3(limbs << (LOGR - 2)), dim3(64), 0, s, c->tw_inv, c->d_mod, map,          \
-                           static_cast<const uint64_t*>(io.in), out, io.in_poly_stride, io.out_poly_stride)
-    KS_FOR_LOG_R(c->logN, KS_LAUNCH)
-#undef KS_LAUNCH
-}
-
-void launch_ntt_inv_cols(const ks_ctx* c, const LimbMap& map, uint64_t* data, uint64_t ps_words, uint32_t n_polys,
-                         const double* scale_tab, bool scale_by_idx, bool out_f64, hipStream_t s) {
-    const uint32_t limbs = map.n * n_polys;
-    if (limbs == 0) return;
-    ProfScope ps("ntt_inv_cols", 2.0 * limbs * c->N * 8.0, s);
-    const int by_idx = scale_by_idx ? 1 : 0;
-#define KS_LAUNCH_INV_COLS(LOGR, TCV, GRID, F64)                                                                               \
-    hipLaunchKernelGGL((ntt_inv_cols<LOGR, TCV, F64>), dim3(GRID), dim3((TCV << LOGR) / 16), 0, s, c->d_tw_inv, c->d_mod, scale_tab, \
-                       by_idx, map, data, ps_words)
-    if (c->logN == 16 && wide_tiles(limbs)) {
-        if (out_f64) KS_LAUNCH_INV_COLS(8, 32, limbs * 8, true);
-        else KS_LAUNCH_INV_COLS(8, 32, limbs * 8, false);
-        return;
-    }
-#define KS_LAUNCH(LOGR)                                                                       \
-    if (out_f64) KS_LAUNCH_INV_COLS(LOGR, (4096 >> LOGR), limbs << (LOGR - 4), true); \
-    else KS_LAUNCH_INV_COLS(LOGR, (4096 >> LOGR), limbs << (LOGR - 4), false)
-    KS_FOR_LOG_R(c->logN, KS_LAUNCH)
-#undef KS_LAUNCH
-#undef KS_LAUNCH_INV_COLS
-}
-
 void launch_ntt_inv(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipStream_t s) {
     const uint32_t g = polys_per_group(c, map);
     for (uint32_t p0 = 0; p0 < io.n_polys; p0 += g) {
-        const uint32_t np = std::min(g, io.n_polys - p0);
-        XformIO part{static_cast<const uint64_t*>(io.in) + (uint64_t)p0 * io.in_poly_stride,
-                     static_cast<uint64_t*>(io.out) + (uint64_t)p0 * io.out_poly_stride, io.in_poly_stride, io.out_poly_stride, np};
-        launch_ntt_inv_rows(c, map, part, s);
-        launch_ntt_inv_cols(c, map, static_cast<uint64_t*>(part.out), io.out_poly_stride, np, c->d_ninv, false, false, s);
+        const uint32_t limbs = map.n * std::min(g, io.n_polys - p0);
+        uint64_t* data = static_cast<uint64_t*>(io.out) + (uint64_t)p0 * io.out_poly_stride;
+        {
+            ProfScope ps("ntt_inv_rows", 2.0 * limbs * c->N * 8.0, s);
+#define KS_LAUNCH(LOGR) \
+    hipLaunchKernelGGL((ntt_inv_rows<LOGR>), dim3(limbs << (LOGR - 2)), dim3(64), 0, s, c->tw_inv, c->d_mod, map, data, io.out_poly_stride)
+            KS_FOR_LOG_R(c->logN, KS_LAUNCH)
+#undef KS_LAUNCH
+        }
+        ProfScope ps("ntt_inv_cols", 2.0 * limbs * c->N * 8.0, s);
+#define KS_LAUNCH_TC(LOGR, TCV)                                                                                                       \
+    hipLaunchKernelGGL((ntt_inv_cols<LOGR, TCV>), dim3(limbs * (256 / TCV)), dim3((TCV << LOGR) / 16), 0, s, c->d_tw_inv, c->d_mod, c->d_ninv, \
+                       map, data, io.out_poly_stride)
+#define KS_LAUNCH(LOGR) KS_LAUNCH_TC(LOGR, (4096 >> LOGR))
+        if (c->logN == 16 && wide_tiles(limbs)) KS_LAUNCH_TC(8, 32);
+        else KS_FOR_LOG_R(c->logN, KS_LAUNCH)
+#undef KS_LAUNCH
+#undef KS_LAUNCH_TC
     }
+}
+
+void launch_inv_rows_packed(const ks_ctx* c, const LimbMap& map, const void* in, uint64_t in_ps, int in_word, uint8_t* out, uint64_t out_ps,
+                            uint32_t n_polys, hipStream_t s) {
+    const uint32_t limbs = map.n * n_polys;
+    if (limbs == 0) return;
+    ProfScope ps("inv_rows_packed", ((in_word == 1 ? 5.0 : in_word) + 5.0) * limbs * c->N, s);
+#define KS_LAUNCH_W(LOGR, WT)                                                                                                          \
+    hipLaunchKernelGGL((inv_rows_packed<LOGR, WT>), dim3(limbs << (LOGR - 2)), dim3(64), 0, s, c->tw_inv, c->d_mod, map,               \
+                       static_cast<const WT*>(in), in_ps, out, out_ps)
+#define KS_LAUNCH(LOGR)                               \
+    if (in_word == 1) KS_LAUNCH_W(LOGR, uint8_t);     \
+    else if (in_word == 4) KS_LAUNCH_W(LOGR, uint32_t); \
+    else KS_LAUNCH_W(LOGR, uint64_t)
+    KS_FOR_LOG_R(c->logN, KS_LAUNCH)
+#undef KS_LAUNCH
+#undef KS_LAUNCH_W
+}
+
+void launch_inv_cols_packed(const ks_ctx* c, const LimbMap& map, uint8_t* data, uint64_t ps_bytes, uint32_t n_polys, const double* scale_tab,
+                            hipStream_t s) {
+    const uint32_t limbs = map.n * n_polys;
+    if (limbs == 0) return;
+    ProfScope ps("inv_cols_packed", 2.0 * limbs * packed_limb_bytes(c->N), s);
+#define KS_LAUNCH(LOGR)                                                                                                              \
+    hipLaunchKernelGGL((inv_cols_packed<LOGR>), dim3(limbs << (LOGR - 4)), dim3(256), 0, s, c->d_tw_inv, c->d_mod, scale_tab, map, data, \
+                       ps_bytes)
+    KS_FOR_LOG_R(c->logN, KS_LAUNCH)
+#undef KS_LAUNCH
 }
 
 void launch_ntt_u32(const ks_ctx* c, const LimbMap& map, uint32_t* data, uint64_t ps_words, uint32_t n_polys, bool inverse,

@@ -90,6 +90,17 @@ __device__ __forceinline__ void row_twiddles_to_lds(double* ta_row, const double
     ta_row[j0] = j0 ? W[(node << u) + g] : 0.0;
 }
 
+// Both passes' twiddles of a wavefront's four rows in LDS, for a kernel that uses them again and again: entry k of the first pass at
+// ta[16 (lane / 16) + k], of the second (load_row_twiddles' t.b) at tb[64 (k - 1) + lane].  The caller synchronises before use.
+__device__ __forceinline__ void store_row_twiddles(double* ta, double* tb, const TwTables& tbl, uint32_t mod_id, uint32_t N, uint32_t node,
+                                                   uint32_t lane, Mod m) {
+    row_twiddles_to_lds(ta + (lane >> 4) * 16, tbl.W + (size_t)mod_id * N, node, lane & 15u);
+    double t[16];
+    load_row_twiddles_b(t, tbl, mod_id, N, node, lane & 15u, m);
+#pragma unroll
+    for (int k = 1; k < 16; ++k) tb[64 * (k - 1) + lane] = t[k];
+}
+
 // Columns (R = 2^LOG_R rows, 4 <= LOG_R <= 8): the first register pass runs global stages 0..3 with the sub-tree below
 // heap node 1; the second one the remaining E = LOG_R - 4 stages on 16 consecutive rows 16 r0 + k, as the last E local
 // stages of a 16-point pass: local stage ul = 4 - E + u is global stage 4 + u, whose block of row 16 r0 + k is
@@ -136,23 +147,26 @@ __device__ __forceinline__ void row_fwd_core_consecutive(double (&v)[16], const 
     radix16_fwd(v, t.b, m);
 }
 
-// The same with the first-pass twiddles read from LDS (ta: 16 doubles of this row) and the second-pass ones in registers.
-__device__ __forceinline__ void row_fwd_core_lds(double (&v)[16], const double* ta, const double (&tb)[16], uint32_t j0, double* lrow,
-                                                 Mod m) {
-    radix16_fwd(v, *reinterpret_cast<const double(*)[16]>(ta), m);
+// radix16_fwd with twiddles from LDS (t[stride * k], k = 1..15), fenced stage by stage so that no more than a stage's are in
+// registers at a time.
+template <int U = 0>
+__device__ __forceinline__ void radix16_fwd_lds(double (&v)[16], const double* t, uint32_t stride, Mod m) {
+    constexpr int HALF = 8 >> U;
+    double w[1 << U];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) lrow[j0 + 17 * k] = v[k];
-    __syncthreads();
+    for (int g = 0; g < (1 << U); ++g) w[g] = t[stride * ((1 << U) + g)];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = lrow[17 * j0 + k];
-    radix16_fwd(v, tb, m);
+    for (int g = 0; g < (1 << U); ++g)
 #pragma unroll
-    for (int k = 0; k < 16; ++k) lrow[17 * j0 + k] = v[k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = lrow[j0 + 17 * k];
+        for (int i = 0; i < HALF; ++i) {
+            const int k = g * 2 * HALF + i;
+            const double x = mulmod_lazy(v[k + HALF], w[g], m);
+            v[k + HALF] = v[k] - x;
+            v[k] = v[k] + x;
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (U < 3) radix16_fwd_lds<U + 1>(v, t, stride, m);
 }
-
 // First 8 inverse stages of one row (t built from the inverse table).  in: v[k] = point j0 + 16 k, |v| <= p.
 // out: same layout, |v| <= 0.51 p.
 __device__ __forceinline__ void row_inv_core(double (&v)[16], const PassTwiddles& t, uint32_t j0, double* lrow, Mod m) {
@@ -212,12 +226,163 @@ __device__ __forceinline__ BufferRsrc make_buffer_rsrc(const void* base, uint64_
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(uint32_t)bytes, 0x00020000);
 }
 
-// Point k of the 16 strided points of a column-pass thread (rows r0 + (R / 16) k): the double at byte offset
-// limb_off + k * 16 R * 8 + lane_off of the buffer, lane_off = 8 (256 r0 + column).
-template <int LOG_R>
-__device__ __forceinline__ double load_strided_point(BufferRsrc rsrc, uint32_t lane_off, uint32_t limb_off, int k) {
-    constexpr uint32_t kStrideBytes = (16u << LOG_R) * 8u;
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)lane_off, (int)(limb_off + k * kStrideBytes), 0));
+// ---- packed limbs ----------------------------------------------------------------------------------------------------
+// Between its kernels a call keeps a limb as N 32-bit low words followed by N bytes, 5 bytes a residue instead of 8: a value v
+// (|v| < 2^39: every lazy representative of the chain, unreduced) is stored as the 40 bits of v + 2^39.  Packing is one addition and
+// a byte permutation, unpacking the reverse.
+//   Elements are ordered for the kernels at both ends, which move 16 values a thread: element 4 (256 g + j) + x is word x of
+// the 16 bytes `j` of a group g of four rows, and byte x of the 4 bytes `j`.  A thread takes four accesses of 16 and four of 4 bytes,
+// each of them contiguous over a wavefront, where 8-byte rows took sixteen.  What the element is depends on the two ends:
+//   rows -> rows  (accumulators, tensor product): j = 64 i + lane, value k = 4 i + x of that lane: row lane / 16, column lane % 16 + 16 k;
+//   rows <-> columns (half-transformed limbs): j is the column and x the row.  A row thread holds 16 columns of one row and a
+// column thread 16 rows of one column, so the row kernels exchange blocks of 4 x 4 among the lanes that share a column group
+// (exchange_rows: one instruction a value, no LDS);
+//   columns -> conversion (sources, see load_source): j is the column, row x of group 4 r0 + q the strided row r0 + (R / 16) (4 q + x):
+// the values that one thread leaves and one thread of the conversion takes.
+constexpr double kPackBias = 0x1.8p52 + 0x1p39;
+KS_HD constexpr uint64_t packed_limb_bytes(uint64_t N) { return 5 * N; }
+
+struct alignas(16) Words4 {
+    uint32_t w[4];
+};
+struct PackedRaw {
+    uint32_t lo[16], hi[4];
+};
+// The lowest bytes of four words.
+__device__ __forceinline__ uint32_t low_bytes(uint32_t h0, uint32_t h1, uint32_t h2, uint32_t h3) {
+    return __builtin_amdgcn_perm(h1, h0, 0x0c0c0400) | __builtin_amdgcn_perm(h3, h2, 0x04000c0c);
+}
+// at: 256 g + lane with STEP 64 (rows), 1024 r0 + column with STEP 256 (columns)
+template <uint32_t STEP>
+__device__ __forceinline__ PackedRaw packed_load(const uint8_t* limb, uint32_t N, uint32_t at) {
+    const Words4* lo = reinterpret_cast<const Words4*>(limb) + at;
+    const uint32_t* hi = reinterpret_cast<const uint32_t*>(limb + 4 * (size_t)N) + at;
+    PackedRaw r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const Words4 q = lo[i * STEP];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) r.lo[4 * i + x] = q.w[x];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.hi[i] = hi[i * STEP];
+    return r;
+}
+template <uint32_t STEP>
+__device__ __forceinline__ void packed_store(uint8_t* limb, uint32_t N, uint32_t at, const PackedRaw& r) {
+    Words4* lo = reinterpret_cast<Words4*>(limb) + at;
+    uint32_t* hi = reinterpret_cast<uint32_t*>(limb + 4 * (size_t)N) + at;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) lo[i * STEP] = Words4{{r.lo[4 * i], r.lo[4 * i + 1], r.lo[4 * i + 2], r.lo[4 * i + 3]}};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) hi[i * STEP] = r.hi[i];
+}
+// Kernels with one thread per slot: 64 consecutive slots are 64 consecutive elements in the rows -> rows order, permuted.
+__device__ __forceinline__ uint32_t packed_element(uint32_t n) {
+    return (n & ~1023u) | (n & 192u) << 2 | (n & 768u) >> 2 | (n & 15u) << 2 | ((n >> 4) & 3u);
+}
+__device__ __forceinline__ double packed_get(const uint8_t* limb, uint32_t N, uint32_t e) {
+    const uint64_t bits = (uint64_t)(0x43380000u | limb[4 * (size_t)N + e]) << 32 | reinterpret_cast<const uint32_t*>(limb)[e];
+    return __builtin_bit_cast(double, bits) - kPackBias;
+}
+
+// The values of slot n of LIMBS limbs stored by a wavefront that holds 64 consecutive slots: the lanes exchange what they hold, so that
+// a lane's neighbours write its neighbours in memory (as permuted stores every 16 lanes touch four times the lines: four rotations of
+// eight ciphertexts, N = 2^16, 315 -> 413 us).  limb: the first of the limbs, `stride` bytes apart; element: packed_element of the
+// wavefront's first slot.
+template <int LIMBS>
+__device__ __forceinline__ void packed_put(uint8_t* limb, uint64_t stride, uint32_t N, uint32_t element, const double (&v)[LIMBS]) {
+    const uint32_t lane = threadIdx.x & 63u, from = ((lane & 3u) * 16 + (lane >> 2)) * 4, e = element + lane;
+    uint32_t h[(LIMBS + 3) / 4 * 4] = {};
+#pragma unroll
+    for (int i = 0; i < LIMBS; ++i) {
+        const uint64_t bits = __builtin_bit_cast(uint64_t, v[i] + kPackBias);
+        reinterpret_cast<uint32_t*>(limb + i * stride)[e] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)from, (int)(uint32_t)bits);
+        h[i] = (uint32_t)(bits >> 32);
+    }
+#pragma unroll
+    for (int i = 0; i < LIMBS; i += 4) {
+        const uint32_t b = (uint32_t)__builtin_amdgcn_ds_bpermute((int)from, (int)low_bytes(h[i], h[i + 1], h[i + 2], h[i + 3]));
+#pragma unroll
+        for (int x = 0; x < 4 && i + x < LIMBS; ++x) (limb + (i + x) * stride)[4 * (size_t)N + e] = (uint8_t)(b >> (8 * x));
+    }
+}
+
+// Byte x of every word -> word x: r[i] byte x becomes r[x] byte i.
+__device__ __forceinline__ void transpose_bytes(uint32_t (&r)[4]) {
+    const uint32_t a = __builtin_amdgcn_perm(r[1], r[0], 0x05010400), b = __builtin_amdgcn_perm(r[3], r[2], 0x05010400);
+    const uint32_t c = __builtin_amdgcn_perm(r[1], r[0], 0x07030602), d = __builtin_amdgcn_perm(r[3], r[2], 0x07030602);
+    r[0] = __builtin_amdgcn_perm(b, a, 0x05040100);
+    r[1] = __builtin_amdgcn_perm(b, a, 0x07060302);
+    r[2] = __builtin_amdgcn_perm(d, c, 0x05040100);
+    r[3] = __builtin_amdgcn_perm(d, c, 0x07060302);
+}
+// Word x of lane l + 16 i becomes word i of lane l + 16 x (l < 16): a 4 x 4 transposition, its own inverse.
+__device__ __forceinline__ void exchange_rows(uint32_t* r) {
+    const auto a = __builtin_amdgcn_permlane32_swap(r[0], r[2], false, false), b = __builtin_amdgcn_permlane32_swap(r[1], r[3], false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false), d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    r[0] = c[0];
+    r[1] = c[1];
+    r[2] = d[0];
+    r[3] = d[1];
+}
+// Sixteen values of a thread, in the order of their elements: byte x of hi[i] goes with lo[4 i + x].
+__device__ __forceinline__ PackedRaw pack(const double (&v)[16], double bias = kPackBias) {
+    PackedRaw r;
+    uint32_t h[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const uint64_t bits = __builtin_bit_cast(uint64_t, v[k] + bias);
+        r.lo[k] = (uint32_t)bits;
+        h[k] = (uint32_t)(bits >> 32);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.hi[i] = low_bytes(h[4 * i], h[4 * i + 1], h[4 * i + 2], h[4 * i + 3]);
+    return r;
+}
+__device__ __forceinline__ double unpack_one(uint32_t lo, uint32_t bytes, int x) {
+    const uint32_t hi = __builtin_amdgcn_perm(0x43380000u, bytes, 0x07060500u + x);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo) - kPackBias;
+}
+__device__ __forceinline__ void unpack(const PackedRaw& r, double (&v)[16]) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = unpack_one(r.lo[k], r.hi[k >> 2], k & 3);
+}
+// The same for a row thread whose limb is in columns order: value k is column 16 k + lane % 16 of the thread's row, and the element
+// that a lane loads or stores belongs to row x of column 64 i + lane.
+__device__ __forceinline__ PackedRaw pack_rows(const double (&v)[16]) {
+    PackedRaw r;
+    uint32_t h[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const uint64_t bits = __builtin_bit_cast(uint64_t, v[k] + kPackBias);
+        r.lo[k] = (uint32_t)bits;
+        h[k] = (uint32_t)(bits >> 32);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) exchange_rows(r.lo + 4 * i);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) r.hi[x] = low_bytes(h[x], h[4 + x], h[8 + x], h[12 + x]);
+    exchange_rows(r.hi);
+    transpose_bytes(r.hi);
+    return r;
+}
+__device__ __forceinline__ void unpack_rows(PackedRaw r, double (&v)[16]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) exchange_rows(r.lo + 4 * i);
+    transpose_bytes(r.hi);
+    exchange_rows(r.hi);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = unpack_one(r.lo[k], r.hi[k & 3], k >> 2);
+}
+
+// Sources of a conversion: y + 0x80808080 of a residue |y| < 2^36 (canonical, or the signed remainder of a rescale) as the low
+// word and the (signed) byte above.  With the top bit of each byte flipped the word is the residue's signed base-256 digits
+// d_0..d_3 (digit = byte - 128), and the byte is d_4, |d_4| <= 17.  The bytes of a thread's 16 values are 16 consecutive ones,
+// inside the 64 bytes of a group of rows that a column tile of 16 owns (the limb is converted in place, tile by tile).
+constexpr double kDigitBias = 6755399441055744.0 + 2155905152.0;   // 1.5 * 2^52 + 0x80808080
+__device__ __forceinline__ uint32_t source_bytes_offset(uint32_t r0, uint32_t col) {
+    return (4 * r0 + ((col >> 2) & 3u)) * 1024 + (col >> 4) * 64 + (col & 3u) * 16;
 }
 
 // Row index of v[k] before / after the column cores, and the first column of the tile.
