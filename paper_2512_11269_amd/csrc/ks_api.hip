@@ -57,13 +57,9 @@ KsWorkspaceWords ks_ws_words(const ks_ctx* c, const Level& lv, uint32_t bc) {
     return w;
 }
 
-// Decompose and raise: d (evaluation domain, `bc` polynomials d_ps words apart) -> lifted [bc][ndig][E] packed.
-// The raised limbs stop after the column half of the forward transform; the row half is left to the
-// fused inner product, or to mod_up_for_gather below.  tile: the conversion kernel of the call (conversion_tile).
-void mod_up(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, uint8_t* coeff, uint8_t* lifted, uint32_t bc,
-            int tile, hipStream_t s, bool d_words32 = false) {
+// mod_up from the row half of the inverse transform on: coeff [bc][ell] packed.
+void mod_up_from_rows(const ks_ctx* c, const Level& lv, uint8_t* coeff, uint8_t* lifted, uint32_t bc, int tile, hipStream_t s) {
     const uint64_t limb = packed_limb_bytes(c->N), coeff_ps = lv.ell * limb, lifted_ps = (uint64_t)lv.ndig * lv.E * limb;
-    launch_inv_rows_packed(c, lv.q_map, d, d_ps, d_words32 ? 4 : 8, coeff, coeff_ps, bc, s);
     // the column half also multiplies by N^-1 (D_j/q_i)^-1 and leaves the sources of the conversion
     launch_inv_cols_packed(c, lv.q_map, coeff, coeff_ps, bc, lv.d_modup_scale, s);
     // algorithmic fp64 work per coefficient: 3 FMAs per source x target plus the 6 instructions that cut the source, shared
@@ -76,6 +72,15 @@ void mod_up(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, uint
     }
     ops += lv.n_new * (3.0 + 4.0 * (c->logN - 8));
     launch_bconv_ntt_cols(c, lv.modup, lv.ell + lv.n_new, coeff, coeff_ps, lifted, lifted_ps, bc, tile, s, ops);
+}
+
+// Decompose and raise: d (evaluation domain, `bc` polynomials d_ps words apart) -> lifted [bc][ndig][E] packed.
+// The raised limbs stop after the column half of the forward transform; the row half is left to the
+// fused inner product, or to mod_up_for_gather below.  tile: the conversion kernel of the call (conversion_tile).
+void mod_up(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, uint8_t* coeff, uint8_t* lifted, uint32_t bc,
+            int tile, hipStream_t s, bool d_words32 = false) {
+    launch_inv_rows_packed(c, lv.q_map, d, d_ps, d_words32 ? 4 : 8, coeff, lv.ell * packed_limb_bytes(c->N), bc, s);
+    mod_up_from_rows(c, lv, coeff, lifted, bc, tile, s);
 }
 
 // Words of workspace the bundle of a chunk of bc ciphertexts takes: low words, then (64-bit operands) the bits above;
@@ -330,7 +335,7 @@ int ks::keyswitch_impl(const ks_ctx* c, const void* d, uint32_t ell, const void*
         const char* dc = static_cast<const char*>(d) + (uint64_t)b0 * d_ps * word;
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
         mod_up(c, lv, dc, d_ps, coeff, lifted, bc, tile, s, words32);
-        launch_rows_inner_product(c, lv, dc, d_ps, lifted, evk, acc, bc, s, words32, words32);
+        launch_rows_inner_product(c, lv, dc, d_ps, lifted, evk, acc, bc, s, (int)word, words32);
         mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * out_bs * word, out_bs, bc, true, tile, s, words32);
     }
     return finish(words32 ? "ks_keyswitch_u32" : "ks_keyswitch");
@@ -571,8 +576,7 @@ static void mod_down_drop(const ks_ctx* c, const Level& lv, uint8_t* acc, uint8_
     launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, addend, 0, 2, 1, bc, s, &fs, out_words32);
 }
 
-// cta, ctb, rlk and out in 64-bit words, or all four in 32-bit words (words32); the tensor product and everything after it
-// in the workspace stay 64-bit.
+// cta, ctb, rlk and out in 64-bit words, or all four in 32-bit words (words32).
 static int hmult_impl(const ks_ctx* c, const void* cta, const void* ctb, uint32_t ell, const void* rlk, void* out, uint32_t batch,
                       void* ws, size_t ws_bytes, void* stream, bool merged, bool words32) {
     int rc = check_pipeline_args(c, ell, 2, cta, ctb, out, ws);
@@ -593,14 +597,13 @@ static int hmult_impl(const ks_ctx* c, const void* cta, const void* ctb, uint32_
         uint8_t* acc = lifted + w.lifted;
         uint8_t* conv = acc + w.acc;
         uint8_t* dq = conv + w.conv;                                    // (d0, d1): [bc][2][ell] packed
-        uint64_t* d2 = reinterpret_cast<uint64_t*>(dq + w.conv);        // [bc][ell][N], the polynomial that is key-switched
-        const uint64_t d2_ps = (uint64_t)ell * N;
+        uint8_t* d2 = dq + w.conv;                                      // [bc][ell] packed, the polynomial that is key-switched
         char* oc = static_cast<char*>(out) + (uint64_t)b0 * out_bs * word;
-        launch_tensor_product(c, static_cast<const char*>(cta) + (uint64_t)b0 * ct_bs * word,
-                              static_cast<const char*>(ctb) + (uint64_t)b0 * ct_bs * word, d2, dq, ell, bc, s, words32);
+        launch_tensor_inv_rows(c, static_cast<const char*>(cta) + (uint64_t)b0 * ct_bs * word,
+                               static_cast<const char*>(ctb) + (uint64_t)b0 * ct_bs * word, ell, dq, d2, coeff, bc, s, words32);
         const int tile = conversion_tile(c, lv.modup, bc, merged ? lv.merged : lv.rescale, 2 * bc);
-        mod_up(c, lv, d2, d2_ps, coeff, lifted, bc, tile, s);
-        launch_rows_inner_product(c, lv, d2, d2_ps, lifted, rlk, acc, bc, s, false, words32, dq);
+        mod_up_from_rows(c, lv, coeff, lifted, bc, tile, s);
+        launch_rows_inner_product(c, lv, d2, w.coeff / bc, lifted, rlk, acc, bc, s, 1, words32, dq);
         mod_down_drop(c, lv, acc, conv, oc, out_bs, dq, bc, tile, s, merged, words32);
     }
     if (merged) return finish(words32 ? "hmult_relin_rescale_merged_u32" : "hmult_relin_rescale_merged");

@@ -1,5 +1,5 @@
 // Slot-wise kernels (Kernel Code Generation, "Elementwise" kernel class): inner products with evaluation keys through the
-// evaluation-domain automorphism (gathers) and the tensor product.  One thread per slot, contiguous segments per wavefront,
+// evaluation-domain automorphism (gathers).  One thread per slot, contiguous segments per wavefront,
 // operands shared by both key components and by all ciphertexts of a group are read once ("load reuse").
 #include "ks_internal.hpp"
 #include "ks_tiles.hpp"
@@ -389,36 +389,6 @@ void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src
 #undef KS_GATHER_32
 #undef KS_GATHER_PACKED_32
 #undef KS_GATHER_PACKED_64
-}
-
-// (b1, a1) x (b2, a2) -> d0 = b1 b2, d1 = a1 b2 + a2 b1, d2 = a1 a2.  d2, the polynomial that is key-switched, goes out as
-// 64-bit words ([b][ell][N]); d0 and d1 are only added back by the last kernel of the chain and go out packed ([b][2][ell] limbs
-// in rows order).
-template <typename W>
-__global__ __launch_bounds__(256) void tensor_product_kernel(const Mod* __restrict__ mods, uint32_t ell, uint32_t N,
-                                                             const W* __restrict__ cta, const W* __restrict__ ctb,
-                                                             uint64_t* __restrict__ d2, uint8_t* __restrict__ dq) {
-    const uint32_t i = blockIdx.y, b = blockIdx.z;
-    const Mod m = mods[i];
-    const uint64_t n = blockIdx.x * 256 + threadIdx.x;
-    const uint64_t ct_off = ((uint64_t)b * 2 * ell + i) * N + n, comp = (uint64_t)ell * N;
-    const double b1 = word_to_f64<W>(cta[ct_off]), a1 = word_to_f64<W>(cta[ct_off + comp]);
-    const double b2 = word_to_f64<W>(ctb[ct_off]), a2 = word_to_f64<W>(ctb[ct_off + comp]);
-    const double sums[2] = {mulmod_lazy(b1, b2, m), reduce_lazy(mulmod_lazy(a1, b2, m) + mulmod_lazy(a2, b1, m), m)};
-    packed_put<2>(dq + ((uint64_t)b * 2 * ell + i) * packed_limb_bytes(N), ell * packed_limb_bytes(N), N, packed_element((uint32_t)n & ~63u), sums);
-    d2[((uint64_t)b * ell + i) * N + n] = f64_to_u64(canon(mulmod_lazy(a1, a2, m), m));
-}
-
-void launch_tensor_product(const ks_ctx* c, const void* cta, const void* ctb, uint64_t* d2, uint8_t* dq, uint32_t ell,
-                           uint32_t batch, hipStream_t s, bool in_words32) {
-    if (batch == 0) return;
-    ProfScope ps("tensor_product", (double)batch * ell * ((in_words32 ? 16 : 32) + 8 + 10) * c->N, s);
-    if (in_words32)
-        hipLaunchKernelGGL(tensor_product_kernel<uint32_t>, dim3(c->N / 256, ell, batch), dim3(256), 0, s, c->d_mod, ell, c->N,
-                           static_cast<const uint32_t*>(cta), static_cast<const uint32_t*>(ctb), d2, dq);
-    else
-        hipLaunchKernelGGL(tensor_product_kernel<uint64_t>, dim3(c->N / 256, ell, batch), dim3(256), 0, s, c->d_mod, ell, c->N,
-                           static_cast<const uint64_t*>(cta), static_cast<const uint64_t*>(ctb), d2, dq);
 }
 
 }  // namespace ks

@@ -249,7 +249,7 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
 // A workgroup = four rows of one limb position; it walks the digits, so d~ is read once and feeds both key
 // components (load reuse), and the accumulators are reduced and written once.
 // ------------------------------------------------------------------------------------------------
-// WD / WK: word types of d and of the key (64-bit, or 32-bit for moduli below 2^32).
+// WD / WK: word types of d (uint8_t: packed) and of the key.
 template <int LOG_R, typename WD, typename WK, bool PREFETCH>
 __global__ __launch_bounds__(64, 2) void rows_inner_product(TwTables tw, TwTables twi, const Mod* __restrict__ mods, DigitRanges dg,
                                                          uint32_t ell, uint32_t E, uint32_t L, uint32_t M,
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(64, 2) void rows_inner_product(TwTables tw, TwTable
 }
 
 void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted,
-                               const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, bool d_words32, bool key_words32,
+                               const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, int d_word, bool key_words32,
                                const uint8_t* drop_addend) {
     if (batch == 0) return;
     DigitRanges dg;
@@ -289,8 +289,8 @@ void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, 
         dg.hi[j] = j < lv.ndig ? lv.digit_hi[j] : 0;
     }
     // reads: every raised digit limb per ciphertext and the key (once per call); writes: both accumulators
-    // d (ell limbs per ciphertext) and the key arrive in boundary words, the raised limbs and the sums packed
-    const double wd = d_words32 ? 4.0 : 8.0, wk = key_words32 ? 4.0 : 8.0;
+    // the key and (but for a tensor product) d arrive in boundary words, the raised limbs and the sums packed
+    const double wd = d_word == 1 ? 5.0 : d_word, wk = key_words32 ? 4.0 : 8.0;
     ProfScope ps("rows_inner_product",
                  ((double)batch * (5.0 * (lv.ndig * lv.E - lv.ell) + wd * lv.ell + 10.0 * lv.E) + wk * 2.0 * lv.ndig * lv.E) * c->N, s);
     const uint32_t tiles = (c->N / 1024) * lv.E;
@@ -304,9 +304,10 @@ void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, 
                        c->M, static_cast<const WDT*>(d), d_ps, lifted, static_cast<const WKT*>(evk), acc, drop_addend, lv.Pmod_last, batch, \
                        prefetch ? 0u : 1u)
 #define KS_LAUNCH_PF(LOGR, PF)                                                \
-    if (d_words32 && key_words32) KS_LAUNCH_IP(LOGR, uint32_t, uint32_t, PF); \
-    else if (key_words32) KS_LAUNCH_IP(LOGR, uint64_t, uint32_t, PF);         \
-    else KS_LAUNCH_IP(LOGR, uint64_t, uint64_t, PF)
+    if (d_word == 4) KS_LAUNCH_IP(LOGR, uint32_t, uint32_t, PF);               \
+    else if (d_word == 8) KS_LAUNCH_IP(LOGR, uint64_t, uint64_t, PF);          \
+    else if (key_words32) KS_LAUNCH_IP(LOGR, uint8_t, uint32_t, PF);           \
+    else KS_LAUNCH_IP(LOGR, uint8_t, uint64_t, PF)
 #define KS_LAUNCH(LOGR)                          \
     if (prefetch) { KS_LAUNCH_PF(LOGR, true); } \
     else { KS_LAUNCH_PF(LOGR, false); }

@@ -207,12 +207,12 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
 // Upload host plans as a PlanSet (allocates; ks_ctx_create and bconv plan registration only).  Returns a HIP error code.
 hipError_t upload_plans(const BConvPlan* host_plans, uint32_t n_plans, uint32_t shape_src, PlanSet* out);
 // Fused row half of the forward transform of the raised digits + inner product with the key.
-// d_words32 / key_words32: d / the key hold one residue per 32-bit word (d_words32 implies key_words32)
-// acc: [b][2][E] packed.  The ciphertext limbs are in rows order; the special limbs have been through the row half of their inverse
+// d_word: bytes of a word of d, 8 or 4, or 1: packed limbs in rows order (then d_ps counts bytes); key_words32: the key holds one residue
+// per 32-bit word (4-byte words of d imply them).  acc: [b][2][E] packed.  The ciphertext limbs are in rows order; the special limbs have been through the row half of their inverse
 // transform and are in columns order.  drop_addend != nullptr: limb ell-1 joins the special limbs after P times limb ell-1 of that
 // addend ([b][2][ell] packed) has been added.
 void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted,
-                               const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, bool d_words32, bool key_words32,
+                               const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, int d_word, bool key_words32,
                                const uint8_t* drop_addend = nullptr);
 // Fused row half of the forward transform of the converted limbs (conv, [b][2][ell] packed) + (acc - conv) P^-1 (+ addend);
 // the ciphertext limbs of acc ([b][2][E] packed) are in rows order.
@@ -316,7 +316,8 @@ int keyswitch_impl(const ks_ctx* c, const void* d, uint32_t ell, const void* evk
 // the device current.  Returns a HIP error code.
 hipError_t bind_static_scratch(int device);
 
-// d0 = b1 b2, d1 = a1 b2 + a2 b1 -> dq [batch][2][ell] packed, rows order; d2 = a1 a2 -> d2 [batch][ell][N] 64-bit words
-void launch_tensor_product(const ks_ctx* c, const void* cta, const void* ctb, uint64_t* d2, uint8_t* dq, uint32_t ell,
-                           uint32_t batch, hipStream_t s, bool in_words32 = false);
+// Tensor product of two ciphertexts ([batch][2][ell][N] words): d0 = b1 b2, d1 = a1 b2 + a2 b1 -> dq [batch][2][ell], d2 = a1 a2 ->
+// d2 [batch][ell], packed limbs in rows order; the row half of d2's inverse transform -> inv [batch][ell] in columns order.
+void launch_tensor_inv_rows(const ks_ctx* c, const void* cta, const void* ctb, uint32_t ell, uint8_t* dq, uint8_t* d2, uint8_t* inv,
+                            uint32_t batch, hipStream_t s, bool in_words32);
 }  // namespace ks

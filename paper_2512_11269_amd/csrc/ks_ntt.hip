@@ -192,6 +192,22 @@ __global__ __launch_bounds__(64) void inv_rows_packed(TwTables twi, const Mod* _
                                    out + poly * out_ps + limb * packed_limb_bytes(N), rg, threadIdx.x, lds);
 }
 
+// cta, ctb: [b][2][ell][N] words; dq: [b][2][ell], d2 and inv: [b][ell] packed limbs.
+// Bound by its traffic, four limbs of words in and four packed ones out: eight pairs, 35 limbs, N = 2^16, 180 us (5.3 TB/s), where a
+// tensor product by slots and the row half on its own took 166 + 50.
+template <int LOG_R, typename W>
+__global__ __launch_bounds__(64, 2) void tensor_inv_rows(TwTables twi, const Mod* __restrict__ mods, uint32_t ell, const W* __restrict__ cta,
+                                                         const W* __restrict__ ctb, uint8_t* __restrict__ dq, uint8_t* __restrict__ d2,
+                                                         uint8_t* __restrict__ inv) {
+    constexpr uint32_t N = 256u << LOG_R;
+    constexpr uint64_t LIMB = packed_limb_bytes(N);
+    __shared__ double lds[4 * kRowPitch];
+    const uint32_t rg = blockIdx.x, i = blockIdx.y, b = blockIdx.z;
+    const uint64_t ct = ((uint64_t)b * 2 * ell + i) * N, one = (uint64_t)b * ell + i, two = (uint64_t)b * 2 * ell + i;
+    task_tensor_inv_rows<LOG_R, W>(twi, mods[i], i, cta + ct, ctb + ct, (uint64_t)ell * N, dq + two * LIMB, dq + (two + ell) * LIMB, d2 + one * LIMB,
+                                   inv + one * LIMB, rg, threadIdx.x, lds);
+}
+
 // Out: [x * scale]_m as sources of a conversion; scale_tab holds N^-1 times the conversion's (D / s_i)^-1, by position in the map.
 template <int LOG_R>
 __global__ __launch_bounds__(256) void inv_cols_packed(const double* __restrict__ twi, const Mod* __restrict__ mods,
@@ -398,6 +414,21 @@ void launch_inv_rows_packed(const ks_ctx* c, const LimbMap& map, const void* in,
 #define KS_LAUNCH(LOGR)                               \
     if (in_word == 1) KS_LAUNCH_W(LOGR, uint8_t);     \
     else if (in_word == 4) KS_LAUNCH_W(LOGR, uint32_t); \
+    else KS_LAUNCH_W(LOGR, uint64_t)
+    KS_FOR_LOG_R(c->logN, KS_LAUNCH)
+#undef KS_LAUNCH
+#undef KS_LAUNCH_W
+}
+
+void launch_tensor_inv_rows(const ks_ctx* c, const void* cta, const void* ctb, uint32_t ell, uint8_t* dq, uint8_t* d2, uint8_t* inv,
+                            uint32_t batch, hipStream_t s, bool in_words32) {
+    if (batch == 0) return;
+    ProfScope ps("tensor_inv_rows", (double)batch * ell * ((in_words32 ? 16 : 32) + 20) * c->N, s);
+#define KS_LAUNCH_W(LOGR, WT)                                                                                                    \
+    hipLaunchKernelGGL((tensor_inv_rows<LOGR, WT>), dim3(c->N / 1024, ell, batch), dim3(64), 0, s, c->tw_inv, c->d_mod, ell,     \
+                       static_cast<const WT*>(cta), static_cast<const WT*>(ctb), dq, d2, inv)
+#define KS_LAUNCH(LOGR)                        \
+    if (in_words32) KS_LAUNCH_W(LOGR, uint32_t); \
     else KS_LAUNCH_W(LOGR, uint64_t)
     KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH

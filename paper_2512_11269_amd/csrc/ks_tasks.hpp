@@ -49,6 +49,45 @@ __device__ __forceinline__ void task_inv_rows_packed(const TwTables& twi, Mod m,
     packed_store<64>(op, N, rg * 256 + lane, pack_rows(v));
 }
 
+// ---- tensor product of two ciphertexts (b1, a1) x (b2, a2) and the row half of the inverse transform of a1 a2 -----------
+// One wavefront: four rows (group rg) of one limb.  d0 = b1 b2 and d1 = a1 b2 + a2 b1 are only added back by the last kernel of the
+// call, d2 = a1 a2 is one digit of the inner product as it is: packed, rows order.  inv: the transformed d2, columns order.
+// x1 / x2: that limb of b1 and b2, the limbs of a1 and a2 `comp` words behind.
+template <int LOG_R, typename W>
+__device__ __forceinline__ void task_tensor_inv_rows(const TwTables& twi, Mod m, uint32_t mod_id, const W* __restrict__ x1,
+                                                     const W* __restrict__ x2, uint64_t comp, uint8_t* __restrict__ d0, uint8_t* __restrict__ d1,
+                                                     uint8_t* __restrict__ d2, uint8_t* __restrict__ inv, uint32_t rg, uint32_t lane,
+                                                     double* lds_wave) {
+    constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R;
+    const uint32_t j0 = lane & 15, rr = lane >> 4, row = rg * 4 + rr, off = row * 256 + j0, at = rg * 256 + lane;
+    W b1[16], a1[16], b2[16], a2[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        a1[k] = x1[comp + off + 16 * k];
+        a2[k] = x2[comp + off + 16 * k];
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        b1[k] = x1[off + 16 * k];
+        b2[k] = x2[off + 16 * k];
+    }
+    PassTwiddles t;
+    double v[16], u[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+        u[k] = reduce_lazy(mulmod_lazy(word_to_f64<W>(a1[k]), word_to_f64<W>(b2[k]), m) + mulmod_lazy(word_to_f64<W>(a2[k]), word_to_f64<W>(b1[k]), m), m);
+    packed_store<64>(d1, N, at, pack(u));
+#pragma unroll
+    for (int k = 0; k < 16; ++k) u[k] = mulmod_lazy(word_to_f64<W>(b1[k]), word_to_f64<W>(b2[k]), m);
+    packed_store<64>(d0, N, at, pack(u));
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = mulmod_lazy(word_to_f64<W>(a1[k]), word_to_f64<W>(a2[k]), m);
+    packed_store<64>(d2, N, at, pack(v));
+    load_row_twiddles(t, twi, mod_id, N, R + row, j0, m);
+    row_inv_core(v, t, j0, lds_wave + rr * kRowPitch, m);
+    packed_store<64>(inv, N, at, pack_rows(v));
+}
+
 // ---- inverse transform, column half, in place: raw doubles in, canonical [x * scale]_m out ------------------------------
 // Wi: the modulus's inverse twiddle table; tile: TC columns; tid < TC * R / 16; lds: TC * R doubles.
 template <int LOG_R, int TC>
@@ -279,7 +318,7 @@ __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ 
 // The ciphertext limbs of the sums are left for the last kernel of the call in rows order.  The special limbs, and limb ell - 1
 // where drop_b says that it is dropped (drop_b: that batch item's addend [2][ell], packed; null otherwise), go through the row
 // half of their inverse transform and are left in columns order.
-// WD / WK: word types of d and of the key (64-bit, or 32-bit for moduli below 2^32).
+// WD / WK: word types of d and of the key (64-bit, or 32-bit for moduli below 2^32; uint8_t: d in packed limbs, rows order).
 // PREFETCH: loads are requested in the order x(0), key(0), x(1), key(1), ... and return in that order.
 // While digit j is transformed, key(j) and x(j + 1) are in flight; every key slot is refilled with the next digit's as soon
 // as its product is done, so key(j + 1) has the whole transform of digit j + 1 to arrive.
@@ -311,7 +350,13 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
     };
     const auto own = [&](uint32_t j) { return pos >= dg.lo[j] && pos < dg.hi[j]; };
     const auto request = [&](uint32_t j, Source& x) {
-        if (own(j)) {
+        if constexpr (sizeof(WD) == 1) {
+            const PackedRaw t = packed_load<64>(own(j) ? d_b + pos * LIMB : lifted_b + ((uint64_t)j * E + pos) * LIMB, N, at);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) x.w[k] = t.lo[k];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x.w[16 + k] = t.hi[k];
+        } else if (own(j)) {
             const WD* src = d_b + (uint64_t)pos * N + off;
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
@@ -332,7 +377,15 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
         }
     };
     const auto values = [&](uint32_t j, const Source& s, double (&x)[16]) {
-        if (own(j)) {
+        if constexpr (sizeof(WD) == 1) {
+            PackedRaw t;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) t.lo[k] = s.w[k];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) t.hi[k] = s.w[16 + k];
+            if (own(j)) unpack(t, x);
+            else unpack_rows(t, x);
+        } else if (own(j)) {
 #pragma unroll
             for (int k = 0; k < 16; ++k)
                 if constexpr (sizeof(WD) == 8) x[k] = word_to_f64<WD>((uint64_t)s.w[2 * k + 1] << 32 | s.w[2 * k]);
