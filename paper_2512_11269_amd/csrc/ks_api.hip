@@ -187,7 +187,7 @@ extern "C" int ntt_fwd(const ks_ctx* c, uint64_t* data, const uint32_t* mod_ids,
     if (batch == 0) return KS_OK;
     if ((uint64_t)batch * nlimbs > (1u << 26)) return KS_EINVAL;
     const uint64_t ps = (uint64_t)nlimbs * c->N;
-    launch_ntt_fwd(c, map, XformIO{data, data, ps, ps, batch}, static_cast<hipStream_t>(stream));
+    launch_ntt(c, map, data, ps, batch, false, static_cast<hipStream_t>(stream));
     return finish("ntt_fwd");
 }
 
@@ -198,7 +198,7 @@ extern "C" int ntt_inv(const ks_ctx* c, uint64_t* data, const uint32_t* mod_ids,
     if (batch == 0) return KS_OK;
     if ((uint64_t)batch * nlimbs > (1u << 26)) return KS_EINVAL;
     const uint64_t ps = (uint64_t)nlimbs * c->N;
-    launch_ntt_inv(c, map, XformIO{data, data, ps, ps, batch}, static_cast<hipStream_t>(stream));
+    launch_ntt(c, map, data, ps, batch, true, static_cast<hipStream_t>(stream));
     return finish("ntt_inv");
 }
 

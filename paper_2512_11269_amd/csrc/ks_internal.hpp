@@ -169,24 +169,11 @@ struct ProfScope {
     }
 
 // ---- launchers: all asynchronous on `s`, no allocation ----
-// In/out element formats of the two-phase transform.  Intermediate results between the two phases are
-// stored as raw doubles (lazy representatives) in the same 8-byte slots.
-struct XformIO {
-    const void* in;
-    void* out;
-    uint64_t in_poly_stride, out_poly_stride;  // elements between consecutive bundles
-    uint32_t n_polys;
-};
-// forward: coefficient (canonical u64) -> evaluation (canonical u64)
-void launch_ntt_fwd(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipStream_t s);
-// inverse: evaluation (canonical u64) -> coefficient (canonical u64)
-void launch_ntt_inv(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipStream_t s);
+// Both directions on limbs of 64-bit words, in place: coefficients <-> evaluations, canonical residues in and out.
+void launch_ntt(const ks_ctx* c, const LimbMap& map, uint64_t* data, uint64_t ps_words, uint32_t n_polys, bool inverse, hipStream_t s);
 // both directions on limbs in 32-bit words, in place (canonical residues between the two passes as well)
 void launch_ntt_u32(const ks_ctx* c, const LimbMap& map, uint32_t* data, uint64_t ps_words, uint32_t n_polys, bool inverse,
                     hipStream_t s);
-// The two halves of each transform on their own (the fused pipeline replaces some halves by fused kernels).
-void launch_ntt_fwd_cols(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipStream_t s);
-void launch_ntt_fwd_rows(const ks_ctx* c, const LimbMap& map, uint64_t* data, uint64_t ps_words, uint32_t n_polys, hipStream_t s);
 // The inverse transform that feeds a conversion (packed limbs: ks_tiles.hpp).  Rows: `in` holds words of in_word = 8 or 4 bytes, or
 // (1) packed accumulators, converted in place; in_ps counts words (bytes for 1), out_ps bytes.
 void launch_inv_rows_packed(const ks_ctx* c, const LimbMap& map, const void* in, uint64_t in_ps, int in_word, uint8_t* out, uint64_t out_ps,

@@ -3,9 +3,8 @@
 // A limb is viewed as an R x 256 matrix (row-major, R = N / 256).  The forward transform runs its first
 // log2(R) decimation-in-time stages down the columns (butterfly partners R/2 ... 1 rows apart) and its last
 // 8 stages inside the contiguous 256-point rows; the inverse mirrors it.  Each thread owns 16 points: four
-// stages run in registers, then the tile is re-distributed through LDS for the next (up to) four.  Intermediate
-// results between the two kernels of a transform are raw doubles (lazy representatives); only the last
-// kernel reduces to canonical residues.
+// stages run in registers, then the tile is re-distributed through LDS for the next (up to) four.  Between the two kernels of
+// a transform a limb is packed (ks_tiles.hpp); only the last kernel reduces to canonical residues.
 #include <algorithm>
 
 #include "ks_internal.hpp"
@@ -13,60 +12,97 @@
 
 namespace ks {
 
-struct LimbRef {
-    const uint64_t* in;
-    uint64_t* out;
-    uint32_t mod_id, idx;
-};
-
-__device__ __forceinline__ LimbRef locate(const LimbMap& map, uint32_t li, const uint64_t* in, uint64_t* out,
-                                          uint64_t in_ps, uint64_t out_ps, uint32_t N) {
+// Transforms of limbs of 64-bit words, in place.  Between the two passes a limb is packed inside its own bytes
+// (in_place_offsets), 26 bytes moved per residue instead of 32.
+__device__ __forceinline__ uint64_t* locate(const LimbMap& map, uint32_t li, uint64_t* data, uint64_t ps, uint32_t N, uint32_t* mod_id) {
     const uint32_t poly = li / map.n, idx = li - poly * map.n;
-    const uint64_t off = (uint64_t)map.off[idx] * N;
-    return LimbRef{in + poly * in_ps + off, out + poly * out_ps + off, map.mod[idx], idx};
+    *mod_id = map.mod[idx];
+    return data + poly * ps + (uint64_t)map.off[idx] * N;
 }
 
-// forward, columns: canonical u64 in, raw doubles out (|x| <= (1 + 0.501 log2 R) p).
+// forward, columns: canonical words in, packed lazy representatives out (|x| <= (1 + 0.501 log2 R) p).
 template <int LOG_R, int TC>
 __global__ __launch_bounds__((TC << LOG_R) / 16) void ntt_fwd_cols(const double* __restrict__ tw, const Mod* __restrict__ mods, LimbMap map,
-                                                        const uint64_t* in, uint64_t* out, uint64_t in_ps, uint64_t out_ps) {
+                                                        uint64_t* data, uint64_t ps) {
     constexpr uint32_t N = 256u << LOG_R, TILES = 256 / TC;
     __shared__ double lds[LOG_R > 4 ? (TC << LOG_R) : 1];
-    const uint32_t tid = threadIdx.x;
-    const uint32_t li = blockIdx.x / TILES, tile = blockIdx.x - li * TILES;
-    const LimbRef L = locate(map, li, in, out, in_ps, out_ps, N);
-    const Mod m = mods[L.mod_id];
-    const double* W = tw + (size_t)L.mod_id * N;
+    const uint32_t tid = threadIdx.x, li = blockIdx.x / TILES, tile = blockIdx.x - li * TILES;
+    uint32_t mod_id;
+    uint64_t* limb = locate(map, li, data, ps, N, &mod_id);
+    const Mod m = mods[mod_id];
     const uint32_t c = tid & (TC - 1), r0 = tid / TC, col = tile * TC + c;
     double v[16];
     PassTwiddles t;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = u64_to_f64(L.in[col_row_strided<LOG_R>(r0, k) * 256 + col]);
-    load_col_twiddles<LOG_R>(t, W, r0);
+    for (int k = 0; k < 16; ++k) v[k] = u64_to_f64(limb[col_row_strided<LOG_R>(r0, k) * 256 + col]);
+    load_col_twiddles<LOG_R>(t, tw + (size_t)mod_id * N, r0);
     col_fwd_core<LOG_R, TC>(v, t, c, r0, lds, m);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) store_f64(L.out + col_row_grouped<LOG_R>(r0, k) * 256 + col, v[k]);
+    tile_loaded<LOG_R>(v);
+    in_place_store_cols<TC>(limb, r0, col, pack(v));
 }
 
-// forward, rows, in place: raw doubles in, canonical residues out.  One wavefront = four rows.
-template <int LOG_R>
+// forward, rows: packed in, canonical words out.  One wavefront = four rows.  TC: columns of a tile of the column pass.
+template <int LOG_R, int TC>
 __global__ __launch_bounds__(64) void ntt_fwd_rows(TwTables tw, const Mod* __restrict__ mods, LimbMap map, uint64_t* data, uint64_t ps) {
     constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R, GROUPS = R / 4;
     __shared__ double lds[4 * kRowPitch];
-    const uint32_t tid = threadIdx.x;
-    const uint32_t li = blockIdx.x / GROUPS, rg = blockIdx.x - li * GROUPS;
-    const uint32_t poly = li / map.n, idx = li - poly * map.n, mod_id = map.mod[idx];
+    const uint32_t lane = threadIdx.x, li = blockIdx.x / GROUPS, rg = blockIdx.x - li * GROUPS;
+    uint32_t mod_id;
+    uint64_t* limb = locate(map, li, data, ps, N, &mod_id);
     const Mod m = mods[mod_id];
-    const uint32_t j0 = tid & 15, rr = tid >> 4, row = rg * 4 + rr;
-    uint64_t* p = data + poly * ps + (uint64_t)map.off[idx] * N + row * 256;
+    const uint32_t j0 = lane & 15, rr = lane >> 4, row = rg * 4 + rr;
+    uint64_t* p = limb + row * 256 + j0;
+    double v[16];
+    PassTwiddles t;
+    const PackedRaw raw = in_place_load_rows<TC>(limb, rg, lane);
+    load_row_twiddles(t, tw, mod_id, N, R + row, j0, m);
+    unpack_rows(raw, v);
+    row_fwd_core(v, t, j0, lds + rr * kRowPitch, m);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) p[16 * k] = f64_to_u64(canon(reduce_lazy(v[k], m), m));
+}
+
+// inverse, rows first: canonical words in, packed lazy representatives out (|x| <= 0.501 p).
+template <int LOG_R, int TC>
+__global__ __launch_bounds__(64) void ntt_inv_rows(TwTables twi, const Mod* __restrict__ mods, LimbMap map, uint64_t* data, uint64_t ps) {
+    constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R, GROUPS = R / 4;
+    __shared__ double lds[4 * kRowPitch];
+    const uint32_t lane = threadIdx.x, li = blockIdx.x / GROUPS, rg = blockIdx.x - li * GROUPS;
+    uint32_t mod_id;
+    uint64_t* limb = locate(map, li, data, ps, N, &mod_id);
+    const Mod m = mods[mod_id];
+    const uint32_t j0 = lane & 15, rr = lane >> 4, row = rg * 4 + rr;
+    const uint64_t* p = limb + row * 256 + j0;
     double v[16];
     PassTwiddles t;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = load_f64(p + j0 + 16 * k);
-    load_row_twiddles(t, tw, mod_id, N, R + row, j0, m);
-    row_fwd_core(v, t, j0, lds + rr * kRowPitch, m);
+    for (int k = 0; k < 16; ++k) v[k] = u64_to_f64(p[16 * k]);
+    load_row_twiddles(t, twi, mod_id, N, R + row, j0, m);
+    row_inv_core(v, t, j0, lds + rr * kRowPitch, m);
+    in_place_store_rows<TC>(limb, rg, lane, pack_rows(v));
+}
+
+// inverse, columns last: packed in; out = canonical [x N^-1]_m in words.
+template <int LOG_R, int TC>
+__global__ __launch_bounds__((TC << LOG_R) / 16) void ntt_inv_cols(const double* __restrict__ twi, const Mod* __restrict__ mods,
+                                                        const double* __restrict__ ninv, LimbMap map, uint64_t* data, uint64_t ps) {
+    constexpr uint32_t N = 256u << LOG_R, TILES = 256 / TC;
+    __shared__ double lds[LOG_R > 4 ? (TC << LOG_R) : 1];
+    const uint32_t tid = threadIdx.x, li = blockIdx.x / TILES, tile = blockIdx.x - li * TILES;
+    uint32_t mod_id;
+    uint64_t* limb = locate(map, li, data, ps, N, &mod_id);
+    const Mod m = mods[mod_id];
+    const double scale = ninv[mod_id];
+    const uint32_t c = tid & (TC - 1), r0 = tid / TC, col = tile * TC + c;
+    double v[16];
+    PassTwiddles t;
+    const PackedRaw raw = in_place_load_cols<TC>(limb, r0, col);
+    load_col_twiddles<LOG_R>(t, twi + (size_t)mod_id * N, r0);
+    unpack(raw, v);
+    col_inv_core<LOG_R, TC>(v, t, c, r0, lds, m);
+    tile_loaded<LOG_R>(v);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) p[j0 + 16 * k] = f64_to_u64(canon(reduce_lazy(v[k], m), m));
+    for (int k = 0; k < 16; ++k) limb[col_row_strided<LOG_R>(r0, k) * 256 + col] = f64_to_u64(canon(mulmod_lazy(v[k], scale, m), m));
 }
 
 template <int W>
@@ -151,28 +187,6 @@ __global__ __launch_bounds__(64 * G) void gather_bundle_rows(TwTables tw, const 
             reinterpret_cast<HW*>(hi)[slot] = (HW)h;
         }
     }
-}
-
-// inverse, rows first, in place: canonical residues in, raw doubles out (|x| <= 0.501 p).
-template <int LOG_R>
-__global__ __launch_bounds__(64) void ntt_inv_rows(TwTables twi, const Mod* __restrict__ mods, LimbMap map, uint64_t* data, uint64_t ps) {
-    constexpr uint32_t N = 256u << LOG_R, GROUPS = (1u << LOG_R) / 4;
-    __shared__ double lds[4 * kRowPitch];
-    const uint32_t li = blockIdx.x / GROUPS, rg = blockIdx.x - li * GROUPS;
-    const uint32_t poly = li / map.n, idx = li - poly * map.n, mod_id = map.mod[idx];
-    uint64_t* limb = data + poly * ps + (uint64_t)map.off[idx] * N;
-    task_inv_rows<LOG_R, uint64_t>(twi, mods[mod_id], mod_id, limb, limb, rg, threadIdx.x, lds);
-}
-
-// inverse, columns last, in place: raw doubles in; out = canonical [x N^-1]_m.
-template <int LOG_R, int TC>
-__global__ __launch_bounds__((TC << LOG_R) / 16) void ntt_inv_cols(const double* __restrict__ twi, const Mod* __restrict__ mods,
-                                                        const double* __restrict__ ninv, LimbMap map, uint64_t* data, uint64_t ps) {
-    constexpr uint32_t N = 256u << LOG_R, TILES = 256 / TC;
-    __shared__ double lds[LOG_R > 4 ? (TC << LOG_R) : 1];
-    const uint32_t li = blockIdx.x / TILES, tile = blockIdx.x - li * TILES;
-    const LimbRef L = locate(map, li, data, data, ps, ps, N);
-    task_inv_cols<LOG_R, TC>(twi + (size_t)L.mod_id * N, mods[L.mod_id], ninv[L.mod_id], L.out, tile, threadIdx.x, lds);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -301,34 +315,6 @@ __global__ __launch_bounds__((TC << LOG_R) / 16) void ntt_inv_cols_u32(const dou
 // small launches keep the 16-column tiles.
 static bool wide_tiles(uint32_t limbs) { return limbs >= 256; }
 
-void launch_ntt_fwd_cols(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipStream_t s) {
-    const uint32_t limbs = map.n * io.n_polys;
-    if (limbs == 0) return;
-    const uint64_t* in = static_cast<const uint64_t*>(io.in);
-    uint64_t* out = static_cast<uint64_t*>(io.out);
-    ProfScope ps("ntt_fwd_cols", 2.0 * limbs * c->N * 8.0, s);
-    if (c->logN == 16 && wide_tiles(limbs)) {
-        hipLaunchKernelGGL((ntt_fwd_cols<8, 32>), dim3(limbs * 8), dim3(512), 0, s, c->d_tw_fwd, c->d_mod, map, in, out,
-                           io.in_poly_stride, io.out_poly_stride);
-        return;
-    }
-#define KS_LAUNCH(LOGR)                                                                                                          \
-    hipLaunchKernelGGL((ntt_fwd_cols<LOGR, (4096 >> LOGR)>), dim3(limbs << (LOGR - 4)), dim3(256), 0, s, c->d_tw_fwd, c->d_mod, map, in, \
-                       out, io.in_poly_stride, io.out_poly_stride)
-    KS_FOR_LOG_R(c->logN, KS_LAUNCH)
-#undef KS_LAUNCH
-}
-
-void launch_ntt_fwd_rows(const ks_ctx* c, const LimbMap& map, uint64_t* data, uint64_t ps_words, uint32_t n_polys, hipStream_t s) {
-    const uint32_t limbs = map.n * n_polys;
-    if (limbs == 0) return;
-    ProfScope ps("ntt_fwd_rows", 2.0 * limbs * c->N * 8.0, s);
-#define KS_LAUNCH(LOGR) \
-    hipLaunchKernelGGL((ntt_fwd_rows<LOGR>), dim3(limbs << (LOGR - 2)), dim3(64), 0, s, c->tw_fwd, c->d_mod, map, data, ps_words)
-    KS_FOR_LOG_R(c->logN, KS_LAUNCH)
-#undef KS_LAUNCH
-}
-
 void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint8_t* lifted, const void* d, const void* c0, uint64_t ps_words,
                                const GatherBundle& out, bool raised, hipStream_t s) {
     const uint32_t n_new = raised ? lv.lifted_map.n : 0, n_copy = c0 ? 2 * lv.ell : lv.ell;
@@ -368,35 +354,33 @@ static uint32_t polys_per_group(const ks_ctx* c, const LimbMap& map) {
     return (uint32_t)std::max<uint64_t>(1, kGroupBytes / poly_bytes);
 }
 
-void launch_ntt_fwd(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipStream_t s) {
+void launch_ntt(const ks_ctx* c, const LimbMap& map, uint64_t* data, uint64_t ps_words, uint32_t n_polys, bool inverse, hipStream_t s) {
     const uint32_t g = polys_per_group(c, map);
-    for (uint32_t p0 = 0; p0 < io.n_polys; p0 += g) {
-        const uint32_t np = std::min(g, io.n_polys - p0);
-        XformIO part{static_cast<const uint64_t*>(io.in) + (uint64_t)p0 * io.in_poly_stride,
-                     static_cast<uint64_t*>(io.out) + (uint64_t)p0 * io.out_poly_stride, io.in_poly_stride, io.out_poly_stride, np};
-        launch_ntt_fwd_cols(c, map, part, s);
-        launch_ntt_fwd_rows(c, map, static_cast<uint64_t*>(part.out), io.out_poly_stride, np, s);
-    }
-}
-
-void launch_ntt_inv(const ks_ctx* c, const LimbMap& map, const XformIO& io, hipStream_t s) {
-    const uint32_t g = polys_per_group(c, map);
-    for (uint32_t p0 = 0; p0 < io.n_polys; p0 += g) {
-        const uint32_t limbs = map.n * std::min(g, io.n_polys - p0);
-        uint64_t* data = static_cast<uint64_t*>(io.out) + (uint64_t)p0 * io.out_poly_stride;
-        {
-            ProfScope ps("ntt_inv_rows", 2.0 * limbs * c->N * 8.0, s);
-#define KS_LAUNCH(LOGR) \
-    hipLaunchKernelGGL((ntt_inv_rows<LOGR>), dim3(limbs << (LOGR - 2)), dim3(64), 0, s, c->tw_inv, c->d_mod, map, data, io.out_poly_stride)
-            KS_FOR_LOG_R(c->logN, KS_LAUNCH)
-#undef KS_LAUNCH
-        }
-        ProfScope ps("ntt_inv_cols", 2.0 * limbs * c->N * 8.0, s);
+    for (uint32_t p0 = 0; p0 < n_polys; p0 += g) {
+        const uint32_t limbs = map.n * std::min(g, n_polys - p0);
+        uint64_t* part = data + (uint64_t)p0 * ps_words;
+        const double bytes = 13.0 * limbs * c->N;
 #define KS_LAUNCH_TC(LOGR, TCV)                                                                                                       \
-    hipLaunchKernelGGL((ntt_inv_cols<LOGR, TCV>), dim3(limbs * (256 / TCV)), dim3((TCV << LOGR) / 16), 0, s, c->d_tw_inv, c->d_mod, c->d_ninv, \
-                       map, data, io.out_poly_stride)
+    {                                                                                                                                 \
+        const dim3 cols(limbs * (256 / TCV)), cols_block((TCV << LOGR) / 16), rows(limbs << (LOGR - 2)), rows_block(64);              \
+        if (!inverse) {                                                                                                               \
+            {                                                                                                                         \
+                ProfScope ps("ntt_fwd_cols", bytes, s);                                                                               \
+                hipLaunchKernelGGL((ntt_fwd_cols<LOGR, TCV>), cols, cols_block, 0, s, c->d_tw_fwd, c->d_mod, map, part, ps_words);    \
+            }                                                                                                                         \
+            ProfScope ps("ntt_fwd_rows", bytes, s);                                                                                   \
+            hipLaunchKernelGGL((ntt_fwd_rows<LOGR, TCV>), rows, rows_block, 0, s, c->tw_fwd, c->d_mod, map, part, ps_words);          \
+        } else {                                                                                                                      \
+            {                                                                                                                         \
+                ProfScope ps("ntt_inv_rows", bytes, s);                                                                               \
+                hipLaunchKernelGGL((ntt_inv_rows<LOGR, TCV>), rows, rows_block, 0, s, c->tw_inv, c->d_mod, map, part, ps_words);      \
+            }                                                                                                                         \
+            ProfScope ps("ntt_inv_cols", bytes, s);                                                                                   \
+            hipLaunchKernelGGL((ntt_inv_cols<LOGR, TCV>), cols, cols_block, 0, s, c->d_tw_inv, c->d_mod, c->d_ninv, map, part, ps_words); \
+        }                                                                                                                             \
+    }
 #define KS_LAUNCH(LOGR) KS_LAUNCH_TC(LOGR, (4096 >> LOGR))
-        if (c->logN == 16 && wide_tiles(limbs)) KS_LAUNCH_TC(8, 32);
+        if (c->logN == 16 && wide_tiles(limbs)) KS_LAUNCH_TC(8, 32)
         else KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
 #undef KS_LAUNCH_TC

@@ -11,23 +11,6 @@ namespace ks {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-// ---- inverse transform, row half: canonical residues in (64- or 32-bit words), raw doubles out (|x| <= 0.501 p) ----
-// ip / op: the limb's first element; rg: group of four rows; lds_wave: 4 * kRowPitch doubles.
-template <int LOG_R, typename W>
-__device__ __forceinline__ void task_inv_rows(const TwTables& twi, Mod m, uint32_t mod_id, const W* ip,
-                                              uint64_t* op, uint32_t rg, uint32_t lane, double* lds_wave) {
-    constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R;
-    const uint32_t j0 = lane & 15, rr = lane >> 4, row = rg * 4 + rr;
-    double v[16];
-    PassTwiddles t;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = word_to_f64<W>(ip[row * 256 + j0 + 16 * k]);
-    load_row_twiddles(t, twi, mod_id, N, R + row, j0, m);
-    row_inv_core(v, t, j0, lds_wave + rr * kRowPitch, m);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) store_f64(op + row * 256 + j0 + 16 * k, v[k]);
-}
-
 // ---- inverse transform, row half, for a conversion: canonical residues (W words) or a packed limb of accumulators (uint8_t) in,
 // a packed limb in columns order out (in place where the input is packed).
 template <int LOG_R, typename W>
@@ -88,24 +71,7 @@ __device__ __forceinline__ void task_tensor_inv_rows(const TwTables& twi, Mod m,
     packed_store<64>(inv, N, at, pack_rows(v));
 }
 
-// ---- inverse transform, column half, in place: raw doubles in, canonical [x * scale]_m out ------------------------------
-// Wi: the modulus's inverse twiddle table; tile: TC columns; tid < TC * R / 16; lds: TC * R doubles.
-template <int LOG_R, int TC>
-__device__ __forceinline__ void task_inv_cols(const double* __restrict__ Wi, Mod m, double scale, uint64_t* data, uint32_t tile, uint32_t tid,
-                                              double* lds) {
-    const uint32_t c = tid & (TC - 1), r0 = tid / TC, col = tile * TC + c;
-    double v[16];
-    PassTwiddles t;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = load_f64(data + col_row_grouped<LOG_R>(r0, k) * 256 + col);
-    load_col_twiddles<LOG_R>(t, Wi, r0);
-    col_inv_core<LOG_R, TC>(v, t, c, r0, lds, m);
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-        data[col_row_strided<LOG_R>(r0, k) * 256 + col] = f64_to_u64(canon(mulmod_lazy(v[k], scale, m), m));
-}
-
-// ---- the same for a conversion: a packed limb in columns order in, the sources of the conversion out, in place ----------
+// ---- inverse transform, column half, for a conversion: a packed limb in columns order in, the sources of the conversion out, in place ----------
 template <int LOG_R>
 __device__ __forceinline__ void task_inv_cols_packed(const double* __restrict__ Wi, Mod m, double scale, uint8_t* limb, uint32_t tile,
                                                      uint32_t tid, double* lds) {
@@ -117,12 +83,7 @@ __device__ __forceinline__ void task_inv_cols_packed(const double* __restrict__ 
     load_col_twiddles<LOG_R>(t, Wi, r0);
     unpack(raw, v);
     col_inv_core<LOG_R, TC>(v, t, c, r0, lds, m);
-    if constexpr (LOG_R == 4) {
-        // no exchange through LDS above: every byte of the tile has to be read before the bytes of other threads are overwritten
-#pragma unroll
-        for (int k = 0; k < 16; ++k) asm volatile("" : "+v"(v[k]));
-        __syncthreads();
-    }
+    tile_loaded<LOG_R>(v);
 #pragma unroll
     for (int k = 0; k < 16; ++k) v[k] = canon(mulmod_lazy(v[k], scale, m), m);
     const PackedRaw o = pack(v, kDigitBias);

@@ -32,8 +32,6 @@ __device__ __forceinline__ uint32_t galois_source_slot(uint32_t n, uint32_t g, u
 
 constexpr int kRowPitch = 272;  // 256 points + 1 pad per 16: the transposed LDS accesses hit distinct banks
 
-__device__ __forceinline__ double load_f64(const uint64_t* p) { return *reinterpret_cast<const double*>(p); }
-__device__ __forceinline__ void store_f64(uint64_t* p, double v) { *reinterpret_cast<double*>(p) = v; }
 
 // Twiddles of the two register passes of a tile core, loaded ahead of the butterflies.
 struct PassTwiddles {
@@ -277,6 +275,77 @@ __device__ __forceinline__ void packed_store(uint8_t* limb, uint32_t N, uint32_t
 #pragma unroll
     for (int i = 0; i < 4; ++i) hi[i * STEP] = r.hi[i];
 }
+// Columns order inside a limb of 64-bit words, for transforms in place: a tile of TC columns keeps to the bytes of its own columns.  Of
+// the four rows of a group the low words take the first two, 16 bytes a column, and the bytes above half of the third.
+struct InPlaceOffsets {
+    uint32_t lo, hi;
+};
+template <int TC>
+__device__ __forceinline__ InPlaceOffsets in_place_offsets(uint32_t col) {
+    const uint32_t c = col % TC, tile = (col - c) * 8;
+    return InPlaceOffsets{c / (TC / 2) * 2048 + tile + c % (TC / 2) * 16, 4096 + tile + c * 4};
+}
+constexpr uint32_t kQuadBytes = 8192;   // four rows of 256 words
+// rows: lane of group rg; columns: group q of thread (r0, column)
+template <int TC>
+__device__ __forceinline__ PackedRaw in_place_load_rows(const uint64_t* limb, uint32_t rg, uint32_t lane) {
+    const uint8_t* group = reinterpret_cast<const uint8_t*>(limb) + rg * kQuadBytes;
+    PackedRaw r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const InPlaceOffsets o = in_place_offsets<TC>(64 * i + lane);
+        const Words4 w = *reinterpret_cast<const Words4*>(group + o.lo);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) r.lo[4 * i + x] = w.w[x];
+        r.hi[i] = *reinterpret_cast<const uint32_t*>(group + o.hi);
+    }
+    return r;
+}
+template <int TC>
+__device__ __forceinline__ void in_place_store_rows(uint64_t* limb, uint32_t rg, uint32_t lane, const PackedRaw& r) {
+    uint8_t* group = reinterpret_cast<uint8_t*>(limb) + rg * kQuadBytes;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const InPlaceOffsets o = in_place_offsets<TC>(64 * i + lane);
+        *reinterpret_cast<Words4*>(group + o.lo) = Words4{{r.lo[4 * i], r.lo[4 * i + 1], r.lo[4 * i + 2], r.lo[4 * i + 3]}};
+        *reinterpret_cast<uint32_t*>(group + o.hi) = r.hi[i];
+    }
+}
+template <int TC>
+__device__ __forceinline__ PackedRaw in_place_load_cols(const uint64_t* limb, uint32_t r0, uint32_t col) {
+    const InPlaceOffsets o = in_place_offsets<TC>(col);
+    const uint8_t* group = reinterpret_cast<const uint8_t*>(limb) + r0 * (4 * kQuadBytes);
+    PackedRaw r;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const Words4 w = *reinterpret_cast<const Words4*>(group + q * kQuadBytes + o.lo);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) r.lo[4 * q + x] = w.w[x];
+        r.hi[q] = *reinterpret_cast<const uint32_t*>(group + q * kQuadBytes + o.hi);
+    }
+    return r;
+}
+template <int TC>
+__device__ __forceinline__ void in_place_store_cols(uint64_t* limb, uint32_t r0, uint32_t col, const PackedRaw& r) {
+    const InPlaceOffsets o = in_place_offsets<TC>(col);
+    uint8_t* group = reinterpret_cast<uint8_t*>(limb) + r0 * (4 * kQuadBytes);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        *reinterpret_cast<Words4*>(group + q * kQuadBytes + o.lo) = Words4{{r.lo[4 * q], r.lo[4 * q + 1], r.lo[4 * q + 2], r.lo[4 * q + 3]}};
+        *reinterpret_cast<uint32_t*>(group + q * kQuadBytes + o.hi) = r.hi[q];
+    }
+}
+// N = 2^12 has no exchange through LDS between a column tile's loads and its stores: everything has arrived before anything is
+// overwritten.
+template <int LOG_R>
+__device__ __forceinline__ void tile_loaded(double (&v)[16]) {
+    if constexpr (LOG_R == 4) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) asm volatile("" : "+v"(v[k]));
+        __syncthreads();
+    }
+}
+
 // Kernels with one thread per slot: 64 consecutive slots are 64 consecutive elements in the rows -> rows order, permuted.
 __device__ __forceinline__ uint32_t packed_element(uint32_t n) {
     return (n & ~1023u) | (n & 192u) << 2 | (n & 768u) >> 2 | (n & 15u) << 2 | ((n >> 4) & 3u);
