@@ -27,10 +27,10 @@ namespace ks {
 // matrix instructions of all 16 positions (256 result registers) and the kernel drops to one wavefront per SIMD.
 constexpr int mfma_min_blocks(int tl) { return tl == 1 ? 4 : 2; }
 
-template <int LOG_R, int TL, int NM, int NPS, int WAVES>
+template <int LOG_R, int TL, int T, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? mfma_min_blocks(TL) : 1) void bconv_mfma_ntt_cols(const double* __restrict__ tw, const BConvPlan* __restrict__ plans,
                                                            LaunchMeta meta, const uint8_t* __restrict__ y, uint64_t y_ps,
-                                                           uint8_t* __restrict__ out, uint64_t out_ps, uint32_t n_subsets, uint32_t pair) {
+                                                           uint8_t* __restrict__ out, uint64_t out_ps, uint32_t n_polys, uint32_t n_subsets, uint32_t pair) {
     using Shape = MfmaConvShape<LOG_R, TL, WAVES>;
     __shared__ double lds[Shape::LDS_WORDS];
     __shared__ double lds_tw[Shape::LDS_TW_WORDS];
@@ -44,8 +44,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? mfma_min_blocks(TL) : 1) v
     // ciphertexts, L = 35: 438 -> 386 us of conversions).  Not where one round holds the whole launch: there the second fetch is
     // served by the memory-side cache and pairing cost the single-ciphertext key-switch 1.3 % (106.2 -> 107.6 us).
     if (Shape::TC == 8 && pair) tile = (tile & ~15u) | ((tile & 7u) << 1) | ((tile >> 3) & 1u);
-    task_bconv_mfma_cols<LOG_R, TL, NM, NPS, WAVES>(tw, plans[plan_id], PM, y + (uint64_t)blockIdx.z * y_ps, y_ps,
-                                             out + (uint64_t)blockIdx.z * out_ps, tile, t0, threadIdx.x, lds, lds_tw);
+    task_bconv_mfma_cols<LOG_R, TL, T, WAVES>(tw, plans[plan_id], PM, y, y_ps, out, out_ps, blockIdx.z, gridDim.z, n_polys, tile, t0,
+                                                    threadIdx.x, lds, lds_tw);
 }
 
 // Targets per lane half: one gives the most workgroups, three shares the byte-cutting of the sources among the most
@@ -55,22 +55,41 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
                                 uint64_t out_ps, uint32_t n_polys, int tl, bool wide, hipStream_t s) {
     const uint32_t n_src = plans.shape_src, n_plans = plans.n_plans, max_targets = plans.max_targets;
     const BConvPlan* d_plans = plans.d_plans;
-    const uint32_t nm = (n_src + 5) / 6, nps = (n_src + 2 * nm - 1) / (2 * nm);
+    const uint32_t t = mfma_sources(n_src);
     tl = (c->logN == 13 || c->logN == 14) || tl < 2 ? 1 : 3;  // built shapes: one or three targets per lane half
     const int waves = wide && c->logN == 16 && tl == 3 && n_src > 4 ? 8 : 4;
     const uint32_t tiles = c->N / (512 * waves);
     const uint32_t n_subsets = (max_targets + 2 * tl - 1) / (2 * tl);
-    const dim3 grid(tiles, n_plans * n_subsets, n_polys), block(64 * waves);
-#define KS_LAUNCH_MFMA(LOGR, TLV, NMV, NPSV, WV)                                                                                        \
-    hipLaunchKernelGGL((bconv_mfma_ntt_cols<LOGR, TLV, NMV, NPSV, WV>), grid, block, 0, s, c->d_tw_fwd, d_plans, plans.meta, y, y_ps, \
-                       out, out_ps, n_subsets, grid.x * grid.y * grid.z > 512)
-#define KS_MFMA_SHAPE(LOGR, TLV)                                       \
-    if (nm == 1 && nps == 1) KS_LAUNCH_MFMA(LOGR, TLV, 1, 1, 4);       \
-    else if (nm == 1 && nps == 2) KS_LAUNCH_MFMA(LOGR, TLV, 1, 2, 4);  \
-    else if (nm == 1) KS_LAUNCH_MFMA(LOGR, TLV, 1, 3, 4);              \
-    else if (nm == 2 && nps == 2) KS_LAUNCH_MFMA(LOGR, TLV, 2, 2, 4);  \
-    else if (nm == 2) KS_LAUNCH_MFMA(LOGR, TLV, 2, 3, 4);              \
-    else KS_LAUNCH_MFMA(LOGR, TLV, 3, 3, 4)
+    // Polynomials that a workgroup takes in turn, up to eight: each round of workgroups (one or two per compute unit) takes about as
+    // long as another, and a polynomial after
+    // the first an eighth less (its sources arrive under the butterflies of the one before; factors and twiddles are there): four hoisted
+    // rotations of eight ciphertexts, 64 polynomials 8 -> 24, 269 -> 241 us; 16 polynomials 90 -> 84; 13 -> 34, which pays for the loop with
+    // scratch registers, 136 -> 133.
+    const uint32_t slots = waves == 8 ? 256 : 512, per_poly = tiles * n_plans * n_subsets;
+    uint32_t groups = n_polys;
+    double least = 1e30;
+    for (uint32_t z = (n_polys + 7) / 8; z <= n_polys; ++z) {
+        const uint32_t items = (n_polys + z - 1) / z;
+        const double rounds = (double)(((uint64_t)per_poly * z + slots - 1) / slots), cost = rounds * (1.0 + 0.88 * (items - 1));
+        if (cost < least) {
+            least = cost;
+            groups = z;
+        }
+    }
+    const dim3 grid(tiles, n_plans * n_subsets, groups), block(64 * waves);
+#define KS_LAUNCH_MFMA(LOGR, TLV, TV, WV)                                                                                            \
+    hipLaunchKernelGGL((bconv_mfma_ntt_cols<LOGR, TLV, TV, WV>), grid, block, 0, s, c->d_tw_fwd, d_plans, plans.meta, y, y_ps, \
+                       out, out_ps, n_polys, n_subsets, tiles * n_plans * n_subsets * n_polys > 512)
+#define KS_MFMA_SHAPE(LOGR, TLV)                           \
+    switch (t) {                                           \
+        case 1: KS_LAUNCH_MFMA(LOGR, TLV, 1, 4); break;    \
+        case 2: KS_LAUNCH_MFMA(LOGR, TLV, 2, 4); break;    \
+        case 3: KS_LAUNCH_MFMA(LOGR, TLV, 3, 4); break;    \
+        case 4: KS_LAUNCH_MFMA(LOGR, TLV, 4, 4); break;    \
+        case 6: KS_LAUNCH_MFMA(LOGR, TLV, 6, 4); break;    \
+        case 7: KS_LAUNCH_MFMA(LOGR, TLV, 7, 4); break;    \
+        default: KS_LAUNCH_MFMA(LOGR, TLV, 9, 4); break;   \
+    }
 #define KS_LAUNCH_TL(LOGR)                       \
     {                                            \
         if (tl == 1) { KS_MFMA_SHAPE(LOGR, 1); } \
@@ -85,10 +104,11 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
         case 15: KS_LAUNCH_TL(7) break;
         default:
             if (waves == 4) KS_LAUNCH_TL(8)
-            else if (nm == 1) KS_LAUNCH_MFMA(8, 3, 1, 3, 8);
-            else if (nm == 2 && nps == 2) KS_LAUNCH_MFMA(8, 3, 2, 2, 8);
-            else if (nm == 2) KS_LAUNCH_MFMA(8, 3, 2, 3, 8);
-            else KS_LAUNCH_MFMA(8, 3, 3, 3, 8);
+            else if (t == 3) KS_LAUNCH_MFMA(8, 3, 3, 8);
+            else if (t == 4) KS_LAUNCH_MFMA(8, 3, 4, 8);
+            else if (t == 6) KS_LAUNCH_MFMA(8, 3, 6, 8);
+            else if (t == 7) KS_LAUNCH_MFMA(8, 3, 7, 8);
+            else KS_LAUNCH_MFMA(8, 3, 9, 8);
             break;
     }
 #undef KS_LAUNCH_TL
@@ -107,10 +127,11 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
 // 24 polynomials, 12 -> 35 moduli, N = 2^16: 118 us = 5.0 TB/s (64: 5.4), where fp64 accumulation of 12-bit pieces took
 // 187; in 32-bit words 76 against 162; calls of one polynomial, 8 -> 24: 11.9 against 18.6.  Few sources: ks_bconv.hip.
 // ------------------------------------------------------------------------------------------------
-template <int NM, int NPS, int PG, typename W>
+template <int T, int PG, typename W>
 __global__ __launch_bounds__(256) void bconv_mfma_kernel(const BConvPlan* __restrict__ plans, LaunchMeta meta,
                                                          const W* __restrict__ in, uint64_t in_ps,
                                                          W* __restrict__ out, uint64_t out_ps, uint32_t N) {
+    constexpr int NM = mfma_instructions(T);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, h = lane >> 5;
     constexpr int V = PG * (int)sizeof(W) <= 16 ? PG : 16 / (int)sizeof(W);
     struct alignas(V * sizeof(W)) Vec {
@@ -121,24 +142,22 @@ __global__ __launch_bounds__(256) void bconv_mfma_kernel(const BConvPlan* __rest
     const int n_dst = (int)meta.plan[blockIdx.y].n_dst, n_src = (int)P.n_src;
     const W* ip = in + (uint64_t)blockIdx.z * in_ps + n;
     W* op = out + (uint64_t)blockIdx.z * out_ps + n;
-    W xraw[PG][NM][NPS];
-    Mod mi[NM][NPS];
-    double inv[NM][NPS];
+    W xraw[PG][T];
+    Mod mi[T];
+    double inv[T];
 #pragma unroll
-    for (int m = 0; m < NM; ++m)
+    for (int e = 0; e < T; ++e) {
+        const int i = min(2 * e + (int)h, n_src - 1);  // places past the last source repeat it against zero factors
+        const W* src = ip + (uint64_t)P.src_limb[i] * N;
 #pragma unroll
-        for (int e = 0; e < NPS; ++e) {
-            const int i = min((int)((2 * m + h) * NPS + e), n_src - 1);  // slots past the last source repeat it against zero factors
-            const W* src = ip + (uint64_t)P.src_limb[i] * N;
+        for (int g = 0; g < PG; g += V) {
+            const Vec v = *reinterpret_cast<const Vec*>(src + 32 * g);
 #pragma unroll
-            for (int g = 0; g < PG; g += V) {
-                const Vec v = *reinterpret_cast<const Vec*>(src + 32 * g);
-#pragma unroll
-                for (int k = 0; k < V; ++k) xraw[g + k][m][e] = v.w[k];
-            }
-            mi[m][e] = P.src_mod[i];
-            inv[m][e] = P.src_inv[i];
+            for (int k = 0; k < V; ++k) xraw[g + k][e] = v.w[k];
         }
+        mi[e] = P.src_mod[i];
+        inv[e] = P.src_inv[i];
+    }
     // row r of the factor matrix: result register 4 (r / 8) + r % 4 of lane half (r / 4) % 2, i.e. digit plane b of that
     // half's target ua
     const uint32_t r = lane & 31u, hp = (r >> 2) & 1u, j = 4 * (r >> 3) + (r & 3u), ua = min(j / 5, 2u), b = min(j - 5 * ua, 4u);
@@ -160,8 +179,9 @@ __global__ __launch_bounds__(256) void bconv_mfma_kernel(const BConvPlan* __rest
             bq[g][m] = v4i{0, 0, 0, 0};
             uint32_t top = 0;
 #pragma unroll
-            for (int e = 0; e < NPS; ++e) {
-                const double yi = canon(mulmod_lazy(word_to_f64<W>(xraw[g][m][e]), inv[m][e], mi[m][e]), mi[m][e]);
+            for (int e = 0; e < mfma_slot_sources(T, m); ++e) {
+                const int i = mfma_slot_start(T, m) + e;
+                const double yi = canon(mulmod_lazy(word_to_f64<W>(xraw[g][i]), inv[i], mi[i]), mi[i]);
                 const uint64_t bits = __builtin_bit_cast(uint64_t, yi + kDigitBias);
                 bq[g][m][e] = (int)((uint32_t)bits ^ 0x80808080u);
                 top |= ((uint32_t)(bits >> 32) & 0xFFu) << (8 * e);
@@ -210,31 +230,32 @@ __global__ __launch_bounds__(256) void bconv_mfma_kernel(const BConvPlan* __rest
 void launch_bconv_mfma(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const void* in, uint64_t in_ps,
                        void* out, uint64_t out_ps, uint32_t n_polys, hipStream_t s, bool words32) {
     if (n_polys == 0 || plans.n_plans == 0) return;
-    const uint32_t n_src = plans.shape_src, nm = (n_src + 5) / 6, nps = (n_src + 2 * nm - 1) / (2 * nm);
+    const uint32_t t = mfma_sources(plans.shape_src);
     // position groups per wavefront: more of them share the factor loads of a step and widen the accesses, as long as the
     // launch still fills the chip (256 compute units) a few times over
     const uint64_t tiles = (uint64_t)n_polys * plans.n_plans * (c->N / 128);
     const int pg = tiles / 4 >= 1024 ? 4 : tiles / 2 >= 512 ? 2 : 1;
     const dim3 grid(c->N / (128 * pg), plans.n_plans, n_polys), block(256);
     ProfScope ps("bconv_mfma", (double)limbs_moved_per_poly * n_polys * c->N * (words32 ? 4.0 : 8.0), s);
-#define KS_LAUNCH_BM_W(NMV, NPSV, PGV, WT)                                                                                                  \
-    hipLaunchKernelGGL((bconv_mfma_kernel<NMV, NPSV, PGV, WT>), grid, block, 0, s, plans.d_plans, plans.meta, static_cast<const WT*>(in), in_ps, \
+#define KS_LAUNCH_BM_W(TV, PGV, WT)                                                                                                  \
+    hipLaunchKernelGGL((bconv_mfma_kernel<TV, PGV, WT>), grid, block, 0, s, plans.d_plans, plans.meta, static_cast<const WT*>(in), in_ps, \
                        static_cast<WT*>(out), out_ps, c->N)
-#define KS_LAUNCH_BM_PG(NMV, NPSV, WT)                        \
-    if (pg == 4) KS_LAUNCH_BM_W(NMV, NPSV, 4, WT);            \
-    else if (pg == 2) KS_LAUNCH_BM_W(NMV, NPSV, 2, WT);       \
-    else KS_LAUNCH_BM_W(NMV, NPSV, 1, WT)
-#define KS_LAUNCH_BM(NMV, NPSV)                                       \
+#define KS_LAUNCH_BM_PG(TV, WT)                        \
+    if (pg == 4) KS_LAUNCH_BM_W(TV, 4, WT);            \
+    else if (pg == 2) KS_LAUNCH_BM_W(TV, 2, WT);       \
+    else KS_LAUNCH_BM_W(TV, 1, WT)
+#define KS_LAUNCH_BM(TV)                                       \
     {                                                                 \
-        if (words32) { KS_LAUNCH_BM_PG(NMV, NPSV, uint32_t); }        \
-        else { KS_LAUNCH_BM_PG(NMV, NPSV, uint64_t); }                \
+        if (words32) { KS_LAUNCH_BM_PG(TV, uint32_t); }        \
+        else { KS_LAUNCH_BM_PG(TV, uint64_t); }                \
     }
-    if (nm == 1 && nps == 1) KS_LAUNCH_BM(1, 1)
-    else if (nm == 1 && nps == 2) KS_LAUNCH_BM(1, 2)
-    else if (nm == 1) KS_LAUNCH_BM(1, 3)
-    else if (nm == 2 && nps == 2) KS_LAUNCH_BM(2, 2)
-    else if (nm == 2) KS_LAUNCH_BM(2, 3)
-    else KS_LAUNCH_BM(3, 3)
+    if (t == 1) KS_LAUNCH_BM(1)
+    else if (t == 2) KS_LAUNCH_BM(2)
+    else if (t == 3) KS_LAUNCH_BM(3)
+    else if (t == 4) KS_LAUNCH_BM(4)
+    else if (t == 6) KS_LAUNCH_BM(6)
+    else if (t == 7) KS_LAUNCH_BM(7)
+    else KS_LAUNCH_BM(9)
 #undef KS_LAUNCH_BM
 #undef KS_LAUNCH_BM_PG
 #undef KS_LAUNCH_BM_W

@@ -82,9 +82,11 @@ void fill_bconv_plan(const ks_ctx* c, BConvPlan* plan, const uint32_t* src_ids, 
     if (shape_src < n_src) shape_src = n_src;
     plan->n_src = n_src;
     plan->n_dst = n_dst;
-    plan->mfma_nm = (shape_src + 5) / 6;
-    plan->mfma_nps = (shape_src + 2 * plan->mfma_nm - 1) / (2 * plan->mfma_nm);
-    for (uint32_t k = 0; k < (uint32_t)kMfmaSlots * 3; ++k) plan->mfma_src_limb[k] = src_limb[k < n_src ? k : 0];
+    plan->mfma_t = mfma_sources(shape_src);
+    for (uint32_t k = 0; k < (uint32_t)kMfmaSlots * 3; ++k) {
+        const int t = (int)plan->mfma_t, h = k / 3 % 2, m = k / 6, e = k % 3, i = 2 * (mfma_slot_start(t, m) + e) + h;   // source e of slot 2 m + h
+        plan->mfma_src_limb[k] = src_limb[m < mfma_instructions(t) && e < mfma_slot_sources(t, m) && i < (int)n_src ? i : 0];
+    }
     for (uint32_t i = 0; i < n_src; ++i) {
         const uint64_t si = c->mod[src_ids[i]];
         uint64_t prod = 1;
@@ -121,7 +123,8 @@ void fill_bconv_plan(const ks_ctx* c, BConvPlan* plan, const uint32_t* src_ids, 
             }
             start = (start + h_mulmod(prod, 0x80808080ull % mt, mt)) % mt;
             // matrix-core operand rows: digit b of centred([(D / s_i) 256^a]_t), at the byte that pairs with digit a of source i
-            const uint32_t slot = i / plan->mfma_nps, e = i % plan->mfma_nps;
+            const int t_half = (int)plan->mfma_t, of_half = (int)i / 2, m = mfma_slot_of(t_half, of_half);
+            const int slot = 2 * m + (int)i % 2, e = of_half - mfma_slot_start(t_half, m);
             for (int a = 0; a < kMfmaPlanes; ++a) {
                 const uint64_t f = h_mulmod(prod, (1ull << (8 * a)) % mt, mt);
                 int64_t v = f > mt / 2 ? -(int64_t)(mt - f) : (int64_t)f;

@@ -17,6 +17,13 @@ namespace ks {
 constexpr int kMaxLimbsIn = 16; // source limbs a caller may ask for (alpha, K, bconv)
 constexpr int kMaxSrc = 18;     // source slots of a conversion plan: kMaxLimbsIn, the dropped limb of a rescale, one of padding
 constexpr int kMfmaSlots = 6;   // 16-byte operand slots of the matrix-core conversion: 3 instructions x 2 lane halves, 3 sources each
+// Sources per lane half of the matrix-core conversion, of those it is built for; instructions per position; sources of instruction m and
+// the first of them (dealt evenly).
+constexpr uint32_t mfma_sources(uint32_t n_src) { return n_src <= 8 ? (n_src + 1) / 2 : n_src <= 12 ? 6 : n_src <= 14 ? 7 : 9; }
+constexpr int mfma_instructions(int t) { return (t + 2) / 3; }
+constexpr int mfma_slot_sources(int t, int m) { return (t + mfma_instructions(t) - 1 - m) / mfma_instructions(t); }
+constexpr int mfma_slot_start(int t, int m) { return m == 0 ? 0 : mfma_slot_start(t, m - 1) + mfma_slot_sources(t, m - 1); }
+constexpr int mfma_slot_of(int t, int e) { return e < mfma_slot_sources(t, 0) ? 0 : e < mfma_slot_start(t, 2) ? 1 : 2; }
 constexpr int kMfmaPlanes = 5;  // signed base-256 digits of a 36-bit residue or factor
 constexpr int kMaxDst = 256;    // target limbs of one base conversion
 constexpr int kMaxLimbs = 192;  // limbs of one polynomial bundle addressed by a LimbMap
@@ -52,11 +59,11 @@ struct BConvPlan {
     // digits; for every digit position a the factor F_a = centred([(D / s_i) 256^a]_t) is cut the same way into digits
     // e_b, so that y (D / s_i) = sum_b 256^b sum_a d_a e_{a,b} (mod t): five small integer sums per target, each a dot
     // product over (source, a) that the matrix cores accumulate exactly in 32 bits.
-    // The sources are dealt to operand slots of 16 bytes, mfma_nps (1..3) sources per slot, slot = 2 * instruction + lane
-    // half; inside a slot, bytes 4 e + a (a < 4) belong to digit a of the slot's e-th source and byte 12 + e to its digit 4.
+    // Each lane half reads mfma_t = mfma_sources(n) sources, every other one, and puts them into operand slots of
+    // 16 bytes, up to three to a slot, slot = 2 * instruction + lane half; inside a slot, bytes 4 e + a (a < 4) belong to digit a of the slot's e-th source and byte 12 + e to its digit 4.
     // afac[t][b][slot] is the A-operand row of target t, digit plane b, in that byte order (zero where a slot has no source).
-    uint32_t mfma_nm, mfma_nps;                 // instructions per block (1..3), sources per slot
-    uint32_t mfma_src_limb[kMfmaSlots * 3];     // limb of slot-major source k (padding: the first source's limb)
+    uint32_t mfma_t;
+    uint32_t mfma_src_limb[kMfmaSlots * 3];     // limb of the e-th source of a slot at 3 slot + e (padding: the first source's limb)
     alignas(16) int8_t afac[kMaxDst][kMfmaPlanes][kMfmaSlots][16];
     // everything the matrix-core kernel needs to know about a target, in one 32-byte record (one load per lane)
     struct alignas(32) TargetRec {

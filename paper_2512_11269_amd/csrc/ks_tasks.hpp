@@ -120,13 +120,17 @@ struct MfmaConvShape {
     static constexpr uint32_t LDS_WORDS = LOG_R > 4 ? 2 * HALF_WORDS : 1, LDS_TW_WORDS = 2 * TL * TW_WORDS;
 };
 
-// 64 WAVES threads; yp / y_bytes: the source bundle of this polynomial; op: its output bundle; tile: 512 WAVES positions;
-// t0: first of the 2 TL targets (t0 < n_dst); lds: LDS_WORDS doubles; lds_tw: LDS_TW_WORDS doubles.
-template <int LOG_R, int TL, int NM, int NPS, int WAVES>
+// 64 WAVES threads; y / out: the source and output bundles (y_ps and out_ps bytes a polynomial) of polynomials poly0, + step, ... below
+// n_polys; tile: 512 WAVES positions; t0: first of the 2 TL targets (t0 < n_dst); lds: LDS_WORDS doubles; lds_tw: LDS_TW_WORDS doubles.
+// The sources of the next polynomial are requested after the first target of the current one, into the registers that its
+// conversion and that target have freed; factors and twiddles are fetched once.
+template <int LOG_R, int TL, int T, int WAVES>
 __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ tw, const BConvPlan& P, const PlanMeta& PM,
-                                                     const uint8_t* __restrict__ yp, uint64_t y_bytes, uint8_t* __restrict__ op,
-                                                     uint32_t tile, int t0, uint32_t tid, double* lds, double* lds_tw) {
+                                                     const uint8_t* __restrict__ y, uint64_t y_ps, uint8_t* __restrict__ out, uint64_t out_ps,
+                                                     uint32_t poly0, uint32_t step, uint32_t n_polys, uint32_t tile, int t0, uint32_t tid,
+                                                     double* lds, double* lds_tw) {
     using Shape = MfmaConvShape<LOG_R, TL, WAVES>;
+    constexpr int NM = mfma_instructions(T);
     constexpr uint32_t N = 256u << LOG_R, TC = Shape::TC, PADW = Shape::PADW, HALF_WORDS = Shape::HALF_WORDS, TW_WORDS = Shape::TW_WORDS;
     constexpr int E = Shape::E, S = Shape::S;
     const uint32_t lane = tid & 63u, h = lane >> 5, p = (tid >> 6) * 32u + (lane & 31u);
@@ -136,34 +140,35 @@ __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ 
     // B operand: the sources of this lane's slots, already cut into digits (kDigitBias), read through a buffer descriptor
     // (per-lane offset = position + limb).  A source of the 16 positions is four accesses of 16 bytes and, for the fifth
     // digits, one more.  The first ones are requested before anything else.
-    const BufferRsrc ysrd = make_buffer_rsrc(yp, y_bytes);
+    uint32_t voff[T];
+    // quads of positions whose loads are in flight together, and whether position k - 1 is recombined under the matrix
+    // instructions of position k (a second set of result registers) or right away: the single-target shape is kept within 128 registers
+    constexpr int QB = TL == 1 ? (T <= 2 ? 2 : 1) : T <= 2 ? 4 : T <= 4 ? 3 : 1;
+    constexpr bool OVERLAP = TL > 1 && T <= 4;
+    const uint32_t top_off = source_bytes_offset(r0, col) + 4 * N - (r0 * 1024 + col) * 16;   // from a source's first quad
+    Words4 yq[QB][T], ytop[T];
+    BufferRsrc ysrd;
     const auto load4 = [&](uint32_t lane_off, uint32_t off) {
         return __builtin_bit_cast(Words4, __builtin_amdgcn_raw_buffer_load_b128(ysrd, (int)lane_off, (int)off, 0));
     };
-    uint32_t voff[NM][NPS];
-    // quads of positions whose loads are in flight together, and whether position k - 1 is recombined under the matrix
-    // instructions of position k (a second set of result registers) or right away: the single-target shape is kept within 128 registers
-    constexpr int QB = TL == 1 ? (NM * NPS <= 2 ? 2 : 1) : NM * NPS <= 2 ? 4 : NM * NPS <= 4 ? 3 : NM * NPS <= 6 ? 2 : 1;
-    constexpr bool OVERLAP = TL > 1;
-    Words4 yq[QB][NM][NPS], ytop[NM][NPS];
+    const auto request = [&](uint32_t poly) {
+        ysrd = make_buffer_rsrc(y + (uint64_t)poly * y_ps, y_ps);
 #pragma unroll
-    for (int m = 0; m < NM; ++m)
+        for (int q = 0; q < QB; ++q)
 #pragma unroll
-        for (int e = 0; e < NPS; ++e) {
-            // both candidates through scalar registers (a select between two loads would become one per-lane load)
-            const uint32_t limb0 = __builtin_amdgcn_readfirstlane(PM.src_limb[(2 * m) * NPS + e]);
-            const uint32_t limb1 = __builtin_amdgcn_readfirstlane(PM.src_limb[(2 * m + 1) * NPS + e]);
-            const uint32_t limb = (h ? limb1 : limb0) * (uint32_t)packed_limb_bytes(N);
-            voff[m][e] = limb + (r0 * 1024 + col) * 16;
-            yq[0][m][e] = load4(voff[m][e], 0);
-            ytop[m][e] = load4(limb + source_bytes_offset(r0, col), 4 * N);
-        }
+            for (int e = 0; e < T; ++e) {
+                yq[q][e] = load4(voff[e], q * 4096);
+                if (q == 0) ytop[e] = load4(voff[e] + top_off, 0);
+            }
+    };
 #pragma unroll
-    for (int q = 1; q < QB; ++q)
-#pragma unroll
-        for (int m = 0; m < NM; ++m)
-#pragma unroll
-            for (int e = 0; e < NPS; ++e) yq[q][m][e] = load4(voff[m][e], q * 4096);
+    for (int e = 0; e < T; ++e) {
+        // both candidates through scalar registers (a select between two loads would become one per-lane load)
+        const int at = 6 * mfma_slot_of(T, e) + e - mfma_slot_start(T, mfma_slot_of(T, e));
+        const uint32_t limb0 = __builtin_amdgcn_readfirstlane(PM.src_limb[at]), limb1 = __builtin_amdgcn_readfirstlane(PM.src_limb[at + 3]);
+        voff[e] = (h ? limb1 : limb0) * (uint32_t)packed_limb_bytes(N) + (r0 * 1024 + col) * 16;
+    }
+    request(poly0);
 
     // A operand: this lane's row of the factor matrix.  Result register j = 5 u + b sits in row 8 (j / 4) + 4 h' + j % 4,
     // so row r belongs to lane half h' = (r / 4) % 2 and register j = 4 (r / 8) + r % 4.
@@ -189,7 +194,7 @@ __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ 
         mt[u] = rec.m;
         dst_limb[u] = rec.limb;
     }
-    // twiddles of all 2 TL targets -> LDS (requested now, written after the conversion, used after a barrier)
+    // twiddles of all 2 TL targets -> LDS (used after a barrier)
     constexpr uint32_t THREADS = 64 * WAVES;
     constexpr int TW_PER_THREAD = (2 * TL * TW_WORDS + THREADS - 1) / THREADS;
     double twv[TW_PER_THREAD];
@@ -199,6 +204,10 @@ __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ 
         const int t = min(t0 + (int)ht, n_dst - 1);  // ht = half * TL + u, the order of the targets
         twv[i] = tw[(size_t)P.trec[t].mod_id * N + col_twiddle_index<LOG_R>(rem >> 4, rem & 15u)];
     }
+
+#pragma unroll
+    for (int i = 0; i < TW_PER_THREAD; ++i)
+        if (tid + THREADS * i < 2u * TL * TW_WORDS) lds_tw[tid + THREADS * i] = twv[i];
 
     // Software pipeline over the 16 positions, fenced per position so that the schedule below is the one that runs
     // (left alone, the scheduler hoists every matrix instruction and spills): issue the matrix instructions of position k,
@@ -219,57 +228,60 @@ __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ 
             asm volatile("" : "+v"(acc[u][k]));
         }
     };
+#pragma unroll 1
+    for (uint32_t poly = poly0; poly < n_polys; poly += step) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int q = k / 4, x = k % 4;
-        v16i s = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        for (int k = 0; k < 16; ++k) {
+            const int q = k / 4, x = k % 4;
+            v16i s = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            v4i bq = {0, 0, 0, 0};
-#pragma unroll
-            for (int e = 0; e < NPS; ++e) bq[e] = (int)(yq[q % QB][m][e].w[x] ^ 0x80808080u);
-            // byte x of the sources' fifth digits
-            uint32_t top = __builtin_amdgcn_perm(NPS > 1 ? ytop[m][NPS > 1].w[q] : 0u, ytop[m][0].w[q], 0x0c0c0000u + (NPS > 1 ? (x + 4) << 8 : 0xc00) + x);
-            if constexpr (NPS > 2) top = __builtin_amdgcn_perm(ytop[m][NPS - 1].w[q], top, 0x0c000100u + ((x + 4) << 16));
-            bq[3] = (int)top;
-            s = __builtin_amdgcn_mfma_i32_32x32x32_i8(afac[m], bq, s, 0, 0, 0);
-        }
-        if (x == 3 && q + QB < 4) {
-#pragma unroll
-            for (int m = 0; m < NM; ++m)
-#pragma unroll
-                for (int e = 0; e < NPS; ++e) yq[q % QB][m][e] = load4(voff[m][e], (q + QB) * 4096);
-        }
-        sums[OVERLAP ? (k & 1) : 0] = s;
-        if (!OVERLAP) recombine(k);
-        else if (k > 0) recombine(k - 1);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (OVERLAP) recombine(15);
-#pragma unroll
-    for (int i = 0; i < TW_PER_THREAD; ++i)
-        if (tid + THREADS * i < 2u * TL * TW_WORDS) lds_tw[tid + THREADS * i] = twv[i];
-    __syncthreads();
-
-    // column half of the forward transform of each target, both lane halves at once (different moduli per half)
-    double* lh = lds + h * HALF_WORDS;
-#pragma unroll
-    for (int u = 0; u < TL; ++u) {
-        const double* ta = lds_tw + (h * TL + u) * TW_WORDS;
-        radix16_fwd(acc[u], *reinterpret_cast<const double(*)[16]>(ta), mt[u]);
-        if constexpr (E > 0) {
-            if (u > 0) __syncthreads();  // the previous target's reads of the exchange buffer are done
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const uint32_t row = r0 + S * k;
-                lh[row * TC + (row >> 4) * PADW + c] = acc[u][k];
+            for (int m = 0; m < NM; ++m) {
+                constexpr int LAST = T - 1;
+                const int e0 = mfma_slot_start(T, m), n = mfma_slot_sources(T, m);
+                v4i bq = {(int)(yq[q % QB][e0].w[x] ^ 0x80808080u), 0, 0, 0};
+                if (n > 1) bq[1] = (int)(yq[q % QB][min(e0 + 1, LAST)].w[x] ^ 0x80808080u);
+                if (n > 2) bq[2] = (int)(yq[q % QB][min(e0 + 2, LAST)].w[x] ^ 0x80808080u);
+                // byte x of the sources' fifth digits
+                uint32_t top = __builtin_amdgcn_perm(n > 1 ? ytop[min(e0 + 1, LAST)].w[q] : 0u, ytop[e0].w[q], 0x0c0c0000u + (n > 1 ? (x + 4) << 8 : 0xc00) + x);
+                if (n > 2) top = __builtin_amdgcn_perm(ytop[min(e0 + 2, LAST)].w[q], top, 0x0c000100u + ((x + 4) << 16));
+                bq[3] = (int)top;
+                s = __builtin_amdgcn_mfma_i32_32x32x32_i8(afac[m], bq, s, 0, 0, 0);
             }
-            __syncthreads();
+            if (x == 3 && q + QB < 4) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) acc[u][k] = lh[(16 * r0 + k) * TC + r0 * PADW + c];
-            radix16_fwd<4 - E>(acc[u], *reinterpret_cast<const double(*)[16]>(ta + 16 * (1 + r0)), mt[u]);
+                for (int e = 0; e < T; ++e) yq[q % QB][e] = load4(voff[e], (q + QB) * 4096);
+            }
+            sums[OVERLAP ? (k & 1) : 0] = s;
+            if (!OVERLAP) recombine(k);
+            else if (k > 0) recombine(k - 1);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (tgt[u] < n_dst) packed_store<256>(op + (uint64_t)dst_limb[u] * packed_limb_bytes(N), N, r0 * 1024 + col, pack(acc[u]));
+        if (OVERLAP) recombine(15);
+        __syncthreads();   // the twiddles are there, and the previous polynomial's last reads of the exchange buffer are done
+
+        // column half of the forward transform of each target, both lane halves at once (different moduli per half)
+        double* lh = lds + h * HALF_WORDS;
+#pragma unroll
+        for (int u = 0; u < TL; ++u) {
+            uint32_t tw_at = (h * TL + u) * TW_WORDS;
+            asm volatile("" : "+v"(tw_at));   // they stay in LDS: hoisted out of the loop they take sixty registers a target
+            const double* ta = lds_tw + tw_at;
+            radix16_fwd(acc[u], *reinterpret_cast<const double(*)[16]>(ta), mt[u]);
+            if constexpr (E > 0) {
+                if (u > 0) __syncthreads();  // the previous target's reads of the exchange buffer are done
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    const uint32_t row = r0 + S * k;
+                    lh[row * TC + (row >> 4) * PADW + c] = acc[u][k];
+                }
+                __syncthreads();
+#pragma unroll
+                for (int k = 0; k < 16; ++k) acc[u][k] = lh[(16 * r0 + k) * TC + r0 * PADW + c];
+                radix16_fwd<4 - E>(acc[u], *reinterpret_cast<const double(*)[16]>(ta + 16 * (1 + r0)), mt[u]);
+            }
+            if (tgt[u] < n_dst) packed_store<256>(out + (uint64_t)poly * out_ps + (uint64_t)dst_limb[u] * packed_limb_bytes(N), N, r0 * 1024 + col, pack(acc[u]));
+            if (u == 0 && poly + step < n_polys) request(poly + step);
+        }
     }
 }
 
