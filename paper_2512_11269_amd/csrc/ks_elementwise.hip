@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
     }
     struct Raw {
         SlotRaw<G> x;
-        WK k0, k1, w;
+        WK k0, k1;
     };
     auto fetch = [&](uint32_t j, uint32_t r) {
         Raw w;
@@ -255,11 +255,24 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
         w.x = slot_load<G, PACKED>(bundle, j * E + pos, N, sn);
         w.k0 = buffer_load<WK, 2>(key, n * (uint32_t)sizeof(WK), at);
         w.k1 = buffer_load<WK, 2>(key, n * (uint32_t)sizeof(WK), at + M * N * (uint32_t)sizeof(WK));
-        // a null plaintext is the constant 1: the load stays unconditional and its value (a key's residue) is multiplied by 0
-        w.w = buffer_load<WK, 0>(uniform_rsrc(rot.pt[r] ? rot.pt[r] : rot.key[r], (uint64_t)M * N * sizeof(WK)), n * (uint32_t)sizeof(WK),
-                              mid * N * (uint32_t)sizeof(WK));
         return w;
     };
+    Raw qa;
+    if (n_key != 0) qa = fetch(0, 0);
+    // The plaintext slots are used once per digit and once more for c0: each thread keeps its own in LDS (a null plaintext is the
+    // constant 1).  Read from memory every time they were 0.8 of 3.3 GB of a launch.
+    __shared__ double pts[kMacRotations][256];
+#pragma unroll 1
+    for (uint32_t r0 = 0; r0 < rot.n; r0 += 8) {
+        WK w[8];
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) {
+            const void* pt = r0 + i < rot.n ? rot.pt[r0 + i] : nullptr;   // (places past the last rotation are read against a factor of zero)
+            w[i] = pt ? buffer_load<WK>(uniform_rsrc(pt, (uint64_t)M * N * sizeof(WK)), n * (uint32_t)sizeof(WK), mid * N * (uint32_t)sizeof(WK)) : (WK)1;
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) pts[(r0 + i) & (kMacRotations - 1)][threadIdx.x] = word_to_f64<WK>(w[i]);
+    }
     if (n_key != 0) {
         const uint32_t steps = dg.ndig * n_key;
         uint32_t j = 0, r = 0;
@@ -269,8 +282,7 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
         };
         auto products = [&](const Raw& q, uint32_t rq) {
             // the plaintext slot is folded into the key slots, not multiplied per ciphertext
-            const double given = rot.pt[rq] ? 1.0 : 0.0, one = rot.pt[rq] ? 0.0 : 1.0;  // uniform
-            const double w = __builtin_fma(word_to_f64<WK>(q.w), given, one);
+            const double w = pts[rq][threadIdx.x];
             const double k0 = mulmod_lazy(word_to_f64<WK>(q.k0), w, m), k1 = mulmod_lazy(word_to_f64<WK>(q.k1), w, m);
             const SlotRaw<G> s = slot_take<G, PACKED>(q.x);
 #pragma unroll
@@ -281,7 +293,6 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
             }
         };
         // two steps a trip: operands and sums alternate between two register sets instead of being copied
-        Raw qa = fetch(0, 0);
 #pragma unroll 1
         for (uint32_t t = 0; t + 1 < steps; t += 2) {
             const uint32_t ra = r;
@@ -297,7 +308,6 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
     }
     if (pos < ell) {  // uniform: P c0 of every rotation, P c1 of the identities
         const double pm = Pmod[pos];
-        auto plaintext = [&](uint32_t r) { return rot.pt[r] ? static_cast<const WK*>(rot.pt[r])[(uint64_t)mid * N + n] : (WK)1; };
         uint32_t own = 0;
         while (own + 1 < dg.ndig && pos >= dg.hi[own]) ++own;
         if (src.c0) {  // uniform
@@ -308,18 +318,16 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
                 WC x[G];
 #pragma unroll
                 for (int b = 0; b < G; ++b) x[b] = cp[b * src.c0_ps];
-                const double pw = mulmod_lazy(pm, word_to_f64<WK>(plaintext(r)), m);
+                const double pw = mulmod_lazy(pm, pts[r][threadIdx.x], m);
 #pragma unroll
                 for (int b = 0; b < G; ++b) mac_exact(word_to_f64<WC>(x[b]), pw, h0[b], l0[b]);
             }
         } else {
             constexpr uint32_t AHEAD = 2;  // rotations in flight
             SlotRaw<G> x[AHEAD];
-            WK w[AHEAD];
             auto fetch0 = [&](uint32_t r, int i) {
                 r = min(r, rot.n - 1);
                 x[i] = slot_load<G, PACKED>(bundle, dg.ndig * E + pos, N, r < n_key ? galois_source_slot(n, rot.galois[r], logN) : n);
-                w[i] = plaintext(r);
             };
 #pragma unroll
             for (uint32_t i = 0; i < AHEAD; ++i) fetch0(i, i);
@@ -327,7 +335,7 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
             for (uint32_t r0 = 0; r0 < rot.n; r0 += AHEAD) {
 #pragma unroll
                 for (uint32_t i = 0; i < AHEAD; ++i) {
-                    const double pw = mulmod_lazy(r0 + i < rot.n ? pm : 0.0, word_to_f64<WK>(w[i]), m);
+                    const double pw = mulmod_lazy(r0 + i < rot.n ? pm : 0.0, pts[(r0 + i) & (kMacRotations - 1)][threadIdx.x], m);
                     const SlotRaw<G> s = slot_take<G, PACKED>(x[i]);
 #pragma unroll
                     for (int b = 0; b < G; ++b) mac_exact(slot_f64<G, PACKED>(s, b), pw, h0[b], l0[b]);
@@ -338,7 +346,7 @@ __global__ __launch_bounds__(256, 3) void rotate_mac_kernel(const Mod* __restric
 #pragma unroll 1
         for (uint32_t r = n_key; r < rot.n; ++r) {
             const SlotRaw<G> x = slot_load<G, PACKED>(bundle, own * E + pos, N, n);
-            const double pw = mulmod_lazy(pm, word_to_f64<WK>(plaintext(r)), m);
+            const double pw = mulmod_lazy(pm, pts[r][threadIdx.x], m);
 #pragma unroll
             for (int b = 0; b < G; ++b) mac_exact(slot_f64<G, PACKED>(x, b), pw, h1[b], l1[b]);
         }
