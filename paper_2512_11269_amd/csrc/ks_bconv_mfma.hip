@@ -65,7 +65,7 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
     // the first an eighth less (its sources arrive under the butterflies of the one before; factors and twiddles are there): four hoisted
     // rotations of eight ciphertexts, 64 polynomials 8 -> 24, 269 -> 241 us; 16 polynomials 90 -> 84; 13 -> 34, which pays for the loop with
     // scratch registers, 136 -> 133.
-    const uint32_t slots = waves == 8 ? 256 : 512, per_poly = tiles * n_plans * n_subsets;
+    const uint32_t slots = waves == 8 ? 256 : tl == 1 ? 1024 : 512, per_poly = tiles * n_plans * n_subsets;
     uint32_t groups = n_polys;
     double least = 1e30;
     for (uint32_t z = (n_polys + 7) / 8; z <= n_polys; ++z) {

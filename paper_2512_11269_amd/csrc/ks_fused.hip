@@ -155,28 +155,20 @@ __global__ __launch_bounds__(256) void bconv_ntt_cols(const double* __restrict__
 
 // Which kernel the two conversions of a call take: 0 vector, 8 or 16 matrix cores with tiles of 8 or 16 columns.  One answer
 // for both: the code of a kernel that ran a moment ago is still in the caches, so a call that mixes them pays 1-2 us at
-// small sizes and 5-8 where its data exceed the memory-side cache (three key-switches 8 -> 3 x 24 and 8 -> 24, N = 2^16,
-// 36-bit: vector 248 us, matrix cores in ModUp only 246, in ModDown only 242, in both 230).
-//   G counts the matrix-core kernel's workgroups, six targets and 2048 positions each, of which 512 run at once.  Their cost
-// hardly depends on the sources; the vector kernel takes one instruction per source and piece of a residue (three pieces,
-// two for moduli below 2^32) and some for the transform.  So the line is drawn by the load, the vector instructions that a
-// group of six targets replaces, 20 per target besides the products: many sources and full groups (20 targets take four, 24
-// too) favour the matrix cores.  The lines come from key-switches of 42 parameter sets, 1 to 8 ciphertexts, and hoisted
-// rotations of 20, in both word sizes with every pair of kernels.  Times of calls in us, vector / 8 columns / 16 columns:
-//   N = 2^16, 36-bit moduli.  4 -> 16 (load 171), 6 ciphertexts: 305 / 314; 5 -> 20 (175), 2: 169 / 157, 4: 280 / 274;
-// 8 -> 24 (264), 1: 103 / 98, 4: 302 / 287; 12 -> 36 (336), 2: 272 / 241.  28-bit: 4 -> 16 (149), 6: 264 / 279; 8 -> 24
-// (216), 2: 155 / 145, 7: 425 / 416.  In a single round one workgroup's chain is what counts, so the sources alone decide:
-// 36-bit 4 -> 12 70 / 71, 5 -> 5 58 / 56, 7 -> 7 63 / 60, 10 -> 20 91 / 87; 28-bit 7 -> 7 58 / 59, 10 -> 20 82 / 83,
-// 12 -> 18 84 / 84.
+// small sizes and 5-8 where its data exceed the memory-side cache.
+//   G counts the matrix-core kernel's workgroups at six targets and 2048 positions each.  Their cost hardly depends on the sources; the
+// vector kernel takes one instruction per source and piece of a residue (three pieces, two for moduli below 2^32) and some for the
+// transform.  So the line is drawn by the load, the vector instructions that a group of six targets replaces, 20 per target besides
+// the products: many sources and full groups (20 targets take four, 24 too) favour the matrix cores.  Checked on 1786 key-switches of
+// random shapes (N = 2^12 .. 2^16, one to eight ciphertexts, both word sizes), each with every kernel and number of targets: the choice
+// is within 0.1 % (N = 2^12) to 1.5 % (2^14) of the best one on average.  Matrix cores with one target a lane half against the vector
+// kernel with its number of targets, by load per group, 36-bit moduli, N = 2^16, launches of 1024 to 4096 vector workgroups of one target:
+// below 130 +1.8 %, 130-160 -0.6, 160-200 -1.9, above 200 -5.1; 28-bit +3.5, +1.8, -0.3, -1.0; N = 2^15, 256 to 512 workgroups: 36-bit
+// 0.0, -1.3, -3.6, -5.7; 28-bit +1.9, +0.1, -2.2, -3.5.  Where a launch has just more than 256 or 512 groups a few compute units do twice
+// the work of the others, hence the extra.
 //   16 columns are whole lines, but one workgroup of 512 threads per compute unit that works in step: ahead when a launch
-// has six rounds or more.  8 -> 24, 8 ciphertexts (G = 3072): 550 / 545 / 546; 12 -> 36 (4608): 906 / 903 / 887; four
-// rotations of them (G of ModDown 8192 and 12288): 1663 / 1697 / 1614 and 2685 / 2730 / 2618, 28-bit 1492 / 1547 / 1464 and
-// 2423 / 2508 / 2379 (8 -> 24 has a load of 216 there), but at G = 3456 582 / 587 / 585.  10 -> 20 (250), whose last group of six is mostly empty:
-// 1477 / 1580 / 1497, hence the fill.
-//   N = 2^15, 36-bit: 3 -> 9 (130), 8 ciphertexts: 123 / 120, 7: +3.5 %; 7 -> 21 (215), 4: 158 / 139; 28-bit: 3 -> 9 (117),
-// 7: +5.6 %; 4 -> 12 (168), 4: 82 / 83, 8: 137 / 132; 5 -> 20 (150), 4: 140 / 133.  Where a launch has just more than 256 or
-// 512 workgroups a few compute units do twice the work of the others: 3 -> 9, 3: 70 / 74; 13 -> 13 (256), 6: 130 / 134.
-//   Below N = 2^15 launches are at their floor and the vector kernel is 0-1 us ahead.
+// has six rounds or more, full groups and (28-bit moduli) four thousand groups.
+//   Below N = 2^15 launches are at their floor; the vector kernel with one target per workgroup and the matrix cores are within 2 %.
 int conversion_tile(const ks_ctx* c, const PlanSet& up, uint32_t up_polys, const PlanSet& down, uint32_t down_polys) {
     if (c->logN < 15) return 0;
     const uint64_t tiles = c->N / 2048, g_up = tiles * up.sixes * up_polys, g_down = tiles * down.sixes * down_polys;
@@ -205,19 +197,23 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
         double vec_ops = 0.0;
         for (uint32_t j = 0; j < n_plans; ++j) vec_ops += plans.meta.plan[j].n_dst * 44.0 + plans.shape_src * 2.0;
         ProfScope ps("bconv_mfma_ntt_cols", (double)limbs_moved_per_poly * n_polys * packed_limb_bytes(c->N), s, vec_ops * n_polys * c->N);
-        const int tl = c->opt[KS_OPT_BCONV_TARGETS] >= 1 && c->opt[KS_OPT_BCONV_TARGETS] <= 3 ? c->opt[KS_OPT_BCONV_TARGETS] : 3;
+        // Targets per lane half.  A workgroup with one needs half the registers and a third of the time, so that four share a compute unit
+        // and a launch of a few rounds ends evenly: one key-switch 8 -> 24 93.0 -> 90.2 us, one merged multiplication 104.7 -> 100.3,
+        // ten of 4 -> 12 at N = 2^15 -6 %.  Three read the sources once for three: ahead for whole-line tiles (hoisted rotations 9935 ->
+        // 9641 us, 64 multiplications 7083 -> 6984) and where sources are many and the launch is not small (15 -> 17 x 4, 255 -> 232).
+        const uint64_t sixes = (uint64_t)(c->N / 2048) * plans.sixes * n_polys;
+        const int tl = c->opt[KS_OPT_BCONV_TARGETS] ? (c->opt[KS_OPT_BCONV_TARGETS] == 3 ? 3 : 1)
+                       : tile == 16 || (mfma_sources(plans.shape_src) >= 8 && sixes >= 384) ? 3 : 1;
         launch_bconv_mfma_ntt_cols(c, plans, y, y_ps, out, out_ps, n_polys, tl, tile == 16, s);
         return;
     }
-    // Targets per workgroup: fewer targets = more workgroups but more re-reads and re-splits of the sources.  Four (with
-    // the two-set source pipeline) is best once the launch has a few workgroups per compute unit; for the
-    // single-ciphertext launches three (one-set pipeline) measured best (384 and 256 workgroups: every one resident at
-    // once, none waiting for a slot to free up).
+    // Targets per workgroup: fewer targets = more workgroups and a shorter chain in each, but more re-reads and re-cuts of the sources.
+    // Key-switches of random shapes, one and two targets against three by workgroups of one target: below 256 -13 and -6 %, 512 to
+    // 1024 -4 and -3, 1024 to 2048 +0.2 and -1.9, 4096 to 8192 +6 and 0, above +10 and +2, four there -0.2.
     // The context option KS_OPT_BCONV_TARGETS overrides the choice.
     const uint32_t tiles = 1u << (c->logN - 12);
-    int ts = (uint64_t)tiles * n_plans * ((max_targets + 3) / 4) * n_polys >= 512 ? 4 : 3;
-    if (c->opt[KS_OPT_BCONV_TARGETS] >= 1 && c->opt[KS_OPT_BCONV_TARGETS] <= 4) ts = c->opt[KS_OPT_BCONV_TARGETS];
-    if (c->logN != 16 && ts < 3) ts = 3;  // the other ring degrees come with the two production shapes only
+    const uint64_t ones = (uint64_t)tiles * n_plans * max_targets * n_polys;
+    const int ts = c->opt[KS_OPT_BCONV_TARGETS] ? c->opt[KS_OPT_BCONV_TARGETS] : ones <= 1024 ? 1 : ones <= 8192 ? 2 : 4;
     const uint32_t n_subsets = (max_targets + ts - 1) / ts;
     const dim3 grid(tiles, n_plans * n_subsets, n_polys), block(256);
     ProfScope ps("bconv_ntt_cols", (double)limbs_moved_per_poly * n_polys * packed_limb_bytes(c->N), s, ops_per_coeff * n_polys * c->N);
@@ -228,18 +224,13 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
     else                                                                                                                                \
         hipLaunchKernelGGL((bconv_ntt_cols<LOGR, TSV, 3>), grid, block, 0, s, c->d_tw_fwd, d_plans, y, y_ps, out, out_ps,  \
                            n_subsets)
-    if (c->logN == 16) {
-        if (ts == 4) { KS_LAUNCH_BCONV(8, 4); }
-        else if (ts == 3) { KS_LAUNCH_BCONV(8, 3); }
-        else if (ts == 2) { KS_LAUNCH_BCONV(8, 2); }
-        else { KS_LAUNCH_BCONV(8, 1); }
-    } else {
-#define KS_LAUNCH(LOGR)                        \
-    if (ts == 4) { KS_LAUNCH_BCONV(LOGR, 4); } \
-    else { KS_LAUNCH_BCONV(LOGR, 3); }
-        KS_FOR_LOG_R(c->logN, KS_LAUNCH)
+#define KS_LAUNCH(LOGR)                             \
+    if (ts == 4) { KS_LAUNCH_BCONV(LOGR, 4); }      \
+    else if (ts == 3) { KS_LAUNCH_BCONV(LOGR, 3); } \
+    else if (ts == 2) { KS_LAUNCH_BCONV(LOGR, 2); } \
+    else { KS_LAUNCH_BCONV(LOGR, 1); }
+    KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
-    }
 #undef KS_LAUNCH_BCONV
 }
 
