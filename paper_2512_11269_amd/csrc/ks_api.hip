@@ -7,8 +7,8 @@ using namespace ks;
 
 namespace {
 
-// Ciphertexts processed per pass of a pipeline; bounds the workspace.  Eight fill every launch and keep more of the
-// intermediates in the last-level cache than sixteen (3-4 % faster on batched key-switches and multiplications).
+// Ciphertexts that the workspace of a pipeline is sized for; more are processed in passes (rotations of eight, the group of a gather;
+// key-switches and multiplications: ciphertexts_at_a_time).
 constexpr uint32_t kChunk = 8;
 static_assert(kChunk <= kMaxGroup, "ciphertexts of one gather bundle");
 constexpr uint32_t kRotGroup = 4;  // hoisted rotations per gather launch (larger groups measured no faster); bounds the workspace
@@ -169,6 +169,17 @@ extern "C" size_t ks_workspace_bytes(const ks_ctx* c, int op, uint32_t ell, uint
     return (size_t)words * sizeof(uint64_t);
 }
 
+// Ciphertexts that a key-switch or multiplication takes at a time, given the bytes one of them takes: kChunk, or as many as the
+// workspace holds (a caller brings what ks_workspace_bytes asks for, 8 bytes a residue; the packed regions of about thirteen fit) where
+// that makes fewer passes, evenly filled.  Key-switches in passes of eight -> so many: N = 2^12, 12 ciphertexts 79 -> 45 us, 64 327 -> 224;
+// N = 2^14 185 -> 151 and 918 -> 841; N = 2^16, L = 24 803 -> 753 and 4014 -> 3887; multiplications at L = 35, 64 of them 7086 -> 7046.
+// As many passes as before stay as they are (seven and seven for eight and six was up to 12 % slower).
+static uint32_t ciphertexts_at_a_time(const ks_ctx* c, const Level& lv, int op, uint32_t batch, uint64_t bytes_of_one) {
+    if (batch <= kChunk) return batch;
+    const uint32_t fit = (uint32_t)(ks_workspace_bytes(c, op, lv.ell, batch, 0) / bytes_of_one), passes = (batch + fit - 1) / fit;
+    return passes == (batch + kChunk - 1) / kChunk ? kChunk : (batch + passes - 1) / passes;
+}
+
 static int check_map_args(const ks_ctx* c, const void* data, const uint32_t* mod_ids, uint32_t nlimbs, LimbMap* map) {
     if (!c || !data || !mod_ids || nlimbs == 0 || nlimbs > (uint32_t)kMaxLimbs || !aligned16(data)) return KS_EINVAL;
     map->n = nlimbs;
@@ -325,8 +336,10 @@ int ks::keyswitch_impl(const ks_ctx* c, const void* d, uint32_t ell, const void*
     const Level& lv = c->levels[ell - 1];
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint64_t N = c->N, d_ps = (uint64_t)ell * N, out_bs = 2ull * ell * N, word = words32 ? 4 : 8;
-    for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
-        const uint32_t bc = std::min(batch - b0, kChunk);
+    const KsWorkspace one = ks_ws_regions(c, lv, 1);
+    const uint32_t chunk = ciphertexts_at_a_time(c, lv, KS_OP_KEYSWITCH, batch, one.coeff + one.lifted + one.acc + one.conv);
+    for (uint32_t b0 = 0; b0 < batch; b0 += chunk) {
+        const uint32_t bc = std::min(batch - b0, chunk);
         const KsWorkspace w = ks_ws_regions(c, lv, bc);
         uint8_t* coeff = static_cast<uint8_t*>(ws);
         uint8_t* lifted = coeff + w.coeff;
@@ -589,8 +602,11 @@ static int hmult_impl(const ks_ctx* c, const void* cta, const void* ctb, uint32_
     if (merged && !lv.merged.d_plans) return KS_EINVAL;  // K + 1 sources exceed what one conversion takes
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint64_t N = c->N, ct_bs = 2ull * ell * N, out_bs = 2ull * (ell - 1) * N, word = words32 ? 4 : 8;
-    for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
-        const uint32_t bc = std::min(batch - b0, kChunk);
+    const KsWorkspace one = ks_ws_regions(c, lv, 1);
+    // (d0, d1) as large as conv, d2 as coeff
+    const uint32_t chunk = ciphertexts_at_a_time(c, lv, KS_OP_HMULT_RELIN_RESCALE, batch, 2 * one.coeff + one.lifted + one.acc + 2 * one.conv);
+    for (uint32_t b0 = 0; b0 < batch; b0 += chunk) {
+        const uint32_t bc = std::min(batch - b0, chunk);
         const KsWorkspace w = ks_ws_regions(c, lv, bc);
         uint8_t* coeff = static_cast<uint8_t*>(ws);
         uint8_t* lifted = coeff + w.coeff;
