@@ -128,7 +128,7 @@ void mod_down(const ks_ctx* c, const Level& lv, uint8_t* acc, uint8_t* conv, voi
     if (!special_rows_done) launch_inv_rows_packed(c, lv.special_map, acc, acc_ps, 1, acc, acc_ps, 2 * bc, s);
     launch_inv_cols_packed(c, lv.special_map, acc, acc_ps, 2 * bc, c->d_moddown_scale, s);
     launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s, moddown_ops(c, lv));
-    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 0, 0, 1, bc, s, nullptr, out_words32);
+    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 0, nullptr, 0, bc, s, nullptr, out_words32);
 }
 
 }  // namespace
@@ -381,6 +381,7 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
     const Level& lv = c->levels[ell - 1];
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint64_t N = c->N, ct_bs = 2ull * ell * N, out_bs = (uint64_t)n_rot * 2 * ell * N, word = words32 ? 4 : 8;
+    const uint32_t group = std::min(n_rot, kRotGroup);
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
         const KsWorkspace w = ks_ws_regions(c, lv, bc);
@@ -392,13 +393,12 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
         const void* c1 = c0 + (uint64_t)ell * N * word;
         uint8_t* lifted = coeff + w.coeff;
         uint8_t* acc = lifted + w.lifted;
-        const uint32_t group = std::min(n_rot, kRotGroup);
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * group * bc);
         // finished once, shared by every rotation
         const GatherBundle digits = mod_up_for_gather(c, lv, c1, nullptr, ct_bs, coeff, lifted, region, bc, n_rot, tile, s, words32);
         // Rotations go in groups: one gather launch forms the accumulators of the whole group (the raised digits then come
-        // from memory once per group), the inverse transform and the conversion run over the group as one batch, and only
-        // the last kernel, which adds sigma_g(c0) through a rotation's own permutation, runs per rotation.
+        // from memory once per group), and the inverse transform, the conversion and the last kernel, which adds sigma_g(c0) through
+        // each rotation's own permutation, run over the group as one batch.
         uint8_t* conv = acc + (uint64_t)group * w.acc;
         const uint64_t limb = packed_limb_bytes(N), acc_ps = lv.E * limb, conv_ps = ell * limb;
         for (uint32_t r0 = 0; r0 < n_rot; r0 += group) {
@@ -414,10 +414,8 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
             launch_inv_rows_packed(c, lv.special_map, acc, acc_ps, 1, acc, acc_ps, polys, s);
             launch_inv_cols_packed(c, lv.special_map, acc, acc_ps, polys, c->d_moddown_scale, s);
             launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, polys, tile, s, moddown_ops(c, lv));
-            for (uint32_t r = 0; r < rot.n; ++r)
-                launch_rows_moddown_finish(c, lv, acc + r * w.acc, conv + r * w.conv,
-                                           static_cast<char*>(out) + ((uint64_t)b0 * out_bs + (uint64_t)(r0 + r) * 2 * ell * N) * word,
-                                           out_bs, c0, ct_bs, 1, galois[r0 + r], bc, s, nullptr, words32);
+            launch_rows_moddown_finish(c, lv, acc, conv, static_cast<char*>(out) + ((uint64_t)b0 * out_bs + (uint64_t)r0 * 2 * ell * N) * word, out_bs,
+                                       c0, ct_bs, &rot, 2ull * ell * N, bc, s, nullptr, words32);
         }
     }
     return finish(words32 ? "ks_rotate_hoisted_u32" : "ks_rotate_hoisted");
@@ -586,7 +584,7 @@ static void mod_down_drop(const ks_ctx* c, const Level& lv, uint8_t* acc, uint8_
     const double ops = (double)n_src * n_dst * 4.5 + n_dst * (3.0 + 4.0 * (c->logN - 8));
     launch_bconv_ntt_cols(c, merged ? lv.merged : lv.rescale, n_src + n_dst, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s, ops);
     const FinishScale fs{lv.d_Dinv, lv.d_qlinv, n_dst};
-    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, addend, 0, 2, 1, bc, s, &fs, out_words32);
+    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, addend, 0, nullptr, 0, bc, s, &fs, out_words32);
 }
 
 // cta, ctb, rlk and out in 64-bit words, or all four in 32-bit words (words32).

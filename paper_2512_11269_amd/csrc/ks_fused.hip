@@ -311,72 +311,64 @@ void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, 
 // ------------------------------------------------------------------------------------------------
 // out[b][comp][i] = (acc[b][comp][i] - NTT_rows(conv[b][comp][i])) * P^-1 (+ addend), canonical.
 // ------------------------------------------------------------------------------------------------
-// ADDEND: 0 = none, 1 = words, added as they are, 2 = packed ([b][2][ell]), multiplied by addend_mul[i] first.  Compile-time so
-// that the kernel has no branch: behind a run-time test every addend load became its own load-wait-use round trip.  A launch
-// covers the components comp0 .. comp0 + n_comps - 1 of every batch item.
-template <int LOG_R, bool GATHER, int ADDEND, typename W>
+// ADDEND: 0 = none, 1 = words of component 0, read through sigma_galois and added as they are, 2 = packed ([b][2][ell]), multiplied by
+// addend_mul[i] first.  Compile-time so that the kernel has no branch in front of its loads; the components that take no addend
+// in mode 1 branch to the other instance of the task, which is uniform.
+// A launch covers n_rot rotations (1 but for hoisted ones) of every batch item: acc [rot][b][2][E], conv [rot][b][2][ell].
+template <int LOG_R, int ADDEND, typename W>
 __global__ __launch_bounds__(64) void rows_moddown_finish(TwTables tw, const Mod* __restrict__ mods,
                                                           const double* __restrict__ Pinv, const double* __restrict__ addend_mul,
                                                           uint32_t ell, uint32_t E, uint32_t out_limbs, const uint8_t* __restrict__ acc,
-                                                          const uint8_t* __restrict__ conv, W* __restrict__ out, uint64_t out_bs,
-                                                          const void* __restrict__ addend, uint64_t addend_bs, uint32_t comp0,
-                                                          uint32_t n_comps, uint32_t galois) {
+                                                          const uint8_t* __restrict__ conv, W* __restrict__ out, uint64_t out_bs, uint64_t out_rs,
+                                                          const void* __restrict__ addend, uint64_t addend_bs, uint32_t batch, FinishRotations rot) {
     constexpr uint32_t N = 256u << LOG_R;
     constexpr uint64_t LIMB = packed_limb_bytes(N);
     __shared__ double lds[4 * kRowPitch];
     const uint32_t rg = blockIdx.x, i = blockIdx.y;
     // batch items in descending order: the conversion kernel before this one wrote them in ascending order, so the most
     // recently written ones, still in the last-level cache, are read first (4-5 % on this kernel in batched calls)
-    const uint32_t zz = gridDim.z - 1 - blockIdx.z;
-    const uint32_t b = zz / n_comps, comp = comp0 + (zz - b * n_comps);
-    const uint64_t ct_limb = ((uint64_t)b * 2 + comp) * ell + i;
-    const void* adp = nullptr;
-    double admul = 0.0;
-    if constexpr (ADDEND == 1) adp = static_cast<const W*>(addend) + (uint64_t)b * addend_bs + ((uint64_t)comp * ell + i) * N;
+    const uint32_t zz = gridDim.z - 1 - blockIdx.z, comp = zz & 1u, item = zz >> 1, r = item / batch, b = item - r * batch;
+    const uint64_t ct_limb = ((uint64_t)item * 2 + comp) * ell + i;
+    const uint8_t *conv_limb = conv + ct_limb * LIMB, *acc_limb = acc + (((uint64_t)item * 2 + comp) * E + i) * LIMB;
+    W* op = out + (uint64_t)b * out_bs + (uint64_t)r * out_rs + ((uint64_t)comp * out_limbs + i) * N;
     if constexpr (ADDEND == 2) {
-        adp = static_cast<const uint8_t*>(addend) + ct_limb * LIMB;
-        admul = addend_mul[i];
+        task_rows_finish<LOG_R, false, 2, W>(tw, mods[i], i, Pinv[i], addend_mul[i], conv_limb, acc_limb, op,
+                                             static_cast<const uint8_t*>(addend) + ct_limb * LIMB, 1, rg, threadIdx.x, lds);
+    } else if (ADDEND == 1 && comp == 0) {
+        task_rows_finish<LOG_R, true, 1, W>(tw, mods[i], i, Pinv[i], 0.0, conv_limb, acc_limb, op,
+                                            static_cast<const W*>(addend) + (uint64_t)b * addend_bs + (uint64_t)i * N, rot.galois[r], rg, threadIdx.x, lds);
+    } else {
+        task_rows_finish<LOG_R, false, 0, W>(tw, mods[i], i, Pinv[i], 0.0, conv_limb, acc_limb, op, nullptr, 1, rg, threadIdx.x, lds);
     }
-    task_rows_finish<LOG_R, GATHER, ADDEND, W>(tw, mods[i], i, Pinv[i], admul, conv + ct_limb * LIMB,
-                                               acc + (((uint64_t)b * 2 + comp) * E + i) * LIMB,
-                                               out + (uint64_t)b * out_bs + ((uint64_t)comp * out_limbs + i) * N, adp, galois, rg, threadIdx.x, lds);
 }
 
 void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint8_t* acc, const uint8_t* conv, void* out_words, uint64_t out_bs,
-                                const void* addend, uint64_t addend_bs, uint32_t addend_comps, uint32_t galois, uint32_t batch,
+                                const void* addend, uint64_t addend_bs, const MacRotations* rotations, uint64_t out_rs, uint32_t batch,
                                 hipStream_t s, const FinishScale* fs, bool out_words32) {
     if (batch == 0) return;
     const double* mul = fs ? fs->mul : c->d_Pinv;
     const double* admul = fs ? fs->addend_mul : nullptr;
-    const uint32_t out_limbs = fs ? fs->out_limbs : lv.ell;
+    const uint32_t out_limbs = fs ? fs->out_limbs : lv.ell, n_rot = rotations ? rotations->n : 1;
     if (out_limbs == 0) return;
-    if (!addend) addend_comps = 0;
+    FinishRotations rot{};
+    for (uint32_t r = 0; rotations && r < n_rot; ++r) rot.galois[r] = rotations->galois[r];
     const double wo = out_words32 ? 4.0 : 8.0;
-    ProfScope ps("rows_moddown_finish", (double)batch * out_limbs * (2 * 5 + 2 * 5 + 2 * wo + addend_comps * (admul ? 5.0 : wo)) * c->N, s);
-    const dim3 block(64);
-    const uint32_t row_groups = c->N / 1024;
-    // one launch for the components that take the addend, one for those that do not
-    for (int pass = 0; pass < 2; ++pass) {
-        const uint32_t comp0 = pass == 0 ? 0 : addend_comps, n_comps = pass == 0 ? addend_comps : 2 - addend_comps;
-        if (n_comps == 0) continue;
-        const int mode = pass == 1 ? 0 : (admul ? 2 : 1);
-        const dim3 grid(row_groups, out_limbs, batch * n_comps);
-#define KS_LAUNCH_FINISH(LOGR, GATHER, MODE, WT)                                                                                        \
-    hipLaunchKernelGGL((rows_moddown_finish<LOGR, GATHER, MODE, WT>), grid, block, 0, s, c->tw_fwd, c->d_mod, mul, admul, lv.ell, lv.E, \
-                       out_limbs, acc, conv, static_cast<WT*>(out_words), out_bs, addend, addend_bs, comp0, n_comps, galois)
-#define KS_LAUNCH_MODES(LOGR, WT)                                         \
-    if (mode == 2) KS_LAUNCH_FINISH(LOGR, false, 2, WT);                  \
-    else if (mode == 1 && galois != 1) KS_LAUNCH_FINISH(LOGR, true, 1, WT); \
-    else if (mode == 1) KS_LAUNCH_FINISH(LOGR, false, 1, WT);             \
-    else KS_LAUNCH_FINISH(LOGR, false, 0, WT)
+    ProfScope ps("rows_moddown_finish", (double)batch * n_rot * out_limbs * (2 * 5 + 2 * 5 + 2 * wo + (!addend ? 0.0 : fs ? 10.0 : wo)) * c->N, s);
+    const dim3 block(64), grid(c->N / 1024, out_limbs, batch * n_rot * 2);
+#define KS_LAUNCH_FINISH(LOGR, MODE, WT)                                                                                        \
+    hipLaunchKernelGGL((rows_moddown_finish<LOGR, MODE, WT>), grid, block, 0, s, c->tw_fwd, c->d_mod, mul, admul, lv.ell, lv.E, \
+                       out_limbs, acc, conv, static_cast<WT*>(out_words), out_bs, out_rs, addend, addend_bs, batch, rot)
+#define KS_LAUNCH_MODES(LOGR, WT)                       \
+    if (fs) KS_LAUNCH_FINISH(LOGR, 2, WT);              \
+    else if (addend) KS_LAUNCH_FINISH(LOGR, 1, WT);     \
+    else KS_LAUNCH_FINISH(LOGR, 0, WT)
 #define KS_LAUNCH(LOGR)                                   \
     if (out_words32) { KS_LAUNCH_MODES(LOGR, uint32_t); } \
     else { KS_LAUNCH_MODES(LOGR, uint64_t); }
-        KS_FOR_LOG_R(c->logN, KS_LAUNCH)
+    KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
 #undef KS_LAUNCH_MODES
 #undef KS_LAUNCH_FINISH
-    }
 }
 
 // ------------------------------------------------------------------------------------------------

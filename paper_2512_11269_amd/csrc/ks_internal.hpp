@@ -200,6 +200,17 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
                                 uint64_t out_ps, uint32_t n_polys, int tl, bool wide, hipStream_t s);
 // Upload host plans as a PlanSet (allocates; ks_ctx_create and bconv plan registration only).  Returns a HIP error code.
 hipError_t upload_plans(const BConvPlan* host_plans, uint32_t n_plans, uint32_t shape_src, PlanSet* out);
+// Rotations handled by one launch of the gather kernels (more are chained).
+constexpr int kMacRotations = 16;
+struct MacRotations {
+    uint32_t n;
+    uint32_t galois[kMacRotations];
+    const void* key[kMacRotations];  // [dnum][2][L+K][N], 64- or 32-bit words
+    const void* pt[kMacRotations];   // [L+K][N], same word size as the keys
+};
+struct FinishRotations {
+    uint32_t galois[kMacRotations];
+};
 // Fused row half of the forward transform of the raised digits + inner product with the key.
 // d_word: bytes of a word of d, 8 or 4, or 1: packed limbs in rows order (then d_ps counts bytes); key_words32: the key holds one residue
 // per 32-bit word (4-byte words of d imply them).  acc: [b][2][E] packed.  The ciphertext limbs are in rows order; the special limbs have been through the row half of their inverse
@@ -210,8 +221,9 @@ void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, 
                                const uint8_t* drop_addend = nullptr);
 // Fused row half of the forward transform of the converted limbs (conv, [b][2][ell] packed) + (acc - conv) P^-1 (+ addend);
 // the ciphertext limbs of acc ([b][2][E] packed) are in rows order.
-// fs == nullptr: multiply by P^-1, ell output limbs; an addend is in the word size of the output (addend_batch_stride words
-// between batch items) and read through sigma_galois.  Otherwise (division by P and a rescale): multiply by fs->mul[i], add the
+// fs == nullptr: multiply by P^-1, ell output limbs; with `rotations` (their galois elements are read) acc and conv hold that many
+// batches one behind the other, whose outputs are out_rot_stride words apart, and the addend, in the word size of the output and
+// addend_batch_stride words between batch items, is added to component 0 through sigma_galois.  Otherwise (division by P and a rescale): multiply by fs->mul[i], add the
 // packed addend ([b][2][ell]) times fs->addend_mul[i], write the first fs->out_limbs limbs per component.
 struct FinishScale {
     const double* mul;
@@ -220,7 +232,7 @@ struct FinishScale {
 };
 void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint8_t* acc, const uint8_t* conv, void* out,
                                 uint64_t out_batch_stride, const void* addend, uint64_t addend_batch_stride,
-                                uint32_t addend_comps, uint32_t galois, uint32_t batch, hipStream_t s,
+                                const MacRotations* rotations, uint64_t out_rot_stride, uint32_t batch, hipStream_t s,
                                 const FinishScale* fs = nullptr, bool out_words32 = false);
 // Remainder of the dropped limb for a rescale.  acc: [polys][E], the drop_map limbs as sources of a conversion (canonical: y_k on the
 // special limbs, P^-1 times the dropped limb's sum on limb ell-1); limb ell-1 becomes the centred remainder of (sum - converted
@@ -235,14 +247,6 @@ void launch_bconv(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_pe
 void launch_bconv_mfma(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const void* in, uint64_t in_poly_stride,
                        void* out, uint64_t out_poly_stride, uint32_t n_polys, hipStream_t s, bool words32);
 
-// Rotations handled by one launch of the gather kernels (more are chained).
-constexpr int kMacRotations = 16;
-struct MacRotations {
-    uint32_t n;
-    uint32_t galois[kMacRotations];
-    const void* key[kMacRotations];  // [dnum][2][L+K][N], 64- or 32-bit words
-    const void* pt[kMacRotations];   // [L+K][N], same word size as the keys
-};
 // What the sigma_g gathers of a rotation read, for a group of up to 8 ciphertexts: slabs of N slots, slab j E + pos the
 // finished raised digit j at limb position pos (in the slots of a digit's own positions the limbs of the polynomial
 // itself), slabs ndig E + pos, pos < ell, the limbs of the addend c0 where a caller asked for them.  A slot holds the

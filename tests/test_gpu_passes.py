@@ -31,3 +31,25 @@ def test_batches_in_passes(bits, L, Kk, dnum, ell, batch):
             fn(st.ctx, *(a[b:b + 1] for a in args), ell, evk, one, ws)
             assert torch.equal(out[b:b + 1], one), b
         assert bool((buf[words:] == -7).all())
+
+
+@pytest.mark.parametrize("bits", [36, 28])
+@pytest.mark.parametrize("L,Kk,dnum,ell", [(6, 2, 3, 6), (6, 6, 1, 2), (5, 2, 4, 5)])
+@pytest.mark.parametrize("batch,n_rot", [(1, 5), (1, 16), (3, 8), (8, 7), (8, 17), (9, 20)])
+def test_rotations_in_groups(bits, L, Kk, dnum, ell, batch, n_rot):
+    st = Setup(12, L, Kk, dnum, bits=bits)
+    wide = bits == 36
+    word = (lambda t: t) if wide else (lambda t: t.to(torch.int32))
+    fn, op = (K.ks_rotate_hoisted, K.KS_OP_ROTATE_HOISTED) if wide else (K.ks_rotate_hoisted_u32, K.KS_OP_ROTATE_HOISTED_U32)
+    galois = [pow(5, r + 1, 2 * st.N) if r % 3 else 2 * st.N - pow(5, r + 1, 2 * st.N) for r in range(n_rot)]
+    keys = [word(st.uniform(52, 10 + r, (dnum, 2), list(range(L + Kk)))) for r in range(n_rot)]
+    ct = word(st.uniform(52, 1, (batch, 2), list(range(ell))))
+    words = K.ks_workspace_bytes(st.ctx, op, ell, batch, n_rot) // 8
+    buf = torch.full((words + GUARD,), -7, dtype=torch.int64, device="cuda")
+    out = torch.full((batch, n_rot, 2, ell, st.N), -1, dtype=ct.dtype, device="cuda")
+    fn(st.ctx, ct, ell, galois, keys, out, buf[:words])
+    one, ws = torch.empty((batch, 1, 2, ell, st.N), dtype=ct.dtype, device="cuda"), workspace(st.ctx, op, ell, batch, 1)
+    for r in range(n_rot):
+        fn(st.ctx, ct, ell, galois[r:r + 1], keys[r:r + 1], one, ws)
+        assert torch.equal(out[:, r:r + 1], one), r
+    assert bool((buf[words:] == -7).all())
