@@ -11,7 +11,7 @@ namespace {
 // key-switches and multiplications: ciphertexts_at_a_time).
 constexpr uint32_t kChunk = 8;
 static_assert(kChunk <= kMaxGroup, "ciphertexts of one gather bundle");
-constexpr uint32_t kRotGroup = 4;  // hoisted rotations per gather launch (larger groups measured no faster); bounds the workspace
+constexpr uint32_t kRotGroup = 4;  // hoisted rotations that the workspace is sized for; a group of a gather launch
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -381,7 +381,17 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
     const Level& lv = c->levels[ell - 1];
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint64_t N = c->N, ct_bs = 2ull * ell * N, out_bs = (uint64_t)n_rot * 2 * ell * N, word = words32 ? 4 : 8;
-    const uint32_t group = std::min(n_rot, kRotGroup);
+    // Rotations of a group: kRotGroup, or where the launches of so many are small, as many as the workspace holds (about eight, see
+    // ciphertexts_at_a_time), evenly filled.  Sixteen rotations in groups of four -> eight: N = 2^12, 8 ciphertexts 200 -> 152 us; N = 2^14,
+    // 8 ciphertexts 890 -> 816; N = 2^16, one 948 -> 873; but 8 of them 4839 -> 4846 and, 28-bit, 4194 -> 4288; N = 2^15, 8, 28-bit 2083 -> 2140.
+    uint32_t group = std::min(n_rot, kRotGroup);
+    if (const uint32_t bc = std::min(batch, kChunk); (uint64_t)bc * N < 1u << 18) {
+        const KsWorkspace w = ks_ws_regions(c, lv, bc);
+        const uint64_t have = ks_workspace_bytes(c, words32 ? KS_OP_ROTATE_HOISTED_U32 : KS_OP_ROTATE_HOISTED, ell, batch, n_rot);
+        const uint64_t fixed = gather_words(c, lv, bc, false, words32) * 8 + w.coeff + w.lifted;
+        const uint32_t fit = (uint32_t)std::min<uint64_t>(kMacRotations, (have - fixed) / (w.acc + w.conv)), groups = (n_rot + fit - 1) / fit;
+        if (groups < (n_rot + kRotGroup - 1) / kRotGroup) group = (n_rot + groups - 1) / groups;
+    }
     for (uint32_t b0 = 0; b0 < batch; b0 += kChunk) {
         const uint32_t bc = std::min(batch - b0, kChunk);
         const KsWorkspace w = ks_ws_regions(c, lv, bc);
