@@ -36,11 +36,11 @@ CHUNK = 8                        # ciphertexts per internal pass of the batched 
 # "measured" column: FETCH_SIZE and WRITE_SIZE scaled by what the same counters read for a 1 GiB device copy, summed, per
 # launch), keyed by workload and kernel.  tests/test_profiles_consistent.py checks these against that file.
 MEASURED_TRAFFIC_BYTES: dict = {
-    ("keyswitch", "rows_inner_product"): 178500631,
-    ("keyswitch", "rows_moddown_finish"): 68023405,
-    ("keyswitch", "bconv_mfma_ntt_cols"): 53443678,  # mean of the ModUp and the ModDown launch
-    ("keyswitch", "ntt_inv_rows"): 27089621,
-    ("keyswitch", "ntt_inv_cols"): 21370488,         # mean of the 24-limb and the 16-limb launch
+    ("keyswitch", "bconv_mfma_ntt_cols"): 28349023,    # mean of the ModUp and the ModDown launch
+    ("keyswitch", "rows_inner_product"): 161213528,
+    ("keyswitch", "rows_moddown_finish"): 58568102,
+    ("keyswitch", "inv_rows_packed"): 22378512,
+    ("keyswitch", "inv_cols_packed"): 14822854,        # mean of the 24-limb and the 16-limb launch
 }
 
 # Algorithmic bytes of the other workloads (fused-plan accounting: every transform = two passes over its limbs, base
@@ -70,9 +70,20 @@ def _keyswitch_bytes(L, K, dnum, N, batch=1):
 
 
 def _keyswitch_bytes_moved(L, K, dnum, N, batch=1):
-    """What the library's chain moves per key-switch: the fused-plan model with the ciphertext limbs of both
-    accumulators written and read back as 5-byte packed residues instead of 8-byte words (2 * 2 * L limbs at 3/8 less)."""
-    return _keyswitch_bytes(L, K, dnum, N, batch)[1] - 2 * 2 * L * N * 3.0
+    """What the library's seven launches move per key-switch: ciphertext, key and result in 8-byte words, every limb that
+    one kernel writes and the next reads as 5 bytes a residue.  The fused plan has one pass less over the digits (it
+    counts the column half of their inverse transform with the conversion)."""
+    alpha = -(-L // dnum)
+    E = L + K
+    new_limbs = sum(E - (min((j + 1) * alpha, L) - j * alpha) for j in range(dnum))
+    words = L + L + dnum * 2 * E / min(batch, CHUNK) + 2 * L          # d twice (INTT, own slots of the product), key, result
+    packed = (L + 2 * L                                               # INTT rows (written), INTT cols
+              + L + new_limbs                                         # conversion + NTT cols
+              + new_limbs + 2 * E                                     # NTT rows + inner product (+ INTT rows of special limbs)
+              + 2 * 2 * K                                             # INTT cols of special limbs
+              + 2 * K + 2 * L                                         # conversion + NTT cols
+              + 2 * L + 2 * L)                                        # NTT rows + subtract-scale
+    return (8.0 * words + 5.0 * packed) * N
 
 
 def _apply_options(ctx, args):
@@ -199,7 +210,7 @@ def bench_keyswitch(args, torch, K, ks_inputs):
     path = {"fused_plan_MiB": fused / MIB, "compulsory_MiB": compulsory / MIB,
             "fused_plan_GBs": round(fused / (ms * 1e-3) / 1e9, 1), "fused_plan_frac_of_peak": frac(fused, ms),
             "target_frac_of_peak": 0.60,
-            # the same with the packed accumulator limbs counted at their 5 bytes: the bytes the chain really moves
+            # the same with the packed limbs between the kernels counted at their 5 bytes: the bytes the chain really moves
             "moved_MiB": round(_keyswitch_bytes_moved(L, Kk, dnum, N) / MIB, 1),
             "moved_frac_of_peak": frac(_keyswitch_bytes_moved(L, Kk, dnum, N), ms),
             "compulsory_GBs": round(compulsory / (ms * 1e-3) / 1e9, 1),

@@ -116,7 +116,7 @@ static uint32_t gather_grid(const ks_ctx* c, uint32_t E, uint32_t parts_log) {
 // key_r[j][c][pos].  One thread owns one slot of one limb position for all ciphertexts of the group and walks the
 // rotations of the launch; the operands of the next (rotation, digit) are requested before the current products.
 // WK: word type of the keys; PACKED: the bundle's sources have bits above 32.
-// Four rotations of 8 ciphertexts, N = 2^16, E = 32, three digits: 350 -> 315 us, 1.4 GB of compulsory traffic.
+// Four rotations of 8 ciphertexts, N = 2^16, E = 32, three digits: 350 -> 320 us, 1.4 GB of compulsory traffic.
 // The result is packed ([r][b][2][E] limbs in rows order).
 template <int G, typename WK, bool PACKED>
 __global__ __launch_bounds__(256, 4) void inner_product_kernel(const Mod* __restrict__ mods, uint32_t ell, uint32_t E, uint32_t L, uint32_t M,
@@ -214,9 +214,9 @@ void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& 
 // are the OUTER loop and the rotations the inner one, so that between two rotations only one digit's slots are gathered from
 // and about half of them are found in the XCD's L2 (see gather_tile); each key slot is still read once, the plaintext slot
 // once per digit.  The operands of the next (digit, rotation) are requested before the current products.
-// 8 ciphertexts x 16 keyed rotations, three digits, N = 2^16, E = 32: 690 us (28-bit moduli 512), where one thread per slot that
-// walked digits inside rotations and gathered each ciphertext on its own took 1037 (9.6 GB through the fabric, now 4.6 of 7 GB).
-// What bounds it: the stream of keys and plaintexts (2.5 GB; alone 600 us) and fp64 issue (alone 470 us), partly overlapped.
+// 8 ciphertexts x 16 keyed rotations, three digits, N = 2^16, E = 32: 656 us (28-bit moduli 532), where one thread per slot that
+// walked digits inside rotations and gathered each ciphertext on its own took 1037 (9.6 GB through the fabric, now 3.3).
+// What bounds it: the stream of keys and plaintexts (1.9 of 3.1 GB read) and fp64 issue (61 % of the slots), partly overlapped.
 // Three wavefronts per SIMD: squeezed into 128 registers for a fourth, the few spilled words cost more fabric traffic than
 // the occupancy gains (40-100 us more).  Sixteen ciphertexts per launch sharing the key reads measured the same per ciphertext:
 // what the shared keys save, the doubled sources lose in L2.

@@ -287,7 +287,7 @@ void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, 
     const uint32_t tiles = (c->N / 1024) * lv.E;
     const dim3 grid(((tiles + 7) / 8) * 8 * batch), block(64);
     // launches with more than two wavefronts per SIMD (1024 SIMDs) to run take the variant that requests the next digit's
-    // loads early: 3 % faster there (32.1 -> 31.0 us per multiplication at L = 35); the single-ciphertext launch is bound by
+    // loads early (3 % faster there); the single-ciphertext launch is bound by
     // bandwidth and gains nothing from it
     const bool prefetch = grid.x > 2048;
 #define KS_LAUNCH_IP(LOGR, WDT, WKT, PF)                                                                                                 \

@@ -9,8 +9,8 @@
 
 namespace {
 
-// One bootstrapping-level ciphertext (N = 2^16, L = 24, K = 8, dnum = 3: coefficient copy 24 limbs, raised digits 96,
-// accumulators 64, converted limbs 48, packed ciphertext limbs of the accumulators 30 = 262 limbs of 512 KiB).
+// One bootstrapping-level ciphertext (N = 2^16, L = 24, K = 8, dnum = 3), at what ks_workspace_bytes asks for: coefficient copy 24
+// limbs, raised digits 96, accumulators 64, converted limbs 48, 30 more = 262 limbs of 512 KiB (the packed regions fill 145 of them).
 constexpr size_t kStaticScratchBytes = KS_STATIC_WORKSPACE_BYTES;
 constexpr int kMaxDevices = 64;
 
