@@ -90,6 +90,16 @@ KS_HD double mac_reduce(double hi, double lo, Mod m) {
     return reduce_lazy(__builtin_fma(-q, m.p, s) + lo, m);
 }
 
+// The same for moduli below 2^28: 64-bit integer multiply-adds, one instruction a product at the rate of a double-precision FMA.
+// 0 <= x < p and |k| <= p, or |k| <= 0.51 p: kMacTerms or kMacTermsLazy products stay below 2^63, with a start below 2^28.
+KS_HD void mac_int(int32_t x, int32_t k, int64_t& sum) { sum += (int64_t)x * k; }
+// The high word times 2^32 and the low word are both exact doubles; the quotient is at most 250 p < 2^36 in magnitude.
+KS_HD double mac_int_reduce(int64_t sum, Mod m) {
+    const double s = (double)(int32_t)(sum >> 32) * 4294967296.0;
+    const double q = __builtin_rint(s * m.pinv);
+    return reduce_lazy(__builtin_fma(-q, m.p, s) + (double)(uint32_t)sum, m);
+}
+
 // Split an integer-valued |y| < 2^36 into y = y2 + y1 + y0 with y2 a multiple of 2^24 (|y2| <= 2^36), y1 a
 // multiple of 2^12 (|y1| <= 2^23) and |y0| <= 2^11, by rounding to nearest at the two granularities (adding and
 // subtracting 1.5 * 2^(52 + g) rounds to a multiple of 2^g).  Six additions, no products.

@@ -199,6 +199,28 @@ def test_two_piece_conversion_extreme_residues(which, request):
         assert_equal(out, st.ref.keyswitch(host(d), host(evk), ell))
 
 
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("batch,n_rot", [(1, 1), (3, 16), (8, 16), (9, 20)])
+def test_integer_sums_of_the_rotations(batch, n_rot, half):
+    """28-bit moduli in 32-bit words sum their products in 64-bit integers: eight digits and sixteen rotations a launch at the
+    largest products (ciphertexts of modulus - 1, keys of modulus - 1 or, the largest lazy factor, half the modulus)."""
+    st = Setup(12, 8, 1, 8, bits=28)
+    assert max(st.q + st.p) < 1 << 28
+    ell, mods = st.L, torch.tensor(st.q + st.p, dtype=torch.int64, device="cuda")
+    ct = (mods[:ell] - 1).view(1, 1, ell, 1).expand(batch, 2, ell, st.N).contiguous()
+    ct[:, :, :, 1::2] = st.uniform(2010, 1, (batch, 2), list(range(ell)))[:, :, :, 1::2]
+    key = (mods // 2 if half else mods - 1).view(1, 1, -1, 1).expand(8, 2, -1, st.N).contiguous()
+    galois = ks_inputs.galois_elements(st.logN, n_rot)
+    keys, pts = [key] * n_rot, [None] * n_rot
+    out = torch.empty((batch, 2, ell, st.N), dtype=torch.int32, device="cuda")
+    ws = workspace(st.ctx, K.KS_OP_ROTATE_HOISTED_U32, ell, batch, n_rot)
+    K.ks_rotate_mac_hoisted_u32(st.ctx, narrow(ct), ell, galois, [narrow(key)] * n_rot, pts, out, ws)
+    assert_equal(widen(out), st.ref.rotate_mac_hoisted(host(ct), galois, [host(k) for k in keys], pts, ell))
+    out = torch.empty((batch, n_rot, 2, ell, st.N), dtype=torch.int32, device="cuda")
+    K.ks_rotate_hoisted_u32(st.ctx, narrow(ct), ell, galois, [narrow(key)] * n_rot, out, ws)
+    assert_equal(widen(out), st.ref.rotate_hoisted(host(ct), galois, [host(k) for k in keys], ell))
+
+
 @pytest.mark.parametrize("which,ell,batch,n1,n2", [("small28", 4, 2, 3, 2), ("small32", 3, 9, 2, 3), ("boot28", 24, 2, 3, 2)])
 def test_bsgs_linear_transform(which, ell, batch, n1, n2, request):
     """Both hoisting levels with keys, plaintexts, ciphertexts and result in 32-bit words; the identity element (no key)
