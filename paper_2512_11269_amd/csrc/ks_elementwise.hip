@@ -303,7 +303,8 @@ __global__ __launch_bounds__(256, INT ? 4 : 3) void rotate_mac_kernel(const Mod*
     if (n_key != 0) qa = fetch(0, 0);
     // The plaintext slots are used once per digit and once more for c0: each thread keeps its own in LDS (a null plaintext is the
     // constant 1).  Read from memory every time they were 0.8 of 3.3 GB of a launch.
-    __shared__ double pts[kMacRotations][256];
+    extern __shared__ uint64_t pts_lds[];
+    auto pts = [&](uint32_t r) { return reinterpret_cast<WK*>(pts_lds) + r * 256 + threadIdx.x; };
 #pragma unroll 1
     for (uint32_t r0 = 0; r0 < rot.n; r0 += 8) {
         WK w[8];
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(256, INT ? 4 : 3) void rotate_mac_kernel(const Mod*
             w[i] = pt ? buffer_load<WK>(uniform_rsrc(pt, (uint64_t)M * N * sizeof(WK)), n * (uint32_t)sizeof(WK), mid * N * (uint32_t)sizeof(WK)) : (WK)1;
         }
 #pragma unroll
-        for (uint32_t i = 0; i < 8; ++i) pts[(r0 + i) & (kMacRotations - 1)][threadIdx.x] = word_to_f64<WK>(w[i]);
+        for (uint32_t i = 0; i < 8; ++i) *pts(r0 + i) = w[i];
     }
     if (n_key != 0) {
         const uint32_t steps = dg.ndig * n_key;
@@ -324,7 +325,7 @@ __global__ __launch_bounds__(256, INT ? 4 : 3) void rotate_mac_kernel(const Mod*
         };
         auto products = [&](const Raw& q, uint32_t rq) {
             // the plaintext slot is folded into the key slots, not multiplied per ciphertext
-            const double w = pts[rq][threadIdx.x];
+            const double w = word_to_f64<WK>(*pts(rq));
             const Factor k0 = Sum::factor(mulmod_lazy(word_to_f64<WK>(q.k0), w, m)), k1 = Sum::factor(mulmod_lazy(word_to_f64<WK>(q.k1), w, m));
             const SlotRaw<G> s = slot_take<G, PACKED>(q.x);
 #pragma unroll
@@ -360,7 +361,7 @@ __global__ __launch_bounds__(256, INT ? 4 : 3) void rotate_mac_kernel(const Mod*
                 WC x[G];
 #pragma unroll
                 for (int b = 0; b < G; ++b) x[b] = cp[b * src.c0_ps];
-                const Factor pw = Sum::factor(mulmod_lazy(pm, pts[r][threadIdx.x], m));
+                const Factor pw = Sum::factor(mulmod_lazy(pm, word_to_f64<WK>(*pts(r)), m));
 #pragma unroll
                 for (int b = 0; b < G; ++b) s0[b].add(Sum::template word<WC>(x[b]), pw);
             }
@@ -377,7 +378,7 @@ __global__ __launch_bounds__(256, INT ? 4 : 3) void rotate_mac_kernel(const Mod*
             for (uint32_t r0 = 0; r0 < rot.n; r0 += AHEAD) {
 #pragma unroll
                 for (uint32_t i = 0; i < AHEAD; ++i) {
-                    const Factor pw = Sum::factor(mulmod_lazy(r0 + i < rot.n ? pm : 0.0, pts[(r0 + i) & (kMacRotations - 1)][threadIdx.x], m));
+                    const Factor pw = Sum::factor(mulmod_lazy(r0 + i < rot.n ? pm : 0.0, word_to_f64<WK>(*pts(r0 + i)), m));
                     const SlotRaw<G> s = slot_take<G, PACKED>(x[i]);
 #pragma unroll
                     for (int b = 0; b < G; ++b) s0[b].add(Sum::template source<G, PACKED>(s, b), pw);
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(256, INT ? 4 : 3) void rotate_mac_kernel(const Mod*
 #pragma unroll 1
         for (uint32_t r = n_key; r < rot.n; ++r) {
             const SlotRaw<G> x = slot_load<G, PACKED>(bundle, own * E + pos, N, n);
-            const Factor pw = Sum::factor(mulmod_lazy(pm, pts[r][threadIdx.x], m));
+            const Factor pw = Sum::factor(mulmod_lazy(pm, word_to_f64<WK>(*pts(r)), m));
 #pragma unroll
             for (int b = 0; b < G; ++b) s1[b].add(Sum::template source<G, PACKED>(x, b), pw);
         }
@@ -430,8 +431,11 @@ void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src
     const double reads = batch * src_bytes(src) * (lv.ndig * lv.E + lv.ell) + (key_words32 ? 4.0 : 8.0) * (double)rot.n * (2.0 * lv.ndig + 1.0) * lv.E;
     ProfScope ps("rotate_mac", (reads + (double)batch * 10 * lv.E * (accumulate ? 2 : 1)) * c->N, s,
                  (double)rot.n * lv.E * c->N * (4.0 * batch + 6.0) * (2 * lv.ndig + 1));
+    // LDS for the plaintext slots, in rows of eight rotations: 16 KB a workgroup for five rotations in 64-bit words leave the small groups
+    // the occupancy that a fixed 32 KB took from them (one ciphertext, 17 limbs, 28 bits: 76 -> 55 us; 36 bits 105 -> 92)
+    const uint32_t lds_words = (rot.n + 7) / 8 * 8 * 256;
 #define KS_GATHER_LAUNCH(GV, WKT, PK, IS)                                                                                                     \
-    hipLaunchKernelGGL((rotate_mac_kernel<GV, WKT, PK, IS>), dim3(gather_grid(c, lv.E, pl)), dim3(256), 0, s, c->d_mod, c->d_Pmod, lv.ell, lv.E, \
+    hipLaunchKernelGGL((rotate_mac_kernel<GV, WKT, PK, IS>), dim3(gather_grid(c, lv.E, pl)), dim3(256), lds_words * sizeof(WKT), s, c->d_mod, c->d_Pmod, lv.ell, lv.E, \
                        c->L, c->M, c->logN, dg, pl, src, sorted, n_key, u, accumulate ? 1 : 0)
     KS_FOR_GATHER_KERNEL()
 #undef KS_GATHER_LAUNCH
