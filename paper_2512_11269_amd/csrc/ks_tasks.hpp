@@ -341,6 +341,12 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
                     x.w[k] = t;
                 }
             }
+            // Both branches write every entry: stores of 16 here and 20 there are merged into one with a variable index, which keeps the
+            // array in scratch memory (28-bit key-switches, N = 2^16, 17 limbs: one 81.0 -> 79.4 us without it, 16 733 -> 715).
+            if constexpr (sizeof(WD) == 4) {
+#pragma unroll
+                for (int k = 16; k < 20; ++k) x.w[k] = 0;
+            }
         } else {
             const PackedRaw t = packed_load<64>(lifted_b + ((uint64_t)j * E + pos) * LIMB, N, at);
 #pragma unroll
