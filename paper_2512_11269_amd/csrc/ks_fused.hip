@@ -207,13 +207,9 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
         launch_bconv_mfma_ntt_cols(c, plans, y, y_ps, out, out_ps, n_polys, tl, tile == 16, s);
         return;
     }
-    // Targets per workgroup: fewer targets = more workgroups and a shorter chain in each, but more re-reads and re-cuts of the sources.
-    // Key-switches of random shapes, one and two targets against three by workgroups of one target: below 256 -13 and -6 %, 512 to
-    // 1024 -4 and -3, 1024 to 2048 +0.2 and -1.9, 4096 to 8192 +6 and 0, above +10 and +2, four there -0.2.
-    // The context option KS_OPT_BCONV_TARGETS overrides the choice.
+    // Targets per workgroup; the context option KS_OPT_BCONV_TARGETS overrides the choice.
     const uint32_t tiles = 1u << (c->logN - 12);
-    const uint64_t ones = (uint64_t)tiles * n_plans * max_targets * n_polys;
-    const int ts = c->opt[KS_OPT_BCONV_TARGETS] ? c->opt[KS_OPT_BCONV_TARGETS] : ones <= 1024 ? 1 : ones <= 8192 ? 2 : 4;
+    const int ts = c->opt[KS_OPT_BCONV_TARGETS] ? c->opt[KS_OPT_BCONV_TARGETS] : vector_conversion_targets(plans, tiles, n_polys);
     const uint32_t n_subsets = (max_targets + ts - 1) / ts;
     const dim3 grid(tiles, n_plans * n_subsets, n_polys), block(256);
     ProfScope ps("bconv_ntt_cols", (double)limbs_moved_per_poly * n_polys * packed_limb_bytes(c->N), s, ops_per_coeff * n_polys * c->N);

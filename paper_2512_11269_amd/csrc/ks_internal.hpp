@@ -92,6 +92,16 @@ struct PlanSet {
     LaunchMeta meta{};
 };
 
+// Targets that a workgroup of the vector conversion takes: fewer targets = more workgroups and a shorter chain in each, but more re-reads
+// and re-cuts of the sources.  Key-switches of random shapes, one and two targets against three by workgroups of one target: below 256
+// -13 and -6 %, 512 to 1024 -4 and -3, 1024 to 2048 +0.2 and -1.9, 4096 to 8192 +6 and 0, above +10 and +2, four there -0.2.
+//   Digits of different sizes have different numbers of targets: the workgroups counted are those that have work, not the digits times
+// the largest number (110 key-switches on whose ModUp the two counts disagree: 0.2 to 4.4 % less time, 28 bits 8 / 8 / 1 -> 24 79.3 -> 76.8 us).
+inline int vector_conversion_targets(const PlanSet& plans, uint32_t tiles, uint32_t n_polys) {
+    const uint64_t ones = (uint64_t)tiles * plans.targets * n_polys;
+    return ones <= 1024 ? 1 : ones <= 8192 ? 2 : 4;
+}
+
 // Everything the key-switching pipeline needs at one level ell.
 struct Level {
     uint32_t ell = 0, ndig = 0, E = 0;     // E = ell + K extended limb count

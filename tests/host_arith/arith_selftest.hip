@@ -4,6 +4,7 @@
 #include <stdlib.h>
 #include <math.h>
 #include <stdint.h>
+#include "../../paper_2512_11269_amd/csrc/ks_internal.hpp"
 #include "../../paper_2512_11269_amd/csrc/ks_tiles.hpp"
 
 using namespace ks;
@@ -192,8 +193,30 @@ static void check_gather_parts() {
     }
 }
 
+// The targets per workgroup of a conversion follow from the workgroups that have work: digits of different sizes and of one size alike
+// that hold the same number of targets.
+static void check_conversion_targets() {
+    const uint32_t lines[] = {1024, 8192};
+    const int below[] = {1, 2}, above[] = {2, 4};
+    for (int i = 0; i < 2; ++i)
+        for (uint32_t tiles = 1; tiles <= 16; tiles *= 2)
+            for (uint32_t plans = 1; plans <= 4; ++plans)
+                for (uint32_t most = 1; most <= 40; ++most)
+                    for (uint32_t last = plans == 1 ? most : 1; last <= most; ++last) {
+                        PlanSet set;
+                        set.n_plans = plans;
+                        set.max_targets = most;
+                        set.targets = (plans - 1) * most + last;
+                        const uint32_t per_poly = tiles * set.targets, polys = lines[i] / per_poly;
+                        if (polys == 0 || per_poly > lines[i]) continue;
+                        CHECK(vector_conversion_targets(set, tiles, polys) == below[i], "%u plans of %u and %u targets, %u tiles, %u polynomials", plans, most, last, tiles, polys);
+                        CHECK(vector_conversion_targets(set, tiles, polys + 1) == above[i], "%u plans of %u and %u targets, %u tiles, %u polynomials", plans, most, last, tiles, polys + 1);
+                    }
+}
+
 int main() {
     check_gather_parts();
+    check_conversion_targets();
     const uint64_t primes[] = {68718428161ull /* largest, N=2^16 */, 68617633793ull /* 60th, N=2^16 */, 68719403009ull /* largest, N=2^12 */,
                                68718764033ull /* 6th, N=2^12 */, 34359754753ull /* a 35-bit prime = 1 mod 2^17 */,
                                // the rest of the admitted range: the paper's word size, the top of the 32-bit range, a tiny modulus
