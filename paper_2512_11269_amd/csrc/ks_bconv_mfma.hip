@@ -25,10 +25,13 @@ namespace ks {
 
 // Workgroups per compute unit the register allocation must leave room for: without a bound the scheduler hoists the
 // matrix instructions of all 16 positions (256 result registers) and the kernel drops to one wavefront per SIMD.
-constexpr int mfma_min_blocks(int tl) { return tl == 1 ? 4 : 2; }
+// Four where the registers of one target fit into 128: nine sources a half need more and, as four workgroups, spilled 22
+// (key-switch 15 -> 30 moduli, N = 2^16: 116.0 us, three 108.2; 15 -> 15 at N = 2^15 53.8 and 50.3; seven sources a half are
+// 1 % ahead with four).
+constexpr int mfma_min_blocks(int tl, int t) { return tl == 1 ? (t <= 7 ? 4 : 3) : 2; }
 
 template <int LOG_R, int TL, int T, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? mfma_min_blocks(TL) : 1) void bconv_mfma_ntt_cols(const double* __restrict__ tw, const BConvPlan* __restrict__ plans,
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? mfma_min_blocks(TL, T) : 1) void bconv_mfma_ntt_cols(const double* __restrict__ tw, const BConvPlan* __restrict__ plans,
                                                            LaunchMeta meta, const uint8_t* __restrict__ y, uint64_t y_ps,
                                                            uint8_t* __restrict__ out, uint64_t out_ps, uint32_t n_polys, uint32_t n_subsets, uint32_t pair) {
     using Shape = MfmaConvShape<LOG_R, TL, WAVES>;
@@ -65,7 +68,7 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
     // the first an eighth less (its sources arrive under the butterflies of the one before; factors and twiddles are there): four hoisted
     // rotations of eight ciphertexts, 64 polynomials 8 -> 24, 269 -> 241 us; 16 polynomials 90 -> 84; 13 -> 34, which pays for the loop with
     // scratch registers, 136 -> 133.
-    const uint32_t slots = waves == 8 ? 256 : tl == 1 ? 1024 : 512, per_poly = tiles * n_plans * n_subsets;
+    const uint32_t slots = waves == 8 ? 256 : 256 * mfma_min_blocks(tl, (int)t), per_poly = tiles * n_plans * n_subsets;
     uint32_t groups = n_polys;
     double least = 1e30;
     for (uint32_t z = (n_polys + 7) / 8; z <= n_polys; ++z) {

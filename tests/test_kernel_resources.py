@@ -46,8 +46,11 @@ def scratch(tmp_path_factory):
     return found
 
 
-@pytest.mark.parametrize("kernel", ["rows_inner_product"])
+@pytest.mark.parametrize("kernel", [
+    r"rows_inner_product",
+    r"bconv_mfma_ntt_colsILi\dELi1ELi9E",      # one target per lane half, nine sources a half
+])
 def test_no_scratch_memory(scratch, kernel):
-    of_kernel = {name: size for name, size in scratch.items() if re.search(r"\d%s(I|E)" % kernel, name)}
+    of_kernel = {name: size for name, size in scratch.items() if re.search(r"\d" + kernel, name)}
     assert of_kernel
     assert not {name: size for name, size in of_kernel.items() if size}
