@@ -13,7 +13,7 @@
 namespace ks {
 
 // Transforms of limbs of 64-bit words, in place.  Between the two passes a limb is packed inside its own bytes
-// (in_place_offsets), 26 bytes moved per residue instead of 32.
+// (in_place_offsets), 26 bytes moved per residue instead of 32; PACKED = false: doubles in the words' places (transform_packed).
 __device__ __forceinline__ uint64_t* locate(const LimbMap& map, uint32_t li, uint64_t* data, uint64_t ps, uint32_t N, uint32_t* mod_id) {
     const uint32_t poly = li / map.n, idx = li - poly * map.n;
     *mod_id = map.mod[idx];
@@ -21,7 +21,7 @@ __device__ __forceinline__ uint64_t* locate(const LimbMap& map, uint32_t li, uin
 }
 
 // forward, columns: canonical words in, packed lazy representatives out (|x| <= (1 + 0.501 log2 R) p).
-template <int LOG_R, int TC>
+template <int LOG_R, int TC, bool PACKED>
 __global__ __launch_bounds__((TC << LOG_R) / 16) void ntt_fwd_cols(const double* __restrict__ tw, const Mod* __restrict__ mods, LimbMap map,
                                                         uint64_t* data, uint64_t ps) {
     constexpr uint32_t N = 256u << LOG_R, TILES = 256 / TC;
@@ -37,12 +37,17 @@ __global__ __launch_bounds__((TC << LOG_R) / 16) void ntt_fwd_cols(const double*
     for (int k = 0; k < 16; ++k) v[k] = u64_to_f64(limb[col_row_strided<LOG_R>(r0, k) * 256 + col]);
     load_col_twiddles<LOG_R>(t, tw + (size_t)mod_id * N, r0);
     col_fwd_core<LOG_R, TC>(v, t, c, r0, lds, m);
-    tile_loaded<LOG_R>(v);
-    in_place_store_cols<TC>(limb, r0, col, pack(v));
+    if constexpr (PACKED) {
+        tile_loaded<LOG_R>(v);
+        in_place_store_cols<TC>(limb, r0, col, pack(v));
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) limb[col_row_grouped<LOG_R>(r0, k) * 256 + col] = __builtin_bit_cast(uint64_t, v[k]);
+    }
 }
 
 // forward, rows: packed in, canonical words out.  One wavefront = four rows.  TC: columns of a tile of the column pass.
-template <int LOG_R, int TC>
+template <int LOG_R, int TC, bool PACKED>
 __global__ __launch_bounds__(64) void ntt_fwd_rows(TwTables tw, const Mod* __restrict__ mods, LimbMap map, uint64_t* data, uint64_t ps) {
     constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R, GROUPS = R / 4;
     __shared__ double lds[4 * kRowPitch];
@@ -54,16 +59,22 @@ __global__ __launch_bounds__(64) void ntt_fwd_rows(TwTables tw, const Mod* __res
     uint64_t* p = limb + row * 256 + j0;
     double v[16];
     PassTwiddles t;
-    const PackedRaw raw = in_place_load_rows<TC>(limb, rg, lane);
-    load_row_twiddles(t, tw, mod_id, N, R + row, j0, m);
-    unpack_rows(raw, v);
+    if constexpr (PACKED) {
+        const PackedRaw raw = in_place_load_rows<TC>(limb, rg, lane);
+        load_row_twiddles(t, tw, mod_id, N, R + row, j0, m);
+        unpack_rows(raw, v);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = __builtin_bit_cast(double, p[16 * k]);
+        load_row_twiddles(t, tw, mod_id, N, R + row, j0, m);
+    }
     row_fwd_core(v, t, j0, lds + rr * kRowPitch, m);
 #pragma unroll
     for (int k = 0; k < 16; ++k) p[16 * k] = f64_to_u64(canon(reduce_lazy(v[k], m), m));
 }
 
 // inverse, rows first: canonical words in, packed lazy representatives out (|x| <= 0.501 p).
-template <int LOG_R, int TC>
+template <int LOG_R, int TC, bool PACKED>
 __global__ __launch_bounds__(64) void ntt_inv_rows(TwTables twi, const Mod* __restrict__ mods, LimbMap map, uint64_t* data, uint64_t ps) {
     constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R, GROUPS = R / 4;
     __shared__ double lds[4 * kRowPitch];
@@ -72,18 +83,23 @@ __global__ __launch_bounds__(64) void ntt_inv_rows(TwTables twi, const Mod* __re
     uint64_t* limb = locate(map, li, data, ps, N, &mod_id);
     const Mod m = mods[mod_id];
     const uint32_t j0 = lane & 15, rr = lane >> 4, row = rg * 4 + rr;
-    const uint64_t* p = limb + row * 256 + j0;
+    uint64_t* p = limb + row * 256 + j0;
     double v[16];
     PassTwiddles t;
 #pragma unroll
     for (int k = 0; k < 16; ++k) v[k] = u64_to_f64(p[16 * k]);
     load_row_twiddles(t, twi, mod_id, N, R + row, j0, m);
     row_inv_core(v, t, j0, lds + rr * kRowPitch, m);
-    in_place_store_rows<TC>(limb, rg, lane, pack_rows(v));
+    if constexpr (PACKED) {
+        in_place_store_rows<TC>(limb, rg, lane, pack_rows(v));
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) p[16 * k] = __builtin_bit_cast(uint64_t, v[k]);
+    }
 }
 
 // inverse, columns last: packed in; out = canonical [x N^-1]_m in words.
-template <int LOG_R, int TC>
+template <int LOG_R, int TC, bool PACKED>
 __global__ __launch_bounds__((TC << LOG_R) / 16) void ntt_inv_cols(const double* __restrict__ twi, const Mod* __restrict__ mods,
                                                         const double* __restrict__ ninv, LimbMap map, uint64_t* data, uint64_t ps) {
     constexpr uint32_t N = 256u << LOG_R, TILES = 256 / TC;
@@ -96,11 +112,17 @@ __global__ __launch_bounds__((TC << LOG_R) / 16) void ntt_inv_cols(const double*
     const uint32_t c = tid & (TC - 1), r0 = tid / TC, col = tile * TC + c;
     double v[16];
     PassTwiddles t;
-    const PackedRaw raw = in_place_load_cols<TC>(limb, r0, col);
-    load_col_twiddles<LOG_R>(t, twi + (size_t)mod_id * N, r0);
-    unpack(raw, v);
+    if constexpr (PACKED) {
+        const PackedRaw raw = in_place_load_cols<TC>(limb, r0, col);
+        load_col_twiddles<LOG_R>(t, twi + (size_t)mod_id * N, r0);
+        unpack(raw, v);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = __builtin_bit_cast(double, limb[col_row_grouped<LOG_R>(r0, k) * 256 + col]);
+        load_col_twiddles<LOG_R>(t, twi + (size_t)mod_id * N, r0);
+    }
     col_inv_core<LOG_R, TC>(v, t, c, r0, lds, m);
-    tile_loaded<LOG_R>(v);
+    if constexpr (PACKED) tile_loaded<LOG_R>(v);
 #pragma unroll
     for (int k = 0; k < 16; ++k) limb[col_row_strided<LOG_R>(r0, k) * 256 + col] = f64_to_u64(canon(mulmod_lazy(v[k], scale, m), m));
 }
@@ -354,33 +376,52 @@ static uint32_t polys_per_group(const ks_ctx* c, const LimbMap& map) {
     return (uint32_t)std::max<uint64_t>(1, kGroupBytes / poly_bytes);
 }
 
+// Whether a launch of the 64-bit transforms packs its limbs between the two passes.  Not at N <= 2^14 for data of about what the eight
+// L2s hold together (32 MB): the second pass, which writes whole limbs and then has read five eighths of their lines, takes 2 to 4.5 us
+// longer there, more than the first one gains.  Calls as doubles / packed, us, by MiB of data (elsewhere packed is up to 18 % ahead):
+//   inverse, N = 2^12: 18 25.2 / 24.7, 21 24.5 / 26.1, 23 23.6 / 25.9, 27 24.3 / 24.9, 32 24.6 / 24.4; N = 2^13: 17 31.5 / 30.1, 21 25.6 / 30.7,
+// 24 22.7 / 26.2, 32 24.6 / 28.1, 36 28.8 / 28.5; N = 2^14: 18 28.4 / 27.6, 19 27.7 / 28.0, 27 25.8 / 27.9, 35 28.1 / 28.6, 36 28.6 / 28.5
+//   forward, N = 2^12: 20 24.9 / 24.8, 23 23.5 / 25.2, 26 24.6 / 24.6; N = 2^13: 18 25.2 / 24.7, 21 22.5 / 25.4, 25 24.0 / 24.7, 26 25.4 / 23.5;
+// N = 2^14: 18 27.1 / 26.9, 22 24.9 / 26.8, 32 24.7 / 25.4, 34 28.0 / 27.6
+//   N = 2^15: between +2.6 and -4 % for the packed form, 2^16 always ahead.
+static bool transform_packed(const ks_ctx* c, uint32_t limbs, bool inverse) {
+    if (c->logN > 14) return true;
+    const uint64_t bytes = 8ull * limbs * c->N, mib = 1 << 20;
+    const uint64_t most = inverse ? (c->logN == 12 ? 28 : 35) : (c->logN == 14 ? 33 : 25);
+    return bytes < 19 * mib || bytes > most * mib;
+}
+
 void launch_ntt(const ks_ctx* c, const LimbMap& map, uint64_t* data, uint64_t ps_words, uint32_t n_polys, bool inverse, hipStream_t s) {
     const uint32_t g = polys_per_group(c, map);
     for (uint32_t p0 = 0; p0 < n_polys; p0 += g) {
         const uint32_t limbs = map.n * std::min(g, n_polys - p0);
         uint64_t* part = data + (uint64_t)p0 * ps_words;
-        const double bytes = 13.0 * limbs * c->N;
-#define KS_LAUNCH_TC(LOGR, TCV)                                                                                                       \
-    {                                                                                                                                 \
-        const dim3 cols(limbs * (256 / TCV)), cols_block((TCV << LOGR) / 16), rows(limbs << (LOGR - 2)), rows_block(64);              \
-        if (!inverse) {                                                                                                               \
-            {                                                                                                                         \
-                ProfScope ps("ntt_fwd_cols", bytes, s);                                                                               \
-                hipLaunchKernelGGL((ntt_fwd_cols<LOGR, TCV>), cols, cols_block, 0, s, c->d_tw_fwd, c->d_mod, map, part, ps_words);    \
-            }                                                                                                                         \
-            ProfScope ps("ntt_fwd_rows", bytes, s);                                                                                   \
-            hipLaunchKernelGGL((ntt_fwd_rows<LOGR, TCV>), rows, rows_block, 0, s, c->tw_fwd, c->d_mod, map, part, ps_words);          \
-        } else {                                                                                                                      \
-            {                                                                                                                         \
-                ProfScope ps("ntt_inv_rows", bytes, s);                                                                               \
-                hipLaunchKernelGGL((ntt_inv_rows<LOGR, TCV>), rows, rows_block, 0, s, c->tw_inv, c->d_mod, map, part, ps_words);      \
-            }                                                                                                                         \
-            ProfScope ps("ntt_inv_cols", bytes, s);                                                                                   \
-            hipLaunchKernelGGL((ntt_inv_cols<LOGR, TCV>), cols, cols_block, 0, s, c->d_tw_inv, c->d_mod, c->d_ninv, map, part, ps_words); \
-        }                                                                                                                             \
+        const bool packed = transform_packed(c, limbs, inverse);
+        const double bytes = (packed ? 13.0 : 16.0) * limbs * c->N;
+#define KS_LAUNCH_TC(LOGR, TCV, PK)                                                                                                       \
+    {                                                                                                                                     \
+        const dim3 cols(limbs * (256 / TCV)), cols_block((TCV << LOGR) / 16), rows(limbs << (LOGR - 2)), rows_block(64);                  \
+        if (!inverse) {                                                                                                                   \
+            {                                                                                                                             \
+                ProfScope ps("ntt_fwd_cols", bytes, s);                                                                                   \
+                hipLaunchKernelGGL((ntt_fwd_cols<LOGR, TCV, PK>), cols, cols_block, 0, s, c->d_tw_fwd, c->d_mod, map, part, ps_words);    \
+            }                                                                                                                             \
+            ProfScope ps("ntt_fwd_rows", bytes, s);                                                                                       \
+            hipLaunchKernelGGL((ntt_fwd_rows<LOGR, TCV, PK>), rows, rows_block, 0, s, c->tw_fwd, c->d_mod, map, part, ps_words);          \
+        } else {                                                                                                                          \
+            {                                                                                                                             \
+                ProfScope ps("ntt_inv_rows", bytes, s);                                                                                   \
+                hipLaunchKernelGGL((ntt_inv_rows<LOGR, TCV, PK>), rows, rows_block, 0, s, c->tw_inv, c->d_mod, map, part, ps_words);      \
+            }                                                                                                                             \
+            ProfScope ps("ntt_inv_cols", bytes, s);                                                                                       \
+            hipLaunchKernelGGL((ntt_inv_cols<LOGR, TCV, PK>), cols, cols_block, 0, s, c->d_tw_inv, c->d_mod, c->d_ninv, map, part, ps_words); \
+        }                                                                                                                                 \
     }
-#define KS_LAUNCH(LOGR) KS_LAUNCH_TC(LOGR, (4096 >> LOGR))
-        if (c->logN == 16 && wide_tiles(limbs)) KS_LAUNCH_TC(8, 32)
+#define KS_LAUNCH(LOGR)                                                     \
+    if constexpr (LOGR > 6) KS_LAUNCH_TC(LOGR, (4096 >> LOGR), true)        \
+    else if (packed) KS_LAUNCH_TC(LOGR, (4096 >> LOGR), true)               \
+    else KS_LAUNCH_TC(LOGR, (4096 >> LOGR), false)
+        if (c->logN == 16 && wide_tiles(limbs)) KS_LAUNCH_TC(8, 32, true)
         else KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
 #undef KS_LAUNCH_TC
