@@ -126,6 +126,24 @@ KS_HD void split2(double y, double& y1, double& y0) {
     y0 = y - y1;
 }
 
+// The fused conversion takes the 40 bits of y + 0x80808080 (|y| < 2^36; low word w, signed byte `top`) apart as they lie in memory.
+// Three pieces: the low 12 bits, the next 12 in place and what is left shifted down by 24, against f_0, f_1 as above and 2^24 f_2:
+// products of at most 2^47, 2^47 and 2^47.1.  Two (|y| < 2^32): the low 16 bits and the rest, against f_0 and 2^16 f_1, 2^47 and
+// 1.5 * 2^47.  Those of seventeen sources and a start below 2^35, which takes the constants out, stay below 2^52.8.
+template <int PIECES>
+KS_HD void cut_source(uint32_t w, int top, double (&p)[PIECES]) {
+    static_assert(PIECES == 2 || PIECES == 3, "pieces of a source");
+    const uint64_t bits = (uint64_t)(uint32_t)top << 32 | w;
+    if constexpr (PIECES == 3) {
+        p[0] = (double)(w & 0xFFFu);
+        p[1] = (double)(w & 0xFFF000u);
+        p[2] = (double)(int)(uint32_t)(bits >> 24);
+    } else {
+        p[0] = (double)(w & 0xFFFFu);
+        p[1] = (double)(int)(uint32_t)(bits >> 16);
+    }
+}
+
 // Representative in (-p, p) -> canonical [0, p).
 KS_HD double canon(double r, Mod m) { return r < 0.0 ? r + m.p : r; }
 

@@ -34,7 +34,7 @@ __device__ __forceinline__ SourceRaw load_source(BufferRsrc rsrc, uint32_t limb,
 
 // One source of a conversion: acc[t][k] += (y[k] + 0x80808080) * f[t] as exact integers (the constant is taken out by what acc
 // starts from).  The 40 bits of a source point are cut once into PIECES whole numbers, every target adds PIECES products
-// against its centred factors; the bounds of these sums are stated at BConvPlan::hats.
+// against its centred factors; the bounds of these sums are stated at cut_source.
 template <int TS, int PIECES>
 __device__ __forceinline__ void bconv_accumulate(double (&acc)[TS][16], const SourceRaw& y, const double (&f)[TS][3]) {
 #pragma unroll
@@ -42,14 +42,7 @@ __device__ __forceinline__ void bconv_accumulate(double (&acc)[TS][16], const So
         const uint32_t w = y.lo[k >> 2].w[k & 3];
         const int top = (int)(y.top.w[k >> 2] << (24 - 8 * (k & 3))) >> 24;
         double p[PIECES];
-        if constexpr (PIECES == 3) {
-            p[0] = (double)(w & 0xFFFu);
-            p[1] = (double)(w & 0xFFF000u);
-            p[2] = (double)(int)__builtin_amdgcn_alignbit((uint32_t)top, w, 24);
-        } else {
-            p[0] = (double)(w & 0xFFFFu);
-            p[1] = (double)(int)__builtin_amdgcn_alignbit((uint32_t)top, w, 16);
-        }
+        cut_source<PIECES>(w, top, p);
 #pragma unroll
         for (int tt = 0; tt < TS; ++tt)
 #pragma unroll

@@ -48,10 +48,7 @@ struct BConvPlan {
     uint32_t dst_mod_id[kMaxDst];  // modulus id of each target (selects its twiddle table)
     // hats[t][i][k], k = 0..2: centred([(D / s_i) 2^(12 k)]_t) * 2^(-12 k), the factors that go with the three pieces
     // of a split source residue (split3; two pieces and 16 bits where every modulus is below 2^32).  Zero for padding sources.
-    // The fused vector kernel takes y + 0x80808080 (kDigitBias) apart into the low 12 bits, the next 12 in place and what is left
-    // shifted down by 24: factors [0], [1] and [3] = [2] * 2^24.  Products are whole numbers of at most 2^47 (2^12 2^35, 2^24 2^23,
-    // 2^12.1 2^35): three for each of seventeen sources stay below 2^52.8.  With two pieces: the low 16 bits and the rest, [0] and
-    // [3] = [1] * 2^16, 2^16 2^31 and 1.5 2^16 2^31, 2^52.5 in all.
+    // The fused vector kernel (cut_source) uses [0], [1] and [3] = [2] * 2^24; with two pieces [0] and [3] = [1] * 2^16.
     double hats[kMaxDst][kMaxSrc][4];
     // centred(-0x80808080 sum_i [D / s_i]_t), which takes the constant out of the sum
     double dst_start[kMaxDst];

@@ -1,9 +1,11 @@
 // Host-side check of the library's double-precision modular arithmetic (ks_device.hpp) against exact
-// 128-bit integer arithmetic.  Runs entirely on the CPU; prints "OK" and exits 0 when every bound holds.
+// 128-bit integer arithmetic, and of the conversion tables that the built library makes.  Runs entirely on the CPU; prints "OK" and exits 0 when every bound holds.
 #include <stdio.h>
 #include <stdlib.h>
 #include <math.h>
 #include <stdint.h>
+#include <string.h>
+#include <vector>
 #include "../../paper_2512_11269_amd/csrc/ks_internal.hpp"
 #include "../../paper_2512_11269_amd/csrc/ks_tiles.hpp"
 
@@ -82,6 +84,25 @@ static void check_prime(uint64_t p) {
         CHECK((i128)(hi - kMacBias) + (i128)(int64_t)lo == exact, "mac_exact sum");
         const double r = mac_reduce(hi, lo, m);
         CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "mac_reduce");
+    }
+    // mac_int (moduli below 2^28): the same with 64-bit integers, to both ends of their range
+    for (int rep = 0; rep < 3000 && p < (1ull << 28); ++rep) {
+        const int terms = rep % 3 == 0 ? kMacTermsLazy : kMacTerms;
+        int64_t sum = rep % 7 == 0 ? (1ll << 28) - 1 : rep % 7 == 1 ? -(1ll << 28) + 1 : rnd_signed(29);
+        i128 exact = sum;
+        for (int i = 0; i < terms; ++i) {
+            int64_t x = (int64_t)(rnd() % p), k = (int64_t)(rnd() % p);
+            if (rep % 5 == 0) x = p - 1;
+            if (rep % 3 == 0) k = rep % 5 == 0 ? (int64_t)(0.51 * p) * (rep & 1 ? -1 : 1) : k / 2 - (int64_t)(p / 4);
+            else if (rep % 5 == 0) k = rep & 1 ? -(int64_t)p : (int64_t)p;
+            mac_int((int32_t)x, (int32_t)k, sum);
+            exact += (i128)x * k;
+        }
+        CHECK((i128)sum == exact, "mac_int sum of %d terms", terms);
+        const double q = __builtin_rint((double)(int32_t)(sum >> 32) * 4294967296.0 * m.pinv);
+        CHECK(fabs(q) <= 250.0 * (double)p && fabs(q) < 68719476736.0, "mac_int quotient");
+        const double r = mac_int_reduce(sum, m);
+        CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "mac_int_reduce");
     }
     // split3: the pieces add up, have the stated granularity and magnitude; with the centred shifted factors, seventeen
     // sources accumulate exactly and reduce to sum y_i f_i mod p
@@ -185,6 +206,93 @@ static void check_prime(uint64_t p) {
     }
 }
 
+// Primes = 1 (mod 2^13) below 2^bits, largest first.
+static std::vector<uint64_t> primes_below(int bits, int count) {
+    std::vector<uint64_t> found;
+    for (uint64_t p = (1ull << bits) - 8191; (int)found.size() < count; p -= 8192) {
+        bool prime = true;
+        for (uint64_t d = 3; prime && d * d <= p; d += 2) prime = p % d != 0;
+        if (prime) found.push_back(p);
+    }
+    return found;
+}
+
+// The fused conversions as the kernels compute them, from the library's own tables: sources in the bytes that they have in memory, summed
+// in doubles (cut_source) and as the digit planes of the matrix cores, against sum y_i f_i.
+template <int PIECES>
+static void check_conversion(int bits, uint32_t n_src, uint32_t n_extra) {
+    const uint32_t n_dst = 9, n_basis = n_src - n_extra;
+    ks_ctx c;
+    c.mod = primes_below(bits, (int)(n_src + n_dst));
+    c.pieces = PIECES;
+    std::vector<uint32_t> src, dst;
+    std::vector<uint16_t> src_limb, dst_limb;
+    for (uint32_t i = 0; i < n_src; ++i) { src.push_back(i); src_limb.push_back((uint16_t)i); }
+    for (uint32_t t = 0; t < n_dst; ++t) { dst.push_back(n_src + t); dst_limb.push_back((uint16_t)t); }
+    std::vector<BConvPlan> plans(1);
+    BConvPlan& plan = plans[0];
+    fill_bconv_plan(&c, &plan, src.data(), src_limb.data(), n_src, dst.data(), dst_limb.data(), n_dst, 0, n_extra);
+    // the largest sum that the cut admits: every piece and every factor at its end
+    const double f = ldexp(1.0, bits - 1), most = PIECES == 3 ? 4095 * f + 16773120.0 * f / 4096 + (4096 + 128) * f : 65535 * f + (65536 + 32896) * f;
+    CHECK(17 * most + f < 9007199254740992.0, "bound of the sums of %d pieces at %d bits", PIECES, bits);
+    for (int rep = 0; rep < 2000; ++rep) {
+        std::vector<int64_t> y(n_src);
+        for (uint32_t i = 0; i < n_src; ++i) {
+            const int64_t s = (int64_t)c.mod[i];
+            y[i] = (int64_t)(rnd() % (uint64_t)s);
+            if (rep % 4 == 0) y[i] = (int64_t[]){0, s - 1, 0x7F7F7F80, 0x7F7F7F7F, 0xFFFFFF, (s >> 24 << 24) - 0x80808081ll, 1, s / 2}[(rep / 4 + i) % 8];
+            if (y[i] < 0 || y[i] >= s) y[i] = s - 1;
+            if (i >= n_basis) y[i] = rep % 4 == 1 ? -(s / 2) : rep % 4 == 2 ? s / 2 : y[i] - s / 2;   // signed
+        }
+        std::vector<uint32_t> word(n_src);
+        std::vector<int> top(n_src);
+        for (uint32_t i = 0; i < n_src; ++i) {
+            const double biased = (double)y[i] + kDigitBias;
+            uint64_t raw;
+            memcpy(&raw, &biased, 8);
+            word[i] = (uint32_t)raw;
+            top[i] = (int)(int8_t)(raw >> 32);
+        }
+        for (uint32_t t = 0; t < n_dst; ++t) {
+            const Mod m = plan.dst_mod[t];
+            const int64_t mt = (int64_t)c.mod[dst[t]];
+            i128 exact = 0;
+            double acc = plan.dst_start[t];
+            for (uint32_t i = 0; i < n_src; ++i) {
+                int64_t prod = 1;
+                for (uint32_t k = 0; k < n_basis; ++k)
+                    if (k != i) prod = mod_i128((i128)prod * (int64_t)c.mod[k], mt);
+                exact += (i128)y[i] * prod;
+                double piece[PIECES];
+                cut_source<PIECES>(word[i], top[i], piece);
+                for (int k = 0; k < PIECES; ++k) {
+                    acc = __builtin_fma(piece[k], plan.hats[t][i][k + 1 < PIECES ? k : 3], acc);
+                    CHECK(acc == floor(acc) && fabs(acc) < 9007199254740992.0, "conversion sum, %d pieces", PIECES);
+                }
+            }
+            const int64_t want = mod_i128(exact, mt);
+            CHECK(mod_i128((i128)(int64_t)reduce_lazy(acc, m), mt) == want, "conversion, %d pieces of %u sources at %d bits", PIECES, n_src, bits);
+            int64_t planes[kMfmaPlanes] = {};
+            for (int slot = 0; slot < 2 * mfma_instructions((int)plan.mfma_t); ++slot)
+                for (int e = 0; e < mfma_slot_sources((int)plan.mfma_t, slot / 2); ++e) {
+                    const uint32_t i = plan.mfma_src_limb[3 * slot + e];
+                    for (int b = 0; b < kMfmaPlanes; ++b) {
+                        const int8_t* row = plan.afac[t][b][slot];
+                        for (int a = 0; a < 4; ++a) planes[b] += row[4 * e + a] * (int)(int8_t)((word[i] >> (8 * a) & 255u) ^ 128u);
+                        planes[b] += row[12 + e] * top[i];
+                    }
+                }
+            int64_t v = 0;
+            for (int b = kMfmaPlanes - 1; b >= 0; --b) {
+                CHECK(llabs(planes[b]) <= 17ll * 5 * (1 << 14), "digit plane %d", b);
+                v = v * 256 + planes[b];
+            }
+            CHECK(llabs(planes[0] + planes[1] * 256) < (1ll << 31) && llabs(planes[2] + planes[3] * 256) < (1ll << 31), "pairs of digit planes");
+            CHECK(llabs(v) < (1ll << 49) && mod_i128((i128)(int64_t)reduce_lazy((double)v, m), mt) == want, "digit planes of %u sources at %d bits", n_src, bits);
+        }
+    }
+}
+
 // The units of the rotation gathers go to eight XCDs in rounds: the last round leaves at most an eighth of all places idle.
 static void check_gather_parts() {
     for (uint32_t E = 4; E <= 255; ++E) {
@@ -217,6 +325,12 @@ static void check_conversion_targets() {
 int main() {
     check_gather_parts();
     check_conversion_targets();
+    for (uint32_t n_src : {1u, 2u, 5u, 8u, 13u, 16u, 17u}) {
+        const uint32_t n_extra = n_src == 17 || n_src == 2 ? 1 : 0;
+        check_conversion<3>(36, n_src, n_extra);
+        check_conversion<2>(32, n_src, n_extra);
+        check_conversion<2>(28, n_src, n_extra);
+    }
     const uint64_t primes[] = {68718428161ull /* largest, N=2^16 */, 68617633793ull /* 60th, N=2^16 */, 68719403009ull /* largest, N=2^12 */,
                                68718764033ull /* 6th, N=2^12 */, 34359754753ull /* a 35-bit prime = 1 mod 2^17 */,
                                // the rest of the admitted range: the paper's word size, the top of the 32-bit range, a tiny modulus
