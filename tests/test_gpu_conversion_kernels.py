@@ -1,8 +1,8 @@
 """The two base-conversion kernel families -- vector fp64 accumulation and int8 matrix cores (one or three targets per
 lane half) -- forced through the context option, each against the plain-C reference, bit-exact on every residue: the
 standalone conversion, and the fused conversion + column transform inside ks_keyswitch / hmult_relin_rescale_merged.
-Source counts 1 .. 13 cover every operand-slot shape of the matrix-core tables (1, 2 or 3 instructions per position, 1..3
-sources per slot), including digits of different sizes in one launch."""
+Source counts 1 .. 17 cover every operand-slot shape of the matrix-core tables (1, 2 or 3 instructions per position, 1 to 9
+sources a lane half), including digits of different sizes in one launch."""
 
 import pytest
 import torch
@@ -126,6 +126,38 @@ def test_rescale_with_the_most_sources(kernel, targets):
         assert_equal(out, st.ref.hmult_relin_rescale(host(cta), host(ctb), host(rlk), ell))
 
 
+@pytest.mark.parametrize("merged", [False, True])
+def test_rescale_with_many_sources_and_several_polynomials_a_workgroup(merged):
+    """Nine sources a lane half, twelve pairs at N = 2^16: a workgroup of the last conversion takes five polynomials in turn; the signed
+    source of the rescale (K = 16) and the unsigned one of the merged form (K = 15)."""
+    Kk = 15 if merged else 16
+    st, batch = Setup(16, Kk, Kk, 1), 12
+    cta, ctb = (st.uniform(48 + i, 1, (batch, 2), list(range(Kk))) for i in range(2))
+    rlk = st.uniform(50, 2, (1, 2), list(range(2 * Kk)))
+    out = torch.full((batch, 2, Kk - 1, st.N), -1, dtype=torch.int64, device="cuda")
+    fn, ref = (K.hmult_relin_rescale_merged, st.ref.hmult_relin_rescale_merged) if merged else (K.hmult_relin_rescale, st.ref.hmult_relin_rescale)
+    ws = workspace(st.ctx, K.KS_OP_HMULT_RELIN_RESCALE, Kk, batch)
+    fn(st.ctx, cta, ctb, Kk, rlk, out, ws)
+    one = torch.empty_like(out[:1])
+    for b in range(batch):
+        fn(st.ctx, cta[b:b + 1], ctb[b:b + 1], Kk, rlk, one, ws)
+        assert torch.equal(out[b:b + 1], one), b
+    assert_equal(out[-1:], ref(host(cta[-1:]), host(ctb[-1:]), host(rlk), Kk))
+
+
+@pytest.mark.parametrize("logN,L,Kk,dnum", [(12, 5, 2, 3), (13, 9, 3, 3), (15, 2, 1, 2), (15, 9, 3, 3), (16, 10, 5, 2), (16, 14, 7, 2)])
+def test_every_number_of_targets(logN, L, Kk, dnum):
+    """KS_OPT_BCONV_TARGETS: all numbers of targets that either fused kernel can be set to."""
+    st = Setup(logN, L, Kk, dnum)
+    evk, d = st.uniform(51, 1, (dnum, 2), list(range(L + Kk))), st.uniform(51, 2, (2,), list(range(L)))
+    want = st.ref.keyswitch(host(d), host(evk), L)
+    for kernel, targets in ((1, 1), (1, 2), (1, 3), (1, 4), (2, 1), (2, 3)):
+        _select(st, kernel, targets)
+        out = torch.full((2, 2, L, st.N), -1, dtype=torch.int64, device="cuda")
+        K.ks_keyswitch(st.ctx, d, L, evk, out, workspace(st.ctx, K.KS_OP_KEYSWITCH, L, 2))
+        assert_equal(out, want)
+
+
 @pytest.mark.parametrize("batch", [31, 32, 33, 127, 128, 129])
 def test_standalone_conversion_positions_per_wavefront(small, batch):
     """N = 2^12 has 32 wavefront tiles of 128 positions per polynomial: 1, 2 and 4 position groups per wavefront, at the batch sizes
@@ -165,12 +197,17 @@ def test_standalone_conversion_positions_per_wavefront_words32(batch):
 
 
 @pytest.mark.parametrize("logN,L,Kk,dnum,batch", [
-    (16, 16, 4, 4, 8),    # 4 sources (8 columns at most); tiles of 16 with every operand-slot shape they come in: 6, 8, 12 and 13
+    (16, 16, 4, 4, 8),    # 4 sources: vector or 8 columns; tiles of 16 columns with 6, 8, 12 and 13 sources (3, 4, 6 and 7 a lane half)
     (16, 24, 6, 4, 8),
-    (16, 24, 8, 3, 9),    # a last chunk of one ciphertext: 16- and 8-column tiles in one call
+    (16, 24, 8, 3, 9),    # 16-column tiles, all nine in one pass
+    (16, 24, 8, 3, 15),   # passes of eight and seven: 16- and 8-column tiles in one call
     (16, 36, 12, 3, 8),
     (16, 39, 13, 3, 8),
-    (15, 20, 7, 3, 5),    # three targets per lane half at N = 2^15
+    (16, 30, 15, 2, 1),   # nine a lane half: one target per half, three in tiles of 8 and of 16 columns
+    (16, 30, 15, 2, 8),
+    (16, 30, 15, 2, 12),
+    (15, 20, 7, 3, 5),    # N = 2^15: one target per lane half, and three
+    (15, 30, 15, 2, 5),
 ])
 def test_conversion_tiles_of_large_launches(logN, L, Kk, dnum, batch):
     """The kernel that is chosen, the vector kernel and the matrix cores against each other on every residue, and against the

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import paper_2512_11269_amd as K
-from gpu_util import Setup, workspace
+from gpu_util import Setup, assert_equal, host, workspace
 
 pytestmark = pytest.mark.gpu
 
@@ -31,6 +31,55 @@ def test_batches_in_passes(bits, L, Kk, dnum, ell, batch):
             fn(st.ctx, *(a[b:b + 1] for a in args), ell, evk, one, ws)
             assert torch.equal(out[b:b + 1], one), b
         assert bool((buf[words:] == -7).all())
+
+
+@pytest.mark.parametrize("logN,L,Kk,dnum,batch,passes", [
+    (12, 5, 2, 3, 9, 1),       # vector conversions
+    (14, 12, 4, 3, 29, 3),
+    (15, 20, 7, 3, 15, 2),     # matrix cores, eight and seven
+    (16, 24, 8, 3, 17, 2),     # 16-column tiles, nine and eight
+    (16, 24, 8, 3, 15, 2),     # eight and seven: 16- and 8-column tiles
+    (16, 16, 4, 4, 27, 2),     # fourteen and thirteen, vector conversions
+])
+def test_passes_of_a_key_switch(logN, L, Kk, dnum, batch, passes):
+    """The number of passes, with either conversion kernel; every ciphertext as in a call of its own, the last one of each pass against the
+    reference."""
+    st = Setup(logN, L, Kk, dnum)
+    evk, d = st.uniform(53, 1, (dnum, 2), list(range(L + Kk))), st.uniform(53, 2, (batch,), list(range(L)))
+    out = torch.full((batch, 2, L, st.N), -1, dtype=torch.int64, device="cuda")
+    ws = workspace(st.ctx, K.KS_OP_KEYSWITCH, L, batch)
+    K.ks_profile_enable(True)
+    K.ks_keyswitch(st.ctx, d, L, evk, out, ws)
+    launches = {r["kernel"]: r["launches"] for r in K.ks_profile_report()}
+    K.ks_profile_enable(False)
+    assert launches["rows_inner_product"] == passes
+    one = torch.empty_like(out[:1])
+    for b in range(batch):
+        K.ks_keyswitch(st.ctx, d[b:b + 1], L, evk, one, ws)
+        assert torch.equal(out[b:b + 1], one), b
+    size = 8 if passes == -(-batch // 8) else -(-batch // passes)
+    for last in sorted({min((p + 1) * size, batch) - 1 for p in range(passes)}):
+        assert_equal(out[last:last + 1], st.ref.keyswitch(host(d[last:last + 1]), host(evk), L))
+
+
+@pytest.mark.parametrize("logN,L,Kk,dnum,batch,passes", [(14, 9, 3, 3, 27, 3), (15, 20, 7, 3, 13, 1), (16, 12, 6, 2, 15, 2)])
+def test_passes_of_a_multiplication(logN, L, Kk, dnum, batch, passes):
+    st = Setup(logN, L, Kk, dnum)
+    q = list(range(L))
+    cta, ctb, rlk = st.uniform(54, 1, (batch, 2), q), st.uniform(54, 2, (batch, 2), q), st.uniform(54, 3, (dnum, 2), list(range(L + Kk)))
+    ws = workspace(st.ctx, K.KS_OP_HMULT_RELIN_RESCALE, L, batch)
+    for fn, ref in ((K.hmult_relin_rescale, st.ref.hmult_relin_rescale), (K.hmult_relin_rescale_merged, st.ref.hmult_relin_rescale_merged)):
+        out = torch.full((batch, 2, L - 1, st.N), -1, dtype=torch.int64, device="cuda")
+        K.ks_profile_enable(True)
+        fn(st.ctx, cta, ctb, L, rlk, out, ws)
+        launches = {r["kernel"]: r["launches"] for r in K.ks_profile_report()}
+        K.ks_profile_enable(False)
+        assert launches["tensor_inv_rows"] == passes
+        one = torch.empty_like(out[:1])
+        for b in range(batch):
+            fn(st.ctx, cta[b:b + 1], ctb[b:b + 1], L, rlk, one, ws)
+            assert torch.equal(out[b:b + 1], one), b
+        assert_equal(out[-1:], ref(host(cta[-1:]), host(ctb[-1:]), host(rlk), L))
 
 
 @pytest.mark.parametrize("bits", [36, 28])

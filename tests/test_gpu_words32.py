@@ -199,17 +199,19 @@ def test_two_piece_conversion_extreme_residues(which, request):
         assert_equal(out, st.ref.keyswitch(host(d), host(evk), ell))
 
 
-@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("which", ["modulus - 1", "(modulus - 1) / 2", "(modulus + 1) / 2"])
 @pytest.mark.parametrize("batch,n_rot", [(1, 1), (3, 16), (8, 16), (9, 20)])
-def test_integer_sums_of_the_rotations(batch, n_rot, half):
-    """28-bit moduli in 32-bit words sum their products in 64-bit integers: eight digits and sixteen rotations a launch at the
-    largest products (ciphertexts of modulus - 1, keys of modulus - 1 or, the largest lazy factor, half the modulus)."""
+def test_integer_sums_of_the_rotations(batch, n_rot, which):
+    """28-bit moduli in 32-bit words sum their products in 64-bit integers: eight digits and sixteen rotations a launch on ciphertexts of
+    modulus - 1.  Keys of modulus - 1 are the largest factors of the plain rotations, which take the key as it is; the multiplied ones take
+    the lazy residue of key and plaintext, which is furthest from zero, upwards and downwards, at half the modulus."""
     st = Setup(12, 8, 1, 8, bits=28)
     assert max(st.q + st.p) < 1 << 28
     ell, mods = st.L, torch.tensor(st.q + st.p, dtype=torch.int64, device="cuda")
     ct = (mods[:ell] - 1).view(1, 1, ell, 1).expand(batch, 2, ell, st.N).contiguous()
     ct[:, :, :, 1::2] = st.uniform(2010, 1, (batch, 2), list(range(ell)))[:, :, :, 1::2]
-    key = (mods // 2 if half else mods - 1).view(1, 1, -1, 1).expand(8, 2, -1, st.N).contiguous()
+    slots = {"modulus - 1": mods - 1, "(modulus - 1) / 2": mods // 2, "(modulus + 1) / 2": mods // 2 + 1}[which]
+    key = slots.view(1, 1, -1, 1).expand(8, 2, -1, st.N).contiguous()
     galois = ks_inputs.galois_elements(st.logN, n_rot)
     keys, pts = [key] * n_rot, [None] * n_rot
     out = torch.empty((batch, 2, ell, st.N), dtype=torch.int32, device="cuda")
