@@ -52,21 +52,6 @@ struct TwTables {
 // as much data as the row itself.  They factor as W[n 2^u + g] = T^(2^(3-u)) * omega^(2^(3-u) brv_u(g)) with
 // T = W[8 n], so one load, three squarings and eleven products replace fifteen loads (row kernels are
 // bandwidth-bound and have arithmetic to spare).
-__device__ __forceinline__ void load_row_twiddles(PassTwiddles& t, const TwTables& tb, uint32_t mod_id, uint32_t N, uint32_t node,
-                                                  uint32_t j0, Mod m) {
-    load_twiddles16(t.a, tb.W + (size_t)mod_id * N, node);
-    const double* w = tb.w16 + mod_id * 8;
-    const double T1 = tb.trow[(size_t)mod_id * (N / 16) + (node * 16 + j0 - N / 16)];
-    const double T2 = mulmod_lazy(T1, T1, m), T4 = mulmod_lazy(T2, T2, m), T8 = mulmod_lazy(T4, T4, m);
-    t.b[0] = 0.0;
-    t.b[1] = T8;
-    t.b[2] = T4;  t.b[3] = mulmod_lazy(T4, w[4], m);
-    t.b[4] = T2;  t.b[5] = mulmod_lazy(T2, w[4], m);  t.b[6] = mulmod_lazy(T2, w[2], m);  t.b[7] = mulmod_lazy(T2, w[6], m);
-    t.b[8] = T1;  t.b[9] = mulmod_lazy(T1, w[4], m);  t.b[10] = mulmod_lazy(T1, w[2], m); t.b[11] = mulmod_lazy(T1, w[6], m);
-    t.b[12] = mulmod_lazy(T1, w[1], m);  t.b[13] = mulmod_lazy(T1, w[5], m);
-    t.b[14] = mulmod_lazy(T1, w[3], m);  t.b[15] = mulmod_lazy(T1, w[7], m);
-}
-// The same with the first-pass twiddles left out (for kernels that keep them in LDS, see row_twiddles_to_lds).
 __device__ __forceinline__ void load_row_twiddles_b(double (&tb)[16], const TwTables& tbl, uint32_t mod_id, uint32_t N, uint32_t node,
                                                     uint32_t j0, Mod m) {
     const double* w = tbl.w16 + mod_id * 8;
@@ -79,6 +64,12 @@ __device__ __forceinline__ void load_row_twiddles_b(double (&tb)[16], const TwTa
     tb[8] = T1;  tb[9] = mulmod_lazy(T1, w[4], m);  tb[10] = mulmod_lazy(T1, w[2], m); tb[11] = mulmod_lazy(T1, w[6], m);
     tb[12] = mulmod_lazy(T1, w[1], m);  tb[13] = mulmod_lazy(T1, w[5], m);
     tb[14] = mulmod_lazy(T1, w[3], m);  tb[15] = mulmod_lazy(T1, w[7], m);
+}
+// Both passes (kernels that keep the first one's in LDS: row_twiddles_to_lds).
+__device__ __forceinline__ void load_row_twiddles(PassTwiddles& t, const TwTables& tbl, uint32_t mod_id, uint32_t N, uint32_t node,
+                                                  uint32_t j0, Mod m) {
+    load_twiddles16(t.a, tbl.W + (size_t)mod_id * N, node);
+    load_row_twiddles_b(t.b, tbl, mod_id, N, node, j0, m);
 }
 // First-pass twiddles of a row (the 15 table entries below heap node `node`, the same for the row's 16 lanes) placed in
 // 16 doubles of LDS: lane j0 fetches entry j0.  Frees 30 registers per lane where a kernel is short of them; the
