@@ -62,16 +62,7 @@ void mod_up_from_rows(const ks_ctx* c, const Level& lv, uint8_t* coeff, uint8_t*
     const uint64_t limb = packed_limb_bytes(c->N), coeff_ps = lv.ell * limb, lifted_ps = (uint64_t)lv.ndig * lv.E * limb;
     // the column half also multiplies by N^-1 (D_j/q_i)^-1 and leaves the sources of the conversion
     launch_inv_cols_packed(c, lv.q_map, coeff, coeff_ps, bc, lv.d_modup_scale, s);
-    // algorithmic fp64 work per coefficient: 3 FMAs per source x target plus the 6 instructions that cut the source, shared
-    // by four targets (4.5 in all), then per target one reduction and the column stages (8 per butterfly, half a
-    // butterfly per point and stage)
-    double ops = 0.0;
-    for (uint32_t j = 0; j < lv.ndig; ++j) {
-        const double a = lv.digit_hi[j] - lv.digit_lo[j];
-        ops += a * (lv.E - a) * 4.5;
-    }
-    ops += lv.n_new * (3.0 + 4.0 * (c->logN - 8));
-    launch_bconv_ntt_cols(c, lv.modup, lv.ell + lv.n_new, coeff, coeff_ps, lifted, lifted_ps, bc, tile, s, ops);
+    launch_bconv_ntt_cols(c, lv.modup, lv.ell + lv.n_new, coeff, coeff_ps, lifted, lifted_ps, bc, tile, s);
 }
 
 // Decompose and raise: d (evaluation domain, `bc` polynomials d_ps words apart) -> lifted [bc][ndig][E] packed.
@@ -114,11 +105,6 @@ static GatherBundle mod_up_for_gather(const ks_ctx* c, const Level& lv, const vo
     return bundle;
 }
 
-// algorithmic fp64 work per coefficient of the ModDown conversion + column half (see mod_up)
-static double moddown_ops(const ks_ctx* c, const Level& lv) {
-    return (double)c->K * lv.ell * 4.5 + lv.ell * (3.0 + 4.0 * (c->logN - 8));
-}
-
 // Division by P of both accumulators: INTT of the special limbs (in place), fused base conversion + column half, fused row
 // half + (acc - conv) P^-1.
 void mod_down(const ks_ctx* c, const Level& lv, uint8_t* acc, uint8_t* conv, void* out, uint64_t out_bs,
@@ -127,7 +113,7 @@ void mod_down(const ks_ctx* c, const Level& lv, uint8_t* acc, uint8_t* conv, voi
     // the fused inner product already ran the row half of the inverse transform on the special limbs
     if (!special_rows_done) launch_inv_rows_packed(c, lv.special_map, acc, acc_ps, 1, acc, acc_ps, 2 * bc, s);
     launch_inv_cols_packed(c, lv.special_map, acc, acc_ps, 2 * bc, c->d_moddown_scale, s);
-    launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s, moddown_ops(c, lv));
+    launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s);
     launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 0, nullptr, 0, bc, s, nullptr, out_words32);
 }
 
@@ -170,7 +156,7 @@ extern "C" size_t ks_workspace_bytes(const ks_ctx* c, int op, uint32_t ell, uint
 }
 
 // Ciphertexts that a key-switch or multiplication takes at a time, given the bytes one of them takes: kChunk, or as many as the
-// workspace holds (a caller brings what ks_workspace_bytes asks for, 8 bytes a residue; the packed regions of about thirteen fit) where
+// workspace holds (a caller brings what ks_workspace_bytes asks for, 8 bytes a residue; the packed regions of thirteen or fourteen fit) where
 // that makes fewer passes, evenly filled.  Key-switches in passes of eight -> so many: N = 2^12, 12 ciphertexts 79 -> 45 us, 64 327 -> 224;
 // N = 2^14 185 -> 151 and 918 -> 841; N = 2^16, L = 24 803 -> 753 and 4014 -> 3887; multiplications at L = 35, 64 of them 7086 -> 7046.
 // As many passes as before stay as they are (seven and seven for eight and six was up to 12 % slower).
@@ -423,7 +409,7 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
             const uint32_t polys = 2 * rot.n * bc;
             launch_inv_rows_packed(c, lv.special_map, acc, acc_ps, 1, acc, acc_ps, polys, s);
             launch_inv_cols_packed(c, lv.special_map, acc, acc_ps, polys, c->d_moddown_scale, s);
-            launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, polys, tile, s, moddown_ops(c, lv));
+            launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, polys, tile, s);
             launch_rows_moddown_finish(c, lv, acc, conv, static_cast<char*>(out) + ((uint64_t)b0 * out_bs + (uint64_t)r0 * 2 * ell * N) * word, out_bs,
                                        c0, ct_bs, &rot, 2ull * ell * N, bc, s, nullptr, words32);
         }
@@ -591,8 +577,7 @@ static void mod_down_drop(const ks_ctx* c, const Level& lv, uint8_t* acc, uint8_
     launch_inv_cols_packed(c, lv.drop_map, acc, acc_ps, 2 * bc, merged ? lv.d_merged_scale : lv.d_rescale_scale, s);
     if (!merged) launch_rescale_remainder(c, lv, acc, 2 * bc, s);
     const uint32_t n_src = c->K + 1, n_dst = lv.ell - 1;
-    const double ops = (double)n_src * n_dst * 4.5 + n_dst * (3.0 + 4.0 * (c->logN - 8));
-    launch_bconv_ntt_cols(c, merged ? lv.merged : lv.rescale, n_src + n_dst, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s, ops);
+    launch_bconv_ntt_cols(c, merged ? lv.merged : lv.rescale, n_src + n_dst, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s);
     const FinishScale fs{lv.d_Dinv, lv.d_qlinv, n_dst};
     launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, addend, 0, nullptr, 0, bc, s, &fs, out_words32);
 }

@@ -178,17 +178,15 @@ int conversion_tile(const ks_ctx* c, const PlanSet& up, uint32_t up_polys, const
 }
 
 void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint8_t* y, uint64_t y_ps,
-                           uint8_t* out, uint64_t out_ps, uint32_t n_polys, int tile, hipStream_t s, double ops_per_coeff) {
+                           uint8_t* out, uint64_t out_ps, uint32_t n_polys, int tile, hipStream_t s) {
     const uint32_t n_plans = plans.n_plans, max_targets = plans.max_targets;
     const BConvPlan* d_plans = plans.d_plans;
     if (n_polys == 0 || n_plans == 0) return;
     const int kernel = c->opt[KS_OPT_BCONV_KERNEL] ? c->opt[KS_OPT_BCONV_KERNEL] : (tile ? 2 : 1);
     if (kernel == 2) {
-        // algorithmic fp64 / integer vector work per coefficient of this kernel: per target 9 to recombine and reduce the
-        // five sums and 35 for the column half; per source 2 to cut it into bytes (the contraction itself runs on the
-        // matrix cores: 25 int8 multiply-adds per source and target)
-        double vec_ops = 0.0;
-        for (uint32_t j = 0; j < n_plans; ++j) vec_ops += plans.meta.plan[j].n_dst * 44.0 + plans.shape_src * 2.0;
+        // algorithmic vector work per coefficient and target of this kernel: 9 to recombine and reduce the five sums, 4 a column stage, 3 to
+        // pack (the sources come cut into bytes; the contraction runs on the matrix cores: 25 int8 multiply-adds per source and target)
+        const double vec_ops = plans.targets * (12.0 + 4.0 * (c->logN - 8));
         ProfScope ps("bconv_mfma_ntt_cols", (double)limbs_moved_per_poly * n_polys * packed_limb_bytes(c->N), s, vec_ops * n_polys * c->N);
         // Targets per lane half.  A workgroup with one needs half the registers and a third of the time, so that four share a compute unit
         // and a launch of a few rounds ends evenly: one key-switch 8 -> 24 93.0 -> 90.2 us, one merged multiplication 104.7 -> 100.3,
@@ -205,7 +203,10 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
     const int ts = c->opt[KS_OPT_BCONV_TARGETS] ? c->opt[KS_OPT_BCONV_TARGETS] : vector_conversion_targets(plans, tiles, n_polys);
     const uint32_t n_subsets = (max_targets + ts - 1) / ts;
     const dim3 grid(tiles, n_plans * n_subsets, n_polys), block(256);
-    ProfScope ps("bconv_ntt_cols", (double)limbs_moved_per_poly * n_polys * packed_limb_bytes(c->N), s, ops_per_coeff * n_polys * c->N);
+    // algorithmic fp64 work per coefficient: an FMA per source, target and piece, then per target one reduction and the column stages
+    // (8 per butterfly, half a butterfly per point and stage)
+    const double ops = (double)c->pieces * plans.products + plans.targets * (3.0 + 4.0 * (c->logN - 8));
+    ProfScope ps("bconv_ntt_cols", (double)limbs_moved_per_poly * n_polys * packed_limb_bytes(c->N), s, ops * n_polys * c->N);
 #define KS_LAUNCH_BCONV(LOGR, TSV)                                                                                                      \
     if (c->pieces == 2)                                                                                                                 \
         hipLaunchKernelGGL((bconv_ntt_cols<LOGR, TSV, 2>), grid, block, 0, s, c->d_tw_fwd, d_plans, y, y_ps, out, out_ps,  \

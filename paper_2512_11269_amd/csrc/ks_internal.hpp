@@ -201,7 +201,7 @@ int conversion_tile(const ks_ctx* c, const PlanSet& up, uint32_t up_polys, const
 // Fused base conversion + column half of the forward transform, with the kernel `tile` (conversion_tile).  y: packed sources
 // y_i = [x_i N^-1 (D/s_i)^-1]; out: packed limbs ready for the row half; strides in bytes.  One plan per blockIdx.y group.
 void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs_moved_per_poly, const uint8_t* y, uint64_t y_ps,
-                           uint8_t* out, uint64_t out_ps, uint32_t n_polys, int tile, hipStream_t s, double ops_per_coeff = 0.0);
+                           uint8_t* out, uint64_t out_ps, uint32_t n_polys, int tile, hipStream_t s);
 // The same conversion + column half on the matrix cores (ks_bconv_mfma.hip); tl = targets per lane half, 1..3.
 void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uint8_t* y, uint64_t y_ps, uint8_t* out,
                                 uint64_t out_ps, uint32_t n_polys, int tl, bool wide, hipStream_t s);

@@ -293,3 +293,20 @@ def test_sixteen_column_tiles_on_28_bit_moduli():
         out.append(torch.full((8, 4, 2, 24, st.N), -1, dtype=torch.int32, device="cuda"))
         K.ks_rotate_hoisted_u32(st.ctx, ct, 24, g, keys, out[-1], ws)
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("bits,pieces", [(36, 3), (28, 2)])
+def test_operations_that_are_reported(bits, pieces):
+    """The report's work of the fused conversions: per coefficient a multiply-add per source, target and piece (vector kernel), then the
+    reduction and column stages of each target.  Digits of 2, 2 and 1 sources with 5, 5 and 6 targets, and 2 -> 5 for both components."""
+    st = Setup(12, 5, 2, 3, bits=bits)
+    evk, d = st.uniform(52, 1, (3, 2), list(range(7))), st.uniform(52, 2, (1,), list(range(5)))
+    ws, out = workspace(st.ctx, K.KS_OP_KEYSWITCH, 5, 1), torch.empty((1, 2, 5, st.N), dtype=torch.int64, device="cuda")
+    pairs, targets = 2 * 5 + 2 * 5 + 1 * 6 + 2 * (2 * 5), 5 + 5 + 6 + 2 * 5
+    for kernel, name, ops in ((1, "bconv_ntt_cols", pieces * pairs + 19 * targets), (2, "bconv_mfma_ntt_cols", 28 * targets)):
+        _select(st, kernel, 0)
+        K.ks_profile_enable(True)
+        K.ks_keyswitch(st.ctx, d, 5, evk, out, ws)
+        report = {r["kernel"]: r for r in K.ks_profile_report()}
+        K.ks_profile_enable(False)
+        assert report[name]["total_ops"] == ops * st.N
