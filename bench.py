@@ -30,7 +30,7 @@ HBM_PEAK_GBS = 8000.0
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # 256 CU x 4 SIMD x 16 lanes x 2 flop x 2.4 GHz
 MIB = 1024.0 * 1024.0
 GIB = 1024.0 * MIB
-CHUNK = 8                        # ciphertexts per internal pass of the batched pipelines (the key is read once per chunk)
+KEY_SHARE = 8                    # ciphertexts that share one read of the key in the byte models; a pass of the library holds up to fourteen
 
 # HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (profiles/keyswitch_cfg2_hbm_traffic.txt,
 # "measured" column: FETCH_SIZE and WRITE_SIZE scaled by what the same counters read for a 1 GiB device copy, summed, per
@@ -44,7 +44,7 @@ MEASURED_TRAFFIC_BYTES: dict = {
 }
 
 # Algorithmic bytes of the other workloads (fused-plan accounting: every transform = two passes over its limbs, base
-# conversion and products fused into them, keys read once per chunk of ciphertexts), per unit of work.
+# conversion and products fused into them, keys read once for eight ciphertexts), per unit of work.
 CFG3_BYTES_PER_CALL = 222.5 * GIB          # 64 ciphertexts x 16 hoisted rotations
 CFG4_BYTES_PER_DIRECTION = 2 * 2 * 1920 * 65536 * 8.0   # 1920 limb transforms, two passes, read + write
 CFG5_BYTES_PER_HMULT = 698.0 * MIB
@@ -53,12 +53,13 @@ CFG5_BYTES_PER_HMULT = 698.0 * MIB
 def _keyswitch_bytes(L, K, dnum, N, batch=1):
     """Algorithmic traffic of one key-switch in bytes: compulsory (read d and the key, write out) and the
     fused-plan model (every transform = two passes over its limbs, base conversion and products fused).  In a batched
-    call the key is read once per chunk of min(batch, 8) ciphertexts, so each ciphertext is charged that share of it."""
+    call the model reads the key once for min(batch, 8) ciphertexts, whatever the library's passes hold, so that figures stay
+    comparable: each ciphertext is charged that share of it."""
     limb = N * 8
     alpha = -(-L // dnum)
     E = L + K
     new_limbs = sum(E - (min((j + 1) * alpha, L) - j * alpha) for j in range(dnum))
-    key_limbs = dnum * 2 * E / min(batch, CHUNK)
+    key_limbs = dnum * 2 * E / min(batch, KEY_SHARE)
     compulsory = (L + key_limbs + 2 * L) * limb
     fused = (2 * L                                       # INTT rows
              + L + new_limbs                             # INTT cols + conversion + NTT cols
@@ -69,14 +70,14 @@ def _keyswitch_bytes(L, K, dnum, N, batch=1):
     return compulsory, fused
 
 
-def _keyswitch_bytes_moved(L, K, dnum, N, batch=1):
-    """What the library's seven launches move per key-switch: ciphertext, key and result in 8-byte words, every limb that
+def _keyswitch_bytes_moved(L, K, dnum, N):
+    """What the library's seven launches move in a call of one key-switch: ciphertext, key and result in 8-byte words, every limb that
     one kernel writes and the next reads as 5 bytes a residue.  The fused plan has one pass less over the digits (it
     counts the column half of their inverse transform with the conversion)."""
     alpha = -(-L // dnum)
     E = L + K
     new_limbs = sum(E - (min((j + 1) * alpha, L) - j * alpha) for j in range(dnum))
-    words = L + L + dnum * 2 * E / min(batch, CHUNK) + 2 * L          # d twice (INTT, own slots of the product), key, result
+    words = L + L + dnum * 2 * E + 2 * L                              # d twice (INTT, own slots of the product), key, result
     packed = (L + 2 * L                                               # INTT rows (written), INTT cols
               + L + new_limbs                                         # conversion + NTT cols
               + new_limbs + 2 * E                                     # NTT rows + inner product (+ INTT rows of special limbs)
@@ -215,7 +216,7 @@ def bench_keyswitch(args, torch, K, ks_inputs):
             "moved_frac_of_peak": frac(_keyswitch_bytes_moved(L, Kk, dnum, N), ms),
             "compulsory_GBs": round(compulsory / (ms * 1e-3) / 1e9, 1),
             "sum_kernel_ms_per_step": round(sum(k["ms_per_step"] for k in kernels), 4),
-            # algorithmic traffic per ciphertext of a batched call, the key charged once per chunk of 8 (part of this
+            # algorithmic traffic per ciphertext of a batched call, the key charged once for 8 of them (part of this
             # traffic is served by the last-level cache: one key and one workspace are reused by the whole batch)
             "batched_fused_plan_MiB_per_keyswitch": {str(nb): round(_keyswitch_bytes(L, Kk, dnum, N, nb)[1] / MIB, 1) for nb in batched},
             "batched_fused_plan_frac_of_peak": {str(nb): frac(_keyswitch_bytes(L, Kk, dnum, N, nb)[1], v) for nb, v in batched.items()},

@@ -87,7 +87,8 @@ int ks_ctx_set_option(ks_ctx* ctx, int option, int value);
  * (n_rot is only read for KS_OP_ROTATE_HOISTED and KS_OP_ROTATE_HOISTED_U32, which also serve the rotate-multiply-
  * accumulate calls; KS_OP_HMULT_RELIN_RESCALE serves all four multiplication entry points, KS_OP_KEYSWITCH both
  * key-switch word sizes).  Returns 0 for invalid arguments.  Large batches are processed in
- * internal chunks, so the result stops growing beyond a chunk. */
+ * passes, so the result stops growing with the batch at eight ciphertexts.  It is more than eight of them need: calls
+ * use up to all of it, for more ciphertexts (key-switches, multiplications) or rotations a pass. */
 size_t ks_workspace_bytes(const ks_ctx* ctx, int op, uint32_t ell, uint32_t batch, uint32_t n_rot);
 
 const char* ks_strerror(int code);
@@ -129,7 +130,7 @@ int ks_keyswitch(const ks_ctx* ctx, const uint64_t* d, uint32_t ell, const uint6
 /* ks_keyswitch with the boundary tensors in 32-bit words (the paper's word size: Evaluation, "Benchmarks", a 28-bit RNS basis in
  * 32-bit words): d [batch][ell][N], evk [dnum][2][L+K][N] and out [batch][2][ell][N] hold one
  * residue per uint32_t, which halves the traffic of the key, the largest tensor of the operation.  Arithmetic, workspace
- * (KS_OP_KEYSWITCH, 8-byte elements inside) and results are those of ks_keyswitch.  KS_EINVAL unless every modulus
+ * (KS_OP_KEYSWITCH) and results are those of ks_keyswitch.  KS_EINVAL unless every modulus
  * of the context is below 2^32. */
 int ks_keyswitch_u32(const ks_ctx* ctx, const uint32_t* d, uint32_t ell, const uint32_t* evk, uint32_t* out,
                      uint32_t batch, void* ws, size_t ws_bytes, void* stream);
@@ -218,9 +219,9 @@ int hmult_relin_rescale_merged(const ks_ctx* ctx, const uint64_t* cta, const uin
  * Each call below is the entry point of the same name without the suffix with every DEVICE tensor of residues --
  * ciphertexts, keys, plaintexts, results; for the transforms and the conversion the data itself -- holding one
  * residue per uint32_t in the same layout.  Arithmetic and results are identical; the traffic of those tensors
- * halves.  Intermediate values in the workspace stay 8 bytes wide, except that the rotation calls also keep the finished
- * raised digits as 32-bit words (their kernels are bound by re-reading them; the 64-bit rotation calls keep them as a
- * 32-bit word plus a byte).  Every call returns KS_EINVAL unless every modulus
+ * halves.  Intermediate limbs in the workspace are packed in both word sizes, 5 bytes a residue; the rotation calls also keep
+ * the finished raised digits as 32-bit words (their kernels are bound by re-reading them; the 64-bit rotation calls keep
+ * them as a 32-bit word plus four bits), and the BSGS transform its inner result as 64-bit words.  Every call returns KS_EINVAL unless every modulus
  * of the context is below 2^32.  Workspace: the operation code of the 64-bit call, except that the two rotation calls
  * take KS_OP_ROTATE_HOISTED_U32 and the BSGS transform KS_OP_BSGS_U32 (the room their 32-bit raised digits take).
  *   ntt_fwd_u32 / ntt_inv_u32 : in place on [batch][nlimbs][N] uint32_t.

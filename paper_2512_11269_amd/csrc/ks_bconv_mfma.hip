@@ -63,11 +63,13 @@ void launch_bconv_mfma_ntt_cols(const ks_ctx* c, const PlanSet& plans, const uin
     const int waves = wide && c->logN == 16 && tl == 3 && n_src > 4 ? 8 : 4;
     const uint32_t tiles = c->N / (512 * waves);
     const uint32_t n_subsets = (max_targets + 2 * tl - 1) / (2 * tl);
-    // Polynomials that a workgroup takes in turn, up to eight: each round of workgroups (one or two per compute unit) takes about as
+    // Polynomials that a workgroup takes in turn, up to eight: each round of workgroups (one to four per compute unit) takes about as
     // long as another, and a polynomial after
     // the first an eighth less (its sources arrive under the butterflies of the one before; factors and twiddles are there): four hoisted
-    // rotations of eight ciphertexts, 64 polynomials 8 -> 24, 269 -> 241 us; 16 polynomials 90 -> 84; 13 -> 34, which pays for the loop with
-    // scratch registers, 136 -> 133.
+    // rotations of eight ciphertexts, 64 polynomials 8 -> 24, 269 -> 241 us; 16 polynomials 90 -> 84; 13 -> 34 136 -> 133.
+    // Three targets a half pay for the loop with spilled registers: 2 to 4 with four sources a half, 4 to 6 with seven, 17 or 18 with nine.
+    // Forming the lanes' places anew for every polynomial takes those of four away and most of the others', but is slower: sixteen
+    // rotations -0.7 %, key-switches 12 -> 36 x 8 717 -> 728 us, 13 -> 39 x 4 438 -> 450, 14 -> 28 x 8 538 -> 553, 15 -> 30 x 8 569 -> 596.
     const uint32_t slots = waves == 8 ? 256 : 256 * mfma_min_blocks(tl, (int)t), per_poly = tiles * n_plans * n_subsets;
     uint32_t groups = n_polys;
     double least = 1e30;

@@ -256,12 +256,12 @@ void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& 
 // deferred to the whole sum).  One thread owns one slot of one limb position for all ciphertexts of the group; the two
 // running sums of each stay in registers as exact integers (mac_exact) until every rotation of the launch is in.  The digits
 // are the OUTER loop and the rotations the inner one, so that between two rotations only one digit's slots are gathered from
-// and about half of them are found in the XCD's L2 (see gather_tile); each key slot is still read once, the plaintext slot
-// once per digit.  The operands of the next (digit, rotation) are requested before the current products.
-// 8 ciphertexts x 16 keyed rotations, three digits, N = 2^16, E = 32: 656 us (28-bit moduli 532), where one thread per slot that
+// and about half of them are found in the XCD's L2 (see gather_tile); each key slot and each plaintext slot is still read once (the
+// plaintext slots stay in LDS).  The operands of the next (digit, rotation) are requested before the current products.
+// 8 ciphertexts x 16 keyed rotations, three digits, N = 2^16, E = 32: 656 us (28-bit moduli, integer sums, 417), where one thread per slot that
 // walked digits inside rotations and gathered each ciphertext on its own took 1037 (9.6 GB through the fabric, now 3.3).
 // What bounds it: the stream of keys and plaintexts (1.9 of 3.1 GB read) and fp64 issue (61 % of the slots), partly overlapped.
-// Three wavefronts per SIMD: squeezed into 128 registers for a fourth, the few spilled words cost more fabric traffic than
+// Three wavefronts per SIMD (integer sums four): squeezed into 128 registers for a fourth, the few spilled words cost more fabric traffic than
 // the occupancy gains (40-100 us more).  Sixteen ciphertexts per launch sharing the key reads measured the same per ciphertext:
 // what the shared keys save, the doubled sources lose in L2.
 // rot: the n_key rotations that take a key come first, then the identities (the term P (c0, c1), no key read).
