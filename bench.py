@@ -36,11 +36,11 @@ KEY_SHARE = 8                    # ciphertexts that share one read of the key in
 # "measured" column: FETCH_SIZE and WRITE_SIZE scaled by what the same counters read for a 1 GiB device copy, summed, per
 # launch), keyed by workload and kernel.  tests/test_profiles_consistent.py checks these against that file.
 MEASURED_TRAFFIC_BYTES: dict = {
-    ("keyswitch", "bconv_mfma_ntt_cols"): 28349023,    # mean of the ModUp and the ModDown launch
-    ("keyswitch", "rows_inner_product"): 161213528,
-    ("keyswitch", "rows_moddown_finish"): 58568102,
-    ("keyswitch", "inv_rows_packed"): 22378512,
-    ("keyswitch", "inv_cols_packed"): 14822854,        # mean of the 24-limb and the 16-limb launch
+    ("keyswitch", "bconv_mfma_ntt_cols"): 28347475,    # mean of the ModUp and the ModDown launch
+    ("keyswitch", "rows_inner_product"): 161213449,
+    ("keyswitch", "rows_moddown_finish"): 58569257,
+    ("keyswitch", "inv_rows_packed"): 22378514,
+    ("keyswitch", "inv_cols_packed"): 14828999,        # mean of the 24-limb and the 16-limb launch
 }
 
 # Algorithmic bytes of the other workloads (fused-plan accounting: every transform = two passes over its limbs, base
