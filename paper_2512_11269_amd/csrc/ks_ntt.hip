@@ -381,13 +381,13 @@ static uint32_t polys_per_group(const ks_ctx* c, const LimbMap& map) {
 // longer there, more than the first one gains.  Calls as doubles / packed, us, by MiB of data (elsewhere packed is up to 18 % ahead):
 //   inverse, N = 2^12: 18 25.2 / 24.7, 21 24.5 / 26.1, 23 23.6 / 25.9, 27 24.3 / 24.9, 32 24.6 / 24.4; N = 2^13: 17 31.5 / 30.1, 21 25.6 / 30.7,
 // 24 22.7 / 26.2, 32 24.6 / 28.1, 36 28.8 / 28.5; N = 2^14: 18 28.4 / 27.6, 19 27.7 / 28.0, 27 25.8 / 27.9, 35 28.1 / 28.6, 36 28.6 / 28.5
-//   forward, N = 2^12: 20 24.9 / 24.8, 23 23.5 / 25.2, 26 24.6 / 24.6; N = 2^13: 18 25.2 / 24.7, 21 22.5 / 25.4, 25 24.0 / 24.7, 26 25.4 / 23.5;
+//   forward, N = 2^12: 20 24.9 / 24.8, 23 23.5 / 25.2, 26 24.2 / 24.6, 28 24.9 / 23.8; N = 2^13: 18 25.2 / 24.7, 21 22.5 / 25.4, 25 24.0 / 24.7, 26 25.4 / 23.5;
 // N = 2^14: 18 27.1 / 26.9, 22 24.9 / 26.8, 32 24.7 / 25.4, 34 28.0 / 27.6
-//   N = 2^15: between +2.6 and -4 % for the packed form, 2^16 always ahead.
+//   Just past these lines GPUs differ by 4 % either way, as they do at N = 2^15; at 2^16 the packed form is between 2 % behind and 11 % ahead.
 static bool transform_packed(const ks_ctx* c, uint32_t limbs, bool inverse) {
     if (c->logN > 14) return true;
     const uint64_t bytes = 8ull * limbs * c->N, mib = 1 << 20;
-    const uint64_t most = inverse ? (c->logN == 12 ? 28 : 35) : (c->logN == 14 ? 33 : 25);
+    const uint64_t most = inverse ? (c->logN == 12 ? 28 : 35) : (c->logN == 12 ? 26 : c->logN == 13 ? 25 : 33);
     return bytes < 19 * mib || bytes > most * mib;
 }
 

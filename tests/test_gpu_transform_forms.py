@@ -13,7 +13,7 @@ MIB = 1 << 20
 
 
 @pytest.mark.parametrize("logN,inverse,least,most", [
-    (12, False, 19, 25), (13, False, 19, 25), (14, False, 19, 33),
+    (12, False, 19, 26), (13, False, 19, 25), (14, False, 19, 33),
     (12, True, 19, 28), (13, True, 19, 35), (14, True, 19, 35),
     (15, False, None, None), (15, True, None, None), (16, True, None, None),
 ])
