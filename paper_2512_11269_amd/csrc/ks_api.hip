@@ -105,13 +105,32 @@ static GatherBundle mod_up_for_gather(const ks_ctx* c, const Level& lv, const vo
     return bundle;
 }
 
+// Inner product of the raised digits of d with the key, and the division of both sums: by P, or (addend: [b][2][ell] packed) of the sums +
+// P addend by P q_{ell-1} in one conversion to q_0..q_{ell-2}, limb ell-1 joining the special limbs as a source.  merged: ModDown and
+// rescale merged (floor throughout); otherwise floor(/ P), then round(/ q_{ell-1}).  The inner product has already added the dropped
+// limb's addend and run the row half of the inverse transform on the sources.
+void key_sums_and_division(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted, const void* evk, uint8_t* acc,
+                           uint8_t* conv, void* out, uint64_t out_bs, uint32_t bc, int tile, hipStream_t s, int d_word, bool words32,
+                           const uint8_t* addend, bool merged) {
+    const uint64_t limb = packed_limb_bytes(c->N), acc_ps = lv.E * limb, conv_ps = lv.ell * limb;
+    const bool meet = sums_meet_division(c, lv, bc);
+    launch_rows_inner_product(c, lv, d, d_ps, lifted, evk, acc, bc, s, d_word, words32, addend, meet);
+    launch_inv_cols_packed(c, addend ? lv.drop_map : lv.special_map, acc, acc_ps, 2 * bc,
+                           !addend ? c->d_moddown_scale : merged ? lv.d_merged_scale : lv.d_rescale_scale, s);
+    if (addend && !merged) launch_rescale_remainder(c, lv, acc, 2 * bc, s);
+    // K sources and ell targets, or one target less and one source more
+    launch_bconv_ntt_cols(c, !addend ? lv.moddown : merged ? lv.merged : lv.rescale, c->K + lv.ell, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s);
+    const FinishScale fs{lv.d_Dinv, lv.d_qlinv, lv.ell - 1};
+    if (meet) launch_rows_key_finish(c, lv, d, d_ps, lifted, evk, conv, addend, out, out_bs, bc, s, d_word, words32, addend ? &fs : nullptr);
+    else launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, addend, 0, nullptr, 0, bc, s, addend ? &fs : nullptr, words32);
+}
+
 // Division by P of both accumulators: INTT of the special limbs (in place), fused base conversion + column half, fused row
 // half + (acc - conv) P^-1.
 void mod_down(const ks_ctx* c, const Level& lv, uint8_t* acc, uint8_t* conv, void* out, uint64_t out_bs,
-              uint32_t bc, bool special_rows_done, int tile, hipStream_t s, bool out_words32 = false) {
+              uint32_t bc, int tile, hipStream_t s, bool out_words32 = false) {
     const uint64_t limb = packed_limb_bytes(c->N), acc_ps = lv.E * limb, conv_ps = lv.ell * limb;
-    // the fused inner product already ran the row half of the inverse transform on the special limbs
-    if (!special_rows_done) launch_inv_rows_packed(c, lv.special_map, acc, acc_ps, 1, acc, acc_ps, 2 * bc, s);
+    launch_inv_rows_packed(c, lv.special_map, acc, acc_ps, 1, acc, acc_ps, 2 * bc, s);
     launch_inv_cols_packed(c, lv.special_map, acc, acc_ps, 2 * bc, c->d_moddown_scale, s);
     launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s);
     launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, nullptr, 0, nullptr, 0, bc, s, nullptr, out_words32);
@@ -334,8 +353,8 @@ int ks::keyswitch_impl(const ks_ctx* c, const void* d, uint32_t ell, const void*
         const char* dc = static_cast<const char*>(d) + (uint64_t)b0 * d_ps * word;
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
         mod_up(c, lv, dc, d_ps, coeff, lifted, bc, tile, s, words32);
-        launch_rows_inner_product(c, lv, dc, d_ps, lifted, evk, acc, bc, s, (int)word, words32);
-        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * out_bs * word, out_bs, bc, true, tile, s, words32);
+        key_sums_and_division(c, lv, dc, d_ps, lifted, evk, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * out_bs * word, out_bs, bc, tile, s, (int)word,
+                              words32, nullptr, false);
     }
     return finish(words32 ? "ks_keyswitch_u32" : "ks_keyswitch");
 }
@@ -486,7 +505,7 @@ static int rotate_mac_impl(const ks_ctx* c, const void* ct, uint32_t ell, const 
         // finished once, shared by every rotation
         const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, n_rot, tile, s, words32);
         rotate_mac_all(c, lv, digits, galois, rot_keys, pts, n_rot, acc, false, s, words32);
-        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, bc, false, tile, s, words32);
+        mod_down(c, lv, acc, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, bc, tile, s, words32);
     }
     return finish(words32 ? "ks_rotate_mac_hoisted_u32" : "ks_rotate_mac_hoisted");
 }
@@ -538,12 +557,12 @@ static int bsgs_impl(const ks_ctx* c, const void* ct, uint32_t ell, const uint32
         const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, n1 * n2, tile, s, words32);
         for (uint32_t g = 0; g < n2; ++g) {
             rotate_mac_all(c, lv, digits, baby_galois, bkeys, ptv + (size_t)g * n1, n1, acc, false, s, words32);
-            mod_down(c, lv, acc, conv, v, ct_bs, bc, false, tile, s);
+            mod_down(c, lv, acc, conv, v, ct_bs, bc, tile, s);
             const GatherBundle digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, v, ct_bs, coeff, lifted, region_v, bc, 1, tile, s, false,
                                                             giant_galois[g] != 1);
             rotate_mac_all(c, lv, digits_v, giant_galois + g, gkeys + g, nullptr, 1, acc_outer, g != 0, s, words32);
         }
-        mod_down(c, lv, acc_outer, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, bc, false, tile, s,
+        mod_down(c, lv, acc_outer, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, bc, tile, s,
                  words32);
     }
     return finish(words32 ? "ks_bsgs_linear_transform_u32" : "ks_bsgs_linear_transform");
@@ -565,21 +584,6 @@ extern "C" int ks_bsgs_linear_transform_u32(const ks_ctx* c, const uint32_t* ct,
     return bsgs_impl(c, ct, ell, baby_galois, reinterpret_cast<const void* const*>(baby_keys), n1, giant_galois,
                      reinterpret_cast<const void* const*>(giant_keys), n2, reinterpret_cast<const void* const*>(pts), out, batch, ws,
                      ws_bytes, stream, true);
-}
-
-// Division by P q_{ell-1} of acc + P addend in one conversion to q_0..q_{ell-2}, limb ell-1 joining the special limbs as a
-// source.  merged: ModDown and rescale merged (floor throughout); otherwise floor(/ P), then round(/ q_{ell-1}).  The fused
-// inner product has already added the dropped limb's addend and run the row half of the inverse transform on the sources.
-// addend: [b][2][ell] packed.
-static void mod_down_drop(const ks_ctx* c, const Level& lv, uint8_t* acc, uint8_t* conv, void* out, uint64_t out_bs,
-                          const uint8_t* addend, uint32_t bc, int tile, hipStream_t s, bool merged, bool out_words32) {
-    const uint64_t limb = packed_limb_bytes(c->N), acc_ps = lv.E * limb, conv_ps = lv.ell * limb;
-    launch_inv_cols_packed(c, lv.drop_map, acc, acc_ps, 2 * bc, merged ? lv.d_merged_scale : lv.d_rescale_scale, s);
-    if (!merged) launch_rescale_remainder(c, lv, acc, 2 * bc, s);
-    const uint32_t n_src = c->K + 1, n_dst = lv.ell - 1;
-    launch_bconv_ntt_cols(c, merged ? lv.merged : lv.rescale, n_src + n_dst, acc, acc_ps, conv, conv_ps, 2 * bc, tile, s);
-    const FinishScale fs{lv.d_Dinv, lv.d_qlinv, n_dst};
-    launch_rows_moddown_finish(c, lv, acc, conv, out, out_bs, addend, 0, nullptr, 0, bc, s, &fs, out_words32);
 }
 
 // cta, ctb, rlk and out in 64-bit words, or all four in 32-bit words (words32).
@@ -612,8 +616,7 @@ static int hmult_impl(const ks_ctx* c, const void* cta, const void* ctb, uint32_
                                static_cast<const char*>(ctb) + (uint64_t)b0 * ct_bs * word, ell, dq, d2, coeff, bc, s, words32);
         const int tile = conversion_tile(c, lv.modup, bc, merged ? lv.merged : lv.rescale, 2 * bc);
         mod_up_from_rows(c, lv, coeff, lifted, bc, tile, s);
-        launch_rows_inner_product(c, lv, d2, w.coeff / bc, lifted, rlk, acc, bc, s, 1, words32, dq);
-        mod_down_drop(c, lv, acc, conv, oc, out_bs, dq, bc, tile, s, merged, words32);
+        key_sums_and_division(c, lv, d2, w.coeff / bc, lifted, rlk, acc, conv, oc, out_bs, bc, tile, s, 1, words32, dq, merged);
     }
     if (merged) return finish(words32 ? "hmult_relin_rescale_merged_u32" : "hmult_relin_rescale_merged");
     return finish(words32 ? "hmult_relin_rescale_u32" : "hmult_relin_rescale");

@@ -224,20 +224,52 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
 #undef KS_LAUNCH_BCONV
 }
 
+// Where the sums of a launch go (SumsEnd of every batch item).
+template <typename W>
+struct SumsOut {
+    uint8_t* acc;               // [b][2][E] packed
+    const uint8_t* addend;      // [b][2][ell] packed, or null (FINISH == 0: of the limb that is dropped)
+    double drop_mul;
+    const uint8_t* conv;        // [b][2][ell] packed
+    W* out;                     // [b][2][n_pos] words, batch items out_bs apart
+    uint64_t out_bs;
+    const double *mul, *addend_mul;   // by limb
+};
+template <int FINISH, typename W>
+__device__ __forceinline__ SumsEnd<W> sums_end(const SumsOut<W>& o, uint32_t b, uint32_t pos, uint32_t ell, uint32_t E, uint32_t n_pos, uint32_t N) {
+    const uint64_t limb = packed_limb_bytes(N);
+    SumsEnd<W> end{};
+    if constexpr (FINISH == 0) {
+        end.acc = o.acc + (uint64_t)b * 2 * E * limb;
+        end.drop = o.addend ? o.addend + (uint64_t)b * 2 * ell * limb : nullptr;
+        end.drop_mul = o.drop_mul;
+    } else {
+        end.conv = o.conv + (uint64_t)b * 2 * ell * limb;
+        if constexpr (FINISH == 2) end.addend = o.addend + (uint64_t)b * 2 * ell * limb;
+        end.out = o.out + (uint64_t)b * o.out_bs + (uint64_t)pos * N;
+        end.out_comp = (uint64_t)n_pos * N;
+        end.mul = o.mul[pos];
+        if constexpr (FINISH == 2) end.admul = o.addend_mul[pos];
+    }
+    return end;
+}
+
 // ------------------------------------------------------------------------------------------------
-// acc[b][c][pos] = sum_j d~_j[pos] * key[j][c][m(pos)].  For pos inside digit j, d~_j[pos] is the input limb
+// Inner product with the key: sum[c][pos] = sum_j d~_j[pos] * key[j][c][m(pos)].  For pos inside digit j, d~_j[pos] is the input limb
 // itself; otherwise it is the raised limb, whose row half of the forward transform is done here.
 // A workgroup = four rows of one limb position; it walks the digits, so d~ is read once and feeds both key
-// components (load reuse), and the accumulators are reduced and written once.
+// components (load reuse).
+//   Calls of several ciphertexts run it twice (sums_meet_division): ahead of the division on the limbs that the division drops (FINISH == 0),
+// and as its last kernel on the limbs that stay (FINISH > 0), where the sums meet the converted limbs in registers and never exist
+// in memory.
 // ------------------------------------------------------------------------------------------------
-// WD / WK: word types of d (uint8_t: packed) and of the key.
-template <int LOG_R, typename WD, typename WK, bool PREFETCH>
+// WD / WK: word types of d (uint8_t: packed) and of the key; the output has the key's.
+template <int LOG_R, typename WD, typename WK, bool PREFETCH, int FINISH>
 __global__ __launch_bounds__(64, 2) void rows_inner_product(TwTables tw, TwTables twi, const Mod* __restrict__ mods, DigitRanges dg,
                                                          uint32_t ell, uint32_t E, uint32_t L, uint32_t M,
                                                          const WD* __restrict__ d, uint64_t d_ps,
                                                          const uint8_t* __restrict__ lifted, const WK* __restrict__ evk,
-                                                         uint8_t* __restrict__ acc, const uint8_t* __restrict__ drop, double drop_mul,
-                                                         uint32_t batch, uint32_t special_first) {
+                                                         SumsOut<WK> o, uint32_t pos0, uint32_t n_pos, uint32_t batch, uint32_t special_first) {
     constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R;
     constexpr uint64_t LIMB = packed_limb_bytes(N);
     __shared__ InnerProductLds lds;
@@ -246,56 +278,106 @@ __global__ __launch_bounds__(64, 2) void rows_inner_product(TwTables tw, TwTable
     // (row group, position) tile before moving to the next tile, so the key slots and twiddles of a tile are
     // fetched into that L2 once and reused by the whole batch.
     const uint32_t slot = blockIdx.x >> 3, b = slot % batch, tile = (slot / batch) * 8 + (blockIdx.x & 7);
-    if (tile >= (R / 4) * E) return;  // uniform: padding workgroups when the tile count is not a multiple of 8
+    if (tile >= (R / 4) * n_pos) return;  // uniform: padding workgroups when the tile count is not a multiple of 8
     // special_first (launches whose wavefronts are all resident at once, i.e. a single ciphertext): the special limbs take
     // the first workgroup ids.  Their wavefronts have the most arithmetic after their last load (one more transform and the
     // two inverse row passes) and the memory system serves the earliest requests first, so started last they are the tail
     // of the launch (59 k cycles per special wavefront against 37 k for the others; 40.2 -> 37.1 us per launch).  Batched
     // launches keep them last: the next kernel reads exactly these limbs and finds them cached (0.5-2 % per call).
     const uint32_t rg = tile % (R / 4), slot_pos = tile / (R / 4), n_special = E - ell;
-    const uint32_t pos = !special_first ? slot_pos : slot_pos < n_special ? ell + slot_pos : slot_pos - n_special;
-    task_rows_inner_product<LOG_R, WD, WK, PREFETCH>(tw, twi, mods, dg, ell, E, L, M, d + (uint64_t)b * d_ps, lifted + (uint64_t)b * dg.ndig * E * LIMB,
-                                      evk, acc + (uint64_t)b * 2 * E * LIMB, drop ? drop + (uint64_t)b * 2 * ell * LIMB : nullptr, drop_mul,
-                                      pos, rg, threadIdx.x, lds);
+    const uint32_t pos = !special_first ? pos0 + slot_pos : slot_pos < n_special ? ell + slot_pos : slot_pos - n_special;
+    task_rows_inner_product<LOG_R, WD, WK, PREFETCH, FINISH>(tw, twi, mods, dg, ell, E, L, M, d + (uint64_t)b * d_ps,
+                                                             lifted + (uint64_t)b * dg.ndig * E * LIMB, evk,
+                                                             sums_end<FINISH>(o, b, pos, ell, E, n_pos, N), pos, rg, threadIdx.x, lds);
 }
 
-void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted,
-                               const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, int d_word, bool key_words32,
-                               const uint8_t* drop_addend) {
-    if (batch == 0) return;
+// Workgroups of a launch over n_pos limb positions.
+static uint32_t sums_grid(const ks_ctx* c, uint32_t n_pos, uint32_t batch) { return (c->N / 1024 * n_pos + 7) / 8 * 8 * batch; }
+
+// Sums that meet the division save 10 bytes of traffic a residue of the ciphertext limbs, a seventh of a key-switch's; but two launches, the
+// first of them over the special limbs alone, need work for the whole chip each.  The line is at three and a half wavefronts per SIMD in a
+// launch over all limbs.  Calls in two launches against one and a kernel of its own for the division, us, by wavefronts of that launch:
+// N = 2^16, 24 limbs, 2048 102.5 / 98.4, 4096 148.7 / 149.5, 6144 198.3 / 206.4, 8192 243.5 / 258.0, 12288 345.2 / 368.1; 28 bits 4096
+// 133.7 / 135.8, 8192 214.5 / 226.6; 21 limbs multiplied 3712 179.1 / 177.8, 7424 288.6 / 294.5, 14848 536 / 563; N = 2^15 2048 96.2 / 88.5,
+// 4096 140.7 / 140.6, 8192 232.4 / 247.1; N = 2^14 2048 92.1 / 84.3, 3840 293.8 / 302.7.
+bool sums_meet_division(const ks_ctx* c, const Level& lv, uint32_t batch) { return sums_grid(c, lv.E, batch) > 3584; }
+
+template <int FINISH, typename WK>
+static void launch_rows_sums(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted, const void* evk,
+                             const SumsOut<WK>& o, uint32_t pos0, uint32_t n_pos, uint32_t batch, hipStream_t s, int d_word) {
     DigitRanges dg;
     dg.ndig = lv.ndig;
     for (uint32_t j = 0; j < kMaxDigits; ++j) {
         dg.lo[j] = j < lv.ndig ? lv.digit_lo[j] : 0;
         dg.hi[j] = j < lv.ndig ? lv.digit_hi[j] : 0;
     }
-    // reads: every raised digit limb per ciphertext and the key (once per call); writes: both accumulators
-    // the key and (but for a tensor product) d arrive in boundary words, the raised limbs and the sums packed
-    const double wd = d_word == 1 ? 5.0 : d_word, wk = key_words32 ? 4.0 : 8.0;
-    ProfScope ps("rows_inner_product",
-                 ((double)batch * (5.0 * (lv.ndig * lv.E - lv.ell) + wd * lv.ell + 10.0 * lv.E) + wk * 2.0 * lv.ndig * lv.E) * c->N, s);
-    const uint32_t tiles = (c->N / 1024) * lv.E;
-    const dim3 grid(((tiles + 7) / 8) * 8 * batch), block(64);
+    const uint32_t grid = sums_grid(c, n_pos, batch);
     // launches with more than two wavefronts per SIMD (1024 SIMDs) to run take the variant that requests the next digit's
     // loads early (3 % faster there); the single-ciphertext launch is bound by
     // bandwidth and gains nothing from it
-    const bool prefetch = grid.x > 2048;
-#define KS_LAUNCH_IP(LOGR, WDT, WKT, PF)                                                                                                 \
-    hipLaunchKernelGGL((rows_inner_product<LOGR, WDT, WKT, PF>), grid, block, 0, s, c->tw_fwd, c->tw_inv, c->d_mod, dg, lv.ell, lv.E, c->L,  \
-                       c->M, static_cast<const WDT*>(d), d_ps, lifted, static_cast<const WKT*>(evk), acc, drop_addend, lv.Pmod_last, batch, \
-                       prefetch ? 0u : 1u)
-#define KS_LAUNCH_PF(LOGR, PF)                                                \
-    if (d_word == 4) KS_LAUNCH_IP(LOGR, uint32_t, uint32_t, PF);               \
-    else if (d_word == 8) KS_LAUNCH_IP(LOGR, uint64_t, uint64_t, PF);          \
-    else if (key_words32) KS_LAUNCH_IP(LOGR, uint8_t, uint32_t, PF);           \
-    else KS_LAUNCH_IP(LOGR, uint8_t, uint64_t, PF)
-#define KS_LAUNCH(LOGR)                          \
-    if (prefetch) { KS_LAUNCH_PF(LOGR, true); } \
-    else { KS_LAUNCH_PF(LOGR, false); }
+    const bool prefetch = grid > 2048, all = FINISH == 0 && n_pos == lv.E;
+#define KS_LAUNCH_IP(LOGR, WDT, PF)                                                                                                            \
+    hipLaunchKernelGGL((rows_inner_product<LOGR, WDT, WK, PF, FINISH>), dim3(grid), dim3(64), 0, s, c->tw_fwd, c->tw_inv, c->d_mod, dg, lv.ell, \
+                       lv.E, c->L, c->M, static_cast<const WDT*>(d), d_ps, lifted, static_cast<const WK*>(evk), o, pos0, n_pos, batch,          \
+                       all && !prefetch ? 1u : 0u)
+#define KS_LAUNCH_WD(LOGR, WDT)                           \
+    if (prefetch) KS_LAUNCH_IP(LOGR, WDT, true);     \
+    else KS_LAUNCH_IP(LOGR, WDT, false)
+#define KS_LAUNCH(LOGR)                                                     \
+    if constexpr (FINISH == 1) { KS_LAUNCH_IP(LOGR, WK, true); }            \
+    else if constexpr (FINISH == 2) { KS_LAUNCH_IP(LOGR, uint8_t, true); }  \
+    else if (d_word == 1) { KS_LAUNCH_WD(LOGR, uint8_t); }                  \
+    else { KS_LAUNCH_WD(LOGR, WK); }
     KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
-#undef KS_LAUNCH_PF
+#undef KS_LAUNCH_WD
 #undef KS_LAUNCH_IP
+}
+
+// bytes that a launch over n_pos positions, `own` of them in a digit of their own, reads of d, the raised limbs and the key (once per call)
+static double sums_bytes(const Level& lv, uint32_t n_pos, uint32_t own, uint32_t batch, int d_word, bool words32) {
+    return (double)batch * (5.0 * (lv.ndig * n_pos - own) + (d_word == 1 ? 5.0 : d_word) * own) + (words32 ? 4.0 : 8.0) * 2.0 * lv.ndig * n_pos;
+}
+
+void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted,
+                               const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, int d_word, bool words32,
+                               const uint8_t* drop_addend, bool dropped_only) {
+    if (batch == 0) return;
+    const uint32_t pos0 = !dropped_only ? 0 : drop_addend ? lv.ell - 1 : lv.ell, n_pos = lv.E - pos0;
+    ProfScope ps("rows_inner_product", (sums_bytes(lv, n_pos, lv.ell - pos0, batch, d_word, words32) + 10.0 * batch * n_pos) * c->N, s);
+    const auto launch = [&](auto word) {
+        using WK = decltype(word);
+        SumsOut<WK> o{};
+        o.acc = acc;
+        o.addend = drop_addend;
+        o.drop_mul = lv.Pmod_last;
+        launch_rows_sums<0, WK>(c, lv, d, d_ps, lifted, evk, o, pos0, n_pos, batch, s, d_word);
+    };
+    if (words32) launch(uint32_t{});
+    else launch(uint64_t{});
+}
+
+void launch_rows_key_finish(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted, const void* evk,
+                            const uint8_t* conv, const uint8_t* addend, void* out, uint64_t out_bs, uint32_t batch, hipStream_t s,
+                            int d_word, bool words32, const FinishScale* fs) {
+    const uint32_t n_pos = fs ? fs->out_limbs : lv.ell;
+    if (batch == 0 || n_pos == 0) return;
+    ProfScope ps("rows_key_finish",
+                 (sums_bytes(lv, n_pos, n_pos, batch, d_word, words32) + (double)batch * n_pos * (10.0 + (fs ? 10.0 : 0.0) + (words32 ? 8.0 : 16.0))) * c->N, s);
+    const auto launch = [&](auto word) {
+        using WK = decltype(word);
+        SumsOut<WK> o{};
+        o.conv = conv;
+        o.addend = addend;
+        o.out = static_cast<WK*>(out);
+        o.out_bs = out_bs;
+        o.mul = fs ? fs->mul : c->d_Pinv;
+        o.addend_mul = fs ? fs->addend_mul : nullptr;
+        if (fs) launch_rows_sums<2, WK>(c, lv, d, d_ps, lifted, evk, o, 0, n_pos, batch, s, d_word);
+        else launch_rows_sums<1, WK>(c, lv, d, d_ps, lifted, evk, o, 0, n_pos, batch, s, d_word);
+    };
+    if (words32) launch(uint32_t{});
+    else launch(uint64_t{});
 }
 
 // ------------------------------------------------------------------------------------------------

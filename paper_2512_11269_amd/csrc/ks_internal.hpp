@@ -219,13 +219,15 @@ struct FinishRotations {
     uint32_t galois[kMacRotations];
 };
 // Fused row half of the forward transform of the raised digits + inner product with the key.
-// d_word: bytes of a word of d, 8 or 4, or 1: packed limbs in rows order (then d_ps counts bytes); key_words32: the key holds one residue
+// d_word: bytes of a word of d, 8 or 4, or 1: packed limbs in rows order (then d_ps counts bytes); words32: the key holds one residue
 // per 32-bit word (4-byte words of d imply them).  acc: [b][2][E] packed.  The ciphertext limbs are in rows order; the special limbs have been through the row half of their inverse
 // transform and are in columns order.  drop_addend != nullptr: limb ell-1 joins the special limbs after P times limb ell-1 of that
-// addend ([b][2][ell] packed) has been added.
+// addend ([b][2][ell] packed) has been added.  dropped_only: only the limbs that the division drops, the special ones and that one.
 void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted,
-                               const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, int d_word, bool key_words32,
-                               const uint8_t* drop_addend = nullptr);
+                               const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, int d_word, bool words32,
+                               const uint8_t* drop_addend, bool dropped_only);
+// Whether a call forms the sums of the limbs that stay where the division ends (launch_rows_key_finish) instead of in memory.
+bool sums_meet_division(const ks_ctx* c, const Level& lv, uint32_t batch);
 // Fused row half of the forward transform of the converted limbs (conv, [b][2][ell] packed) + (acc - conv) P^-1 (+ addend);
 // the ciphertext limbs of acc ([b][2][E] packed) are in rows order.
 // fs == nullptr: multiply by P^-1, ell output limbs; with `rotations` (their galois elements are read) acc and conv hold that many
@@ -241,6 +243,11 @@ void launch_rows_moddown_finish(const ks_ctx* c, const Level& lv, const uint8_t*
                                 uint64_t out_batch_stride, const void* addend, uint64_t addend_batch_stride,
                                 const MacRotations* rotations, uint64_t out_rot_stride, uint32_t batch, hipStream_t s,
                                 const FinishScale* fs = nullptr, bool out_words32 = false);
+// The inner product on the limbs that stay and launch_rows_moddown_finish in one: out = (sum - conv) P^-1, or with fs (sum - conv) fs->mul[i] +
+// addend fs->addend_mul[i].  out has the key's words.
+void launch_rows_key_finish(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted, const void* evk,
+                            const uint8_t* conv, const uint8_t* addend, void* out, uint64_t out_bs, uint32_t batch, hipStream_t s,
+                            int d_word, bool words32, const FinishScale* fs);
 // Remainder of the dropped limb for a rescale.  acc: [polys][E], the drop_map limbs as sources of a conversion (canonical: y_k on the
 // special limbs, P^-1 times the dropped limb's sum on limb ell-1); limb ell-1 becomes the centred remainder of (sum - converted
 // special part) P^-1 modulo q_{ell-1}, a signed source.

@@ -286,12 +286,16 @@ __device__ __forceinline__ void task_bconv_mfma_cols(const double* __restrict__ 
 }
 
 // ---- row half of the forward transform of the raised limbs + inner product with the key (see ks_fused.hip) ----------
-// One wavefront: four rows (group rg) of limb position pos of one batch item.  d_b / lifted_b / acc_b: that batch item's
-// d [ell][N] words, raised digits [ndig][E] and accumulators [2][E] in packed limbs.
-// The ciphertext limbs of the sums are left for the last kernel of the call in rows order.  The special limbs, and limb ell - 1
-// where drop_b says that it is dropped (drop_b: that batch item's addend [2][ell], packed; null otherwise), go through the row
-// half of their inverse transform and are left in columns order.
-// WD / WK: word types of d and of the key (64-bit, or 32-bit for moduli below 2^32; uint8_t: d in packed limbs, rows order).
+// One wavefront: four rows (group rg) of limb position pos of one batch item.  d_b / lifted_b: that batch item's
+// d [ell][N] words and raised digits [ndig][E] in packed limbs.
+// What becomes of the two sums:
+//   FINISH == 0: they are left in acc ([2][E] packed limbs).  Those of the ciphertext limbs stay there in rows order; those of the special
+// limbs, and of limb ell - 1 where drop says that it is dropped (drop: that batch item's addend [2][ell], packed; null otherwise), go
+// through the row half of their inverse transform and are left in columns order.
+//   FINISH == 1 (ciphertext limbs): the division itself, out = (sum - conv) * mul, conv being the converted limbs [2][ell], whose forward row
+// half is done here; FINISH == 2: + addend * admul (packed, [2][ell]).
+// WD / WK: word types of d and of the key (64-bit, or 32-bit for moduli below 2^32; uint8_t: d in packed limbs, rows order); the output
+// has the key's.
 // PREFETCH: loads are requested in the order x(0), key(0), x(1), key(1), ... and return in that order.
 // While digit j is transformed, key(j) and x(j + 1) are in flight; every key slot is refilled with the next digit's as soon
 // as its product is done, so key(j + 1) has the whole transform of digit j + 1 to arrive.
@@ -299,12 +303,22 @@ struct InnerProductLds {
     double rows[4 * kRowPitch];        // exchange buffer
     double ta[4 * 16], tb[15 * 64];    // twiddles: every digit's transform uses the same ones (store_row_twiddles)
 };
-template <int LOG_R, typename WD, typename WK, bool PREFETCH>
+// What the sums of a task end in (see above).
+template <typename W>
+struct SumsEnd {
+    uint8_t* acc;              // FINISH == 0
+    const uint8_t* drop;
+    double drop_mul;
+    const uint8_t *conv, *addend;   // FINISH > 0
+    W* out;                    // limb pos of component 0
+    uint64_t out_comp;         // words to that of component 1
+    double mul, admul;
+};
+template <int LOG_R, typename WD, typename WK, bool PREFETCH, int FINISH>
 __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, const TwTables& twi, const Mod* __restrict__ mods,
                                                         const DigitRanges& dg, uint32_t ell, uint32_t E, uint32_t L, uint32_t M,
                                                         const WD* __restrict__ d_b, const uint8_t* __restrict__ lifted_b,
-                                                        const WK* __restrict__ evk, uint8_t* __restrict__ acc_b,
-                                                        const uint8_t* __restrict__ drop_b, double drop_mul, uint32_t pos,
+                                                        const WK* __restrict__ evk, const SumsEnd<WK>& end, uint32_t pos,
                                                         uint32_t rg, uint32_t lane, InnerProductLds& lds) {
     constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R;
     constexpr uint64_t LIMB = packed_limb_bytes(N);
@@ -378,8 +392,7 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
             unpack_rows(t, x);
         }
     };
-    const auto transform = [&](uint32_t j, double (&x)[16]) {
-        if (own(j)) return;
+    const auto transform = [&](double (&x)[16]) {
         uint32_t ta_at = rr * 16, tb_at = lane;
         asm volatile("" : "+v"(ta_at), "+v"(tb_at));   // the twiddles stay in LDS: hoisted out of the loop they take sixty registers
         radix16_fwd_lds(x, lds.ta + ta_at, 1, m);
@@ -398,9 +411,15 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
     const WK* keys = evk + (uint64_t)mid * N + off;
     const uint64_t comp = (uint64_t)M * N;
     Source xn;
+    PackedRaw conv, addend;
+    const auto request_end = [&](uint32_t comp) {
+        conv = packed_load<64>(end.conv + ((uint64_t)comp * ell + pos) * LIMB, N, at);
+        if constexpr (FINISH == 2) addend = packed_load<64>(end.addend + ((uint64_t)comp * ell + pos) * LIMB, N, at);
+    };
     request(0, xn);
     store_row_twiddles(lds.ta, lds.tb, tw, mid, N, R + row, lane, m);
     __syncthreads();
+    static_assert(PREFETCH || FINISH == 0, "built forms");
     if constexpr (PREFETCH) {
         WK kc0[16], kc1[16];
 #pragma unroll
@@ -414,7 +433,8 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
             double x[16];
             values(j, xn, x);
             if constexpr (NEXT) request(j + 1, xn);
-            transform(j, x);
+            else if constexpr (FINISH != 0) request_end(0);
+            if (!own(j)) transform(x);
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
                 a0[k] += mulmod_lazy(x[k], word_to_f64<WK>(kc0[k]), m);
@@ -441,7 +461,7 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
             for (int k = 0; k < 16; ++k) k1[k] = kp[comp + 16 * k];
             double x[16];
             values(j, xn, x);
-            transform(j, x);
+            if (!own(j)) transform(x);
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
                 a0[k] += mulmod_lazy(x[k], word_to_f64<WK>(k0[k]), m);
@@ -449,27 +469,46 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
             }
         }
     }
-    uint8_t* o0 = acc_b + (uint64_t)pos * LIMB;
-    uint8_t* o1 = acc_b + ((uint64_t)E + pos) * LIMB;
+    if constexpr (FINISH != 0) {
+        const auto finish = [&](const double (&a)[16], uint32_t comp) {
+            double w[16], ad[16];
+            unpack_rows(conv, w);
+            if constexpr (FINISH == 2) unpack(addend, ad);
+            if (comp == 0) request_end(1);   // ahead of the stores (loads and stores share one in-order counter)
+            transform(w);
+            WK* op = end.out + comp * end.out_comp + off;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        a0[k] = reduce_lazy(a0[k], m);
-        a1[k] = reduce_lazy(a1[k], m);
-    }
-    const bool dropped = drop_b && pos + 1 == ell;  // uniform
-    if (pos < ell && !dropped) {
-        packed_store<64>(o0, N, at, pack(a0));
-        packed_store<64>(o1, N, at, pack(a1));
+            for (int k = 0; k < 16; ++k) {
+                double r = mulmod_lazy(a[k] - w[k], end.mul, m);
+                if constexpr (FINISH == 2) r = reduce_lazy(r + mulmod_lazy(ad[k], end.admul, m), m);
+                op[16 * k] = f64_to_word<WK>(canon(r, m));
+            }
+        };
+        finish(a0, 0);
+        finish(a1, 1);
     } else {
+        uint8_t* o0 = end.acc + (uint64_t)pos * LIMB;
+        uint8_t* o1 = end.acc + ((uint64_t)E + pos) * LIMB;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            a0[k] = reduce_lazy(a0[k], m);
+            a1[k] = reduce_lazy(a1[k], m);
+        }
+        const bool dropped = end.drop && pos + 1 == ell;  // uniform
+        if (pos < ell && !dropped) {
+            packed_store<64>(o0, N, at, pack(a0));
+            packed_store<64>(o1, N, at, pack(a1));
+            return;
+        }
         if (dropped) {  // the limb a rescale drops becomes a source like the special limbs, its addend included
-            const PackedRaw r0 = packed_load<64>(drop_b + (uint64_t)pos * LIMB, N, at), r1 = packed_load<64>(drop_b + ((uint64_t)ell + pos) * LIMB, N, at);
+            const PackedRaw r0 = packed_load<64>(end.drop + (uint64_t)pos * LIMB, N, at), r1 = packed_load<64>(end.drop + ((uint64_t)ell + pos) * LIMB, N, at);
             double d0[16], d1[16];
             unpack(r0, d0);
             unpack(r1, d1);
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
-                a0[k] = reduce_lazy(a0[k] + mulmod_lazy(d0[k], drop_mul, m), m);
-                a1[k] = reduce_lazy(a1[k] + mulmod_lazy(d1[k], drop_mul, m), m);
+                a0[k] = reduce_lazy(a0[k] + mulmod_lazy(d0[k], end.drop_mul, m), m);
+                a1[k] = reduce_lazy(a1[k] + mulmod_lazy(d1[k], end.drop_mul, m), m);
             }
         }
         // Special limbs go straight into ModDown: the row half of their inverse transform works on the very

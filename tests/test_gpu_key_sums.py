@@ -1,0 +1,44 @@
+"""The forms of the inner product with the key: sums that meet the division in registers, and sums in memory."""
+
+import pytest
+import torch
+
+import paper_2512_11269_amd as K
+from gpu_util import Setup, assert_equal, host, workspace
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bits", [36, 28])
+@pytest.mark.parametrize("logN,L,Kk,dnum,ell,batch", [
+    (16, 5, 5, 1, 5, 6),      # one digit: no raised ciphertext limb
+    (16, 6, 2, 3, 6, 8),
+    (16, 7, 3, 3, 7, 6),      # short last digit
+    (16, 7, 3, 3, 4, 9),      # a digit of one limb
+    (15, 10, 3, 4, 10, 9),
+    (15, 18, 3, 6, 17, 6),    # more digits than a wavefront for each takes
+])
+def test_sums_meet_the_division(bits, logN, L, Kk, dnum, ell, batch):
+    """Every ciphertext of a batch as in a call of its own, whose sums go through memory; the first and the last against the reference."""
+    st = Setup(logN, L, Kk, dnum, bits=bits)
+    wide = bits == 36
+    word = (lambda t: t) if wide else (lambda t: t.to(torch.int32))
+    evk = word(st.uniform(61, 1, (dnum, 2), list(range(L + Kk))))
+    d, cta, ctb = (word(st.uniform(61, 2 + i, lead, list(range(ell)))) for i, lead in enumerate(((batch,), (batch, 2), (batch, 2))))
+    fns = (K.ks_keyswitch, K.hmult_relin_rescale, K.hmult_relin_rescale_merged) if wide else \
+        (K.ks_keyswitch_u32, K.hmult_relin_rescale_u32, K.hmult_relin_rescale_merged_u32)
+    refs = (st.ref.keyswitch, st.ref.hmult_relin_rescale, st.ref.hmult_relin_rescale_merged)
+    for i, (fn, ref) in enumerate(zip(fns, refs)):
+        args, limbs, op = ((d,), ell, K.KS_OP_KEYSWITCH) if i == 0 else ((cta, ctb), ell - 1, K.KS_OP_HMULT_RELIN_RESCALE)
+        out = torch.full((batch, 2, limbs, st.N), -1, dtype=evk.dtype, device="cuda")
+        K.ks_profile_enable(True)
+        fn(st.ctx, *args, ell, evk, out, workspace(st.ctx, op, ell, batch))
+        ran = {r["kernel"] for r in K.ks_profile_report()}
+        K.ks_profile_enable(False)
+        assert "rows_key_finish" in ran and "rows_moddown_finish" not in ran
+        one, ws = torch.empty_like(out[:1]), workspace(st.ctx, op, ell, 1)
+        for b in range(batch):
+            fn(st.ctx, *(a[b:b + 1] for a in args), ell, evk, one, ws)
+            assert torch.equal(out[b:b + 1], one), b
+        for b in (0, batch - 1):
+            assert_equal(out[b:b + 1].long(), ref(*(host(a[b:b + 1].long()) for a in args), host(evk.long()), ell))
