@@ -224,6 +224,10 @@ void launch_bconv_ntt_cols(const ks_ctx* c, const PlanSet& plans, uint32_t limbs
 #undef KS_LAUNCH_BCONV
 }
 
+// Digits that rows_split takes: its LDS stays below 64 KB.
+constexpr uint32_t kSplitDigits = 4;
+static_assert(rows_split_lds(kSplitDigits) <= 65536, "LDS of rows_split");
+
 // Where the sums of a launch go (SumsEnd of every batch item).
 template <typename W>
 struct SumsOut {
@@ -291,6 +295,27 @@ __global__ __launch_bounds__(64, 2) void rows_inner_product(TwTables tw, TwTable
                                                              sums_end<FINISH>(o, b, pos, ell, E, n_pos, N), pos, rg, threadIdx.x, lds);
 }
 
+template <int LOG_R, typename WD, typename WK>
+__global__ __launch_bounds__(64 * (kSplitDigits + 2), 2) void rows_inner_product_split(TwTables tw, TwTables twi, const Mod* __restrict__ mods,
+                                                      DigitRanges dg, uint32_t ell, uint32_t E, uint32_t L, uint32_t M,
+                                                      const WD* __restrict__ d, uint64_t d_ps, const uint8_t* __restrict__ lifted,
+                                                      const WK* __restrict__ evk, uint8_t* __restrict__ acc,
+                                                      const uint8_t* __restrict__ drop, double drop_mul, uint32_t batch) {
+    constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R;
+    constexpr uint64_t LIMB = packed_limb_bytes(N);
+    extern __shared__ double split_lds[];
+    const uint32_t slot = blockIdx.x >> 3, b = slot % batch, tile = (slot / batch) * 8 + (blockIdx.x & 7);   // as above
+    if (tile >= (R / 4) * E) return;  // uniform
+    const uint32_t rg = tile % (R / 4), slot_pos = tile / (R / 4), n_special = E - ell, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t pos = slot_pos < n_special ? ell + slot_pos : slot_pos - n_special;   // the longest chains first
+    SumsEnd<WK> end{};
+    end.acc = acc + (uint64_t)b * 2 * E * LIMB;
+    end.drop = drop ? drop + (uint64_t)b * 2 * ell * LIMB : nullptr;
+    end.drop_mul = drop_mul;
+    task_rows_split<LOG_R, WD, WK>(tw, twi, mods, dg, ell, E, L, M, d + (uint64_t)b * d_ps, lifted + (uint64_t)b * dg.ndig * E * LIMB, evk,
+                                   end, pos, rg, wave, threadIdx.x & 63u, split_lds);
+}
+
 // Workgroups of a launch over n_pos limb positions.
 static uint32_t sums_grid(const ks_ctx* c, uint32_t n_pos, uint32_t batch) { return (c->N / 1024 * n_pos + 7) / 8 * 8 * batch; }
 
@@ -316,12 +341,22 @@ static void launch_rows_sums(const ks_ctx* c, const Level& lv, const void* d, ui
     // loads early (3 % faster there); the single-ciphertext launch is bound by
     // bandwidth and gains nothing from it
     const bool prefetch = grid > 2048, all = FINISH == 0 && n_pos == lv.E;
+    // A wavefront per digit and component where all workgroups are resident at once: three a compute unit (up to three digits, 118 registers
+    // and 42 KB of LDS) or two (four digits).  One key-switch, a wavefront for everything -> split: N = 2^12, 48 workgroups 33.6 -> 29.8 us, 256
+    // 39.1 -> 33.1; N = 2^13 192 38.0 -> 34.5, 384 45.3 -> 37.8; N = 2^14 512 48.6 -> 44.1, 720 54.1 -> 53.0, 768 54.6 -> 53.5, but 1024
+    // 59.8 -> 64.8; N = 2^15 256 49.0 -> 45.0, 800 59.7 -> 63.9; N = 2^16 640 46.4 -> 45.3; 28 bits 768 46.6 -> 44.6.
+    const bool split = all && lv.ndig <= kSplitDigits && grid <= (lv.ndig <= 3 ? 768u : 512u);
 #define KS_LAUNCH_IP(LOGR, WDT, PF)                                                                                                            \
     hipLaunchKernelGGL((rows_inner_product<LOGR, WDT, WK, PF, FINISH>), dim3(grid), dim3(64), 0, s, c->tw_fwd, c->tw_inv, c->d_mod, dg, lv.ell, \
                        lv.E, c->L, c->M, static_cast<const WDT*>(d), d_ps, lifted, static_cast<const WK*>(evk), o, pos0, n_pos, batch,          \
                        all && !prefetch ? 1u : 0u)
+#define KS_LAUNCH_SPLIT(LOGR, WDT)                                                                                                             \
+    hipLaunchKernelGGL((rows_inner_product_split<LOGR, WDT, WK>), dim3(grid), dim3(64 * (lv.ndig + 2)), rows_split_lds(lv.ndig), s, c->tw_fwd,  \
+                       c->tw_inv, c->d_mod, dg, lv.ell, lv.E, c->L, c->M, static_cast<const WDT*>(d), d_ps, lifted,                            \
+                       static_cast<const WK*>(evk), o.acc, o.addend, o.drop_mul, batch)
 #define KS_LAUNCH_WD(LOGR, WDT)                           \
-    if (prefetch) KS_LAUNCH_IP(LOGR, WDT, true);     \
+    if (split) KS_LAUNCH_SPLIT(LOGR, WDT);                \
+    else if (prefetch) KS_LAUNCH_IP(LOGR, WDT, true);     \
     else KS_LAUNCH_IP(LOGR, WDT, false)
 #define KS_LAUNCH(LOGR)                                                     \
     if constexpr (FINISH == 1) { KS_LAUNCH_IP(LOGR, WK, true); }            \
@@ -331,6 +366,7 @@ static void launch_rows_sums(const ks_ctx* c, const Level& lv, const void* d, ui
     KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
 #undef KS_LAUNCH_WD
+#undef KS_LAUNCH_SPLIT
 #undef KS_LAUNCH_IP
 }
 

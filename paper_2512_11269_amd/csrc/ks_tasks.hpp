@@ -522,6 +522,144 @@ __device__ __forceinline__ void task_rows_inner_product(const TwTables& tw, cons
     }
 }
 
+// ---- the same (FINISH == 0) for launches of few wavefronts: a workgroup per four rows, a wavefront per digit and one per key component ----
+// A wavefront of task_rows_inner_product works through its digits one after the other (load, transform, products) and then through both
+// components; where a launch leaves the chip idle that chain is its time.  Here every load of the four rows is requested at once:
+// wavefront j < ndig transforms digit j and leaves it in LDS, wavefront ndig + c multiplies by the keys of component c, adds and does
+// what follows for that component.
+// Every wavefront passes the same three barriers: twiddles ready, digits ready, digits read.
+// lds: rows_split_lds(ndig) bytes.
+struct RowTwiddlesLds {
+    double ta[4 * 16], tb[15 * 64];
+};
+constexpr uint32_t kRowsBuffer = 4 * kRowPitch;   // doubles: four rows of an exchange buffer
+constexpr uint32_t rows_split_lds(uint32_t ndig) {
+    return (ndig < 2 ? 2 : ndig) * kRowsBuffer * 8 + 2 * (uint32_t)sizeof(RowTwiddlesLds);
+}
+template <int LOG_R, typename WD, typename WK>
+__device__ __forceinline__ void task_rows_split(const TwTables& tw, const TwTables& twi, const Mod* __restrict__ mods, const DigitRanges& dg,
+                                                uint32_t ell, uint32_t E, uint32_t L, uint32_t M, const WD* __restrict__ d_b,
+                                                const uint8_t* __restrict__ lifted_b, const WK* __restrict__ evk, const SumsEnd<WK>& end,
+                                                uint32_t pos, uint32_t rg, uint32_t wave, uint32_t lane, double* lds) {
+    constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R;
+    constexpr uint64_t LIMB = packed_limb_bytes(N);
+    const uint32_t mid = pos < ell ? pos : L + (pos - ell);
+    const Mod m = mods[mid];
+    const uint32_t j0 = lane & 15, rr = lane >> 4, row = rg * 4 + rr;
+    const uint32_t off = row * 256 + j0, at = rg * 256 + lane;
+    RowTwiddlesLds* tf = reinterpret_cast<RowTwiddlesLds*>(lds);   // forward, then inverse
+    RowTwiddlesLds* ti = tf + 1;
+    double* rows = reinterpret_cast<double*>(tf + 2);
+    const bool dropped = end.drop && pos + 1 == ell, divided = pos >= ell || dropped;   // uniform
+    if (wave < dg.ndig) {
+        const uint32_t j = wave;
+        const bool own = pos >= dg.lo[j] && pos < dg.hi[j];   // uniform
+        double* lrow = rows + j * kRowsBuffer + rr * kRowPitch;
+        double x[16];
+        if (own) {
+            if constexpr (sizeof(WD) == 1) {
+                const PackedRaw t = packed_load<64>(reinterpret_cast<const uint8_t*>(d_b) + pos * LIMB, N, at);
+                unpack(t, x);
+            } else {
+                const WD* src = d_b + (uint64_t)pos * N + off;
+#pragma unroll
+                for (int k = 0; k < 16; ++k) x[k] = word_to_f64<WD>(src[16 * k]);
+            }
+#pragma unroll
+            for (int k = 0; k < 16; ++k) lrow[j0 + 17 * k] = x[k];
+            __syncthreads();
+        } else {
+            const PackedRaw t = packed_load<64>(lifted_b + ((uint64_t)j * E + pos) * LIMB, N, at);
+            __syncthreads();
+            unpack_rows(t, x);
+            radix16_fwd_lds(x, tf->ta + rr * 16, 1, m);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) lrow[j0 + 17 * k] = x[k];
+            wave_lds_sync();
+#pragma unroll
+            for (int k = 0; k < 16; ++k) x[k] = lrow[17 * j0 + k];
+            radix16_fwd_lds(x, tf->tb + lane - 64, 64, m);
+            wave_lds_sync();
+#pragma unroll
+            for (int k = 0; k < 16; ++k) lrow[17 * j0 + k] = x[k];
+        }
+        __syncthreads();
+        __syncthreads();
+        return;
+    }
+    const uint32_t c = wave - dg.ndig;
+    const uint64_t comp = (uint64_t)M * N;
+    const WK* keys = evk + (uint64_t)mid * N + off + c * comp;
+    // keys requested ahead of everything else; the others follow when these are used
+    constexpr uint32_t AHEAD = 2;
+    WK key[AHEAD][16];
+#pragma unroll
+    for (uint32_t a = 0; a < AHEAD; ++a) {
+        const WK* kp = keys + (uint64_t)min(a, dg.ndig - 1) * 2 * comp;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) key[a][k] = kp[16 * k];
+    }
+    if (c == 1 || divided) {
+        const TwTables t{c ? tw.W : twi.W, c ? tw.trow : twi.trow, c ? tw.w16 : twi.w16};
+        RowTwiddlesLds* to = c ? tf : ti;
+        store_row_twiddles(to->ta, to->tb, t, mid, N, R + row, lane, m);
+    }
+    __syncthreads();
+    __syncthreads();
+    double a[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a[k] = 0.0;
+#pragma unroll 1
+    for (uint32_t j = 0; j < dg.ndig; j += AHEAD) {
+        if (j != 0) {
+#pragma unroll
+            for (uint32_t i = 0; i < AHEAD; ++i) {
+                const WK* kp = keys + (uint64_t)min(j + i, dg.ndig - 1) * 2 * comp;
+#pragma unroll
+                for (int k = 0; k < 16; ++k) key[i][k] = kp[16 * k];
+            }
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < AHEAD; ++i) {
+            if (j + i >= dg.ndig) break;
+            const double* x = rows + (j + i) * kRowsBuffer + rr * kRowPitch + j0;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) a[k] += mulmod_lazy(x[17 * k], word_to_f64<WK>(key[i][k]), m);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a[k] = reduce_lazy(a[k], m);
+    __syncthreads();   // both components have read the digits: their buffers are free
+    uint8_t* out = end.acc + ((uint64_t)c * E + pos) * LIMB;
+    if (!divided) {
+        packed_store<64>(out, N, at, pack(a));
+        return;
+    }
+    double* lrow = rows + c * kRowsBuffer + rr * kRowPitch;
+    if (dropped) {
+        double ad[16];
+        unpack(packed_load<64>(end.drop + ((uint64_t)c * ell + pos) * LIMB, N, at), ad);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) a[k] = reduce_lazy(a[k] + mulmod_lazy(ad[k], end.drop_mul, m), m);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) lrow[j0 + 17 * k] = a[k];
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a[k] = lrow[17 * j0 + k];
+    radix16_inv_lds(a, ti->tb + lane - 64, 64, m);
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) lrow[17 * j0 + k] = reduce_lazy(a[k], m);
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a[k] = lrow[j0 + 17 * k];
+    radix16_inv_lds(a, ti->ta + rr * 16, 1, m);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a[k] = reduce_lazy(a[k], m);
+    packed_store<64>(out, N, at, pack_rows(a));
+}
+
 // ---- row half of the forward transform of the converted limbs + (acc - conv) * mul (+ addend) ------------------------
 // One wavefront: four rows (group rg) of limb i.  conv / acc: that limb of the converted limbs and of the accumulators, packed; op: of the
 // output.  adp: that limb of the addend.  ADDEND: 0 = none, 1 = words like the output's, read through sigma_galois where GATHER,

@@ -156,6 +156,30 @@ __device__ __forceinline__ void radix16_fwd_lds(double (&v)[16], const double* t
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (U < 3) radix16_fwd_lds<U + 1>(v, t, stride, m);
 }
+// radix16_inv the same way.
+template <int U = 3>
+__device__ __forceinline__ void radix16_inv_lds(double (&v)[16], const double* t, uint32_t stride, Mod m) {
+    constexpr int HALF = 8 >> U;
+    double w[1 << U];
+#pragma unroll
+    for (int g = 0; g < (1 << U); ++g) w[g] = t[stride * ((1 << U) + g)];
+#pragma unroll
+    for (int g = 0; g < (1 << U); ++g)
+#pragma unroll
+        for (int i = 0; i < HALF; ++i) {
+            const int k = g * 2 * HALF + i;
+            const double x = v[k], y = v[k + HALF];
+            v[k] = x + y;
+            v[k + HALF] = mulmod_lazy(x - y, w[g], m);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (U > 0) radix16_inv_lds<U - 1>(v, t, stride, m);
+}
+// What a wavefront wrote to LDS can be read by its other lanes (LDS takes a wavefront's accesses in order; this keeps the compiler to it).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 // First 8 inverse stages of one row (t built from the inverse table).  in: v[k] = point j0 + 16 k, |v| <= p.
 // out: same layout, |v| <= 0.51 p.
 __device__ __forceinline__ void row_inv_core(double (&v)[16], const PassTwiddles& t, uint32_t j0, double* lrow, Mod m) {

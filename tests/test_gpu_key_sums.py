@@ -42,3 +42,33 @@ def test_sums_meet_the_division(bits, logN, L, Kk, dnum, ell, batch):
             assert torch.equal(out[b:b + 1], one), b
         for b in (0, batch - 1):
             assert_equal(out[b:b + 1].long(), ref(*(host(a[b:b + 1].long()) for a in args), host(evk.long()), ell))
+
+
+@pytest.mark.parametrize("bits", [36, 28])
+@pytest.mark.parametrize("logN,L,Kk,dnum,ell,batch", [
+    (12, 4, 2, 2, 4, 1),
+    (12, 3, 3, 1, 3, 2),      # one digit
+    (12, 7, 2, 4, 7, 3),      # as many digits as the form takes, a short last one
+    (12, 7, 2, 4, 3, 14),
+    (13, 5, 2, 3, 2, 1),      # launches padded to eight workgroups
+    (14, 4, 4, 1, 1, 9),      # one limb
+    (15, 8, 4, 3, 8, 2),      # 768 workgroups
+    (15, 9, 4, 3, 9, 2),      # the form with a wavefront for everything
+])
+def test_a_wavefront_per_digit_and_component(bits, logN, L, Kk, dnum, ell, batch):
+    st = Setup(logN, L, Kk, dnum, bits=bits)
+    wide = bits == 36
+    word = (lambda t: t) if wide else (lambda t: t.to(torch.int32))
+    evk = word(st.uniform(62, 1, (dnum, 2), list(range(L + Kk))))
+    d, cta, ctb = (word(st.uniform(62, 2 + i, lead, list(range(ell)))) for i, lead in enumerate(((batch,), (batch, 2), (batch, 2))))
+    fns = (K.ks_keyswitch, K.hmult_relin_rescale, K.hmult_relin_rescale_merged) if wide else \
+        (K.ks_keyswitch_u32, K.hmult_relin_rescale_u32, K.hmult_relin_rescale_merged_u32)
+    refs = (st.ref.keyswitch, st.ref.hmult_relin_rescale, st.ref.hmult_relin_rescale_merged)
+    for i, (fn, ref) in enumerate(zip(fns, refs)):
+        if i and ell < 2:
+            continue
+        args, limbs, op = ((d,), ell, K.KS_OP_KEYSWITCH) if i == 0 else ((cta, ctb), ell - 1, K.KS_OP_HMULT_RELIN_RESCALE)
+        out = torch.full((batch, 2, limbs, st.N), -1, dtype=evk.dtype, device="cuda")
+        fn(st.ctx, *args, ell, evk, out, workspace(st.ctx, op, ell, batch))
+        for b in sorted({0, batch - 1}):
+            assert_equal(out[b:b + 1].long(), ref(*(host(a[b:b + 1].long()) for a in args), host(evk.long()), ell))
