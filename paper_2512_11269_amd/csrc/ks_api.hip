@@ -478,6 +478,23 @@ static void rotate_mac_all(const ks_ctx* c, const Level& lv, const GatherBundle&
     }
 }
 
+// u_i = sum_r pt_{i, r} * rot_{g_r}(ct) for n rows of diagonals (ptv [n][n_rot]), u_i u_stride bytes apart
+static void rotate_mac_rows_all(const ks_ctx* c, const Level& lv, const GatherBundle& src, const uint32_t* galois, const void* const* keys,
+                                const void* const* ptv, uint32_t n_rot, uint32_t n, uint8_t* u, uint64_t u_stride, hipStream_t s, bool key_words32) {
+    for (uint32_t r0 = 0; r0 < n_rot; r0 += kMacRotations) {
+        MacRotations rot{};
+        MacRows rows{};
+        rot.n = std::min<uint32_t>(n_rot - r0, kMacRotations);
+        rows.n = n;
+        for (uint32_t r = 0; r < rot.n; ++r) {
+            rot.galois[r] = galois[r0 + r];
+            rot.key[r] = keys[r0 + r];
+            for (uint32_t i = 0; i < n; ++i) rows.pt[i][r] = ptv[(size_t)i * n_rot + r0 + r];
+        }
+        launch_rotate_mac_rows(c, lv, src, rot, rows, u, u_stride, r0 != 0, s, key_words32);
+    }
+}
+
 static int rotate_mac_impl(const ks_ctx* c, const void* ct, uint32_t ell, const uint32_t* galois, const void* const* rot_keys,
                            const void* const* pts, uint32_t n_rot, void* out, uint32_t batch, void* ws, size_t ws_bytes, void* stream,
                            bool words32) {
@@ -549,18 +566,33 @@ static int bsgs_impl(const ks_ctx* c, const void* ct, uint32_t ell, const uint32
         uint64_t* region_v = region + gather_words(c, lv, bc, true, words32);   // sources of the outer level: the current inner result
         uint8_t* coeff = reinterpret_cast<uint8_t*>(region_v + gather_words(c, lv, bc, false, false));
         uint8_t* lifted = coeff + w.coeff;          // scratch of a ModUp
-        uint8_t* acc = lifted + w.lifted;           // inner sum of the current giant step
-        uint8_t* conv = acc + w.acc;
+        uint8_t* conv = lifted + w.lifted;
         uint8_t* acc_outer = conv + w.conv;         // outer sum over the giant steps
         uint64_t* v = reinterpret_cast<uint64_t*>(acc_outer + w.acc);   // [bc][2][ell][N] inner result of the current giant step (64-bit words)
+        uint8_t* acc = reinterpret_cast<uint8_t*>(v + (uint64_t)bc * 2 * ell * N);   // inner sums of the giant steps at hand
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
         const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, n1 * n2, tile, s, words32);
-        for (uint32_t g = 0; g < n2; ++g) {
-            rotate_mac_all(c, lv, digits, baby_galois, bkeys, ptv + (size_t)g * n1, n1, acc, false, s, words32);
-            mod_down(c, lv, acc, conv, v, ct_bs, bc, tile, s);
-            const GatherBundle digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, v, ct_bs, coeff, lifted, region_v, bc, 1, tile, s, false,
-                                                            giant_galois[g] != 1);
-            rotate_mac_all(c, lv, digits_v, giant_galois + g, gkeys + g, nullptr, 1, acc_outer, g != 0, s, words32);
+        // Inner sums of four or two giant steps at a time where the workspace holds them (a caller brings what ks_workspace_bytes asks for, 8
+        // bytes a residue) and the bundle has c0.  Groups of more than four are two halves there, which have to pay with shared keys for what
+        // they load twice: four rows, more than one digit.  Eight baby and four giant steps, N = 2^16, us by rows at a time, 1 / 2 / 4: three
+        // digits, one ciphertext 1220 / 980 / 822, four 2423 / 2180 / 1908, five 2905 / 3025 / 2583, eight 4143 / 4347 / 3638; two digits, four
+        // 1884 / 1737 / 1563, eight 3253 / 3438 / 2967; one digit, one 595 / 537, four 1161 / 1152, eight 2023 / 2217; 28 bits, three digits,
+        // one 894 / 772 / 672, eight 3627 / 3443 / 3215.
+        const uint64_t have = ks_workspace_bytes(c, words32 ? KS_OP_BSGS_U32 : KS_OP_BSGS, ell, bc, 0), used = acc - static_cast<uint8_t*>(ws);
+        const uint64_t fit = digits.c0 ? 1 : (have - used) / w.acc;
+        const bool small = bc <= 4, rows4 = fit >= kMacRows && (small || lv.ndig > 1), rows2 = fit >= 2 && small;
+        for (uint32_t g0 = 0, n; g0 < n2; g0 += n) {
+            n = rows4 && n2 - g0 >= kMacRows ? kMacRows : rows2 && n2 - g0 >= 2 ? 2 : 1;
+            const void* const* pts = ptv + (size_t)g0 * n1;
+            if (n == 1) rotate_mac_all(c, lv, digits, baby_galois, bkeys, pts, n1, acc, false, s, words32);
+            else rotate_mac_rows_all(c, lv, digits, baby_galois, bkeys, pts, n1, n, acc, w.acc, s, words32);
+            for (uint32_t i = 0; i < n; ++i) {
+                const uint32_t g = g0 + i;
+                mod_down(c, lv, acc + i * w.acc, conv, v, ct_bs, bc, tile, s);
+                const GatherBundle digits_v = mod_up_for_gather(c, lv, v + (uint64_t)ell * N, v, ct_bs, coeff, lifted, region_v, bc, 1, tile, s, false,
+                                                                giant_galois[g] != 1);
+                rotate_mac_all(c, lv, digits_v, giant_galois + g, gkeys + g, nullptr, 1, acc_outer, g != 0, s, words32);
+            }
         }
         mod_down(c, lv, acc_outer, conv, static_cast<char*>(out) + (uint64_t)b0 * ct_bs * word, ct_bs, bc, tile, s,
                  words32);

@@ -319,6 +319,16 @@ void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& 
 void launch_rotate_mac(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint8_t* u,
                        bool accumulate, hipStream_t s, bool key_words32 = false);
 
+// The sums of several rows of diagonals over the same rotations in one launch: u_i (+)= sum_r pt[i][r] * (...) as above, i < n (2 or
+// kMacRows), u_i u_stride bytes apart.  The bundle holds c0.
+constexpr uint32_t kMacRows = 4;
+struct MacRows {
+    uint32_t n;
+    const void* pt[kMacRows][kMacRotations];
+};
+void launch_rotate_mac_rows(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, const MacRows& rows, uint8_t* u,
+                            uint64_t u_stride, bool accumulate, hipStream_t s, bool key_words32);
+
 // The key-switch chain behind ks_keyswitch / ks_keyswitch_u32 (argument checks included); ws is any device buffer of
 // at least ks_workspace_bytes(KS_OP_KEYSWITCH) bytes, whose contents need no initialisation.
 int keyswitch_impl(const ks_ctx* c, const void* d, uint32_t ell, const void* evk, void* out, uint32_t batch, void* ws,

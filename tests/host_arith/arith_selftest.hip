@@ -85,6 +85,26 @@ static void check_prime(uint64_t p) {
         const double r = mac_reduce(hi, lo, m);
         CHECK(fabs(r) <= lim && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "mac_reduce");
     }
+    // mac_wide: as many products as it takes, of the largest operands of one sign (the largest roundings) and of others, from a lazy start
+    for (int rep = 0; rep < 3000; ++rep) {
+        const int64_t start = rep % 3 == 0 ? 0 : rnd_signed(37);
+        double hi = (double)start;
+        uint64_t lo = (uint32_t)start;
+        i128 exact = start;
+        const double most = 68719476736.0;   // 2^36
+        for (int i = 0; i < kMacWideTerms; ++i) {
+            int64_t x = rep % 5 == 0 ? (int64_t)most - (int64_t)(rnd() & 0xFF) : rep % 5 == 1 ? rnd_signed(37) : (int64_t)(rnd() % p);
+            int64_t k = rep % 7 == 0 ? (int64_t)most - (int64_t)(rnd() & 0xFF) : (int64_t)(rnd() % p);
+            if (rep % 5 == 1 && (x > (int64_t)most || x < -(int64_t)most)) x /= 2;
+            if (p < (1ull << 35)) { x %= (int64_t)p; k %= (int64_t)p; }
+            mac_wide((double)x, (double)k, (uint32_t)x, (uint32_t)k, hi, lo);
+            exact += (i128)x * k;
+        }
+        uint32_t low;
+        const double r = mac_wide_reduce(hi, lo, m, &low);
+        CHECK(fabs(r) <= 0.51 * (double)p + 2147483648.0 && mod_i128((i128)(int64_t)r, p) == mod_i128(exact, p), "mac_wide_reduce");
+        CHECK(low == (uint32_t)(int64_t)r, "mac_wide_reduce low word");
+    }
     // mac_int (moduli below 2^28): the same with 64-bit integers, to both ends of their range
     for (int rep = 0; rep < 3000 && p < (1ull << 28); ++rep) {
         const int terms = rep % 3 == 0 ? kMacTermsLazy : kMacTerms;
