@@ -1,0 +1,394 @@
+// Gathers that hold the sums of several rows of diagonals, and gathers that meet the division (see ks_gather.hpp).
+#include <algorithm>
+
+#include "ks_gather.hpp"
+#include "ks_tasks.hpp"
+
+namespace ks {
+
+// ------------------------------------------------------------------------------------------------
+// Several rows of diagonals over the same rotations (the inner sums of a baby-step giant-step transform).  The rotated ciphertext of a
+// baby step, sum_j sigma_b(digit_j) key_{b,j} (+ P sigma_b(c0)), is the same for every giant step: a thread forms it once for a slot, reduces
+// it and multiplies it by the plaintext slots of `R` giant steps, whose sums it holds.  Keys and gathered slots, which are what
+// rotate_mac_kernel reads, are then read once for R sums instead of for each.
+//   Four rows of sixteen diagonals, eight ciphertexts, three digits, N = 2^16: 2280 us as four launches of rotate_mac_kernel, 1393; 28 bits
+// 1668 -> 768.  What bounds it: the traffic (keys 1.6 GB, plaintexts 1.1, slots), with half of the issue slots.
+//   The sums of R = 4 rows take the registers that eight ciphertexts would: a workgroup takes H, up to four, the two halves of a bundle of
+// more on the same slots in one workgroup, which so finds keys and plaintexts in cache the second time.  A half's slots of one (position, half of the
+// limb) and three digits are 1.8 MB at N = 2^16, which stay in that XCD's L2 from one rotation to the next.
+//   Two wavefronts a SIMD do not hide a load of the next step (1684 us): with a set of operands for each digit, up to three, a load has the
+// time of a whole rotation.
+// ------------------------------------------------------------------------------------------------
+// 256 threads a half (both in a launch where they have H ciphertexts each); half0: the first of them.
+template <int H, int R, typename WK, bool PACKED, bool INT, uint32_t DIGITS>
+__global__ __launch_bounds__(512, 2) void rotate_mac_rows_kernel(const Mod* __restrict__ mods, const double* __restrict__ Pmod, uint32_t ell,
+                                                                 uint32_t E, uint32_t L, uint32_t M, uint32_t logN, DigitRanges dg,
+                                                                 uint32_t parts_log, GatherBundle bundle, MacRotations rot, MacRows rows,
+                                                                 uint32_t n_key, uint32_t half0, uint8_t* __restrict__ u,
+                                                                 uint64_t u_stride, int accumulate) {
+    using Sum = WideSum<INT>;
+    using Factor = typename Sum::Factor;
+    const uint32_t N = 1u << logN;
+    const GatherTile tile = gather_tile(E, logN, parts_log);
+    if (!tile.valid) return;  // uniform
+    const uint32_t half = half0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), pos = tile.pos, n = tile.n;
+    const uint32_t mid = pos < ell ? pos : L + (pos - ell);
+    const Mod m = mods[mid];
+    const uint64_t slots = ((uint64_t)dg.ndig * E + ell) * N;
+    const uint32_t hi_bytes = gather_hi_bytes(bundle.group);
+    const HalfSource src{uniform_rsrc(bundle.lo, slots * 4 * bundle.group), uniform_rsrc(bundle.hi, PACKED ? slots * hi_bytes : 0), bundle.group, half, hi_bytes};
+    const uint64_t comp = E * packed_limb_bytes(N);
+    uint8_t* up = u + (uint64_t)half * 8 * comp + (uint64_t)pos * packed_limb_bytes(N);
+    Sum s[R][2 * H];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int b = 0; b < 2 * H; ++b) s[i][b].start(accumulate ? packed_get(up + i * u_stride + b * comp, N, packed_element(n)) : 0.0);
+    const Factor pm = [&] {
+        const double v = pos < ell ? Pmod[pos] : 0.0;
+        return Sum::word((WK)v);
+    }();
+    struct Raw {
+        HalfRaw<H> x;
+        WK k0, k1;
+    };
+    auto fetch = [&](uint32_t r, uint32_t j) {
+        Raw w;
+        const uint32_t sn = galois_source_slot(n, rot.galois[r], logN);
+        // a key is below 4 GB: [8][2][255][2^16] words of at most 8 bytes
+        const BufferRsrc key = uniform_rsrc(rot.key[r], (uint64_t)dg.ndig * 2 * M * N * sizeof(WK));
+        const uint32_t at = (j * 2 * M + mid) * N * (uint32_t)sizeof(WK);
+        w.x = half_load<H, PACKED>(src, j * E + pos, N, sn);
+        w.k0 = buffer_load<WK>(key, n * (uint32_t)sizeof(WK), at);
+        w.k1 = buffer_load<WK>(key, n * (uint32_t)sizeof(WK), at + M * N * (uint32_t)sizeof(WK));
+        return w;
+    };
+    const auto plaintexts = [&](uint32_t r, WK (&w)[R]) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const void* pt = rows.pt[i][r];   // uniform; null: the constant 1
+            w[i] = pt ? buffer_load<WK>(uniform_rsrc(pt, (uint64_t)M * N * sizeof(WK)), n * (uint32_t)sizeof(WK), mid * N * (uint32_t)sizeof(WK)) : (WK)1;
+        }
+    };
+    // One rotation after the other.  DIGITS: what a step has used is requested again for the next rotation, so that a load has a whole
+    // rotation to arrive; 0: any number of digits, one step ahead.
+    if (n_key != 0) {   // uniform
+        constexpr uint32_t SETS = DIGITS ? DIGITS : 1;
+        Raw set[SETS];
+#pragma unroll
+        for (uint32_t j = 0; j < SETS; ++j) set[j] = fetch(0, j);
+#pragma unroll 1
+        for (uint32_t r = 0; r < n_key; ++r) {
+            const uint32_t after = min(r + 1, n_key - 1);
+            WK w[R];
+            plaintexts(r, w);
+            // (above ell the addend's slabs have none for this position: any other is read against a factor of zero)
+            const HalfRaw<H> c0 = half_load<H, PACKED>(src, dg.ndig * E + min(pos, ell - 1), N, galois_source_slot(n, rot.galois[r], logN));
+            Sum t[2 * H];
+#pragma unroll
+            for (int b = 0; b < 2 * H; ++b) t[b].start(0.0);
+            const auto step = [&](const Raw& q) {
+                __builtin_amdgcn_sched_barrier(0);
+                const Factor k0 = Sum::word(q.k0), k1 = Sum::word(q.k1);
+                Factor x[H];
+                half_take<H, PACKED, INT>(src, q.x, x);
+#pragma unroll
+                for (int b = 0; b < H; ++b) {
+                    t[2 * b].add(x[b], k0);
+                    t[2 * b + 1].add(x[b], k1);
+                }
+            };
+            if constexpr (DIGITS != 0) {
+#pragma unroll
+                for (uint32_t j = 0; j < DIGITS; ++j) {
+                    step(set[j]);
+                    set[j] = fetch(after, j);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+#pragma unroll 1
+                for (uint32_t j = 0; j < dg.ndig; ++j) {
+                    const bool last = j + 1 == dg.ndig;
+                    const Raw next = fetch(last ? after : r, last ? 0 : j + 1);
+                    step(set[0]);
+                    set[0] = next;
+                }
+            }
+            Factor x[H];
+            half_take<H, PACKED, INT>(src, c0, x);
+#pragma unroll
+            for (int b = 0; b < H; ++b) t[2 * b].add(x[b], pm);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int b = 0; b < 2 * H; ++b) {
+                const Factor v = t[b].reduced(m);
+#pragma unroll
+                for (int i = 0; i < R; ++i) s[i][b].add(v, Sum::word(w[i]));
+                __builtin_amdgcn_sched_barrier(0);   // one at a time: the registers are taken
+            }
+        }
+    }
+    if (pos < ell) {  // uniform: P (c0, c1) of the identities
+        uint32_t own = 0;
+        while (own + 1 < dg.ndig && pos >= dg.hi[own]) ++own;
+#pragma unroll 1
+        for (uint32_t r = n_key; r < rot.n; ++r) {
+            WK w[R];
+            plaintexts(r, w);
+            const HalfRaw<H> r0 = half_load<H, PACKED>(src, dg.ndig * E + pos, N, n), r1 = half_load<H, PACKED>(src, own * E + pos, N, n);
+            Factor x[2][H];
+            half_take<H, PACKED, INT>(src, r0, x[0]);
+            half_take<H, PACKED, INT>(src, r1, x[1]);
+#pragma unroll
+            for (int b = 0; b < 2 * H; ++b) {
+                Sum t;
+                t.start(0.0);
+                t.add(x[b & 1][b / 2], pm);
+                const Factor v = t.reduced(m);
+#pragma unroll
+                for (int i = 0; i < R; ++i) s[i][b].add(v, Sum::word(w[i]));
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        double sums[2 * H];
+#pragma unroll
+        for (int b = 0; b < 2 * H; ++b) sums[b] = s[i][b].result(m);
+        packed_put<2 * H>(up + i * u_stride, comp, N, packed_element(n & ~63u), sums);
+    }
+}
+
+void launch_rotate_mac_rows(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, const MacRows& rows, uint8_t* u,
+                            uint64_t u_stride, bool accumulate, hipStream_t s, bool key_words32) {
+    if (rot.n == 0) return;
+    // quarters where the slots of a half are more than an XCD's L2 keeps beside the streams: eight ciphertexts, N = 2^16, three digits (3.5 MB)
+    // 1472 -> 1393 us; two digits (2.4 MB) 1350 -> 1336, 28 bits (3.1 MB) 768 -> 790, two ciphertexts 669 -> 677
+    const bool large = lv.ndig * src.group * src_bytes(src) * (c->N / 2) > 3.3 * (1 << 20);
+    const uint32_t pl = std::max(gather_parts_log(lv.E), large ? 2u : 1u);
+    DigitRanges dg;
+    dg.ndig = lv.ndig;
+    for (uint32_t j = 0; j < kMaxDigits; ++j) {
+        dg.lo[j] = j < lv.ndig ? lv.digit_lo[j] : 0;
+        dg.hi[j] = j < lv.ndig ? lv.digit_hi[j] : 0;
+    }
+    MacRotations sorted = rot;
+    MacRows pts = rows;
+    uint32_t n_key = 0, n_id = 0;
+    for (int pass = 0; pass < 2; ++pass)
+        for (uint32_t r = 0; r < rot.n; ++r) {
+            if ((rot.galois[r] == 1) != (pass == 1)) continue;
+            const uint32_t to = n_key + n_id;
+            sorted.galois[to] = rot.galois[r];
+            sorted.key[to] = rot.key[r];
+            for (uint32_t i = 0; i < rows.n; ++i) pts.pt[i][to] = rows.pt[i][r];
+            ++(pass == 0 ? n_key : n_id);
+        }
+    // reads and writes as rotate_mac's, but one pass over slots and keys for all rows
+    const double wk = key_words32 ? 4.0 : 8.0;
+    const double reads = src.group * src_bytes(src) * (lv.ndig * lv.E + lv.ell) + wk * (double)rot.n * (2.0 * lv.ndig + rows.n) * lv.E;
+    ProfScope ps("rotate_mac_rows", (reads + (double)src.group * 10 * lv.E * rows.n * (accumulate ? 2 : 1)) * c->N, s,
+                 (double)rot.n * lv.E * c->N * 4.0 * src.group * (2 * lv.ndig + 1 + 2 * rows.n));
+    const bool words32 = !src.hi, ints = words32 && integer_sums(c);
+    const auto launch = [&](uint32_t h, uint32_t half0, uint32_t n_halves) {
+        const dim3 grid(gather_grid(c, lv.E, pl)), block(256 * n_halves);
+#define KS_LAUNCH_ROWS(HV, RV, WKT, PK, IS, DG)                                                                                                \
+    hipLaunchKernelGGL((rotate_mac_rows_kernel<HV, RV, WKT, PK, IS, DG>), grid, block, 0, s, c->d_mod, c->d_Pmod, lv.ell, lv.E, c->L, c->M,     \
+                       c->logN, dg, pl, src, sorted, pts, n_key, half0, u, u_stride, accumulate ? 1 : 0)
+#define KS_LAUNCH_R(HV, WKT, PK, IS)                                                              \
+    if (rows.n != kMacRows) KS_LAUNCH_ROWS(HV, 2, WKT, PK, IS, 0);                                \
+    else if (HV == 4 && lv.ndig == 1) KS_LAUNCH_ROWS(HV, kMacRows, WKT, PK, IS, HV == 4 ? 1 : 0); \
+    else if (HV == 4 && lv.ndig == 2) KS_LAUNCH_ROWS(HV, kMacRows, WKT, PK, IS, HV == 4 ? 2 : 0); \
+    else if (HV == 4 && lv.ndig == 3) KS_LAUNCH_ROWS(HV, kMacRows, WKT, PK, IS, HV == 4 ? 3 : 0); \
+    else KS_LAUNCH_ROWS(HV, kMacRows, WKT, PK, IS, 0)
+#define KS_LAUNCH_H(HV)                                              \
+    {                                                                \
+        if (ints) { KS_LAUNCH_R(HV, uint32_t, false, true); }        \
+        else if (words32) { KS_LAUNCH_R(HV, uint32_t, false, false); } \
+        else { KS_LAUNCH_R(HV, uint64_t, true, false); }             \
+    }
+        switch (h) {
+            case 1: KS_LAUNCH_H(1) break;
+            case 2: KS_LAUNCH_H(2) break;
+            case 3: KS_LAUNCH_H(3) break;
+            default: KS_LAUNCH_H(4) break;
+        }
+#undef KS_LAUNCH_H
+#undef KS_LAUNCH_R
+#undef KS_LAUNCH_ROWS
+    };
+    if (src.group <= 4) launch(src.group, 0, 1);
+    else if (src.group == 8) launch(4, 0, 2);
+    else {
+        launch(4, 0, 1);
+        launch(src.group - 4, 1, 1);
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The end of a group of hoisted rotations on the ciphertext limbs: out[r][b][c] = (sum_j sigma_r(src_j) key_r[j][c] - NTT_rows(conv[r][b][c]))
+// P^-1 + [c = 0] sigma_r(c0[b]), canonical.  The sums meet the converted limbs in LDS and registers and never exist in memory, where they
+// were 10 bytes a residue written and read again.
+//   A workgroup owns four rows of one limb position for H ciphertexts (a half of a bundle of more than four, as above) and walks the
+// rotations of the group.  For each, a wavefront per ciphertext and component runs the row half of the converted limb's transform and
+// leaves it in LDS; then every wavefront takes 64 slots at a time, as the gathers do.  Two workgroups a compute unit (78 KB of LDS,
+// 128 registers), so that one gathers while the other transforms.  Four rotations of eight ciphertexts, three digits, 24 limbs, N = 2^16: 521 us,
+// where the two kernels took 243 + 418.
+// ------------------------------------------------------------------------------------------------
+template <int LOG_R, int H, typename W, bool PACKED, bool INT>
+__global__ __launch_bounds__(128 * H, H == 4 ? 4 : 3) void rotate_finish_kernel(TwTables tw, const Mod* __restrict__ mods, const double* __restrict__ Pinv,
+                                                                   uint32_t ell, uint32_t E, uint32_t M, uint32_t ndig, uint32_t parts_log,
+                                                                   GatherBundle bundle, MacRotations rot, const uint8_t* __restrict__ conv,
+                                                                   W* __restrict__ out, uint64_t out_bs, uint64_t out_rs,
+                                                                   const W* __restrict__ c0, uint64_t c0_bs, uint32_t half0, uint32_t n_halves,
+                                                                   uint32_t per_group) {
+    using Sum = WideSum<INT>;
+    using Factor = typename Sum::Factor;
+    constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R, LOGN = LOG_R + 8;
+    constexpr uint64_t LIMB = packed_limb_bytes(N);
+    __shared__ double rows[2 * H][4 * kRowPitch];
+    __shared__ RowTwiddlesLds tl;
+    // gather_tile with 1024 slots, the halves of a tile next to each other
+    const uint32_t per_unit = 1u << (LOGN - 10 - parts_log), turn = blockIdx.x >> 3, local = turn / n_halves, half = half0 + turn % n_halves;
+    const uint32_t unit = (local / per_unit) * 8 + (blockIdx.x & 7);
+    if (unit >= (ell << parts_log)) return;  // uniform
+    const uint32_t pos = unit >> parts_log, rg = (unit & ((1u << parts_log) - 1)) * per_unit + local % per_unit;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u, j0 = lane & 15u, rr = lane >> 4;
+    const Mod m = mods[pos];
+    const double mul = Pinv[pos];
+    const uint64_t slots = (uint64_t)ndig * E * N;
+    const uint32_t hi_bytes = gather_hi_bytes(bundle.group);
+    const HalfSource src{uniform_rsrc(bundle.lo, slots * 4 * bundle.group), uniform_rsrc(bundle.hi, PACKED ? slots * hi_bytes : 0), bundle.group, half, hi_bytes};
+    // the converted limb of this wavefront: ciphertext wave / 2 of the half, component wave % 2
+    const uint8_t* cv = conv + ((uint64_t)(half * 8 + wave) * ell + pos) * LIMB;
+    const uint64_t cv_rs = (uint64_t)bundle.group * 2 * ell * LIMB;
+    const uint32_t r_first = blockIdx.y * per_group, r_last = min(r_first + per_group, rot.n) - 1;
+    PackedRaw raw = packed_load<64>(cv + r_first * cv_rs, N, rg * 256 + lane);
+    if (wave == 0) store_row_twiddles(tl.ta, tl.tb, tw, pos, N, R + rg * 4 + rr, lane, m);
+    __syncthreads();
+    double* lrow = rows[wave] + rr * kRowPitch;
+#pragma unroll 1
+    for (uint32_t r = r_first; r <= r_last; ++r) {
+        {
+            double w[16];
+            unpack_rows(raw, w);
+            raw = packed_load<64>(cv + min(r + 1, r_last) * cv_rs, N, rg * 256 + lane);
+            uint32_t ta_at = rr * 16, tb_at = lane;
+            asm volatile("" : "+v"(ta_at), "+v"(tb_at));   // the twiddles stay in LDS: hoisted out of the loop they take sixty registers
+            radix16_fwd_lds(w, tl.ta + ta_at, 1, m);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) lrow[j0 + 17 * k] = w[k];
+            wave_lds_sync();
+#pragma unroll
+            for (int k = 0; k < 16; ++k) w[k] = lrow[17 * j0 + k];
+            radix16_fwd_lds(w, tl.tb + tb_at - 64, 64, m);
+            wave_lds_sync();
+#pragma unroll
+            for (int k = 0; k < 16; ++k) lrow[17 * j0 + k] = w[k];
+        }
+        __syncthreads();
+        // a key is below 4 GB: [8][2][255][2^16] words of at most 8 bytes
+        const BufferRsrc key = uniform_rsrc(rot.key[r], (uint64_t)ndig * 2 * M * N * sizeof(W));
+        const uint32_t g = rot.galois[r];
+#pragma unroll 1
+        for (uint32_t tile = wave; tile < 16; tile += 2 * H) {
+            const uint32_t at = tile * 64 + lane, n = rg * 1024 + at, sn = galois_source_slot(n, g, LOGN);
+            struct Raw {
+                HalfRaw<H> x;
+                W k0, k1;
+            };
+            const auto fetch = [&](uint32_t j) {
+                Raw q;
+                const uint32_t limb = (j * 2 * M + pos) * N * (uint32_t)sizeof(W);
+                q.x = half_load<H, PACKED>(src, j * E + pos, N, sn);
+                q.k0 = buffer_load<W>(key, n * (uint32_t)sizeof(W), limb);
+                q.k1 = buffer_load<W>(key, n * (uint32_t)sizeof(W), limb + M * N * (uint32_t)sizeof(W));
+                return q;
+            };
+            Raw cur = fetch(0);
+            W add[H];
+#pragma unroll
+            for (int b = 0; b < H; ++b) add[b] = c0[(uint64_t)(half * 4 + b) * c0_bs + (uint64_t)pos * N + sn];
+            Sum t[2 * H];
+#pragma unroll
+            for (int b = 0; b < 2 * H; ++b) t[b].start(0.0);
+#pragma unroll 1
+            for (uint32_t j = 0; j < ndig; ++j) {
+                const Raw next = fetch(min(j + 1, ndig - 1));
+                const Factor k0 = Sum::word(cur.k0), k1 = Sum::word(cur.k1);
+                Factor x[H];
+                half_take<H, PACKED, INT>(src, cur.x, x);
+#pragma unroll
+                for (int b = 0; b < H; ++b) {
+                    t[2 * b].add(x[b], k0);
+                    t[2 * b + 1].add(x[b], k1);
+                }
+                cur = next;
+            }
+            const uint32_t p = at & 255u, in_row = (at >> 8) * kRowPitch + p + (p >> 4);
+            W* op = out + (uint64_t)(half * 4) * out_bs + (uint64_t)r * out_rs + (uint64_t)pos * N + n;
+#pragma unroll
+            for (int b = 0; b < 2 * H; ++b) {
+                double v = mulmod_lazy(t[b].result(m) - rows[b][in_row], mul, m);
+                if (b % 2 == 0) v = reduce_lazy(v + word_to_f64<W>(add[b / 2]), m);
+                op[(uint64_t)(b / 2) * out_bs + (b & 1) * ((uint64_t)ell * N)] = f64_to_word<W>(canon(v, m));
+            }
+        }
+        __syncthreads();   // the converted limbs have been read
+    }
+}
+
+// Wavefronts with work are what decides, one per rotation, ciphertext, component and four rows: calls with the sums in memory -> meeting the
+// division, us: N = 2^16, 24 limbs, eight ciphertexts 16 rotations (98304) 4839 -> 4181, one rotation (24576) 591 -> 556, one ciphertext 8
+// rotations (24576) 464 -> 447, three ciphertexts one rotation (9216) 259 -> 273; 28 bits, eight 4219 -> 3517; N = 2^15, 20 limbs, two 8
+// rotations (20480) 334 -> 327, one (10240) 235 -> 246; N = 2^14, 11 limbs, eight 16 rotations (22528) 568 -> 546, four (11264) 319 -> 335;
+// N = 2^13, 10 limbs, eight (10240) 304 -> 311.
+bool rotations_meet_division(const ks_ctx* c, const Level& lv, uint32_t group, uint32_t n_rot) {
+    return lv.ell * (c->N / 1024) * 2 * group * n_rot > 16384;
+}
+
+void launch_rotate_finish(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, const uint8_t* conv, void* out,
+                          uint64_t out_bs, uint64_t out_rs, const void* c0, uint64_t c0_bs, hipStream_t s, bool words32) {
+    if (rot.n == 0) return;
+    const uint32_t pl = std::min(lv.ell % 4 == 1 || lv.ell % 4 == 2 ? 2u : 1u, c->logN - 10);
+    const double wk = words32 ? 4.0 : 8.0;
+    ProfScope ps("rotate_finish", (src_bytes(src) * src.group * lv.ndig + (double)rot.n * (wk * 2.0 * lv.ndig + (10.0 + 3.0 * wk) * src.group)) * lv.ell * c->N, s);
+    const uint32_t grid = ((lv.ell << pl) + 7) / 8 * 8 * ((c->N / 1024) >> pl);
+    const bool ints = !src.hi && integer_sums(c);
+    // Rotations that a workgroup walks (the next one's converted limb is requested early, twiddles stay): all, unless that leaves too few
+    // workgroups.  Eight ciphertexts, N = 2^16, 24 limbs (3072), all of four 4181 us, two 4240, one 4409; N = 2^15, 20 limbs (1280) 928, 950,
+    // 975; but four at N = 2^15 (640) all 512, two 491; eight at N = 2^14, 11 limbs (352) all 588, two 546.
+    const uint32_t workgroups = grid * (src.group == 8 ? 2 : 1), shares = workgroups < 1280 ? (2560 + workgroups - 1) / workgroups : 1;
+    const uint32_t per_group = (rot.n + shares - 1) / shares;
+    const auto launch = [&](uint32_t h, uint32_t half0, uint32_t n_halves) {
+#define KS_LAUNCH_RF(LOGR, HV, WT, PK, IS)                                                                                                     \
+    hipLaunchKernelGGL((rotate_finish_kernel<LOGR, HV, WT, PK, IS>), dim3(grid * n_halves, (rot.n + per_group - 1) / per_group), dim3(128 * HV), 0, s, c->tw_fwd, c->d_mod, c->d_Pinv, \
+                       lv.ell, lv.E, c->M, lv.ndig, pl, src, rot, conv, static_cast<WT*>(out), out_bs, out_rs, static_cast<const WT*>(c0), c0_bs, \
+                       half0, n_halves, per_group)
+#define KS_LAUNCH_H(LOGR, HV)                                               \
+    {                                                                       \
+        if (ints) { KS_LAUNCH_RF(LOGR, HV, uint32_t, false, true); }        \
+        else if (words32) { KS_LAUNCH_RF(LOGR, HV, uint32_t, false, false); } \
+        else { KS_LAUNCH_RF(LOGR, HV, uint64_t, true, false); }             \
+    }
+#define KS_LAUNCH(LOGR)                        \
+    switch (h) {                               \
+        case 1: KS_LAUNCH_H(LOGR, 1) break;    \
+        case 2: KS_LAUNCH_H(LOGR, 2) break;    \
+        case 3: KS_LAUNCH_H(LOGR, 3) break;    \
+        default: KS_LAUNCH_H(LOGR, 4) break;   \
+    }
+        KS_FOR_LOG_R(c->logN, KS_LAUNCH)
+#undef KS_LAUNCH
+#undef KS_LAUNCH_H
+#undef KS_LAUNCH_RF
+    };
+    if (src.group <= 4) launch(src.group, 0, 1);
+    else if (src.group == 8) launch(4, 0, 2);
+    else {
+        launch(4, 0, 1);
+        launch(src.group - 4, 1, 1);
+    }
+}
+
+}  // namespace ks

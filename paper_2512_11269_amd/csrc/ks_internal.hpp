@@ -310,8 +310,16 @@ void launch_gather_bundle_rows(const ks_ctx* c, const Level& lv, const uint8_t* 
 // src_j[pos] = slab j E + pos of the bundle.
 // key_words32: keys (and plaintexts) hold one residue per 32-bit word; 32-bit sources imply 32-bit keys.
 // acc: [r][b][2][E], packed limbs in rows order.
+// special_only: only the limbs that the division drops.
 void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, uint8_t* acc, hipStream_t s,
-                          bool key_words32 = false);
+                          bool key_words32, bool special_only);
+
+// Whether a group of rotations of `group` ciphertexts forms the sums of the ciphertext limbs where the division ends (launch_rotate_finish)
+// instead of in memory.
+bool rotations_meet_division(const ks_ctx* c, const Level& lv, uint32_t group, uint32_t n_rot);
+// launch_inner_product on the ciphertext limbs and launch_rows_moddown_finish with rotations in one; conv: [r][b][2][ell] packed.
+void launch_rotate_finish(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, const uint8_t* conv, void* out,
+                          uint64_t out_bs, uint64_t out_rs, const void* c0, uint64_t c0_bs, hipStream_t s, bool words32);
 
 // u[b][c][pos] (+)= sum_r pt_r[pos] * (sum_j sigma_r(src_j)[pos] key_r[j][c][pos] + [c = 0][pos < ell] P sigma_r(c0)[pos]);
 // src: c1 and its finished raised digits, and c0.  u: packed limbs in rows order.  accumulate: add to what u already holds.
