@@ -341,11 +341,13 @@ static void launch_rows_sums(const ks_ctx* c, const Level& lv, const void* d, ui
     // loads early (3 % faster there); the single-ciphertext launch is bound by
     // bandwidth and gains nothing from it
     const bool prefetch = grid > 2048, all = FINISH == 0 && n_pos == lv.E;
-    // A wavefront per digit and component where all workgroups are resident at once: three a compute unit (up to three digits, 118 registers
-    // and 42 KB of LDS) or two (four digits).  One key-switch, a wavefront for everything -> split: N = 2^12, 48 workgroups 33.6 -> 29.8 us, 256
-    // 39.1 -> 33.1; N = 2^13 192 38.0 -> 34.5, 384 45.3 -> 37.8; N = 2^14 512 48.6 -> 44.1, 720 54.1 -> 53.0, 768 54.6 -> 53.5, but 1024
-    // 59.8 -> 64.8; N = 2^15 256 49.0 -> 45.0, 800 59.7 -> 63.9; N = 2^16 640 46.4 -> 45.3; 28 bits 768 46.6 -> 44.6.
-    const bool split = all && lv.ndig <= kSplitDigits && grid <= (lv.ndig <= 3 ? 768u : 512u);
+    // A wavefront per digit and component where all workgroups are resident at once, three a compute unit (118 registers and 42 KB of LDS at
+    // three digits) or two (four digits); fewer digits have less to take apart.  One key-switch, a wavefront for everything -> split: three
+    // digits, N = 2^12, 256 workgroups 39.1 -> 33.1 us, N = 2^14 512 48.6 -> 44.1, 768 54.6 -> 53.5, but 1024 59.8 -> 64.8; N = 2^15 256
+    // 49.0 -> 45.0, 800 59.7 -> 63.9; four, N = 2^13 384 45.3 -> 37.8; two, N = 2^12 48 33.6 -> 29.8, N = 2^13 192 38.0 -> 34.5, N = 2^15 576
+    // 52.0 -> 53.3; one, N = 2^12 128 33.2 -> 31.4, N = 2^14 512 41.2 -> 42.1.
+    const uint32_t most[kSplitDigits] = {256, 512, 768, 512};
+    const bool split = all && lv.ndig <= kSplitDigits && grid <= most[lv.ndig - 1];
 #define KS_LAUNCH_IP(LOGR, WDT, PF)                                                                                                            \
     hipLaunchKernelGGL((rows_inner_product<LOGR, WDT, WK, PF, FINISH>), dim3(grid), dim3(64), 0, s, c->tw_fwd, c->tw_inv, c->d_mod, dg, lv.ell, \
                        lv.E, c->L, c->M, static_cast<const WDT*>(d), d_ps, lifted, static_cast<const WK*>(evk), o, pos0, n_pos, batch,          \
