@@ -4,7 +4,8 @@
 //  * bconv_ntt_cols       base conversion of a digit feeding the column half of the forward transform of
 //                         each target limb: the converted limb never exists in memory in coefficient form.
 //  * rows_inner_product   row half of the forward transform of every raised limb feeding the inner product
-//                         with the key: the raised limb never exists in memory in evaluation form.
+//                         with the key: the raised limb never exists in memory in evaluation form.  In calls of several
+//                         ciphertexts the ciphertext limbs' sums meet the converted limbs there and do not exist in memory either.
 //  * rows_moddown_finish  row half of the forward transform of the converted special part feeding
 //                         (acc - conv) * P^-1 (+ addend).
 //
