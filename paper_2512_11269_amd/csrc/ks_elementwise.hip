@@ -23,7 +23,7 @@ __global__ __launch_bounds__(256, 4) void inner_product_kernel(const Mod* __rest
     using Sum = MacSum<INT>;
     using Factor = typename Sum::Factor;
     const uint32_t N = 1u << logN;
-    const GatherTile tile = gather_tile(E - pos0, logN, parts_log);
+    const GatherTile tile = gather_tile(E - pos0, logN, parts_log, threadIdx.x);
     if (!tile.valid) return;  // uniform
     const uint32_t pos = pos0 + tile.pos, n = tile.n, mid = pos < ell ? pos : L + (pos - ell);
     const Mod m = mods[mid];
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256, INT ? 4 : 3) void rotate_mac_kernel(const Mod*
     using Sum = MacSum<INT>;
     using Factor = typename Sum::Factor;
     const uint32_t N = 1u << logN;
-    const GatherTile tile = gather_tile(E, logN, parts_log);
+    const GatherTile tile = gather_tile(E, logN, parts_log, threadIdx.x);
     if (!tile.valid) return;  // uniform
     const uint32_t pos = tile.pos, n = tile.n, mid = pos < ell ? pos : L + (pos - ell);
     const Mod m = mods[mid];

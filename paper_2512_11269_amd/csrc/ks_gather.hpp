@@ -118,18 +118,18 @@ struct MacSum<true> {
 // (position, half) are the bundle's slots of that position and half: 1.2 MB per digit for eight ciphertexts at N = 2^16,
 // where the whole limb position of a chunk is 7 MB.  Consecutive workgroup ids go to the eight XCDs in turn, each with a
 // 4 MB L2 of its own, so unit u = (position, part) goes to the workgroups of XCD u % 8, which walk one unit after the other:
-// every rotation but the first finds its sources in that L2.  parts_log: gather_parts_log.
+// every rotation but the first finds its sources in that L2.  parts_log: gather_parts_log; thread: 0 .. 255.
 struct GatherTile {
     uint32_t pos, n;
     bool valid;
 };
-__device__ __forceinline__ GatherTile gather_tile(uint32_t E, uint32_t logN, uint32_t parts_log) {
+__device__ __forceinline__ GatherTile gather_tile(uint32_t E, uint32_t logN, uint32_t parts_log, uint32_t thread) {
     const uint32_t per_unit = 1u << (logN - 8 - parts_log), local = blockIdx.x >> 3;
     const uint32_t unit = (local / per_unit) * 8 + (blockIdx.x & 7);
     GatherTile t;
     t.valid = unit < (E << parts_log);
     t.pos = unit >> parts_log;
-    t.n = (((unit & ((1u << parts_log) - 1)) * per_unit + local % per_unit) << 8) + (threadIdx.x & 255u);
+    t.n = (((unit & ((1u << parts_log) - 1)) * per_unit + local % per_unit) << 8) + thread;
     return t;
 }
 inline uint32_t gather_grid(const ks_ctx* c, uint32_t E, uint32_t parts_log) {

@@ -29,7 +29,7 @@ __global__ __launch_bounds__(512, 2) void rotate_mac_rows_kernel(const Mod* __re
     using Sum = WideSum<INT>;
     using Factor = typename Sum::Factor;
     const uint32_t N = 1u << logN;
-    const GatherTile tile = gather_tile(E, logN, parts_log);
+    const GatherTile tile = gather_tile(E, logN, parts_log, threadIdx.x & 255u);
     if (!tile.valid) return;  // uniform
     const uint32_t half = half0 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), pos = tile.pos, n = tile.n;
     const uint32_t mid = pos < ell ? pos : L + (pos - ell);
