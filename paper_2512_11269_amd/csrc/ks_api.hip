@@ -424,14 +424,14 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
                 rot.key[r] = rot_keys[r0 + r];
                 rot.pt[r] = nullptr;
             }
-            const bool meet = rotations_meet_division(c, lv, bc, rot.n);
+            const bool meet = rotations_meet_division(c, lv, bc, rot.n, words32);
             launch_inner_product(c, lv, digits, rot, acc, s, words32, meet);
             const uint32_t polys = 2 * rot.n * bc;
             launch_inv_rows_packed(c, lv.special_map, acc, acc_ps, 1, acc, acc_ps, polys, s);
             launch_inv_cols_packed(c, lv.special_map, acc, acc_ps, polys, c->d_moddown_scale, s);
             launch_bconv_ntt_cols(c, lv.moddown, c->K + lv.ell, acc, acc_ps, conv, conv_ps, polys, tile, s);
             char* to = static_cast<char*>(out) + ((uint64_t)b0 * out_bs + (uint64_t)r0 * 2 * ell * N) * word;
-            if (meet) launch_rotate_finish(c, lv, digits, rot, conv, to, out_bs, 2ull * ell * N, c0, ct_bs, s, words32);
+            if (meet) launch_rotate_finish(c, lv, digits, rot, conv, to, out_bs, c0, s, words32);
             else launch_rows_moddown_finish(c, lv, acc, conv, to, out_bs, c0, ct_bs, &rot, 2ull * ell * N, bc, s, nullptr, words32);
         }
     }

@@ -235,44 +235,54 @@ void launch_rotate_mac_rows(const ks_ctx* c, const Level& lv, const GatherBundle
 // 128 registers), so that one gathers while the other transforms.  Four rotations of eight ciphertexts, three digits, 24 limbs, N = 2^16: 521 us,
 // where the two kernels took 243 + 418.
 // ------------------------------------------------------------------------------------------------
-template <int LOG_R, int H, typename W, bool PACKED, bool INT>
-__global__ __launch_bounds__(128 * H, H == 4 ? 4 : 3) void rotate_finish_kernel(TwTables tw, const Mod* __restrict__ mods, const double* __restrict__ Pinv,
-                                                                   uint32_t ell, uint32_t E, uint32_t M, uint32_t ndig, uint32_t parts_log,
-                                                                   GatherBundle bundle, MacRotations rot, const uint8_t* __restrict__ conv,
-                                                                   W* __restrict__ out, uint64_t out_bs, uint64_t out_rs,
-                                                                   const W* __restrict__ c0, uint64_t c0_bs, uint32_t half0, uint32_t n_halves,
-                                                                   uint32_t per_group) {
+// Wavefronts of a workgroup that holds H ciphertexts: eight for three as well, of which two only gather (sixteen blocks of 64 slots are three
+// turns of six wavefronts but two of eight; 28 bits, five digits, 13 limbs, ten rotations of three 790 -> 581 us).
+constexpr int finish_waves(int h) { return h == 3 ? 8 : 2 * h; }
+struct RotateFinishArgs {
+    TwTables tw;
+    const Mod* mods;
+    const double* Pinv;
+    uint32_t ell, E, M, ndig;
+    const uint8_t* conv;
+    void* out;
+    uint64_t out_bs;
+    const void* c0;
+    uint32_t per_group, half0;
+};
+template <int LOG_R, int H, int WAVES, typename W, bool PACKED, bool INT>
+__device__ __forceinline__ void rotate_finish(const RotateFinishArgs& a, const GatherBundle& bundle, const MacRotations& rot, uint32_t pos, uint32_t rg,
+                                              uint32_t half, double (*rows)[4 * kRowPitch], RowTwiddlesLds& tl) {
     using Sum = WideSum<INT>;
     using Factor = typename Sum::Factor;
     constexpr uint32_t N = 256u << LOG_R, R = 1u << LOG_R, LOGN = LOG_R + 8;
     constexpr uint64_t LIMB = packed_limb_bytes(N);
-    __shared__ double rows[2 * H][4 * kRowPitch];
-    __shared__ RowTwiddlesLds tl;
-    // gather_tile with 1024 slots, the halves of a tile next to each other
-    const uint32_t per_unit = 1u << (LOGN - 10 - parts_log), turn = blockIdx.x >> 3, local = turn / n_halves, half = half0 + turn % n_halves;
-    const uint32_t unit = (local / per_unit) * 8 + (blockIdx.x & 7);
-    if (unit >= (ell << parts_log)) return;  // uniform
-    const uint32_t pos = unit >> parts_log, rg = (unit & ((1u << parts_log) - 1)) * per_unit + local % per_unit;
+    // Blocks of 64 slots that a wavefront has in hand at once: one block of one ciphertext is too few loads in flight (28 bits, four digits,
+    // 20 limbs, fourteen rotations, one block 572, four 465 us).
+    constexpr int FEW = 16 / (H * WAVES), TILES = FEW > 4 ? 4 : FEW < 1 ? 1 : FEW;
+    const uint32_t ell = a.ell, E = a.E, M = a.M, ndig = a.ndig;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u, j0 = lane & 15u, rr = lane >> 4;
-    const Mod m = mods[pos];
-    const double mul = Pinv[pos];
+    const bool transforms = 2 * H == WAVES || wave < 2 * H;   // uniform
+    const Mod m = a.mods[pos];
+    const double mul = a.Pinv[pos];
     const uint64_t slots = (uint64_t)ndig * E * N;
     const uint32_t hi_bytes = gather_hi_bytes(bundle.group);
     const HalfSource src{uniform_rsrc(bundle.lo, slots * 4 * bundle.group), uniform_rsrc(bundle.hi, PACKED ? slots * hi_bytes : 0), bundle.group, half, hi_bytes};
     // the converted limb of this wavefront: ciphertext wave / 2 of the half, component wave % 2
-    const uint8_t* cv = conv + ((uint64_t)(half * 8 + wave) * ell + pos) * LIMB;
+    const uint8_t* cv = a.conv + ((uint64_t)(half * 8 + (transforms ? wave : 0)) * ell + pos) * LIMB;
     const uint64_t cv_rs = (uint64_t)bundle.group * 2 * ell * LIMB;
-    const uint32_t r_first = blockIdx.y * per_group, r_last = min(r_first + per_group, rot.n) - 1;
+    const uint32_t r_first = blockIdx.y * a.per_group, r_last = min(r_first + a.per_group, rot.n) - 1;
     PackedRaw raw = packed_load<64>(cv + r_first * cv_rs, N, rg * 256 + lane);
-    if (wave == 0) store_row_twiddles(tl.ta, tl.tb, tw, pos, N, R + rg * 4 + rr, lane, m);
+    if (wave == 0) store_row_twiddles(tl.ta, tl.tb, a.tw, pos, N, R + rg * 4 + rr, lane, m);
     __syncthreads();
-    double* lrow = rows[wave] + rr * kRowPitch;
 #pragma unroll 1
     for (uint32_t r = r_first; r <= r_last; ++r) {
-        {
+        if (transforms) {
+            double* lrow = rows[wave] + rr * kRowPitch;
             double w[16];
             unpack_rows(raw, w);
-            raw = packed_load<64>(cv + min(r + 1, r_last) * cv_rs, N, rg * 256 + lane);
+            uint32_t from = lane;
+            asm volatile("" : "+v"(from));   // the offset is formed anew: kept across the loop it spills
+            raw = packed_load<64>(cv + min(r + 1, r_last) * cv_rs, N, rg * 256 + from);
             uint32_t ta_at = rr * 16, tb_at = lane;
             asm volatile("" : "+v"(ta_at), "+v"(tb_at));   // the twiddles stay in LDS: hoisted out of the loop they take sixty registers
             radix16_fwd_lds(w, tl.ta + ta_at, 1, m);
@@ -291,104 +301,152 @@ __global__ __launch_bounds__(128 * H, H == 4 ? 4 : 3) void rotate_finish_kernel(
         const BufferRsrc key = uniform_rsrc(rot.key[r], (uint64_t)ndig * 2 * M * N * sizeof(W));
         const uint32_t g = rot.galois[r];
 #pragma unroll 1
-        for (uint32_t tile = wave; tile < 16; tile += 2 * H) {
-            const uint32_t at = tile * 64 + lane, n = rg * 1024 + at, sn = galois_source_slot(n, g, LOGN);
+        for (uint32_t tile = wave; tile < 16; tile += TILES * WAVES) {
             struct Raw {
-                HalfRaw<H> x;
-                W k0, k1;
+                HalfRaw<H> x[TILES];
+                W k0[TILES], k1[TILES];
             };
+            uint32_t n[TILES], sn[TILES];
+#pragma unroll
+            for (int i = 0; i < TILES; ++i) {
+                n[i] = rg * 1024 + (tile + i * WAVES) * 64 + lane;
+                sn[i] = galois_source_slot(n[i], g, LOGN);
+            }
             const auto fetch = [&](uint32_t j) {
                 Raw q;
                 const uint32_t limb = (j * 2 * M + pos) * N * (uint32_t)sizeof(W);
-                q.x = half_load<H, PACKED>(src, j * E + pos, N, sn);
-                q.k0 = buffer_load<W>(key, n * (uint32_t)sizeof(W), limb);
-                q.k1 = buffer_load<W>(key, n * (uint32_t)sizeof(W), limb + M * N * (uint32_t)sizeof(W));
+#pragma unroll
+                for (int i = 0; i < TILES; ++i) {
+                    q.x[i] = half_load<H, PACKED>(src, j * E + pos, N, sn[i]);
+                    q.k0[i] = buffer_load<W>(key, n[i] * (uint32_t)sizeof(W), limb);
+                    q.k1[i] = buffer_load<W>(key, n[i] * (uint32_t)sizeof(W), limb + M * N * (uint32_t)sizeof(W));
+                }
                 return q;
             };
             Raw cur = fetch(0);
-            W add[H];
+            W add[TILES][H];
+            Sum t[TILES][2 * H];
 #pragma unroll
-            for (int b = 0; b < H; ++b) add[b] = c0[(uint64_t)(half * 4 + b) * c0_bs + (uint64_t)pos * N + sn];
-            Sum t[2 * H];
+            for (int i = 0; i < TILES; ++i) {
 #pragma unroll
-            for (int b = 0; b < 2 * H; ++b) t[b].start(0.0);
+                for (int b = 0; b < H; ++b)
+                    add[i][b] = static_cast<const W*>(a.c0)[(uint64_t)(half * 4 + b) * (2ull * ell * N) + (uint64_t)pos * N + sn[i]];
+#pragma unroll
+                for (int b = 0; b < 2 * H; ++b) t[i][b].start(0.0);
+            }
 #pragma unroll 1
             for (uint32_t j = 0; j < ndig; ++j) {
                 const Raw next = fetch(min(j + 1, ndig - 1));
-                const Factor k0 = Sum::word(cur.k0), k1 = Sum::word(cur.k1);
-                Factor x[H];
-                half_take<H, PACKED, INT>(src, cur.x, x);
 #pragma unroll
-                for (int b = 0; b < H; ++b) {
-                    t[2 * b].add(x[b], k0);
-                    t[2 * b + 1].add(x[b], k1);
+                for (int i = 0; i < TILES; ++i) {
+                    const Factor k0 = Sum::word(cur.k0[i]), k1 = Sum::word(cur.k1[i]);
+                    Factor x[H];
+                    half_take<H, PACKED, INT>(src, cur.x[i], x);
+#pragma unroll
+                    for (int b = 0; b < H; ++b) {
+                        t[i][2 * b].add(x[b], k0);
+                        t[i][2 * b + 1].add(x[b], k1);
+                    }
                 }
                 cur = next;
             }
-            const uint32_t p = at & 255u, in_row = (at >> 8) * kRowPitch + p + (p >> 4);
-            W* op = out + (uint64_t)(half * 4) * out_bs + (uint64_t)r * out_rs + (uint64_t)pos * N + n;
 #pragma unroll
-            for (int b = 0; b < 2 * H; ++b) {
-                double v = mulmod_lazy(t[b].result(m) - rows[b][in_row], mul, m);
-                if (b % 2 == 0) v = reduce_lazy(v + word_to_f64<W>(add[b / 2]), m);
-                op[(uint64_t)(b / 2) * out_bs + (b & 1) * ((uint64_t)ell * N)] = f64_to_word<W>(canon(v, m));
+            for (int i = 0; i < TILES; ++i) {
+                const uint32_t at = n[i] & 1023u, p = at & 255u, in_row = (at >> 8) * kRowPitch + p + (p >> 4);
+                W* op = static_cast<W*>(a.out) + (uint64_t)(half * 4) * a.out_bs + (uint64_t)r * (2ull * ell * N) + (uint64_t)pos * N + n[i];
+#pragma unroll
+                for (int b = 0; b < 2 * H; ++b) {
+                    double v = mulmod_lazy(t[i][b].result(m) - rows[b][in_row], mul, m);
+                    if (b % 2 == 0) v = reduce_lazy(v + word_to_f64<W>(add[i][b / 2]), m);
+                    op[(uint64_t)(b / 2) * a.out_bs + (b & 1) * ((uint64_t)ell * N)] = f64_to_word<W>(canon(v, m));
+                }
             }
         }
         __syncthreads();   // the converted limbs have been read
     }
 }
+// H: ciphertexts of the first half, HB: of the second (0: this launch has the half half0 alone).  Both halves in one launch, next to each other:
+// the second finds the keys in cache (six ciphertexts, two digits, four limbs, eight rotations 356 us in two launches, 320 in one).
+template <int LOG_R, int H, int HB, typename W, bool PACKED, bool INT>
+__global__ __launch_bounds__(64 * finish_waves(H), H >= 3 ? 4 : 3) void rotate_finish_kernel(RotateFinishArgs a, uint32_t parts_log, GatherBundle bundle,
+                                                                                              MacRotations rot) {
+    constexpr uint32_t LOGN = LOG_R + 8, HALVES = HB ? 2 : 1;
+    __shared__ double rows[2 * H][4 * kRowPitch];
+    __shared__ RowTwiddlesLds tl;
+    // gather_tile with 1024 slots, the halves of a tile next to each other
+    const uint32_t per_unit = 1u << (LOGN - 10 - parts_log), turn = blockIdx.x >> 3, local = turn / HALVES, half = turn % HALVES;
+    const uint32_t unit = (local / per_unit) * 8 + (blockIdx.x & 7);
+    if (unit >= (a.ell << parts_log)) return;  // uniform
+    uint32_t pos = unit >> parts_log, rg = (unit & ((1u << parts_log) - 1)) * per_unit + local % per_unit;
+    if (HB == 0 || HB == H || half == 0) {  // uniform
+        rotate_finish<LOG_R, H, finish_waves(H), W, PACKED, INT>(a, bundle, rot, pos, rg, HB == 0 ? a.half0 : HB == H ? half : 0, rows, tl);
+    } else if constexpr (HB != 0) {
+        asm volatile("" : "+s"(pos), "+s"(rg));   // nothing of this half is computed ahead of the branch
+        rotate_finish<LOG_R, HB, finish_waves(H), W, PACKED, INT>(a, bundle, rot, pos, rg, 1, rows, tl);
+    }
+}
 
-// Wavefronts with work are what decides, one per rotation, ciphertext, component and four rows: calls with the sums in memory -> meeting the
-// division, us: N = 2^16, 24 limbs, eight ciphertexts 16 rotations (98304) 4839 -> 4181, one rotation (24576) 591 -> 556, one ciphertext 8
-// rotations (24576) 464 -> 447, three ciphertexts one rotation (9216) 259 -> 273; 28 bits, eight 4219 -> 3517; N = 2^15, 20 limbs, two 8
-// rotations (20480) 334 -> 327, one (10240) 235 -> 246; N = 2^14, 11 limbs, eight 16 rotations (22528) 568 -> 546, four (11264) 319 -> 335;
-// N = 2^13, 10 limbs, eight (10240) 304 -> 311.
-bool rotations_meet_division(const ks_ctx* c, const Level& lv, uint32_t group, uint32_t n_rot) {
-    return lv.ell * (c->N / 1024) * 2 * group * n_rot > 16384;
+// Wavefronts with work decide, one per rotation, ciphertext, component and four rows; many digits and few ciphertexts make a rotation's
+// gathers, which the sums in memory run at more wavefronts a SIMD, the longer part.  Calls with the sums in memory -> meeting the division, us,
+// N = 2^16, 24 limbs, three digits, sixteen rotations: one ciphertext 863 -> 805 (24576 wavefronts), two 1330 -> 1187, three 1858 -> 1678,
+// four 2480 -> 2153, six 3688 -> 3289, seven 4264 -> 3686, eight 4818 -> 4159 (98304); 28 bits, one 644 -> 560, five 2625 -> 2326, eight 4143 -> 3459.
+//   Line: one ciphertext, N = 2^16, 12 limbs (9216) 342 -> 310, but six, N = 2^15, 7 limbs, four digits (16128) 245 -> 254.  Below N = 2^15, where
+// keys and slots stay in cache: three digits, 9 limbs, eight ciphertexts (18432) 250 -> 261, four, 14 limbs, seven (25088) 1218 -> 1123; five, 13
+// limbs, eight (29952) 743 -> 782.  Five ciphertexts are two launches, the second for one: two digits, 7 limbs (17920) 653 -> 668, 17 limbs (43520)
+// 1348 -> 1311; three, N = 2^15, 15 limbs (38400) 490 -> 506, 28 bits, N = 2^16, 9 limbs (23040) 573 -> 538; 28 bits, four, N = 2^15, 13 limbs (20800)
+// 287 -> 305.  Six ciphertexts, six digits, 17 limbs (52224) 1495 -> 1549.
+bool rotations_meet_division(const ks_ctx* c, const Level& lv, uint32_t group, uint32_t n_rot, bool words32) {
+    const uint32_t wavefronts = lv.ell * (c->N / 1024) * 2 * group * n_rot;
+    const uint32_t most = group == 5 ? (words32 ? 3 : 2) : group == 6 ? 5 : kMaxDigits;
+    if (c->logN < 15) return wavefronts > 22000 && lv.ndig <= std::min(most, 4u);
+    return wavefronts > (group == 5 ? 22000 : 16384) && lv.ndig <= most;
 }
 
 void launch_rotate_finish(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, const uint8_t* conv, void* out,
-                          uint64_t out_bs, uint64_t out_rs, const void* c0, uint64_t c0_bs, hipStream_t s, bool words32) {
+                          uint64_t out_bs, const void* c0, hipStream_t s, bool words32) {
     if (rot.n == 0) return;
     const uint32_t pl = std::min(lv.ell % 4 == 1 || lv.ell % 4 == 2 ? 2u : 1u, c->logN - 10);
     const double wk = words32 ? 4.0 : 8.0;
     ProfScope ps("rotate_finish", (src_bytes(src) * src.group * lv.ndig + (double)rot.n * (wk * 2.0 * lv.ndig + (10.0 + 3.0 * wk) * src.group)) * lv.ell * c->N, s);
     const uint32_t grid = ((lv.ell << pl) + 7) / 8 * 8 * ((c->N / 1024) >> pl);
     const bool ints = !src.hi && integer_sums(c);
-    // Rotations that a workgroup walks (the next one's converted limb is requested early, twiddles stay): all, unless that leaves too few
-    // workgroups.  Eight ciphertexts, N = 2^16, 24 limbs (3072), all of four 4181 us, two 4240, one 4409; N = 2^15, 20 limbs (1280) 928, 950,
-    // 975; but four at N = 2^15 (640) all 512, two 491; eight at N = 2^14, 11 limbs (352) all 588, two 546.
-    const uint32_t workgroups = grid * (src.group == 8 ? 2 : 1), shares = workgroups < 1280 ? (2560 + workgroups - 1) / workgroups : 1;
-    const uint32_t per_group = (rot.n + shares - 1) / shares;
-    const auto launch = [&](uint32_t h, uint32_t half0, uint32_t n_halves) {
-#define KS_LAUNCH_RF(LOGR, HV, WT, PK, IS)                                                                                                     \
-    hipLaunchKernelGGL((rotate_finish_kernel<LOGR, HV, WT, PK, IS>), dim3(grid * n_halves, (rot.n + per_group - 1) / per_group), dim3(128 * HV), 0, s, c->tw_fwd, c->d_mod, c->d_Pinv, \
-                       lv.ell, lv.E, c->M, lv.ndig, pl, src, rot, conv, static_cast<WT*>(out), out_bs, out_rs, static_cast<const WT*>(c0), c0_bs, \
-                       half0, n_halves, per_group)
-#define KS_LAUNCH_H(LOGR, HV)                                               \
-    {                                                                       \
-        if (ints) { KS_LAUNCH_RF(LOGR, HV, uint32_t, false, true); }        \
-        else if (words32) { KS_LAUNCH_RF(LOGR, HV, uint32_t, false, false); } \
-        else { KS_LAUNCH_RF(LOGR, HV, uint64_t, true, false); }             \
+    // Rotations that a workgroup walks: the next one's converted limb is requested early and the twiddles stay, which saves about a seventh of
+    // a rotation each time (eight ciphertexts, N = 2^16, 24 limbs, 3072 workgroups, all of four 4181 us, two 4240, one 4409), but the last
+    // round of workgroups, up to six, three or two a compute unit by their LDS, should be full (one ciphertext, 27 limbs, 1728, all of five
+    // rotations 424 us, one 368; four, N = 2^15, 20 limbs, 640, all of eight 512, two 491).
+    const uint32_t workgroups = grid * (src.group > 4 ? 2 : 1), resident = 256 * (src.group == 1 ? 6 : src.group == 2 ? 3 : 2);
+    uint32_t per_group = rot.n, least = ~0u;
+    for (uint32_t shares = 1; shares <= rot.n; ++shares) {
+        const uint32_t per = (rot.n + shares - 1) / shares, cost = (workgroups * ((rot.n + per - 1) / per) + resident - 1) / resident * (7 * per + 1);
+        if (cost < least) least = cost, per_group = per;
     }
-#define KS_LAUNCH(LOGR)                        \
-    switch (h) {                               \
-        case 1: KS_LAUNCH_H(LOGR, 1) break;    \
-        case 2: KS_LAUNCH_H(LOGR, 2) break;    \
-        case 3: KS_LAUNCH_H(LOGR, 3) break;    \
-        default: KS_LAUNCH_H(LOGR, 4) break;   \
+    RotateFinishArgs a{c->tw_fwd, c->d_mod, c->d_Pinv, lv.ell, lv.E, c->M, lv.ndig, conv, out, out_bs, c0, per_group, 0};
+#define KS_LAUNCH_RF(LOGR, HV, HBV, WT, PK, IS)                                                                                               \
+    hipLaunchKernelGGL((rotate_finish_kernel<LOGR, HV, HBV, WT, PK, IS>), dim3(grid * ((HBV) ? 2 : 1), (rot.n + per_group - 1) / per_group), \
+                       dim3(64 * finish_waves(HV)), 0, s, a, pl, src, rot)
+#define KS_LAUNCH_H(LOGR, HV, HBV)                                               \
+    {                                                                            \
+        if (ints) { KS_LAUNCH_RF(LOGR, HV, HBV, uint32_t, false, true); }        \
+        else if (words32) { KS_LAUNCH_RF(LOGR, HV, HBV, uint32_t, false, false); } \
+        else { KS_LAUNCH_RF(LOGR, HV, HBV, uint64_t, true, false); }             \
     }
-        KS_FOR_LOG_R(c->logN, KS_LAUNCH)
+#define KS_LAUNCH(LOGR)                           \
+    switch (src.group) {                          \
+        case 1: KS_LAUNCH_H(LOGR, 1, 0) break;    \
+        case 2: KS_LAUNCH_H(LOGR, 2, 0) break;    \
+        case 3: KS_LAUNCH_H(LOGR, 3, 0) break;    \
+        case 4: KS_LAUNCH_H(LOGR, 4, 0) break;    \
+        case 5: KS_LAUNCH_H(LOGR, 4, 0)           \
+            a.half0 = 1;                          \
+            KS_LAUNCH_H(LOGR, 1, 0) break;        \
+        case 6: KS_LAUNCH_H(LOGR, 4, 2) break;    \
+        case 7: KS_LAUNCH_H(LOGR, 4, 3) break;    \
+        default: KS_LAUNCH_H(LOGR, 4, 4) break;   \
+    }
+    KS_FOR_LOG_R(c->logN, KS_LAUNCH)
 #undef KS_LAUNCH
 #undef KS_LAUNCH_H
 #undef KS_LAUNCH_RF
-    };
-    if (src.group <= 4) launch(src.group, 0, 1);
-    else if (src.group == 8) launch(4, 0, 2);
-    else {
-        launch(4, 0, 1);
-        launch(src.group - 4, 1, 1);
-    }
 }
 
 }  // namespace ks

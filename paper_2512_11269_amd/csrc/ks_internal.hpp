@@ -316,10 +316,11 @@ void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& 
 
 // Whether a group of rotations of `group` ciphertexts forms the sums of the ciphertext limbs where the division ends (launch_rotate_finish)
 // instead of in memory.
-bool rotations_meet_division(const ks_ctx* c, const Level& lv, uint32_t group, uint32_t n_rot);
+bool rotations_meet_division(const ks_ctx* c, const Level& lv, uint32_t group, uint32_t n_rot, bool words32);
 // launch_inner_product on the ciphertext limbs and launch_rows_moddown_finish with rotations in one; conv: [r][b][2][ell] packed.
+// out: [b][r][2][ell] words, batch items out_bs apart; c0: [b][2][ell] words.
 void launch_rotate_finish(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, const uint8_t* conv, void* out,
-                          uint64_t out_bs, uint64_t out_rs, const void* c0, uint64_t c0_bs, hipStream_t s, bool words32);
+                          uint64_t out_bs, const void* c0, hipStream_t s, bool words32);
 
 // u[b][c][pos] (+)= sum_r pt_r[pos] * (sum_j sigma_r(src_j)[pos] key_r[j][c][pos] + [c = 0][pos < ell] P sigma_r(c0)[pos]);
 // src: c1 and its finished raised digits, and c0.  u: packed limbs in rows order.  accumulate: add to what u already holds.
