@@ -113,7 +113,7 @@ void key_sums_and_division(const ks_ctx* c, const Level& lv, const void* d, uint
                            uint8_t* conv, void* out, uint64_t out_bs, uint32_t bc, int tile, hipStream_t s, int d_word, bool words32,
                            const uint8_t* addend, bool merged) {
     const uint64_t limb = packed_limb_bytes(c->N), acc_ps = lv.E * limb, conv_ps = lv.ell * limb;
-    const bool meet = sums_meet_division(c, lv, bc);
+    const bool meet = sums_meet_division(c, lv, addend ? lv.ell - 1 : lv.ell, bc);
     launch_rows_inner_product(c, lv, d, d_ps, lifted, evk, acc, bc, s, d_word, words32, addend, meet);
     launch_inv_cols_packed(c, addend ? lv.drop_map : lv.special_map, acc, acc_ps, 2 * bc,
                            !addend ? c->d_moddown_scale : merged ? lv.d_merged_scale : lv.d_rescale_scale, s);

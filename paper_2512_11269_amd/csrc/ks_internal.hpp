@@ -226,8 +226,8 @@ struct FinishRotations {
 void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted,
                                const void* evk, uint8_t* acc, uint32_t batch, hipStream_t s, int d_word, bool words32,
                                const uint8_t* drop_addend, bool dropped_only);
-// Whether a call forms the sums of the limbs that stay where the division ends (launch_rows_key_finish) instead of in memory.
-bool sums_meet_division(const ks_ctx* c, const Level& lv, uint32_t batch);
+// Whether a call forms the sums of the n_stay limbs that stay where the division ends (launch_rows_key_finish) instead of in memory.
+bool sums_meet_division(const ks_ctx* c, const Level& lv, uint32_t n_stay, uint32_t batch);
 // Fused row half of the forward transform of the converted limbs (conv, [b][2][ell] packed) + (acc - conv) P^-1 (+ addend);
 // the ciphertext limbs of acc ([b][2][E] packed) are in rows order.
 // fs == nullptr: multiply by P^-1, ell output limbs; with `rotations` (their galois elements are read) acc and conv hold that many
