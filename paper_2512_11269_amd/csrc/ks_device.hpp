@@ -92,7 +92,8 @@ KS_HD double mac_reduce(double hi, double lo, Mod m) {
 
 // The same in two instructions where the low words of both factors are at hand as integers: hi is the sum of the products in doubles,
 // rounded at each step, and the low 32 bits of lo are the exact sum modulo 2^32, which tell by how much hi is off as long as that is less
-// than 2^31.  For |x|, |k| <= 2^36 and T products the sum stays below T 2^72 and the roundings below T^2 2^19: T <= kMacWideTerms.
+// than 2^31.  Requires |x| <= 2^36 (a residue, or a sum that mac_wide_reduce left: 0.51 p + 2^31, which may be more than p) and |k| <= p.  The sum
+// of T products then stays below T 2^36 p <= T 2^72 and the roundings below T^2 2^19: T <= kMacWideTerms.
 constexpr int kMacWideTerms = 60;
 KS_HD void mac_wide(double x, double k, uint32_t x_low, uint32_t k_low, double& hi, uint64_t& lo) {
     hi = __builtin_fma(x, k, hi);
@@ -101,7 +102,7 @@ KS_HD void mac_wide(double x, double k, uint32_t x_low, uint32_t k_low, double& 
 // The sum as a representative |r| <= 0.51 p + 2^31, and its low word.
 KS_HD double mac_wide_reduce(double hi, uint64_t lo, Mod m, uint32_t* low) {
     constexpr double kRound = 6755399441055744.0;   // 1.5 * 2^52: the low word of x + kRound is that of the integer x, |x| < 2^51
-    const double q = __builtin_rint(hi * m.pinv), r = __builtin_fma(-q, m.p, hi);   // |q| < 2^43; r is an integer below 2^36: exact
+    const double q = __builtin_rint(hi * m.pinv), r = __builtin_fma(-q, m.p, hi);   // |q| <= T 2^36 < 2^42; r is an integer below 2^36: exact
     const uint32_t q_low = (uint32_t)__builtin_bit_cast(uint64_t, q + kRound), r_low = (uint32_t)__builtin_bit_cast(uint64_t, r + kRound);
     const uint32_t p_low = (uint32_t)__builtin_bit_cast(uint64_t, m.p + kRound);
     const int32_t off = (int32_t)((uint32_t)lo - r_low - q_low * p_low);

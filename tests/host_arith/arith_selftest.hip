@@ -93,10 +93,11 @@ static void check_prime(uint64_t p) {
         i128 exact = start;
         const double most = 68719476736.0;   // 2^36
         for (int i = 0; i < kMacWideTerms; ++i) {
-            int64_t x = rep % 5 == 0 ? (int64_t)most - (int64_t)(rnd() & 0xFF) : rep % 5 == 1 ? rnd_signed(37) : (int64_t)(rnd() % p);
-            int64_t k = rep % 7 == 0 ? (int64_t)most - (int64_t)(rnd() & 0xFF) : (int64_t)(rnd() % p);
+            // the first factor is any of up to 2^36 (the reduced sum that it may be exceeds a small modulus), the second a residue
+            const int64_t reduced = (int64_t)(0.51 * (double)p) + 2147483648ll;
+            int64_t x = rep % 5 == 0 ? (int64_t)most - (int64_t)(rnd() & 0xFF) : rep % 5 == 1 ? rnd_signed(37) : rep % 5 == 2 ? (i & 1 ? -reduced : reduced) : (int64_t)(rnd() % p);
+            int64_t k = rep % 7 == 0 ? (int64_t)p - (int64_t)(rnd() & 0xFF) : (int64_t)(rnd() % p);
             if (rep % 5 == 1 && (x > (int64_t)most || x < -(int64_t)most)) x /= 2;
-            if (p < (1ull << 35)) { x %= (int64_t)p; k %= (int64_t)p; }
             mac_wide((double)x, (double)k, (uint32_t)x, (uint32_t)k, hi, lo);
             exact += (i128)x * k;
         }
