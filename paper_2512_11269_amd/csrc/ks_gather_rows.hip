@@ -197,7 +197,6 @@ void launch_rotate_mac_rows(const ks_ctx* c, const Level& lv, const GatherBundle
                        c->logN, dg, pl, src, sorted, pts, n_key, half0, u, u_stride, accumulate ? 1 : 0)
 #define KS_LAUNCH_R(HV, WKT, PK, IS)                                                              \
     if (rows.n != kMacRows) KS_LAUNCH_ROWS(HV, 2, WKT, PK, IS, 0);                                \
-    else if (HV == 4 && lv.ndig == 1) KS_LAUNCH_ROWS(HV, kMacRows, WKT, PK, IS, HV == 4 ? 1 : 0); \
     else if (HV == 4 && lv.ndig == 2) KS_LAUNCH_ROWS(HV, kMacRows, WKT, PK, IS, HV == 4 ? 2 : 0); \
     else if (HV == 4 && lv.ndig == 3) KS_LAUNCH_ROWS(HV, kMacRows, WKT, PK, IS, HV == 4 ? 3 : 0); \
     else KS_LAUNCH_ROWS(HV, kMacRows, WKT, PK, IS, 0)
