@@ -47,8 +47,10 @@ def scratch(tmp_path_factory):
 
 
 @pytest.mark.parametrize("kernel", [
-    r"rows_inner_product",
+    r"rows_inner_product",                     # its split form too
     r"inner_product_kernel",
+    r"rotate_mac_rows_kernel",
+    r"rotate_finish_kernel",
     r"bconv_mfma_ntt_colsILi\dELi1ELi9E",      # one target per lane half, nine sources a half
 ])
 def test_no_scratch_memory(scratch, kernel):
