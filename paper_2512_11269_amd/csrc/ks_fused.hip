@@ -335,6 +335,16 @@ bool sums_meet_division(const ks_ctx* c, const Level& lv, uint32_t n_stay, uint3
     return sums_grid(c, lv.E, batch) > (lv.ndig > 4 ? 5888 : 3584) && sums_grid(c, n_stay, batch) > 1280;
 }
 
+// A wavefront per digit and component where all workgroups are resident at once, three a compute unit (118 registers and 42 KB of LDS at
+// three digits) or two (four digits); fewer digits have less to take apart.  One key-switch, a wavefront for everything -> split: three
+// digits, N = 2^12, 256 workgroups 39.1 -> 33.1 us, N = 2^14 512 48.6 -> 44.1, 768 54.6 -> 53.5, but 1024 59.8 -> 64.8; N = 2^15 256
+// 49.0 -> 45.0, 800 59.7 -> 63.9; four, N = 2^13 384 45.3 -> 37.8; two, N = 2^12 48 33.6 -> 29.8, N = 2^13 192 38.0 -> 34.5, N = 2^15 576
+// 52.0 -> 53.3; one, N = 2^12 128 33.2 -> 31.4, N = 2^14 512 41.2 -> 42.1.
+static bool split_sums(const ks_ctx* c, const Level& lv, uint32_t batch) {
+    constexpr uint32_t most[kSplitDigits] = {256, 512, 768, 512};
+    return lv.ndig <= kSplitDigits && sums_grid(c, lv.E, batch) <= most[lv.ndig - 1];
+}
+
 template <int FINISH, typename WK>
 static void launch_rows_sums(const ks_ctx* c, const Level& lv, const void* d, uint64_t d_ps, const uint8_t* lifted, const void* evk,
                              const SumsOut<WK>& o, uint32_t pos0, uint32_t n_pos, uint32_t batch, hipStream_t s, int d_word) {
@@ -349,13 +359,7 @@ static void launch_rows_sums(const ks_ctx* c, const Level& lv, const void* d, ui
     // loads early (3 % faster there); the single-ciphertext launch is bound by
     // bandwidth and gains nothing from it
     const bool prefetch = grid > 2048, all = FINISH == 0 && n_pos == lv.E;
-    // A wavefront per digit and component where all workgroups are resident at once, three a compute unit (118 registers and 42 KB of LDS at
-    // three digits) or two (four digits); fewer digits have less to take apart.  One key-switch, a wavefront for everything -> split: three
-    // digits, N = 2^12, 256 workgroups 39.1 -> 33.1 us, N = 2^14 512 48.6 -> 44.1, 768 54.6 -> 53.5, but 1024 59.8 -> 64.8; N = 2^15 256
-    // 49.0 -> 45.0, 800 59.7 -> 63.9; four, N = 2^13 384 45.3 -> 37.8; two, N = 2^12 48 33.6 -> 29.8, N = 2^13 192 38.0 -> 34.5, N = 2^15 576
-    // 52.0 -> 53.3; one, N = 2^12 128 33.2 -> 31.4, N = 2^14 512 41.2 -> 42.1.
-    const uint32_t most[kSplitDigits] = {256, 512, 768, 512};
-    const bool split = all && lv.ndig <= kSplitDigits && grid <= most[lv.ndig - 1];
+    const bool split = all && split_sums(c, lv, batch);
 #define KS_LAUNCH_IP(LOGR, WDT, PF)                                                                                                            \
     hipLaunchKernelGGL((rows_inner_product<LOGR, WDT, WK, PF, FINISH>), dim3(grid), dim3(64), 0, s, c->tw_fwd, c->tw_inv, c->d_mod, dg, lv.ell, \
                        lv.E, c->L, c->M, static_cast<const WDT*>(d), d_ps, lifted, static_cast<const WK*>(evk), o, pos0, n_pos, batch,          \
@@ -390,7 +394,8 @@ void launch_rows_inner_product(const ks_ctx* c, const Level& lv, const void* d, 
                                const uint8_t* drop_addend, bool dropped_only) {
     if (batch == 0) return;
     const uint32_t pos0 = !dropped_only ? 0 : drop_addend ? lv.ell - 1 : lv.ell, n_pos = lv.E - pos0;
-    ProfScope ps("rows_inner_product", (sums_bytes(lv, n_pos, lv.ell - pos0, batch, d_word, words32) + 10.0 * batch * n_pos) * c->N, s);
+    ProfScope ps(!dropped_only && split_sums(c, lv, batch) ? "rows_inner_product_split" : "rows_inner_product",
+                 (sums_bytes(lv, n_pos, lv.ell - pos0, batch, d_word, words32) + 10.0 * batch * n_pos) * c->N, s);
     const auto launch = [&](auto word) {
         using WK = decltype(word);
         SumsOut<WK> o{};

@@ -72,17 +72,18 @@ def test_calls_that_sums_in_memory_serve_better(bits, logN, L, Kk, dnum, ell, ba
 
 
 @pytest.mark.parametrize("bits", [36, 28])
-@pytest.mark.parametrize("logN,L,Kk,dnum,ell,batch", [
-    (12, 4, 2, 2, 4, 1),
-    (12, 3, 3, 1, 3, 2),      # one digit
-    (12, 7, 2, 4, 7, 3),      # as many digits as the form takes, a short last one
-    (12, 7, 2, 4, 3, 14),
-    (13, 5, 2, 3, 2, 1),      # launches padded to eight workgroups
-    (14, 4, 4, 1, 1, 9),      # one limb
-    (15, 8, 4, 3, 8, 2),      # 768 workgroups
-    (15, 9, 4, 3, 9, 2),      # the form with a wavefront for everything
+@pytest.mark.parametrize("logN,L,Kk,dnum,ell,batch,split", [
+    (12, 4, 2, 2, 4, 1, True),
+    (12, 3, 3, 1, 3, 2, True),      # one digit
+    (12, 7, 2, 4, 7, 3, True),      # as many digits as the form takes, a short last one
+    (12, 7, 2, 4, 3, 14, True),
+    (13, 5, 2, 3, 2, 1, True),      # launches padded to eight workgroups
+    (14, 4, 4, 1, 1, 3, True),      # one limb, 240 workgroups
+    (15, 8, 4, 3, 8, 2, True),      # 768 workgroups
+    (15, 9, 4, 3, 9, 2, False),     # the form with a wavefront for everything
+    (14, 4, 4, 1, 1, 9, False),
 ])
-def test_a_wavefront_per_digit_and_component(bits, logN, L, Kk, dnum, ell, batch):
+def test_a_wavefront_per_digit_and_component(bits, logN, L, Kk, dnum, ell, batch, split):
     st = Setup(logN, L, Kk, dnum, bits=bits)
     wide = bits == 36
     word = (lambda t: t) if wide else (lambda t: t.to(torch.int32))
@@ -96,6 +97,10 @@ def test_a_wavefront_per_digit_and_component(bits, logN, L, Kk, dnum, ell, batch
             continue
         args, limbs, op = ((d,), ell, K.KS_OP_KEYSWITCH) if i == 0 else ((cta, ctb), ell - 1, K.KS_OP_HMULT_RELIN_RESCALE)
         out = torch.full((batch, 2, limbs, st.N), -1, dtype=evk.dtype, device="cuda")
+        K.ks_profile_enable(True)
         fn(st.ctx, *args, ell, evk, out, workspace(st.ctx, op, ell, batch))
+        ran = {r["kernel"] for r in K.ks_profile_report()}
+        K.ks_profile_enable(False)
+        assert ("rows_inner_product_split" in ran) == split and ("rows_inner_product" in ran) != split
         for b in sorted({0, batch - 1}):
             assert_equal(out[b:b + 1].long(), ref(*(host(a[b:b + 1].long()) for a in args), host(evk.long()), ell))
