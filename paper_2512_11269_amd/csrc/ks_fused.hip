@@ -327,12 +327,12 @@ static uint32_t sums_grid(const ks_ctx* c, uint32_t n_pos, uint32_t batch) { ret
 // 345.2 / 368.1; 28 bits 4096 133.7 / 135.8, 8192 214.5 / 226.6; 21 limbs multiplied 3712 179.1 / 177.8, 7424 288.6 / 294.5, 14848 536 / 563;
 // N = 2^15 2048 96.2 / 88.5, 4096 140.7 / 140.6, 8192 232.4 / 247.1; N = 2^14 2048 92.1 / 84.3, 3840 293.8 / 302.7.
 //   More than four digits make the traffic saved a smaller part and a wavefront, and so the last round, longer: five, 3840 152.2 / 147.2 and
-// 170.3 / 167.4, 6144 248.2 / 251.1; seven, 3680 204.7 / 198.2; eight, 5760 321.8 / 317.4, 9216 466.5 / 473.0.
+// 170.3 / 167.4, 6144 248.2 / 251.1; six, 4480 205.0 / 210.7; seven, 3680 204.7 / 198.2; eight, 9216 466.5 / 473.0.
 //   And a launch of the limbs that stay for itself: 512 wavefronts of 4096 83.9 / 80.0, 832 of 6656 120.1 / 116.6, 1280 of 4864 101.7 / 98.9 and of
 // 4160 91.6 / 92.4, 1536 of 5632 111.9 / 113.2, 1664 of 8320 141.2 / 142.9; multiplications 256 of 4096 91.9 / 87.6, 1152 of 4032 114.0 / 112.1,
 // 1536 of 6656 146.6 / 148.5.
 bool sums_meet_division(const ks_ctx* c, const Level& lv, uint32_t n_stay, uint32_t batch) {
-    return sums_grid(c, lv.E, batch) > (lv.ndig > 4 ? 5888 : 3584) && sums_grid(c, n_stay, batch) > 1280;
+    return sums_grid(c, lv.E, batch) > (lv.ndig > 4 ? 4096 : 3584) && sums_grid(c, n_stay, batch) > 1280;
 }
 
 // A wavefront per digit and component where all workgroups are resident at once, three a compute unit (118 registers and 42 KB of LDS at
