@@ -424,7 +424,7 @@ static int rotate_hoisted_impl(const ks_ctx* c, const void* ct, uint32_t ell, co
                 rot.key[r] = rot_keys[r0 + r];
                 rot.pt[r] = nullptr;
             }
-            const bool meet = rotations_meet_division(c, lv, bc, rot.n, words32);
+            const bool meet = rotations_meet_division(c, lv, bc, rot.n);
             launch_inner_product(c, lv, digits, rot, acc, s, words32, meet);
             const uint32_t polys = 2 * rot.n * bc;
             launch_inv_rows_packed(c, lv.special_map, acc, acc_ps, 1, acc, acc_ps, polys, s);

@@ -390,15 +390,15 @@ __global__ __launch_bounds__(64 * finish_waves(H), H >= 3 ? 4 : 3) void rotate_f
 // N = 2^16, 24 limbs, three digits, sixteen rotations: one ciphertext 863 -> 805 (24576 wavefronts), two 1330 -> 1187, three 1858 -> 1678,
 // four 2480 -> 2153, six 3688 -> 3289, seven 4264 -> 3686, eight 4818 -> 4159 (98304); 28 bits, one 644 -> 560, five 2625 -> 2326, eight 4143 -> 3459.
 //   Line: one ciphertext, N = 2^16, 12 limbs (9216) 342 -> 310, but six, N = 2^15, 7 limbs, four digits (16128) 245 -> 254.  Below N = 2^15, where
-// keys and slots stay in cache: three digits, 9 limbs, eight ciphertexts (18432) 250 -> 261, four, 14 limbs, seven (25088) 1218 -> 1123; five, 13
-// limbs, eight (29952) 743 -> 782.  Five ciphertexts are two launches, the second for one: two digits, 7 limbs (17920) 653 -> 668, 17 limbs (43520)
-// 1348 -> 1311; three, N = 2^15, 15 limbs (38400) 490 -> 506, 28 bits, N = 2^16, 9 limbs (23040) 573 -> 538; 28 bits, four, N = 2^15, 13 limbs (20800)
-// 287 -> 305.  Six ciphertexts, six digits, 17 limbs (52224) 1495 -> 1549.
-bool rotations_meet_division(const ks_ctx* c, const Level& lv, uint32_t group, uint32_t n_rot, bool words32) {
+// keys and slots stay in cache: two digits, 9 limbs, seven ciphertexts (18144) 928 -> 925, three, 9 limbs, eight (18432) 250 -> 261, four, 14 limbs,
+// seven (25088) 1218 -> 1123, five, 13 limbs, eight (29952) 743 -> 782.  Five ciphertexts are two launches, the second for one: two digits, 7 limbs
+// (17920) 653 -> 668, 8 limbs (20480) 816 -> 804, 17 limbs (43520) 1354 -> 1312; three, 21 limbs (53760) 880 -> 865; five, 13 limbs (33280)
+// 877 -> 976.  Six, six digits, 17 limbs (52224) 1495 -> 1549.
+bool rotations_meet_division(const ks_ctx* c, const Level& lv, uint32_t group, uint32_t n_rot) {
     const uint32_t wavefronts = lv.ell * (c->N / 1024) * 2 * group * n_rot;
-    const uint32_t most = group == 5 ? (words32 ? 3 : 2) : group == 6 ? 5 : kMaxDigits;
-    if (c->logN < 15) return wavefronts > 22000 && lv.ndig <= std::min(most, 4u);
-    return wavefronts > (group == 5 ? 22000 : 16384) && lv.ndig <= most;
+    const uint32_t most = group == 5 ? 3 : group == 6 ? 5 : kMaxDigits;
+    if (c->logN < 15) return wavefronts > (lv.ndig <= 2 ? 16384 : 22000) && lv.ndig <= std::min(most, 4u);
+    return wavefronts > (group == 5 ? 20000 : 16384) && lv.ndig <= most;
 }
 
 void launch_rotate_finish(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, const uint8_t* conv, void* out,
@@ -409,20 +409,24 @@ void launch_rotate_finish(const ks_ctx* c, const Level& lv, const GatherBundle& 
     ProfScope ps("rotate_finish", (src_bytes(src) * src.group * lv.ndig + (double)rot.n * (wk * 2.0 * lv.ndig + (10.0 + 3.0 * wk) * src.group)) * lv.ell * c->N, s);
     const uint32_t grid = ((lv.ell << pl) + 7) / 8 * 8 * ((c->N / 1024) >> pl);
     const bool ints = !src.hi && integer_sums(c);
-    // Rotations that a workgroup walks: the next one's converted limb is requested early and the twiddles stay, which saves about a seventh of
-    // a rotation each time (eight ciphertexts, N = 2^16, 24 limbs, 3072 workgroups, all of four 4181 us, two 4240, one 4409), but the last
-    // round of workgroups, up to six, three or two a compute unit by their LDS, should be full (one ciphertext, 27 limbs, 1728, all of five
-    // rotations 424 us, one 368; four, N = 2^15, 20 limbs, 640, all of eight 512, two 491).
-    const uint32_t workgroups = grid * (src.group > 4 ? 2 : 1), resident = 256 * (src.group == 1 ? 6 : src.group == 2 ? 3 : 2);
-    uint32_t per_group = rot.n, least = ~0u;
-    for (uint32_t shares = 1; shares <= rot.n; ++shares) {
-        const uint32_t per = (rot.n + shares - 1) / shares, cost = (workgroups * ((rot.n + per - 1) / per) + resident - 1) / resident * (7 * per + 1);
-        if (cost < least) least = cost, per_group = per;
-    }
-    RotateFinishArgs a{c->tw_fwd, c->d_mod, c->d_Pinv, lv.ell, lv.E, c->M, lv.ndig, conv, out, out_bs, c0, per_group, 0};
+    // Rotations that a workgroup walks: the next one's converted limb is requested early and the twiddles stay, which saves about a quarter of
+    // a rotation each time (eight ciphertexts, N = 2^16, 24 limbs, 3072 workgroups, all of four 4181 us, two 4240, one 4409), but a launch of
+    // few rounds of workgroups (up to six, three or two a compute unit by their LDS) ends in half a round on average.  All of them unless
+    // fewer are clearly ahead (one ciphertext, 27 limbs, 1728, all of five rotations 424 us, one 368; four, N = 2^15, 20 limbs, 640, all of
+    // eight 512, two 491; eight, N = 2^15, 26 limbs, 1664, all of five 885, one 919).
+    const auto rotations = [&](int h, uint32_t halves) {
+        const uint32_t workgroups = grid * halves, resident = 256 * (h == 1 ? 6 : h == 2 ? 3 : 2);
+        const auto cost = [&](uint32_t per) { return (2 * workgroups * ((rot.n + per - 1) / per) + resident) * (4 * per + 1); };
+        uint32_t best = rot.n;
+        for (uint32_t per = rot.n; per > 0; --per)
+            if (cost(per) < cost(best)) best = per;
+        return 40 * cost(best) < 39 * cost(rot.n) ? best : rot.n;
+    };
+    RotateFinishArgs a{c->tw_fwd, c->d_mod, c->d_Pinv, lv.ell, lv.E, c->M, lv.ndig, conv, out, out_bs, c0, 0, 0};
 #define KS_LAUNCH_RF(LOGR, HV, HBV, WT, PK, IS)                                                                                               \
-    hipLaunchKernelGGL((rotate_finish_kernel<LOGR, HV, HBV, WT, PK, IS>), dim3(grid * ((HBV) ? 2 : 1), (rot.n + per_group - 1) / per_group), \
-                       dim3(64 * finish_waves(HV)), 0, s, a, pl, src, rot)
+    a.per_group = rotations(HV, (HBV) ? 2 : 1);                                                                                               \
+    hipLaunchKernelGGL((rotate_finish_kernel<LOGR, HV, HBV, WT, PK, IS>),                                                                     \
+                       dim3(grid * ((HBV) ? 2 : 1), (rot.n + a.per_group - 1) / a.per_group), dim3(64 * finish_waves(HV)), 0, s, a, pl, src, rot)
 #define KS_LAUNCH_H(LOGR, HV, HBV)                                               \
     {                                                                            \
         if (ints) { KS_LAUNCH_RF(LOGR, HV, HBV, uint32_t, false, true); }        \

@@ -316,7 +316,7 @@ void launch_inner_product(const ks_ctx* c, const Level& lv, const GatherBundle& 
 
 // Whether a group of rotations of `group` ciphertexts forms the sums of the ciphertext limbs where the division ends (launch_rotate_finish)
 // instead of in memory.
-bool rotations_meet_division(const ks_ctx* c, const Level& lv, uint32_t group, uint32_t n_rot, bool words32);
+bool rotations_meet_division(const ks_ctx* c, const Level& lv, uint32_t group, uint32_t n_rot);
 // launch_inner_product on the ciphertext limbs and launch_rows_moddown_finish with rotations in one; conv: [r][b][2][ell] packed.
 // out: [b][r][2][ell] words, batch items out_bs apart; c0: [b][2][ell] words.
 void launch_rotate_finish(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, const uint8_t* conv, void* out,

@@ -57,9 +57,9 @@ def test_rotations_meet_the_division(bits, logN, L, Kk, dnum, ell, batch, n_rot)
     (14, 10, 2, 5, 10, 8, 8, {}),             # below N = 2^15: few wavefronts, many digits
     (14, 15, 3, 5, 14, 7, 8, {}),             # many digits
     (16, 6, 1, 6, 6, 6, 4, {}),               # six ciphertexts, six digits
-    (15, 9, 3, 3, 9, 5, 8, {28}),             # five ciphertexts, three digits: in 32-bit words only
-    (15, 12, 3, 4, 12, 5, 8, {}),
-    (15, 9, 5, 2, 9, 5, 8, {36, 28}),
+    (15, 12, 3, 4, 12, 5, 8, {}),             # five ciphertexts: more than three digits, or few wavefronts
+    (15, 7, 3, 3, 7, 5, 8, {}),
+    (15, 9, 3, 3, 9, 5, 8, {36, 28}),
 ])
 def test_forms_that_sums_in_memory_serve_better(bits, logN, L, Kk, dnum, ell, batch, n_rot, meets):
     st = Setup(logN, L, Kk, dnum, bits=bits)
