@@ -575,11 +575,14 @@ static int bsgs_impl(const ks_ctx* c, const void* ct, uint32_t ell, const uint32
         const int tile = conversion_tile(c, lv.modup, bc, lv.moddown, 2 * bc);
         const GatherBundle digits = mod_up_for_gather(c, lv, c0 + (uint64_t)ell * N * word, c0, ct_bs, coeff, lifted, region, bc, n1 * n2, tile, s, words32);
         // Inner sums of four or two giant steps at a time where the workspace holds them (a caller brings what ks_workspace_bytes asks for, 8
-        // bytes a residue) and the bundle has c0.  Groups of more than four are two halves there, which have to pay with shared keys for what
-        // they load twice: four rows, more than one digit (and one digit has little to share: up to two ciphertexts).  Eight baby and four giant steps, N = 2^16, us by rows at a time, 1 / 2 / 4: three
-        // digits, one ciphertext 1220 / 980 / 822, four 2423 / 2180 / 1908, five 2905 / 3025 / 2583, eight 4143 / 4347 / 3638; two digits, four
-        // 1884 / 1737 / 1563, eight 3253 / 3438 / 2967; one digit, one 595 / 537, four 1161 / 1152, eight 2023 / 2217; 28 bits, three digits,
-        // one 894 / 772 / 672, eight 3627 / 3443 / 3215.
+        // bytes a residue: four of three digits, three of two digits with a short second one and of one digit) and the bundle has c0.  Groups of
+        // more than four are two halves there, which have to pay with shared keys for what they load twice: four rows, more than one digit (and
+        // one digit has little to share: up to two ciphertexts).  Eight baby and four giant steps, N = 2^16, us by rows at a time, 1 / 2 / 4:
+        // three digits, one ciphertext 1220 / 980 / 822, four 2423 / 2180 / 1908, five 2905 / 3025 / 2583, eight 4143 / 4347 / 3638; two digits,
+        // four 1884 / 1737 / 1563, eight 3253 / 3438 / 2967; one digit, one 595 / 537, four 1161 / 1152, eight 2023 / 2217; 28 bits, three
+        // digits, one 894 / 772 / 672, eight 3627 / 3443 / 3215.  Few baby steps gain less but gain, one row -> rows at a time: three digits, 24
+        // limbs, two baby steps, four ciphertexts 2116 -> 2007, eight 6279 -> 6017, four baby steps, three 2340 -> 2100, eight 3481 -> 3230;
+        // two digits, two baby steps, one (8 limbs) 329 -> 312, four (11 limbs) 1159 -> 1151; N = 2^15, 9 limbs, one 284 -> 267, four 639 -> 625.
         const uint64_t have = ks_workspace_bytes(c, words32 ? KS_OP_BSGS_U32 : KS_OP_BSGS, ell, bc, 0), used = acc - static_cast<uint8_t*>(ws);
         const uint64_t fit = digits.c0 ? 1 : (have - used) / w.acc;
         const bool small = bc <= (lv.ndig > 1 ? 4 : 2), rows4 = fit >= kMacRows && (small || lv.ndig > 1), rows2 = fit >= 2 && small;

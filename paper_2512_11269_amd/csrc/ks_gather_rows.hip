@@ -11,11 +11,13 @@ namespace ks {
 // baby step, sum_j sigma_b(digit_j) key_{b,j} (+ P sigma_b(c0)), is the same for every giant step: a thread forms it once for a slot, reduces
 // it and multiplies it by the plaintext slots of `R` giant steps, whose sums it holds.  Keys and gathered slots, which are what
 // rotate_mac_kernel reads, are then read once for R sums instead of for each.
-//   Four rows of sixteen diagonals, eight ciphertexts, three digits, N = 2^16: 2280 us as four launches of rotate_mac_kernel, 1393; 28 bits
-// 1668 -> 768.  What bounds it: the traffic (keys 1.6 GB, plaintexts 1.1, slots), with half of the issue slots.
-//   The sums of R = 4 rows take the registers that eight ciphertexts would: a workgroup takes H, up to four, the two halves of a bundle of
-// more on the same slots in one workgroup, which so finds keys and plaintexts in cache the second time.  A half's slots of one (position, half of the
-// limb) and three digits are 1.8 MB at N = 2^16, which stay in that XCD's L2 from one rotation to the next.
+//   Four rows of sixteen diagonals, eight ciphertexts, three digits, N = 2^16: 2280 us as four launches of rotate_mac_kernel, 1338; 28 bits
+// 1668 -> 768.  What bounds it: traffic beyond the L2, 8.6 GB read and 0.7 written by the counters (6.9 TB/s), where keys (1.6 GB), plaintexts
+// (1.1), slots (0.3) and sums once would be 3.7; the vector units are 62 % busy.
+//   The sums of R = 4 rows take the registers that eight ciphertexts would: a wavefront takes up to four, and a bundle of more is two halves of its
+// ciphertexts.  Of eight, 256 threads of a workgroup take either half, on the same slots and keys; of five to seven they are two launches.
+// What a workgroup's rotations read again is the slots of one (position, part of the limb) for the ciphertexts of the launch: three digits of eight
+// 3.5 MB for half of a limb of N = 2^16, 1.8 MB for a quarter (launch_rotate_mac_rows chooses).
 //   Two wavefronts a SIMD do not hide a load of the next step (1684 us): with a set of operands for each digit, up to three, a load has the
 // time of a whole rotation.
 // ------------------------------------------------------------------------------------------------
@@ -162,9 +164,11 @@ __global__ __launch_bounds__(512, 2) void rotate_mac_rows_kernel(const Mod* __re
 void launch_rotate_mac_rows(const ks_ctx* c, const Level& lv, const GatherBundle& src, const MacRotations& rot, const MacRows& rows, uint8_t* u,
                             uint64_t u_stride, bool accumulate, hipStream_t s, bool key_words32) {
     if (rot.n == 0) return;
-    // quarters where the slots of a half are more than an XCD's L2 keeps beside the streams: eight ciphertexts, N = 2^16, three digits (3.5 MB)
-    // 1472 -> 1393 us; two digits (2.4 MB) 1350 -> 1336, 28 bits (3.1 MB) 768 -> 790, two ciphertexts 669 -> 677
-    const bool large = lv.ndig * src.group * src_bytes(src) * (c->N / 2) > 3.3 * (1 << 20);
+    // quarters of a limb where the slots of a half are more than an XCD's L2 of 4 MB keeps beside the streams, a crossover between measured sizes:
+    // eight ciphertexts, N = 2^16, halves -> quarters, three digits (3.5 MB) 1472 -> 1393 us; 28 bits (3.1 MB) 768 -> 790, two digits (2.4 MB) 1350 -> 1336,
+    // two ciphertexts 669 -> 677
+    constexpr double kKeptSlots = 3.3 * (1 << 20);
+    const bool large = lv.ndig * src.group * src_bytes(src) * (c->N / 2) > kKeptSlots;
     const uint32_t pl = std::max(gather_parts_log(lv.E), large ? 2u : 1u);
     DigitRanges dg;
     dg.ndig = lv.ndig;
@@ -228,11 +232,11 @@ void launch_rotate_mac_rows(const ks_ctx* c, const Level& lv, const GatherBundle
 // The end of a group of hoisted rotations on the ciphertext limbs: out[r][b][c] = (sum_j sigma_r(src_j) key_r[j][c] - NTT_rows(conv[r][b][c]))
 // P^-1 + [c = 0] sigma_r(c0[b]), canonical.  The sums meet the converted limbs in LDS and registers and never exist in memory, where they
 // were 10 bytes a residue written and read again.
-//   A workgroup owns four rows of one limb position for H ciphertexts (a half of a bundle of more than four, as above) and walks the
+//   A workgroup owns four rows of one limb position for H ciphertexts (a half of a bundle of more than four, as above) and walks
 // rotations of the group.  For each, a wavefront per ciphertext and component runs the row half of the converted limb's transform and
-// leaves it in LDS; then every wavefront takes 64 slots at a time, as the gathers do.  Two workgroups a compute unit (78 KB of LDS,
-// 128 registers), so that one gathers while the other transforms.  Four rotations of eight ciphertexts, three digits, 24 limbs, N = 2^16: 521 us,
-// where the two kernels took 243 + 418.
+// leaves it in LDS; then every wavefront takes blocks of 64 slots, as the gathers do.  Two workgroups a compute unit (78 KB of LDS,
+// 128 registers), so that one gathers while the other transforms.  Four rotations of eight ciphertexts, three digits, 24 limbs, N = 2^16: 494 us,
+// where the two kernels took 243 + 418.  What bounds it: traffic, 2.0 GB read beyond the L2 and 0.8 written (5.6 TB/s), and the vector units, 55 % busy.
 // ------------------------------------------------------------------------------------------------
 // Wavefronts of a workgroup that holds H ciphertexts: eight for three as well, of which two only gather (sixteen blocks of 64 slots are three
 // turns of six wavefronts but two of eight; 28 bits, five digits, 13 limbs, ten rotations of three 790 -> 581 us).
