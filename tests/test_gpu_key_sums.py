@@ -49,6 +49,7 @@ def test_sums_meet_the_division(bits, logN, L, Kk, dnum, ell, batch):
     (15, 14, 14, 1, 2, 8, (True, True, True)),        # few limbs stay
     (16, 8, 8, 1, 3, 8, (False, True, True)),         # a multiplication leaves one less
     (16, 10, 2, 5, 10, 5, (True, True, True)),        # many digits
+    (15, 18, 3, 6, 17, 6, (True, True, True)),
 ])
 def test_calls_that_sums_in_memory_serve_better(bits, logN, L, Kk, dnum, ell, batch, in_memory):
     st = Setup(logN, L, Kk, dnum, bits=bits)

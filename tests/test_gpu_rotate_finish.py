@@ -56,6 +56,9 @@ def test_rotations_meet_the_division(bits, logN, L, Kk, dnum, ell, batch, n_rot)
 @pytest.mark.parametrize("logN,L,Kk,dnum,ell,batch,n_rot,meets", [
     (14, 10, 2, 5, 10, 8, 8, {}),             # below N = 2^15: few wavefronts, many digits
     (14, 15, 3, 5, 14, 7, 8, {}),             # many digits
+    (14, 14, 5, 3, 13, 8, 10, {}),            # three digits, few wavefronts
+    (13, 24, 8, 3, 23, 8, 12, {}),
+    (16, 7, 7, 1, 7, 5, 6, {}),               # five ciphertexts, few wavefronts
     (16, 6, 1, 6, 6, 6, 4, {}),               # six ciphertexts, six digits
     (15, 12, 3, 4, 12, 5, 8, {}),             # five ciphertexts: more than three digits, or few wavefronts
     (15, 7, 3, 3, 7, 5, 8, {}),
